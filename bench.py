@@ -46,6 +46,7 @@ PRODUCT_INSTRUCTIONS = {"l1": 3.0, "cosine": 2.0, "jensen_shannon": 24.0, "jacca
 # column-slot strip: a 16-bit slot; hash: two buckets of 16 bytes; Bloom: two filter words;
 # bitmap with ranks: one 8-byte word), and per staged row for the value (4, or 1 for the set metrics).
 LOOKUP_BYTES = {1: 0, 2: 2, 3: 32, 4: 8, 5: 8}
+COLUMN_LISTS = 6          # "staging kind" of the column-list kernel, which stages nothing
 
 CALLS = {
     # name: (config, kind of call, metric, label)
@@ -257,6 +258,13 @@ def main():
         with open(traffic_file) as f:
             stored_traffic = json.load(f)
 
+    def shared_columns(config):
+        """Columns that a row of A and a row of B both store, over all pairs."""
+        A, B = host[config]
+        cols = int(A["n_cols"])
+        return float(np.dot(np.bincount(A["indices"], minlength=cols).astype(np.float64),
+                            np.bincount(B["indices"], minlength=cols).astype(np.float64)))
+
     def roofline(name):
         config, kind, metric, label = CALLS[name]
         m, n, nnz_b = shape[config]
@@ -270,8 +278,10 @@ def main():
         scan_ms = float(np.mean([sum(r["ms"] for r in recs if r["name"] == "scan") for recs in per_step]))
         all_ms = float(np.mean([sum(r["ms"] for r in recs) for recs in per_step]))
         alg = algorithmic_bytes(rec["a_rows"], nnz_b, n, kind != "knn")
-        visits = float(rec["a_rows"]) * nnz_b / (ms * 1e-3)
         R, staging = rec["rows_per_group"], rec["staging_kind"]
+        # the column lists (staging kind 6) visit only the columns two rows share; the launch covers all rows of A
+        lists = staging == COLUMN_LISTS
+        visits = (shared_columns(config) if lists else float(rec["a_rows"]) * nnz_b) / (ms * 1e-3)
         # vector ALU: the product's own instructions, nothing else counted
         per_visit = PRODUCT_INSTRUCTIONS[metric]
         alu = {"achieved": visits * per_visit, "peak": ALU_LANE_OPS, "unit": "lane-instructions/s",
@@ -279,6 +289,8 @@ def main():
         # LDS: what a lane must read per step (the column's map entry, the R staged values)
         value_bytes = 1.0 if metric == "jaccard" else 4.0
         lds_per_visit = LOOKUP_BYTES.get(staging, 0) / float(R) + value_bytes
+        if lists:                                         # a pair's sums, read and written
+            lds_per_visit = 32.0 if metric == "jensen_shannon" else 16.0
         lds = {"achieved": visits * lds_per_visit, "peak": LDS_PEAK_BYTES, "unit": "B/s",
                "frac": round(visits * lds_per_visit / LDS_PEAK_BYTES, 4), "lds_bytes_per_visit": round(lds_per_visit, 3)}
         bound = "alu" if alu["frac"] >= lds["frac"] else "lds"
@@ -288,7 +300,8 @@ def main():
             "bound": bound, "achieved": binding["achieved"], "peak": binding["peak"], "unit": binding["unit"],
             "frac": binding["frac"], "traffic": None, "traffic_source": None,
             "call": label,
-            "kernel": "spd_scan_kernel (%s, R=%d rows of A per workgroup, staging kind %d%s)"
+            "kernel": ("spd_match_kernel (%s, R=%d row of A per wavefront, staging kind %d%s)" if lists else
+                       "spd_scan_kernel (%s, R=%d rows of A per workgroup, staging kind %d%s)")
                       % (metric, R, staging, ", fused top-%d" % KNN_K if kind == "knn" else ""),
             "launch_ms": round(ms, 4), "visits_per_s": visits, "a_rows_in_launch": rec["a_rows"],
             "rows_per_group": R, "staging_kind": staging, "workgroups": rec["workgroups"], "block": rec["block"],
@@ -306,7 +319,7 @@ def main():
             "row_pairs_per_s_of_call": m * float(n) / (wall[name] / profile_steps),
         }
         key = ROOFLINE_KEYS.get(name, "roofline_" + name)
-        if key in stored_traffic:
+        if key in stored_traffic and not lists:           # (the stored counters are the staged scan's)
             st = stored_traffic[key]
             out["traffic"] = st["bytes_per_launch"]
             out["traffic_source"] = "stored, not measured in this run: " + st["source"]

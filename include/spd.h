@@ -153,7 +153,8 @@ spd_status spd_knn(spd_handle *handle, const spd_csr *Q, const spd_csr *Index, s
  * protocol fits the whole dataset, then queries it batch by batch).  spd_index_create does what
  * every spd_pairwise / spd_knn call does for B - reads its row pointers back, bins its rows by
  * degree, repacks it and sums its row norms for `metric` (`p`: SPD_MINKOWSKI only) - into device
- * memory the index owns (about 8 bytes per stored entry and 40 per row); spd_index_pairwise /
+ * memory the index owns (about 8 bytes per stored entry and 40 per row, and where the column lists serve
+ * the metric (option "match_lists") up to 20 bytes per stored entry more); spd_index_pairwise /
  * spd_index_knn then return exactly what spd_pairwise / spd_knn return for the same operands.
  * The index keeps the pointers of `Index`, not a copy: the three arrays must stay valid and
  * unchanged until spd_index_destroy.  The work is enqueued on the creating handle's stream; use
@@ -302,6 +303,12 @@ spd_status spd_csr_validate(spd_handle *handle, const spd_csr *M, int require_no
  *                 and are stored as whole 32-byte sectors.  1 (default): where it pays (A of 2^18 or
  *                 more stored entries and 1,024 or more rows, B's rows under 96 entries on average);
  *                 0: never; 2: wherever the distance allows it
+ *   "match_lists" the second way of computing a distance: B's rows are cut into tiles, each tile's entries
+ *                 listed by column, and a wavefront walks the lists of its row of A, so that only the
+ *                 columns two rows share cost anything (not for Chebyshev and the semirings that are not
+ *                 spelled as a distance).  1 (default): where it pays (sparse and long enough operands, and
+ *                 no knob of the staged scan turned); 0: never; 2: wherever the product has it and the
+ *                 scratch holds the lists.  The sums' order differs between the two ways.
  *   "check_plan"  1: verify every index the kernels will form from the plan before launching
  *   "profile"     1: bracket every kernel launch with HIP events (see spd_profile_read)
  * Unknown names or values out of range return SPD_ERR_UNSUPPORTED. */
@@ -310,9 +317,10 @@ spd_status spd_set_option(spd_handle *handle, const char *name, int64_t value);
 /* Kernel timings of the last spd_pairwise / spd_knn call made with option "profile" = 1.
  * One record per launch, in launch order.  Waits for the call's kernels to finish. */
 typedef struct {
-    char name[24];        /* "pack_b", "scan", "finalize", "knn_merge"                   */
+    char name[24];        /* "pack_b", "lists_b", "scan", "finalize", "knn_merge"        */
     int32_t rows_per_group; /* scan: R, the rows of A staged together; else 0            */
-    int32_t staging_kind; /* scan: 1 dense strip, 2 column-slot strip, 3 hash, 4 Bloom, 5 bitmap; else 0 */
+    int32_t staging_kind; /* scan: 1 dense strip, 2 column-slot strip, 3 hash, 4 Bloom, 5 bitmap,
+                                6 column lists ("match_lists"); else 0 */
     int32_t block;        /* scan: threads per workgroup; else 0                          */
     int32_t lds_bytes;    /* scan: dynamic LDS per workgroup; else 0                      */
     int64_t a_rows;       /* scan: rows (or slices of rows) of A the launch covers        */

@@ -17,6 +17,7 @@
 
 #include "../../include/spd.h"
 #include "spd_kernels.h"
+#include "spd_match.h"
 #include "spd_plan.h"
 
 using namespace spd;
@@ -131,6 +132,7 @@ struct spd_handle {
     bool no_byte_counters = false;   // option "byte_counters" 0: set metrics through the dot product
     int cuckoo_attempts = 3;     // option "cuckoo_attempts"
     int knn_seed = 1;            // option "knn_seed"
+    int match_lists = 1;         // option "match_lists": 0 never, 1 where it pays, 2 wherever the product allows it
     int swap_operands = 1;       // option "swap_operands": 0 never, 1 where it pays, 2 wherever the distance allows it
     int side_streams = 3;        // option "side_streams": how many internal streams the small launches may use beside the large one
     static constexpr int kSideStreams = 3;
@@ -157,6 +159,9 @@ struct spd_index {
     void *dev = nullptr;
     size_t dev_bytes = 0;
     BDevice bd;
+    MatchB match{};              // the column lists of the same rows, where the product has them (list == nullptr: none)
+    void *match_dev = nullptr;
+    int match_op = -1;
 };
 
 namespace {
@@ -487,10 +492,220 @@ bool operands_swap_pays(const spd_csr *A, const spd_csr *B) {
     return A->nnz >= ((int64_t)1 << 18) && A->n_rows >= 1024 && B->nnz <= 96 * B->n_rows;
 }
 
+// ------------------------------------------------------------------------------------
+// Column lists (spd_match.h): the second way of computing a distance
+// ------------------------------------------------------------------------------------
+// The product a call's kernels run.
+int product_of(const spd_handle *h, int metric, float p) {
+    int op = metric_info(metric).op;
+    // the set metrics count shared columns in byte lanes, or (option) as a dot product of 0/1 values
+    if (op == OP_CNT && (h->no_byte_counters || h->opt.force_kind == KIND_BLOOM)) op = OP_DOT;
+    // Minkowski: the small integer degrees share one set of kernels, every other degree has its own
+    if (op == OP_MINK && degree_class(metric == SPD_L2_UNEXPANDED ? 2.0f : p) == 0) op = OP_MINK_ANY;
+    return op;
+}
+
+struct MatchLayout { size_t list, ptr, norms, end; };
+MatchLayout layout_match(const MatchShape &s, int64_t n, int64_t nnz, Carver &cv) {
+    MatchLayout L;
+    L.list = cv.take((size_t)s.list_entries(nnz) * 8);
+    L.ptr = cv.take((size_t)s.n_tiles * (size_t)s.ptr_stride * 4);
+    L.norms = cv.take((size_t)n * 16);
+    L.end = cv.off;
+    return L;
+}
+MatchB match_b_at(const MatchShape &s, const MatchLayout &L, unsigned char *dev) {
+    return MatchB{reinterpret_cast<uint2 *>(dev + L.list), reinterpret_cast<uint32_t *>(dev + L.ptr),
+                  reinterpret_cast<double *>(dev + L.norms), s};
+}
+// Grid of the column-list kernel: groups of tiles times slices of A's rows, one workgroup for each
+// compute unit of the chip.  Where the lists are more than the L2 caches hold, the tiles are dealt to the
+// eight XCDs, and the workgroups of an XCD go through its tiles together; smaller lists are in every L2
+// anyway, and each tile is a group.  Rows of A that hold more than a third of a wavefront's share of
+// the entries are shared by the wavefronts of a workgroup.
+struct MatchGrid { int slices = 1, groups = 1, by_xcd = 0; int64_t shared_len = 0; };
+MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int64_t m, int64_t nnz_a, int64_t nnz_b, bool knn) {
+    MatchGrid g;
+    const int64_t cus = std::max(1, opt.n_cus), rows_slices = std::max<int64_t>(1, (m + s.waves - 1) / s.waves);
+    if (s.n_tiles >= 16 && nnz_b * 8 > kMatchL2Bytes) {
+        const int64_t per_xcd = std::max<int64_t>(1, cus / 8);
+        g.by_xcd = 1;
+        g.slices = (int)std::min(per_xcd, rows_slices);
+        g.groups = (int)std::min<int64_t>(s.n_tiles, per_xcd / g.slices * 8);
+    } else {
+        // (k-NN: as few groups as fill the chip, since every group's lists start empty)
+        g.groups = (int)std::min<int64_t>(s.n_tiles, knn ? (cus + rows_slices - 1) / rows_slices : cus);
+        g.slices = (int)std::max<int64_t>(1, std::min(rows_slices, cus / g.groups));
+    }
+    const int64_t tiles = (s.n_tiles + g.groups - 1) / g.groups;
+    const int64_t share = nnz_a * tiles / ((int64_t)g.slices * s.waves);
+    g.shared_len = std::max<int64_t>(256, share / 3);
+    return g;
+}
+struct MatchScratch { MatchLayout b; size_t rows, norms_a, tau, part, row_off, row_lists, end; };
+MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int64_t m, int64_t n, int64_t nnz_b, int knn_k, bool with_b) {
+    MatchScratch L{};
+    Carver cv;
+    if (with_b) L.b = layout_match(s, n, nnz_b, cv);
+    L.rows = cv.take((size_t)m * sizeof(MatchRow));
+    L.norms_a = cv.take((size_t)m * 16);
+    if (knn_k > 0) {
+        L.tau = cv.take((size_t)m * 8);
+        L.row_off = cv.take((size_t)m * 8);
+        L.row_lists = cv.take((size_t)m * 4);
+        L.part = cv.take((size_t)m * (size_t)g.groups * (size_t)knn_k * sizeof(KnnEntry));
+    }
+    L.end = cv.off;
+    return L;
+}
+// The knobs that pick the staged scan's paths: a caller that turns one wants that kernel.
+bool scan_knobs_untouched(const spd_handle *h) {
+    const PlanOptions d;
+    const PlanOptions &o = h->opt;
+    return o.force_kind == d.force_kind && o.max_rows == d.max_rows && o.split_len == d.split_len && o.window == d.window &&
+           o.chunks == d.chunks && o.chunk_scale == d.chunk_scale && o.waves_per_cu == d.waves_per_cu &&
+           o.bloom_long_rows == d.bloom_long_rows && o.sort_slack == d.sort_slack && o.partial_groups == d.partial_groups &&
+           o.lds_budget >= 64 * 1024 && !h->no_byte_counters && h->cuckoo_attempts == 3 && h->knn_seed == 1 &&
+           h->swap_operands == 1;
+}
+// The list bounds, a word per tile and column, are kept to the size of the lists, or to 64 MiB.
+bool match_bounds_fit(const MatchShape &s, int64_t nnz) {
+    return (int64_t)s.n_tiles * s.ptr_stride <= std::max<int64_t>(2 * nnz, 16 << 20);
+}
+bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring) {
+    if (h->match_lists == 0 || semiring || !match_serves(op)) return false;
+    if (A->n_rows <= 0 || B->n_rows <= 0 || A->n_cols <= 0 || A->n_cols >= ((int64_t)1 << 31) - 8) return false;
+        const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz);
+    // (list positions are 32-bit byte offsets)
+    if (s.n_tiles <= 0 || s.list_entries(B->nnz) >= ((int64_t)1 << 29)) return false;
+    if (h->match_lists == 2) return true;
+    if (!scan_knobs_untouched(h)) return false;
+    // The staged scan costs the same for every visit (a row of A, a stored entry of B); the lists cost a build,
+    // some 17 ps an entry of B, and then a third to a half of a visit per visit, less for the products that
+    // are dear (their visits that meet nothing pay in full in the staged scan).  Both sides measured, staged /
+    // lists in ms:  10,000 x 10,000 rows of 38, L1 0.65 / 0.41;  3,207 x 1,172 of them 0.15 / 0.16;  1,024 x
+    // 300,000 of 230, cosine 11.4 / 6.7;  97 x 113,185 of them 0.86 / 0.96;  4,096 x 65,536 of 1,820, L1 87 / 36,
+    // Jensen-Shannon 349 / 59;  126 x 2,556 of them, KL 0.55 / 0.83.  The set metrics stay with the staged
+    // scan, whose visit is a byte add (605 x 168,903 rows of 230, Dice 3.0 / 3.5).
+    if (op == OP_CNT) return false;
+    const bool light = op == OP_DOT || op == OP_L1 || op == OP_HAMM;
+    const double weight = light ? 1.0 : (op == OP_CANB ? 2.0 : (op == OP_KL ? 2.5 : (op == OP_JS ? 4.5 : 3.5)));
+    const double work = (double)A->n_rows * (double)B->nnz * weight;
+    const double mean = (double)B->nnz / (double)B->n_rows;
+    if (work < (mean <= 64.0 ? 1.5e8 : 3e9) || (double)A->n_rows * weight < 400.0) return false;
+    // where an eighth of B's cells are stored (half, for a dear product), most visits meet something
+    if (mean > (light ? 0.125 : 0.5) * (double)A->n_cols) return false;
+    return match_bounds_fit(s, B->nnz);
+}
+
+spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, int op, int knn_k, const OpParams &q,
+                     const MetricInfo &mi, const MatchShape &s, const MatchGrid &g, const MatchScratch &L, const int64_t *a_ip,
+                     const int64_t *b_ip, size_t ip_bytes, float *out, int64_t *out_idx, float *out_dist, const spd_index *index) {
+    const int64_t m = A->n_rows, n = B->n_rows;
+    if (!index)
+        for (int64_t j = 0; j < n; ++j)
+            if (b_ip[j] > b_ip[j + 1] || b_ip[0] != 0) return fail(h, SPD_ERR_BAD_CSR, "B: row pointers are not ascending from 0");
+    for (int64_t i = 0; i < m; ++i)
+        if (a_ip[i] > a_ip[i + 1] || a_ip[0] != 0) return fail(h, SPD_ERR_BAD_CSR, "A: row pointers are not ascending from 0");
+    spd_status st = ensure_workspace(h, L.end);
+    if (st != SPD_OK) return st;
+    unsigned char *ws = reinterpret_cast<unsigned char *>(h->ws);
+    hipError_t e;
+    MatchB mb = index ? index->match : match_b_at(s, L.b, ws);
+    if (!index) {
+        LaunchTimer lt(h, "lists_b", 0, 0, 0, 0, 0, s.n_tiles);
+        e = launch_match_build(h->stream, B->indptr, B->indices, B->values, n, B->nnz, (uint32_t)B->n_cols, mb,
+                               match_cell_bytes(op), metric, mi.transform, mi.norm, q.p);
+        if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
+        lt.done();
+    }
+    double *norms_a = reinterpret_cast<double *>(ws + L.norms_a);
+    e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, metric, mi.transform, mi.norm, q.p, q.k, norms_a);
+    if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
+    // A's rows, longest first (to within an eighth of their length): a counting sort into the pinned buffer
+    int64_t shared = 0;
+    st = ensure_pinned(h, align256(ip_bytes) + (size_t)m * sizeof(MatchRow));
+    if (st != SPD_OK) return st;
+    MatchRow *rows = reinterpret_cast<MatchRow *>(reinterpret_cast<unsigned char *>(h->pinned) + align256(ip_bytes));
+    {
+        auto bucket = [](int64_t len) -> uint32_t {
+            uint32_t v = (uint32_t)len, b;
+            if (v < 16) b = v;
+            else { const int lg = 31 - __builtin_clz(v); b = (uint32_t)(lg - 3) * 8u + ((v >> (lg - 3)) & 7u) + 8u; }
+            return 255u - std::min(b, 255u);
+        };
+        uint32_t at[257] = {0u};
+        for (int64_t i = 0; i < m; ++i) ++at[bucket(a_ip[i + 1] - a_ip[i]) + 1];
+        for (int b = 1; b <= 256; ++b) at[b] += at[b - 1];
+        for (int64_t i = 0; i < m; ++i) {
+            const int64_t len = a_ip[i + 1] - a_ip[i];
+            shared += len > g.shared_len ? 1 : 0;
+            rows[at[bucket(len)]++] = MatchRow{a_ip[i], (int32_t)len, (int32_t)i};
+        }
+    }
+    e = hipMemcpyAsync(ws + L.rows, rows, (size_t)m * sizeof(MatchRow), hipMemcpyHostToDevice, h->stream);
+    if (e != hipSuccess) return hip_fail(h, e, "upload of A's rows");
+    MatchArgs a;
+    a.a_indices = A->indices;
+    a.a_values = A->values;
+    a.rows = reinterpret_cast<const MatchRow *>(ws + L.rows);
+    a.m = (int32_t)m;
+    a.norms_a = norms_a;
+    a.b_indptr = B->indptr;
+    a.b_nnz = B->nnz;
+    a.b = mb;
+    a.n = n;
+    a.k = (uint32_t)A->n_cols;
+    a.transform = mi.transform;
+    a.q = q;
+    a.m_shared = (int32_t)shared;
+    a.slices = g.slices;
+    a.groups = g.groups;
+    a.by_xcd = g.by_xcd;
+    a.out = out;
+    a.knn_k = knn_k;
+    a.knn_part = reinterpret_cast<KnnEntry *>(ws + L.part);
+    a.knn_tau = reinterpret_cast<unsigned long long *>(ws + L.tau);
+    if (knn_k > 0) {
+        e = launch_match_knn_begin(h->stream, a.knn_tau, reinterpret_cast<int64_t *>(ws + L.row_off),
+                                   reinterpret_cast<int32_t *>(ws + L.row_lists), a.knn_part, m, g.groups, knn_k);
+        if (e != hipSuccess) return hip_fail(h, e, "k-NN start kernel");
+    }
+    {
+        LaunchTimer lt(h, "scan", 1, kMatchStagingKind, s.waves * kWave, s.lds_bytes, m, (int64_t)g.groups * g.slices);
+        e = launch_match(h->stream, op, a, s.lds_bytes);
+        if (e != hipSuccess) return hip_fail(h, e, "column-list scan kernel");
+        lt.done();
+    }
+    if (knn_k > 0) {
+        LaunchTimer lt(h, "knn_merge", 0, 0, 0, 0, m, (m + 3) / 4);
+        e = launch_knn_merge(h->stream, a.knn_part, reinterpret_cast<const int64_t *>(ws + L.row_off),
+                             reinterpret_cast<const int32_t *>(ws + L.row_lists), m, knn_k, metric == SPD_INNER_PRODUCT ? 1 : 0,
+                             out_idx, out_dist);
+        if (e != hipSuccess) return hip_fail(h, e, "k-NN merge kernel");
+        lt.done();
+    }
+    return SPD_OK;
+}
+
 spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, float p, const spd_semiring *semiring,
                int knn_k, float *out, int64_t *out_idx, float *out_dist, const spd_index *index = nullptr) {
     metric = effective_metric(metric, p);
-    const bool swapped = knn_k == 0 && !index && operands_may_swap(metric, semiring) &&
+    const int op = product_of(h, metric, p);
+    MatchShape match{};
+    MatchGrid match_g;
+    MatchScratch match_l{};
+    bool lists = match_wanted(h, A, B, op, semiring) && (!index || index->match.list);
+    if (lists) {
+        match = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz);
+        match_g = match_grid(h->opt, match, A->n_rows, A->nnz, B->nnz, knn_k > 0);
+        match_l = layout_match_call(match, match_g, A->n_rows, B->n_rows, B->nnz, knn_k, index == nullptr);
+        if (index && (index->match_op != op || std::memcmp(&index->match.shape, &match, sizeof match) != 0))
+            lists = false;              // (created under other options)
+        // (a caller's scratch that does not hold the lists still serves the staged scan)
+        if (h->ws_external && match_l.end > h->ws_bytes) lists = false;
+    }
+    const bool swapped = !lists && knn_k == 0 && !index && operands_may_swap(metric, semiring) &&
                          (h->swap_operands == 2 || (h->swap_operands == 1 && operands_swap_pays(A, B)));
     if (swapped) std::swap(A, B);           // from here on A is the staged operand, B the streamed one
     const int64_t m = A->n_rows, n = B->n_rows;
@@ -544,6 +759,9 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     }
     if (a_ip[m] != A->nnz || (!index && b_ip[n] != B->nnz)) return fail(h, SPD_ERR_BAD_CSR, "indptr[n_rows] != nnz");
     lap("indptr d2h");
+    if (lists)
+        return run_match(h, A, B, metric, op, knn_k, op_params(metric, p, A->n_cols, nullptr), metric_info(metric), match, match_g,
+                         match_l, a_ip, b_ip, ip_bytes, out, out_idx, out_dist, index);
 
     // ---- B first: plan it, upload its plan and start the repack, so that the device is
     //      busy while the host plans A (an index brings all of that with it) ---------------
@@ -552,11 +770,6 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     if (semiring) mi.transform = (int)semiring->transform;
     APlan &ap = h->plan_of_a;
     const BPlan &bp = index ? index->plan : h->plan_of_b;
-    // the set metrics count shared columns in byte lanes, or (option) as a dot product of 0/1 values
-    int op = mi.op;
-    if (op == OP_CNT && (h->no_byte_counters || h->opt.force_kind == KIND_BLOOM)) op = OP_DOT;
-    // Minkowski: the small integer degrees share one set of kernels, every other degree has its own
-    if (op == OP_MINK && degree_class(metric == SPD_L2_UNEXPANDED ? 2.0f : p) == 0) op = OP_MINK_ANY;
     // A is planned on the helper thread meanwhile; every way out of this function waits for it
     std::string why_a;
     {
@@ -949,6 +1162,14 @@ spd_status spd_workspace_bytes(const spd_handle *h, const spd_csr *A, const spd_
     // (a pairwise call may exchange the roles of its operands)
     if (k_neighbors == 0 && h->swap_operands != 0 && operands_may_swap((int)metric, nullptr))
         *bytes = std::max(*bytes, workspace_bound(h, B, A, (int)metric, 0));
+    // (a call may take the column lists; Minkowski of degree 1 runs as L1)
+    for (const int as_metric : {(int)metric, metric == SPD_MINKOWSKI ? (int)SPD_L1 : (int)metric}) {
+        const int op = product_of(h, as_metric, 2.0f);
+        if (!match_wanted(h, A, B, op, nullptr)) continue;
+        const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, B->n_cols, B->nnz);
+        const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, k_neighbors > 0);
+        *bytes = std::max(*bytes, layout_match_call(s, g, A->n_rows, B->n_rows, B->nnz, k_neighbors, true).end);
+    }
     return SPD_OK;
 }
 
@@ -1090,7 +1311,7 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
     const int64_t n = Index->n_rows;
     spd_index *ix = new (std::nothrow) spd_index();
     if (!ix) return fail(h, SPD_ERR_WORKSPACE, "out of host memory");
-    struct Guard { spd_index *p; ~Guard() { if (p) { if (p->dev) (void)hipFree(p->dev); delete p; } } } guard{ix};
+    struct Guard { spd_index *p; ~Guard() { if (p) { if (p->dev) (void)hipFree(p->dev); if (p->match_dev) (void)hipFree(p->match_dev); delete p; } } } guard{ix};
     ix->matrix = *Index;
     ix->metric = (int)metric;
     ix->p = p;
@@ -1133,6 +1354,21 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
                           reinterpret_cast<unsigned char *>(h->pinned), run_as, mi, q, (uint32_t)Index->n_cols, ix->bd);
         if (st != SPD_OK) return st;
     }
+    const int op = product_of(h, run_as, p);
+    if (n > 0 && h->match_lists != 0 && match_serves(op) && Index->n_cols < ((int64_t)1 << 31) - 8) {
+        const MatchShape s = match_shape(h->opt.lds_budget, op, n, Index->n_cols, Index->nnz);
+        if (s.n_tiles > 0 && s.list_entries(Index->nnz) < ((int64_t)1 << 29) && (h->match_lists == 2 || (op != OP_CNT && match_bounds_fit(s, Index->nnz)))) {
+            Carver lists;
+            const MatchLayout L = layout_match(s, n, Index->nnz, lists);
+            e = hipMalloc(&ix->match_dev, std::max<size_t>(lists.off, 256));
+            if (e != hipSuccess) { ix->match_dev = nullptr; return fail(h, SPD_ERR_WORKSPACE, std::string("hipMalloc of the index failed: ") + hipGetErrorString(e)); }
+            ix->match = match_b_at(s, L, reinterpret_cast<unsigned char *>(ix->match_dev));
+            ix->match_op = op;
+            e = launch_match_build(h->stream, Index->indptr, Index->indices, Index->values, n, Index->nnz, (uint32_t)Index->n_cols,
+                                   ix->match, match_cell_bytes(op), run_as, mi.transform, mi.norm, q.p);
+            if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
+        }
+    }
     guard.p = nullptr;
     *out = ix;
     return SPD_OK;
@@ -1145,6 +1381,7 @@ spd_status spd_index_destroy(spd_handle *h, spd_index *index) {
     hipError_t e = hipStreamSynchronize(h->stream);      // calls that read the index may still be running
     (void)e;
     if (index->dev) (void)hipFree(index->dev);
+    if (index->match_dev) (void)hipFree(index->match_dev);
     delete index;
     return SPD_OK;
 }
@@ -1248,6 +1485,9 @@ spd_status spd_set_option(spd_handle *h, const char *name, int64_t value) {
     } else if (s == "cuckoo_attempts") {
         if (value < 0 || value > 3) return fail(h, SPD_ERR_UNSUPPORTED, "cuckoo_attempts must lie in [0, 3]");
         h->cuckoo_attempts = (int)value;
+    } else if (s == "match_lists") {
+        if (value < 0 || value > 2) return fail(h, SPD_ERR_UNSUPPORTED, "match_lists must be 0, 1 or 2");
+        h->match_lists = (int)value;
     } else if (s == "swap_operands") {
         if (value < 0 || value > 2) return fail(h, SPD_ERR_UNSUPPORTED, "swap_operands must be 0, 1 or 2");
         h->swap_operands = (int)value;

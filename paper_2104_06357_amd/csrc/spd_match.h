@@ -1,0 +1,95 @@
+// Launch interface of the column-list kernels (spd_match*.hip).
+//
+// The staged scan (spd_scan_impl.h) visits every stored entry of B once per row of A and looks up
+// whether the row stores the entry's column; where the rows share few columns nearly all of these
+// visits meet nothing.  The column lists turn the loop round: the rows of B are cut into tiles, and
+// per tile the entries are listed by column (a transpose of the tile, made on the device in each
+// call).  A wavefront takes one row of A, walks the lists of that row's columns only, and adds
+// product(a, b) to one sum per row of the tile, which lie in its own strip of LDS.  Work is done for
+// the columns that two rows share and for nothing else; a column of A costs one step of 64 lanes per
+// 64 entries of its list.  A strip is private to its wavefront, and a row of B appears at most once in
+// a list, so no two lanes of a step meet in one sum and the sums are formed in the order of A's
+// columns: the results do not depend on the schedule.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "spd_kernels.h"
+
+namespace spd {
+
+// One row of A as the kernels take them, longest first.
+struct MatchRow { int64_t start; int32_t len, row; };
+
+// How B's rows are cut: into tiles of rows, and the columns of a tile into blocks (a power of two of them),
+// each with room for its entries and for `dense_per_block` columns kept as one value per row of the tile.
+struct MatchShape {
+    int32_t tile_rows, n_tiles, waves;      // n_tiles 0: the product or the sizes do not fit
+    int32_t block_shift, blocks, dense_per_block, dense_from;      // dense_from: entries that make a column dense
+    uint32_t stage;                         // entries of a block that pass through LDS together
+    int64_t ptr_stride, tile_extra;         // words of a tile's list bounds; entries beyond the tile's own
+    uint32_t lds_bytes, build_lds_bytes;
+    SPD_HD int64_t list_entries(int64_t nnz) const { return nnz + n_tiles * tile_extra + 64; }
+};
+MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, int64_t nnz);
+
+struct MatchB {
+    uint2 *list;            // {byte offset of the row's sums in a strip, value bits}, by tile, column block and column;
+                            // a dense column: tile_rows values, 0 where the row has none.  (A stored zero keeps
+                            // its place in a list and points to a spare cell behind the strip's last; 64 spare
+                            // entries at the end, which a step may read.)
+    uint32_t *ptr;          // n_tiles * ptr_stride: where a column's list begins, from the tile's first entry on, at
+                            // column + its block's number (a block has a word more for its last list's end);
+                            // kMatchDense is set where the column is dense
+    double *norms;          // n * 2, derived
+    MatchShape shape;
+};
+constexpr uint32_t kMatchDense = 0x80000000u;
+
+struct MatchArgs {
+    const int32_t *a_indices;
+    const float *a_values;
+    const MatchRow *rows;
+    int32_t m;
+    const double *norms_a;        // m * 2, derived, by row number
+    const int64_t *b_indptr;
+    int64_t b_nnz;
+    MatchB b;
+    int64_t n;
+    uint32_t k;
+    int32_t transform;
+    OpParams q;
+    int32_t m_shared;             // the first rows, which the wavefronts of a workgroup share
+    int32_t slices, groups;       // grid: groups of tiles (g, g + groups, ...) x slices of A's rows (s, s + slices, ...)
+    int32_t by_xcd;               // 1: the slices of a group share an XCD
+    float *out;                   // pairwise: m x n
+    int32_t knn_k;                // 0: pairwise
+    KnnEntry *knn_part;           // (row * groups + group) * knn_k
+    unsigned long long *knn_tau;  // per row: the tightest k-th (distance, index) key of any group
+};
+
+constexpr int64_t kMatchStaticLds = 256;        // upper bound of the kernel's static __shared__ use
+constexpr int kMatchStagingKind = 6;            // how spd_profile_read names this kernel's staging
+constexpr int64_t kMatchL2Bytes = 4 << 20;      // of one XCD
+// Wavefronts of a workgroup, of which a compute unit holds one: the strips share its LDS, and where a pair's
+// sums take 16 bytes or more, fewer and longer strips keep the lists longer than half a wavefront.
+constexpr int match_waves(size_t cell_bytes) { return cell_bytes >= 16 ? 12 : 16; }
+// Bytes a pair's sums take in a strip.
+int match_cell_bytes(int op);
+// The products the column lists serve.
+SPD_HD constexpr bool match_serves(int op) {
+    return op == OP_DOT || op == OP_L1 || op == OP_CANB || op == OP_HAMM || op == OP_KL || op == OP_JS || op == OP_CNT ||
+           op == OP_MINK || op == OP_MINK_ANY;
+}
+
+hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
+                              int metric, int transform, int norm, float p, double k, double *norms);
+hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int metric,
+                              int transform, int norm, float p);
+// k-NN: the rows' bounds, and where each row's candidate lists lie.
+hipError_t launch_match_knn_begin(hipStream_t st, unsigned long long *tau, int64_t *row_off, int32_t *row_lists, KnnEntry *part,
+                                  int64_t m, int lists, int k);
+hipError_t launch_match(hipStream_t st, int op, const MatchArgs &args, uint32_t lds_bytes);
+
+}  // namespace spd

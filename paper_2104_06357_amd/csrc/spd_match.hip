@@ -1,0 +1,394 @@
+// The column lists of B (a transpose per tile of rows), row norms, and the dispatch of the column-list
+// kernel to its products.
+#include <cmath>
+
+#include "spd_match_impl.h"
+
+namespace spd {
+
+// ------------------------------------------------------------------------------------
+// row norms (A): G lanes to the row, four entries of a lane in flight
+// ------------------------------------------------------------------------------------
+template <int G>
+__global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__restrict__ indptr, const float *__restrict__ values,
+                                                              int64_t n_rows, int64_t nnz, int metric, int transform, int norm,
+                                                              float p, double k, double *__restrict__ norms) {
+    const int sub = (int)threadIdx.x % G;
+    const int64_t row = (int64_t)blockIdx.x * (256 / G) + (int)threadIdx.x / G;
+    if (row >= n_rows) return;
+    const int64_t begin = clamp_i64(indptr[row], 0, nnz), end = clamp_i64(indptr[row + 1], begin, nnz);
+    double s0 = 0.0, s1 = 0.0;
+    for (int64_t e = begin + sub; e < end; e += 4 * G) {
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = e + u * G < end ? values[e + u * G] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (e + u * G < end) norm_accumulate(norm, transform_value(transform, v[u]), p, s0, s1);
+    }
+#pragma unroll
+    for (int d = std::min(G, kWave) / 2; d >= 1; d >>= 1) { s0 += __shfl_xor(s0, d); s1 += __shfl_xor(s1, d); }
+    if constexpr (G > kWave) {           // one row to the workgroup: its wavefronts' sums in a fixed order
+        __shared__ double s_sum[G / kWave][2];
+        if (sub % kWave == 0) { s_sum[sub / kWave][0] = s0; s_sum[sub / kWave][1] = s1; }
+        __syncthreads();
+        s0 = 0.0; s1 = 0.0;
+#pragma unroll
+        for (int w = 0; w < G / kWave; ++w) { s0 += s_sum[w][0]; s1 += s_sum[w][1]; }
+    }
+    if (sub == 0) {
+        double d0, d1;
+        norm_derive(metric, k, s0, s1, d0, d1);
+        norms[(size_t)row * 2] = d0;
+        norms[(size_t)row * 2 + 1] = d1;
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// B: a tile's entries by column.  A workgroup takes a run of column blocks of one tile.  The rows ascend in
+// their columns, so a row's entries of a block are a stretch of it, found where the block before ended:
+// every entry is read once to count and once (from the caches) to place.  Counters and the block's piece
+// of the list lie in LDS and the piece is written out whole.  (Counters in memory that eight XCDs share
+// run at 2.6e10 atomics a second: 300,000 rows of 230 entries took 7.1 ms; one workgroup per tile with
+// scattered 8-byte stores 1.74 ms.)  The order inside a list is whatever the wavefronts make it: no sum
+// depends on it, because a row of B appears in a list at most once.
+// ------------------------------------------------------------------------------------
+constexpr int kBuildThreads = 1024;
+constexpr uint32_t kBuildDense = 32;            // dense columns of a block at most
+
+template <int G>
+__global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
+                                                                        const float *__restrict__ values, int64_t n_rows, int64_t nnz,
+                                                                        uint32_t cols, MatchB b, uint32_t blocks_per_wg, uint32_t wgs, int cell_bytes,
+                                                                        int transform) {
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    __shared__ uint32_t s_wave[kBuildThreads / kWave];
+    __shared__ uint32_t s_dense[kBuildDense];
+    const MatchShape &shape = b.shape;
+    const uint32_t block_cols = 1u << shape.block_shift, blocks = (uint32_t)shape.blocks;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int nw = kBuildThreads / kWave, groups = kBuildThreads / G, kRows = 4;
+    const int sub = tid % G, group = tid / G, group_shift = lane / G * G;
+    constexpr uint64_t group_mask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull);
+    const int T = shape.tile_rows;
+    const int tile = (int)(blockIdx.x / wgs), part = (int)(blockIdx.x % wgs);
+    const int64_t j0 = (int64_t)tile * T;
+    const int rows = (int)min((int64_t)T, n_rows - j0);
+    const int64_t row_first = clamp_i64(indptr[j0], 0, nnz);             // of the rows' entries
+    const int64_t first = row_first + tile * shape.tile_extra;            // of the tile's lists
+    const int64_t list_end = shape.list_entries(nnz) - 64;
+    uint2 *s_stage = reinterpret_cast<uint2 *>(s_raw);                              // stage entries
+    uint32_t *s_count = reinterpret_cast<uint32_t *>(s_raw + (size_t)shape.stage * 8);   // block_cols counters, a multiple of 4
+    uint32_t *s_cur = s_count + block_cols;                                   // where a row's block begins ...
+    uint32_t *s_next = s_cur + T;                                                   // ... and the next one
+    uint32_t *s_end = s_next + T;
+    uint32_t *ptr = b.ptr + (size_t)tile * (size_t)shape.ptr_stride;
+    const uint32_t block_first = (uint32_t)part * blocks_per_wg;
+    const uint32_t block_last = min(block_first + blocks_per_wg, blocks);
+    if (block_first >= block_last) return;
+    uint32_t base = 0u;                               // entries of the columns before the block
+    {
+        const uint32_t c_first = block_first * block_cols;
+        uint32_t mine = 0u;
+        for (int r = tid; r < rows; r += kBuildThreads) {
+            const uint32_t begin = (uint32_t)(clamp_i64(indptr[j0 + r], row_first, nnz) - row_first);
+            const uint32_t end = max(begin, (uint32_t)(clamp_i64(indptr[j0 + r + 1], row_first, nnz) - row_first));
+            uint32_t lo = begin, hi = c_first == 0u ? begin : end;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if ((uint32_t)indices[row_first + mid] < c_first) lo = mid + 1; else hi = mid;
+            }
+            s_cur[r] = lo;
+            s_end[r] = end;
+            mine += lo - begin;
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) mine += (uint32_t)__shfl_xor((int)mine, d);
+        if (lane == 0) s_wave[wave] = mine;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < nw; ++w) base += s_wave[w];
+        base += block_first * (uint32_t)shape.dense_per_block * ((uint32_t)T / 2u);
+    }
+    for (uint32_t block = block_first; block < block_last; ++block) {
+        const uint32_t c0 = block * block_cols, range = min(block_cols, cols - c0);
+        for (uint32_t i = tid; i < block_cols; i += kBuildThreads) s_count[i] = 0u;
+        __syncthreads();
+        // count: G lanes to the row, four rows' first loads in flight together
+        for (int r0 = group; r0 < rows; r0 += kRows * groups) {
+            uint32_t pos[kRows], end[kRows], c[kRows];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const int r = r0 + u * groups;
+                pos[u] = r < rows ? s_cur[r] : 0u;
+                end[u] = r < rows ? s_end[r] : 0u;
+                c[u] = pos[u] + sub < end[u] ? (uint32_t)indices[row_first + pos[u] + sub] : 0xFFFFFFFFu;
+            }
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const int r = r0 + u * groups;
+                for (;;) {
+                    const bool in = c[u] - c0 < range;
+                    if (in) atomicAdd(&s_count[c[u] - c0], 1u);
+                    const uint32_t n = (uint32_t)__popcll((__ballot(in) >> group_shift) & group_mask);
+                    pos[u] += n;
+                    if (n < (uint32_t)G) break;
+                    c[u] = pos[u] + sub < end[u] ? (uint32_t)indices[row_first + pos[u] + sub] : 0xFFFFFFFFu;
+                }
+                if (r < rows && sub == 0) s_next[r] = pos[u];
+            }
+        }
+        __syncthreads();
+        // which columns are dense: the first of the block that reach the mark, in column order (so that the
+        // same columns are dense in every run)
+        auto scan4 = [&](uint32_t mine, uint32_t &carry) {          // exclusive over the workgroup, from `carry` on
+            uint32_t incl = mine;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const uint32_t up = (uint32_t)__shfl_up((int)incl, d);
+                if (lane >= d) incl += up;
+            }
+            if (lane == 63) s_wave[wave] = incl;
+            __syncthreads();
+            uint32_t at = carry + incl - mine;
+#pragma unroll
+            for (int w = 0; w < nw; ++w) { at += w < wave ? s_wave[w] : 0u; carry += s_wave[w]; }
+            __syncthreads();
+            return at;
+        };
+        const uint32_t half = (uint32_t)T / 2u, mark = (uint32_t)shape.dense_from;
+        uint32_t n_dense = 0u, total = 0u;
+        for (uint32_t i0 = 0; i0 < block_cols; i0 += 4 * kBuildThreads) {
+            const uint32_t i = i0 + 4u * (uint32_t)tid;
+            uint32_t v[4] = {0u, 0u, 0u, 0u};
+            if (i < block_cols)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) v[x] = s_count[i + x];
+            uint32_t mine = 0u;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) mine += v[x] >= mark ? 1u : 0u;
+            uint32_t rank = scan4(mine, n_dense), size[4], is_dense = 0u, sum = 0u;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const bool d = v[x] >= mark && rank < (uint32_t)shape.dense_per_block;
+                if (v[x] >= mark) ++rank;
+                is_dense |= d ? 1u << x : 0u;
+                size[x] = d ? half : v[x];
+                sum += size[x];
+            }
+            // counts -> starts: from the tile's first entry in memory, from the block's in LDS
+            uint32_t at = scan4(sum, total), r = rank - mine;
+            if (i < block_cols) {
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const uint32_t flag = (is_dense >> x) & 1u ? kMatchDense : 0u;
+                    if (flag) s_dense[r] = at;
+                    if (v[x] >= mark) ++r;
+                    s_count[i + x] = at | flag;
+                    if (i + x < range) ptr[c0 + block + i + x] = (base + at) | flag;
+                    at += size[x];
+                }
+            }
+        }
+        if (tid == 0) ptr[c0 + block + range] = base + total;
+        n_dense = min(n_dense, (uint32_t)shape.dense_per_block);
+        __syncthreads();
+        uint2 *__restrict__ list = b.list + first + base;          // the block's piece
+        const int64_t room = list_end - (first + base);            // (never reached while the row pointers hold)
+        for (uint32_t d = 0; d < n_dense; ++d)
+            for (uint32_t i = s_dense[d] + (uint32_t)tid; i < s_dense[d] + half; i += kBuildThreads) {
+                if (i < shape.stage) s_stage[i] = make_uint2(0u, 0u);
+                else if (i < room) list[i] = make_uint2(0u, 0u);
+            }
+        __threadfence_block();
+        __syncthreads();
+        // place
+        for (int r0 = group; r0 < rows; r0 += kRows * groups) {
+            uint32_t pos[kRows], end[kRows], c[kRows];
+            float v[kRows];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const int r = r0 + u * groups;
+                pos[u] = (r < rows ? s_cur[r] : 0u) + sub;
+                end[u] = r < rows ? s_next[r] : 0u;
+                c[u] = pos[u] < end[u] ? (uint32_t)indices[row_first + pos[u]] : 0xFFFFFFFFu;
+                v[u] = pos[u] < end[u] ? values[row_first + pos[u]] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const int r = r0 + u * groups;
+                while (pos[u] < end[u]) {
+                    const float t = transform_value(transform, v[u]);
+                    if (c[u] - c0 < range) {
+                        uint32_t *count = &s_count[c[u] - c0];
+                        uint32_t at = *count & ~kMatchDense;
+                        if (*count & kMatchDense) {
+                            at += (uint32_t)r >> 1;
+                            if (at < shape.stage) reinterpret_cast<float *>(&s_stage[at])[r & 1] = t;
+                            else if (at < room) reinterpret_cast<float *>(&list[at])[r & 1] = t;
+                        } else {
+                            // (a stored zero is absent: it goes to the spare cell behind the tile's)
+                            const uint2 entry = make_uint2((uint32_t)(t != 0.0f ? r : T) * (uint32_t)cell_bytes, __float_as_uint(t));
+                            at = atomicAdd(count, 1u);
+                            if (at < shape.stage) s_stage[at] = entry;
+                            else if (at < room) list[at] = entry;
+                        }
+                    }
+                    pos[u] += G;
+                    if (pos[u] < end[u]) { c[u] = (uint32_t)indices[row_first + pos[u]]; v[u] = values[row_first + pos[u]]; }
+                }
+            }
+        }
+        __syncthreads();
+        const uint32_t staged = min(total, shape.stage);
+        for (uint32_t i = tid; i < staged; i += kBuildThreads)
+            if (i < room) list[i] = s_stage[i];
+        if (tid == 0) s_wave[0] = 0u;
+        __syncthreads();
+        {
+            // the next block's piece begins behind this one's entries and its room for dense columns
+            uint32_t mine = 0u;
+            for (int r = tid; r < rows; r += kBuildThreads) { mine += s_next[r] - s_cur[r]; s_cur[r] = s_next[r]; }
+            if (mine) atomicAdd(&s_wave[0], mine);
+        }
+        __syncthreads();
+        base += s_wave[0] + (uint32_t)shape.dense_per_block * half;
+        __syncthreads();
+    }
+}
+
+hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
+                              int metric, int transform, int norm, float p, double k, double *norms) {
+    if (n_rows <= 0) return hipSuccess;
+    auto go = [&](auto g) {
+        constexpr int G = decltype(g)::value;
+        const int per = 256 / G;
+        hipLaunchKernelGGL((spd_match_norms_kernel<G>), dim3((unsigned)((n_rows + per - 1) / per)), dim3(256), 0, st, indptr, values,
+                           n_rows, nnz, metric, transform, norm, p, k, norms);
+    };
+    const int64_t mean = nnz / n_rows;
+    // (rows of power-law lengths: a wavefront alone takes 60 us over 24,000 entries)
+    if (mean >= 128) go(std::integral_constant<int, 256>{});
+    else if (mean >= 16) go(std::integral_constant<int, 64>{});
+    else go(std::integral_constant<int, 4>{});
+    return hipGetLastError();
+}
+
+MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, int64_t nnz) {
+    MatchShape s{};
+    const int cell = match_cell_bytes(op);
+    if (cell == 0 || n <= 0 || n_cols <= 0) return s;
+    s.waves = match_waves((size_t)cell);
+    const int64_t strip = (lds_budget - kMatchStaticLds) / s.waves;
+    int64_t most = (strip / cell - 1) / kWave * kWave;          // (a spare cell behind them)
+    if (most < kWave) return s;
+    // A list of 65 entries takes two steps of 64 like one of 128.  Where the mean list of the largest tile
+    // is between one and four steps long, a smaller tile's that just fills whole steps (with room for the
+    // spread of a random column's count) is cheaper: 65,536 x 26,000 rows of 7 %, lists of 54 instead of 81.
+    const double per_cell = (double)nnz / (double)n / (double)n_cols;
+    if (per_cell * (double)most < 256.0)
+        for (int q = 3; q >= 1; --q) {
+            const double root = std::sqrt(64.0 * q + 0.4225) - 0.65;             // mean + 1.3 sqrt(mean) = 64 q
+            const int64_t rows = (int64_t)(root * root / std::max(per_cell, 1e-12)) / kWave * kWave;
+            if (rows >= kWave && rows <= most) { most = rows; break; }
+        }
+    const int64_t tiles = (n + most - 1) / most;
+    if (tiles > (1 << 30)) return s;
+    s.tile_rows = (int32_t)(((n + tiles - 1) / tiles + kWave - 1) / kWave * kWave);
+    s.lds_bytes = (uint32_t)(s.waves * (s.tile_rows + 1) * cell);
+    // A block of columns: an eighth of the LDS for counters at most, and entries for four fifths, on the mean,
+    // of what the row positions leave for its piece of the lists (the rest of a fuller block goes straight to
+    // memory; narrower blocks read a row's lines more often).  Dense columns may take half as much again.
+    const int64_t usable = lds_budget - 1024, rows_bytes = 12 * (int64_t)s.tile_rows;
+    if (usable < rows_bytes + 4096) return s;
+    int shift = 2;
+    while ((4 << (shift + 1)) <= usable / 8 && (1 << shift) < n_cols) ++shift;
+    const int64_t room = usable - rows_bytes - ((int64_t)4 << shift);
+    s.stage = (uint32_t)(room / 8);
+    const double per_col = per_cell * (double)s.tile_rows;
+    while (shift > 2 && per_col * (double)(1 << shift) * 1.25 > (double)s.stage) --shift;
+    // a workgroup for every compute unit, where there are columns enough
+    const int64_t tiles_now = (n + s.tile_rows - 1) / s.tile_rows;
+    while (shift > 8 && tiles_now * ((n_cols + (1 << shift) - 1) >> shift) < 256) --shift;
+    s.block_shift = shift;
+    s.blocks = (int32_t)((n_cols + (1 << shift) - 1) >> shift);
+    s.dense_per_block = (int32_t)std::min<double>(kBuildDense, std::max(1.0, per_cell * (double)(1 << shift)));
+    // a step of 64 rows of a dense column costs this share of a list's step
+    const double cost = op == OP_DOT ? 0.3 : (op == OP_L1 || op == OP_CNT || op == OP_HAMM || op == OP_CANB ? 0.4 : 0.5);
+    s.dense_from = std::max(1, (int32_t)(cost * s.tile_rows));
+    s.ptr_stride = (n_cols + s.blocks + 3) / 4 * 4;
+    s.tile_extra = (int64_t)s.blocks * s.dense_per_block * (s.tile_rows / 2);
+    s.build_lds_bytes = s.stage * 8u + (4u << shift) + (uint32_t)rows_bytes;
+    s.n_tiles = (int32_t)((n + s.tile_rows - 1) / s.tile_rows);
+    return s;
+}
+
+hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int metric,
+                              int transform, int norm, float p) {
+    if (n_rows <= 0) return hipSuccess;
+    hipError_t e = launch_match_norms(st, indptr, values, n_rows, nnz, metric, transform, norm, p, (double)k, b.norms);
+    if (e != hipSuccess) return e;
+    // some 2,048 workgroups (a run of blocks looks its rows' first entries up once)
+    const MatchShape &s = b.shape;
+    const uint32_t per_wg = std::max(1u, (uint32_t)((uint64_t)s.blocks * (uint64_t)s.n_tiles / 2048u));
+    const uint32_t wgs = ((uint32_t)s.blocks + per_wg - 1u) / per_wg;
+    const double per_row = (double)nnz / (double)n_rows / (double)s.blocks;
+    auto go = [&](auto g) {
+        auto kern = spd_match_build_kernel<decltype(g)::value>;
+        static std::atomic<uint32_t> allowed[kMatchDevices];
+        hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes);
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL(kern, dim3((unsigned)s.n_tiles * wgs), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
+                           nnz, k, b, per_wg, wgs, cell_bytes, transform);
+        return hipGetLastError();
+    };
+    if (per_row >= 8.0) return go(std::integral_constant<int, 16>{});
+    return per_row >= 3.0 ? go(std::integral_constant<int, 8>{}) : go(std::integral_constant<int, 4>{});
+}
+
+__global__ void __launch_bounds__(256) spd_match_knn_begin_kernel(unsigned long long *tau, int64_t *row_off, int32_t *row_lists,
+                                                                  KnnEntry *part, int64_t m, int lists, int k) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, per = (int64_t)lists * k;
+    if (i < m) {
+        tau[i] = kKnnUnused;
+        row_off[i] = i * per;
+        row_lists[i] = lists;
+    }
+    for (int64_t e = i; e < m * per; e += (int64_t)gridDim.x * 256) part[e] = KnnEntry{__builtin_huge_valf(), 0x7fffffff};
+}
+hipError_t launch_match_knn_begin(hipStream_t st, unsigned long long *tau, int64_t *row_off, int32_t *row_lists, KnnEntry *part,
+                                  int64_t m, int lists, int k) {
+    if (m <= 0) return hipSuccess;
+    const int64_t blocks = std::max<int64_t>((m + 255) / 256, std::min<int64_t>(2048, (m * lists * k + 255) / 256));
+    hipLaunchKernelGGL(spd_match_knn_begin_kernel, dim3((unsigned)blocks), dim3(256), 0, st, tau, row_off, row_lists, part, m, lists, k);
+    return hipGetLastError();
+}
+
+hipError_t launch_match_a(hipStream_t st, int op, const MatchArgs &args, uint32_t lds_bytes);
+hipError_t launch_match_b(hipStream_t st, int op, const MatchArgs &args, uint32_t lds_bytes);
+
+int match_cell_bytes(int op) {
+    switch (op) {
+    case OP_DOT: return sizeof(MatchCell<OP_DOT>);
+    case OP_L1: return sizeof(MatchCell<OP_L1>);
+    case OP_CANB: return sizeof(MatchCell<OP_CANB>);
+    case OP_HAMM: return sizeof(MatchCell<OP_HAMM>);
+    case OP_CNT: return sizeof(MatchCell<OP_CNT>);
+    case OP_KL: return sizeof(MatchCell<OP_KL>);
+    case OP_JS: return sizeof(MatchCell<OP_JS>);
+    case OP_MINK: return sizeof(MatchCell<OP_MINK>);
+    case OP_MINK_ANY: return sizeof(MatchCell<OP_MINK_ANY>);
+    default: return 0;
+    }
+}
+
+hipError_t launch_match(hipStream_t st, int op, const MatchArgs &args, uint32_t lds_bytes) {
+    switch (op) {
+    case OP_DOT: case OP_L1: case OP_HAMM: case OP_CNT: case OP_CANB: return launch_match_a(st, op, args, lds_bytes);
+    case OP_KL: case OP_JS: case OP_MINK: case OP_MINK_ANY: return launch_match_b(st, op, args, lds_bytes);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace spd

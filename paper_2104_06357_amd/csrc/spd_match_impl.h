@@ -1,0 +1,505 @@
+// The column-list kernel (see spd_match.h).  Included by the spd_match_*.hip translation units.
+#pragma once
+#include "spd_match.h"
+#include "spd_scan_impl.h"
+
+namespace spd {
+
+__device__ __forceinline__ int64_t clamp_i64(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
+
+// What a strip holds per row of the tile.
+template <int OP> struct alignas(sizeof(typename Op<OP>::Acc) == 16 ? 16 : alignof(typename Op<OP>::Acc)) MatchCell {
+    typename Op<OP>::Acc acc;
+};
+
+// One column both rows store: the products of Op<OP>, without the tests for absent entries that the
+// staged scan needs (neither lists nor rows hold zeros).
+template <int OP> __device__ __forceinline__ void match_visit(typename Op<OP>::Acc &x, float a, float b, const OpParams &q) {
+    if constexpr (OP == OP_CNT) {
+        x.c += 1;
+    } else if constexpr (OP == OP_HAMM) {
+        x.c += (a != b) ? -1 : -2;
+    } else if constexpr (OP == OP_CANB) {
+        x.v += (double)fast_div(fabsf(a - b), fabsf(a) + fabsf(b)) - 2.0;
+    } else if constexpr (OP == OP_MINK) {
+        for_degree(q.p, [&](auto tag) { Op<OP>::template visit_as<decltype(tag)::value>(x, a, Op<OP>::prep(b, q), q); });
+    } else {
+        Op<OP>::visit(x, a, Op<OP>::prep(b, q), q);
+    }
+}
+
+// Lane l receives lane 63 - l's value.
+__device__ __forceinline__ uint64_t wave_reverse(uint64_t v) {
+    const int from = (63 - (int)__lane_id()) << 2;
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(v >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)v);
+}
+constexpr int kMatchLocks = 32;          // k-NN: locks of a workgroup, by row
+
+// One column of A against a row that may not store it (b = 0, which adds nothing).
+template <int OP> __device__ __forceinline__ void dense_visit(typename Op<OP>::Acc &x, float a, float b, const OpParams &q) {
+    if constexpr (OP == OP_MINK) {
+        for_degree(q.p, [&](auto tag) { Op<OP>::template visit_as<decltype(tag)::value>(x, a, Op<OP>::prep(b, q), q); });
+    } else {
+        Op<OP>::visit(x, a, Op<OP>::prep(b, q), q);
+    }
+}
+
+// Keeps what is computed into t and cell where the source has it (else it sinks into the branch that uses it).
+template <typename Acc> __device__ __forceinline__ void pin(Acc &t, uint32_t &cell) {
+    constexpr int N = (int)(sizeof(Acc) / 4);
+    uint32_t w[N];
+    __builtin_memcpy(w, &t, sizeof(Acc));
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(w[i]));
+    asm volatile("" : "+v"(cell));
+    __builtin_memcpy(&t, w, sizeof(Acc));
+}
+
+template <typename Acc> __device__ __forceinline__ void match_add(unsigned char *cell, const Acc &t) {
+    if constexpr (sizeof(Acc) == 8) {
+        double v;
+        __builtin_memcpy(&v, &t, 8);
+        __hip_atomic_fetch_add(reinterpret_cast<double *>(cell), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    } else {
+        int v;
+        __builtin_memcpy(&v, &t, 4);
+        __hip_atomic_fetch_add(reinterpret_cast<int *>(cell), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
+}
+
+constexpr int kMatchUnroll = 4;          // list steps whose loads are in flight together
+
+template <int OP, bool KNN>
+__global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) spd_match_kernel(const MatchArgs args) {
+    using O = Op<OP>;
+    using Cell = MatchCell<OP>;
+    constexpr int U = kMatchUnroll, D = sizeof(Cell) <= 8 ? 10 : 7, nw = match_waves(sizeof(Cell));
+    extern __shared__ __align__(16) unsigned char dyn[];
+    __shared__ int s_next;
+    __shared__ int s_lock[KNN ? kMatchLocks : 1];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
+    const int T = args.b.shape.tile_rows;
+    const uint32_t strip_bytes = (uint32_t)(T + 1) * (uint32_t)sizeof(Cell);
+    const uint32_t strip_at = (uint32_t)wave * strip_bytes;
+    unsigned char *strip = dyn + strip_at;
+    // Workgroups go round the eight XCDs in turn: with `by_xcd` the slices of one group of tiles, which
+    // read the same lists at about the same time, share an XCD and its L2.
+    int group, slice;
+    if (args.by_xcd) {
+        const int xcd = (int)blockIdx.x & 7, within = (int)blockIdx.x >> 3;
+        slice = within % args.slices;
+        group = within / args.slices * 8 + xcd;
+    } else {
+        slice = (int)blockIdx.x % args.slices;
+        group = (int)blockIdx.x / args.slices;
+    }
+    if (group >= args.b.shape.n_tiles) return;
+    const int my_tiles = (args.b.shape.n_tiles - group + args.groups - 1) / args.groups;      // group, group + groups, ...
+    Cell zero;
+    O::init(zero.acc);
+    for (int i = lane; i <= T; i += kWave) reinterpret_cast<Cell *>(strip)[i] = zero;
+    if (tid == 0) s_next = 0;
+    if (KNN && tid < kMatchLocks) s_lock[tid] = 0;
+    __syncthreads();
+
+    const uint32_t lane8 = (uint32_t)lane * 8u;
+    // 64 entries of a row of A, one per lane, on their way to the strip: first the entries, then the lists of
+    // their columns, then the lists' entries.  Each stage is loaded while the stage before it is at work on
+    // something else, so that the three round trips to memory are not waited for in turn.
+    struct Entries { uint32_t c; float v; };
+    struct Lists { uint32_t first, last; float a; };
+    auto load_entries = [&](int64_t start, int len, int e0) {
+        Entries x{0xFFFFFFFFu, 0.0f};
+        if (e0 + lane < len) {
+            x.c = (uint32_t)args.a_indices[start + e0 + lane];
+            x.v = args.a_values[start + e0 + lane];
+        }
+        return x;
+    };
+    auto load_lists = [&](int tile, const Entries &x) {
+        const uint32_t *__restrict__ ptr = args.b.ptr + (size_t)tile * (size_t)args.b.shape.ptr_stride;
+        Lists y{0u, 0u, 0.0f};
+        if (x.c < args.k) {
+            const uint32_t at = x.c + (x.c >> args.b.shape.block_shift);
+            y.first = ptr[at];
+            y.last = ptr[at + 1];
+        }
+        y.a = x.v;
+        return y;
+    };
+    // The batch's dense columns: one value per row of the tile, lane by lane, summed in registers; then the strip.
+    auto walk_dense = [&](const unsigned char *__restrict__ list, uint32_t first8, float a, uint64_t mask) {
+        const uint32_t lane4 = (uint32_t)lane * 4u;
+        for (int i0 = 0; i0 < T; i0 += D * kWave) {
+            typename O::Acc sum[D];
+            float cur[D], nxt[D];
+            uint32_t from_row[D];               // (past the tile's end its last rows are read again, and not added)
+#pragma unroll
+            for (int d = 0; d < D; ++d) from_row[d] = (uint32_t)min(i0 + d * kWave, T - kWave);
+#pragma unroll
+            for (int d = 0; d < D; ++d) O::init(sum[d]);
+            auto fetch = [&](float (&into)[D], int e) {
+                const unsigned char *col = list + (uint32_t)__builtin_amdgcn_readlane((int)first8, e);
+#pragma unroll
+                for (int d = 0; d < D; ++d) into[d] = *reinterpret_cast<const float *>((col + from_row[d] * 4u) + lane4);
+            };
+            auto visit = [&](const float (&from)[D], int e) {
+                const float ae = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), e));
+#pragma unroll
+                for (int d = 0; d < D; ++d) dense_visit<OP>(sum[d], ae, from[d], args.q);
+            };
+            uint64_t left = mask;
+            int e = (int)__builtin_ctzll(left);
+            fetch(cur, e);
+            for (;;) {
+                left &= left - 1;
+                const int e1 = left ? (int)__builtin_ctzll(left) : e;
+                fetch(nxt, e1);
+                __builtin_amdgcn_sched_barrier(0);
+                visit(cur, e);
+                if (!left) break;
+                left &= left - 1;
+                e = left ? (int)__builtin_ctzll(left) : e1;
+                fetch(cur, e);
+                __builtin_amdgcn_sched_barrier(0);
+                visit(nxt, e1);
+                if (!left) break;
+            }
+            Cell cell[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) cell[d] = reinterpret_cast<const Cell *>(strip)[from_row[d] + (uint32_t)lane];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                O::combine(cell[d].acc, sum[d]);
+                if (i0 + d * kWave < T) reinterpret_cast<Cell *>(strip)[from_row[d] + (uint32_t)lane] = cell[d];
+            }
+        }
+    };
+    auto walk_lists = [&](int tile, const Lists &y) {
+        const int64_t tile_first = clamp_i64(args.b_indptr[(int64_t)tile * T], 0, args.b_nnz) + tile * args.b.shape.tile_extra;
+        const unsigned char *__restrict__ list = reinterpret_cast<const unsigned char *>(args.b.list + tile_first);
+        const uint32_t list_n = (uint32_t)(args.b.shape.list_entries(args.b_nnz) - 64 - tile_first);     // (no access leaves the lists)
+        const float a = transform_value(args.transform, y.a);
+        uint32_t first = min(y.first & ~kMatchDense, list_n);
+        const bool dense = (y.first & kMatchDense) != 0u && a != 0.0f && first + (uint32_t)(T / 2) <= list_n;
+        const uint64_t dense_mask = __ballot(dense);
+        if (dense_mask != 0) walk_dense(list, first * 8u, a, dense_mask);
+        const uint32_t last = a != 0.0f && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
+        // steps of 64 list entries: how many there are up to and including this lane's list
+        const int steps = (int)((last - first + 63u) >> 6);
+        int incl = steps;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int up = __shfl_up(incl, d);
+            if (lane >= d) incl += up;
+        }
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (total == 0) return;
+        const uint32_t base8 = first * 8u - 512u * (uint32_t)(incl - steps);      // step t reads from byte base8 + 512 t on
+        const uint32_t last8 = last * 8u;
+        // A step is described by scalars alone (where it reads, how many bytes are its list's, A's value): the
+        // lanes' part of it is one load, the lookup and the sum.  A short list's load runs into the next one
+        // (or the 64 spare entries at the end of the lists), and those lanes add nothing.
+        uint2 cur[U], nxt[U];
+        float cur_a[U], nxt_a[U];
+        uint32_t cur_n[U], nxt_n[U];
+        auto fetch = [&](uint2 (&into)[U], float (&av)[U], uint32_t (&bytes)[U], int t0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int t = min(t0 + u, total - 1);
+                const int e = (int)__popcll(__ballot(incl <= t));
+                const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base8, e) + 512u * (uint32_t)t;
+                const uint32_t left = (uint32_t)__builtin_amdgcn_readlane((int)last8, e) - at;
+                av[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), e));
+                bytes[u] = t0 + u < total ? left : 0u;           // (steps past the last one read it again and add nothing)
+                into[u] = *reinterpret_cast<const uint2 *>((list + at) + lane8);
+            }
+        };
+        auto add = [&](const uint2 (&from)[U], const float (&av)[U], const uint32_t (&bytes)[U]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                // (where there is one sum, everything but the LDS add itself is done for all lanes: a branch around it costs more)
+                const bool ok = lane8 < bytes[u];
+                const float b = __uint_as_float(from[u].y);
+                if constexpr (sizeof(Cell) <= 8) {
+                    // one sum: an LDS add that nothing waits for
+                    typename O::Acc t;
+                    O::init(t);
+                    match_visit<OP>(t, av[u], b, args.q);
+                    uint32_t cell = strip_at + from[u].x;
+                    pin(t, cell);
+                    if (ok) match_add(dyn + cell, t);
+                } else {
+                    if (ok) {
+                        Cell *cell = reinterpret_cast<Cell *>(strip + from[u].x);
+                        Cell c = *cell;
+                        match_visit<OP>(c.acc, av[u], b, args.q);
+                        *cell = c;
+                    }
+                }
+            }
+        };
+        fetch(cur, cur_a, cur_n, 0);
+        for (int t = 0;;) {
+            fetch(nxt, nxt_a, nxt_n, t + U);
+            __builtin_amdgcn_sched_barrier(0);          // keep the loads ahead of the arithmetic
+            add(cur, cur_a, cur_n);
+            t += U;
+            if (t >= total) break;
+            fetch(cur, cur_a, cur_n, t + U);
+            __builtin_amdgcn_sched_barrier(0);
+            add(nxt, nxt_a, nxt_n);
+            t += U;
+            if (t >= total) break;
+        }
+        // (a lane reads later what other lanes of its wavefront wrote: LDS serves a wavefront in order, the
+        // fence keeps the compiler to that order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    // The tile's distances from the wavefront's strip, in row order: one coalesced store per 64 rows; the
+    // strip is clear again afterwards.
+    auto finish = [&](int tile, int row) {
+        const int64_t j0 = (int64_t)tile * T;
+        const int tile_n = (int)min((int64_t)T, args.n - j0);
+        const double na0 = args.norms_a[(size_t)row * 2], na1 = args.norms_a[(size_t)row * 2 + 1];
+        // f(row of the tile, its sums, its norms) for every row, four per lane at a time, a lane's last row first
+        auto for_strip = [&](auto &&f) {
+            constexpr int F = 4;
+            for (int i0 = (tile_n - 1) / (F * kWave) * (F * kWave) + lane; i0 >= 0; i0 -= F * kWave) {
+                double2 nb[F];
+                Cell c[F];
+#pragma unroll
+                for (int u = 0; u < F; ++u) {
+                    const int i = min(i0 + u * kWave, tile_n - 1);
+                    nb[u] = *reinterpret_cast<const double2 *>(args.b.norms + (size_t)(j0 + i) * 2);
+                    c[u] = reinterpret_cast<const Cell *>(strip)[i];
+                }
+#pragma unroll
+                for (int u = F - 1; u >= 0; --u)
+                    if (i0 + u * kWave < tile_n) f(i0 + u * kWave, c[u], nb[u].x, nb[u].y);
+            }
+        };
+        if constexpr (!KNN) {
+            for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
+                constexpr int MT = decltype(metric_tag)::value;
+                float *__restrict__ out = args.out + (size_t)row * (size_t)args.n + (size_t)j0;
+                for_strip([&](int i, const Cell &c, double nb0, double nb1) {
+                    __builtin_nontemporal_store(finish_as<MT>(args.q, O::v0(c.acc), O::v1(c.acc), O::v2(c.acc), na0, na1, nb0, nb1), out + i);
+                    reinterpret_cast<Cell *>(strip)[i] = zero;
+                });
+            });
+        } else {
+            // the distances replace the sums; every lane keeps the smallest of its rows' (the first of equal ones)
+            float least_d = __builtin_huge_valf();
+            int least_i = -1;
+            for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
+                constexpr int MT = decltype(metric_tag)::value;
+                for_strip([&](int i, const Cell &c, double nb0, double nb1) {
+                    float d = finish_as<MT>(args.q, O::v0(c.acc), O::v1(c.acc), O::v2(c.acc), na0, na1, nb0, nb1);
+                    if constexpr (MT == MT_INNER) d = 0.0f - d;
+                    *reinterpret_cast<float *>(reinterpret_cast<Cell *>(strip) + i) = d;
+                    const bool closer = d <= least_d;
+                    least_d = closer ? d : least_d;
+                    least_i = closer ? i : least_i;
+                });
+            });
+            const uint64_t least = least_i >= 0 ? knn_key(least_d, (int)(j0 + least_i)) : kKnnUnused;
+            const int k = args.knn_k;
+            auto kth_of = [&](uint64_t sorted, int at) {
+                return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(sorted >> 32), at) << 32) |
+                       (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)sorted, at);
+            };
+            // no key above `bound` can be among the k best: the tightest k-th key of any list of this row so
+            // far, and the k-th smallest of the lanes' smallest keys (k rows of this tile lie at or below it;
+            // at k = 32 of 1,216 rows some 44 do, and the sort below sees these alone)
+            uint64_t bound = (uint64_t)__atomic_load_n(&args.knn_tau[row], __ATOMIC_RELAXED);
+            uint64_t best = kKnnUnused;                           // the k best of this tile, ascending over the lanes
+            int waiting = (int)__popcll(__ballot(least < kKnnUnused && least <= bound));
+            if (waiting > 8) {
+                const uint64_t kth = kth_of(wave_sort_desc(least, lane), kWave - k);
+                bound = kth < bound ? kth : bound;
+            }
+            const bool any = waiting > 0;
+            uint64_t queue = kKnnUnused;
+            int queued = 0;
+            auto merge = [&]() {
+                const uint64_t c = wave_sort_desc(lane < queued ? queue : kKnnUnused, lane);
+                best = wave_merge_asc(c < best ? c : best, lane);
+                if (lane >= k) best = kKnnUnused;
+                const uint64_t now = kth_of(best, k - 1);
+                bound = now < bound ? now : bound;
+                queued = 0;
+            };
+            for (int i0 = 0; i0 < tile_n; i0 += kWave) {
+                const int i = i0 + lane;
+                Cell *cell = reinterpret_cast<Cell *>(strip) + i;
+                float d = __builtin_nanf("");                     // (passes no bound)
+                if (i < tile_n) {
+                    if (any) d = *reinterpret_cast<float *>(cell);
+                    *cell = zero;
+                }
+                if (__ballot(d <= float_from_order_key((uint32_t)(bound >> 32))) == 0) continue;
+                const uint64_t key = knn_key(d, (int)(j0 + i));
+                bool pass = d == d && key <= bound;
+                uint64_t mask = __ballot(pass);
+                if (mask == 0) continue;
+                if (queued + (int)__popcll(mask) > kWave) {
+                    merge();
+                    pass = pass && key <= bound;
+                    mask = __ballot(pass);
+                    if (mask == 0) continue;
+                }
+                // the passing lanes' keys go to the queue's next places (a permutation of the lanes)
+                const int n_pass = (int)__popcll(mask);
+                const int to = pass ? queued + (int)lane_rank_in(mask) : queued + n_pass + (int)lane_rank_in(~mask);
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_permute((to & 63) << 2, (int)(uint32_t)key);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_permute((to & 63) << 2, (int)(uint32_t)(key >> 32));
+                if (lane >= queued && lane < queued + n_pass) queue = ((uint64_t)hi << 32) | lo;
+                queued += n_pass;
+            }
+            if (any) {
+                merge();                                          // (what is queued joins the tile's list, if it has one)
+                // into the row's list of this group, under a lock (two wavefronts of the workgroup may be at one row, in
+                // different tiles); the holder waits for nothing
+                int *lock = &s_lock[row & (kMatchLocks - 1)];
+                int first_lane = lane;
+                asm volatile("" : "+v"(first_lane));              // (see the claim below)
+                if (first_lane == 0) {
+                    int spins = 0;
+                    while (atomicCAS(lock, 0, 1) != 0 && ++spins < kKnnLockSpins) __builtin_amdgcn_s_sleep(1);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                KnnEntry *part = args.knn_part + ((size_t)row * (size_t)args.groups + (size_t)group) * (size_t)k;
+                const uint64_t theirs = lane < k ? knn_key(part[lane].d, part[lane].j) : kKnnUnused;
+                const uint64_t turned = wave_reverse(theirs);
+                best = wave_merge_asc(turned < best ? turned : best, lane);
+                if (lane >= k) best = kKnnUnused;
+                if (lane < k) part[lane] = KnnEntry{float_from_order_key((uint32_t)(best >> 32)), (int)(uint32_t)best};
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                const uint64_t now = kth_of(best, k - 1);
+                if (first_lane == 0) {
+                    __atomic_store_n(lock, 0, __ATOMIC_RELAXED);
+                    if (now < kKnnUnused) atomicMin(&args.knn_tau[row], (unsigned long long)now);
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+
+    // ---- the longest rows: a sixteenth of the row to each wavefront, the strips summed in a fixed order --
+    // (a wavefront alone would hold its workgroup up long after the others are done)
+    for (int ti = 0; ti < my_tiles; ++ti) {
+        const int tile = group + ti * args.groups;
+        int owner = 0;
+        for (int at = slice; at < args.m_shared; at += args.slices) {
+            const MatchRow rw = args.rows[at];
+            const int row = wave_uniform(rw.row), len = wave_uniform(rw.len);
+            const int begin = (int)((int64_t)len * wave / nw), end = (int)((int64_t)len * (wave + 1) / nw);
+            Entries x = load_entries(rw.start + begin, end - begin, 0);
+            for (int e0 = 0; e0 < end - begin; e0 += kWave) {
+                const Lists y = load_lists(tile, x);
+                x = load_entries(rw.start + begin, end - begin, e0 + kWave);
+                walk_lists(tile, y);
+            }
+            __syncthreads();
+            for (int i = tid; i < T; i += nw * kWave) {
+                Cell sum = reinterpret_cast<Cell *>(dyn)[i];
+                reinterpret_cast<Cell *>(dyn)[i] = zero;
+#pragma unroll
+                for (int w = 1; w < nw; ++w) {
+                    Cell *cell = reinterpret_cast<Cell *>(dyn + (size_t)w * strip_bytes) + i;
+                    O::combine(sum.acc, cell->acc);
+                    *cell = zero;
+                }
+                reinterpret_cast<Cell *>(dyn + (size_t)owner * strip_bytes)[i] = sum;
+            }
+            __syncthreads();
+            if (wave == owner) finish(tile, row);
+            owner = owner + 1 < nw ? owner + 1 : 0;
+        }
+    }
+
+    // ---- the other rows: one wavefront each, no waiting for one another ------------------------------
+    const int rows_here = args.m - args.m_shared > slice ? (args.m - args.m_shared - slice + args.slices - 1) / args.slices : 0;
+    if (rows_here == 0) return;
+    // A wavefront takes (tile, row) after (tile, row) and goes through their batches of 64 entries as one
+    // stream: while the lists of one batch are walked, the list bounds of the next one and the entries of
+    // the one after that are on their way.
+    struct Place { int tile, row, len, e0; int64_t start; };        // e0: of the batch; row < 0: there is none
+    auto claim = [&]() {
+        // (the lane number is hidden from the compiler here: were `lane == 0` also to close the loop's body,
+        // it would thread the two tests together and let the other lanes round the loop ahead of lane 0)
+        int at = 0, claimer = lane;
+        asm volatile("" : "+v"(claimer));
+        if (claimer == 0) at = atomicAdd(&s_next, 1);
+        at = wave_uniform(at);
+        const int ti = at / rows_here;
+        Place p{0, -1, 0, 0, 0};
+        if (ti < my_tiles) {
+            const MatchRow rw = args.rows[args.m_shared + slice + (at - ti * rows_here) * args.slices];
+            p.tile = group + ti * args.groups;
+            p.row = wave_uniform(rw.row);
+            p.len = wave_uniform(rw.len);
+            p.start = rw.start;
+        }
+        return p;
+    };
+    Place ahead = claim();                       // where the stream goes on once the row below is through
+    auto advance = [&](const Place &p) {         // the batch after p
+        Place q = p;
+        q.e0 += kWave;
+        if (q.row >= 0 && q.e0 >= q.len) { q = ahead; ahead = claim(); }
+        return q;
+    };
+    Place p0 = ahead;
+    ahead = claim();
+    Entries x = load_entries(p0.start, p0.len, 0);
+    Place p1 = advance(p0);
+    Lists y = load_lists(p0.tile, x);
+    x = load_entries(p1.start, p1.len, p1.e0);
+    while (p0.row >= 0) {
+        const Place p2 = advance(p1);
+        const Lists y1 = load_lists(p1.tile, x);
+        x = load_entries(p2.start, p2.len, p2.e0);
+        walk_lists(p0.tile, y);
+        if (p0.e0 + kWave >= p0.len) finish(p0.tile, p0.row);
+        p0 = p1;
+        p1 = p2;
+        y = y1;
+    }
+}
+
+// Raises a kernel's LDS limit, once per device (`allowed`: the instance's own).
+constexpr int kMatchDevices = 64;
+template <typename Kernel> static hipError_t allow_lds(Kernel kern, std::atomic<uint32_t> (&allowed)[kMatchDevices], uint32_t bytes) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const bool known = dev >= 0 && dev < kMatchDevices;
+    if (known && allowed[dev].load(std::memory_order_acquire) >= bytes) return hipSuccess;
+    // to the most any launch may ask for, so that no two launches set it against each other
+    const uint32_t want = std::max<uint32_t>(bytes, 160u * 1024u - (uint32_t)kMatchStaticLds);
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)want);
+    if (e == hipSuccess) {
+        if (known) allowed[dev].store(want, std::memory_order_release);
+        return e;
+    }
+    // a device with less LDS: ask for what this launch needs
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+template <int OP, bool KNN> static hipError_t launch_match_op(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
+    auto kern = spd_match_kernel<OP, KNN>;
+    static std::atomic<uint32_t> allowed[kMatchDevices];
+    hipError_t e = allow_lds(kern, allowed, lds_bytes);
+    if (e != hipSuccess) return e;
+    const int64_t groups = args.by_xcd ? (args.groups + 7) / 8 * 8 : args.groups;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(groups * args.slices)), dim3((unsigned)(match_waves(sizeof(MatchCell<OP>)) * kWave)), lds_bytes, st, args);
+    return hipGetLastError();
+}
+template <int OP> static hipError_t launch_match_either(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
+    return args.knn_k > 0 ? launch_match_op<OP, true>(st, args, lds_bytes) : launch_match_op<OP, false>(st, args, lds_bytes);
+}
+
+}  // namespace spd

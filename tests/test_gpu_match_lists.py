@@ -1,0 +1,144 @@
+"""The column lists (option "match_lists"): B transposed per tile of rows, a wavefront per row of A.
+Parity with the CPU oracle through the C-ABI at the sizes where tiles, lists and batches end (needs an
+MI355X; run with -m gpu)."""
+import numpy as np
+import pytest
+
+import oracle
+from gen import synth
+from test_gpu_parity import _p_of
+from util import ALL_METRICS, ORACLE_NAME, assert_distances_close, assert_knn_matches
+
+pytestmark = pytest.mark.gpu
+
+SERVED = [m for m in ALL_METRICS if m != "chebyshev"]
+
+
+@pytest.fixture(scope="module")
+def spd():
+    import paper_2104_06357_amd as lib
+    return lib
+
+
+def _np(t):
+    import torch
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+def _matrix(rng, rows, cols, lengths):
+    """Rows of the given lengths (in turn) with columns that every row, few rows or one row stores, a stored zero
+    in some, an empty row first."""
+    d = np.zeros((rows, cols))
+    for r in range(1 if rows > 1 else 0, rows):
+        n = min(lengths[r % len(lengths)], cols)
+        d[r, rng.choice(cols, size=n, replace=False)] = rng.integers(1, 9, size=n) / 8.0
+        if n and r % 3:
+            d[r, 2] = rng.integers(1, 5) / 4.0          # a list of two thirds of the tile
+    out = synth.from_dense(np.asarray(d.astype(np.float32), dtype=np.float64))
+    zero = rng.choice(len(out["values"]), size=max(1, len(out["values"]) // 50), replace=False)
+    out["values"][zero] = 0.0
+    return out
+
+
+def _lists(spd, **options):
+    h = spd.Handle()
+    h.set_option("match_lists", 2)
+    for name, value in options.items():
+        h.set_option(name, value)
+    return h
+
+
+# rows of B: one, around a wavefront, several tiles with a short last one (an 8 KB budget makes a tile of 64
+# rows for one 8-byte sum, 128 for the counts); rows of A: fewer than the wavefronts of a workgroup, and more
+@pytest.mark.parametrize("metric", SERVED)
+@pytest.mark.parametrize("m,n,cols,budget", [(1, 1, 5, 163840), (3, 63, 70, 163840), (70, 65, 200, 163840), (18, 1300, 300, 163840),
+                                             (5, 129, 140, 32768), (150, 1000, 130, 32768)])
+def test_edges(spd, metric, m, n, cols, budget):
+    rng = np.random.default_rng(m * 1000 + n)
+    A = _matrix(rng, m, cols, (3, 64, 65, 1, 130, 0, 17))
+    B = _matrix(rng, n, cols, (2, 5, 0, 40, 9))
+    print("match lists", metric, m, n, cols, budget, flush=True)
+    h = _lists(spd, lds_budget=budget, profile=1)
+    p = _p_of(metric)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], p)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    assert_distances_close(_np(h.pairwise(dA, dB, metric, p)), want, metric)
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    k = min(n, 33)
+    idx, dist = h.knn(dA, dB, metric, k, p)
+    assert_knn_matches(_np(idx), _np(dist), want, k, metric, metric)
+    index = h.index_create(dB, metric, p)
+    assert np.array_equal(_np(index.pairwise(dA)), _np(h.pairwise(dA, dB, metric, p)))
+    i2, d2 = index.knn(dA, k)
+    assert np.array_equal(_np(i2), _np(idx)) and np.array_equal(_np(d2), _np(dist))
+    index.close()
+    h.close()
+
+
+@pytest.mark.parametrize("metric", ["l2_expanded", "l1", "hamming", "jensen_shannon", "minkowski"])
+@pytest.mark.parametrize("m,n,cols,lengths_a,lengths_b", [
+    (20, 1300, 1203, (1200, 257, 256, 900, 5, 0, 1203), (30, 3, 200)),           # rows that wavefronts share, one per tile and more
+    (33, 21_001, 3_001, (40, 2, 300, 0, 64), (31, 0, 37, 40)),                  # tiles dealt to the XCDs: 16 or more, lists beyond an L2
+])
+def test_shared_rows_and_many_tiles(spd, metric, m, n, cols, lengths_a, lengths_b):
+    rng = np.random.default_rng(n)
+
+    def matrix(rows, lengths):
+        indptr, indices, values = [0], [], []
+        for r in range(rows):
+            c = np.unique(rng.integers(0, cols, size=lengths[r % len(lengths)]))
+            indices.append(c)
+            values.append(rng.integers(0, 9, size=len(c)) / 8.0)                 # an eighth of them stored zeros
+            indptr.append(indptr[-1] + len(c))
+        return {"n_rows": rows, "n_cols": cols, "indptr": np.asarray(indptr, dtype=np.int64),
+                "indices": np.concatenate(indices).astype(np.int32), "values": np.concatenate(values).astype(np.float32)}
+
+    A, B = matrix(m, lengths_a), matrix(n, lengths_b)
+    print("match lists", metric, m, n, cols, flush=True)
+    h = _lists(spd)
+    p = _p_of(metric)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], p)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    assert_distances_close(_np(h.pairwise(dA, dB, metric, p)), want, metric)
+    idx, dist = h.knn(dA, dB, metric, 64, p)
+    assert_knn_matches(_np(idx), _np(dist), want, 64, metric, metric)
+    h.close()
+
+
+@pytest.mark.parametrize("metric", ["cosine", "jensen_shannon", "jaccard", "minkowski"])
+def test_same_as_the_staged_scan(spd, metric):
+    """Several thousand rows by the shapes of the synthetic data, rows longer than a batch, lists longer than a step."""
+    A, B = synth.workload(1, scale=0.3)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    p = _p_of(metric)
+    lists, staged = _lists(spd), spd.Handle()
+    staged.set_option("match_lists", 0)
+    got, want = _np(lists.pairwise(dA, dB, metric, p)), _np(staged.pairwise(dA, dB, metric, p))
+    # two roundings to single precision of sums that differ by the order of their double precision terms
+    assert np.allclose(got, want, rtol=2.5e-7, atol=1e-7)
+    assert np.array_equal(got, _np(lists.pairwise(dA, dB, metric, p)))          # and the same bits every time
+    gi, gd = lists.knn(dA, dB, metric, 32, p)
+    wi, wd = staged.knn(dA, dB, metric, 32, p)
+    assert np.allclose(_np(gd), _np(wd), rtol=2.5e-7, atol=1e-7)
+    assert np.mean(_np(gi) != _np(wi)) <= 1e-3
+    lists.close()
+    staged.close()
+
+
+def test_refusals_and_small_scratch(spd):
+    import torch
+    A, B = synth.workload(0)
+    h = _lists(spd)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    bad = dict(A, indptr=A["indptr"].copy())
+    bad["indptr"][3] = bad["indptr"][5] + 1
+    for first, second in ((spd.DeviceCsr.from_host(bad), dB), (dA, spd.DeviceCsr.from_host(bad))):
+        with pytest.raises(spd.SpdError) as e:
+            h.pairwise(first, second, "l1")
+        assert e.value.status_name == "SPD_ERR_BAD_CSR"
+    want = oracle.pairwise(A, B, "manhattan")
+    need = h.workspace_bytes(dA, dB, "l1")
+    h.set_workspace(torch.empty(need, dtype=torch.uint8, device="cuda"))
+    assert_distances_close(_np(h.pairwise(dA, dB, "l1")), want, "documented scratch")
+    h.close()
