@@ -74,7 +74,10 @@ template <int OP, bool KNN>
 __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) spd_match_kernel(const MatchArgs args) {
     using O = Op<OP>;
     using Cell = MatchCell<OP>;
-    constexpr int U = kMatchUnroll, D = sizeof(Cell) <= 8 ? 10 : 7, nw = match_waves(sizeof(Cell));
+    // D: 64-row pieces of a dense column that are summed in registers together; the largest tiles hold 19 for one
+    // fp64 sum (one round of 19 against two of 10: 2,048 queries of 300,000 rows of 230, 10.5 -> 10.2 ms; 13 and 6
+    // leave half a round idle: 11.3), 39 for a count and 13 for two sums
+    constexpr int U = kMatchUnroll, D = sizeof(Cell) == 8 ? 19 : (sizeof(Cell) == 4 ? 13 : 7), nw = match_waves(sizeof(Cell));
     extern __shared__ __align__(16) unsigned char dyn[];
     __shared__ int s_next;
     __shared__ int s_lock[KNN ? kMatchLocks : 1];
