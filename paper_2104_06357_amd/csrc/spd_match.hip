@@ -267,8 +267,9 @@ hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float
                            n_rows, nnz, metric, transform, norm, p, k, norms);
     };
     const int64_t mean = nnz / n_rows;
-    // (rows of power-law lengths: a wavefront alone takes 60 us over 24,000 entries)
-    if (mean >= 128) go(std::integral_constant<int, 256>{});
+    // (28,301 rows of power-law lengths: the longest, 24,000 entries, takes a wavefront alone 72 us and a workgroup 46;
+    // with many rows the workgroups' own cost counts: 300,000 rows of 230 take 354 us that way and 137 us otherwise)
+    if (mean >= 128 && n_rows <= 65536) go(std::integral_constant<int, 256>{});
     else if (mean >= 16) go(std::integral_constant<int, 64>{});
     else go(std::integral_constant<int, 4>{});
     return hipGetLastError();
