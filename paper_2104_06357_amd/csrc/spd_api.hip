@@ -491,6 +491,15 @@ bool operands_may_swap(int metric, const spd_semiring *semiring) {
 bool operands_swap_pays(const spd_csr *A, const spd_csr *B) {
     return A->nnz >= ((int64_t)1 << 18) && A->n_rows >= 1024 && B->nnz <= 96 * B->n_rows;
 }
+// (of a pairwise call without an index)
+bool swap_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, const spd_semiring *semiring) {
+    return operands_may_swap(metric, semiring) && (h->swap_operands == 2 || (h->swap_operands == 1 && operands_swap_pays(A, B)));
+}
+
+// What the planner, or check_rows in its place, found wrong with an operand.
+spd_status refuse_plan(spd_handle *h, const char *name, const std::string &why) {
+    return fail(h, why.find("pointers") != std::string::npos ? SPD_ERR_BAD_CSR : SPD_ERR_UNSUPPORTED, std::string(name) + ": " + why);
+}
 
 // ------------------------------------------------------------------------------------
 // Column lists (spd_match.h): the second way of computing a distance
@@ -575,7 +584,7 @@ bool match_bounds_fit(const MatchShape &s, int64_t nnz) {
 bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring) {
     if (h->match_lists == 0 || semiring || !match_serves(op)) return false;
     if (A->n_rows <= 0 || B->n_rows <= 0 || A->n_cols <= 0 || A->n_cols >= ((int64_t)1 << 31) - 8) return false;
-        const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz);
+    const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz);
     // (list positions are 32-bit byte offsets)
     if (s.n_tiles <= 0 || s.list_entries(B->nnz) >= ((int64_t)1 << 29)) return false;
     if (h->match_lists == 2) return true;
@@ -602,12 +611,16 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
                      const MetricInfo &mi, const MatchShape &s, const MatchGrid &g, const MatchScratch &L, const int64_t *a_ip,
                      const int64_t *b_ip, size_t ip_bytes, float *out, int64_t *out_idx, float *out_dist, const spd_index *index) {
     const int64_t m = A->n_rows, n = B->n_rows;
-    if (!index)
-        for (int64_t j = 0; j < n; ++j)
-            if (b_ip[j] > b_ip[j + 1] || b_ip[0] != 0) return fail(h, SPD_ERR_BAD_CSR, "B: row pointers are not ascending from 0");
-    for (int64_t i = 0; i < m; ++i)
-        if (a_ip[i] > a_ip[i + 1] || a_ip[0] != 0) return fail(h, SPD_ERR_BAD_CSR, "A: row pointers are not ascending from 0");
-    spd_status st = ensure_workspace(h, L.end);
+    // (the staged scan's planner refuses a row that is longer than the column count in the operand it stages)
+    auto refused = [&](const char *name, const int64_t *ip, int64_t rows, bool staged) {
+        const std::string why = check_rows(ip, rows, staged ? A->n_cols : INT64_MAX);
+        return why.empty() ? SPD_OK : refuse_plan(h, name, why);
+    };
+    const bool b_staged = knn_k == 0 && !index && swap_wanted(h, A, B, metric, nullptr);
+    spd_status st = index ? SPD_OK : refused("B", b_ip, n, b_staged);
+    if (st == SPD_OK) st = refused("A", a_ip, m, !b_staged);
+    if (st != SPD_OK) return st;
+    st = ensure_workspace(h, L.end);
     if (st != SPD_OK) return st;
     unsigned char *ws = reinterpret_cast<unsigned char *>(h->ws);
     hipError_t e;
@@ -705,8 +718,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         // (a caller's scratch that does not hold the lists still serves the staged scan)
         if (h->ws_external && match_l.end > h->ws_bytes) lists = false;
     }
-    const bool swapped = !lists && knn_k == 0 && !index && operands_may_swap(metric, semiring) &&
-                         (h->swap_operands == 2 || (h->swap_operands == 1 && operands_swap_pays(A, B)));
+    const bool swapped = !lists && knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
     if (swapped) std::swap(A, B);           // from here on A is the staged operand, B the streamed one
     const int64_t m = A->n_rows, n = B->n_rows;
     const int64_t out_stride_staged = swapped ? 1 : n, out_stride_streamed = swapped ? m : 1;
@@ -790,7 +802,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         PlanOptions opt_b = h->opt;
         opt_b.window = window_for(h->opt, knn_k > 0 || swapped ? WINDOW_NO_SCATTERED_STORES : WINDOW_SCATTERED_STORES);
         why = plan_b(b_ip, n, opt_b, h->plan_of_b);
-        if (!why.empty()) return fail(h, why.find("pointers") != std::string::npos ? SPD_ERR_BAD_CSR : SPD_ERR_UNSUPPORTED, "B: " + why);
+        if (!why.empty()) return refuse_plan(h, "B", why);
         lap("plan b");
     }
     int a_kind = 0, a_max_r = 1, a_min_r = 1;
@@ -845,7 +857,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     // ---- A, while the repack runs -------------------------------------------------------
     h->helper.wait();
     why = why_a;
-    if (!why.empty()) return fail(h, why.find("pointers") != std::string::npos ? SPD_ERR_BAD_CSR : SPD_ERR_UNSUPPORTED, "A: " + why);
+    if (!why.empty()) return refuse_plan(h, "A", why);
     lap("wait for plan a");
     {
         PlanOptions opt_c = h->opt;
@@ -1337,7 +1349,7 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
     } catch (const std::exception &ex) {
         why = std::string("planning failed: ") + ex.what();
     }
-    if (!why.empty()) return fail(h, why.find("pointers") != std::string::npos ? SPD_ERR_BAD_CSR : SPD_ERR_UNSUPPORTED, "Index: " + why);
+    if (!why.empty()) return refuse_plan(h, "Index", why);
     Carver cv;
     const BLayout bl = layout_b(ix->plan, n, cv);
     ix->dev_bytes = std::max<size_t>(cv.off, 256);

@@ -32,6 +32,16 @@ int occupancy_bucket(uint32_t stage_bytes, int64_t lds_total) {
 
 }  // namespace
 
+std::string check_rows(const int64_t *indptr, int64_t n_rows, int64_t longest) {
+    if (n_rows && indptr[0] != 0) return "indptr[0] != 0";
+    int64_t too_long = -1;
+    for (int64_t j = 0; j < n_rows; ++j) {
+        if (indptr[j + 1] < indptr[j]) return fmt("row pointers decrease at row", j);
+        if (too_long < 0 && indptr[j + 1] - indptr[j] > longest) too_long = j;
+    }
+    return too_long < 0 ? std::string() : fmt("row longer than the column count", too_long);
+}
+
 // ------------------------------------------------------------------------------------
 // B: slabs of 64 lanes
 // ------------------------------------------------------------------------------------

@@ -261,6 +261,10 @@ struct BPlan {
 std::string plan_staging(int64_t n_cols, int metric, int op, bool knn, const PlanOptions &opt, int &kind, int &max_r,
                          int &min_r, uint64_t &dmax);
 
+// What plan_a and plan_b find wrong with row pointers, for the calls that run without their plans: empty
+// if nothing.  No row may hold more than `longest` entries.
+std::string check_rows(const int64_t *indptr, int64_t n_rows, int64_t longest);
+
 // Both return an empty string on success, else the reason.
 std::string plan_b(const int64_t *indptr, int64_t n_rows, const PlanOptions &opt, BPlan &out);
 // With opt.consecutive_groups the staged rows are not sorted by length: rows 8q .. 8q+7 (32q .. 32q+31

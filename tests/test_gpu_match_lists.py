@@ -126,6 +126,59 @@ def test_same_as_the_staged_scan(spd, metric):
     staged.close()
 
 
+@pytest.mark.parametrize("entry", ["pairwise", "knn", "index_pairwise"])
+@pytest.mark.parametrize("fault", ["row longer than the column count", "pointers do not begin at 0", "pointers decrease", "last pointer"])
+def test_what_the_staged_scan_refuses_is_refused(spd, entry, fault):
+    """The same operands, malformed one at a time, through both ways: the same status, and where nothing is refused (the
+    scan looks at the lengths of the operand it stages alone) none from either."""
+    rng = np.random.default_rng(3)
+    good = _matrix(rng, 40, 30, (3, 17, 0, 9))
+
+    def malformed():
+        m = {name: (value.copy() if hasattr(value, "copy") else value) for name, value in good.items()}
+        if fault == "row longer than the column count":         # (a column twice: 40 entries in 30 columns)
+            long_row = np.sort(np.concatenate([np.arange(30), np.arange(10)])).astype(np.int32)
+            m["indices"] = np.concatenate([m["indices"], long_row])
+            m["values"] = np.concatenate([m["values"], np.full(40, 0.5, dtype=np.float32)])
+            m["indptr"] = np.concatenate([m["indptr"], m["indptr"][-1:] + 40])
+            m["n_rows"] += 1
+        elif fault == "pointers do not begin at 0":
+            m["indptr"][0] = 1
+        elif fault == "pointers decrease":
+            m["indptr"][5] = m["indptr"][9] + 1
+        else:
+            m["indptr"][-1] += 1
+        return m
+
+    def status(lists, swap, A, B):
+        h = spd.Handle()
+        h.set_option("match_lists", lists)
+        h.set_option("swap_operands", swap)
+        dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+        try:
+            if entry == "pairwise":
+                h.pairwise(dA, dB, "l1")
+            elif entry == "knn":
+                h.knn(dA, dB, "l1", 3)
+            else:
+                ix = h.index_create(dB, "l1")
+                try:
+                    ix.pairwise(dA)
+                finally:
+                    ix.close()
+            return "SPD_OK"
+        except spd.SpdError as e:
+            return e.status_name
+        finally:
+            h.close()
+
+    for A, B in ((malformed(), good), (good, malformed())):
+        for swap in (0, 2):
+            print("refusals", entry, fault, swap, flush=True)
+            assert status(2, swap, A, B) == status(0, swap, A, B)
+    assert status(2, 0, malformed(), good) != "SPD_OK"
+
+
 def test_refusals_and_small_scratch(spd):
     import torch
     A, B = synth.workload(0)
