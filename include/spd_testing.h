@@ -34,6 +34,19 @@ spd_status spd_host_plan_summary(const int64_t *a_indptr, int64_t a_rows, const 
                                  const char *const *option_names, const int64_t *option_values,
                                  int n_options, char *json, size_t cap);
 
+/* Whether a call on operands of these sizes (`k_neighbors` = 0 for pairwise, `with_index` for the calls
+ * on a prepared index) takes the column lists (option "match_lists"), and how it cuts them. */
+typedef struct {
+    int32_t wanted;
+    int32_t tiles, tile_rows;       /* of B */
+    int32_t slices, groups;         /* workgroups: slices of A's rows times groups of tiles */
+    int64_t scratch_bytes;
+} spd_list_plan;
+spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int64_t b_nnz, int64_t n_cols,
+                              spd_metric metric, float p, int k_neighbors, int with_index,
+                              const char *const *option_names, const int64_t *option_values, int n_options,
+                              spd_list_plan *out);
+
 #ifdef __cplusplus
 }
 #endif

@@ -94,7 +94,7 @@ def lib():
                    "spd_pairwise_static",
                    "spd_knn", "spd_semiring_pairwise", "spd_semiring_knn", "spd_index_create", "spd_index_destroy",
                    "spd_index_pairwise", "spd_index_knn", "spd_csr_validate", "spd_set_option", "spd_host_pair_value",
-                   "spd_host_plan_summary"):
+                   "spd_host_plan_summary", "spd_host_list_plan"):
             getattr(L, fn).restype = ctypes.c_int
         _lib = L
     return _lib

@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/spd.h"
+#include "../../include/spd_testing.h"
 #include "spd_kernels.h"
 #include "spd_match.h"
 #include "spd_plan.h"
@@ -581,7 +582,44 @@ bool scan_knobs_untouched(const spd_handle *h) {
 bool match_bounds_fit(const MatchShape &s, int64_t nnz) {
     return (int64_t)s.n_tiles * s.ptr_stride <= std::max<int64_t>(2 * nnz, 16 << 20);
 }
-bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring) {
+// Whether the lists cost less than the staged scan, in picoseconds of the whole chip.  A wavefront pays for
+// every entry of its row of A in every tile (its list's bounds; a step, where the list is not empty; what a
+// long list takes beyond one step), with k-NN for the selection in every (tile, row) too, and the last round of
+// (tile, row)s leaves wavefronts idle.  The staged scan pays for every visit (a staged row, a streamed entry;
+// more where longer staged rows leave fewer of them a place in LDS).  The constants are fitted to both ways' times
+// of 3,600 pairs of operands (100 to 12,000 rows against 600 to 300,000, rows of 2 to 4,000 entries, A's 1/30 to
+// 60 times as long as B's, uniform and Zipf columns, every product but the counts, k-NN with k = 10 to 64 and
+// pairwise).  Of 1,941 that the conditions on work and density in match_wanted let through, 452 took longer by
+// lists by a tenth or more, up to nine times; of the 1,338 that this lets through, 36, up to 1.7 times (and 19 of
+// 545 in 1,500 other pairs, up to 1.8 times, in columns far from uniform, which row pointers do not show).  Both
+// sides, staged / lists in ms:
+//   1,000 x 10,000 rows of 1,360 and 20 entries over 20,000 columns, L1            0.14 / 0.70
+//   766 x 3,599 rows of 1,468 and 35 over 20,000, Minkowski (p = 3), k = 32        0.15 / 1.03
+//   8,934 x 10,816 rows of 598 and 9 over 60,000, Jensen-Shannon (B staged)        36.7 / 1.49
+bool match_pays(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const MatchShape &s, bool swapped, bool knn) {
+    const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz;
+    const bool wide = match_cell_bytes(op) >= 16;
+    const double list = nnz_b / n / (double)A->n_cols * (double)s.tile_rows;          // entries, on the mean
+    const double entry = 30.0 + (wide ? 80.0 : 40.0) * std::min(1.0, list) + (wide ? 60.0 : 40.0) * list / 64.0;
+    const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn);
+    const double items = std::ceil(std::ceil(m / g.slices) * std::ceil((double)s.n_tiles / g.groups) / s.waves);     // of a wavefront
+    const double idle = items * s.waves * (double)h->opt.n_cus / (m * s.n_tiles);
+    const double lists = idle * s.n_tiles * (entry * nnz_a + (knn ? 2000.0 * m : 0.0)) + m * n;
+    double visit = 0.6;
+    switch (op) {
+    case OP_DOT: case OP_L1: visit = 0.12; break;
+    case OP_HAMM: visit = 0.15; break;
+    case OP_CANB: visit = 0.29; break;
+    case OP_KL: visit = 0.34; break;
+    case OP_JS: visit = 0.72; break;
+    default: break;
+    }
+    visit += 7e-5 * (swapped ? nnz_b / n : nnz_a / m);
+    const double staged = visit * (swapped ? n * nnz_a : m * nnz_b) + (knn ? 2.6 : 2.0) * m * n;
+    return lists <= 0.9 * staged;
+}
+// `swapped`: the staged scan would exchange the operands' roles.
+bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn) {
     if (h->match_lists == 0 || semiring || !match_serves(op)) return false;
     if (A->n_rows <= 0 || B->n_rows <= 0 || A->n_cols <= 0 || A->n_cols >= ((int64_t)1 << 31) - 8) return false;
     const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz);
@@ -589,9 +627,7 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     if (s.n_tiles <= 0 || s.list_entries(B->nnz) >= ((int64_t)1 << 29)) return false;
     if (h->match_lists == 2) return true;
     if (!scan_knobs_untouched(h)) return false;
-    // The staged scan costs the same for every visit (a row of A, a stored entry of B); the lists cost a build,
-    // some 17 ps an entry of B, and then a third to a half of a visit per visit, less for the products that
-    // are dear (their visits that meet nothing pay in full in the staged scan).  Both sides measured, staged /
+    // The build takes some 17 ps an entry of B, and a call's other launches have a price too.  Both sides measured, staged /
     // lists in ms:  10,000 x 10,000 rows of 38, L1 0.65 / 0.41;  3,207 x 1,172 of them 0.15 / 0.16;  1,024 x
     // 300,000 of 230, cosine 11.4 / 6.7;  97 x 113,185 of them 0.86 / 0.96;  4,096 x 65,536 of 1,820, L1 87 / 36,
     // Jensen-Shannon 349 / 59;  126 x 2,556 of them, KL 0.55 / 0.83.  The set metrics stay with the staged
@@ -604,7 +640,7 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     if (work < (mean <= 64.0 ? 1.5e8 : 3e9) || (double)A->n_rows * weight < 400.0) return false;
     // where an eighth of B's cells are stored (half, for a dear product), most visits meet something
     if (mean > (light ? 0.125 : 0.5) * (double)A->n_cols) return false;
-    return match_bounds_fit(s, B->nnz);
+    return match_bounds_fit(s, B->nnz) && match_pays(h, A, B, op, s, swapped, knn);
 }
 
 spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, int op, int knn_k, const OpParams &q,
@@ -708,7 +744,8 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     MatchShape match{};
     MatchGrid match_g;
     MatchScratch match_l{};
-    bool lists = match_wanted(h, A, B, op, semiring) && (!index || index->match.list);
+    const bool swap = knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
+    bool lists = match_wanted(h, A, B, op, semiring, swap, knn_k > 0) && (!index || index->match.list);
     if (lists) {
         match = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz);
         match_g = match_grid(h->opt, match, A->n_rows, A->nnz, B->nnz, knn_k > 0);
@@ -718,7 +755,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         // (a caller's scratch that does not hold the lists still serves the staged scan)
         if (h->ws_external && match_l.end > h->ws_bytes) lists = false;
     }
-    const bool swapped = !lists && knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
+    const bool swapped = swap && !lists;
     if (swapped) std::swap(A, B);           // from here on A is the staged operand, B the streamed one
     const int64_t m = A->n_rows, n = B->n_rows;
     const int64_t out_stride_staged = swapped ? 1 : n, out_stride_streamed = swapped ? m : 1;
@@ -1177,7 +1214,8 @@ spd_status spd_workspace_bytes(const spd_handle *h, const spd_csr *A, const spd_
     // (a call may take the column lists; Minkowski of degree 1 runs as L1)
     for (const int as_metric : {(int)metric, metric == SPD_MINKOWSKI ? (int)SPD_L1 : (int)metric}) {
         const int op = product_of(h, as_metric, 2.0f);
-        if (!match_wanted(h, A, B, op, nullptr)) continue;
+        const bool swap = k_neighbors == 0 && swap_wanted(h, A, B, as_metric, nullptr);
+        if (!match_wanted(h, A, B, op, nullptr, swap, k_neighbors > 0)) continue;
         const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, B->n_cols, B->nnz);
         const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, k_neighbors > 0);
         *bytes = std::max(*bytes, layout_match_call(s, g, A->n_rows, B->n_rows, B->nnz, k_neighbors, true).end);
@@ -1536,5 +1574,32 @@ const char *spd_metric_name(spd_metric metric) {
 }
 
 const char *spd_version(void) { return "spd 0.1 (gfx950)"; }
+
+// A test hook (include/spd_testing.h): it touches no GPU.
+spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int64_t b_nnz, int64_t n_cols, spd_metric metric, float p,
+                              int k_neighbors, int with_index, const char *const *option_names, const int64_t *option_values,
+                              int n_options, spd_list_plan *out) {
+    if (!out) return SPD_ERR_NULL;
+    if ((int)metric < 0 || (int)metric >= SPD_METRIC_COUNT) return SPD_ERR_BAD_METRIC;
+    spd_handle h;
+    for (int i = 0; i < n_options; ++i) {
+        const spd_status st = spd_set_option(&h, option_names[i], option_values[i]);
+        if (st != SPD_OK) return st;
+    }
+    const spd_csr A{a_rows, n_cols, a_nnz, nullptr, nullptr, nullptr, nullptr}, B{b_rows, n_cols, b_nnz, nullptr, nullptr, nullptr, nullptr};
+    const int run_as = effective_metric((int)metric, p), op = product_of(&h, run_as, p);
+    const bool knn = k_neighbors > 0, swap = !knn && !with_index && swap_wanted(&h, &A, &B, run_as, nullptr);
+    std::memset(out, 0, sizeof *out);
+    out->wanted = match_wanted(&h, &A, &B, op, nullptr, swap, knn);
+    const MatchShape s = match_shape(h.opt.lds_budget, op, b_rows, n_cols, b_nnz);
+    if (s.n_tiles <= 0) return SPD_OK;
+    const MatchGrid g = match_grid(h.opt, s, a_rows, a_nnz, b_nnz, knn);
+    out->tiles = s.n_tiles;
+    out->tile_rows = s.tile_rows;
+    out->slices = g.slices;
+    out->groups = g.groups;
+    out->scratch_bytes = (int64_t)layout_match_call(s, g, a_rows, b_rows, b_nnz, k_neighbors, !with_index).end;
+    return SPD_OK;
+}
 
 }  // extern "C"

@@ -36,3 +36,19 @@ def host_plan_summary(a_indptr, b_indptr, n_cols, metric, k_neighbors=0, **optio
     if st != 0:
         raise SpdError(st, text)
     return json.loads(text)
+
+
+class _ListPlan(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_int32) for name in ("wanted", "tiles", "tile_rows", "slices", "groups")] + [("scratch_bytes", ctypes.c_int64)]
+
+
+def host_list_plan(a_rows, a_nnz, b_rows, b_nnz, n_cols, metric, p=2.0, k_neighbors=0, with_index=False, **options) -> dict:
+    names = (ctypes.c_char_p * max(1, len(options)))(*[k.encode() for k in options])
+    vals = (ctypes.c_int64 * max(1, len(options)))(*[int(v) for v in options.values()])
+    out = _ListPlan()
+    i64 = ctypes.c_int64
+    st = lib().spd_host_list_plan(i64(a_rows), i64(a_nnz), i64(b_rows), i64(b_nnz), i64(n_cols), metric_id(metric), ctypes.c_float(p),
+                                  int(k_neighbors), int(with_index), names, vals, len(options), ctypes.byref(out))
+    if st != 0:
+        raise SpdError(st, "spd_host_list_plan")
+    return {name: getattr(out, name) for name, _ in _ListPlan._fields_}

@@ -223,3 +223,37 @@ def test_quotients_inside_the_logarithms_on_the_host(metric):
     A = synth.from_dense(np.array([[1.0, 0.5]])); B = synth.from_dense(np.array([[1e-8, 0.5]]))
     got = spd.testing.host_pair_value("jensen_shannon", 2.0, 2, A["indices"], A["values"], B["indices"], B["values"])
     assert abs(got - 0.5887) < 1e-4
+
+
+def _wanted(m, mean_a, n, mean_b, cols, metric, **more):
+    return bool(spd.testing.host_list_plan(m, m * mean_a, n, n * mean_b, cols, metric, **more)["wanted"])
+
+
+@pytest.mark.parametrize("metric", ["l1", "cosine", "hamming", "canberra", "kl_divergence", "jensen_shannon", "minkowski"])
+def test_column_lists_are_left_alone_where_a_is_long_against_b(metric):
+    """The lists cost a step per entry of A and tile, the staged scan a visit per staged row and streamed entry: for a given
+    B, long enough rows of A turn the choice, once, whatever else the call is."""
+    for with_index, k in ((False, 32), (True, 0), (True, 32)):
+        choice = [_wanted(2_000, mean_a, 10_000, 20, 20_000, metric, k_neighbors=k, with_index=with_index)
+                  for mean_a in (1, 3, 10, 30, 100, 300, 1_000, 3_000)]
+        assert choice[1] and not choice[-2] and not choice[-1], (with_index, k, choice)
+        assert choice[1:] == sorted(choice[1:], reverse=True), choice
+
+
+def test_column_lists_against_the_scan_that_would_run():
+    # both ways measured, staged / lists in ms: 0.14 / 0.70, 0.14 / 0.90, 0.15 / 1.03, 2.18 / 6.52
+    assert not _wanted(1_000, 1_360, 10_000, 20, 20_000, "l1")
+    assert not _wanted(1_000, 1_346, 10_000, 20, 20_000, "l1", k_neighbors=32)
+    assert not _wanted(766, 1_468, 3_599, 35, 20_000, "minkowski", p=3.0, k_neighbors=32, with_index=True)
+    assert not _wanted(436, 2_548, 217_842, 50, 200_000, "hamming")
+    # a pairwise call that would stage B and stream the long rows of A: 36.7 / 1.49
+    assert _wanted(8_934, 598, 10_816, 9, 60_000, "jensen_shannon")
+    # operands of one law: 0.65 / 0.41, 11.4 / 6.7, 17.1 / 10.2, 87 / 36, 349 / 59, 2.67 / 1.16
+    assert _wanted(10_000, 37, 10_000, 37, 20_000, "l1") and _wanted(10_000, 37, 10_000, 37, 20_000, "cosine")
+    assert _wanted(1_024, 228, 300_000, 228, 102_660, "cosine")
+    assert _wanted(2_048, 228, 300_000, 228, 102_660, "hellinger", k_neighbors=32, with_index=True)
+    assert _wanted(4_096, 1_820, 65_536, 1_820, 26_000, "l1") and _wanted(4_096, 1_820, 65_536, 1_820, 26_000, "jensen_shannon")
+    assert _wanted(1_531, 160, 28_301, 160, 194_000, "canberra")
+    # and the option decides where it is asked to
+    assert not _wanted(10_000, 37, 10_000, 37, 20_000, "l1", match_lists=0)
+    assert _wanted(766, 1_468, 3_599, 35, 20_000, "minkowski", match_lists=2)
