@@ -306,9 +306,11 @@ spd_status spd_csr_validate(spd_handle *handle, const spd_csr *M, int require_no
  *   "match_lists" the second way of computing a distance: B's rows are cut into tiles, each tile's entries
  *                 listed by column, and a wavefront walks the lists of its row of A, so that only the
  *                 columns two rows share cost anything (not for Chebyshev and the semirings that are not
- *                 spelled as a distance).  1 (default): where it pays (sparse and long enough operands, and
- *                 no knob of the staged scan turned); 0: never; 2: wherever the product has it and the
- *                 scratch holds the lists.  The sums' order differs between the two ways.
+ *                 spelled as a distance).  1 (default): where it pays (sparse and long enough operands, A's
+ *                 rows not too long against B's, no knob of the staged scan turned); 0: never; 2: wherever
+ *                 the product has it.  A call whose lists the caller's scratch does not hold, or the device
+ *                 has no memory for, runs by the staged scan; the handle asks the device for that much again
+ *                 only after the option is set again.  The sums' order differs between the two ways.
  *   "check_plan"  1: verify every index the kernels will form from the plan before launching
  *   "profile"     1: bracket every kernel launch with HIP events (see spd_profile_read)
  * Unknown names or values out of range return SPD_ERR_UNSUPPORTED. */

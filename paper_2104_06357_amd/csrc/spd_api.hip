@@ -134,6 +134,7 @@ struct spd_handle {
     int cuckoo_attempts = 3;     // option "cuckoo_attempts"
     int knn_seed = 1;            // option "knn_seed"
     int match_lists = 1;         // option "match_lists": 0 never, 1 where it pays, 2 wherever the product allows it
+    size_t lists_refused = SIZE_MAX;     // the least scratch for the column lists that the device had no memory for
     int swap_operands = 1;       // option "swap_operands": 0 never, 1 where it pays, 2 wherever the distance allows it
     int side_streams = 3;        // option "side_streams": how many internal streams the small launches may use beside the large one
     static constexpr int kSideStreams = 3;
@@ -656,9 +657,7 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     spd_status st = index ? SPD_OK : refused("B", b_ip, n, b_staged);
     if (st == SPD_OK) st = refused("A", a_ip, m, !b_staged);
     if (st != SPD_OK) return st;
-    st = ensure_workspace(h, L.end);
-    if (st != SPD_OK) return st;
-    unsigned char *ws = reinterpret_cast<unsigned char *>(h->ws);
+    unsigned char *ws = reinterpret_cast<unsigned char *>(h->ws);         // (run() has seen to its size)
     hipError_t e;
     MatchB mb = index ? index->match : match_b_at(s, L.b, ws);
     if (!index) {
@@ -739,6 +738,11 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
 
 spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, float p, const spd_semiring *semiring,
                int knn_k, float *out, int64_t *out_idx, float *out_dist, const spd_index *index = nullptr) {
+    for (auto &t : h->timed) { h->event_pool.push_back(t.start); h->event_pool.push_back(t.stop); }
+    h->timed.clear();
+    if (A->n_rows == 0 || B->n_rows == 0) return SPD_OK;
+    hipError_t e = hipSetDevice(h->device);
+    if (e != hipSuccess) return hip_fail(h, e, "hipSetDevice");
     metric = effective_metric(metric, p);
     const int op = product_of(h, metric, p);
     MatchShape match{};
@@ -754,6 +758,18 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
             lists = false;              // (created under other options)
         // (a caller's scratch that does not hold the lists still serves the staged scan)
         if (h->ws_external && match_l.end > h->ws_bytes) lists = false;
+        // (and so does a device that has no memory left for them; so much is not asked for again)
+        if (lists && !h->ws_external) {
+            const spd_status st = match_l.end < h->lists_refused ? ensure_workspace(h, match_l.end) : SPD_ERR_WORKSPACE;
+            if (st == SPD_ERR_WORKSPACE) {
+                h->lists_refused = std::min(h->lists_refused, match_l.end);
+                h->err.clear();
+                (void)hipGetLastError();
+                lists = false;
+            } else if (st != SPD_OK) {
+                return st;
+            }
+        }
     }
     const bool swapped = swap && !lists;
     if (swapped) std::swap(A, B);           // from here on A is the staged operand, B the streamed one
@@ -768,11 +784,6 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         std::fprintf(stderr, "[spd host] %-12s %8.1f us\n", what, std::chrono::duration<double, std::micro>(t - t_begin).count());
         t_begin = t;
     };
-    for (auto &t : h->timed) { h->event_pool.push_back(t.start); h->event_pool.push_back(t.stop); }
-    h->timed.clear();
-    if (m == 0 || n == 0) return SPD_OK;
-    hipError_t e = hipSetDevice(h->device);
-    if (e != hipSuccess) return hip_fail(h, e, "hipSetDevice");
 
     // ---- row pointers on the host: the caller's copies, or read back (the call's only
     //      synchronisation) ----------------------------------------------------------------
@@ -1538,6 +1549,7 @@ spd_status spd_set_option(spd_handle *h, const char *name, int64_t value) {
     } else if (s == "match_lists") {
         if (value < 0 || value > 2) return fail(h, SPD_ERR_UNSUPPORTED, "match_lists must be 0, 1 or 2");
         h->match_lists = (int)value;
+        h->lists_refused = SIZE_MAX;
     } else if (s == "swap_operands") {
         if (value < 0 || value > 2) return fail(h, SPD_ERR_UNSUPPORTED, "swap_operands must be 0, 1 or 2");
         h->swap_operands = (int)value;

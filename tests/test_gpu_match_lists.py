@@ -195,3 +195,42 @@ def test_refusals_and_small_scratch(spd):
     h.set_workspace(torch.empty(need, dtype=torch.uint8, device="cuda"))
     assert_distances_close(_np(h.pairwise(dA, dB, "l1")), want, "documented scratch")
     h.close()
+
+
+@pytest.fixture()
+def scarce(spd):
+    """Operands whose lists (a word per tile and column) take more memory than the device has left, and whose scan takes
+    some megabytes."""
+    import torch
+    rng = np.random.default_rng(8)
+    cols = 2_000_000_000
+
+    def matrix(rows):
+        c = np.sort(rng.integers(0, 40, size=(rows, 6)) + 49_999_999 * rng.integers(0, 40, size=(rows, 1)), axis=1)
+        keep = np.concatenate([np.ones((rows, 1), bool), np.diff(c, axis=1) > 0], axis=1)
+        return {"n_rows": rows, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum(keep.sum(1))]).astype(np.int64),
+                "indices": c[keep].astype(np.int32), "values": rng.integers(1, 9, size=int(keep.sum())).astype(np.float32)}
+
+    dA, dB = spd.DeviceCsr.from_host(matrix(5)), spd.DeviceCsr.from_host(matrix(2_000))
+    staged = spd.Handle()
+    staged.set_option("match_lists", 0)
+    want = _np(staged.pairwise(dA, dB, "minkowski", 3.0))
+    staged.close()
+    h = _lists(spd, profile=1)
+    need = h.workspace_bytes(dA, dB, "minkowski")
+    assert need > 30 << 30
+    filler = torch.empty(torch.cuda.mem_get_info()[0] - need // 2, dtype=torch.uint8, device="cuda")
+    yield h, dA, dB, want
+    h.close()
+    del filler
+    torch.cuda.empty_cache()
+
+
+def test_a_call_without_memory_for_the_lists_takes_the_scan(scarce):
+    h, dA, dB, want = scarce
+    print("lists beyond the device's memory", flush=True)
+    for _ in range(2):
+        assert np.array_equal(_np(h.pairwise(dA, dB, "minkowski", 3.0)), want)
+        assert all(r["staging_kind"] != 6 for r in h.profile_read() if r["name"] == "scan")
+    idx, dist = h.knn(dA, dB, "minkowski", 4, 3.0)
+    assert np.array_equal(_np(dist), np.sort(want, axis=1)[:, :4])
