@@ -1421,13 +1421,16 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         if (s.n_tiles > 0 && s.list_entries(Index->nnz) < ((int64_t)1 << 29) && (h->match_lists == 2 || (op != OP_CNT && match_bounds_fit(s, Index->nnz)))) {
             Carver lists;
             const MatchLayout L = layout_match(s, n, Index->nnz, lists);
-            e = hipMalloc(&ix->match_dev, std::max<size_t>(lists.off, 256));
-            if (e != hipSuccess) { ix->match_dev = nullptr; return fail(h, SPD_ERR_WORKSPACE, std::string("hipMalloc of the index failed: ") + hipGetErrorString(e)); }
-            ix->match = match_b_at(s, L, reinterpret_cast<unsigned char *>(ix->match_dev));
-            ix->match_op = op;
-            e = launch_match_build(h->stream, Index->indptr, Index->indices, Index->values, n, Index->nnz, (uint32_t)Index->n_cols,
-                                   ix->match, match_cell_bytes(op), run_as, mi.transform, mi.norm, q.p);
-            if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
+            if (hipMalloc(&ix->match_dev, std::max<size_t>(lists.off, 256)) == hipSuccess) {
+                ix->match = match_b_at(s, L, reinterpret_cast<unsigned char *>(ix->match_dev));
+                ix->match_op = op;
+                e = launch_match_build(h->stream, Index->indptr, Index->indices, Index->values, n, Index->nnz, (uint32_t)Index->n_cols,
+                                       ix->match, match_cell_bytes(op), run_as, mi.transform, mi.norm, q.p);
+                if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
+            } else {                     // (no memory left for the lists: the packed copy serves every call)
+                ix->match_dev = nullptr;
+                (void)hipGetLastError();
+            }
         }
     }
     guard.p = nullptr;

@@ -234,3 +234,13 @@ def test_a_call_without_memory_for_the_lists_takes_the_scan(scarce):
         assert all(r["staging_kind"] != 6 for r in h.profile_read() if r["name"] == "scan")
     idx, dist = h.knn(dA, dB, "minkowski", 4, 3.0)
     assert np.array_equal(_np(dist), np.sort(want, axis=1)[:, :4])
+
+
+def test_an_index_without_memory_for_the_lists_keeps_the_packed_copy(scarce):
+    h, dA, dB, want = scarce
+    print("index, lists beyond the device's memory", flush=True)
+    ix = h.index_create(dB, "minkowski", 3.0)
+    assert np.array_equal(_np(ix.pairwise(dA)), want)
+    idx, dist = ix.knn(dA, 4)
+    assert np.array_equal(_np(dist), np.sort(want, axis=1)[:, :4])
+    ix.close()
