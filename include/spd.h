@@ -153,8 +153,9 @@ spd_status spd_knn(spd_handle *handle, const spd_csr *Q, const spd_csr *Index, s
  * protocol fits the whole dataset, then queries it batch by batch).  spd_index_create does what
  * every spd_pairwise / spd_knn call does for B - reads its row pointers back, bins its rows by
  * degree, repacks it and sums its row norms for `metric` (`p`: SPD_MINKOWSKI only) - into device
- * memory the index owns (about 8 bytes per stored entry and 40 per row, and where the column lists serve
- * the metric (option "match_lists") up to 20 bytes per stored entry more); spd_index_pairwise /
+ * memory the index owns (about 8 bytes per stored entry and 40 per row, and where calls may want the
+ * column lists (option "match_lists" as it stands at creation) and they take no more than that, up to 20
+ * bytes per stored entry, 16 per row and 1 MiB more); spd_index_pairwise /
  * spd_index_knn then return exactly what spd_pairwise / spd_knn return for the same operands.
  * The index keeps the pointers of `Index`, not a copy: the three arrays must stay valid and
  * unchanged until spd_index_destroy.  The work is enqueued on the creating handle's stream; use

@@ -41,6 +41,7 @@ typedef struct {
     int32_t tiles, tile_rows;       /* of B */
     int32_t slices, groups;         /* workgroups: slices of A's rows times groups of tiles */
     int64_t scratch_bytes;
+    int64_t index_bytes;            /* what an index keeps of lists; 0: none */
 } spd_list_plan;
 spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int64_t b_nnz, int64_t n_cols,
                               spd_metric metric, float p, int k_neighbors, int with_index,

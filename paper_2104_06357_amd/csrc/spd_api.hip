@@ -583,6 +583,32 @@ bool scan_knobs_untouched(const spd_handle *h) {
 bool match_bounds_fit(const MatchShape &s, int64_t nnz) {
     return (int64_t)s.n_tiles * s.ptr_stride <= std::max<int64_t>(2 * nnz, 16 << 20);
 }
+bool match_light(int op) { return op == OP_DOT || op == OP_L1 || op == OP_HAMM; }
+// Whether B's rows have lists for a product at all, under the option's setting.
+bool match_possible(const spd_handle *h, const spd_csr *B, int op, MatchShape &s) {
+    if (h->match_lists == 0 || !match_serves(op)) return false;
+    if (B->n_rows <= 0 || B->n_cols <= 0 || B->n_cols >= ((int64_t)1 << 31) - 8) return false;
+    s = match_shape(h->opt.lds_budget, op, B->n_rows, B->n_cols, B->nnz);
+    // (list positions are 32-bit byte offsets)
+    return s.n_tiles > 0 && s.list_entries(B->nnz) < ((int64_t)1 << 29);
+}
+// Whether some call could do better by them, as far as B tells.
+bool match_suits(const spd_handle *h, const spd_csr *B, int op, const MatchShape &s) {
+    // the set metrics stay with the staged scan, whose visit is a byte add (605 x 168,903 rows of 230, Dice 3.0 / 3.5 ms)
+    if (op == OP_CNT || !scan_knobs_untouched(h)) return false;
+    // where an eighth of B's cells are stored (half, for a dear product), most visits meet something
+    if ((double)B->nnz > (match_light(op) ? 0.125 : 0.5) * (double)B->n_cols * (double)B->n_rows) return false;
+    return match_bounds_fit(s, B->nnz);
+}
+// Whether an index keeps the lists, and their layout in its memory: only lists that a call may want, and no more of
+// them than the header states (a small B over many columns has more bounds than entries).
+bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape &s, MatchLayout &L) {
+    if (!match_possible(h, B, op, s)) return false;
+    Carver cv;
+    L = layout_match(s, B->n_rows, B->nnz, cv);
+    if (h->match_lists == 2) return true;
+    return match_suits(h, B, op, s) && (int64_t)L.end <= 20 * B->nnz + 16 * B->n_rows + (1 << 20);
+}
 // Whether the lists cost less than the staged scan, in picoseconds of the whole chip.  A wavefront pays for
 // every entry of its row of A in every tile (its list's bounds; a step, where the list is not empty; what a
 // long list takes beyond one step), with k-NN for the selection in every (tile, row) too, and the last round of
@@ -621,27 +647,20 @@ bool match_pays(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op,
 }
 // `swapped`: the staged scan would exchange the operands' roles.
 bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn) {
-    if (h->match_lists == 0 || semiring || !match_serves(op)) return false;
-    if (A->n_rows <= 0 || B->n_rows <= 0 || A->n_cols <= 0 || A->n_cols >= ((int64_t)1 << 31) - 8) return false;
-    const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz);
-    // (list positions are 32-bit byte offsets)
-    if (s.n_tiles <= 0 || s.list_entries(B->nnz) >= ((int64_t)1 << 29)) return false;
+    MatchShape s;
+    if (semiring || A->n_rows <= 0 || !match_possible(h, B, op, s)) return false;
     if (h->match_lists == 2) return true;
-    if (!scan_knobs_untouched(h)) return false;
+    if (!match_suits(h, B, op, s)) return false;
     // The build takes some 17 ps an entry of B, and a call's other launches have a price too.  Both sides measured, staged /
     // lists in ms:  10,000 x 10,000 rows of 38, L1 0.65 / 0.41;  3,207 x 1,172 of them 0.15 / 0.16;  1,024 x
     // 300,000 of 230, cosine 11.4 / 6.7;  97 x 113,185 of them 0.86 / 0.96;  4,096 x 65,536 of 1,820, L1 87 / 36,
-    // Jensen-Shannon 349 / 59;  126 x 2,556 of them, KL 0.55 / 0.83.  The set metrics stay with the staged
-    // scan, whose visit is a byte add (605 x 168,903 rows of 230, Dice 3.0 / 3.5).
-    if (op == OP_CNT) return false;
-    const bool light = op == OP_DOT || op == OP_L1 || op == OP_HAMM;
+    // Jensen-Shannon 349 / 59;  126 x 2,556 of them, KL 0.55 / 0.83.
+    const bool light = match_light(op);
     const double weight = light ? 1.0 : (op == OP_CANB ? 2.0 : (op == OP_KL ? 2.5 : (op == OP_JS ? 4.5 : 3.5)));
     const double work = (double)A->n_rows * (double)B->nnz * weight;
     const double mean = (double)B->nnz / (double)B->n_rows;
     if (work < (mean <= 64.0 ? 1.5e8 : 3e9) || (double)A->n_rows * weight < 400.0) return false;
-    // where an eighth of B's cells are stored (half, for a dear product), most visits meet something
-    if (mean > (light ? 0.125 : 0.5) * (double)A->n_cols) return false;
-    return match_bounds_fit(s, B->nnz) && match_pays(h, A, B, op, s, swapped, knn);
+    return match_pays(h, A, B, op, s, swapped, knn);
 }
 
 spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, int op, int knn_k, const OpParams &q,
@@ -1416,21 +1435,18 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         if (st != SPD_OK) return st;
     }
     const int op = product_of(h, run_as, p);
-    if (n > 0 && h->match_lists != 0 && match_serves(op) && Index->n_cols < ((int64_t)1 << 31) - 8) {
-        const MatchShape s = match_shape(h->opt.lds_budget, op, n, Index->n_cols, Index->nnz);
-        if (s.n_tiles > 0 && s.list_entries(Index->nnz) < ((int64_t)1 << 29) && (h->match_lists == 2 || (op != OP_CNT && match_bounds_fit(s, Index->nnz)))) {
-            Carver lists;
-            const MatchLayout L = layout_match(s, n, Index->nnz, lists);
-            if (hipMalloc(&ix->match_dev, std::max<size_t>(lists.off, 256)) == hipSuccess) {
-                ix->match = match_b_at(s, L, reinterpret_cast<unsigned char *>(ix->match_dev));
-                ix->match_op = op;
-                e = launch_match_build(h->stream, Index->indptr, Index->indices, Index->values, n, Index->nnz, (uint32_t)Index->n_cols,
-                                       ix->match, match_cell_bytes(op), run_as, mi.transform, mi.norm, q.p);
-                if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
-            } else {                     // (no memory left for the lists: the packed copy serves every call)
-                ix->match_dev = nullptr;
-                (void)hipGetLastError();
-            }
+    MatchShape shape;
+    MatchLayout lists;
+    if (index_keeps_lists(h, Index, op, shape, lists)) {
+        if (hipMalloc(&ix->match_dev, lists.end) == hipSuccess) {
+            ix->match = match_b_at(shape, lists, reinterpret_cast<unsigned char *>(ix->match_dev));
+            ix->match_op = op;
+            e = launch_match_build(h->stream, Index->indptr, Index->indices, Index->values, n, Index->nnz, (uint32_t)Index->n_cols,
+                                   ix->match, match_cell_bytes(op), run_as, mi.transform, mi.norm, q.p);
+            if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
+        } else {                         // (no memory left for the lists: the packed copy serves every call)
+            ix->match_dev = nullptr;
+            (void)hipGetLastError();
         }
     }
     guard.p = nullptr;
@@ -1613,6 +1629,9 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     out->tile_rows = s.tile_rows;
     out->slices = g.slices;
     out->groups = g.groups;
+    MatchShape kept;
+    MatchLayout L;
+    out->index_bytes = index_keeps_lists(&h, &B, op, kept, L) ? (int64_t)L.end : 0;
     out->scratch_bytes = (int64_t)layout_match_call(s, g, a_rows, b_rows, b_nnz, k_neighbors, !with_index).end;
     return SPD_OK;
 }

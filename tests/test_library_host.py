@@ -257,3 +257,27 @@ def test_column_lists_against_the_scan_that_would_run():
     # and the option decides where it is asked to
     assert not _wanted(10_000, 37, 10_000, 37, 20_000, "l1", match_lists=0)
     assert _wanted(766, 1_468, 3_599, 35, 20_000, "minkowski", match_lists=2)
+
+
+def test_an_index_keeps_lists_that_calls_may_want_within_the_stated_memory():
+    def kept(n, mean, cols, metric, **more):
+        plan = spd.testing.host_list_plan(1_000, 30_000, n, int(n * mean), cols, metric, with_index=True, **more)
+        assert more.get("match_lists") == 2 or plan["index_bytes"] <= 20 * int(n * mean) + 16 * n + (1 << 20)
+        return plan["index_bytes"]
+
+    rng = np.random.default_rng(17)
+    for _ in range(2_000):
+        cols = int(2 ** rng.uniform(4, 30))
+        kept(int(2 ** rng.uniform(0, 22)), min(2 ** rng.uniform(-2, 12), cols), cols, ALL_METRICS[rng.integers(len(ALL_METRICS))])
+    # more list bounds than entries (24 MB of them for 17,600 entries); a cell in six stored; set metrics; scan knobs turned
+    assert kept(8_000, 2.2, 858_000, "cosine") == 0 and kept(100, 10, 1_000_000, "l1") == 0
+    assert kept(20_000, 50, 300, "l1") == 0 and kept(20_000, 50, 300, "jensen_shannon") > 0
+    assert kept(20_000, 50, 20_000, "jaccard") == 0
+    assert kept(20_000, 50, 20_000, "l1") > 0 and kept(20_000, 50, 20_000, "l1", force_kind=3) == 0
+    assert kept(20_000, 50, 20_000, "l1", match_lists=0) == 0 and kept(8_000, 2.2, 858_000, "cosine", match_lists=2) > 0
+    # the working range
+    for n, mean, cols in ((300, 37, 20_000), (12_000, 37, 20_000), (5_000, 228, 102_660), (300_000, 228, 102_660), (500, 1_820, 26_000),
+                          (60_000, 1_820, 26_000), (2_000, 160, 194_000), (200_000, 160, 194_000)):
+        # (Minkowski's tiles are half as long: over 194,000 columns their bounds outgrow rows of 160)
+        for metric in ("cosine", "l1", "canberra", "jensen_shannon") + (("minkowski",) if cols < 194_000 else ()):
+            assert kept(n, mean, cols, metric) > 0, (n, mean, cols, metric)
