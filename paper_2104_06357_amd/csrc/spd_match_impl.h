@@ -418,7 +418,13 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
                 reinterpret_cast<Cell *>(dyn + (size_t)owner * strip_bytes)[i] = sum;
             }
             __syncthreads();
-            if (wave == owner) finish(tile, row);
+            if (wave == owner) {
+                finish(tile, row);
+                // (dense columns add behind the last tile's end too: 0, unless the entry of A is not finite.  Nothing reads
+                // these sums here, but the tiles begin again below, and an earlier one has rows there)
+                if (tile == args.b.shape.n_tiles - 1)
+                    for (int i = lane; i < T; i += kWave) reinterpret_cast<Cell *>(strip)[i] = zero;
+            }
             owner = owner + 1 < nw ? owner + 1 : 0;
         }
     }

@@ -197,6 +197,34 @@ def test_refusals_and_small_scratch(spd):
     h.close()
 
 
+@pytest.mark.parametrize("metric", ["inner_product", "cosine", "kl_divergence"])
+def test_a_value_that_is_not_finite_stays_in_its_row(spd, metric):
+    """Row 7 of A, shared by a workgroup's wavefronts, meets a dense column of B with an infinity: what it leaves behind the
+    last tile's end must not reach the distances of the rows that the same wavefronts take next."""
+    rng = np.random.default_rng(77)
+    cols, m, n = 3_001, 520, 21_001                    # 18 tiles in 8 groups, 32 slices of A's rows
+
+    def matrix(rows, lengths):
+        c = [np.unique(np.concatenate([[2], rng.integers(0, cols, size=lengths[r % len(lengths)])])) for r in range(rows)]
+        return {"n_rows": rows, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum([len(x) for x in c])]).astype(np.int64),
+                "indices": np.concatenate(c).astype(np.int32), "values": (rng.integers(1, 9, size=sum(map(len, c))) / 8.0).astype(np.float32)}
+
+    A, B = matrix(m, (40,) * 7 + (1_200,) + (40,) * 512), matrix(n, (31, 29, 37, 40))
+    plan = spd.testing.host_list_plan(m, int(A["indptr"][-1]), n, int(B["indptr"][-1]), cols, metric, match_lists=2)
+    assert plan["groups"] < plan["tiles"] and n % plan["tile_rows"] != 0
+    bad = dict(A, values=A["values"].copy())
+    bad["values"][A["indptr"][7] + int(np.searchsorted(A["indices"][A["indptr"][7]:A["indptr"][8]], 2))] = np.inf
+    h = _lists(spd)
+    dB = spd.DeviceCsr.from_host(B)
+    want, got = (_np(h.pairwise(spd.DeviceCsr.from_host(M), dB, metric)) for M in (A, bad))
+    others = np.arange(m) != 7
+    assert np.array_equal(got[others], want[others])
+    wi, wd = h.knn(spd.DeviceCsr.from_host(A), dB, metric, 9)
+    gi, gd = h.knn(spd.DeviceCsr.from_host(bad), dB, metric, 9)
+    assert np.array_equal(_np(gi)[others], _np(wi)[others]) and np.array_equal(_np(gd)[others], _np(wd)[others])
+    h.close()
+
+
 @pytest.fixture()
 def scarce(spd):
     """Operands whose lists (a word per tile and column) take more memory than the device has left, and whose scan takes
