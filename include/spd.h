@@ -320,7 +320,8 @@ spd_status spd_set_option(spd_handle *handle, const char *name, int64_t value);
 /* Kernel timings of the last spd_pairwise / spd_knn call made with option "profile" = 1.
  * One record per launch, in launch order.  Waits for the call's kernels to finish. */
 typedef struct {
-    char name[24];        /* "pack_b", "lists_b", "scan", "finalize", "knn_merge"        */
+    char name[24];        /* "pack_b", "scan", "finalize", "knn_merge"; with the column lists "norms_b",
+                                "lists_b", "norms_a", "knn_begin", "scan", "knn_merge"              */
     int32_t rows_per_group; /* scan: R, the rows of A staged together; else 0            */
     int32_t staging_kind; /* scan: 1 dense strip, 2 column-slot strip, 3 hash, 4 Bloom, 5 bitmap,
                                 6 column lists ("match_lists"); else 0 */

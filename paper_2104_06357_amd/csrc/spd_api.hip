@@ -663,6 +663,20 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     return match_pays(h, A, B, op, s, swapped, knn);
 }
 
+// The norms and the lists of B's rows.
+spd_status stage_lists(spd_handle *h, const spd_csr *B, const MatchB &mb, int op, int metric, const MetricInfo &mi, const OpParams &q) {
+    LaunchTimer norms(h, "norms_b", 0, 0, 0, 0, 0, 0);
+    hipError_t e = launch_match_norms(h->stream, B->indptr, B->values, B->n_rows, B->nnz, metric, mi.transform, mi.norm, q.p, q.k, mb.norms);
+    if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
+    norms.done();
+    LaunchTimer lists(h, "lists_b", 0, 0, 0, 0, 0, mb.shape.n_tiles);
+    e = launch_match_build(h->stream, B->indptr, B->indices, B->values, B->n_rows, B->nnz, (uint32_t)B->n_cols, mb,
+                           match_cell_bytes(op), mi.transform);
+    if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
+    lists.done();
+    return SPD_OK;
+}
+
 spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, int op, int knn_k, const OpParams &q,
                      const MetricInfo &mi, const MatchShape &s, const MatchGrid &g, const MatchScratch &L, const int64_t *a_ip,
                      const int64_t *b_ip, size_t ip_bytes, float *out, int64_t *out_idx, float *out_dist, const spd_index *index) {
@@ -680,15 +694,16 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     hipError_t e;
     MatchB mb = index ? index->match : match_b_at(s, L.b, ws);
     if (!index) {
-        LaunchTimer lt(h, "lists_b", 0, 0, 0, 0, 0, s.n_tiles);
-        e = launch_match_build(h->stream, B->indptr, B->indices, B->values, n, B->nnz, (uint32_t)B->n_cols, mb,
-                               match_cell_bytes(op), metric, mi.transform, mi.norm, q.p);
-        if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
-        lt.done();
+        const spd_status st_b = stage_lists(h, B, mb, op, metric, mi, q);
+        if (st_b != SPD_OK) return st_b;
     }
     double *norms_a = reinterpret_cast<double *>(ws + L.norms_a);
-    e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, metric, mi.transform, mi.norm, q.p, q.k, norms_a);
-    if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
+    {
+        LaunchTimer lt(h, "norms_a", 0, 0, 0, 0, 0, 0);
+        e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, metric, mi.transform, mi.norm, q.p, q.k, norms_a);
+        if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
+        lt.done();
+    }
     // A's rows, longest first (to within an eighth of their length): a counting sort into the pinned buffer
     int64_t shared = 0;
     st = ensure_pinned(h, align256(ip_bytes) + (size_t)m * sizeof(MatchRow));
@@ -734,9 +749,11 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     a.knn_part = reinterpret_cast<KnnEntry *>(ws + L.part);
     a.knn_tau = reinterpret_cast<unsigned long long *>(ws + L.tau);
     if (knn_k > 0) {
+        LaunchTimer lt(h, "knn_begin", 0, 0, 0, 0, m, 0);
         e = launch_match_knn_begin(h->stream, a.knn_tau, reinterpret_cast<int64_t *>(ws + L.row_off),
                                    reinterpret_cast<int32_t *>(ws + L.row_lists), a.knn_part, m, g.groups, knn_k);
         if (e != hipSuccess) return hip_fail(h, e, "k-NN start kernel");
+        lt.done();
     }
     {
         LaunchTimer lt(h, "scan", 1, kMatchStagingKind, s.waves * kWave, s.lds_bytes, m, (int64_t)g.groups * g.slices);
@@ -1441,9 +1458,8 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         if (hipMalloc(&ix->match_dev, lists.end) == hipSuccess) {
             ix->match = match_b_at(shape, lists, reinterpret_cast<unsigned char *>(ix->match_dev));
             ix->match_op = op;
-            e = launch_match_build(h->stream, Index->indptr, Index->indices, Index->values, n, Index->nnz, (uint32_t)Index->n_cols,
-                                   ix->match, match_cell_bytes(op), run_as, mi.transform, mi.norm, q.p);
-            if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
+            st = stage_lists(h, Index, ix->match, op, run_as, mi, q);
+            if (st != SPD_OK) return st;
         } else {                         // (no memory left for the lists: the packed copy serves every call)
             ix->match_dev = nullptr;
             (void)hipGetLastError();

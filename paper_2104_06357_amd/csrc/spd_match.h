@@ -85,8 +85,7 @@ SPD_HD constexpr bool match_serves(int op) {
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
                               int metric, int transform, int norm, float p, double k, double *norms);
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
-                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int metric,
-                              int transform, int norm, float p);
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int transform);
 // k-NN: the rows' bounds, and where each row's candidate lists lie.
 hipError_t launch_match_knn_begin(hipStream_t st, unsigned long long *tau, int64_t *row_off, int32_t *row_lists, KnnEntry *part,
                                   int64_t m, int lists, int k);

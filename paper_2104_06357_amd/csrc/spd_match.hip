@@ -325,11 +325,8 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
 }
 
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
-                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int metric,
-                              int transform, int norm, float p) {
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int transform) {
     if (n_rows <= 0) return hipSuccess;
-    hipError_t e = launch_match_norms(st, indptr, values, n_rows, nnz, metric, transform, norm, p, (double)k, b.norms);
-    if (e != hipSuccess) return e;
     // some 2,048 workgroups (a run of blocks looks its rows' first entries up once)
     const MatchShape &s = b.shape;
     const uint32_t per_wg = std::max(1u, (uint32_t)((uint64_t)s.blocks * (uint64_t)s.n_tiles / 2048u));

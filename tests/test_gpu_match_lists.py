@@ -197,6 +197,28 @@ def test_refusals_and_small_scratch(spd):
     h.close()
 
 
+def test_the_profile_has_a_record_for_every_launch(spd):
+    A, B = synth.workload(0)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = _lists(spd, profile=1)
+
+    def names(call):
+        call()
+        records = h.profile_read()
+        assert all(r["ms"] > 0.0 for r in records)
+        return [r["name"] for r in records]
+
+    build = ["norms_b", "lists_b"]
+    assert names(lambda: h.pairwise(dA, dB, "l1")) == build + ["norms_a", "scan"]
+    assert names(lambda: h.knn(dA, dB, "l1", 5)) == build + ["norms_a", "knn_begin", "scan", "knn_merge"]
+    ix = h.index_create(dB, "l1")
+    assert [r["name"] for r in h.profile_read()] == ["pack_b"] + build
+    assert names(lambda: ix.pairwise(dA)) == ["norms_a", "scan"]
+    assert names(lambda: ix.knn(dA, 5)) == ["norms_a", "knn_begin", "scan", "knn_merge"]
+    ix.close()
+    h.close()
+
+
 @pytest.mark.parametrize("metric", ["inner_product", "cosine", "kl_divergence"])
 def test_a_value_that_is_not_finite_stays_in_its_row(spd, metric):
     """Row 7 of A, shared by a workgroup's wavefronts, meets a dense column of B with an infinity: what it leaves behind the
