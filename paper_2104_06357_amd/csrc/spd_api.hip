@@ -553,6 +553,10 @@ MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int64_t m, int
     g.shared_len = std::max<int64_t>(256, share / 3);
     return g;
 }
+// (tile, row)s that the wavefronts of a workgroup share out among themselves, numbered in 32 bits.
+int64_t match_items(const MatchShape &s, const MatchGrid &g, int64_t m) {
+    return ((m + g.slices - 1) / g.slices) * ((s.n_tiles + g.groups - 1) / g.groups);
+}
 struct MatchScratch { MatchLayout b; size_t rows, norms_a, tau, part, row_off, row_lists, end; };
 MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int64_t m, int64_t n, int64_t nnz_b, int knn_k, bool with_b) {
     MatchScratch L{};
@@ -629,7 +633,7 @@ bool match_pays(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op,
     const double list = nnz_b / n / (double)A->n_cols * (double)s.tile_rows;          // entries, on the mean
     const double entry = 30.0 + (wide ? 80.0 : 40.0) * std::min(1.0, list) + (wide ? 60.0 : 40.0) * list / 64.0;
     const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn);
-    const double items = std::ceil(std::ceil(m / g.slices) * std::ceil((double)s.n_tiles / g.groups) / s.waves);     // of a wavefront
+    const double items = std::ceil((double)match_items(s, g, A->n_rows) / s.waves);     // of a wavefront
     const double idle = items * s.waves * (double)h->opt.n_cus / (m * s.n_tiles);
     const double lists = idle * s.n_tiles * (entry * nnz_a + (knn ? 2000.0 * m : 0.0)) + m * n;
     double visit = 0.6;
@@ -649,6 +653,7 @@ bool match_pays(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op,
 bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn) {
     MatchShape s;
     if (semiring || A->n_rows <= 0 || !match_possible(h, B, op, s)) return false;
+    if (match_items(s, match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
     if (h->match_lists == 2) return true;
     if (!match_suits(h, B, op, s)) return false;
     // The build takes some 17 ps an entry of B, and a call's other launches have a price too.  Both sides measured, staged /

@@ -259,6 +259,18 @@ def test_column_lists_against_the_scan_that_would_run():
     assert _wanted(766, 1_468, 3_599, 35, 20_000, "minkowski", match_lists=2)
 
 
+def test_column_lists_only_where_a_workgroup_can_number_its_work():
+    """A workgroup's (tile, row)s are numbered in 32 bits: 6.25 million rows of a slice in 2,056 tiles are more."""
+    def plan(m):
+        return spd.testing.host_list_plan(m, 2 * m, 20_000_000, 200_000_000, 100_000, "l1", k_neighbors=4, match_lists=2)
+
+    for m in (10_000, 1_000_000, 16_000_000, 200_000_000, 2_000_000_000):
+        p = plan(m)
+        items = -(-m // p["slices"]) * -(-p["tiles"] // p["groups"])
+        assert bool(p["wanted"]) == (items < 1 << 30), p
+    assert plan(16_000_000)["wanted"] and not plan(200_000_000)["wanted"]
+
+
 def test_an_index_keeps_lists_that_calls_may_want_within_the_stated_memory():
     def kept(n, mean, cols, metric, **more):
         plan = spd.testing.host_list_plan(1_000, 30_000, n, int(n * mean), cols, metric, with_index=True, **more)
