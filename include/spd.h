@@ -312,7 +312,8 @@ spd_status spd_csr_validate(spd_handle *handle, const spd_csr *M, int require_no
  *                 the product has it.  A call whose lists the caller's scratch does not hold, or the device
  *                 has no memory for, runs by the staged scan; the handle asks the device for that much again
  *                 only after the option is set again.  The sums' order differs between the two ways.
- *   "check_plan"  1: verify every index the kernels will form from the plan before launching
+ *   "check_plan"  1: verify every index the kernels will form from the plan before the scan is launched (with
+ *                 the column lists: the cut of B into tiles and blocks, the grid, A's rows)
  *   "profile"     1: bracket every kernel launch with HIP events (see spd_profile_read)
  * Unknown names or values out of range return SPD_ERR_UNSUPPORTED. */
 spd_status spd_set_option(spd_handle *handle, const char *name, int64_t value);

@@ -40,6 +40,7 @@ typedef struct {
     int32_t wanted;
     int32_t tiles, tile_rows;       /* of B */
     int32_t slices, groups;         /* workgroups: slices of A's rows times groups of tiles */
+    int32_t consistent;             /* what option "check_plan" finds of the cut */
     int64_t scratch_bytes;
     int64_t index_bytes;            /* what an index keeps of lists; 0: none */
 } spd_list_plan;

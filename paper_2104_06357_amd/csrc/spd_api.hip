@@ -573,6 +573,38 @@ MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int64_t 
     L.end = cv.off;
     return L;
 }
+// Option "check_plan" for the column lists: what the kernels' indexes and LDS rest on.  Empty if consistent.
+std::string match_check(const PlanOptions &opt, const MatchShape &s, const MatchGrid &g, int op, int64_t m, int64_t n, int64_t n_cols,
+                        int64_t nnz_b) {
+    const int64_t T = s.tile_rows, tiles = s.n_tiles, blocks = s.blocks, cell = match_cell_bytes(op);
+    if (T < kWave || T % kWave != 0 || tiles * T < n || (tiles - 1) * T >= n) return "tiles do not cover B";
+    if (s.waves != match_waves((size_t)cell) || (int64_t)s.lds_bytes != s.waves * (T + 1) * cell ||
+        (int64_t)s.lds_bytes + kMatchStaticLds > opt.lds_budget) return "strips over the LDS";
+    if (s.block_shift < 2 || s.block_shift > 30 || (blocks << s.block_shift) < n_cols || ((blocks - 1) << s.block_shift) >= n_cols)
+        return "column blocks";
+    if (s.ptr_stride < n_cols + blocks) return "list bounds";
+    if (s.dense_per_block < 1 || s.dense_per_block > (int32_t)kBuildDense || s.dense_from < 1 ||
+        s.tile_extra != blocks * s.dense_per_block * (T / 2)) return "dense columns";
+    if (s.list_entries(nnz_b) >= (int64_t)1 << 29) return "list positions";
+    const int64_t build = (int64_t)s.stage * 8 + ((int64_t)4 << s.block_shift) + 12 * T;
+    if ((int64_t)s.build_lds_bytes != build || build + 1024 > opt.lds_budget) return "build over the LDS";
+    if (g.slices < 1 || g.groups < 1 || g.groups > tiles || (g.by_xcd && g.groups < tiles && g.groups % 8 != 0)) return "grid";
+    if (match_items(s, g, m) >= (int64_t)1 << 30) return "(tile, row)s of a workgroup";
+    return std::string();
+}
+// ... and A's rows as the kernel takes them: every row once, where the row pointers say, the first ones shared.
+std::string match_check_rows(const MatchRow *rows, int64_t m, int64_t shared, int64_t shared_len, const int64_t *a_ip) {
+    std::vector<bool> seen((size_t)m, false);
+    int64_t longer = 0;
+    for (int64_t i = 0; i < m; ++i) {
+        const MatchRow &r = rows[i];
+        if (r.row < 0 || r.row >= m || seen[(size_t)r.row]) return "A's rows are not a permutation";
+        seen[(size_t)r.row] = true;
+        if (r.start != a_ip[r.row] || r.start + r.len != a_ip[r.row + 1]) return "A row range";
+        longer += r.len > shared_len ? 1 : 0;
+    }
+    return shared == longer ? std::string() : "shared rows";
+}
 // The knobs that pick the staged scan's paths: a caller that turns one wants that kernel.
 bool scan_knobs_untouched(const spd_handle *h) {
     const PlanOptions d;
@@ -695,6 +727,11 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     spd_status st = index ? SPD_OK : refused("B", b_ip, n, b_staged);
     if (st == SPD_OK) st = refused("A", a_ip, m, !b_staged);
     if (st != SPD_OK) return st;
+    if (h->check_plan) {
+        std::string why = match_check(h->opt, s, g, op, m, n, A->n_cols, B->nnz);
+        if (why.empty() && L.end > h->ws_bytes) why = "scratch";
+        if (!why.empty()) return fail(h, SPD_ERR_UNSUPPORTED, "internal plan check failed: " + why);
+    }
     unsigned char *ws = reinterpret_cast<unsigned char *>(h->ws);         // (run() has seen to its size)
     hipError_t e;
     MatchB mb = index ? index->match : match_b_at(s, L.b, ws);
@@ -729,6 +766,10 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
             shared += len > g.shared_len ? 1 : 0;
             rows[at[bucket(len)]++] = MatchRow{a_ip[i], (int32_t)len, (int32_t)i};
         }
+    }
+    if (h->check_plan) {
+        const std::string why = match_check_rows(rows, m, shared, g.shared_len, a_ip);
+        if (!why.empty()) return fail(h, SPD_ERR_UNSUPPORTED, "internal plan check failed: " + why);
     }
     e = hipMemcpyAsync(ws + L.rows, rows, (size_t)m * sizeof(MatchRow), hipMemcpyHostToDevice, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "upload of A's rows");
@@ -1653,6 +1694,7 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     MatchShape kept;
     MatchLayout L;
     out->index_bytes = index_keeps_lists(&h, &B, op, kept, L) ? (int64_t)L.end : 0;
+    out->consistent = match_check(h.opt, s, g, op, a_rows, b_rows, n_cols, b_nnz).empty();
     out->scratch_bytes = (int64_t)layout_match_call(s, g, a_rows, b_rows, b_nnz, k_neighbors, !with_index).end;
     return SPD_OK;
 }

@@ -68,6 +68,7 @@ struct MatchArgs {
     unsigned long long *knn_tau;  // per row: the tightest k-th (distance, index) key of any group
 };
 
+constexpr uint32_t kBuildDense = 32;            // dense columns of a block at most
 constexpr int64_t kMatchStaticLds = 256;        // upper bound of the kernel's static __shared__ use
 constexpr int kMatchStagingKind = 6;            // how spd_profile_read names this kernel's staging
 constexpr int64_t kMatchL2Bytes = 4 << 20;      // of one XCD

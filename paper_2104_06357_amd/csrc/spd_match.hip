@@ -54,7 +54,6 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
 // depends on it, because a row of B appears in a list at most once.
 // ------------------------------------------------------------------------------------
 constexpr int kBuildThreads = 1024;
-constexpr uint32_t kBuildDense = 32;            // dense columns of a block at most
 
 template <int G>
 __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,

@@ -39,7 +39,7 @@ def host_plan_summary(a_indptr, b_indptr, n_cols, metric, k_neighbors=0, **optio
 
 
 class _ListPlan(ctypes.Structure):
-    _fields_ = [(name, ctypes.c_int32) for name in ("wanted", "tiles", "tile_rows", "slices", "groups")] + [
+    _fields_ = [(name, ctypes.c_int32) for name in ("wanted", "tiles", "tile_rows", "slices", "groups", "consistent")] + [
         (name, ctypes.c_int64) for name in ("scratch_bytes", "index_bytes")]
 
 

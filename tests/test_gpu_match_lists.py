@@ -44,6 +44,7 @@ def _matrix(rng, rows, cols, lengths):
 def _lists(spd, **options):
     h = spd.Handle()
     h.set_option("match_lists", 2)
+    h.set_option("check_plan", 1)
     for name, value in options.items():
         h.set_option(name, value)
     return h

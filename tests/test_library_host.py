@@ -271,6 +271,21 @@ def test_column_lists_only_where_a_workgroup_can_number_its_work():
     assert plan(16_000_000)["wanted"] and not plan(200_000_000)["wanted"]
 
 
+def test_the_cut_of_the_column_lists_is_consistent():
+    """What check_plan verifies, over random sizes, with the lists wanted wherever a product has them."""
+    rng = np.random.default_rng(23)
+    wanted = 0
+    for _ in range(4_000):
+        m, n, cols = (int(2 ** rng.uniform(0, e)) for e in (24, 24, 31))
+        mean_a, mean_b = (min(2 ** rng.uniform(-2, 12), cols) for _ in range(2))
+        metric = ALL_METRICS[rng.integers(len(ALL_METRICS))]
+        plan = spd.testing.host_list_plan(m, int(m * mean_a), n, int(n * mean_b), cols, metric, k_neighbors=int(rng.integers(0, 2)) * min(n, 64),
+                                          match_lists=2, lds_budget=int(rng.choice([8192, 20000, 65536, 163840])))
+        wanted += plan["wanted"]
+        assert plan["consistent"] or not plan["wanted"], (m, n, cols, metric, plan)
+    assert wanted > 1_000
+
+
 def test_an_index_keeps_lists_that_calls_may_want_within_the_stated_memory():
     def kept(n, mean, cols, metric, **more):
         plan = spd.testing.host_list_plan(1_000, 30_000, n, int(n * mean), cols, metric, with_index=True, **more)
