@@ -5,7 +5,8 @@
  * The operation is the one stated in Section 2 of "GPU Semiring Primitives for Sparse
  * Neighborhood Methods": A is m x k, B is n x k, both in CSR with ascending columns
  * inside each row, and the result is the dense m x n matrix C with C[i][j] = d(A_i, B_j),
- * produced without transposing or copying the inputs in full.  Each distance of Table 1
+ * with scratch proportional to the inputs: B is copied once per call, packed for the staged scan or
+ * listed by column tile by tile (option "match_lists").  Each distance of Table 1
  * is a product()/sum() pair; the distances of the dot-product family are finished by
  * an expansion function over row norms (Section 3.4), the others apply their product over
  * the union of the non-zero columns of the two rows (Section 2.2, Eq. 2).  k-NN follows
@@ -25,6 +26,9 @@
  *    stream at all, so the planning of one call runs while the kernels of the one before it do.
  *    A host copy that differs from the device array gives wrong results (its last entry is
  *    checked against nnz, and no access leaves the arrays).
+ *  - Sums are carried in fp64 and rounded once.  The order of a pair's terms, and with it the last place of
+ *    its distance, depends on the way the call is computed (option "match_lists") and on how it is cut, that is
+ *    on the sizes of both operands, the options and the scratch; equal calls give equal bits.
  *  - Scratch memory comes from the handle's own grow-only allocation, or from the caller
  *    through spd_set_workspace().
  *  - A handle serves one call at a time (calls on one handle from several threads must be
@@ -123,8 +127,10 @@ spd_status spd_pairwise(spd_handle *handle, const spd_csr *A, const spd_csr *B, 
                         float p, float *out);
 
 /* spd_pairwise for callers that cannot allocate device memory: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  Same arguments and same result as spd_pairwise,
- * but the call allocates nothing (no hipMalloc, hipHostMalloc, hipFree, stream or event creation):
+ * serving loops, harnesses that forbid hipMalloc.  Same arguments as spd_pairwise, and the same result
+ * bit for bit where both take the same way; the array holds the lists (option "match_lists") of a smaller B
+ * than it holds the packed copy of, and from there on the call runs by the staged scan, whose results may differ
+ * in the last place.  The call allocates nothing (no hipMalloc, hipHostMalloc, hipFree, stream or event creation):
  * its scratch is a static array of SPD_STATIC_SCRATCH_BYTES bytes that every GPU the library runs
  * on holds from the library's first use there until the process ends, and its plans pass through
  * the SPD_STATIC_STAGING_BYTES bytes of pinned memory every handle holds from spd_create.
@@ -134,7 +140,7 @@ spd_status spd_pairwise(spd_handle *handle, const spd_csr *A, const spd_csr *B, 
  *    (B up to some 3.5 million stored entries fits; spd_last_error gives the bytes needed).
  *  - Everything runs on the handle's stream (no internal side streams), launch timing is off.
  *  - All calls on one GPU, from any handle, share that GPU's array and leave their data in it:
- *    no kernel reads scratch it has not written in the same call, so nothing needs clearing, but
+ *    no result depends on scratch that was not written in the same call, so nothing needs clearing, but
  *    two calls that overlap in time on one GPU (two handles, two streams) race.  Calls on one
  *    stream, or ordered by events, are safe. */
 #define SPD_STATIC_SCRATCH_BYTES (32u << 20)
@@ -156,11 +162,14 @@ spd_status spd_knn(spd_handle *handle, const spd_csr *Q, const spd_csr *Index, s
  * memory the index owns (about 8 bytes per stored entry and 40 per row, and where calls may want the
  * column lists (option "match_lists" as it stands at creation) and they take no more than that, up to 20
  * bytes per stored entry, 16 per row and 1 MiB more); spd_index_pairwise /
- * spd_index_knn then return exactly what spd_pairwise / spd_knn return for the same operands.
+ * spd_index_knn then return what spd_pairwise / spd_knn return for the same operands: bit for bit where
+ * both take the same way (k-NN calls do wherever the index keeps the lists; a pairwise call without an index may
+ * exchange its operands' roles, and with them the way it takes), and else to the last place.
  * The index keeps the pointers of `Index`, not a copy: the three arrays must stay valid and
  * unchanged until spd_index_destroy.  The work is enqueued on the creating handle's stream; use
  * the index with that handle (or, after synchronising its stream, with another handle on the same
- * device).  The planner options "split_len" and "window" are read at creation.
+ * device).  The planner options "split_len" and "window" are read at creation, and the lists are kept
+ * for the "lds_budget" and "match_lists" of that time: calls under others run by the staged scan.
  * spd_index_destroy waits for the handle's stream before it frees the memory. */
 spd_status spd_index_create(spd_handle *handle, const spd_csr *Index, spd_metric metric, float p,
                             spd_index **index);

@@ -198,6 +198,66 @@ def test_refusals_and_small_scratch(spd):
     h.close()
 
 
+def test_scratch_for_the_scan_alone(spd):
+    """Scratch that holds what the staged scan needs and not the lists, lent by the caller or the static array: the same bits as
+    the staged scan, and two roundings of reordered fp64 sums from the lists."""
+    import torch
+    A, B = synth.workload(1, scale=7.5)
+    A = synth.slice_rows(A, 0, 500)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    lists, staged = _lists(spd, profile=1), spd.Handle()
+    staged.set_option("match_lists", 0)
+    kinds = lambda h: {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"}
+    for metric in ("cosine", "jensen_shannon"):
+        sizes = (A["n_rows"], int(A["indptr"][-1]), B["n_rows"], int(B["indptr"][-1]), B["n_cols"], metric)
+        assert spd.testing.host_list_plan(*sizes, match_lists=2)["scratch_bytes"] > 32 << 20
+        assert spd.testing.host_list_plan(*sizes)["wanted"]                 # (by default too)
+        want, scan = lists.pairwise(dA, dB, metric), staged.pairwise(dA, dB, metric)
+        assert kinds(lists) == {6}
+        assert torch.allclose(want, scan, rtol=2.5e-7, atol=1e-7)
+        got = torch.empty_like(want)
+        lists.pairwise_static(dA, dB, metric, got)
+        assert torch.equal(got, scan)
+        lists.set_workspace(torch.empty(32 << 20, dtype=torch.uint8, device="cuda"))
+        assert torch.equal(lists.pairwise(dA, dB, metric), scan) and 6 not in kinds(lists)
+        lists.set_workspace(None)
+    lists.close()
+    staged.close()
+
+
+def test_an_index_under_other_options_and_on_other_streams(spd):
+    """The lists of an index serve the options it was created under; a second handle on a stream of its own reads the same ones."""
+    import torch
+    A, B = synth.workload(1, scale=0.3)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = _lists(spd, profile=1)
+    kinds = lambda handle: {r["staging_kind"] for r in handle.profile_read() if r["name"] == "scan"}
+    want = oracle.pairwise(A, B, "canberra")
+    plain = h.pairwise(dA, dB, "canberra")
+    ix = h.index_create(dB, "canberra")
+    assert torch.equal(ix.pairwise(dA), plain) and kinds(h) == {6}
+    for name, value, before in (("lds_budget", 98304, 163840), ("match_lists", 0, 2)):
+        h.set_option(name, value)
+        assert_distances_close(_np(ix.pairwise(dA)), want, name)
+        assert 6 not in kinds(h)
+        h.set_option(name, before)
+    assert torch.equal(ix.pairwise(dA), plain) and kinds(h) == {6}
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        other = _lists(spd, profile=1)
+        view = type(ix)(other, ix._ptr, dB)
+        for _ in range(3):                                      # both at once
+            theirs, ours = view.pairwise(dA), ix.pairwise(dA)
+            torch.cuda.synchronize()
+            assert torch.equal(theirs, plain) and torch.equal(ours, plain)
+        assert kinds(other) == {6}
+        view._ptr = None                                        # (ix owns it)
+        other.close()
+    ix.close()
+    h.close()
+
+
 def test_the_profile_has_a_record_for_every_launch(spd):
     A, B = synth.workload(0)
     dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
