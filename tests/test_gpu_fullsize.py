@@ -49,7 +49,19 @@ def _timed(capsys, label, fn):
     return out
 
 
-def test_config2_bag_of_words_tile(spd, capsys):
+# "match_lists" 1, the default, computes the distances of these shapes by column lists, 0 by the staged scan
+BOTH_WAYS = pytest.mark.parametrize("lists", [1, 0], ids=["column lists", "staged scan"])
+COLUMN_LISTS = 6
+
+
+def _way(h, lists):
+    """The last call of a handle with option "profile" took the way that was asked for."""
+    kinds = {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"}
+    assert kinds == {COLUMN_LISTS} if lists else COLUMN_LISTS not in kinds, kinds
+
+
+@BOTH_WAYS
+def test_config2_bag_of_words_tile(spd, capsys, lists):
     """1,024 queries (one output tile of 1.2 GB) against the 300,000-row index."""
     import torch
     Q, I = synth.workload(2)
@@ -60,11 +72,14 @@ def test_config2_bag_of_words_tile(spd, capsys):
     dQ, dI = spd.DeviceCsr.from_host(tile), spd.DeviceCsr.from_host(I)
     h = spd.Handle()
     h.set_option("check_plan", 1)
+    h.set_option("profile", 1)
+    h.set_option("match_lists", lists)
     out = torch.empty((tile["n_rows"], I["n_rows"]), dtype=torch.float32, device="cuda")
     ra = _extremes_and_sample(tile, 64, rng)
     rb = _extremes_and_sample(I, 2048, rng)
     for metric in ("cosine", "inner_product", "hellinger"):
         _timed(capsys, "config2 " + metric, lambda: h.pairwise(dQ, dI, metric, out=out))
+        _way(h, lists)
         want = oracle.pairwise(tile, I, ORACLE_NAME[metric], rows_a=ra, rows_b=rb)
         assert_distances_close(_gather(out, ra, rb), want, "config2 " + metric)
         progress(capsys, "config2 %s checked against the oracle" % metric)
@@ -74,19 +89,22 @@ def test_config2_bag_of_words_tile(spd, capsys):
     assert float((cos + ip - 1.0).abs().max()) < 2e-6
     # correlation (means over all 102,660 columns) on the same tile
     _timed(capsys, "config2 correlation", lambda: h.pairwise(dQ, dI, "correlation", out=out))
+    _way(h, lists)
     want = oracle.pairwise(tile, I, "correlation", rows_a=ra, rows_b=rb)
     assert_distances_close(_gather(out, ra, rb), want, "config2 correlation")
     del out
     # the fused top-32 of the same tile: full distance rows of a sample of the queries
     rq = _extremes_and_sample(tile, 12, rng)
     idx, dist = _timed(capsys, "config2 knn cosine", lambda: h.knn(dQ, dI, "cosine", 32))
+    _way(h, lists)
     rows = oracle.pairwise(tile, I, "cosine", rows_a=rq)
     assert_knn_matches(idx.cpu().numpy()[rq], dist.cpu().numpy()[rq], rows, 32, "cosine", "config2 knn cosine")
     progress(capsys, "config2 knn cosine checked against the oracle")
     h.close()
 
 
-def test_config3_count_matrix_tile(spd, capsys):
+@BOTH_WAYS
+def test_config3_count_matrix_tile(spd, capsys, lists):
     """A 4,096-row query tile of the 65,536-row self-join, union-family metrics."""
     import torch
     M, _ = synth.workload(3)
@@ -100,6 +118,8 @@ def test_config3_count_matrix_tile(spd, capsys):
     dQ, dM = spd.DeviceCsr.from_host(tile), spd.DeviceCsr.from_host(M)
     h = spd.Handle()
     h.set_option("check_plan", 1)
+    h.set_option("profile", 1)
+    h.set_option("match_lists", lists)
     out = torch.empty((tile["n_rows"], M["n_rows"]), dtype=torch.float32, device="cuda")
     heavy_in_tile = np.nonzero(np.isin(tile_rows, heavy))[0]
     ra = _extremes_and_sample(tile, 64, rng, extra=heavy_in_tile)
@@ -107,6 +127,7 @@ def test_config3_count_matrix_tile(spd, capsys):
     rb = _extremes_and_sample(M, 2048, rng, extra=list(heavy) + list(tile_rows[ra]))
     for metric in ("kl_divergence", "jensen_shannon", "canberra", "l1"):
         _timed(capsys, "config3 " + metric, lambda: h.pairwise(dQ, dM, metric, out=out))
+        _way(h, lists)
         want = oracle.pairwise(tile, M, ORACLE_NAME[metric], rows_a=ra, rows_b=rb)
         assert_distances_close(_gather(out, ra, rb), want, "config3 " + metric)
         progress(capsys, "config3 %s checked against the oracle" % metric)
@@ -114,6 +135,7 @@ def test_config3_count_matrix_tile(spd, capsys):
     rq = _extremes_and_sample(tile, 8, rng, extra=heavy_in_tile[:2])
     for metric in ("l1", "jensen_shannon"):
         idx, dist = _timed(capsys, "config3 knn " + metric, lambda: h.knn(dQ, dM, metric, 32))
+        _way(h, lists)
         idx, dist = idx.cpu().numpy(), dist.cpu().numpy()
         rows = oracle.pairwise(tile, M, ORACLE_NAME[metric], rows_a=rq)
         assert_knn_matches(idx[rq], dist[rq], rows, 32, metric, "config3 knn " + metric)
@@ -209,13 +231,15 @@ def test_shape6_ratings_like(spd, capsys):
     # 194,000 columns: the bitmap of the columns leaves room for the 24,000-entry row as a whole
     assert all(c["kind"] == 5 for c in plan["classes"]) and plan["spilled_rows"] == 0
     _knn_tile_against_oracle(spd, capsys, "shape6", M, tile_rows, ("cosine", "l1"), 32, 8)
+    _knn_tile_against_oracle(spd, capsys, "shape6 (staged scan)", M, tile_rows, ("cosine",), 32, 8, options=(("match_lists", 0),))
     # behind a hash table that row is cut into slices
     hashed = spd.testing.host_plan_summary(tile_ip, M["indptr"], M["n_cols"], "l1", k_neighbors=32, force_kind=3)
     assert hashed["spilled_rows"] >= 1
     _knn_tile_against_oracle(spd, capsys, "shape6 (hash staging)", M, tile_rows, ("l1",), 32, 8, options=(("force_kind", 3),))
 
 
-def test_output_of_more_than_2_to_32_distances(spd, capsys):
+@BOTH_WAYS
+def test_output_of_more_than_2_to_32_distances(spd, capsys, lists):
     """70,000 x 70,000 rows of the config-1 kind: 4.9e9 distances (19.6 GB), so every product
     of a row number and a row length in the kernels' addressing has to be formed in 64 bits."""
     import torch
@@ -224,6 +248,8 @@ def test_output_of_more_than_2_to_32_distances(spd, capsys):
     progress(capsys, "70,000-row pair generated")
     dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
     h = spd.Handle()
+    h.set_option("profile", 1)
+    h.set_option("match_lists", lists)
     out = torch.empty((A["n_rows"], B["n_rows"]), dtype=torch.float32, device="cuda")
     rng = np.random.default_rng(7)
     ra = _extremes_and_sample(A, 48, rng, extra=(0, A["n_rows"] - 1, 61_357, 65_536))
@@ -231,6 +257,7 @@ def test_output_of_more_than_2_to_32_distances(spd, capsys):
     for metric in ("cosine", "l1"):
         out.fill_(float("nan"))
         _timed(capsys, "70,000 x 70,000 %s" % metric, lambda: h.pairwise(dA, dB, metric, out=out))
+        _way(h, lists)
         want = oracle.pairwise(A, B, ORACLE_NAME[metric], rows_a=ra, rows_b=rb)
         assert_distances_close(_gather(out, ra, rb), want, metric)
         # nothing was left unwritten, nothing was written past the end

@@ -50,11 +50,12 @@ def _lists(spd, **options):
     return h
 
 
-# rows of B: one, around a wavefront, several tiles with a short last one (an 8 KB budget makes a tile of 64
-# rows for one 8-byte sum, 128 for the counts); rows of A: fewer than the wavefronts of a workgroup, and more
+# rows of B: one, around a wavefront, several tiles with a short last one (32 KB of LDS make tiles of 448 rows for a
+# count, 192 for one fp64 sum, 128 for two and 64 for Minkowski's three; 20 KB 256, 128, 64 and 64); rows of A: fewer than
+# the wavefronts of a workgroup, and more
 @pytest.mark.parametrize("metric", SERVED)
 @pytest.mark.parametrize("m,n,cols,budget", [(1, 1, 5, 163840), (3, 63, 70, 163840), (70, 65, 200, 163840), (18, 1300, 300, 163840),
-                                             (5, 129, 140, 32768), (150, 1000, 130, 32768)])
+                                             (5, 129, 140, 32768), (150, 1000, 130, 32768), (17, 257, 90, 20480)])
 def test_edges(spd, metric, m, n, cols, budget):
     rng = np.random.default_rng(m * 1000 + n)
     A = _matrix(rng, m, cols, (3, 64, 65, 1, 130, 0, 17))
@@ -105,6 +106,40 @@ def test_shared_rows_and_many_tiles(spd, metric, m, n, cols, lengths_a, lengths_
     idx, dist = h.knn(dA, dB, metric, 64, p)
     assert_knn_matches(_np(idx), _np(dist), want, 64, metric, metric)
     h.close()
+
+
+@pytest.mark.parametrize("metric", ["cosine", "l1", "hamming", "canberra", "kl_divergence", "jensen_shannon", "minkowski"])
+@pytest.mark.parametrize("mean_a,mean_b", [(600, 2), (400, 60), (2, 900), (30, 30)])
+def test_operands_of_different_laws_and_the_way_they_take(spd, metric, mean_a, mean_b):
+    """Long rows against short ones, either way round, wherever the lists are wanted and where the default puts them."""
+    rng = np.random.default_rng(mean_a)
+    cols, m, n = 5_000, 700, 2_600
+
+    def matrix(rows, mean):
+        c = [np.unique(rng.integers(0, cols, size=int(x))) for x in rng.poisson(mean, size=rows)]
+        return {"n_rows": rows, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum([len(x) for x in c])]).astype(np.int64),
+                "indices": np.concatenate(c).astype(np.int32), "values": (rng.integers(1, 9, size=sum(map(len, c))) / 8.0).astype(np.float32)}
+
+    A, B = matrix(m, mean_a), matrix(n, mean_b)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    p = _p_of(metric)
+    rows = np.unique(rng.integers(0, m, size=40))
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], p, rows_a=rows)
+    lists, default = _lists(spd), spd.Handle()
+    default.set_option("profile", 1)
+    for h in (lists, default):
+        for k in (0, 17):
+            print("laws", metric, mean_a, mean_b, k, flush=True)
+            if k == 0:
+                assert_distances_close(_np(h.pairwise(dA, dB, metric, p))[rows], want, metric)
+            else:
+                idx, dist = h.knn(dA, dB, metric, k, p)
+                assert_knn_matches(_np(idx)[rows], _np(dist)[rows], want, k, metric, metric)
+            if h is default:
+                plan = spd.testing.host_list_plan(m, int(A["indptr"][-1]), n, int(B["indptr"][-1]), cols, metric, p, k_neighbors=k)
+                assert ({r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}) == bool(plan["wanted"])
+    lists.close()
+    default.close()
 
 
 @pytest.mark.parametrize("metric", ["cosine", "jensen_shannon", "jaccard", "minkowski"])
@@ -180,7 +215,7 @@ def test_what_the_staged_scan_refuses_is_refused(spd, entry, fault):
     assert status(2, 0, malformed(), good) != "SPD_OK"
 
 
-def test_refusals_and_small_scratch(spd):
+def test_refusals_and_documented_scratch(spd):
     import torch
     A, B = synth.workload(0)
     h = _lists(spd)

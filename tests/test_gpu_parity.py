@@ -291,9 +291,11 @@ def config1(spd):
 
 @pytest.mark.parametrize("metric", ["l1", "l2_expanded", "cosine", "chebyshev", "minkowski",
                                     "canberra", "jaccard", "correlation", "hamming"])
-def test_config1_sampled_pairs(handle, config1, metric):
+@pytest.mark.parametrize("lists", [1, 0], ids=["column lists", "staged scan"])
+def test_config1_sampled_pairs(handle, config1, metric, lists):
     A, B, dA, dB = config1
-    print("config1 pairwise", metric, flush=True)
+    print("config1 pairwise", metric, lists, flush=True)
+    handle.set_option("match_lists", lists)
     rng = np.random.default_rng(1)
     ra, rb = _sample_rows(A, 64, rng), _sample_rows(B, 2048, rng)
     got = _run_pairwise(handle, dA, dB, metric, _p_of(metric))

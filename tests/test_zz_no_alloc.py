@@ -26,11 +26,13 @@ def _both(spd, h, A, B, metric, p=2.0):
     return got.cpu().numpy(), want.cpu().numpy()
 
 
-def test_two_calls_in_a_row_the_second_smaller(spd):
-    """Config 1 (10,000 x 10,000, three launches), then config 0 (256 x 256) through the same
-    array, which still holds the first call's data: each must equal spd_pairwise."""
+@pytest.mark.parametrize("lists", [1, 0], ids=["column lists", "staged scan"])
+def test_two_calls_in_a_row_the_second_smaller(spd, lists):
+    """Config 1 (10,000 x 10,000: by column lists the default, three launches of the staged scan without), then config 0
+    (256 x 256) through the same array, which still holds the first call's data: each must equal spd_pairwise."""
     h = spd.Handle()
     h.set_option("check_plan", 1)
+    h.set_option("match_lists", lists)
     print("static entry: config 1, l1", flush=True)
     A, B = synth.workload(1)
     got, want = _both(spd, h, A, B, "l1")
