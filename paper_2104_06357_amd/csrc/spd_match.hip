@@ -267,7 +267,9 @@ hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float
     };
     const int64_t mean = nnz / n_rows;
     // (28,301 rows of power-law lengths: the longest, 24,000 entries, takes a wavefront alone 72 us and a workgroup 46;
-    // with many rows the workgroups' own cost counts: 300,000 rows of 230 take 354 us that way and 137 us otherwise)
+    // with many rows the workgroups' own cost counts: 300,000 rows of 230 take 354 us that way and 137 us otherwise.
+    // What a workgroup to the row helps is one long row, which mean and row count only stand for: 65,536 rows of 1,820
+    // take the same either way, and even rows of 230 lose by it, 60,000 of them some 40 us in proportion)
     if (mean >= 128 && n_rows <= 65536) go(std::integral_constant<int, 256>{});
     else if (mean >= 16) go(std::integral_constant<int, 64>{});
     else go(std::integral_constant<int, 4>{});

@@ -1,5 +1,5 @@
 """The prepared index (spd_index_create / spd_index_pairwise / spd_index_knn): the same results as
-spd_pairwise / spd_knn, bit for bit, and parity with the CPU oracle (needs an MI355X)."""
+spd_pairwise / spd_knn, bit for bit on operands that take one way of computing them, and parity with the CPU oracle (needs an MI355X)."""
 import numpy as np
 import pytest
 
