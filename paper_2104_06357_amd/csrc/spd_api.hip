@@ -579,7 +579,7 @@ std::string match_check(const PlanOptions &opt, const MatchShape &s, const Match
     const int64_t T = s.tile_rows, tiles = s.n_tiles, blocks = s.blocks, cell = match_cell_bytes(op);
     if (T < kWave || T % kWave != 0 || tiles * T < n || (tiles - 1) * T >= n) return "tiles do not cover B";
     if (s.waves != match_waves((size_t)cell) || (int64_t)s.lds_bytes != s.waves * (T + 1) * cell ||
-        (int64_t)s.lds_bytes + kMatchStaticLds > opt.lds_budget) return "strips over the LDS";
+        (int64_t)s.lds_bytes + match_static_lds(cell) > opt.lds_budget) return "strips over the LDS";
     if (s.block_shift < 2 || s.block_shift > 30 || (blocks << s.block_shift) < n_cols || ((blocks - 1) << s.block_shift) >= n_cols)
         return "column blocks";
     if (s.ptr_stride < n_cols + blocks) return "list bounds";

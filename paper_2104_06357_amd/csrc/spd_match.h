@@ -6,10 +6,11 @@
 // per tile the entries are listed by column (a transpose of the tile, made on the device in each
 // call).  A wavefront takes one row of A, walks the lists of that row's columns only, and adds
 // product(a, b) to one sum per row of the tile, which lie in its own strip of LDS.  Work is done for
-// the columns that two rows share and for nothing else; a column of A costs one step of 64 lanes per
-// 64 entries of its list.  A strip is private to its wavefront, and a row of B appears at most once in
-// a list, so no two lanes of a step meet in one sum and the sums are formed in the order of A's
-// columns: the results do not depend on the schedule.
+// the columns that two rows share and for nothing else.  Where a pair has one sum the lists are walked
+// in chunks of 16 entries, four chunks of any lists to a step; elsewhere a step is up to 64 entries of one
+// list.  A strip is private to its wavefront, and the sums are formed in the order of A's columns (a row of
+// B appears at most once in a list, and lanes that meet in one sum are served in ascending order, which
+// is that order): the results do not depend on the schedule.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -21,6 +22,10 @@ namespace spd {
 // One row of A as the kernels take them, longest first.
 struct MatchRow { int64_t start; int32_t len, row; };
 
+// Entries behind the last list, which a step may read and does not use: 15 of a chunk, 63 of a step, and with a tile of
+// 64 rows the 18 other pieces of a dense column that are summed together (half an entry a row).
+constexpr int64_t kMatchSpare = 640;
+
 // How B's rows are cut: into tiles of rows, and the columns of a tile into blocks (a power of two of them),
 // each with room for its entries and for `dense_per_block` columns kept as one value per row of the tile.
 struct MatchShape {
@@ -29,15 +34,15 @@ struct MatchShape {
     uint32_t stage;                         // entries of a block that pass through LDS together
     int64_t ptr_stride, tile_extra;         // words of a tile's list bounds; entries beyond the tile's own
     uint32_t lds_bytes, build_lds_bytes;
-    SPD_HD int64_t list_entries(int64_t nnz) const { return nnz + n_tiles * tile_extra + 64; }
+    SPD_HD int64_t list_entries(int64_t nnz) const { return nnz + n_tiles * tile_extra + kMatchSpare; }
 };
 MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, int64_t nnz);
 
 struct MatchB {
     uint2 *list;            // {byte offset of the row's sums in a strip, value bits}, by tile, column block and column;
                             // a dense column: tile_rows values, 0 where the row has none.  (A stored zero keeps
-                            // its place in a list and points to a spare cell behind the strip's last; 64 spare
-                            // entries at the end, which a step may read.)
+                            // its place in a list and points to a spare cell behind the strip's last; kMatchSpare
+                            // entries at the end.)
     uint32_t *ptr;          // n_tiles * ptr_stride: where a column's list begins, from the tile's first entry on, at
                             // column + its block's number (a block has a word more for its last list's end);
                             // kMatchDense is set where the column is dense
@@ -69,7 +74,8 @@ struct MatchArgs {
 };
 
 constexpr uint32_t kBuildDense = 32;            // dense columns of a block at most
-constexpr int64_t kMatchStaticLds = 256;        // upper bound of the kernel's static __shared__ use
+// Upper bound of the kernel's static __shared__ use (one sum per pair: 64 words to a wavefront).
+constexpr int64_t match_static_lds(int64_t cell_bytes) { return 256 + (cell_bytes <= 8 ? 16 * 256 : 0); }
 constexpr int kMatchStagingKind = 6;            // how spd_profile_read names this kernel's staging
 constexpr int64_t kMatchL2Bytes = 4 << 20;      // of one XCD
 // Wavefronts of a workgroup, of which a compute unit holds one: the strips share its LDS, and where a pair's

@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     const int rows = (int)min((int64_t)T, n_rows - j0);
     const int64_t row_first = clamp_i64(indptr[j0], 0, nnz);             // of the rows' entries
     const int64_t first = row_first + tile * shape.tile_extra;            // of the tile's lists
-    const int64_t list_end = shape.list_entries(nnz) - 64;
+    const int64_t list_end = shape.list_entries(nnz) - kMatchSpare;
     uint2 *s_stage = reinterpret_cast<uint2 *>(s_raw);                              // stage entries
     uint32_t *s_count = reinterpret_cast<uint32_t *>(s_raw + (size_t)shape.stage * 8);   // block_cols counters, a multiple of 4
     uint32_t *s_cur = s_count + block_cols;                                   // where a row's block begins ...
@@ -281,19 +281,28 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     const int cell = match_cell_bytes(op);
     if (cell == 0 || n <= 0 || n_cols <= 0) return s;
     s.waves = match_waves((size_t)cell);
-    const int64_t strip = (lds_budget - kMatchStaticLds) / s.waves;
+    const int64_t strip = (lds_budget - match_static_lds(cell)) / s.waves;
     int64_t most = (strip / cell - 1) / kWave * kWave;          // (a spare cell behind them)
     if (most < kWave) return s;
-    // A list of 65 entries takes two steps of 64 like one of 128.  Where the mean list of the largest tile
-    // is between one and four steps long, a smaller tile's that just fills whole steps (with room for the
-    // spread of a random column's count) is cheaper: 65,536 x 26,000 rows of 7 %, lists of 54 instead of 81.
     const double per_cell = (double)nnz / (double)n / (double)n_cols;
-    if (per_cell * (double)most < 256.0)
+    if (cell <= 8) {
+        // The lists of a tile that the workgroups of an XCD walk together: within twice its L2 (65,536 x 26,000 rows of 7 %,
+        // L1: tiles of 256 rows 33.8 ms, 384 29.9, 512 28.6, 640 31.2, 768 34.0, 1,216 36.7), as long as a list is two
+        // chunks of 16 on the mean; where tiles of all the LDS are within it, the largest (300,000 rows of 230, cosine:
+        // 576 rows 9.0 ms, 832 7.0, 1,216 5.7).
+        const int64_t within = (int64_t)((double)(2 * kMatchL2Bytes / 8) / std::max(per_cell * (double)n_cols, 1e-12)) / kWave * kWave;
+        const int64_t least = ((int64_t)(32.0 / std::max(per_cell, 1e-9)) + kWave - 1) / kWave * kWave;
+        most = std::max<int64_t>(kWave, std::min(most, std::max(within, least)));
+    } else if (per_cell * (double)most < 256.0) {
+        // A list of 65 entries takes two steps of 64 like one of 128.  Where the mean list of the largest tile
+        // is between one and four steps long, a smaller tile's that just fills whole steps (with room for the
+        // spread of a random column's count) is cheaper: 65,536 x 26,000 rows of 7 %, lists of 54 instead of 81.
         for (int q = 3; q >= 1; --q) {
             const double root = std::sqrt(64.0 * q + 0.4225) - 0.65;             // mean + 1.3 sqrt(mean) = 64 q
             const int64_t rows = (int64_t)(root * root / std::max(per_cell, 1e-12)) / kWave * kWave;
             if (rows >= kWave && rows <= most) { most = rows; break; }
         }
+    }
     const int64_t tiles = (n + most - 1) / most;
     if (tiles > (1 << 30)) return s;
     s.tile_rows = (int32_t)(((n + tiles - 1) / tiles + kWave - 1) / kWave * kWave);

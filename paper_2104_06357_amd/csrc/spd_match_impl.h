@@ -56,17 +56,52 @@ template <typename Acc> __device__ __forceinline__ void pin(Acc &t, uint32_t &ce
     __builtin_memcpy(&t, w, sizeof(Acc));
 }
 
-template <typename Acc> __device__ __forceinline__ void match_add(unsigned char *cell, const Acc &t) {
+// (the cell by its LDS address: an offset from a __shared__ array costs another addition)
+template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(uint32_t address) {
+    return (__attribute__((address_space(3))) T *)(uintptr_t)address;
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+template <typename Acc> __device__ __forceinline__ void match_add(uint32_t cell, const Acc &t) {
     if constexpr (sizeof(Acc) == 8) {
         double v;
         __builtin_memcpy(&v, &t, 8);
-        __hip_atomic_fetch_add(reinterpret_cast<double *>(cell), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        __hip_atomic_fetch_add(lds_at<double>(cell), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     } else {
         int v;
         __builtin_memcpy(&v, &t, 4);
-        __hip_atomic_fetch_add(reinterpret_cast<int *>(cell), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        __hip_atomic_fetch_add(lds_at<int>(cell), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
 }
+
+// Inclusive sum and maximum over the wavefront's lanes (the maximum of values that are not negative).
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_or_zero(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int wave_scan_add(int v) {
+    v += dpp_or_zero<0x111, 0xf>(v);                   // row_shr:1, 2, 4, 8
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    v += dpp_or_zero<0x142, 0xa>(v);                   // row_bcast:15 into rows 1 and 3, row_bcast:31 into 2 and 3
+    v += dpp_or_zero<0x143, 0xc>(v);
+    return v;
+}
+__device__ __forceinline__ int wave_scan_max(int v) {
+    v = max(v, dpp_or_zero<0x111, 0xf>(v));
+    v = max(v, dpp_or_zero<0x112, 0xf>(v));
+    v = max(v, dpp_or_zero<0x114, 0xf>(v));
+    v = max(v, dpp_or_zero<0x118, 0xf>(v));
+    v = max(v, dpp_or_zero<0x142, 0xa>(v));
+    v = max(v, dpp_or_zero<0x143, 0xc>(v));
+    return v;
+}
+// Lane I of every row of 16 lanes, in all lanes of the row (row_newbcast).
+template <int I> __device__ __forceinline__ uint32_t row_lane(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + I, 0xf, 0xf, true);
+}
+template <int I> __device__ __forceinline__ float row_lane(float v) { return __uint_as_float(row_lane<I>(__float_as_uint(v))); }
 
 constexpr int kMatchUnroll = 4;          // list steps whose loads are in flight together
 
@@ -81,11 +116,12 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
     extern __shared__ __align__(16) unsigned char dyn[];
     __shared__ int s_next;
     __shared__ int s_lock[KNN ? kMatchLocks : 1];
+    __shared__ int s_owner[sizeof(Cell) <= 8 ? nw : 1][sizeof(Cell) <= 8 ? kWave : 1];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
     const int T = args.b.shape.tile_rows;
     const uint32_t strip_bytes = (uint32_t)(T + 1) * (uint32_t)sizeof(Cell);
-    const uint32_t strip_at = (uint32_t)wave * strip_bytes;
-    unsigned char *strip = dyn + strip_at;
+    unsigned char *strip = dyn + (uint32_t)wave * strip_bytes;
+    const uint32_t strip_at = (uint32_t)wave_uniform((int)lds_address(strip));
     // Workgroups go round the eight XCDs in turn: with `by_xcd` the slices of one group of tiles, which
     // read the same lists at about the same time, share an XCD and its L2.
     int group, slice;
@@ -137,15 +173,13 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
         for (int i0 = 0; i0 < T; i0 += D * kWave) {
             typename O::Acc sum[D];
             float cur[D], nxt[D];
-            uint32_t from_row[D];               // (past the tile's end its last rows are read again, and not added)
-#pragma unroll
-            for (int d = 0; d < D; ++d) from_row[d] = (uint32_t)min(i0 + d * kWave, T - kWave);
 #pragma unroll
             for (int d = 0; d < D; ++d) O::init(sum[d]);
+            // (past the tile's end what lies behind the column is read, or the spare entries at the end of the lists, and not added)
             auto fetch = [&](float (&into)[D], int e) {
-                const unsigned char *col = list + (uint32_t)__builtin_amdgcn_readlane((int)first8, e);
+                const unsigned char *col = list + ((uint32_t)__builtin_amdgcn_readlane((int)first8, e) + (uint32_t)i0 * 4u);
 #pragma unroll
-                for (int d = 0; d < D; ++d) into[d] = *reinterpret_cast<const float *>((col + from_row[d] * 4u) + lane4);
+                for (int d = 0; d < D; ++d) into[d] = *reinterpret_cast<const float *>(col + lane4 + d * (kWave * 4));
             };
             auto visit = [&](const float (&from)[D], int e) {
                 const float ae = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), e));
@@ -169,41 +203,28 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
                 visit(nxt, e1);
                 if (!left) break;
             }
-            Cell cell[D];
+            Cell *cells = reinterpret_cast<Cell *>(strip) + i0 + lane;
 #pragma unroll
-            for (int d = 0; d < D; ++d) cell[d] = reinterpret_cast<const Cell *>(strip)[from_row[d] + (uint32_t)lane];
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                O::combine(cell[d].acc, sum[d]);
-                if (i0 + d * kWave < T) reinterpret_cast<Cell *>(strip)[from_row[d] + (uint32_t)lane] = cell[d];
-            }
+            for (int d = 0; d < D; ++d)
+                if (i0 + d * kWave < T) {
+                    Cell cell = cells[d * kWave];
+                    O::combine(cell.acc, sum[d]);
+                    cells[d * kWave] = cell;
+                }
         }
     };
-    auto walk_lists = [&](int tile, const Lists &y) {
-        const int64_t tile_first = clamp_i64(args.b_indptr[(int64_t)tile * T], 0, args.b_nnz) + tile * args.b.shape.tile_extra;
-        const unsigned char *__restrict__ list = reinterpret_cast<const unsigned char *>(args.b.list + tile_first);
-        const uint32_t list_n = (uint32_t)(args.b.shape.list_entries(args.b_nnz) - 64 - tile_first);     // (no access leaves the lists)
-        const float a = transform_value(args.transform, y.a);
-        uint32_t first = min(y.first & ~kMatchDense, list_n);
-        const bool dense = (y.first & kMatchDense) != 0u && a != 0.0f && first + (uint32_t)(T / 2) <= list_n;
-        const uint64_t dense_mask = __ballot(dense);
-        if (dense_mask != 0) walk_dense(list, first * 8u, a, dense_mask);
-        const uint32_t last = a != 0.0f && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
+    // Several sums per pair: a step is up to 64 entries of one list, and no two lanes of a step meet in one row's sums.
+    auto walk_steps = [&](const unsigned char *__restrict__ list, uint32_t first, uint32_t last, float a) {
         // steps of 64 list entries: how many there are up to and including this lane's list
         const int steps = (int)((last - first + 63u) >> 6);
-        int incl = steps;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int up = __shfl_up(incl, d);
-            if (lane >= d) incl += up;
-        }
+        const int incl = wave_scan_add(steps);
         const int total = __builtin_amdgcn_readlane(incl, 63);
         if (total == 0) return;
         const uint32_t base8 = first * 8u - 512u * (uint32_t)(incl - steps);      // step t reads from byte base8 + 512 t on
         const uint32_t last8 = last * 8u;
         // A step is described by scalars alone (where it reads, how many bytes are its list's, A's value): the
         // lanes' part of it is one load, the lookup and the sum.  A short list's load runs into the next one
-        // (or the 64 spare entries at the end of the lists), and those lanes add nothing.
+        // (or the spare entries at the end of the lists), and those lanes add nothing.
         uint2 cur[U], nxt[U];
         float cur_a[U], nxt_a[U];
         uint32_t cur_n[U], nxt_n[U];
@@ -221,27 +242,13 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
         };
         auto add = [&](const uint2 (&from)[U], const float (&av)[U], const uint32_t (&bytes)[U]) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                // (where there is one sum, everything but the LDS add itself is done for all lanes: a branch around it costs more)
-                const bool ok = lane8 < bytes[u];
-                const float b = __uint_as_float(from[u].y);
-                if constexpr (sizeof(Cell) <= 8) {
-                    // one sum: an LDS add that nothing waits for
-                    typename O::Acc t;
-                    O::init(t);
-                    match_visit<OP>(t, av[u], b, args.q);
-                    uint32_t cell = strip_at + from[u].x;
-                    pin(t, cell);
-                    if (ok) match_add(dyn + cell, t);
-                } else {
-                    if (ok) {
-                        Cell *cell = reinterpret_cast<Cell *>(strip + from[u].x);
-                        Cell c = *cell;
-                        match_visit<OP>(c.acc, av[u], b, args.q);
-                        *cell = c;
-                    }
+            for (int u = 0; u < U; ++u)
+                if (lane8 < bytes[u]) {
+                    Cell *cell = reinterpret_cast<Cell *>(strip + from[u].x);
+                    Cell c = *cell;
+                    match_visit<OP>(c.acc, av[u], __uint_as_float(from[u].y), args.q);
+                    *cell = c;
                 }
-            }
         };
         fetch(cur, cur_a, cur_n, 0);
         for (int t = 0;;) {
@@ -256,6 +263,125 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
             t += U;
             if (t >= total) break;
         }
+    };
+    // One sum per pair: the lists are cut into chunks of 16 entries, and a step is four chunks, one to a quarter of the
+    // wavefront, whichever lists they belong to (a step of one list alone is filled to 62 % by 300,000 rows of 230 and to 28 %
+    // by ratings; its 13 vector instructions are 8 here: 10,000 x 10,000 rows of 38, L1, 421 -> 340 us a call, 1,024 x 300,000
+    // rows of 230, cosine, 6.6 -> 5.6 ms, 1,531 x 28,301 ratings, Canberra, 1.13 -> 0.75 ms).  What bounds it now: vector
+    // loads of 8 bytes take the L1 16 clocks a step whatever they touch, and an LDS add of 64 doubles at random rows 23.
+    // 64 chunks are described at a time, a chunk to a lane: lane 16 g + i
+    // holds chunk 4 i + g, so that step i finds its four descriptions in lane i of each quarter (a DPP broadcast).  Chunks
+    // follow one another over the steps and over the lanes of a step in the order of A's columns, and LDS serves the
+    // lanes that meet in one sum in ascending order: a sum is formed in the order of A's columns here too.
+    auto walk_chunks = [&](const unsigned char *__restrict__ list, uint32_t first, uint32_t last, float a) {
+        const int chunks = (int)((last - first + 15u) >> 4);
+        const int incl = wave_scan_add(chunks), excl = incl - chunks;
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (total == 0) return;
+        const uint32_t base8 = first * 8u - 128u * (uint32_t)excl;               // chunk q reads from byte base8 + 128 q on
+        const uint32_t last8 = last * 8u;
+        const int turned = ((lane & 15) << 2) | (lane >> 4);
+        const uint32_t lane8 = (uint32_t)(lane & 15) * 8u;
+        struct Chunk { uint32_t at, left; float a; };                            // left: bytes of its list from `at` on
+        int *owner = s_owner[wave];
+        owner[lane] = 0;
+        int tag = 64, carry = 0;
+        // Which list a chunk belongs to: every list marks its first chunk with its lane, and a running maximum carries the
+        // marks on (a mark of an earlier group is below the tag).
+        auto describe = [&](int q0) {
+            const uint32_t start = (uint32_t)(excl - q0);
+            if (chunks > 0 && start < 64u) owner[start] = tag + lane;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            int e = owner[lane];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            e = wave_scan_max(max(e, tag + carry));
+            carry = __builtin_amdgcn_readlane(e, 63) & 63;
+            tag += 64;
+            const int from = (__builtin_amdgcn_ds_bpermute(turned << 2, e) & 63) << 2;
+            const int q = q0 + turned;
+            Chunk c;
+            c.at = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)base8) + 128u * (uint32_t)q;
+            c.left = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)last8) - c.at;
+            c.a = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(a)));
+            if (q >= total) { c.at = 0u; c.left = 0u; }
+            return c;
+        };
+        auto fetch = [&](uint2 (&into)[U], const Chunk &c, auto block) {
+            constexpr int I = decltype(block)::value * U;
+            into[0] = *reinterpret_cast<const uint2 *>(list + (row_lane<I>(c.at) + lane8));
+            into[1] = *reinterpret_cast<const uint2 *>(list + (row_lane<I + 1>(c.at) + lane8));
+            into[2] = *reinterpret_cast<const uint2 *>(list + (row_lane<I + 2>(c.at) + lane8));
+            into[3] = *reinterpret_cast<const uint2 *>(list + (row_lane<I + 3>(c.at) + lane8));
+        };
+        auto add_one = [&](const uint2 &from, uint32_t left, float av) {
+            // (everything but the LDS add itself is done for all lanes: a branch around it costs more)
+            typename O::Acc t;
+            O::init(t);
+            match_visit<OP>(t, av, __uint_as_float(from.y), args.q);
+            uint32_t cell = strip_at + from.x;
+            pin(t, cell);
+            if (lane8 < left) match_add(cell, t);
+        };
+        auto add = [&](const uint2 (&from)[U], const Chunk &c, auto block) {
+            constexpr int I = decltype(block)::value * U;
+            add_one(from[0], row_lane<I>(c.left), row_lane<I>(c.a));
+            add_one(from[1], row_lane<I + 1>(c.left), row_lane<I + 1>(c.a));
+            add_one(from[2], row_lane<I + 2>(c.left), row_lane<I + 2>(c.a));
+            add_one(from[3], row_lane<I + 3>(c.left), row_lane<I + 3>(c.a));
+        };
+        constexpr std::integral_constant<int, 0> b0{};
+        constexpr std::integral_constant<int, 1> b1{};
+        constexpr std::integral_constant<int, 2> b2{};
+        constexpr std::integral_constant<int, 3> b3{};
+        uint2 x[U], y[U];
+        Chunk c = describe(0);
+        fetch(x, c, b0);
+        if (total <= 4 * U) {                                   // a few entries: no more steps than they take
+            add_one(x[0], row_lane<0>(c.left), row_lane<0>(c.a));
+            if (total <= 4) return;
+            add_one(x[1], row_lane<1>(c.left), row_lane<1>(c.a));
+            if (total <= 8) return;
+            add_one(x[2], row_lane<2>(c.left), row_lane<2>(c.a));
+            if (total <= 12) return;
+            add_one(x[3], row_lane<3>(c.left), row_lane<3>(c.a));
+            return;
+        }
+        fetch(y, c, b1);
+        for (int left = total;;) {                              // chunks from this group on
+            Chunk next = c;
+            if (left > 64) next = describe(total - left + 64);
+            __builtin_amdgcn_sched_barrier(0);                  // (keep the loads ahead of the arithmetic)
+            add(x, c, b0);
+            if (left <= 16) break;
+            fetch(x, c, b2);
+            __builtin_amdgcn_sched_barrier(0);
+            add(y, c, b1);
+            if (left <= 32) break;
+            fetch(y, c, b3);
+            __builtin_amdgcn_sched_barrier(0);
+            add(x, c, b2);
+            if (left <= 48) break;
+            fetch(x, next, b0);
+            __builtin_amdgcn_sched_barrier(0);
+            add(y, c, b3);
+            left -= 64;
+            if (left <= 0) break;
+            fetch(y, next, b1);
+            c = next;
+        }
+    };
+    auto walk_lists = [&](int tile, const Lists &y) {
+        const int64_t tile_first = clamp_i64(args.b_indptr[(int64_t)tile * T], 0, args.b_nnz) + tile * args.b.shape.tile_extra;
+        const unsigned char *__restrict__ list = reinterpret_cast<const unsigned char *>(args.b.list + tile_first);
+        const uint32_t list_n = (uint32_t)(args.b.shape.list_entries(args.b_nnz) - kMatchSpare - tile_first);     // (no access leaves the lists)
+        const float a = transform_value(args.transform, y.a);
+        uint32_t first = min(y.first & ~kMatchDense, list_n);
+        const bool dense = (y.first & kMatchDense) != 0u && a != 0.0f && first + (uint32_t)(T / 2) <= list_n;
+        const uint64_t dense_mask = __ballot(dense);
+        if (dense_mask != 0) walk_dense(list, first * 8u, a, dense_mask);
+        const uint32_t last = a != 0.0f && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
+        if constexpr (sizeof(Cell) <= 8) walk_chunks(list, first, last, a);
+        else walk_steps(list, first, last, a);
         // (a lane reads later what other lanes of its wavefront wrote: LDS serves a wavefront in order, the
         // fence keeps the compiler to that order)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -488,7 +614,7 @@ template <typename Kernel> static hipError_t allow_lds(Kernel kern, std::atomic<
     const bool known = dev >= 0 && dev < kMatchDevices;
     if (known && allowed[dev].load(std::memory_order_acquire) >= bytes) return hipSuccess;
     // to the most any launch may ask for, so that no two launches set it against each other
-    const uint32_t want = std::max<uint32_t>(bytes, 160u * 1024u - (uint32_t)kMatchStaticLds);
+    const uint32_t want = std::max<uint32_t>(bytes, 160u * 1024u - (uint32_t)match_static_lds(8));
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)want);
     if (e == hipSuccess) {
         if (known) allowed[dev].store(want, std::memory_order_release);

@@ -78,6 +78,41 @@ def test_edges(spd, metric, m, n, cols, budget):
     h.close()
 
 
+@pytest.mark.parametrize("metric", ["inner_product", "l1", "hamming", "canberra"])
+def test_chunks_of_a_batch(spd, metric):
+    """A step is four chunks of 16 entries of any lists: rows of A whose batches of 64 entries end on, before and behind a
+    chunk, a step, four steps and a group of 64 chunks, and rows of B that every list of a step holds (they meet in one sum
+    there).  The values are powers of two, so every sum is exact whatever its order."""
+    rng = np.random.default_rng(16)
+    n, lengths = 640, (1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 127, 128, 129, 0)
+    cols = 64 * len(lengths)
+    B = np.zeros((n, cols))
+    for c in range(cols):                                  # lists of those lengths, 64 of each; rows 0 to 9 in most of them
+        L = lengths[c % len(lengths)]
+        rows = np.concatenate([np.arange(min(10, L)), 10 + rng.choice(n - 10, size=max(0, L - 10), replace=False)])
+        B[rows, c] = 2.0 ** rng.integers(-2, 3, size=L)
+    A = []
+    for count in (1, 2, 3, 4, 5, 8, 9, 12, 13, 16, 17, 31, 32, 33, 48, 49, 63, 64, 65, 128, 130):
+        for L in (1, 16, 17, 33, 129, None):               # `count` lists of one length, or of all lengths
+            of = np.arange(cols) if L is None else np.flatnonzero(np.arange(cols) % len(lengths) == lengths.index(L))
+            row = np.zeros(cols)
+            chosen = rng.choice(of, size=min(count, len(of)), replace=False)
+            row[chosen] = 2.0 ** rng.integers(-2, 3, size=len(chosen))
+            A.append(row)
+    A, B = synth.from_dense(np.array(A)), synth.from_dense(B)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric])
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = _lists(spd)
+    got = _np(h.pairwise(dA, dB, metric))
+    if metric in ("inner_product", "l1"):
+        assert np.array_equal(got, want.astype(np.float32))
+    else:
+        assert_distances_close(got, want, metric)
+    idx, dist = h.knn(dA, dB, metric, 20)
+    assert_knn_matches(_np(idx), _np(dist), want, 20, metric, metric)
+    h.close()
+
+
 @pytest.mark.parametrize("metric", ["l2_expanded", "l1", "hamming", "jensen_shannon", "minkowski"])
 @pytest.mark.parametrize("m,n,cols,lengths_a,lengths_b", [
     (20, 1300, 1203, (1200, 257, 256, 900, 5, 0, 1203), (30, 3, 200)),           # rows that wavefronts share, one per tile and more
