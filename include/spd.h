@@ -317,8 +317,9 @@ spd_status spd_csr_validate(spd_handle *handle, const spd_csr *M, int require_no
  *                 listed by column, and a wavefront walks the lists of its row of A, so that only the
  *                 columns two rows share cost anything (not for Chebyshev and the semirings that are not
  *                 spelled as a distance).  1 (default): where it pays (sparse and long enough operands, A's
- *                 rows not too long against B's, no knob of the staged scan turned); 0: never; 2: wherever
- *                 the product has it.  A call whose lists the caller's scratch does not hold, or the device
+ *                 rows not too long against B's, no knob of the staged scan turned), over very many columns
+ *                 after a copy of both operands over the columns that A stores; 0: never; 2: wherever the product
+ *                 has it; 3: the same, over A's columns.  A call whose lists the caller's scratch does not hold, or the device
  *                 has no memory for, runs by the staged scan; the handle asks the device for that much again
  *                 only after the option is set again.  The sums' order differs between the two ways.
  *   "check_plan"  1: verify every index the kernels will form from the plan before the scan is launched (with
@@ -331,7 +332,8 @@ spd_status spd_set_option(spd_handle *handle, const char *name, int64_t value);
  * One record per launch, in launch order.  Waits for the call's kernels to finish. */
 typedef struct {
     char name[24];        /* "pack_b", "scan", "finalize", "knn_merge"; with the column lists "norms_b",
-                                "lists_b", "norms_a", "knn_begin", "scan", "knn_merge"              */
+                                ("columns", over A's columns) "lists_b", "norms_a", "knn_begin", "scan",
+                                "knn_merge"                                                          */
     int32_t rows_per_group; /* scan: R, the rows of A staged together; else 0            */
     int32_t staging_kind; /* scan: 1 dense strip, 2 column-slot strip, 3 hash, 4 Bloom, 5 bitmap,
                                 6 column lists ("match_lists"); else 0 */

@@ -133,7 +133,7 @@ struct spd_handle {
     bool no_byte_counters = false;   // option "byte_counters" 0: set metrics through the dot product
     int cuckoo_attempts = 3;     // option "cuckoo_attempts"
     int knn_seed = 1;            // option "knn_seed"
-    int match_lists = 1;         // option "match_lists": 0 never, 1 where it pays, 2 wherever the product allows it
+    int match_lists = 1;         // option "match_lists": 0 never, 1 where it pays, 2 wherever the product allows it, 3 over A's columns
     size_t lists_refused = SIZE_MAX;     // the least scratch for the column lists that the device had no memory for
     int swap_operands = 1;       // option "swap_operands": 0 never, 1 where it pays, 2 wherever the distance allows it
     int side_streams = 3;        // option "side_streams": how many internal streams the small launches may use beside the large one
@@ -516,25 +516,26 @@ int product_of(const spd_handle *h, int metric, float p) {
     return op;
 }
 
-struct MatchLayout { size_t list, ptr, norms, end; };
+struct MatchLayout { size_t list, ptr, norms, least, end; };
 MatchLayout layout_match(const MatchShape &s, int64_t n, int64_t nnz, Carver &cv) {
     MatchLayout L;
     L.list = cv.take((size_t)s.list_entries(nnz) * 8);
     L.ptr = cv.take((size_t)s.n_tiles * (size_t)s.ptr_stride * 4);
     L.norms = cv.take((size_t)n * 16);
+    L.least = cv.take((size_t)s.n_tiles * 16);
     L.end = cv.off;
     return L;
 }
 MatchB match_b_at(const MatchShape &s, const MatchLayout &L, unsigned char *dev) {
     return MatchB{reinterpret_cast<uint2 *>(dev + L.list), reinterpret_cast<uint32_t *>(dev + L.ptr),
-                  reinterpret_cast<double *>(dev + L.norms), s};
+                  reinterpret_cast<double *>(dev + L.norms), reinterpret_cast<double *>(dev + L.least), s, nullptr};
 }
 // Grid of the column-list kernel: groups of tiles times slices of A's rows, one workgroup for each
 // compute unit of the chip.  Where the lists are more than the L2 caches hold, the tiles are dealt to the
 // eight XCDs, and the workgroups of an XCD go through its tiles together; smaller lists are in every L2
 // anyway, and each tile is a group.  Rows of A that hold more than a third of a wavefront's share of
 // the entries are shared by the wavefronts of a workgroup.
-struct MatchGrid { int slices = 1, groups = 1, by_xcd = 0; int64_t shared_len = 0; };
+struct MatchGrid { int slices = 1, groups = 1, by_xcd = 0, run = 1; int64_t shared_len = 0; };
 MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int64_t m, int64_t nnz_a, int64_t nnz_b, bool knn) {
     MatchGrid g;
     const int64_t cus = std::max(1, opt.n_cus), rows_slices = std::max<int64_t>(1, (m + s.waves - 1) / s.waves);
@@ -551,17 +552,38 @@ MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int64_t m, int
     const int64_t tiles = (s.n_tiles + g.groups - 1) / g.groups;
     const int64_t share = nnz_a * tiles / ((int64_t)g.slices * s.waves);
     g.shared_len = std::max<int64_t>(256, share / 3);
+    // A wavefront goes through a run of tiles with a row: as many as leave every wavefront four rows' runs, and whose lists
+    // (and bounds) together lie in half of an L2.  What a row costs besides its lists is then paid once a run, and with
+    // k-NN its nearest are merged into the row's list once a run.
+    const double tile_bytes = 8.0 * (double)nnz_b / s.n_tiles + 4.0 * (double)s.ptr_stride;
+    const int64_t rows_here = std::max<int64_t>(1, m / g.slices);
+    g.run = (int)std::max<int64_t>(1, std::min<int64_t>({tiles, (int64_t)((double)(kMatchL2Bytes / 2) / tile_bytes), rows_here * tiles / (4 * s.waves)}));
     return g;
 }
 // (tile, row)s that the wavefronts of a workgroup share out among themselves, numbered in 32 bits.
 int64_t match_items(const MatchShape &s, const MatchGrid &g, int64_t m) {
     return ((m + g.slices - 1) / g.slices) * ((s.n_tiles + g.groups - 1) / g.groups);
 }
-struct MatchScratch { MatchLayout b; size_t rows, norms_a, tau, part, row_off, row_lists, end; };
-MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int64_t m, int64_t n, int64_t nnz_b, int knn_k, bool with_b) {
+struct ColumnsLayout { size_t words, sums, totals, masks, before, a_indices, b_indptr, b_indices, b_values; };
+struct MatchScratch { MatchLayout b; ColumnsLayout c; size_t rows, norms_a, tau, part, row_off, row_lists, end; };
+// `columns`: 0, or the operands' column count where both are copied over A's columns first (spd_match_columns.hip).
+MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int64_t m, int64_t nnz_a, int64_t n, int64_t nnz_b, int knn_k,
+                               bool with_b, int64_t columns) {
     MatchScratch L{};
     Carver cv;
     if (with_b) L.b = layout_match(s, n, nnz_b, cv);
+    if (columns > 0) {
+        const size_t words = ((size_t)columns + 31) / 32, masks = ((size_t)nnz_b + 63) / 64;
+        L.c.words = cv.take(words * 8);
+        L.c.sums = cv.take(std::max(words, masks) / 64 * 4 + 256);
+        L.c.totals = cv.take(8);
+        L.c.masks = cv.take(masks * 8);
+        L.c.before = cv.take(masks * 4);
+        L.c.a_indices = cv.take((size_t)nnz_a * 4);
+        L.c.b_indptr = cv.take((size_t)(n + 1) * 8);
+        L.c.b_indices = cv.take((size_t)nnz_b * 4);
+        L.c.b_values = cv.take((size_t)nnz_b * 4);
+    }
     L.rows = cv.take((size_t)m * sizeof(MatchRow));
     L.norms_a = cv.take((size_t)m * 16);
     if (knn_k > 0) {
@@ -578,8 +600,8 @@ std::string match_check(const PlanOptions &opt, const MatchShape &s, const Match
                         int64_t nnz_b) {
     const int64_t T = s.tile_rows, tiles = s.n_tiles, blocks = s.blocks, cell = match_cell_bytes(op);
     if (T < kWave || T % kWave != 0 || tiles * T < n || (tiles - 1) * T >= n) return "tiles do not cover B";
-    if (s.waves != match_waves((size_t)cell) || (int64_t)s.lds_bytes != s.waves * (T + 1) * cell ||
-        (int64_t)s.lds_bytes + match_static_lds(cell) > opt.lds_budget) return "strips over the LDS";
+    if (s.waves != match_waves((int)cell) || s.lds_bytes != (uint32_t)s.waves * match_strip_bytes((int)cell, (int)T) ||
+        (int64_t)s.lds_bytes + match_static_lds((int)cell) > opt.lds_budget) return "strips over the LDS";
     if (s.block_shift < 2 || s.block_shift > 30 || (blocks << s.block_shift) < n_cols || ((blocks - 1) << s.block_shift) >= n_cols)
         return "column blocks";
     if (s.ptr_stride < n_cols + blocks) return "list bounds";
@@ -588,7 +610,7 @@ std::string match_check(const PlanOptions &opt, const MatchShape &s, const Match
     if (s.list_entries(nnz_b) >= (int64_t)1 << 29) return "list positions";
     const int64_t build = (int64_t)s.stage * 8 + ((int64_t)4 << s.block_shift) + 12 * T;
     if ((int64_t)s.build_lds_bytes != build || build + 1024 > opt.lds_budget) return "build over the LDS";
-    if (g.slices < 1 || g.groups < 1 || g.groups > tiles || (g.by_xcd && g.groups < tiles && g.groups % 8 != 0)) return "grid";
+    if (g.slices < 1 || g.groups < 1 || g.run < 1 || g.run > tiles || g.groups > tiles || (g.by_xcd && g.groups < tiles && g.groups % 8 != 0)) return "grid";
     if (match_items(s, g, m) >= (int64_t)1 << 30) return "(tile, row)s of a workgroup";
     return std::string();
 }
@@ -630,8 +652,7 @@ bool match_possible(const spd_handle *h, const spd_csr *B, int op, MatchShape &s
 }
 // Whether some call could do better by them, as far as B tells.
 bool match_suits(const spd_handle *h, const spd_csr *B, int op, const MatchShape &s) {
-    // the set metrics stay with the staged scan, whose visit is a byte add (605 x 168,903 rows of 230, Dice 3.0 / 3.5 ms)
-    if (op == OP_CNT || !scan_knobs_untouched(h)) return false;
+    if (!scan_knobs_untouched(h)) return false;
     // where an eighth of B's cells are stored (half, for a dear product), most visits meet something
     if ((double)B->nnz > (match_light(op) ? 0.125 : 0.5) * (double)B->n_cols * (double)B->n_rows) return false;
     return match_bounds_fit(s, B->nnz);
@@ -643,43 +664,45 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
     Carver cv;
     L = layout_match(s, B->n_rows, B->nnz, cv);
     if (h->match_lists == 2) return true;
+    if (op == OP_CNT) return false;                // (counts come out the same by the scan, which is as fast where a call has no B to prepare)
     return match_suits(h, B, op, s) && (int64_t)L.end <= 20 * B->nnz + 16 * B->n_rows + (1 << 20);
 }
-// Whether the lists cost less than the staged scan, in picoseconds of the whole chip.  A wavefront pays for
-// every entry of its row of A in every tile (its list's bounds; a step, where the list is not empty; what a
-// long list takes beyond one step), with k-NN for the selection in every (tile, row) too, and the last round of
-// (tile, row)s leaves wavefronts idle.  The staged scan pays for every visit (a staged row, a streamed entry;
-// more where longer staged rows leave fewer of them a place in LDS).  The constants are fitted to both ways' times
-// of 3,600 pairs of operands (100 to 12,000 rows against 600 to 300,000, rows of 2 to 4,000 entries, A's 1/30 to
-// 60 times as long as B's, uniform and Zipf columns, every product but the counts, k-NN with k = 10 to 64 and
-// pairwise).  Of 1,941 that the conditions on work and density in match_wanted let through, 452 took longer by
-// lists by a tenth or more, up to nine times; of the 1,338 that this lets through, 36, up to 1.7 times (and 19 of
-// 545 in 1,500 other pairs, up to 1.8 times, in columns far from uniform, which row pointers do not show).  Both
-// sides, staged / lists in ms:
-//   1,000 x 10,000 rows of 1,360 and 20 entries over 20,000 columns, L1            0.14 / 0.70
-//   766 x 3,599 rows of 1,468 and 35 over 20,000, Minkowski (p = 3), k = 32        0.15 / 1.03
-//   8,934 x 10,816 rows of 598 and 9 over 60,000, Jensen-Shannon (B staged)        36.7 / 1.49
-bool match_pays(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const MatchShape &s, bool swapped, bool knn) {
+// What a call costs by lists and by the staged scan, in picoseconds of the whole chip.  A wavefront pays for every entry of
+// its row of A in every tile (its list's bounds; a step, where the list is not empty; what a long list takes beyond one
+// step), with k-NN for the selection in every (tile, row) too, and the last round of (tile, row)s leaves wavefronts idle.
+// The staged scan pays for every visit (a staged row, a streamed entry).  Both pay for what they make of B, for the pairs
+// they finish, and for their launches.  The constants are fitted to both ways' times of 3,000 pairs of operands (100 to
+// 12,000 rows against 600 to 300,000, rows of 1.5 to 4,000 entries, A's 1/30 to 60 times as long as B's, uniform and Zipf
+// columns, 2,000 to 2^20 of them, every product, k-NN with k = 10 to 64 and pairwise); they are within a factor of 1.5 of
+// the times of most, because row pointers do not show how A's columns meet B's.
+double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, const MatchShape &s, bool knn, bool copied) {
     const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz;
-    const bool wide = match_cell_bytes(op) >= 16;
-    const double list = nnz_b / n / (double)A->n_cols * (double)s.tile_rows;          // entries, on the mean
-    const double entry = 30.0 + (wide ? 80.0 : 40.0) * std::min(1.0, list) + (wide ? 60.0 : 40.0) * list / 64.0;
+    const bool wide = match_doubles(op) + match_counts(op) > 1;
+    const double list = nnz_b / n / (double)columns * (double)s.tile_rows;             // entries, on the mean
     const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn);
     const double items = std::ceil((double)match_items(s, g, A->n_rows) / s.waves);     // of a wavefront
     const double idle = items * s.waves * (double)h->opt.n_cus / (m * s.n_tiles);
-    const double lists = idle * s.n_tiles * (entry * nnz_a + (knn ? 2000.0 * m : 0.0)) + m * n;
+    // (over A's columns alone the lists that A walks are longer than the mean)
+    const double entry = copied ? (wide ? 45.0 + 75.0 * std::min(1.0, list) + 160.0 * list / 64.0 : 25.0 + 27.0 * std::min(1.0, list) + 80.0 * list / 64.0)
+                                : (wide ? 45.0 + 65.0 * std::min(1.0, list) + 95.0 * list / 64.0 : 22.0 + 13.0 * std::min(1.0, list) + 42.0 * list / 64.0);
+    const double row = knn ? (wide ? 1600.0 : 2300.0) : 300.0;
+    return (copied ? 105e6 : 65e6) + 28.0 * nnz_b + idle * s.n_tiles * (entry * nnz_a + row * m) + 0.9 * m * n;
+}
+double staged_cost(const spd_csr *A, const spd_csr *B, int op, bool swapped, bool knn) {
+    const double m = (double)A->n_rows, n = (double)B->n_rows;
     double visit = 0.6;
     switch (op) {
-    case OP_DOT: case OP_L1: visit = 0.12; break;
-    case OP_HAMM: visit = 0.15; break;
-    case OP_CANB: visit = 0.29; break;
-    case OP_KL: visit = 0.34; break;
-    case OP_JS: visit = 0.72; break;
+    case OP_DOT: case OP_L1: visit = 0.115; break;
+    case OP_HAMM: visit = 0.155; break;
+    case OP_CANB: visit = 0.285; break;
+    case OP_KL: visit = 0.32; break;
+    case OP_JS: visit = 0.74; break;
+    case OP_CNT: visit = 0.04; break;
     default: break;
     }
-    visit += 7e-5 * (swapped ? nnz_b / n : nnz_a / m);
-    const double staged = visit * (swapped ? n * nnz_a : m * nnz_b) + (knn ? 2.6 : 2.0) * m * n;
-    return lists <= 0.9 * staged;
+    // (longer staged rows leave fewer of them a place in LDS; a set metric's take a byte)
+    if (op != OP_CNT) visit += 4e-5 * (swapped ? (double)B->nnz / n : (double)A->nnz / m);
+    return 100e6 + 20.0 * (double)B->nnz + visit * (swapped ? n * (double)A->nnz : m * (double)B->nnz) + (knn ? 4.4 : 2.4) * m * n;
 }
 // `swapped`: the staged scan would exchange the operands' roles.
 bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn) {
@@ -688,26 +711,62 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     if (match_items(s, match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
     if (h->match_lists == 2) return true;
     if (!match_suits(h, B, op, s)) return false;
-    // The build takes some 17 ps an entry of B, and a call's other launches have a price too.  Both sides measured, staged /
-    // lists in ms:  10,000 x 10,000 rows of 38, L1 0.65 / 0.41;  3,207 x 1,172 of them 0.15 / 0.16;  1,024 x
-    // 300,000 of 230, cosine 11.4 / 6.7;  97 x 113,185 of them 0.86 / 0.96;  4,096 x 65,536 of 1,820, L1 87 / 36,
-    // Jensen-Shannon 349 / 59;  126 x 2,556 of them, KL 0.55 / 0.83.
-    const bool light = match_light(op);
-    const double weight = light ? 1.0 : (op == OP_CANB ? 2.0 : (op == OP_KL ? 2.5 : (op == OP_JS ? 4.5 : 3.5)));
-    const double work = (double)A->n_rows * (double)B->nnz * weight;
-    const double mean = (double)B->nnz / (double)B->n_rows;
-    if (work < (mean <= 64.0 ? 1.5e8 : 3e9) || (double)A->n_rows * weight < 400.0) return false;
-    return match_pays(h, A, B, op, s, swapped, knn);
+    // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.34; 1,024 x 300,000 of 230, cosine
+    // 11.4 / 5.6; 4,096 x 65,536 of 1,820, L1 87 / 29, Jensen-Shannon 349 / 51; 1,000 x 10,000 of 1,360 and 20, L1 0.14 /
+    // 0.70; set metrics: 2,435 x 6,447 ratings, Dice 0.62 / 0.28, 1,187 x 6,303 rows of 214, Russell-Rao 0.34 / 0.39, 680 x
+    // 20,302 of them 0.55 / 0.60.  Of 1,264 pairs of operands with one of the other products, the line between them lets 9 of
+    // ten of those through that gain a tenth or more, and 2 in a hundred that lose as much, up to a third; the set metrics'
+    // estimate is the coarser, and their line the stricter for it (7 of 178, up to a quarter).
+    return lists_cost(h, A, B, A->n_cols, op, s, knn, false) <= (op == OP_CNT ? 0.7 : 0.85) * staged_cost(A, B, op, swapped, knn);
+}
+// The columns that lists over A's columns alone are laid out for (how many A stores, the host does not know).
+int64_t columns_of(const spd_csr *A) { return std::min(A->n_cols, std::max<int64_t>(A->nnz, 1)); }
+// Whether a call is computed by lists over the columns that A stores, after a copy of both operands over these.
+bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn) {
+    if (semiring || h->match_lists == 0 || !match_serves(op) || A->n_rows <= 0 || A->nnz <= 0 || B->n_rows <= 0 || B->nnz <= 0) return false;
+    if (A->n_cols > kMatchMostColumns) return false;
+    const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
+    if (s.n_tiles <= 0 || s.list_entries(B->nnz) >= ((int64_t)1 << 29)) return false;
+    if (match_items(s, match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
+    if (h->match_lists == 3) return true;
+    if (h->match_lists != 1 || !scan_knobs_untouched(h) || !match_bounds_fit(s, B->nnz)) return false;
+    // (where the lists over all columns have room for their bounds, the copy is not worth its time)
+    MatchShape all;
+    if (match_possible(h, B, op, all) && match_bounds_fit(all, B->nnz)) return false;
+    // Both sides measured, staged / lists over A's columns in ms, k-NN: 4,096 x 500,000 sets over 2^20 columns, Jaccard 30.6 /
+    // 11.6, 3,331 x 9,539 of them 0.93 / 0.67, 87 x 21,712 0.79 / 0.45; 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.7 /
+    // 2.0, 335 x 16,402 of them, L1 0.10 / 0.12.  Of 381 pairs of operands 9 lose a tenth or more behind this line, up to a half.
+    return lists_cost(h, A, B, columns_of(A), op, s, knn, true) <= 0.95 * staged_cost(A, B, op, swapped, knn);
+}
+// The way a call is computed: 0 the staged scan, 1 lists over all columns, 2 lists over the columns that A stores; and how.
+struct MatchWay { int way = 0; int64_t columns = 0; MatchShape s{}; MatchGrid g; MatchScratch L{}; };
+MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, int knn_k,
+                   bool with_index, bool index_has_lists) {
+    MatchWay w;
+    const bool knn = knn_k > 0;
+    if (h->match_lists != 3 && match_wanted(h, A, B, op, semiring, swapped, knn) && (!with_index || index_has_lists)) w.way = 1;
+    else if (columns_wanted(h, A, B, op, semiring, swapped, knn)) w.way = 2;
+    if (w.way == 0) return w;
+    w.columns = w.way == 2 ? columns_of(A) : A->n_cols;
+    w.s = match_shape(h->opt.lds_budget, op, B->n_rows, w.columns, B->nnz);
+    w.g = match_grid(h->opt, w.s, A->n_rows, A->nnz, B->nnz, knn);
+    w.L = layout_match_call(w.s, w.g, A->n_rows, A->nnz, B->n_rows, B->nnz, knn_k, w.way == 2 || !with_index, w.way == 2 ? A->n_cols : 0);
+    return w;
 }
 
-// The norms and the lists of B's rows.
-spd_status stage_lists(spd_handle *h, const spd_csr *B, const MatchB &mb, int op, int metric, const MetricInfo &mi, const OpParams &q) {
+
+// The norms of B's rows, and their lists.
+spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int metric, const MetricInfo &mi, const OpParams &q) {
     LaunchTimer norms(h, "norms_b", 0, 0, 0, 0, 0, 0);
     hipError_t e = launch_match_norms(h->stream, B->indptr, B->values, B->n_rows, B->nnz, metric, mi.transform, mi.norm, q.p, q.k, mb.norms);
+    if (e == hipSuccess) e = launch_match_least(h->stream, B->n_rows, mb);
     if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
     norms.done();
+    return SPD_OK;
+}
+spd_status stage_lists(spd_handle *h, const spd_csr *B, const MatchB &mb, int op, const MetricInfo &mi) {
     LaunchTimer lists(h, "lists_b", 0, 0, 0, 0, 0, mb.shape.n_tiles);
-    e = launch_match_build(h->stream, B->indptr, B->indices, B->values, B->n_rows, B->nnz, (uint32_t)B->n_cols, mb,
+    hipError_t e = launch_match_build(h->stream, B->indptr, B->indices, B->values, B->n_rows, B->nnz, (uint32_t)B->n_cols, mb,
                            match_cell_bytes(op), mi.transform);
     if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
     lists.done();
@@ -715,29 +774,46 @@ spd_status stage_lists(spd_handle *h, const spd_csr *B, const MatchB &mb, int op
 }
 
 spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, int op, int knn_k, const OpParams &q,
-                     const MetricInfo &mi, const MatchShape &s, const MatchGrid &g, const MatchScratch &L, const int64_t *a_ip,
-                     const int64_t *b_ip, size_t ip_bytes, float *out, int64_t *out_idx, float *out_dist, const spd_index *index) {
+                     const MetricInfo &mi, const MatchWay &way, const int64_t *a_ip, const int64_t *b_ip, size_t ip_bytes, float *out,
+                     int64_t *out_idx, float *out_dist, const spd_index *index) {
     const int64_t m = A->n_rows, n = B->n_rows;
-    // (the staged scan's planner refuses a row that is longer than the column count in the operand it stages)
-    auto refused = [&](const char *name, const int64_t *ip, int64_t rows, bool staged) {
-        const std::string why = check_rows(ip, rows, staged ? A->n_cols : INT64_MAX);
-        return why.empty() ? SPD_OK : refuse_plan(h, name, why);
-    };
-    const bool b_staged = knn_k == 0 && !index && swap_wanted(h, A, B, metric, nullptr);
-    spd_status st = index ? SPD_OK : refused("B", b_ip, n, b_staged);
-    if (st == SPD_OK) st = refused("A", a_ip, m, !b_staged);
-    if (st != SPD_OK) return st;
+    const MatchShape &s = way.s;
+    const MatchGrid &g = way.g;
+    const MatchScratch &L = way.L;
+    const bool compact = way.way == 2, index_lists = index && !compact;
+    spd_status st = SPD_OK;
     if (h->check_plan) {
-        std::string why = match_check(h->opt, s, g, op, m, n, A->n_cols, B->nnz);
+        std::string why = match_check(h->opt, s, g, op, m, n, way.columns, B->nnz);
         if (why.empty() && L.end > h->ws_bytes) why = "scratch";
         if (!why.empty()) return fail(h, SPD_ERR_UNSUPPORTED, "internal plan check failed: " + why);
     }
     unsigned char *ws = reinterpret_cast<unsigned char *>(h->ws);         // (run() has seen to its size)
     hipError_t e;
-    MatchB mb = index ? index->match : match_b_at(s, L.b, ws);
-    if (!index) {
-        const spd_status st_b = stage_lists(h, B, mb, op, metric, mi, q);
-        if (st_b != SPD_OK) return st_b;
+    MatchB mb = index_lists ? index->match : match_b_at(s, L.b, ws);
+    const int32_t *a_indices = A->indices;
+    spd_csr listed = *B;
+    if (!index_lists) {
+        st = stage_norms(h, B, mb, metric, mi, q);
+        if (st != SPD_OK) return st;
+        if (compact) {
+            const MatchColumns c{reinterpret_cast<uint2 *>(ws + L.c.words), reinterpret_cast<uint32_t *>(ws + L.c.sums),
+                                 reinterpret_cast<uint32_t *>(ws + L.c.totals), reinterpret_cast<uint64_t *>(ws + L.c.masks),
+                                 reinterpret_cast<uint32_t *>(ws + L.c.before), reinterpret_cast<int32_t *>(ws + L.c.a_indices),
+                                 reinterpret_cast<int64_t *>(ws + L.c.b_indptr), reinterpret_cast<int32_t *>(ws + L.c.b_indices),
+                                 reinterpret_cast<float *>(ws + L.c.b_values)};
+            LaunchTimer lt(h, "columns", 0, 0, 0, 0, 0, 0);
+            e = launch_match_columns(h->stream, A->indices, A->nnz, B->indptr, B->indices, B->values, n, B->nnz, (uint32_t)A->n_cols, c);
+            if (e != hipSuccess) return hip_fail(h, e, "column kernels");
+            lt.done();
+            a_indices = c.a_indices;
+            listed.indptr = c.b_indptr;
+            listed.indices = c.b_indices;
+            listed.values = c.b_values;
+            listed.n_cols = way.columns;
+            mb.cols = c.totals;
+        }
+        st = stage_lists(h, &listed, mb, op, mi);
+        if (st != SPD_OK) return st;
     }
     double *norms_a = reinterpret_cast<double *>(ws + L.norms_a);
     {
@@ -774,22 +850,23 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     e = hipMemcpyAsync(ws + L.rows, rows, (size_t)m * sizeof(MatchRow), hipMemcpyHostToDevice, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "upload of A's rows");
     MatchArgs a;
-    a.a_indices = A->indices;
+    a.a_indices = a_indices;
     a.a_values = A->values;
     a.rows = reinterpret_cast<const MatchRow *>(ws + L.rows);
     a.m = (int32_t)m;
     a.norms_a = norms_a;
-    a.b_indptr = B->indptr;
+    a.b_indptr = listed.indptr;
     a.b_nnz = B->nnz;
     a.b = mb;
     a.n = n;
-    a.k = (uint32_t)A->n_cols;
+    a.k = (uint32_t)way.columns;
     a.transform = mi.transform;
     a.q = q;
     a.m_shared = (int32_t)shared;
     a.slices = g.slices;
     a.groups = g.groups;
     a.by_xcd = g.by_xcd;
+    a.run = g.run;
     a.out = out;
     a.knn_k = knn_k;
     a.knn_part = reinterpret_cast<KnnEntry *>(ws + L.part);
@@ -818,6 +895,12 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     return SPD_OK;
 }
 
+// (the staged scan's planner refuses a row that is longer than the column count in the operand it stages)
+spd_status refuse_rows(spd_handle *h, const char *name, const int64_t *ip, int64_t rows, int64_t n_cols, bool staged) {
+    const std::string why = check_rows(ip, rows, staged ? n_cols : INT64_MAX);
+    return why.empty() ? SPD_OK : refuse_plan(h, name, why);
+}
+
 spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, float p, const spd_semiring *semiring,
                int knn_k, float *out, int64_t *out_idx, float *out_dist, const spd_index *index = nullptr) {
     for (auto &t : h->timed) { h->event_pool.push_back(t.start); h->event_pool.push_back(t.stop); }
@@ -827,24 +910,19 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     if (e != hipSuccess) return hip_fail(h, e, "hipSetDevice");
     metric = effective_metric(metric, p);
     const int op = product_of(h, metric, p);
-    MatchShape match{};
-    MatchGrid match_g;
-    MatchScratch match_l{};
     const bool swap = knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
-    bool lists = match_wanted(h, A, B, op, semiring, swap, knn_k > 0) && (!index || index->match.list);
+    const MatchWay way = match_way(h, A, B, op, semiring, swap, knn_k, index != nullptr, index && index->match.list);
+    bool lists = way.way != 0;
     if (lists) {
-        match = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz);
-        match_g = match_grid(h->opt, match, A->n_rows, A->nnz, B->nnz, knn_k > 0);
-        match_l = layout_match_call(match, match_g, A->n_rows, B->n_rows, B->nnz, knn_k, index == nullptr);
-        if (index && (index->match_op != op || std::memcmp(&index->match.shape, &match, sizeof match) != 0))
+        if (way.way == 1 && index && (index->match_op != op || std::memcmp(&index->match.shape, &way.s, sizeof way.s) != 0))
             lists = false;              // (created under other options)
         // (a caller's scratch that does not hold the lists still serves the staged scan)
-        if (h->ws_external && match_l.end > h->ws_bytes) lists = false;
+        if (h->ws_external && way.L.end > h->ws_bytes) lists = false;
         // (and so does a device that has no memory left for them; so much is not asked for again)
         if (lists && !h->ws_external) {
-            const spd_status st = match_l.end < h->lists_refused ? ensure_workspace(h, match_l.end) : SPD_ERR_WORKSPACE;
+            const spd_status st = way.L.end < h->lists_refused ? ensure_workspace(h, way.L.end) : SPD_ERR_WORKSPACE;
             if (st == SPD_ERR_WORKSPACE) {
-                h->lists_refused = std::min(h->lists_refused, match_l.end);
+                h->lists_refused = std::min(h->lists_refused, way.L.end);
                 h->err.clear();
                 (void)hipGetLastError();
                 lists = false;
@@ -901,9 +979,15 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     }
     if (a_ip[m] != A->nnz || (!index && b_ip[n] != B->nnz)) return fail(h, SPD_ERR_BAD_CSR, "indptr[n_rows] != nnz");
     lap("indptr d2h");
+    if (lists) {
+        const bool b_staged = knn_k == 0 && !index && swap;
+        st = index ? SPD_OK : refuse_rows(h, "B", b_ip, n, A->n_cols, b_staged);
+        if (st == SPD_OK) st = refuse_rows(h, "A", a_ip, m, A->n_cols, !b_staged);
+        if (st != SPD_OK) return st;
+    }
     if (lists)
-        return run_match(h, A, B, metric, op, knn_k, op_params(metric, p, A->n_cols, nullptr), metric_info(metric), match, match_g,
-                         match_l, a_ip, b_ip, ip_bytes, out, out_idx, out_dist, index);
+        return run_match(h, A, B, metric, op, knn_k, op_params(metric, p, A->n_cols, nullptr), metric_info(metric), way, a_ip, b_ip,
+                         ip_bytes, out, out_idx, out_dist, index);
 
     // ---- B first: plan it, upload its plan and start the repack, so that the device is
     //      busy while the host plans A (an index brings all of that with it) ---------------
@@ -1308,10 +1392,11 @@ spd_status spd_workspace_bytes(const spd_handle *h, const spd_csr *A, const spd_
     for (const int as_metric : {(int)metric, metric == SPD_MINKOWSKI ? (int)SPD_L1 : (int)metric}) {
         const int op = product_of(h, as_metric, 2.0f);
         const bool swap = k_neighbors == 0 && swap_wanted(h, A, B, as_metric, nullptr);
-        if (!match_wanted(h, A, B, op, nullptr, swap, k_neighbors > 0)) continue;
-        const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, B->n_cols, B->nnz);
-        const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, k_neighbors > 0);
-        *bytes = std::max(*bytes, layout_match_call(s, g, A->n_rows, B->n_rows, B->nnz, k_neighbors, true).end);
+        // (an index without lists leaves a call to the way behind them)
+        for (const bool index : {false, true}) {
+            const MatchWay w = match_way(h, A, B, op, nullptr, swap, k_neighbors, index, false);
+            if (w.way != 0) *bytes = std::max(*bytes, w.L.end);
+        }
     }
     return SPD_OK;
 }
@@ -1504,7 +1589,8 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         if (hipMalloc(&ix->match_dev, lists.end) == hipSuccess) {
             ix->match = match_b_at(shape, lists, reinterpret_cast<unsigned char *>(ix->match_dev));
             ix->match_op = op;
-            st = stage_lists(h, Index, ix->match, op, run_as, mi, q);
+            st = stage_norms(h, Index, ix->match, run_as, mi, q);
+            if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, mi);
             if (st != SPD_OK) return st;
         } else {                         // (no memory left for the lists: the packed copy serves every call)
             ix->match_dev = nullptr;
@@ -1628,7 +1714,7 @@ spd_status spd_set_option(spd_handle *h, const char *name, int64_t value) {
         if (value < 0 || value > 3) return fail(h, SPD_ERR_UNSUPPORTED, "cuckoo_attempts must lie in [0, 3]");
         h->cuckoo_attempts = (int)value;
     } else if (s == "match_lists") {
-        if (value < 0 || value > 2) return fail(h, SPD_ERR_UNSUPPORTED, "match_lists must be 0, 1 or 2");
+        if (value < 0 || value > 3) return fail(h, SPD_ERR_UNSUPPORTED, "match_lists must be 0, 1, 2 or 3");
         h->match_lists = (int)value;
         h->lists_refused = SIZE_MAX;
     } else if (s == "swap_operands") {
@@ -1695,7 +1781,7 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     MatchLayout L;
     out->index_bytes = index_keeps_lists(&h, &B, op, kept, L) ? (int64_t)L.end : 0;
     out->consistent = match_check(h.opt, s, g, op, a_rows, b_rows, n_cols, b_nnz).empty();
-    out->scratch_bytes = (int64_t)layout_match_call(s, g, a_rows, b_rows, b_nnz, k_neighbors, !with_index).end;
+    out->scratch_bytes = (int64_t)layout_match_call(s, g, a_rows, a_nnz, b_rows, b_nnz, k_neighbors, !with_index, 0).end;
     return SPD_OK;
 }
 

@@ -15,6 +15,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "spd_kernels.h"
 
 namespace spd {
@@ -39,7 +41,7 @@ struct MatchShape {
 MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, int64_t nnz);
 
 struct MatchB {
-    uint2 *list;            // {byte offset of the row's sums in a strip, value bits}, by tile, column block and column;
+    uint2 *list;            // {byte offset of the row's first sum in a strip, value bits}, by tile, column block and column;
                             // a dense column: tile_rows values, 0 where the row has none.  (A stored zero keeps
                             // its place in a list and points to a spare cell behind the strip's last; kMatchSpare
                             // entries at the end.)
@@ -47,7 +49,9 @@ struct MatchB {
                             // column + its block's number (a block has a word more for its last list's end);
                             // kMatchDense is set where the column is dense
     double *norms;          // n * 2, derived
+    double *least;          // n_tiles * 2: the norms of a tile's row of the least first norm
     MatchShape shape;
+    const uint32_t *cols;   // nullptr, or on the device how many columns there are (no more than the shape was made for)
 };
 constexpr uint32_t kMatchDense = 0x80000000u;
 
@@ -67,22 +71,41 @@ struct MatchArgs {
     int32_t m_shared;             // the first rows, which the wavefronts of a workgroup share
     int32_t slices, groups;       // grid: groups of tiles (g, g + groups, ...) x slices of A's rows (s, s + slices, ...)
     int32_t by_xcd;               // 1: the slices of a group share an XCD
+    int32_t run;                  // tiles of its group that a wavefront goes through with a row
     float *out;                   // pairwise: m x n
     int32_t knn_k;                // 0: pairwise
     KnnEntry *knn_part;           // (row * groups + group) * knn_k
     unsigned long long *knn_tau;  // per row: the tightest k-th (distance, index) key of any group
 };
 
+// Both operands over the columns that A stores (spd_match_columns.hip).
+struct MatchColumns {
+    uint2 *words;                 // per 32 columns: the marked ones' bits, and how many are marked before
+    uint32_t *sums, *totals;      // scratch of the scans; {columns, entries of B} that stay
+    uint64_t *masks;              // per 64 entries of B: which stay
+    uint32_t *before;             // ... and how many stay before
+    int32_t *a_indices;
+    int64_t *b_indptr;
+    int32_t *b_indices;
+    float *b_values;
+};
+
+constexpr int64_t kMatchMostColumns = 1 << 28;    // that are renumbered (16 bytes per 64 of them)
 constexpr uint32_t kBuildDense = 32;            // dense columns of a block at most
-// Upper bound of the kernel's static __shared__ use (one sum per pair: 64 words to a wavefront).
-constexpr int64_t match_static_lds(int64_t cell_bytes) { return 256 + (cell_bytes <= 8 ? 16 * 256 : 0); }
 constexpr int kMatchStagingKind = 6;            // how spd_profile_read names this kernel's staging
 constexpr int64_t kMatchL2Bytes = 4 << 20;      // of one XCD
+// Bytes that a pair's sums take in a strip: its doubles and its count.
+SPD_HD constexpr int match_doubles(int op) {
+    return op == OP_DOT || op == OP_L1 || op == OP_CANB || op == OP_KL ? 1 : (op == OP_JS || op == OP_MINK || op == OP_MINK_ANY ? 2 : 0);
+}
+SPD_HD constexpr int match_counts(int op) { return op == OP_HAMM || op == OP_CNT || op == OP_KL || op == OP_MINK || op == OP_MINK_ANY ? 1 : 0; }
+SPD_HD constexpr int match_cell_bytes(int op) { return 8 * match_doubles(op) + 4 * match_counts(op); }
+SPD_HD constexpr uint32_t match_strip_bytes(int cell_bytes, int tile_rows) { return ((uint32_t)(tile_rows + 1) * (uint32_t)cell_bytes + 7u) / 8u * 8u; }
 // Wavefronts of a workgroup, of which a compute unit holds one: the strips share its LDS, and where a pair's
-// sums take 16 bytes or more, fewer and longer strips keep the lists longer than half a wavefront.
-constexpr int match_waves(size_t cell_bytes) { return cell_bytes >= 16 ? 12 : 16; }
-// Bytes a pair's sums take in a strip.
-int match_cell_bytes(int op);
+// sums take 16 bytes or more, there are fewer and longer strips.
+SPD_HD constexpr int match_waves(int cell_bytes) { return cell_bytes >= 16 ? 12 : 16; }
+// Upper bound of the kernel's static __shared__ use (64 words to a wavefront, the locks).
+SPD_HD constexpr int64_t match_static_lds(int cell_bytes) { return 256 + match_waves(cell_bytes) * 256; }
 // The products the column lists serve.
 SPD_HD constexpr bool match_serves(int op) {
     return op == OP_DOT || op == OP_L1 || op == OP_CANB || op == OP_HAMM || op == OP_KL || op == OP_JS || op == OP_CNT ||
@@ -91,8 +114,11 @@ SPD_HD constexpr bool match_serves(int op) {
 
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
                               int metric, int transform, int norm, float p, double k, double *norms);
+hipError_t launch_match_least(hipStream_t st, int64_t n_rows, const MatchB &b);
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
                               int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int transform);
+hipError_t launch_match_columns(hipStream_t st, const int32_t *a_indices, int64_t a_nnz, const int64_t *b_indptr, const int32_t *b_indices,
+                                const float *b_values, int64_t b_rows, int64_t b_nnz, uint32_t n_cols, const MatchColumns &c);
 // k-NN: the rows' bounds, and where each row's candidate lists lie.
 hipError_t launch_match_knn_begin(hipStream_t st, unsigned long long *tau, int64_t *row_off, int32_t *row_lists, KnnEntry *part,
                                   int64_t m, int lists, int k);

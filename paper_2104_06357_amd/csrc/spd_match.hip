@@ -54,17 +54,22 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
 // depends on it, because a row of B appears in a list at most once.
 // ------------------------------------------------------------------------------------
 constexpr int kBuildThreads = 1024;
+// Rows of a tile whose stretch of a block is longer than kBuildPasses loads of their lanes are left to whole wavefronts, as many of
+// them as fit the list (500,000 rows of 1 to 50,000 entries over 242,000 columns: four lanes went 160 times through
+// memory for one row while the workgroup waited: 7.6 ms for all lists, and 2.6 with whole wavefronts).
+constexpr int kBuildLong = 64, kBuildPasses = 8;
 
 template <int G>
 __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                         const float *__restrict__ values, int64_t n_rows, int64_t nnz,
-                                                                        uint32_t cols, MatchB b, uint32_t blocks_per_wg, uint32_t wgs, int cell_bytes,
+                                                                        uint32_t most_cols, MatchB b, uint32_t blocks_per_wg, uint32_t wgs, int unit,
                                                                         int transform) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     __shared__ uint32_t s_wave[kBuildThreads / kWave];
-    __shared__ uint32_t s_dense[kBuildDense];
+    __shared__ uint32_t s_dense[kBuildDense], s_long[kBuildLong], s_longs;
     const MatchShape &shape = b.shape;
-    const uint32_t block_cols = 1u << shape.block_shift, blocks = (uint32_t)shape.blocks;
+    const uint32_t cols = b.cols ? min(*b.cols, most_cols) : most_cols;
+    const uint32_t block_cols = 1u << shape.block_shift, blocks = min((uint32_t)shape.blocks, (cols + block_cols - 1u) >> shape.block_shift);
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int nw = kBuildThreads / kWave, groups = kBuildThreads / G, kRows = 4;
     const int sub = tid % G, group = tid / G, group_shift = lane / G * G;
@@ -112,6 +117,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     for (uint32_t block = block_first; block < block_last; ++block) {
         const uint32_t c0 = block * block_cols, range = min(block_cols, cols - c0);
         for (uint32_t i = tid; i < block_cols; i += kBuildThreads) s_count[i] = 0u;
+        if (tid == 0) s_longs = 0u;
         __syncthreads();
         // count: G lanes to the row, four rows' first loads in flight together
         for (int r0 = group; r0 < rows; r0 += kRows * groups) {
@@ -126,18 +132,52 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 const int r = r0 + u * groups;
-                for (;;) {
+                for (int pass = 1;; ++pass) {
                     const bool in = c[u] - c0 < range;
                     if (in) atomicAdd(&s_count[c[u] - c0], 1u);
                     const uint32_t n = (uint32_t)__popcll((__ballot(in) >> group_shift) & group_mask);
                     pos[u] += n;
                     if (n < (uint32_t)G) break;
+                    if (pass >= kBuildPasses) {
+                        uint32_t at = (uint32_t)kBuildLong;
+                        if (sub == 0) at = atomicAdd(&s_longs, 1u);
+                        at = (uint32_t)__shfl((int)at, group_shift);
+                        if (at < (uint32_t)kBuildLong) {
+                            if (sub == 0) s_long[at] = (uint32_t)r;
+                            break;
+                        }
+                        pass = -0x40000000;                      // (no place left: these lanes go on)
+                    }
                     c[u] = pos[u] + sub < end[u] ? (uint32_t)indices[row_first + pos[u] + sub] : 0xFFFFFFFFu;
                 }
                 if (r < rows && sub == 0) s_next[r] = pos[u];
             }
         }
         __syncthreads();
+        const int longs = (int)min(s_longs, (uint32_t)kBuildLong);
+        if (longs > 0) {
+            for (int at = wave; at < longs; at += nw) {
+                const int r = (int)s_long[at];
+                uint32_t pos = s_next[r];
+                const uint32_t end = s_end[r];
+                for (uint32_t n = kRows * 64u; n == kRows * 64u;) {
+                    uint32_t c[kRows];
+#pragma unroll
+                    for (int u = 0; u < kRows; ++u)
+                        c[u] = pos + (uint32_t)(u * 64 + lane) < end ? (uint32_t)indices[row_first + pos + (uint32_t)(u * 64 + lane)] : 0xFFFFFFFFu;
+                    n = 0u;
+#pragma unroll
+                    for (int u = 0; u < kRows; ++u) {
+                        const bool in = c[u] - c0 < range;
+                        if (in) atomicAdd(&s_count[c[u] - c0], 1u);
+                        n += (uint32_t)__popcll(__ballot(in));
+                    }
+                    pos += n;
+                }
+                if (lane == 0) s_next[r] = pos;
+            }
+            __syncthreads();
+        }
         // which columns are dense: the first of the block that reach the mark, in column order (so that the
         // same columns are dense in every run)
         auto scan4 = [&](uint32_t mine, uint32_t &carry) {          // exclusive over the workgroup, from `carry` on
@@ -202,14 +242,35 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         __threadfence_block();
         __syncthreads();
         // place
+        auto place = [&](uint32_t c, float v, int r) {
+            const float t = transform_value(transform, v);
+            if (c - c0 >= range) return;
+            uint32_t *count = &s_count[c - c0];
+            uint32_t at = *count & ~kMatchDense;
+            if (*count & kMatchDense) {
+                at += (uint32_t)r >> 1;
+                if (at < shape.stage) reinterpret_cast<float *>(&s_stage[at])[r & 1] = t;
+                else if (at < room) reinterpret_cast<float *>(&list[at])[r & 1] = t;
+            } else {
+                // (a stored zero is absent: it goes to the spare row behind the tile's)
+                const uint2 entry = make_uint2((uint32_t)(t != 0.0f ? r : T) * (uint32_t)unit, __float_as_uint(t));
+                at = atomicAdd(count, 1u);
+                if (at < shape.stage) s_stage[at] = entry;
+                else if (at < room) list[at] = entry;
+            }
+        };
+        constexpr uint32_t kShort = (uint32_t)(G * kBuildPasses);         // a stretch beyond it may be a whole wavefront's
         for (int r0 = group; r0 < rows; r0 += kRows * groups) {
             uint32_t pos[kRows], end[kRows], c[kRows];
             float v[kRows];
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 const int r = r0 + u * groups;
-                pos[u] = (r < rows ? s_cur[r] : 0u) + sub;
+                pos[u] = r < rows ? s_cur[r] : 0u;
                 end[u] = r < rows ? s_next[r] : 0u;
+                if (longs > 0 && end[u] - pos[u] >= kShort)
+                    for (int at = 0; at < longs; ++at) end[u] = s_long[at] == (uint32_t)r ? pos[u] : end[u];
+                pos[u] += sub;
                 c[u] = pos[u] < end[u] ? (uint32_t)indices[row_first + pos[u]] : 0xFFFFFFFFu;
                 v[u] = pos[u] < end[u] ? values[row_first + pos[u]] : 0.0f;
             }
@@ -217,25 +278,26 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             for (int u = 0; u < kRows; ++u) {
                 const int r = r0 + u * groups;
                 while (pos[u] < end[u]) {
-                    const float t = transform_value(transform, v[u]);
-                    if (c[u] - c0 < range) {
-                        uint32_t *count = &s_count[c[u] - c0];
-                        uint32_t at = *count & ~kMatchDense;
-                        if (*count & kMatchDense) {
-                            at += (uint32_t)r >> 1;
-                            if (at < shape.stage) reinterpret_cast<float *>(&s_stage[at])[r & 1] = t;
-                            else if (at < room) reinterpret_cast<float *>(&list[at])[r & 1] = t;
-                        } else {
-                            // (a stored zero is absent: it goes to the spare cell behind the tile's)
-                            const uint2 entry = make_uint2((uint32_t)(t != 0.0f ? r : T) * (uint32_t)cell_bytes, __float_as_uint(t));
-                            at = atomicAdd(count, 1u);
-                            if (at < shape.stage) s_stage[at] = entry;
-                            else if (at < room) list[at] = entry;
-                        }
-                    }
+                    place(c[u], v[u], r);
                     pos[u] += G;
                     if (pos[u] < end[u]) { c[u] = (uint32_t)indices[row_first + pos[u]]; v[u] = values[row_first + pos[u]]; }
                 }
+            }
+        }
+        for (int at = wave; at < longs; at += nw) {
+            const int r = (int)s_long[at];
+            const uint32_t end = s_next[r];
+            for (uint32_t pos = s_cur[r]; pos < end; pos += kRows * 64u) {
+                uint32_t c[kRows];
+                float v[kRows];
+#pragma unroll
+                for (int u = 0; u < kRows; ++u) {
+                    const uint32_t e = pos + (uint32_t)(u * 64 + lane);
+                    c[u] = e < end ? (uint32_t)indices[row_first + e] : 0xFFFFFFFFu;
+                    v[u] = e < end ? values[row_first + e] : 0.0f;
+                }
+#pragma unroll
+                for (int u = 0; u < kRows; ++u) place(c[u], v[u], r);
             }
         }
         __syncthreads();
@@ -276,37 +338,56 @@ hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float
     return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(256) spd_match_least_kernel(const double *__restrict__ norms, int64_t n_rows, int tile_rows,
+                                                              double *__restrict__ least) {
+    __shared__ double s_least[256][2];
+    const int64_t j0 = (int64_t)blockIdx.x * tile_rows;
+    const int rows = (int)min((int64_t)tile_rows, n_rows - j0), tid = (int)threadIdx.x;
+    double d0 = __builtin_huge_val(), d1 = 0.0;
+    for (int r = tid; r < rows; r += 256) {
+        const double2 nb = *reinterpret_cast<const double2 *>(norms + (size_t)(j0 + r) * 2);
+        if (nb.x < d0) { d0 = nb.x; d1 = nb.y; }
+    }
+    s_least[tid][0] = d0;
+    s_least[tid][1] = d1;
+    for (int half = 128; half >= 1; half >>= 1) {
+        __syncthreads();
+        if (tid < half && s_least[tid + half][0] < s_least[tid][0]) {
+            s_least[tid][0] = s_least[tid + half][0];
+            s_least[tid][1] = s_least[tid + half][1];
+        }
+    }
+    if (tid < 2) least[(size_t)blockIdx.x * 2 + tid] = s_least[0][tid];
+}
+hipError_t launch_match_least(hipStream_t st, int64_t n_rows, const MatchB &b) {
+    if (n_rows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(spd_match_least_kernel, dim3((unsigned)b.shape.n_tiles), dim3(256), 0, st, b.norms, n_rows, (int)b.shape.tile_rows, b.least);
+    return hipGetLastError();
+}
+
 MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, int64_t nnz) {
     MatchShape s{};
     const int cell = match_cell_bytes(op);
     if (cell == 0 || n <= 0 || n_cols <= 0) return s;
-    s.waves = match_waves((size_t)cell);
+    s.waves = match_waves(cell);
     const int64_t strip = (lds_budget - match_static_lds(cell)) / s.waves;
-    int64_t most = (strip / cell - 1) / kWave * kWave;          // (a spare cell behind them)
+    int64_t most = ((strip - 7) / cell - 1) / kWave * kWave;    // (a spare row behind them)
     if (most < kWave) return s;
     const double per_cell = (double)nnz / (double)n / (double)n_cols;
     if (cell <= 8) {
         // The lists of a tile that the workgroups of an XCD walk together: within twice its L2 (65,536 x 26,000 rows of 7 %,
         // L1: tiles of 256 rows 33.8 ms, 384 29.9, 512 28.6, 640 31.2, 768 34.0, 1,216 36.7), as long as a list is two
         // chunks of 16 on the mean; where tiles of all the LDS are within it, the largest (300,000 rows of 230, cosine:
-        // 576 rows 9.0 ms, 832 7.0, 1,216 5.7).
+        // 576 rows 9.0 ms, 832 7.0, 1,216 5.7).  (Dearer products are bound by their arithmetic: Jensen-Shannon on the
+        // 65,536 rows 55.3, 51.8, 51.4 and, with all the LDS holds, 832 rows, 51.1.)
         const int64_t within = (int64_t)((double)(2 * kMatchL2Bytes / 8) / std::max(per_cell * (double)n_cols, 1e-12)) / kWave * kWave;
         const int64_t least = ((int64_t)(32.0 / std::max(per_cell, 1e-9)) + kWave - 1) / kWave * kWave;
         most = std::max<int64_t>(kWave, std::min(most, std::max(within, least)));
-    } else if (per_cell * (double)most < 256.0) {
-        // A list of 65 entries takes two steps of 64 like one of 128.  Where the mean list of the largest tile
-        // is between one and four steps long, a smaller tile's that just fills whole steps (with room for the
-        // spread of a random column's count) is cheaper: 65,536 x 26,000 rows of 7 %, lists of 54 instead of 81.
-        for (int q = 3; q >= 1; --q) {
-            const double root = std::sqrt(64.0 * q + 0.4225) - 0.65;             // mean + 1.3 sqrt(mean) = 64 q
-            const int64_t rows = (int64_t)(root * root / std::max(per_cell, 1e-12)) / kWave * kWave;
-            if (rows >= kWave && rows <= most) { most = rows; break; }
-        }
     }
     const int64_t tiles = (n + most - 1) / most;
     if (tiles > (1 << 30)) return s;
     s.tile_rows = (int32_t)(((n + tiles - 1) / tiles + kWave - 1) / kWave * kWave);
-    s.lds_bytes = (uint32_t)(s.waves * (s.tile_rows + 1) * cell);
+    s.lds_bytes = (uint32_t)s.waves * match_strip_bytes(cell, s.tile_rows);
     // A block of columns: an eighth of the LDS for counters at most, and entries for four fifths, on the mean,
     // of what the row positions leave for its piece of the lists (the rest of a fuller block goes straight to
     // memory; narrower blocks read a row's lines more often).  Dense columns may take half as much again.
@@ -345,10 +426,10 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
     auto go = [&](auto g) {
         auto kern = spd_match_build_kernel<decltype(g)::value>;
         static std::atomic<uint32_t> allowed[kMatchDevices];
-        hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes);
+        hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(kern, dim3((unsigned)s.n_tiles * wgs), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
-                           nnz, k, b, per_wg, wgs, cell_bytes, transform);
+                           nnz, k, b, per_wg, wgs, cell_bytes >= 8 ? 8 : 4, transform);
         return hipGetLastError();
     };
     if (per_row >= 8.0) return go(std::integral_constant<int, 16>{});
@@ -375,21 +456,6 @@ hipError_t launch_match_knn_begin(hipStream_t st, unsigned long long *tau, int64
 
 hipError_t launch_match_a(hipStream_t st, int op, const MatchArgs &args, uint32_t lds_bytes);
 hipError_t launch_match_b(hipStream_t st, int op, const MatchArgs &args, uint32_t lds_bytes);
-
-int match_cell_bytes(int op) {
-    switch (op) {
-    case OP_DOT: return sizeof(MatchCell<OP_DOT>);
-    case OP_L1: return sizeof(MatchCell<OP_L1>);
-    case OP_CANB: return sizeof(MatchCell<OP_CANB>);
-    case OP_HAMM: return sizeof(MatchCell<OP_HAMM>);
-    case OP_CNT: return sizeof(MatchCell<OP_CNT>);
-    case OP_KL: return sizeof(MatchCell<OP_KL>);
-    case OP_JS: return sizeof(MatchCell<OP_JS>);
-    case OP_MINK: return sizeof(MatchCell<OP_MINK>);
-    case OP_MINK_ANY: return sizeof(MatchCell<OP_MINK_ANY>);
-    default: return 0;
-    }
-}
 
 hipError_t launch_match(hipStream_t st, int op, const MatchArgs &args, uint32_t lds_bytes) {
     switch (op) {

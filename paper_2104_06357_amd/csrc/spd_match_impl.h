@@ -7,9 +7,85 @@ namespace spd {
 
 __device__ __forceinline__ int64_t clamp_i64(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// What a strip holds per row of the tile.
-template <int OP> struct alignas(sizeof(typename Op<OP>::Acc) == 16 ? 16 : alignof(typename Op<OP>::Acc)) MatchCell {
-    typename Op<OP>::Acc acc;
+// (LDS by address: an offset from a __shared__ array costs another addition)
+template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(uint32_t address) {
+    return (__attribute__((address_space(3))) T *)(uintptr_t)address;
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+// A strip holds a pair's sums in planes, one for each number of Op<OP>::Acc (its doubles, then its count), so that the
+// rows of neighbouring lanes lie in different banks.  `at`: LDS address of the strip, `plane`: bytes of a plane of doubles.
+template <int OP> struct Sums {
+    using Acc = typename Op<OP>::Acc;
+    static constexpr int kDoubles = match_doubles(OP), kCounts = match_counts(OP);
+    static constexpr bool kOne = kDoubles + kCounts == 1;
+    static constexpr uint32_t kUnit = kDoubles ? 8u : 4u;          // bytes from a row's first number to the next row's
+    static __device__ __forceinline__ Acc get(uint32_t at, uint32_t plane, uint32_t row) {
+        Acc x;
+        Op<OP>::init(x);
+#pragma unroll
+        for (int p = 0; p < kDoubles; ++p) {
+            const double v = *lds_at<double>(at + (uint32_t)p * plane + row * 8u);
+            __builtin_memcpy(reinterpret_cast<unsigned char *>(&x) + 8 * p, &v, 8);
+        }
+        if constexpr (kCounts) {
+            const int v = *lds_at<int>(at + (uint32_t)kDoubles * plane + row * 4u);
+            __builtin_memcpy(reinterpret_cast<unsigned char *>(&x) + 8 * kDoubles, &v, 4);
+        }
+        return x;
+    }
+    static __device__ __forceinline__ void put(uint32_t at, uint32_t plane, uint32_t row, const Acc &x) {
+#pragma unroll
+        for (int p = 0; p < kDoubles; ++p) {
+            double v;
+            __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * p, 8);
+            *lds_at<double>(at + (uint32_t)p * plane + row * 8u) = v;
+        }
+        if constexpr (kCounts) {
+            int v;
+            __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * kDoubles, 4);
+            *lds_at<int>(at + (uint32_t)kDoubles * plane + row * 4u) = v;
+        }
+    }
+    // Adds to the sums of the row whose first number lies `offset` bytes into the strip.
+    static __device__ __forceinline__ void add(uint32_t at, uint32_t plane, uint32_t offset, const Acc &x) {
+#pragma unroll
+        for (int p = 0; p < kDoubles; ++p) {
+            double v;
+            __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * p, 8);
+            __hip_atomic_fetch_add(lds_at<double>(at + (uint32_t)p * plane + offset), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        }
+        if constexpr (kCounts) {
+            int v;
+            __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * kDoubles, 4);
+            __hip_atomic_fetch_add(lds_at<int>(at + (uint32_t)kDoubles * plane + (kDoubles ? offset >> 1 : offset)), v, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WAVEFRONT);
+        }
+    }
+    // A strip of one number: the row's, which becomes zero bits (what init() makes).
+    static __device__ __forceinline__ Acc take(uint32_t at) {
+        Acc x;
+        if constexpr (kDoubles) {
+            const unsigned long long v = __hip_atomic_exchange(lds_at<unsigned long long>(at), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            __builtin_memcpy(&x, &v, 8);
+        } else {
+            const uint32_t v = __hip_atomic_exchange(lds_at<uint32_t>(at), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            __builtin_memcpy(&x, &v, 4);
+        }
+        return x;
+    }
+    static __device__ __forceinline__ bool is_zero(const Acc &x) {
+        if constexpr (kDoubles) {
+            unsigned long long v;
+            __builtin_memcpy(&v, &x, 8);
+            return v == 0ull;
+        } else {
+            uint32_t v;
+            __builtin_memcpy(&v, &x, 4);
+            return v == 0u;
+        }
+    }
 };
 
 // One column both rows store: the products of Op<OP>, without the tests for absent entries that the
@@ -56,25 +132,6 @@ template <typename Acc> __device__ __forceinline__ void pin(Acc &t, uint32_t &ce
     __builtin_memcpy(&t, w, sizeof(Acc));
 }
 
-// (the cell by its LDS address: an offset from a __shared__ array costs another addition)
-template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(uint32_t address) {
-    return (__attribute__((address_space(3))) T *)(uintptr_t)address;
-}
-__device__ __forceinline__ uint32_t lds_address(const void *p) {
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
-}
-template <typename Acc> __device__ __forceinline__ void match_add(uint32_t cell, const Acc &t) {
-    if constexpr (sizeof(Acc) == 8) {
-        double v;
-        __builtin_memcpy(&v, &t, 8);
-        __hip_atomic_fetch_add(lds_at<double>(cell), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    } else {
-        int v;
-        __builtin_memcpy(&v, &t, 4);
-        __hip_atomic_fetch_add(lds_at<int>(cell), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    }
-}
-
 // Inclusive sum and maximum over the wavefront's lanes (the maximum of values that are not negative).
 template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_or_zero(int v) {
     return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
@@ -106,22 +163,22 @@ template <int I> __device__ __forceinline__ float row_lane(float v) { return __u
 constexpr int kMatchUnroll = 4;          // list steps whose loads are in flight together
 
 template <int OP, bool KNN>
-__global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) spd_match_kernel(const MatchArgs args) {
+__global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd_match_kernel(const MatchArgs args) {
     using O = Op<OP>;
-    using Cell = MatchCell<OP>;
+    using S = Sums<OP>;
+    using Acc = typename O::Acc;
     // D: 64-row pieces of a dense column that are summed in registers together; the largest tiles hold 19 for one
     // fp64 sum (one round of 19 against two of 10: 2,048 queries of 300,000 rows of 230, 10.5 -> 10.2 ms; 13 and 6
     // leave half a round idle: 11.3), 39 for a count and 13 for two sums
-    constexpr int U = kMatchUnroll, D = sizeof(Cell) == 8 ? 19 : (sizeof(Cell) == 4 ? 13 : 7), nw = match_waves(sizeof(Cell));
+    constexpr int U = kMatchUnroll, D = S::kOne ? (S::kDoubles ? 19 : 13) : 7, nw = match_waves(match_cell_bytes(OP));
     extern __shared__ __align__(16) unsigned char dyn[];
     __shared__ int s_next;
     __shared__ int s_lock[KNN ? kMatchLocks : 1];
-    __shared__ int s_owner[sizeof(Cell) <= 8 ? nw : 1][sizeof(Cell) <= 8 ? kWave : 1];
+    __shared__ int s_owner[nw][kWave];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
     const int T = args.b.shape.tile_rows;
-    const uint32_t strip_bytes = (uint32_t)(T + 1) * (uint32_t)sizeof(Cell);
-    unsigned char *strip = dyn + (uint32_t)wave * strip_bytes;
-    const uint32_t strip_at = (uint32_t)wave_uniform((int)lds_address(strip));
+    const uint32_t strip_bytes = match_strip_bytes(match_cell_bytes(OP), T), plane = (uint32_t)(T + 1) * 8u;
+    const uint32_t strips_at = lds_address(dyn), strip_at = (uint32_t)wave_uniform((int)(strips_at + (uint32_t)wave * strip_bytes));
     // Workgroups go round the eight XCDs in turn: with `by_xcd` the slices of one group of tiles, which
     // read the same lists at about the same time, share an XCD and its L2.
     int group, slice;
@@ -135,14 +192,13 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
     }
     if (group >= args.b.shape.n_tiles) return;
     const int my_tiles = (args.b.shape.n_tiles - group + args.groups - 1) / args.groups;      // group, group + groups, ...
-    Cell zero;
-    O::init(zero.acc);
-    for (int i = lane; i <= T; i += kWave) reinterpret_cast<Cell *>(strip)[i] = zero;
+    Acc zero;
+    O::init(zero);
+    for (int i = lane; i <= T; i += kWave) S::put(strip_at, plane, (uint32_t)i, zero);
     if (tid == 0) s_next = 0;
     if (KNN && tid < kMatchLocks) s_lock[tid] = 0;
     __syncthreads();
 
-    const uint32_t lane8 = (uint32_t)lane * 8u;
     // 64 entries of a row of A, one per lane, on their way to the strip: first the entries, then the lists of
     // their columns, then the lists' entries.  Each stage is loaded while the stage before it is at work on
     // something else, so that the three round trips to memory are not waited for in turn.
@@ -161,8 +217,11 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
         Lists y{0u, 0u, 0.0f};
         if (x.c < args.k) {
             const uint32_t at = x.c + (x.c >> args.b.shape.block_shift);
-            y.first = ptr[at];
-            y.last = ptr[at + 1];
+            // (both in one load: 64 lanes at as many lines take the L1 as long for four bytes as for eight)
+            struct __attribute__((packed, aligned(4))) Two { uint32_t first, last; };
+            const Two two = *reinterpret_cast<const Two *>(ptr + at);
+            y.first = two.first;
+            y.last = two.last;
         }
         y.a = x.v;
         return y;
@@ -172,7 +231,7 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
         const uint32_t lane4 = (uint32_t)lane * 4u;
         for (int i0 = 0; i0 < T; i0 += D * kWave) {
             typename O::Acc sum[D];
-            float cur[D], nxt[D];
+            float cur[D];
 #pragma unroll
             for (int d = 0; d < D; ++d) O::init(sum[d]);
             // (past the tile's end what lies behind the column is read, or the spare entries at the end of the lists, and not added)
@@ -187,84 +246,41 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
                 for (int d = 0; d < D; ++d) dense_visit<OP>(sum[d], ae, from[d], args.q);
             };
             uint64_t left = mask;
-            int e = (int)__builtin_ctzll(left);
-            fetch(cur, e);
-            for (;;) {
-                left &= left - 1;
-                const int e1 = left ? (int)__builtin_ctzll(left) : e;
-                fetch(nxt, e1);
-                __builtin_amdgcn_sched_barrier(0);
-                visit(cur, e);
-                if (!left) break;
-                left &= left - 1;
-                e = left ? (int)__builtin_ctzll(left) : e1;
+            if constexpr (KNN && D == 19) {                       // (no registers for a second column in flight)
+                for (; left; left &= left - 1) {
+                    const int e = (int)__builtin_ctzll(left);
+                    fetch(cur, e);
+                    visit(cur, e);
+                }
+            } else {
+                float nxt[D];
+                int e = (int)__builtin_ctzll(left);
                 fetch(cur, e);
-                __builtin_amdgcn_sched_barrier(0);
-                visit(nxt, e1);
-                if (!left) break;
+                for (;;) {
+                    left &= left - 1;
+                    const int e1 = left ? (int)__builtin_ctzll(left) : e;
+                    fetch(nxt, e1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    visit(cur, e);
+                    if (!left) break;
+                    left &= left - 1;
+                    e = left ? (int)__builtin_ctzll(left) : e1;
+                    fetch(cur, e);
+                    __builtin_amdgcn_sched_barrier(0);
+                    visit(nxt, e1);
+                    if (!left) break;
+                }
             }
-            Cell *cells = reinterpret_cast<Cell *>(strip) + i0 + lane;
 #pragma unroll
             for (int d = 0; d < D; ++d)
                 if (i0 + d * kWave < T) {
-                    Cell cell = cells[d * kWave];
-                    O::combine(cell.acc, sum[d]);
-                    cells[d * kWave] = cell;
+                    Acc acc = S::get(strip_at, plane, (uint32_t)(i0 + lane + d * kWave));
+                    O::combine(acc, sum[d]);
+                    S::put(strip_at, plane, (uint32_t)(i0 + lane + d * kWave), acc);
                 }
         }
     };
-    // Several sums per pair: a step is up to 64 entries of one list, and no two lanes of a step meet in one row's sums.
-    auto walk_steps = [&](const unsigned char *__restrict__ list, uint32_t first, uint32_t last, float a) {
-        // steps of 64 list entries: how many there are up to and including this lane's list
-        const int steps = (int)((last - first + 63u) >> 6);
-        const int incl = wave_scan_add(steps);
-        const int total = __builtin_amdgcn_readlane(incl, 63);
-        if (total == 0) return;
-        const uint32_t base8 = first * 8u - 512u * (uint32_t)(incl - steps);      // step t reads from byte base8 + 512 t on
-        const uint32_t last8 = last * 8u;
-        // A step is described by scalars alone (where it reads, how many bytes are its list's, A's value): the
-        // lanes' part of it is one load, the lookup and the sum.  A short list's load runs into the next one
-        // (or the spare entries at the end of the lists), and those lanes add nothing.
-        uint2 cur[U], nxt[U];
-        float cur_a[U], nxt_a[U];
-        uint32_t cur_n[U], nxt_n[U];
-        auto fetch = [&](uint2 (&into)[U], float (&av)[U], uint32_t (&bytes)[U], int t0) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = min(t0 + u, total - 1);
-                const int e = (int)__popcll(__ballot(incl <= t));
-                const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base8, e) + 512u * (uint32_t)t;
-                const uint32_t left = (uint32_t)__builtin_amdgcn_readlane((int)last8, e) - at;
-                av[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), e));
-                bytes[u] = t0 + u < total ? left : 0u;           // (steps past the last one read it again and add nothing)
-                into[u] = *reinterpret_cast<const uint2 *>((list + at) + lane8);
-            }
-        };
-        auto add = [&](const uint2 (&from)[U], const float (&av)[U], const uint32_t (&bytes)[U]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (lane8 < bytes[u]) {
-                    Cell *cell = reinterpret_cast<Cell *>(strip + from[u].x);
-                    Cell c = *cell;
-                    match_visit<OP>(c.acc, av[u], __uint_as_float(from[u].y), args.q);
-                    *cell = c;
-                }
-        };
-        fetch(cur, cur_a, cur_n, 0);
-        for (int t = 0;;) {
-            fetch(nxt, nxt_a, nxt_n, t + U);
-            __builtin_amdgcn_sched_barrier(0);          // keep the loads ahead of the arithmetic
-            add(cur, cur_a, cur_n);
-            t += U;
-            if (t >= total) break;
-            fetch(cur, cur_a, cur_n, t + U);
-            __builtin_amdgcn_sched_barrier(0);
-            add(nxt, nxt_a, nxt_n);
-            t += U;
-            if (t >= total) break;
-        }
-    };
-    // One sum per pair: the lists are cut into chunks of 16 entries, and a step is four chunks, one to a quarter of the
+    // The lists are cut into chunks of 16 entries, and a step is four chunks, one to a quarter of the
     // wavefront, whichever lists they belong to (a step of one list alone is filled to 62 % by 300,000 rows of 230 and to 28 %
     // by ratings; its 13 vector instructions are 8 here: 10,000 x 10,000 rows of 38, L1, 421 -> 340 us a call, 1,024 x 300,000
     // rows of 230, cosine, 6.6 -> 5.6 ms, 1,531 x 28,301 ratings, Canberra, 1.13 -> 0.75 ms).  What bounds it now: vector
@@ -273,10 +289,13 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
     // holds chunk 4 i + g, so that step i finds its four descriptions in lane i of each quarter (a DPP broadcast).  Chunks
     // follow one another over the steps and over the lanes of a step in the order of A's columns, and LDS serves the
     // lanes that meet in one sum in ascending order: a sum is formed in the order of A's columns here too.
-    auto walk_chunks = [&](const unsigned char *__restrict__ list, uint32_t first, uint32_t last, float a) {
+    // What a walk of no more than four steps leaves behind for the k-NN's finish: the chunks it took, and the lanes' entries.
+    struct Few { int total; uint32_t cell[U], left[U]; };
+    auto walk_chunks = [&](const unsigned char *__restrict__ list, uint32_t first, uint32_t last, float a, Few &few) {
         const int chunks = (int)((last - first + 15u) >> 4);
         const int incl = wave_scan_add(chunks), excl = incl - chunks;
         const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (KNN) few.total += total;
         if (total == 0) return;
         const uint32_t base8 = first * 8u - 128u * (uint32_t)excl;               // chunk q reads from byte base8 + 128 q on
         const uint32_t last8 = last * 8u;
@@ -318,9 +337,9 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
             typename O::Acc t;
             O::init(t);
             match_visit<OP>(t, av, __uint_as_float(from.y), args.q);
-            uint32_t cell = strip_at + from.x;
-            pin(t, cell);
-            if (lane8 < left) match_add(cell, t);
+            uint32_t offset = from.x;
+            pin(t, offset);
+            if (lane8 < left) S::add(strip_at, plane, offset, t);
         };
         auto add = [&](const uint2 (&from)[U], const Chunk &c, auto block) {
             constexpr int I = decltype(block)::value * U;
@@ -337,6 +356,14 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
         Chunk c = describe(0);
         fetch(x, c, b0);
         if (total <= 4 * U) {                                   // a few entries: no more steps than they take
+            if constexpr (KNN) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) few.cell[u] = x[u].x;
+                few.left[0] = row_lane<0>(c.left);
+                few.left[1] = row_lane<1>(c.left);
+                few.left[2] = row_lane<2>(c.left);
+                few.left[3] = row_lane<3>(c.left);
+            }
             add_one(x[0], row_lane<0>(c.left), row_lane<0>(c.a));
             if (total <= 4) return;
             add_one(x[1], row_lane<1>(c.left), row_lane<1>(c.a));
@@ -370,7 +397,7 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
             c = next;
         }
     };
-    auto walk_lists = [&](int tile, const Lists &y) {
+    auto walk_lists = [&](int tile, const Lists &y, Few &few) {
         const int64_t tile_first = clamp_i64(args.b_indptr[(int64_t)tile * T], 0, args.b_nnz) + tile * args.b.shape.tile_extra;
         const unsigned char *__restrict__ list = reinterpret_cast<const unsigned char *>(args.b.list + tile_first);
         const uint32_t list_n = (uint32_t)(args.b.shape.list_entries(args.b_nnz) - kMatchSpare - tile_first);     // (no access leaves the lists)
@@ -378,80 +405,94 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
         uint32_t first = min(y.first & ~kMatchDense, list_n);
         const bool dense = (y.first & kMatchDense) != 0u && a != 0.0f && first + (uint32_t)(T / 2) <= list_n;
         const uint64_t dense_mask = __ballot(dense);
-        if (dense_mask != 0) walk_dense(list, first * 8u, a, dense_mask);
+        if (dense_mask != 0) {
+            if (KNN) few.total += 4 * U + 1;
+            walk_dense(list, first * 8u, a, dense_mask);
+        }
         const uint32_t last = a != 0.0f && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
-        if constexpr (sizeof(Cell) <= 8) walk_chunks(list, first, last, a);
-        else walk_steps(list, first, last, a);
+        walk_chunks(list, first, last, a, few);
         // (a lane reads later what other lanes of its wavefront wrote: LDS serves a wavefront in order, the
         // fence keeps the compiler to that order)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
+    // What finish() reads of a row of A, loaded while the row's last lists are walked.
+    struct RowOf { double na0, na1; uint64_t bound; };
+    auto load_row = [&](int row) {
+        RowOf r{args.norms_a[(size_t)row * 2], args.norms_a[(size_t)row * 2 + 1], kKnnUnused};
+        if constexpr (KNN) r.bound = (uint64_t)__atomic_load_n(&args.knn_tau[row], __ATOMIC_RELAXED);
+        return r;
+    };
+    // k-NN: what the tiles of a row's run have found so far.
+    uint64_t bound = kKnnUnused;          // no key above it can be among the k best
+    uint64_t best = kKnnUnused;           // the k best, ascending over the lanes ...
+    uint64_t queue = kKnnUnused;          // ... and `queued` keys that are not merged yet
+    int queued = 0;
+    bool any = false;
     // The tile's distances from the wavefront's strip, in row order: one coalesced store per 64 rows; the
-    // strip is clear again afterwards.
-    auto finish = [&](int tile, int row) {
+    // strip is clear again afterwards.  `flush`: the row's run of tiles ends here.
+    auto finish = [&](int tile, int row, const RowOf &of, const Few &few, bool flush) {
         const int64_t j0 = (int64_t)tile * T;
         const int tile_n = (int)min((int64_t)T, args.n - j0);
-        const double na0 = args.norms_a[(size_t)row * 2], na1 = args.norms_a[(size_t)row * 2 + 1];
-        // f(row of the tile, its sums, its norms) for every row, four per lane at a time, a lane's last row first
-        auto for_strip = [&](auto &&f) {
-            constexpr int F = 4;
-            for (int i0 = (tile_n - 1) / (F * kWave) * (F * kWave) + lane; i0 >= 0; i0 -= F * kWave) {
-                double2 nb[F];
-                Cell c[F];
+        const double na0 = of.na0, na1 = of.na1;
+        constexpr int F = 4;                                      // rows of a lane that are in flight together
+        // F rows of a lane from row i0 of the tile on: their sums and norms, by constant offsets from one address each (the
+        // rows beyond the tile's last repeat it), and their places cleared again.  (With an address and a bound for every row,
+        // 25 vector instructions per 64 rows, a call on 10,000 x 10,000 rows of 38 spent more on this than on the lists.)
+        const unsigned char *const norm_at = reinterpret_cast<const unsigned char *>(args.b.norms + (size_t)j0 * 2);
+        const uint32_t lane4 = (uint32_t)lane * 4u, lane16 = (uint32_t)lane * 16u;
+        auto load_round = [&](int i0, Acc (&c)[F], double2 (&nb)[F]) {
+            if (i0 + F * kWave <= tile_n) {
+                const unsigned char *from = norm_at + (uint32_t)i0 * 16u;
+#pragma unroll
+                for (int u = 0; u < F; ++u) nb[u] = *reinterpret_cast<const double2 *>(from + lane16 + u * (kWave * 16));
+#pragma unroll
+                for (int u = 0; u < F; ++u) c[u] = S::get(strip_at, plane, (uint32_t)(i0 + lane + u * kWave));
+            } else {
 #pragma unroll
                 for (int u = 0; u < F; ++u) {
-                    const int i = min(i0 + u * kWave, tile_n - 1);
-                    nb[u] = *reinterpret_cast<const double2 *>(args.b.norms + (size_t)(j0 + i) * 2);
-                    c[u] = reinterpret_cast<const Cell *>(strip)[i];
+                    const int i = min(i0 + u * kWave + lane, tile_n - 1);
+                    nb[u] = *reinterpret_cast<const double2 *>(norm_at + (uint32_t)i * 16u);
+                    c[u] = S::get(strip_at, plane, (uint32_t)i);
                 }
-#pragma unroll
-                for (int u = F - 1; u >= 0; --u)
-                    if (i0 + u * kWave < tile_n) f(i0 + u * kWave, c[u], nb[u].x, nb[u].y);
             }
+        };
+        auto clear_round = [&](int i0) {
+#pragma unroll
+            for (int u = 0; u < F; ++u)
+                if (i0 + u * kWave < T) S::put(strip_at, plane, (uint32_t)(i0 + lane + u * kWave), zero);          // (a tile is whole wavefronts of rows)
         };
         if constexpr (!KNN) {
             for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
                 constexpr int MT = decltype(metric_tag)::value;
                 float *__restrict__ out = args.out + (size_t)row * (size_t)args.n + (size_t)j0;
-                for_strip([&](int i, const Cell &c, double nb0, double nb1) {
-                    __builtin_nontemporal_store(finish_as<MT>(args.q, O::v0(c.acc), O::v1(c.acc), O::v2(c.acc), na0, na1, nb0, nb1), out + i);
-                    reinterpret_cast<Cell *>(strip)[i] = zero;
-                });
+                for (int i0 = 0; i0 < tile_n; i0 += F * kWave) {
+                    Acc c[F];
+                    double2 nb[F];
+                    load_round(i0, c, nb);
+                    unsigned char *to = reinterpret_cast<unsigned char *>(out + i0);
+                    if (i0 + F * kWave <= tile_n) {
+#pragma unroll
+                        for (int u = 0; u < F; ++u) {
+                            const float d = finish_as<MT>(args.q, O::v0(c[u]), O::v1(c[u]), O::v2(c[u]), na0, na1, nb[u].x, nb[u].y);
+                            __builtin_nontemporal_store(d, reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
+                        }
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < F; ++u)
+                            if (i0 + u * kWave + lane < tile_n)
+                                __builtin_nontemporal_store(finish_as<MT>(args.q, O::v0(c[u]), O::v1(c[u]), O::v2(c[u]), na0, na1, nb[u].x, nb[u].y),
+                                                            reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
+                    }
+                    clear_round(i0);
+                }
             });
         } else {
-            // the distances replace the sums; every lane keeps the smallest of its rows' (the first of equal ones)
-            float least_d = __builtin_huge_valf();
-            int least_i = -1;
-            for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
-                constexpr int MT = decltype(metric_tag)::value;
-                for_strip([&](int i, const Cell &c, double nb0, double nb1) {
-                    float d = finish_as<MT>(args.q, O::v0(c.acc), O::v1(c.acc), O::v2(c.acc), na0, na1, nb0, nb1);
-                    if constexpr (MT == MT_INNER) d = 0.0f - d;
-                    *reinterpret_cast<float *>(reinterpret_cast<Cell *>(strip) + i) = d;
-                    const bool closer = d <= least_d;
-                    least_d = closer ? d : least_d;
-                    least_i = closer ? i : least_i;
-                });
-            });
-            const uint64_t least = least_i >= 0 ? knn_key(least_d, (int)(j0 + least_i)) : kKnnUnused;
             const int k = args.knn_k;
             auto kth_of = [&](uint64_t sorted, int at) {
                 return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(sorted >> 32), at) << 32) |
                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)sorted, at);
             };
-            // no key above `bound` can be among the k best: the tightest k-th key of any list of this row so
-            // far, and the k-th smallest of the lanes' smallest keys (k rows of this tile lie at or below it;
-            // at k = 32 of 1,216 rows some 44 do, and the sort below sees these alone)
-            uint64_t bound = (uint64_t)__atomic_load_n(&args.knn_tau[row], __ATOMIC_RELAXED);
-            uint64_t best = kKnnUnused;                           // the k best of this tile, ascending over the lanes
-            int waiting = (int)__popcll(__ballot(least < kKnnUnused && least <= bound));
-            if (waiting > 8) {
-                const uint64_t kth = kth_of(wave_sort_desc(least, lane), kWave - k);
-                bound = kth < bound ? kth : bound;
-            }
-            const bool any = waiting > 0;
-            uint64_t queue = kKnnUnused;
-            int queued = 0;
+            bound = of.bound < bound ? of.bound : bound;          // (the tightest k-th key of any list of this row so far)
             auto merge = [&]() {
                 const uint64_t c = wave_sort_desc(lane < queued ? queue : kKnnUnused, lane);
                 best = wave_merge_asc(c < best ? c : best, lane);
@@ -460,35 +501,126 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
                 bound = now < bound ? now : bound;
                 queued = 0;
             };
-            for (int i0 = 0; i0 < tile_n; i0 += kWave) {
-                const int i = i0 + lane;
-                Cell *cell = reinterpret_cast<Cell *>(strip) + i;
-                float d = __builtin_nanf("");                     // (passes no bound)
-                if (i < tile_n) {
-                    if (any) d = *reinterpret_cast<float *>(cell);
-                    *cell = zero;
+            auto distances = [&](float (&d)[F], const Acc (&c)[F], const double2 (&nb)[F]) {
+                for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
+                    constexpr int MT = decltype(metric_tag)::value;
+#pragma unroll
+                    for (int u = 0; u < F; ++u) {
+                        d[u] = finish_as<MT>(args.q, O::v0(c[u]), O::v1(c[u]), O::v2(c[u]), na0, na1, nb[u].x, nb[u].y);
+                        if constexpr (MT == MT_INNER) d[u] = 0.0f - d[u];
+                    }
+                });
+            };
+            // Whether a row that shares no column could pass: the distances of one sum grow with the row's first norm, so none is
+            // nearer than the tile's row of the least.  (Correlation's do not.)
+            bool few_only = false;
+            if constexpr (S::kOne) {
+                if (few.total <= 4 * F && args.q.metric != MT_CORRELATION) {
+                    float d = 0.0f;
+                    for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
+                        constexpr int MT = decltype(metric_tag)::value;
+                        d = finish_as<MT>(args.q, O::v0(zero), O::v1(zero), O::v2(zero), na0, na1,
+                                          args.b.least[(size_t)tile * 2], args.b.least[(size_t)tile * 2 + 1]);
+                        if constexpr (MT == MT_INNER) d = 0.0f - d;
+                    });
+                    few_only = d == d && knn_key(d, (int)j0) > bound;
                 }
-                if (__ballot(d <= float_from_order_key((uint32_t)(bound >> 32))) == 0) continue;
-                const uint64_t key = knn_key(d, (int)(j0 + i));
-                bool pass = d == d && key <= bound;
-                uint64_t mask = __ballot(pass);
-                if (mask == 0) continue;
-                if (queued + (int)__popcll(mask) > kWave) {
-                    merge();
-                    pass = pass && key <= bound;
-                    mask = __ballot(pass);
-                    if (mask == 0) continue;
-                }
-                // the passing lanes' keys go to the queue's next places (a permutation of the lanes)
-                const int n_pass = (int)__popcll(mask);
-                const int to = pass ? queued + (int)lane_rank_in(mask) : queued + n_pass + (int)lane_rank_in(~mask);
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_permute((to & 63) << 2, (int)(uint32_t)key);
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_permute((to & 63) << 2, (int)(uint32_t)(key >> 32));
-                if (lane >= queued && lane < queued + n_pass) queue = ((uint64_t)hi << 32) | lo;
-                queued += n_pass;
             }
-            if (any) {
-                merge();                                          // (what is queued joins the tile's list, if it has one)
+            // The row's first tile goes twice through the strip: first the distances replace the sums and every lane keeps the
+            // smallest of its rows' (the first of equal ones); the k-th smallest of the lanes' smallest keys bounds the
+            // tile's k-th (k rows of this tile lie at or below it; at k = 32 of 1,216 rows some 44 do).
+            bool first = !few_only && bound == kKnnUnused, stored = false;
+            float least_d = __builtin_huge_valf();
+            int least_i = -1;
+            const int last0 = few_only ? 0 : (tile_n - 1) / (F * kWave) * (F * kWave);
+            for (int i0 = few_only && few.total == 0 ? -1 : last0; i0 >= 0;) {
+                float d[F];
+                int i[F];
+                if (stored) {
+#pragma unroll
+                    for (int u = 0; u < F; ++u) {
+                        i[u] = i0 + u * kWave + lane;
+                        d[u] = *lds_at<float>(strip_at + (uint32_t)min(i[u], tile_n - 1) * S::kUnit);
+                        d[u] = i[u] < tile_n ? d[u] : __builtin_nanf("");
+                    }
+                } else {
+                    Acc c[F];
+                    double2 nb[F];
+                    if (S::kOne && few_only) {
+                        // A few entries met the row: one lane of those that met a sum takes it and leaves its place clear
+                        if constexpr (S::kOne) {
+                            static_assert(F == U, "a step's entries to a place of the round");
+#pragma unroll
+                            for (int u = 0; u < F; ++u) {
+                                c[u] = zero;
+                                if (few.total > 4 * u && (uint32_t)(lane & 15) * 8u < few.left[u]) c[u] = S::take(strip_at + few.cell[u]);
+                            }
+#pragma unroll
+                            for (int u = 0; u < F; ++u) {
+                                i[u] = S::is_zero(c[u]) ? tile_n : (int)(few.cell[u] / S::kUnit);
+                                nb[u] = make_double2(0.0, 0.0);
+                                if (few.total > 4 * u) nb[u] = *reinterpret_cast<const double2 *>(args.b.norms + (size_t)(j0 + min(i[u], tile_n - 1)) * 2);
+                            }
+                        }
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < F; ++u) i[u] = i0 + u * kWave + lane;
+                        load_round(i0, c, nb);
+                    }
+                    distances(d, c, nb);
+#pragma unroll
+                    for (int u = 0; u < F; ++u) d[u] = i[u] < tile_n ? d[u] : __builtin_nanf("");
+                }
+                if (first && !stored) {
+#pragma unroll
+                    for (int u = F - 1; u >= 0; --u) {
+                        if (i[u] < tile_n) *lds_at<float>(strip_at + (uint32_t)i[u] * S::kUnit) = d[u];
+                        const bool closer = d[u] <= least_d;
+                        least_d = closer ? d[u] : least_d;
+                        least_i = closer ? i[u] : least_i;
+                    }
+                } else {
+                    if (!few_only) clear_round(i0);
+                    const float nearest = fminf(fminf(d[0], d[1]), fminf(d[2], d[3]));        // (ignores what is not a number)
+                    if (__ballot(nearest <= float_from_order_key((uint32_t)(bound >> 32))) != 0) {
+#pragma unroll 1
+                        for (int u = 0; u < F; ++u) {
+                            const float du = u < 2 ? (u == 0 ? d[0] : d[1]) : (u == 2 ? d[2] : d[3]);
+                            const int iu = u < 2 ? (u == 0 ? i[0] : i[1]) : (u == 2 ? i[2] : i[3]);
+                            if (__ballot(du <= float_from_order_key((uint32_t)(bound >> 32))) == 0) continue;
+                            const uint64_t key = knn_key(du, (int)(j0 + iu));
+                            bool pass = du == du && key <= bound;
+                            uint64_t mask = __ballot(pass);
+                            if (mask == 0) continue;
+                            any = true;
+                            if (queued + (int)__popcll(mask) > kWave) {
+                                merge();
+                                pass = pass && key <= bound;
+                                mask = __ballot(pass);
+                                if (mask == 0) continue;
+                            }
+                            // the passing lanes' keys go to the queue's next places (a permutation of the lanes)
+                            const int n_pass = (int)__popcll(mask);
+                            const int to = pass ? queued + (int)lane_rank_in(mask) : queued + n_pass + (int)lane_rank_in(~mask);
+                            const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_permute((to & 63) << 2, (int)(uint32_t)key);
+                            const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_permute((to & 63) << 2, (int)(uint32_t)(key >> 32));
+                            if (lane >= queued && lane < queued + n_pass) queue = ((uint64_t)hi << 32) | lo;
+                            queued += n_pass;
+                        }
+                    }
+                }
+                i0 -= F * kWave;
+                if (i0 < 0) {
+                    if (!first || stored) break;
+                    stored = true;
+                    const uint64_t least = least_i >= 0 ? knn_key(least_d, (int)(j0 + least_i)) : kKnnUnused;
+                    const uint64_t kth = kth_of(wave_sort_desc(least, lane), kWave - k);
+                    bound = kth < bound ? kth : bound;
+                    i0 = last0;
+                }
+            }
+            if (flush && any) {
+                merge();                                          // (what is queued joins the run's list, if it has one)
                 // into the row's list of this group, under a lock (two wavefronts of the workgroup may be at one row, in
                 // different tiles); the holder waits for nothing
                 int *lock = &s_lock[row & (kMatchLocks - 1)];
@@ -512,6 +644,11 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
                     if (now < kKnnUnused) atomicMin(&args.knn_tau[row], (unsigned long long)now);
                 }
             }
+            if (flush) {
+                bound = best = queue = kKnnUnused;
+                queued = 0;
+                any = false;
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
@@ -526,30 +663,31 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
             const int row = wave_uniform(rw.row), len = wave_uniform(rw.len);
             const int begin = (int)((int64_t)len * wave / nw), end = (int)((int64_t)len * (wave + 1) / nw);
             Entries x = load_entries(rw.start + begin, end - begin, 0);
+            Few few{};
             for (int e0 = 0; e0 < end - begin; e0 += kWave) {
                 const Lists y = load_lists(tile, x);
                 x = load_entries(rw.start + begin, end - begin, e0 + kWave);
-                walk_lists(tile, y);
+                walk_lists(tile, y, few);
             }
+            few.total = 4 * U + 1;
             __syncthreads();
             for (int i = tid; i < T; i += nw * kWave) {
-                Cell sum = reinterpret_cast<Cell *>(dyn)[i];
-                reinterpret_cast<Cell *>(dyn)[i] = zero;
+                Acc sum = S::get(strips_at, plane, (uint32_t)i);
+                S::put(strips_at, plane, (uint32_t)i, zero);
 #pragma unroll
                 for (int w = 1; w < nw; ++w) {
-                    Cell *cell = reinterpret_cast<Cell *>(dyn + (size_t)w * strip_bytes) + i;
-                    O::combine(sum.acc, cell->acc);
-                    *cell = zero;
+                    O::combine(sum, S::get(strips_at + (uint32_t)w * strip_bytes, plane, (uint32_t)i));
+                    S::put(strips_at + (uint32_t)w * strip_bytes, plane, (uint32_t)i, zero);
                 }
-                reinterpret_cast<Cell *>(dyn + (size_t)owner * strip_bytes)[i] = sum;
+                S::put(strips_at + (uint32_t)owner * strip_bytes, plane, (uint32_t)i, sum);
             }
             __syncthreads();
             if (wave == owner) {
-                finish(tile, row);
+                finish(tile, row, load_row(row), few, true);
                 // (dense columns add behind the last tile's end too: 0, unless the entry of A is not finite.  Nothing reads
                 // these sums here, but the tiles begin again below, and an earlier one has rows there)
                 if (tile == args.b.shape.n_tiles - 1)
-                    for (int i = lane; i < T; i += kWave) reinterpret_cast<Cell *>(strip)[i] = zero;
+                    for (int i = lane; i < T; i += kWave) S::put(strip_at, plane, (uint32_t)i, zero);
             }
             owner = owner + 1 < nw ? owner + 1 : 0;
         }
@@ -558,10 +696,10 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
     // ---- the other rows: one wavefront each, no waiting for one another ------------------------------
     const int rows_here = args.m - args.m_shared > slice ? (args.m - args.m_shared - slice + args.slices - 1) / args.slices : 0;
     if (rows_here == 0) return;
-    // A wavefront takes (tile, row) after (tile, row) and goes through their batches of 64 entries as one
+    // A wavefront takes a row and a run of tiles after another and goes through their batches of 64 entries as one
     // stream: while the lists of one batch are walked, the list bounds of the next one and the entries of
     // the one after that are on their way.
-    struct Place { int tile, row, len, e0; int64_t start; };        // e0: of the batch; row < 0: there is none
+    struct Place { int tile, row, len, e0, tiles; int64_t start; };       // e0: of the batch; tiles: left of the run; row < 0: there is none
     auto claim = [&]() {
         // (the lane number is hidden from the compiler here: were `lane == 0` also to close the loop's body,
         // it would thread the two tests together and let the other lanes round the loop ahead of lane 0)
@@ -569,22 +707,32 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
         asm volatile("" : "+v"(claimer));
         if (claimer == 0) at = atomicAdd(&s_next, 1);
         at = wave_uniform(at);
-        const int ti = at / rows_here;
-        Place p{0, -1, 0, 0, 0};
+        const int run = at / rows_here, ti = run * args.run;
+        Place p{0, -1, 0, 0, 0, 0};
         if (ti < my_tiles) {
-            const MatchRow rw = args.rows[args.m_shared + slice + (at - ti * rows_here) * args.slices];
+            const MatchRow rw = args.rows[args.m_shared + slice + (at - run * rows_here) * args.slices];
             p.tile = group + ti * args.groups;
+            p.tiles = min(args.run, my_tiles - ti);
             p.row = wave_uniform(rw.row);
             p.len = wave_uniform(rw.len);
             p.start = rw.start;
         }
         return p;
     };
-    Place ahead = claim();                       // where the stream goes on once the row below is through
+    Place ahead = claim();                       // where the stream goes on once the run below is through
     auto advance = [&](const Place &p) {         // the batch after p
         Place q = p;
         q.e0 += kWave;
-        if (q.row >= 0 && q.e0 >= q.len) { q = ahead; ahead = claim(); }
+        if (q.row >= 0 && q.e0 >= q.len) {
+            if (q.tiles > 1) {
+                q.e0 = 0;
+                --q.tiles;
+                q.tile += args.groups;
+            } else {
+                q = ahead;
+                ahead = claim();
+            }
+        }
         return q;
     };
     Place p0 = ahead;
@@ -593,12 +741,19 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
     Place p1 = advance(p0);
     Lists y = load_lists(p0.tile, x);
     x = load_entries(p1.start, p1.len, p1.e0);
+    Few few{};
     while (p0.row >= 0) {
         const Place p2 = advance(p1);
         const Lists y1 = load_lists(p1.tile, x);
         x = load_entries(p2.start, p2.len, p2.e0);
-        walk_lists(p0.tile, y);
-        if (p0.e0 + kWave >= p0.len) finish(p0.tile, p0.row);
+        const RowOf of = load_row(p0.row);
+        walk_lists(p0.tile, y, few);
+        if (p0.e0 + kWave >= p0.len) {
+            finish(p0.tile, p0.row, of, few, p0.tiles <= 1);
+            few.total = 0;
+        } else if (KNN) {
+            few.total += 4 * U + 1;                             // (the entries of several batches are not at hand together)
+        }
         p0 = p1;
         p1 = p2;
         y = y1;
@@ -607,30 +762,32 @@ __global__ void __launch_bounds__(match_waves(sizeof(MatchCell<OP>)) * kWave) sp
 
 // Raises a kernel's LDS limit, once per device (`allowed`: the instance's own).
 constexpr int kMatchDevices = 64;
-template <typename Kernel> static hipError_t allow_lds(Kernel kern, std::atomic<uint32_t> (&allowed)[kMatchDevices], uint32_t bytes) {
+template <typename Kernel> static hipError_t allow_lds(Kernel kern, std::atomic<uint32_t> (&allowed)[kMatchDevices], uint32_t bytes,
+                                                            uint32_t static_bytes) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     const bool known = dev >= 0 && dev < kMatchDevices;
     if (known && allowed[dev].load(std::memory_order_acquire) >= bytes) return hipSuccess;
     // to the most any launch may ask for, so that no two launches set it against each other
-    const uint32_t want = std::max<uint32_t>(bytes, 160u * 1024u - (uint32_t)match_static_lds(8));
+    const uint32_t want = std::max<uint32_t>(bytes, 160u * 1024u - static_bytes);
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)want);
     if (e == hipSuccess) {
         if (known) allowed[dev].store(want, std::memory_order_release);
         return e;
     }
     // a device with less LDS: ask for what this launch needs
+    (void)hipGetLastError();
     return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 template <int OP, bool KNN> static hipError_t launch_match_op(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
     auto kern = spd_match_kernel<OP, KNN>;
     static std::atomic<uint32_t> allowed[kMatchDevices];
-    hipError_t e = allow_lds(kern, allowed, lds_bytes);
+    hipError_t e = allow_lds(kern, allowed, lds_bytes, (uint32_t)match_static_lds(match_cell_bytes(OP)));
     if (e != hipSuccess) return e;
     const int64_t groups = args.by_xcd ? (args.groups + 7) / 8 * 8 : args.groups;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(groups * args.slices)), dim3((unsigned)(match_waves(sizeof(MatchCell<OP>)) * kWave)), lds_bytes, st, args);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(groups * args.slices)), dim3((unsigned)(match_waves(match_cell_bytes(OP)) * kWave)), lds_bytes, st, args);
     return hipGetLastError();
 }
 template <int OP> static hipError_t launch_match_either(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {

@@ -378,6 +378,62 @@ def test_a_value_that_is_not_finite_stays_in_its_row(spd, metric):
     h.close()
 
 
+# columns: one word of 32, its end, a workgroup's 4,096 words and beyond them; entries of B: under a mask of 64, at the ends of
+# masks and of a workgroup's 4,096 entries, and more than 1,024 workgroups (the sums of sums)
+@pytest.mark.parametrize("metric", SERVED)
+@pytest.mark.parametrize("m,n,cols,lengths_a,lengths_b", [(1, 1, 5, (3,), (4,)), (3, 63, 33, (1, 7, 0), (1, 1, 0, 2)),
+                                                          (21, 1300, 131_073, (2, 65, 0, 300, 1), (5, 0, 40, 3)),
+                                                          (40, 1025, 4_000, (1, 2, 3), (4,)), (9, 64, 1 << 21, (64, 700), (64, 128))])
+def test_lists_over_the_columns_of_a(spd, metric, m, n, cols, lengths_a, lengths_b):
+    rng = np.random.default_rng(cols + n)
+    head = rng.choice(cols, size=min(cols, 60), replace=False)             # most entries lie here, the others anywhere
+
+    def matrix(rows, lengths):
+        c = [np.unique(np.concatenate([rng.choice(head, size=min(len(head), (3 * k + 3) // 4), replace=False), rng.integers(0, cols, size=k // 4)]))
+             if (k := lengths[r % len(lengths)]) else np.zeros(0, np.int64) for r in range(rows)]
+        values = rng.integers(0, 9, size=sum(map(len, c))) / 8.0           # (a stored zero among them)
+        return {"n_rows": rows, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum([len(x) for x in c])]).astype(np.int64),
+                "indices": np.concatenate(c).astype(np.int32), "values": values.astype(np.float32)}
+
+    A, B = matrix(m, lengths_a), matrix(n, lengths_b)
+    print("lists over A's columns", metric, m, n, cols, flush=True)
+    p, k = _p_of(metric), min(n, 33)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], p)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = _lists(spd, match_lists=3, profile=1)
+    assert_distances_close(_np(h.pairwise(dA, dB, metric, p)), want, metric)
+    assert [r["name"] for r in h.profile_read()][:3] == ["norms_b", "columns", "lists_b"]
+    idx, dist = h.knn(dA, dB, metric, k, p)
+    assert_knn_matches(_np(idx), _np(dist), want, k, metric, metric)
+    index = h.index_create(dB, metric, p)
+    assert np.array_equal(_np(index.pairwise(dA)), _np(h.pairwise(dA, dB, metric, p)))
+    i2, d2 = index.knn(dA, k)
+    assert np.array_equal(_np(i2), _np(idx)) and np.array_equal(_np(d2), _np(dist))
+    index.close()
+    h.close()
+
+
+def test_columns_of_many_entries(spd):
+    """Enough entries of B for a second round of the sums of sums, values that are exact in any order."""
+    rng = np.random.default_rng(3)
+    cols, m, n, per = 300_000, 24, 70_000, 62                              # 4.3 M entries: 1,060 workgroups
+    cb = np.sort(np.concatenate([rng.integers(0, 40, size=(n, 2)), rng.integers(0, cols, size=(n, per - 2))], axis=1), axis=1)
+    keep = np.concatenate([np.ones((n, 1), bool), np.diff(cb, axis=1) > 0], axis=1)
+    B = {"n_rows": n, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum(keep.sum(1))]).astype(np.int64),
+         "indices": cb[keep].astype(np.int32), "values": rng.integers(1, 5, size=int(keep.sum())).astype(np.float32)}
+    rows = [np.unique(np.concatenate([np.arange(r, 40, 3), rng.integers(0, cols, size=50 * r)])) for r in range(m)]
+    A = {"n_rows": m, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64),
+         "indices": np.concatenate(rows).astype(np.int32), "values": rng.integers(1, 5, size=sum(map(len, rows))).astype(np.float32)}
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    staged, h = _lists(spd, match_lists=0), _lists(spd, match_lists=3)
+    for metric in ("inner_product", "l1", "jaccard"):
+        assert np.array_equal(_np(h.pairwise(dA, dB, metric)), _np(staged.pairwise(dA, dB, metric)))
+        for got, want in zip(h.knn(dA, dB, metric, 10), staged.knn(dA, dB, metric, 10)):
+            assert np.array_equal(_np(got), _np(want))
+    staged.close()
+    h.close()
+
+
 @pytest.fixture()
 def scarce(spd):
     """Operands whose lists (a word per tile and column) take more memory than the device has left, and whose scan takes
