@@ -322,6 +322,9 @@ spd_status spd_csr_validate(spd_handle *handle, const spd_csr *M, int require_no
  *                 has it; 3: the same, over A's columns.  A call whose lists the caller's scratch does not hold, or the device
  *                 has no memory for, runs by the staged scan; the handle asks the device for that much again
  *                 only after the option is set again.  The sums' order differs between the two ways.
+ *   "direct"      1 (default): a small call (up to 2,048 columns, 2^19 pairs, 2^16 stored entries an operand, k-NN over up to
+ *                 1,024 rows; not Chebyshev and the semirings that are not spelled as a distance; no other
+ *                 knob turned, no lent scratch) is one launch that reads both operands where they lie; 0: never
  *   "check_plan"  1: verify every index the kernels will form from the plan before the scan is launched (with
  *                 the column lists: the cut of B into tiles and blocks, the grid, A's rows)
  *   "profile"     1: bracket every kernel launch with HIP events (see spd_profile_read)
@@ -333,10 +336,11 @@ spd_status spd_set_option(spd_handle *handle, const char *name, int64_t value);
 typedef struct {
     char name[24];        /* "pack_b", "scan", "finalize", "knn_merge"; with the column lists "norms_b",
                                 ("columns", over A's columns) "lists_b", "norms_a", "knn_begin", "scan",
-                                "knn_merge"                                                          */
+                                "knn_merge"; a small call: "scan"                                    */
     int32_t rows_per_group; /* scan: R, the rows of A staged together; else 0            */
     int32_t staging_kind; /* scan: 1 dense strip, 2 column-slot strip, 3 hash, 4 Bloom, 5 bitmap,
-                                6 column lists ("match_lists"); else 0 */
+                                6 column lists ("match_lists"), 7 none
+                                ("direct"); else 0 */
     int32_t block;        /* scan: threads per workgroup; else 0                          */
     int32_t lds_bytes;    /* scan: dynamic LDS per workgroup; else 0                      */
     int64_t a_rows;       /* scan: rows (or slices of rows) of A the launch covers        */

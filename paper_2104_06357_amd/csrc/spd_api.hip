@@ -11,12 +11,14 @@
 #include <condition_variable>
 #include <functional>
 #include <mutex>
+#include <optional>
 #include <string>
 #include <thread>
 #include <vector>
 
 #include "../../include/spd.h"
 #include "../../include/spd_testing.h"
+#include "spd_direct.h"
 #include "spd_kernels.h"
 #include "spd_match.h"
 #include "spd_plan.h"
@@ -136,6 +138,7 @@ struct spd_handle {
     int match_lists = 1;         // option "match_lists": 0 never, 1 where it pays, 2 wherever the product allows it, 3 over A's columns
     size_t lists_refused = SIZE_MAX;     // the least scratch for the column lists that the device had no memory for
     int swap_operands = 1;       // option "swap_operands": 0 never, 1 where it pays, 2 wherever the distance allows it
+    int direct = 1;              // option "direct": 0 never, 1 where it pays
     int side_streams = 3;        // option "side_streams": how many internal streams the small launches may use beside the large one
     static constexpr int kSideStreams = 3;
     hipStream_t side[kSideStreams] = {nullptr, nullptr, nullptr};
@@ -895,6 +898,38 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     return SPD_OK;
 }
 
+// Whether a call is small enough for the one launch of spd_direct.hip: few columns, so that its strips fit (and no row that
+// the lists or the scan would share out), and so few pairs and entries that the launches and uploads of the other ways
+// are what they cost.
+bool direct_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, int knn_k) {
+    if (semiring || h->direct == 0 || !direct_serves(op) || A->n_cols <= 0 || A->n_cols > kDirectColumns) return false;
+    if (knn_k > 0 && B->n_rows > kDirectKnnRows) return false;
+    // (scratch that the caller lends is asked for as before: a call it does not hold is refused)
+    if ((h->ws_external && !h->no_alloc) || !scan_knobs_untouched(h) || h->match_lists != 1) return false;
+    return A->n_rows * B->n_rows <= ((int64_t)1 << 19) && A->nnz <= (1 << 16) && B->nnz <= (1 << 16);
+}
+// (A and B have been looked through: check_rows)
+spd_status run_direct(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, int op, int knn_k, const OpParams &q,
+                      const MetricInfo &mi, float *out, int64_t *out_idx, float *out_dist) {
+    DirectArgs a;
+    a.a = DirectCsr{A->indptr, A->indices, A->values, A->n_rows, A->nnz};
+    a.b = DirectCsr{B->indptr, B->indices, B->values, B->n_rows, B->nnz};
+    a.q = q;
+    a.transform = mi.transform;
+    a.norm = mi.norm;
+    a.k = (uint32_t)A->n_cols;
+    a.out = out;
+    a.knn_k = knn_k;
+    a.out_idx = out_idx;
+    a.out_dist = out_dist;
+    LaunchTimer lt(h, "scan", kDirectRows, kDirectStagingKind, 256, direct_lds_bytes(A->n_cols, B->n_rows, knn_k), A->n_rows,
+                   (A->n_rows + kDirectRows - 1) / kDirectRows * (knn_k > 0 ? 1 : (B->n_rows + 255) / 256));
+    const hipError_t e = launch_direct(h->stream, op, a);
+    if (e != hipSuccess) return hip_fail(h, e, "direct kernel");
+    lt.done();
+    return SPD_OK;
+}
+
 // (the staged scan's planner refuses a row that is longer than the column count in the operand it stages)
 spd_status refuse_rows(spd_handle *h, const char *name, const int64_t *ip, int64_t rows, int64_t n_cols, bool staged) {
     const std::string why = check_rows(ip, rows, staged ? n_cols : INT64_MAX);
@@ -912,7 +947,8 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     const int op = product_of(h, metric, p);
     const bool swap = knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
     const MatchWay way = match_way(h, A, B, op, semiring, swap, knn_k, index != nullptr, index && index->match.list);
-    bool lists = way.way != 0;
+    const bool direct = direct_wanted(h, A, B, op, semiring, knn_k);
+    bool lists = way.way != 0 && !direct;
     if (lists) {
         if (way.way == 1 && index && (index->match_op != op || std::memcmp(&index->match.shape, &way.s, sizeof way.s) != 0))
             lists = false;              // (created under other options)
@@ -931,7 +967,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
             }
         }
     }
-    const bool swapped = swap && !lists;
+    const bool swapped = swap && !lists && !direct;
     if (swapped) std::swap(A, B);           // from here on A is the staged operand, B the streamed one
     const int64_t m = A->n_rows, n = B->n_rows;
     const int64_t out_stride_staged = swapped ? 1 : n, out_stride_streamed = swapped ? m : 1;
@@ -947,15 +983,16 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
 
     // ---- row pointers on the host: the caller's copies, or read back (the call's only
     //      synchronisation) ----------------------------------------------------------------
-    PinnedLease lease(h);
     const bool same = !index && A->indptr == B->indptr && m == n;
     const int64_t *a_host = A->host_indptr ? A->host_indptr : (same ? B->host_indptr : nullptr);
     const int64_t *b_host = index ? nullptr : (B->host_indptr ? B->host_indptr : (same ? A->host_indptr : nullptr));
     const bool copy_a = !a_host;
     const bool copy_b = !index && !same && !b_host;
     const size_t ip_bytes = (copy_a ? (size_t)(m + 1) * 8 : 0) + (copy_b ? (size_t)(n + 1) * 8 : 0);
+    std::optional<PinnedLease> lease;
+    if (!direct || ip_bytes) lease.emplace(h);           // (a direct call stages nothing else)
     // (sized for the two plan uploads as well, which follow the row pointers in the buffer)
-    spd_status st = ensure_pinned(h, ip_bytes + (index ? 0 : 32 * ((size_t)n + 4096)) + 48 * ((size_t)m + 4096));
+    spd_status st = direct && !ip_bytes ? SPD_OK : ensure_pinned(h, ip_bytes + (index ? 0 : 32 * ((size_t)n + 4096)) + 48 * ((size_t)m + 4096));
     if (st != SPD_OK) return st;
     // where the two arrays are read from: the caller's memory, or the start of the pinned buffer
     auto locate = [&](const int64_t *&a_at, const int64_t *&b_at) {
@@ -979,12 +1016,13 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     }
     if (a_ip[m] != A->nnz || (!index && b_ip[n] != B->nnz)) return fail(h, SPD_ERR_BAD_CSR, "indptr[n_rows] != nnz");
     lap("indptr d2h");
-    if (lists) {
+    if (lists || direct) {
         const bool b_staged = knn_k == 0 && !index && swap;
         st = index ? SPD_OK : refuse_rows(h, "B", b_ip, n, A->n_cols, b_staged);
         if (st == SPD_OK) st = refuse_rows(h, "A", a_ip, m, A->n_cols, !b_staged);
         if (st != SPD_OK) return st;
     }
+    if (direct) return run_direct(h, A, B, metric, op, knn_k, op_params(metric, p, A->n_cols, nullptr), metric_info(metric), out, out_idx, out_dist);
     if (lists)
         return run_match(h, A, B, metric, op, knn_k, op_params(metric, p, A->n_cols, nullptr), metric_info(metric), way, a_ip, b_ip,
                          ip_bytes, out, out_idx, out_dist, index);
@@ -1713,6 +1751,9 @@ spd_status spd_set_option(spd_handle *h, const char *name, int64_t value) {
     } else if (s == "cuckoo_attempts") {
         if (value < 0 || value > 3) return fail(h, SPD_ERR_UNSUPPORTED, "cuckoo_attempts must lie in [0, 3]");
         h->cuckoo_attempts = (int)value;
+    } else if (s == "direct") {
+        if (value < 0 || value > 1) return fail(h, SPD_ERR_UNSUPPORTED, "direct must be 0 or 1");
+        h->direct = (int)value;
     } else if (s == "match_lists") {
         if (value < 0 || value > 3) return fail(h, SPD_ERR_UNSUPPORTED, "match_lists must be 0, 1, 2 or 3");
         h->match_lists = (int)value;

@@ -1,0 +1,126 @@
+"""Small calls in one launch (option "direct"): parity with the CPU oracle where strips, workgroups and batches of
+entries end, and the refusals of the other ways (needs an MI355X; run with -m gpu)."""
+import numpy as np
+import pytest
+
+import oracle
+from gen import synth
+from test_gpu_parity import _p_of
+from util import ALL_METRICS, ORACLE_NAME, assert_distances_close, assert_knn_matches
+
+pytestmark = pytest.mark.gpu
+
+SERVED = [m for m in ALL_METRICS if m != "chebyshev"]
+
+
+@pytest.fixture(scope="module")
+def spd():
+    import paper_2104_06357_amd as lib
+    return lib
+
+
+def _np(t):
+    import torch
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+def _matrix(rng, rows, cols, lengths):
+    d = np.zeros((rows, cols))
+    for r in range(rows):
+        k = min(lengths[r % len(lengths)], cols)
+        d[r, rng.choice(cols, size=k, replace=False)] = rng.integers(1, 9, size=k) / 8.0
+    out = synth.from_dense(np.asarray(d.astype(np.float32), dtype=np.float64))
+    out["values"][::17] = 0.0                              # stored zeros are absent
+    return out
+
+
+def _kinds(h):
+    return [(r["name"], r["staging_kind"]) for r in h.profile_read()]
+
+
+# rows of A: around the four of a workgroup; rows of B: around a wavefront, the 256 of a workgroup and the 1,024 of k-NN; columns:
+# one, and as many as a strip has; rows of 0 to all entries, around the four that are in flight
+@pytest.mark.parametrize("metric", SERVED)
+@pytest.mark.parametrize("m,n,cols,lengths", [(1, 1, 1, (1,)), (3, 63, 40, (0, 1, 4, 5, 40)), (4, 65, 512, (10, 8, 3)),
+                                              (5, 257, 2048, (7, 64, 0, 9)), (9, 1024, 300, (2, 3, 4)), (700, 700, 512, (10, 12, 9))])
+def test_parity(spd, metric, m, n, cols, lengths):
+    rng = np.random.default_rng(m + 10 * n)
+    A, B, p = _matrix(rng, m, cols, lengths), _matrix(rng, n, cols, lengths[::-1]), _p_of(metric)
+    print("direct", metric, m, n, cols, flush=True)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], p)
+    h = spd.Handle()
+    h.set_option("profile", 1)
+    k = min(n, 64)
+    for host in (True, False):                             # (row pointers on the GPU alone are read back)
+        dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+        if not host:
+            dA, dB = (spd.DeviceCsr(x.n_rows, x.n_cols, x.indptr, x.indices, x.values, host_indptr=None) for x in (dA, dB))
+        got = _np(h.pairwise(dA, dB, metric, p))
+        assert _kinds(h) == [("scan", 7)]
+        assert_distances_close(got, want, metric)
+        idx, dist = h.knn(dA, dB, metric, k, p)
+        assert _kinds(h) == [("scan", 7)]
+        assert_knn_matches(_np(idx), _np(dist), want, k, metric, metric)
+    out = h.pairwise(dA, dB, metric, p)
+    index = h.index_create(dB, metric, p)
+    assert np.array_equal(_np(index.pairwise(dA)), _np(out))
+    i2, d2 = index.knn(dA, k)
+    assert np.array_equal(_np(i2), _np(idx)) and np.array_equal(_np(d2), _np(dist))
+    index.close()
+    h.set_option("direct", 0)                              # the general path over the same operands
+    assert_distances_close(_np(h.pairwise(dA, dB, metric, p)), want, metric)
+    assert ("scan", 7) not in _kinds(h)
+    h.close()
+
+
+def test_where_it_ends(spd):
+    """One row, column, pair or entry more than it takes, k-NN over too many rows, products and knobs it does not have."""
+    rng = np.random.default_rng(4)
+    h = spd.Handle()
+    h.set_option("profile", 1)
+
+    def kinds(m, n, cols, metric="l1", k=0, per=1):
+        A, B = (spd.DeviceCsr.from_host({"n_rows": r, "n_cols": cols, "indptr": np.arange(r + 1, dtype=np.int64) * per,
+                                         "indices": np.concatenate([np.sort(rng.choice(cols, size=per, replace=False)) for _ in range(r)]).astype(np.int32),
+                                         "values": np.ones(r * per, np.float32)}) for r in (m, n))
+        h.knn(A, B, metric, k) if k else h.pairwise(A, B, metric)
+        return {kind for name, kind in _kinds(h) if name == "scan"}
+
+    assert kinds(512, 1024, 2048) == {7} and 7 not in kinds(512, 1025, 2048) and 7 not in kinds(512, 1024, 2049)
+    assert kinds(8, 1024, 64, k=3) == {7} and 7 not in kinds(8, 1025, 64, k=3)
+    assert kinds(8, 1024, 100, per=64) == {7} and 7 not in kinds(8, 1025, 100, per=64)
+    assert 7 not in kinds(8, 64, 64, "chebyshev")
+    h.set_option("max_rows", 4)
+    assert 7 not in kinds(8, 64, 64)
+    h.close()
+
+
+def test_what_is_refused(spd):
+    import torch
+    h, staged = spd.Handle(), spd.Handle()
+    staged.set_option("direct", 0)
+
+    def matrix(indptr, cols, host):
+        ip = np.asarray(indptr, dtype=np.int64)
+        nnz = int(ip[-1])
+        t = lambda a: torch.as_tensor(a, device="cuda")
+        return spd.DeviceCsr(len(ip) - 1, cols, t(ip), t(np.arange(max(nnz, 1), dtype=np.int32) % cols)[:nnz],
+                             torch.ones(nnz, device="cuda"), host_indptr=ip if host else None)
+
+    good = lambda host: matrix([0, 2, 4], 4, host)
+    for host in (True, False):
+        for bad in ([0, 3, 2], [1, 2, 3], [0, 7, 8]):      # decreasing, not from 0, longer than the column count
+            for call in (lambda x, A, B: x.pairwise(A, B, "l1"), lambda x, A, B: x.knn(A, B, "cosine", 1)):
+                for A, B in ((matrix(bad, 4, host), good(host)), (good(host), matrix(bad, 4, host))):
+                    got = []
+                    for x in (h, staged):
+                        try:
+                            call(x, A, B)
+                            torch.cuda.synchronize()
+                            got.append("taken")
+                        except spd.SpdError as e:
+                            got.append(e.status_name)
+                    assert got[0] == got[1], (bad, host, got)
+    h.close()
+    staged.close()
