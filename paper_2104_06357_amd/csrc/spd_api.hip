@@ -759,10 +759,10 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
 
 
 // The norms of B's rows, and their lists.
-spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int metric, const MetricInfo &mi, const OpParams &q) {
+spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int metric, const MetricInfo &mi, const OpParams &q, bool knn) {
     LaunchTimer norms(h, "norms_b", 0, 0, 0, 0, 0, 0);
     hipError_t e = launch_match_norms(h->stream, B->indptr, B->values, B->n_rows, B->nnz, metric, mi.transform, mi.norm, q.p, q.k, mb.norms);
-    if (e == hipSuccess) e = launch_match_least(h->stream, B->n_rows, mb);
+    if (e == hipSuccess && knn) e = launch_match_least(h->stream, B->n_rows, mb);
     if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
     norms.done();
     return SPD_OK;
@@ -796,7 +796,7 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     const int32_t *a_indices = A->indices;
     spd_csr listed = *B;
     if (!index_lists) {
-        st = stage_norms(h, B, mb, metric, mi, q);
+        st = stage_norms(h, B, mb, metric, mi, q, knn_k > 0);
         if (st != SPD_OK) return st;
         if (compact) {
             const MatchColumns c{reinterpret_cast<uint2 *>(ws + L.c.words), reinterpret_cast<uint32_t *>(ws + L.c.sums),
@@ -1627,7 +1627,7 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         if (hipMalloc(&ix->match_dev, lists.end) == hipSuccess) {
             ix->match = match_b_at(shape, lists, reinterpret_cast<unsigned char *>(ix->match_dev));
             ix->match_op = op;
-            st = stage_norms(h, Index, ix->match, run_as, mi, q);
+            st = stage_norms(h, Index, ix->match, run_as, mi, q, true);
             if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, mi);
             if (st != SPD_OK) return st;
         } else {                         // (no memory left for the lists: the packed copy serves every call)

@@ -7,40 +7,74 @@
 namespace spd {
 
 // ------------------------------------------------------------------------------------
-// row norms (A): G lanes to the row, four entries of a lane in flight
+// row norms: G lanes to the row, four entries of a lane in flight; with up to 64 lanes to the row, rows of more than 64
+// entries a lane wait for the whole workgroup, one after the other (500,000 rows of 1 to 50,000 entries: 332 us while a
+// wavefront went through the longest alone, 260 now)
 // ------------------------------------------------------------------------------------
 template <int G>
 __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__restrict__ indptr, const float *__restrict__ values,
                                                               int64_t n_rows, int64_t nnz, int metric, int transform, int norm,
                                                               float p, double k, double *__restrict__ norms) {
-    const int sub = (int)threadIdx.x % G;
-    const int64_t row = (int64_t)blockIdx.x * (256 / G) + (int)threadIdx.x / G;
-    if (row >= n_rows) return;
-    const int64_t begin = clamp_i64(indptr[row], 0, nnz), end = clamp_i64(indptr[row + 1], begin, nnz);
-    double s0 = 0.0, s1 = 0.0;
-    for (int64_t e = begin + sub; e < end; e += 4 * G) {
-        float v[4];
+    constexpr int kRows = 256 / G;
+    constexpr int64_t kLong = G < 256 ? 64 * G : INT64_MAX;
+    __shared__ int s_long[kRows], s_longs;
+    __shared__ double s_sum[256 / kWave][2];
+    const int tid = (int)threadIdx.x, sub = tid % G;
+    const int64_t row0 = (int64_t)blockIdx.x * kRows, row = row0 + tid / G;
+    auto sums = [&](int64_t from, int64_t end, int stride, double &s0, double &s1) {
+        for (int64_t e = from; e < end; e += 4 * stride) {
+            float v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = e + u * G < end ? values[e + u * G] : 0.0f;
+            for (int u = 0; u < 4; ++u) v[u] = e + u * stride < end ? values[e + u * stride] : 0.0f;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (e + u * G < end) norm_accumulate(norm, transform_value(transform, v[u]), p, s0, s1);
-    }
+            for (int u = 0; u < 4; ++u)
+                if (e + u * stride < end) norm_accumulate(norm, transform_value(transform, v[u]), p, s0, s1);
+        }
 #pragma unroll
-    for (int d = std::min(G, kWave) / 2; d >= 1; d >>= 1) { s0 += __shfl_xor(s0, d); s1 += __shfl_xor(s1, d); }
-    if constexpr (G > kWave) {           // one row to the workgroup: its wavefronts' sums in a fixed order
-        __shared__ double s_sum[G / kWave][2];
-        if (sub % kWave == 0) { s_sum[sub / kWave][0] = s0; s_sum[sub / kWave][1] = s1; }
-        __syncthreads();
-        s0 = 0.0; s1 = 0.0;
-#pragma unroll
-        for (int w = 0; w < G / kWave; ++w) { s0 += s_sum[w][0]; s1 += s_sum[w][1]; }
-    }
-    if (sub == 0) {
+        for (int d = kWave / 2; d >= 1; d >>= 1)
+            if (d < stride) { s0 += __shfl_xor(s0, d); s1 += __shfl_xor(s1, d); }
+    };
+    auto write = [&](int64_t r, double s0, double s1) {
         double d0, d1;
         norm_derive(metric, k, s0, s1, d0, d1);
-        norms[(size_t)row * 2] = d0;
-        norms[(size_t)row * 2 + 1] = d1;
+        norms[(size_t)r * 2] = d0;
+        norms[(size_t)r * 2 + 1] = d1;
+    };
+    // a row by all 256 lanes: its wavefronts' sums in a fixed order
+    auto by_all = [&](int64_t r, int64_t begin, int64_t end) {
+        double s0 = 0.0, s1 = 0.0;
+        sums(begin + tid, end, 256, s0, s1);
+        if (tid % kWave == 0) { s_sum[tid / kWave][0] = s0; s_sum[tid / kWave][1] = s1; }
+        __syncthreads();
+        if (tid == 0) {
+            s0 = 0.0; s1 = 0.0;
+#pragma unroll
+            for (int w = 0; w < 256 / kWave; ++w) { s0 += s_sum[w][0]; s1 += s_sum[w][1]; }
+            write(r, s0, s1);
+        }
+    };
+    int64_t begin = 0, end = 0;
+    if (row < n_rows) {
+        begin = clamp_i64(indptr[row], 0, nnz);
+        end = clamp_i64(indptr[row + 1], begin, nnz);
+    }
+    if constexpr (G == 256) {
+        by_all(row, begin, end);                             // (a row to the workgroup: there is one)
+    } else {
+        if (tid == 0) s_longs = 0;
+        __syncthreads();
+        const bool is_long = end - begin > kLong;
+        if (is_long && sub == 0) s_long[atomicAdd(&s_longs, 1)] = tid / G;
+        double s0 = 0.0, s1 = 0.0;
+        sums(begin + sub, is_long ? begin : end, G, s0, s1);
+        if (row < n_rows && !is_long && sub == 0) write(row, s0, s1);
+        __syncthreads();
+        const int longs = s_longs;
+        for (int at = 0; at < longs; ++at) {
+            const int64_t r = row0 + s_long[at], from = clamp_i64(indptr[r], 0, nnz);
+            by_all(r, from, clamp_i64(indptr[r + 1], from, nnz));
+            __syncthreads();
+        }
     }
 }
 
@@ -331,7 +365,8 @@ hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float
     // (28,301 rows of power-law lengths: the longest, 24,000 entries, takes a wavefront alone 72 us and a workgroup 46;
     // with many rows the workgroups' own cost counts: 300,000 rows of 230 take 354 us that way and 137 us otherwise.
     // What a workgroup to the row helps is one long row, which mean and row count only stand for: 65,536 rows of 1,820
-    // take the same either way, and even rows of 230 lose by it, 60,000 of them some 40 us in proportion)
+    // take the same either way, and even rows of 230 lose by it, 60,000 of them some 40 us in proportion.  With 16 lanes to
+    // the row 10,000 rows of 38 take 17 to 20 us, with 64 11 to 15)
     if (mean >= 128 && n_rows <= 65536) go(std::integral_constant<int, 256>{});
     else if (mean >= 16) go(std::integral_constant<int, 64>{});
     else go(std::integral_constant<int, 4>{});
@@ -388,21 +423,24 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     if (tiles > (1 << 30)) return s;
     s.tile_rows = (int32_t)(((n + tiles - 1) / tiles + kWave - 1) / kWave * kWave);
     s.lds_bytes = (uint32_t)s.waves * match_strip_bytes(cell, s.tile_rows);
-    // A block of columns: an eighth of the LDS for counters at most, and entries for four fifths, on the mean,
-    // of what the row positions leave for its piece of the lists (the rest of a fuller block goes straight to
+    // A block of columns: an eighth of the LDS for counters, or twice that, and entries for four fifths, on the mean,
+    // of what counters and row positions leave for its piece of the lists (the rest of a fuller block goes straight to
     // memory; narrower blocks read a row's lines more often).  Dense columns may take half as much again.
     const int64_t usable = lds_budget - 1024, rows_bytes = 12 * (int64_t)s.tile_rows;
     if (usable < rows_bytes + 4096) return s;
+    const double per_col = per_cell * (double)s.tile_rows;
+    auto stage_of = [&](int shift) { return (usable - rows_bytes - ((int64_t)4 << shift)) / 8; };
     int shift = 2;
     while ((4 << (shift + 1)) <= usable / 8 && (1 << shift) < n_cols) ++shift;
-    const int64_t room = usable - rows_bytes - ((int64_t)4 << shift);
-    s.stage = (uint32_t)(room / 8);
-    const double per_col = per_cell * (double)s.tile_rows;
-    while (shift > 2 && per_col * (double)(1 << shift) * 1.25 > (double)s.stage) --shift;
+    // (sparse blocks, many of them: what a block costs besides its entries.  500,000 sets over 242,000 columns, 2,432 rows to
+    // the tile: 2.6 ms with 4,096 columns to the block, 2.0 with 8,192)
+    if ((n_cols >> shift) >= 16 && (4 << (shift + 1)) <= usable / 4) ++shift;
+    while (shift > 2 && per_col * (double)(1 << shift) * 1.25 > (double)stage_of(shift)) --shift;
     // a workgroup for every compute unit, where there are columns enough
     const int64_t tiles_now = (n + s.tile_rows - 1) / s.tile_rows;
     while (shift > 8 && tiles_now * ((n_cols + (1 << shift) - 1) >> shift) < 256) --shift;
     s.block_shift = shift;
+    s.stage = (uint32_t)stage_of(shift);
     s.blocks = (int32_t)((n_cols + (1 << shift) - 1) >> shift);
     s.dense_per_block = (int32_t)std::min<double>(kBuildDense, std::max(1.0, per_cell * (double)(1 << shift)));
     // a step of 64 rows of a dense column costs this share of a list's step
