@@ -680,14 +680,16 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
 // the times of most, because row pointers do not show how A's columns meet B's.
 double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, const MatchShape &s, bool knn, bool copied) {
     const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz;
-    const bool wide = match_doubles(op) + match_counts(op) > 1;
+    const bool wide = match_doubles(op) + match_counts(op) > 1, dear = op == OP_JS;
     const double list = nnz_b / n / (double)columns * (double)s.tile_rows;             // entries, on the mean
     const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn);
     const double items = std::ceil((double)match_items(s, g, A->n_rows) / s.waves);     // of a wavefront
     const double idle = items * s.waves * (double)h->opt.n_cus / (m * s.n_tiles);
     // (over A's columns alone the lists that A walks are longer than the mean)
-    const double entry = copied ? (wide ? 45.0 + 75.0 * std::min(1.0, list) + 160.0 * list / 64.0 : 25.0 + 27.0 * std::min(1.0, list) + 80.0 * list / 64.0)
-                                : (wide ? 45.0 + 65.0 * std::min(1.0, list) + 95.0 * list / 64.0 : 22.0 + 13.0 * std::min(1.0, list) + 42.0 * list / 64.0);
+    const double entry = copied ? (wide ? 45.0 + 75.0 * std::min(1.0, list) + 160.0 * list / 64.0
+                                   : dear ? 35.0 + 45.0 * std::min(1.0, list) + 120.0 * list / 64.0 : 25.0 + 27.0 * std::min(1.0, list) + 80.0 * list / 64.0)
+                                : (wide ? 45.0 + 65.0 * std::min(1.0, list) + 95.0 * list / 64.0
+                                   : dear ? 30.0 + 30.0 * std::min(1.0, list) + 75.0 * list / 64.0 : 22.0 + 13.0 * std::min(1.0, list) + 42.0 * list / 64.0);
     const double row = knn ? (wide ? 1600.0 : 2300.0) : 300.0;
     return (copied ? 105e6 : 65e6) + 28.0 * nnz_b + idle * s.n_tiles * (entry * nnz_a + row * m) + 0.9 * m * n;
 }

@@ -6,9 +6,8 @@
 // per tile the entries are listed by column (a transpose of the tile, made on the device in each
 // call).  A wavefront takes one row of A, walks the lists of that row's columns only, and adds
 // product(a, b) to one sum per row of the tile, which lie in its own strip of LDS.  Work is done for
-// the columns that two rows share and for nothing else.  Where a pair has one sum the lists are walked
-// in chunks of 16 entries, four chunks of any lists to a step; elsewhere a step is up to 64 entries of one
-// list.  A strip is private to its wavefront, and the sums are formed in the order of A's columns (a row of
+// the columns that two rows share and for nothing else.  The lists are walked in chunks of 16 entries,
+// four chunks of any lists to a step.  A strip is private to its wavefront, and the sums are formed in the order of A's columns (a row of
 // B appears at most once in a list, and lanes that meet in one sum are served in ascending order, which
 // is that order): the results do not depend on the schedule.
 #pragma once
@@ -24,7 +23,7 @@ namespace spd {
 // One row of A as the kernels take them, longest first.
 struct MatchRow { int64_t start; int32_t len, row; };
 
-// Entries behind the last list, which a step may read and does not use: 15 of a chunk, 63 of a step, and with a tile of
+// Entries behind the last list, which a step may read and does not use: 15 of a chunk, and with a tile of
 // 64 rows the 18 other pieces of a dense column that are summed together (half an entry a row).
 constexpr int64_t kMatchSpare = 640;
 
@@ -96,7 +95,7 @@ constexpr int kMatchStagingKind = 6;            // how spd_profile_read names th
 constexpr int64_t kMatchL2Bytes = 4 << 20;      // of one XCD
 // Bytes that a pair's sums take in a strip: its doubles and its count.
 SPD_HD constexpr int match_doubles(int op) {
-    return op == OP_DOT || op == OP_L1 || op == OP_CANB || op == OP_KL ? 1 : (op == OP_JS || op == OP_MINK || op == OP_MINK_ANY ? 2 : 0);
+    return op == OP_DOT || op == OP_L1 || op == OP_CANB || op == OP_KL || op == OP_JS ? 1 : (op == OP_MINK || op == OP_MINK_ANY ? 2 : 0);
 }
 SPD_HD constexpr int match_counts(int op) { return op == OP_HAMM || op == OP_CNT || op == OP_KL || op == OP_MINK || op == OP_MINK_ANY ? 1 : 0; }
 SPD_HD constexpr int match_cell_bytes(int op) { return 8 * match_doubles(op) + 4 * match_counts(op); }

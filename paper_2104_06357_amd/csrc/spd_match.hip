@@ -413,8 +413,8 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
         // The lists of a tile that the workgroups of an XCD walk together: within twice its L2 (65,536 x 26,000 rows of 7 %,
         // L1: tiles of 256 rows 33.8 ms, 384 29.9, 512 28.6, 640 31.2, 768 34.0, 1,216 36.7), as long as a list is two
         // chunks of 16 on the mean; where tiles of all the LDS are within it, the largest (300,000 rows of 230, cosine:
-        // 576 rows 9.0 ms, 832 7.0, 1,216 5.7).  (Dearer products are bound by their arithmetic: Jensen-Shannon on the
-        // 65,536 rows 55.3, 51.8, 51.4 and, with all the LDS holds, 832 rows, 51.1.)
+        // 576 rows 9.0 ms, 832 7.0, 1,216 5.7).  (Jensen-Shannon is bound by its
+        // arithmetic: on the 65,536 rows 512 rows to the tile 38.7, 1,216 37.3.)
         const int64_t within = (int64_t)((double)(2 * kMatchL2Bytes / 8) / std::max(per_cell * (double)n_cols, 1e-12)) / kWave * kWave;
         const int64_t least = ((int64_t)(32.0 / std::max(per_cell, 1e-9)) + kWave - 1) / kWave * kWave;
         most = std::max<int64_t>(kWave, std::min(most, std::max(within, least)));

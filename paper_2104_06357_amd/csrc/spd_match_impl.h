@@ -89,19 +89,31 @@ template <int OP> struct Sums {
 };
 
 // One column both rows store: the products of Op<OP>, without the tests for absent entries that the
-// staged scan needs (neither lists nor rows hold zeros).
-template <int OP> __device__ __forceinline__ void match_visit(typename Op<OP>::Acc &x, float a, float b, const OpParams &q) {
+// staged scan needs (neither lists nor rows hold zeros).  Returns whether the column counts; where it does not, x
+// is not to be used.  match_walks: whether any column of an entry of A can count.
+template <int OP> __device__ __forceinline__ bool match_walks(float a) { return OP == OP_JS || OP == OP_KL ? a > 0.0f : a != 0.0f; }
+template <int OP> __device__ __forceinline__ bool match_visit(typename Op<OP>::Acc &x, float a, float b, const OpParams &q) {
     if constexpr (OP == OP_CNT) {
-        x.c += 1;
+        x.c = 1;
     } else if constexpr (OP == OP_HAMM) {
-        x.c += (a != b) ? -1 : -2;
+        x.c = (a != b) ? -1 : -2;
     } else if constexpr (OP == OP_CANB) {
-        x.v += (double)fast_div(fabsf(a - b), fabsf(a) + fabsf(b)) - 2.0;
+        x.v = (double)fast_div(fabsf(a - b), fabsf(a) + fabsf(b)) - 2.0;
+    } else if constexpr (OP == OP_JS) {
+        x.v = (double)Op<OP>::term(a, b) - ((double)a + (double)b);
+        return b > 0.0f;
+    } else if constexpr (OP == OP_KL) {
+        x.v = (double)(a * fast_log2(divide(a, divisor_of(b))));
+        x.hits = 1;
+        return b > 0.0f;
     } else if constexpr (OP == OP_MINK) {
+        Op<OP>::init(x);
         for_degree(q.p, [&](auto tag) { Op<OP>::template visit_as<decltype(tag)::value>(x, a, Op<OP>::prep(b, q), q); });
     } else {
+        Op<OP>::init(x);
         Op<OP>::visit(x, a, Op<OP>::prep(b, q), q);
     }
+    return true;
 }
 
 // Lane l receives lane 63 - l's value.
@@ -170,7 +182,8 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // D: 64-row pieces of a dense column that are summed in registers together; the largest tiles hold 19 for one
     // fp64 sum (one round of 19 against two of 10: 2,048 queries of 300,000 rows of 230, 10.5 -> 10.2 ms; 13 and 6
     // leave half a round idle: 11.3), 39 for a count and 13 for two sums
-    constexpr int U = kMatchUnroll, D = S::kOne ? (S::kDoubles ? 19 : 13) : 7, nw = match_waves(match_cell_bytes(OP));
+    // (Jensen-Shannon needs its registers for the logarithms)
+    constexpr int U = kMatchUnroll, D = S::kOne ? (OP == OP_JS ? 10 : (S::kDoubles ? 19 : 13)) : 7, nw = match_waves(match_cell_bytes(OP));
     extern __shared__ __align__(16) unsigned char dyn[];
     __shared__ int s_next;
     __shared__ int s_lock[KNN ? kMatchLocks : 1];
@@ -335,11 +348,10 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         auto add_one = [&](const uint2 &from, uint32_t left, float av) {
             // (everything but the LDS add itself is done for all lanes: a branch around it costs more)
             typename O::Acc t;
-            O::init(t);
-            match_visit<OP>(t, av, __uint_as_float(from.y), args.q);
+            const bool counts = match_visit<OP>(t, av, __uint_as_float(from.y), args.q);
             uint32_t offset = from.x;
             pin(t, offset);
-            if (lane8 < left) S::add(strip_at, plane, offset, t);
+            if (lane8 < left && counts) S::add(strip_at, plane, offset, t);
         };
         auto add = [&](const uint2 (&from)[U], const Chunk &c, auto block) {
             constexpr int I = decltype(block)::value * U;
@@ -403,13 +415,13 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         const uint32_t list_n = (uint32_t)(args.b.shape.list_entries(args.b_nnz) - kMatchSpare - tile_first);     // (no access leaves the lists)
         const float a = transform_value(args.transform, y.a);
         uint32_t first = min(y.first & ~kMatchDense, list_n);
-        const bool dense = (y.first & kMatchDense) != 0u && a != 0.0f && first + (uint32_t)(T / 2) <= list_n;
+        const bool dense = (y.first & kMatchDense) != 0u && match_walks<OP>(a) && first + (uint32_t)(T / 2) <= list_n;
         const uint64_t dense_mask = __ballot(dense);
         if (dense_mask != 0) {
             if (KNN) few.total += 4 * U + 1;
             walk_dense(list, first * 8u, a, dense_mask);
         }
-        const uint32_t last = a != 0.0f && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
+        const uint32_t last = match_walks<OP>(a) && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
         walk_chunks(list, first, last, a, few);
         // (a lane reads later what other lanes of its wavefront wrote: LDS serves a wavefront in order, the
         // fence keeps the compiler to that order)

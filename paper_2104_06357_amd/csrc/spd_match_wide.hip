@@ -1,4 +1,4 @@
-// Column-list kernels of the products with several sums per pair (see spd_match_impl.h).
+// Column-list kernels of the products with several sums per pair or with logarithms (see spd_match_impl.h).
 #include "spd_match_impl.h"
 
 namespace spd {

@@ -104,13 +104,13 @@ inline int split_len_for(const PlanOptions &opt, int64_t nnz_b) {
 // Sums a pair carries through the slices of a spilled row.
 SPD_HD constexpr int metric_planes(int metric) {
     return (metric == MT_MINKOWSKI || metric == MT_L2_UNEXPANDED || metric == MT_SEMI_SUM)
-               ? 3 : ((metric == MT_JS || metric == MT_KL_STRICT) ? 2 : 1);
+               ? 3 : (metric == MT_KL_STRICT ? 2 : 1);
 }
 
 // Metrics whose sum() is a maximum: a staged row's largest one-sided contributions are ranked
 // beside the value table, and the slices of a spilled row are joined by max.
 SPD_HD constexpr bool sum_is_max(int metric) { return metric == MT_CHEBYSHEV || metric == MT_SEMI_EXT; }
-// Products that carry two fp64 sums (or more) per pair: at most 8 rows are staged together.
+// Products that carry two fp64 sums (or more) per pair, or the registers of two logarithms: at most 8 rows are staged together.
 SPD_HD constexpr bool wide_sums(int metric) {
     return metric == MT_JS || metric == MT_MINKOWSKI || metric == MT_L2_UNEXPANDED || metric == MT_SEMI_SUM || metric == MT_SEMI_EXT;
 }

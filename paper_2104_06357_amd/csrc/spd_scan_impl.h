@@ -291,9 +291,7 @@ template <> __device__ __forceinline__ Op<OP_MINK_ANY>::Acc acc_shfl_xor<OP_MINK
 template <> __device__ __forceinline__ Op<OP_KL>::Acc acc_shfl_xor<OP_KL>(const Op<OP_KL>::Acc &a, int m) {
     Op<OP_KL>::Acc r; r.v = __shfl_xor(a.v, m); r.hits = __shfl_xor(a.hits, m); return r;
 }
-template <> __device__ __forceinline__ Op<OP_JS>::Acc acc_shfl_xor<OP_JS>(const Op<OP_JS>::Acc &a, int m) {
-    Op<OP_JS>::Acc r; r.f = __shfl_xor(a.f, m); r.s = __shfl_xor(a.s, m); return r;
-}
+SPD_ACC_SHFL1(OP_JS, v)
 
 // ------------------------------------------------------------------------------------
 // column -> slot of the staged value table
