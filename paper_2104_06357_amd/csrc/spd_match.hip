@@ -409,7 +409,7 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     int64_t most = ((strip - 7) / cell - 1) / kWave * kWave;    // (a spare row behind them)
     if (most < kWave) return s;
     const double per_cell = (double)nnz / (double)n / (double)n_cols;
-    if (cell <= 8) {
+    if (cell <= 8 && op != OP_JS) {
         // The lists of a tile that the workgroups of an XCD walk together: within twice its L2 (65,536 x 26,000 rows of 7 %,
         // L1: tiles of 256 rows 33.8 ms, 384 29.9, 512 28.6, 640 31.2, 768 34.0, 1,216 36.7), as long as a list is two
         // chunks of 16 on the mean; where tiles of all the LDS are within it, the largest (300,000 rows of 230, cosine:
