@@ -691,7 +691,10 @@ double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64
                                 : (wide ? 45.0 + 65.0 * std::min(1.0, list) + 95.0 * list / 64.0
                                    : dear ? 30.0 + 30.0 * std::min(1.0, list) + 75.0 * list / 64.0 : 22.0 + 13.0 * std::min(1.0, list) + 42.0 * list / 64.0);
     const double row = knn ? (wide ? 1600.0 : 2300.0) : 300.0;
-    return (copied ? 105e6 : 65e6) + 28.0 * nnz_b + idle * s.n_tiles * (entry * nnz_a + row * m) + 0.9 * m * n;
+    // (the lists' bounds, a word per tile and column: 89 x 8,333 rows of 2.2 over 858,000 columns, k-NN, L1, staged / lists 99 / 137
+    // us, 1,514 x 20,515 of them, cosine, 200 / 235; without this term both went to the lists)
+    const double bounds = copied ? 0.0 : 11.0 * (double)s.n_tiles * (double)s.ptr_stride;
+    return (copied ? 105e6 : 65e6) + bounds + 28.0 * nnz_b + idle * s.n_tiles * (entry * nnz_a + row * m) + 0.9 * m * n;
 }
 double staged_cost(const spd_csr *A, const spd_csr *B, int op, bool swapped, bool knn) {
     const double m = (double)A->n_rows, n = (double)B->n_rows;
