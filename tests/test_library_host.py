@@ -259,6 +259,13 @@ def test_column_lists_against_the_scan_that_would_run():
     assert _wanted(766, 1_468, 3_599, 35, 20_000, "minkowski", match_lists=2)
 
 
+@pytest.mark.parametrize("m,n,metric,k", [(89, 8_333, "l1", 64), (1_514, 20_515, "cosine", 10), (1_783, 12_134, "cosine", 10)])
+def test_column_lists_count_their_bounds(m, n, metric, k):
+    """A word per tile and column: few rows of two entries over very many columns, staged / lists in us 99 / 137, 200 / 235,
+    166 / 191."""
+    assert not _wanted(m, 2, n, 2, 858_000, metric, k_neighbors=k)
+
+
 def test_column_lists_only_where_a_workgroup_can_number_its_work():
     """A workgroup's (tile, row)s are numbered in 32 bits: 6.25 million rows of a slice in 2,056 tiles are more."""
     def plan(m):
@@ -279,7 +286,7 @@ def test_the_cut_of_the_column_lists_is_consistent():
         m, n, cols = (int(2 ** rng.uniform(0, e)) for e in (24, 24, 31))
         mean_a, mean_b = (min(2 ** rng.uniform(-2, 12), cols) for _ in range(2))
         metric = ALL_METRICS[rng.integers(len(ALL_METRICS))]
-        plan = spd.testing.host_list_plan(m, int(m * mean_a), n, int(n * mean_b), cols, metric, k_neighbors=int(rng.integers(0, 2)) * min(n, 64),
+        plan = spd.testing.host_list_plan(m, m * mean_a, n, n * mean_b, cols, metric, k_neighbors=int(rng.integers(0, 2)) * min(n, 64),
                                           match_lists=2, lds_budget=int(rng.choice([8192, 20000, 65536, 163840])))
         wanted += plan["wanted"]
         assert plan["consistent"] or not plan["wanted"], (m, n, cols, metric, plan)
