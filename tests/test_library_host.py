@@ -286,7 +286,7 @@ def test_the_cut_of_the_column_lists_is_consistent():
         m, n, cols = (int(2 ** rng.uniform(0, e)) for e in (24, 24, 31))
         mean_a, mean_b = (min(2 ** rng.uniform(-2, 12), cols) for _ in range(2))
         metric = ALL_METRICS[rng.integers(len(ALL_METRICS))]
-        plan = spd.testing.host_list_plan(m, m * mean_a, n, n * mean_b, cols, metric, k_neighbors=int(rng.integers(0, 2)) * min(n, 64),
+        plan = spd.testing.host_list_plan(m, int(m * mean_a), n, int(n * mean_b), cols, metric, k_neighbors=int(rng.integers(0, 2)) * min(n, 64),
                                           match_lists=2, lds_budget=int(rng.choice([8192, 20000, 65536, 163840])))
         wanted += plan["wanted"]
         assert plan["consistent"] or not plan["wanted"], (m, n, cols, metric, plan)
