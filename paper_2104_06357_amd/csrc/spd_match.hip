@@ -392,6 +392,7 @@ __global__ void __launch_bounds__(256) spd_match_least_kernel(const double *__re
             s_least[tid][1] = s_least[tid + half][1];
         }
     }
+    __syncthreads();                                          // (thread 1 stores what thread 0 has just written)
     if (tid < 2) least[(size_t)blockIdx.x * 2 + tid] = s_least[0][tid];
 }
 hipError_t launch_match_least(hipStream_t st, int64_t n_rows, const MatchB &b) {

@@ -378,6 +378,41 @@ def test_a_value_that_is_not_finite_stays_in_its_row(spd, metric):
     h.close()
 
 
+@pytest.mark.parametrize("metric", ["l1", "l2_expanded", "hellinger", "canberra", "jensen_shannon", "hamming"])
+def test_the_row_of_the_least_norm_wherever_it_lies_in_its_tile(spd, metric):
+    """k-NN passes over a tile that a row meets in a few entries where the tile's row of the least norm is no nearer than the k-th
+    neighbour so far: one short row per tile, at the places where the search for it goes from lane to lane, is the nearest
+    of all rows that share no column with the query, the nearer the later its tile."""
+    cols, m = 30_000, 1_024
+
+    def plan(n):
+        return spd.testing.host_list_plan(m, 2 * m, n, 4 * n, cols, metric, k_neighbors=2, match_lists=2)
+
+    tile = max(plan(n)["tile_rows"] for n in (40_000, 400_000))
+    places = (0, 1, 63, 64, 127, 128, 255, 256, 257, tile - 1, 17)
+    n = tile * len(places) - 40
+    assert plan(n)["tile_rows"] == tile and plan(n)["tiles"] == len(places) > plan(n)["groups"]
+    rng = np.random.default_rng(n)
+    c = np.sort(rng.integers(1_000, cols - 4, size=(n, 1)) + np.arange(4), axis=1)
+    values = np.full((n, 4), 2.0)
+    for t, at in enumerate(places):
+        values[t * tile + at] = 0.0                        # (stored zeros are absent: one entry stays)
+        values[t * tile + at, 0] = 1.0 - t / 16.0
+    B = {"n_rows": n, "n_cols": cols, "indptr": np.arange(n + 1, dtype=np.int64) * 4, "indices": c.reshape(-1).astype(np.int32),
+         "values": values.reshape(-1).astype(np.float32)}
+    ca = np.stack([np.arange(m) % 900, 1_000 + np.arange(m) * 28], axis=1)     # (the second column meets a row here and there)
+    A = {"n_rows": m, "n_cols": cols, "indptr": np.arange(m + 1, dtype=np.int64) * 2, "indices": ca.reshape(-1).astype(np.int32),
+         "values": np.full(2 * m, 0.5, np.float32)}
+    rows = np.arange(0, m, 17)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], rows_a=rows)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = _lists(spd)
+    for k in (1, 2, 13):
+        idx, dist = h.knn(dA, dB, metric, k)
+        assert_knn_matches(_np(idx)[rows], _np(dist)[rows], want, k, metric, "%s k=%d" % (metric, k))
+    h.close()
+
+
 # columns: one word of 32, its end, a workgroup's 4,096 words and beyond them; entries of B: under a mask of 64, at the ends of
 # masks and of a workgroup's 4,096 entries, and more than 1,024 workgroups (the sums of sums)
 @pytest.mark.parametrize("metric", SERVED)
