@@ -43,6 +43,7 @@ typedef struct {
     int32_t consistent;             /* what option "check_plan" finds of the cut */
     int64_t scratch_bytes;
     int64_t index_bytes;            /* what an index keeps of lists; 0: none */
+    int32_t run;                    /* tiles that a wavefront goes through with a row of A */
 } spd_list_plan;
 spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int64_t b_nnz, int64_t n_cols,
                               spd_metric metric, float p, int k_neighbors, int with_index,

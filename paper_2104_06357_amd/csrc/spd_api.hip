@@ -1823,6 +1823,7 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     out->tile_rows = s.tile_rows;
     out->slices = g.slices;
     out->groups = g.groups;
+    out->run = g.run;
     MatchShape kept;
     MatchLayout L;
     out->index_bytes = index_keeps_lists(&h, &B, op, kept, L) ? (int64_t)L.end : 0;

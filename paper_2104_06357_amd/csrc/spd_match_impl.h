@@ -473,6 +473,11 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             for (int u = 0; u < F; ++u)
                 if (i0 + u * kWave < T) S::put(strip_at, plane, (uint32_t)(i0 + lane + u * kWave), zero);          // (a tile is whole wavefronts of rows)
         };
+        // Dense columns add behind the last tile's end too: 0, unless the entry of A is not finite.  Nothing reads these sums
+        // here, but the wavefront's next tile may be an earlier one, which has rows there.
+        auto clear_behind = [&]() {
+            for (int i0 = (tile_n + F * kWave - 1) / (F * kWave) * (F * kWave); i0 < T; i0 += F * kWave) clear_round(i0);
+        };
         if constexpr (!KNN) {
             for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
                 constexpr int MT = decltype(metric_tag)::value;
@@ -498,6 +503,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                     clear_round(i0);
                 }
             });
+            clear_behind();
         } else {
             const int k = args.knn_k;
             auto kth_of = [&](uint64_t sorted, int at) {
@@ -631,6 +637,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                     i0 = last0;
                 }
             }
+            if (!few_only) clear_behind();                        // (few entries: no dense column)
             if (flush && any) {
                 merge();                                          // (what is queued joins the run's list, if it has one)
                 // into the row's list of this group, under a lock (two wavefronts of the workgroup may be at one row, in
@@ -694,13 +701,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 S::put(strips_at + (uint32_t)owner * strip_bytes, plane, (uint32_t)i, sum);
             }
             __syncthreads();
-            if (wave == owner) {
-                finish(tile, row, load_row(row), few, true);
-                // (dense columns add behind the last tile's end too: 0, unless the entry of A is not finite.  Nothing reads
-                // these sums here, but the tiles begin again below, and an earlier one has rows there)
-                if (tile == args.b.shape.n_tiles - 1)
-                    for (int i = lane; i < T; i += kWave) S::put(strip_at, plane, (uint32_t)i, zero);
-            }
+            if (wave == owner) finish(tile, row, load_row(row), few, true);
             owner = owner + 1 < nw ? owner + 1 : 0;
         }
     }

@@ -413,6 +413,40 @@ def test_the_row_of_the_least_norm_wherever_it_lies_in_its_tile(spd, metric):
     h.close()
 
 
+@pytest.mark.parametrize("metric", ["inner_product", "cosine", "kl_divergence"])
+def test_a_value_that_is_not_finite_stays_in_its_row_over_runs_of_tiles(spd, metric):
+    """Every 20th row of A, each one wavefront's but the first, which the workgroup's wavefronts share, meets a dense column of B
+    with an infinity.  A wavefront goes through a run of three tiles with a row: behind the last, short tile come an
+    earlier, full one and another row."""
+    rng = np.random.default_rng(78)
+    cols, m = 3_001, 2_100
+
+    def matrix(rows, lengths):
+        c = [np.unique(np.concatenate([[2], rng.integers(0, cols, size=lengths[r % len(lengths)])])) for r in range(rows)]
+        return {"n_rows": rows, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum([len(x) for x in c])]).astype(np.int64),
+                "indices": np.concatenate(c).astype(np.int32), "values": (rng.integers(1, 9, size=sum(map(len, c))) / 8.0).astype(np.float32)}
+
+    most = max(spd.testing.host_list_plan(m, 40 * m, n, 45 * n, cols, metric, match_lists=2)["tile_rows"] for n in (40_000, 400_000))
+    n = 17 * most + most * 9 // 16                     # 18 tiles in 8 groups, 32 slices of A's rows; column 2 is dense in the last tile too
+    A, B = matrix(m, (40,) * 7 + (1_200,) + (40,) * (m - 8)), matrix(n, (43, 41, 49, 52))
+    for k in (0, 9):
+        plan = spd.testing.host_list_plan(m, int(A["indptr"][-1]), n, int(B["indptr"][-1]), cols, metric, k_neighbors=k, match_lists=2)
+        assert plan["tile_rows"] == most and plan["tiles"] == 18 and plan["groups"] == 8 and plan["run"] >= 3
+    assert -(-(n - 17 * most) // 256) * 256 < most     # (rows that no result is read from, and a round of 256 rows does not reach)
+    bad = dict(A, values=A["values"].copy())
+    rows = np.arange(7, m, 20)
+    for r in rows:
+        bad["values"][A["indptr"][r] + int(np.searchsorted(A["indices"][A["indptr"][r]:A["indptr"][r + 1]], 2))] = np.inf
+    others = np.setdiff1d(np.arange(m), rows)
+    h = _lists(spd)
+    dB = spd.DeviceCsr.from_host(B)
+    want, got = (_np(h.pairwise(spd.DeviceCsr.from_host(M), dB, metric))[others] for M in (A, bad))
+    assert np.array_equal(got, want)
+    (wi, wd), (gi, gd) = (h.knn(spd.DeviceCsr.from_host(M), dB, metric, 9) for M in (A, bad))
+    assert np.array_equal(_np(gi)[others], _np(wi)[others]) and np.array_equal(_np(gd)[others], _np(wd)[others])
+    h.close()
+
+
 # columns: one word of 32, its end, a workgroup's 4,096 words and beyond them; entries of B: under a mask of 64, at the ends of
 # masks and of a workgroup's 4,096 entries, and more than 1,024 workgroups (the sums of sums)
 @pytest.mark.parametrize("metric", SERVED)
