@@ -373,6 +373,8 @@ hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float
     return hipGetLastError();
 }
 
+// (a norm that is not a number is the least: the distances turn a sum that is not a number into 0)
+__device__ __forceinline__ bool less_norm(double a, double than) { return !(a >= than) && than == than; }
 __global__ void __launch_bounds__(256) spd_match_least_kernel(const double *__restrict__ norms, int64_t n_rows, int tile_rows,
                                                               double *__restrict__ least) {
     __shared__ double s_least[256][2];
@@ -381,13 +383,13 @@ __global__ void __launch_bounds__(256) spd_match_least_kernel(const double *__re
     double d0 = __builtin_huge_val(), d1 = 0.0;
     for (int r = tid; r < rows; r += 256) {
         const double2 nb = *reinterpret_cast<const double2 *>(norms + (size_t)(j0 + r) * 2);
-        if (nb.x < d0) { d0 = nb.x; d1 = nb.y; }
+        if (less_norm(nb.x, d0)) { d0 = nb.x; d1 = nb.y; }
     }
     s_least[tid][0] = d0;
     s_least[tid][1] = d1;
     for (int half = 128; half >= 1; half >>= 1) {
         __syncthreads();
-        if (tid < half && s_least[tid + half][0] < s_least[tid][0]) {
+        if (tid < half && less_norm(s_least[tid + half][0], s_least[tid][0])) {
             s_least[tid][0] = s_least[tid + half][0];
             s_least[tid][1] = s_least[tid + half][1];
         }

@@ -413,6 +413,32 @@ def test_the_row_of_the_least_norm_wherever_it_lies_in_its_tile(spd, metric):
     h.close()
 
 
+@pytest.mark.parametrize("metric", ["l1", "l2_expanded", "hellinger", "cosine", "canberra", "jensen_shannon"])
+def test_a_tile_is_not_passed_over_for_a_norm_that_is_not_a_number(spd, metric):
+    """A row of B that holds a NaN shares no column with the queries and lies in a late tile, behind rows that bound the k-th
+    distance: the neighbours are the staged scan's, which takes a sum that is not a number for 0."""
+    cols, m, most = 30_000, 1_024, 1_216
+    n = 11 * most - 40
+    rng = np.random.default_rng(5)
+    c = np.sort(rng.integers(1_000, cols - 4, size=(n, 1)) + np.arange(4), axis=1)
+    values = np.full((n, 4), 2.0)
+    values[9 * most + 300, 1] = values[10 * most + 7, 3] = np.nan
+    B = {"n_rows": n, "n_cols": cols, "indptr": np.arange(n + 1, dtype=np.int64) * 4, "indices": c.reshape(-1).astype(np.int32),
+         "values": values.reshape(-1).astype(np.float32)}
+    A = {"n_rows": m, "n_cols": cols, "indptr": np.arange(m + 1, dtype=np.int64) * 2,
+         "indices": np.stack([np.arange(m) % 900, 900 + np.arange(m) % 100], axis=1).reshape(-1).astype(np.int32),
+         "values": np.full(2 * m, 0.5, np.float32)}
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    plan = spd.testing.host_list_plan(m, 2 * m, n, 4 * n, cols, metric, k_neighbors=3, match_lists=2)
+    assert plan["tile_rows"] == most and plan["tiles"] == 11 > plan["groups"]
+    h, staged = _lists(spd), _lists(spd, match_lists=0)
+    for k in (1, 5):
+        for got, want in zip(h.knn(dA, dB, metric, k), staged.knn(dA, dB, metric, k)):
+            assert np.array_equal(_np(got), _np(want)), (metric, k)
+    staged.close()
+    h.close()
+
+
 @pytest.mark.parametrize("metric", ["inner_product", "cosine", "kl_divergence"])
 def test_a_value_that_is_not_finite_stays_in_its_row_over_runs_of_tiles(spd, metric):
     """Every 20th row of A, each one wavefront's but the first, which the workgroup's wavefronts share, meets a dense column of B
