@@ -322,9 +322,10 @@ spd_status spd_csr_validate(spd_handle *handle, const spd_csr *M, int require_no
  *                 has it; 3: the same, over A's columns.  A call whose lists the caller's scratch does not hold, or the device
  *                 has no memory for, runs by the staged scan; the handle asks the device for that much again
  *                 only after the option is set again.  The sums' order differs between the two ways.
- *   "direct"      1 (default): a small call (up to 2,048 columns, 2^19 pairs, 2^16 stored entries an operand, k-NN over up to
- *                 1,024 rows; not Chebyshev and the semirings that are not spelled as a distance; no other
- *                 knob turned, no lent scratch) is one launch that reads both operands where they lie; 0: never
+ *   "direct"      1 (default): a small call (up to 2,048 columns, 2^19 pairs, 2^16 stored entries an operand, 2^15 rows of B, k-NN
+ *                 over up to 1,024; not Chebyshev and the semirings that are not spelled as a distance; no other
+ *                 knob turned, no lent scratch) whose rows of B are short enough for it to be the fastest way is one launch
+ *                 that reads both operands where they lie; 0: never
  *   "check_plan"  1: verify every index the kernels will form from the plan before the scan is launched (with
  *                 the column lists: the cut of B into tiles and blocks, the grid, A's rows)
  *   "profile"     1: bracket every kernel launch with HIP events (see spd_profile_read)

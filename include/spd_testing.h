@@ -50,6 +50,11 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
                               const char *const *option_names, const int64_t *option_values, int n_options,
                               spd_list_plan *out);
 
+/* Lanes to a row of B in the one launch that a call on operands of these sizes is by default (option "direct");
+ * 0: it runs by the other ways. */
+spd_status spd_host_direct_lanes(const int64_t *b_indptr, int64_t b_rows, int64_t a_rows, int64_t a_nnz, int64_t n_cols,
+                                 spd_metric metric, float p, int k_neighbors, int with_index, int *lanes);
+
 #ifdef __cplusplus
 }
 #endif

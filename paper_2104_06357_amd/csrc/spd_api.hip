@@ -157,6 +157,7 @@ struct spd_handle {
 // the device the plan's arrays, the packed slabs and the row norms in one allocation.
 struct spd_index {
     spd_csr matrix;              // the caller's arrays (they must stay valid and unchanged)
+    int64_t chain = 0, knn_chain = 0;    // of its rows (direct_knn_chain), where a call may be one launch
     int metric = 0;
     float p = 1.0f;
     int device = 0;
@@ -903,19 +904,62 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     return SPD_OK;
 }
 
-// Whether a call is small enough for the one launch of spd_direct.hip: few columns, so that its strips fit (and no row that
-// the lists or the scan would share out), and so few pairs and entries that the launches and uploads of the other ways
-// are what they cost.
-bool direct_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, int knn_k) {
+// Whether a call can be the one launch of spd_direct.hip: few columns, so that its strips fit, and few pairs and entries.
+bool direct_possible(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, int knn_k) {
     if (semiring || h->direct == 0 || !direct_serves(op) || A->n_cols <= 0 || A->n_cols > kDirectColumns) return false;
     if (knn_k > 0 && B->n_rows > kDirectKnnRows) return false;
     // (scratch that the caller lends is asked for as before: a call it does not hold is refused)
     if ((h->ws_external && !h->no_alloc) || !scan_knobs_untouched(h) || h->match_lists != 1) return false;
-    return A->n_rows * B->n_rows <= ((int64_t)1 << 19) && A->nnz <= (1 << 16) && B->nnz <= (1 << 16);
+    return B->n_rows <= kDirectMostRows && A->n_rows * B->n_rows <= ((int64_t)1 << 19) && A->nnz <= (1 << 16) && B->nnz <= (1 << 16);
+}
+// Entries that a lane to each row of B goes through one after the other, the chain of a call: the longest row, or with k-NN, where all
+// rows pass through a workgroup, 256 at a time, the longest of a wavefront's 64 rows each time.
+int64_t direct_knn_chain(const int64_t *ip, int64_t n) {
+    constexpr int kWaves = kDirectRowsB / kWave;
+    int64_t of[kWaves] = {0};
+    for (int64_t j0 = 0; j0 < n; j0 += kWave) {
+        int64_t longest = 0;
+        for (int64_t j = j0; j < std::min(n, j0 + kWave); ++j) longest = std::max(longest, ip[j + 1] - ip[j]);
+        of[j0 / kWave % kWaves] += longest;
+    }
+    return *std::max_element(of, of + kWaves);
+}
+// Lanes to a row of B; 0: the call's launch would take longer than the other ways do.  In microseconds: a launch, and in
+// every round of workgroups that the chip holds the chain of a lane's entries, whose loads are waited for four at a time, and with
+// k-NN the selection; against the launches, the uploads and the host's planning of the other ways.  The constants are fitted
+// to both ways' times of 10,000 pairs of operands (1 to 2^19 rows of 0 to 2,048 entries, one long row among short ones, Zipf
+// and equal lengths, 1 to 2,048 columns, every product, with an index and without).  Of 13,900 others two in 1,000 lose more
+// than a twentieth by the line between them, up to 1.5 times; while a lane took every row, whatever its length, a third did, up
+// to 53 times.  Both sides, other ways / one launch in us:
+//   7 x 194 rows of 1 and 337 over 512 columns, L1                                  52 / 91 with one lane, 30 with four
+//   16 x 1,024 rows of 17 and 53 (Zipf, the longest 1,000), Minkowski, k = 10       73 / 3,546 with one lane
+//   256 x 256 rows of 10, L1                                                        27 / 8.5 with one
+// Four lanes to the row from 16 entries on: at chains of 8 to 16 either takes the same (0.95 to 0.97), at 16 to 24 four
+// take 0.75 times as long, at 64 to 96 0.4 to 0.5 times.
+int direct_lanes(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int knn_k, int64_t chain, bool with_index) {
+    const double m = (double)A->n_rows, n = (double)B->n_rows, cus = (double)std::max(1, h->opt.n_cus);
+    const bool knn = knn_k > 0;
+    const int lanes = chain >= 16 ? kDirectLanes : 1;
+    double entry = 0.82;
+    switch (op) {
+    case OP_DOT: case OP_L1: entry = 0.24; break;
+    case OP_HAMM: case OP_CNT: case OP_KL: entry = 0.31; break;
+    case OP_CANB: entry = 0.36; break;
+    case OP_JS: entry = 0.49; break;
+    case OP_MINK_ANY: entry = 0.6; break;
+    default: break;
+    }
+    const double groups = std::ceil(m / kDirectRows) * (knn ? 1.0 : std::ceil(n / kDirectRowsB));
+    const int held = std::max(1, std::min(2048 / (kDirectRowsB * lanes), (160 * 1024) / (int)(direct_lds_bytes(A->n_cols, B->n_rows, knn_k) + 64)));
+    const double rounds = std::ceil(groups / (cus * held));
+    const double one = 7.0 + rounds * ((double)chain * entry / lanes + (knn ? (lanes > 1 ? 0.018 : 0.012) * n : 0.0)) + 1e-6 * m * (double)B->nnz + 2e-3 * groups;
+    const double others = (knn ? 39.0 : 28.0) - (with_index ? 11.0 : 0.0) + 2.5e-3 * m + (with_index ? 0.12e-3 : 0.42e-3) * (double)B->nnz +
+                          0.15e-3 * (double)A->nnz + (knn ? 50e-6 : 6e-6) * m * n;
+    return one <= 0.85 * others ? lanes : 0;
 }
 // (A and B have been looked through: check_rows)
 spd_status run_direct(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, int op, int knn_k, const OpParams &q,
-                      const MetricInfo &mi, float *out, int64_t *out_idx, float *out_dist) {
+                      const MetricInfo &mi, int lanes, float *out, int64_t *out_idx, float *out_dist) {
     DirectArgs a;
     a.a = DirectCsr{A->indptr, A->indices, A->values, A->n_rows, A->nnz};
     a.b = DirectCsr{B->indptr, B->indices, B->values, B->n_rows, B->nnz};
@@ -927,17 +971,17 @@ spd_status run_direct(spd_handle *h, const spd_csr *A, const spd_csr *B, int met
     a.knn_k = knn_k;
     a.out_idx = out_idx;
     a.out_dist = out_dist;
-    LaunchTimer lt(h, "scan", kDirectRows, kDirectStagingKind, 256, direct_lds_bytes(A->n_cols, B->n_rows, knn_k), A->n_rows,
-                   (A->n_rows + kDirectRows - 1) / kDirectRows * (knn_k > 0 ? 1 : (B->n_rows + 255) / 256));
-    const hipError_t e = launch_direct(h->stream, op, a);
+    LaunchTimer lt(h, "scan", kDirectRows, kDirectStagingKind, kDirectRowsB * lanes, direct_lds_bytes(A->n_cols, B->n_rows, knn_k), A->n_rows,
+                   (A->n_rows + kDirectRows - 1) / kDirectRows * (knn_k > 0 ? 1 : (B->n_rows + kDirectRowsB - 1) / kDirectRowsB));
+    const hipError_t e = launch_direct(h->stream, op, a, lanes);
     if (e != hipSuccess) return hip_fail(h, e, "direct kernel");
     lt.done();
     return SPD_OK;
 }
 
 // (the staged scan's planner refuses a row that is longer than the column count in the operand it stages)
-spd_status refuse_rows(spd_handle *h, const char *name, const int64_t *ip, int64_t rows, int64_t n_cols, bool staged) {
-    const std::string why = check_rows(ip, rows, staged ? n_cols : INT64_MAX);
+spd_status refuse_rows(spd_handle *h, const char *name, const int64_t *ip, int64_t rows, int64_t n_cols, bool staged, int64_t *longest = nullptr) {
+    const std::string why = check_rows(ip, rows, staged ? n_cols : INT64_MAX, longest);
     return why.empty() ? SPD_OK : refuse_plan(h, name, why);
 }
 
@@ -952,7 +996,71 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     const int op = product_of(h, metric, p);
     const bool swap = knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
     const MatchWay way = match_way(h, A, B, op, semiring, swap, knn_k, index != nullptr, index && index->match.list);
-    const bool direct = direct_wanted(h, A, B, op, semiring, knn_k);
+
+    // ---- row pointers on the host: the caller's copies, or read back (the call's only
+    //      synchronisation) ----------------------------------------------------------------
+    const spd_csr *const A0 = A, *const B0 = B;
+    const bool same = !index && A->indptr == B->indptr && A->n_rows == B->n_rows;
+    const int64_t *a_host = A->host_indptr ? A->host_indptr : (same ? B->host_indptr : nullptr);
+    const int64_t *b_host = index ? nullptr : (B->host_indptr ? B->host_indptr : (same ? A->host_indptr : nullptr));
+    const bool copy_a = !a_host;
+    const bool copy_b = !index && !same && !b_host;
+    const size_t ip_bytes = (copy_a ? (size_t)(A->n_rows + 1) * 8 : 0) + (copy_b ? (size_t)(B->n_rows + 1) * 8 : 0);
+    bool swapped = false;
+    std::optional<PinnedLease> lease;
+    const int64_t *a_ip = nullptr, *b_ip = nullptr;
+    // where the two arrays are read from: the caller's memory, or the start of the pinned buffer
+    auto locate = [&]() {
+        int64_t *pin = reinterpret_cast<int64_t *>(h->pinned);
+        a_ip = a_host ? a_host : pin;
+        b_ip = b_host ? b_host : (same ? a_ip : pin + (copy_a ? A0->n_rows + 1 : 0));
+        if (swapped) std::swap(a_ip, b_ip);
+    };
+    // (into a buffer that holds `more` bytes behind them)
+    auto read_rows = [&](size_t more) -> spd_status {
+        lease.emplace(h);
+        const spd_status st = ensure_pinned(h, ip_bytes + more);
+        if (st != SPD_OK) return st;
+        int64_t *pin = reinterpret_cast<int64_t *>(h->pinned);
+        if (copy_a) {
+            e = hipMemcpyAsync(pin, A0->indptr, (size_t)(A0->n_rows + 1) * 8, hipMemcpyDeviceToHost, h->stream);
+            if (e != hipSuccess) return hip_fail(h, e, "copy of A.indptr");
+        }
+        if (copy_b) {
+            e = hipMemcpyAsync(pin + (copy_a ? A0->n_rows + 1 : 0), B0->indptr, (size_t)(B0->n_rows + 1) * 8, hipMemcpyDeviceToHost, h->stream);
+            if (e != hipSuccess) return hip_fail(h, e, "copy of B.indptr");
+        }
+        if (copy_a || copy_b) {
+            e = hipStreamSynchronize(h->stream);
+            if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
+        }
+        return SPD_OK;
+    };
+    spd_status st = SPD_OK;
+    auto check_ends = [&]() -> spd_status {
+        if (a_ip[A->n_rows] != A->nnz || (!index && b_ip[B->n_rows] != B->nnz)) return fail(h, SPD_ERR_BAD_CSR, "indptr[n_rows] != nnz");
+        return SPD_OK;
+    };
+    // (a small call's way depends on the lengths of B's rows, where even equal ones would do; row pointers that are not at hand
+    // are read back for it)
+    int direct = 0;
+    bool b_checked = false;
+    if (direct_possible(h, A, B, op, semiring, knn_k)) {
+        int64_t chain = (B->nnz + B->n_rows - 1) / B->n_rows;
+        if (index) chain = knn_k > 0 ? index->knn_chain : index->chain;
+        direct = direct_lanes(h, A, B, op, knn_k, chain, index != nullptr);
+        if (direct && !index) {
+            if (ip_bytes) st = read_rows(80 * ((size_t)std::max(A->n_rows, B->n_rows) + 4096));         // (whichever operand is staged)
+            if (st != SPD_OK) return st;
+            locate();
+            st = check_ends();
+            if (st == SPD_OK) st = refuse_rows(h, "B", b_ip, B->n_rows, A->n_cols, false, &chain);
+            if (st != SPD_OK) return st;
+            b_checked = true;
+            if (knn_k > 0) chain = direct_knn_chain(b_ip, B->n_rows);
+            direct = direct_lanes(h, A, B, op, knn_k, chain, false);
+        }
+    }
     bool lists = way.way != 0 && !direct;
     if (lists) {
         if (way.way == 1 && index && (index->match_op != op || std::memcmp(&index->match.shape, &way.s, sizeof way.s) != 0))
@@ -961,18 +1069,18 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         if (h->ws_external && way.L.end > h->ws_bytes) lists = false;
         // (and so does a device that has no memory left for them; so much is not asked for again)
         if (lists && !h->ws_external) {
-            const spd_status st = way.L.end < h->lists_refused ? ensure_workspace(h, way.L.end) : SPD_ERR_WORKSPACE;
-            if (st == SPD_ERR_WORKSPACE) {
+            const spd_status room = way.L.end < h->lists_refused ? ensure_workspace(h, way.L.end) : SPD_ERR_WORKSPACE;
+            if (room == SPD_ERR_WORKSPACE) {
                 h->lists_refused = std::min(h->lists_refused, way.L.end);
                 h->err.clear();
                 (void)hipGetLastError();
                 lists = false;
-            } else if (st != SPD_OK) {
-                return st;
+            } else if (room != SPD_OK) {
+                return room;
             }
         }
     }
-    const bool swapped = swap && !lists && !direct;
+    swapped = swap && !lists && !direct;
     if (swapped) std::swap(A, B);           // from here on A is the staged operand, B the streamed one
     const int64_t m = A->n_rows, n = B->n_rows;
     const int64_t out_stride_staged = swapped ? 1 : n, out_stride_streamed = swapped ? m : 1;
@@ -986,48 +1094,22 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         t_begin = t;
     };
 
-    // ---- row pointers on the host: the caller's copies, or read back (the call's only
-    //      synchronisation) ----------------------------------------------------------------
-    const bool same = !index && A->indptr == B->indptr && m == n;
-    const int64_t *a_host = A->host_indptr ? A->host_indptr : (same ? B->host_indptr : nullptr);
-    const int64_t *b_host = index ? nullptr : (B->host_indptr ? B->host_indptr : (same ? A->host_indptr : nullptr));
-    const bool copy_a = !a_host;
-    const bool copy_b = !index && !same && !b_host;
-    const size_t ip_bytes = (copy_a ? (size_t)(m + 1) * 8 : 0) + (copy_b ? (size_t)(n + 1) * 8 : 0);
-    std::optional<PinnedLease> lease;
-    if (!direct || ip_bytes) lease.emplace(h);           // (a direct call stages nothing else)
-    // (sized for the two plan uploads as well, which follow the row pointers in the buffer)
-    spd_status st = direct && !ip_bytes ? SPD_OK : ensure_pinned(h, ip_bytes + (index ? 0 : 32 * ((size_t)n + 4096)) + 48 * ((size_t)m + 4096));
+    if (!lease && (!direct || ip_bytes)) {               // (a direct call stages nothing else)
+        // (sized for the two plan uploads as well, which follow the row pointers in the buffer)
+        st = read_rows((index ? 0 : 32 * ((size_t)n + 4096)) + 48 * ((size_t)m + 4096));
+        if (st != SPD_OK) return st;
+    }
+    locate();
+    st = check_ends();
     if (st != SPD_OK) return st;
-    // where the two arrays are read from: the caller's memory, or the start of the pinned buffer
-    auto locate = [&](const int64_t *&a_at, const int64_t *&b_at) {
-        int64_t *pin = reinterpret_cast<int64_t *>(h->pinned);
-        a_at = a_host ? a_host : pin;
-        b_at = b_host ? b_host : (same ? a_at : pin + (copy_a ? m + 1 : 0));
-    };
-    const int64_t *a_ip = nullptr, *b_ip = nullptr;
-    locate(a_ip, b_ip);
-    if (copy_a) {
-        e = hipMemcpyAsync(const_cast<int64_t *>(a_ip), A->indptr, (size_t)(m + 1) * 8, hipMemcpyDeviceToHost, h->stream);
-        if (e != hipSuccess) return hip_fail(h, e, "copy of A.indptr");
-    }
-    if (copy_b) {
-        e = hipMemcpyAsync(const_cast<int64_t *>(b_ip), B->indptr, (size_t)(n + 1) * 8, hipMemcpyDeviceToHost, h->stream);
-        if (e != hipSuccess) return hip_fail(h, e, "copy of B.indptr");
-    }
-    if (copy_a || copy_b) {
-        e = hipStreamSynchronize(h->stream);
-        if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
-    }
-    if (a_ip[m] != A->nnz || (!index && b_ip[n] != B->nnz)) return fail(h, SPD_ERR_BAD_CSR, "indptr[n_rows] != nnz");
     lap("indptr d2h");
     if (lists || direct) {
         const bool b_staged = knn_k == 0 && !index && swap;
-        st = index ? SPD_OK : refuse_rows(h, "B", b_ip, n, A->n_cols, b_staged);
+        st = index || (b_checked && !b_staged) ? SPD_OK : refuse_rows(h, "B", b_ip, n, A->n_cols, b_staged);
         if (st == SPD_OK) st = refuse_rows(h, "A", a_ip, m, A->n_cols, !b_staged);
         if (st != SPD_OK) return st;
     }
-    if (direct) return run_direct(h, A, B, metric, op, knn_k, op_params(metric, p, A->n_cols, nullptr), metric_info(metric), out, out_idx, out_dist);
+    if (direct) return run_direct(h, A, B, metric, op, knn_k, op_params(metric, p, A->n_cols, nullptr), metric_info(metric), direct, out, out_idx, out_dist);
     if (lists)
         return run_match(h, A, B, metric, op, knn_k, op_params(metric, p, A->n_cols, nullptr), metric_info(metric), way, a_ip, b_ip,
                          ip_bytes, out, out_idx, out_dist, index);
@@ -1096,7 +1178,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         st = ensure_pinned(h, pin_a + (size_t)m * (sizeof(ARow) + 16) + (64 << 10));
         if (st != SPD_OK) return st;
         std::memcpy(h->pinned, keep.data(), ip_bytes);
-        locate(a_ip, b_ip);
+        locate();
     }
     BDevice bd;
     auto stage_b = [&]() -> spd_status {
@@ -1600,6 +1682,9 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         b_ip = pin;
     }
     if (b_ip[n] != Index->nnz) return fail(h, SPD_ERR_BAD_CSR, "indptr[n_rows] != nnz");
+    if (n <= kDirectMostRows)
+        for (int64_t j = 0; j < n; ++j) ix->chain = std::max(ix->chain, b_ip[j + 1] - b_ip[j]);
+    if (n <= kDirectKnnRows) ix->knn_chain = direct_knn_chain(b_ip, n);
     std::string why;
     try {
         PlanOptions opt_b = h->opt;
@@ -1829,6 +1914,20 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     out->index_bytes = index_keeps_lists(&h, &B, op, kept, L) ? (int64_t)L.end : 0;
     out->consistent = match_check(h.opt, s, g, op, a_rows, b_rows, n_cols, b_nnz).empty();
     out->scratch_bytes = (int64_t)layout_match_call(s, g, a_rows, a_nnz, b_rows, b_nnz, k_neighbors, !with_index, 0).end;
+    return SPD_OK;
+}
+
+spd_status spd_host_direct_lanes(const int64_t *b_indptr, int64_t b_rows, int64_t a_rows, int64_t a_nnz, int64_t n_cols, spd_metric metric,
+                                 float p, int k_neighbors, int with_index, int *lanes) {
+    if (!b_indptr || !lanes) return SPD_ERR_NULL;
+    if ((int)metric < 0 || (int)metric >= SPD_METRIC_COUNT) return SPD_ERR_BAD_METRIC;
+    spd_handle h;
+    const spd_csr A{a_rows, n_cols, a_nnz, nullptr, nullptr, nullptr, nullptr}, B{b_rows, n_cols, b_indptr[b_rows], nullptr, nullptr, nullptr, nullptr};
+    const int op = product_of(&h, effective_metric((int)metric, p), p);
+    int64_t chain = 0;
+    if (!check_rows(b_indptr, b_rows, INT64_MAX, &chain).empty()) return SPD_ERR_BAD_CSR;
+    if (k_neighbors > 0) chain = direct_knn_chain(b_indptr, b_rows);
+    *lanes = direct_possible(&h, &A, &B, op, nullptr, k_neighbors) ? direct_lanes(&h, &A, &B, op, k_neighbors, chain, with_index != 0) : 0;
     return SPD_OK;
 }
 

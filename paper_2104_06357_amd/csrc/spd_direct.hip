@@ -2,16 +2,17 @@
 //
 // Where the operands are a few thousand entries the plan, its uploads, the repack and their launches are all
 // that a call costs (256 x 256 rows of 10, L1: 27 us a call, one after the other, of which the scan is 5).  Here a
-// workgroup puts four rows of A into a strip of LDS, four values to a column, and a lane takes a row of B
-// where the caller has it, looks its columns up and sums the row's norm on the way.  No scratch, no upload, no
-// second launch.  Bound by the latency of a row's entries (four in flight) and by the launch itself.
+// workgroup puts four rows of A into a strip of LDS, four values to a column, and a lane, or four where rows are longer, takes a
+// row of B where the caller has it, looks its columns up and sums the row's norm on the way.  No scratch, no upload, no
+// second launch.  Bound by the latency of a row's entries (four of a lane in flight) and by the launch itself: 7 x 194
+// rows of 337, L1, 91 us with a lane to the row, 30 with four.
 #include "spd_direct.h"
 #include "spd_scan_impl.h"
 
 namespace spd {
 
 namespace {
-constexpr int kDirectThreads = 256, kDirectUnroll = 4;
+constexpr int kDirectUnroll = 4;
 __device__ __forceinline__ int64_t clamped(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
 }  // namespace
 
@@ -19,17 +20,20 @@ uint32_t direct_lds_bytes(int64_t n_cols, int64_t n, int knn_k) {
     return (uint32_t)(n_cols * (kDirectRows * 4) + (knn_k > 0 ? n * (kDirectRows * 4) : 0));
 }
 
-template <int OP, bool KNN>
-__global__ void __launch_bounds__(kDirectThreads) spd_direct_kernel(const DirectArgs args) {
+// G: lanes to a row of B.
+template <int OP, bool KNN, int G>
+__global__ void __launch_bounds__(kDirectRowsB * G) spd_direct_kernel(const DirectArgs args) {
     using O = Op<OP>;
+    using Acc = typename O::Acc;
+    constexpr int kThreads = kDirectRowsB * G;
     extern __shared__ __align__(16) float s_strip[];              // [column][row of A], then with k-NN [row of A][row of B]
     __shared__ double s_norm[kDirectRows][2];
-    static_assert(kDirectRows == kDirectThreads / kWave, "a wavefront to a row of A");
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
+    static_assert(kDirectRows * kWave <= kThreads && (G == 1 || G == kDirectRows), "a wavefront to a row of A, a lane of a row of B too");
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6), sub = tid % G;
     const int64_t i0 = (int64_t)blockIdx.x * kDirectRows, n = args.b.rows;
-    for (uint32_t c = (uint32_t)tid; c < args.k; c += kDirectThreads) reinterpret_cast<float4 *>(s_strip)[c] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (uint32_t c = (uint32_t)tid; c < args.k; c += kThreads) reinterpret_cast<float4 *>(s_strip)[c] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     __syncthreads();
-    {
+    if (wave < kDirectRows) {
         const int64_t i = i0 + wave;
         double s0 = 0.0, s1 = 0.0;
         if (i < args.a.rows) {
@@ -48,24 +52,24 @@ __global__ void __launch_bounds__(kDirectThreads) spd_direct_kernel(const Direct
     __syncthreads();
     float *s_dist = s_strip + (size_t)args.k * kDirectRows;
     // (k-NN: every row of B passes through the workgroup; pairwise: 256 of them)
-    const int64_t j_first = KNN ? 0 : (int64_t)blockIdx.y * kDirectThreads, j_last = KNN ? n : min(n, j_first + kDirectThreads);
-    for (int64_t j = j_first + tid; j < j_last; j += kDirectThreads) {
+    const int64_t j_first = KNN ? 0 : (int64_t)blockIdx.y * kDirectRowsB, j_last = KNN ? n : min(n, j_first + kDirectRowsB);
+    for (int64_t j = j_first + tid / G; j < j_last; j += kDirectRowsB) {
         const int64_t begin = clamped(args.b.indptr[j], 0, args.b.nnz), end = clamped(args.b.indptr[j + 1], begin, args.b.nnz);
-        typename O::Acc acc[kDirectRows];
+        Acc acc[kDirectRows];
 #pragma unroll
         for (int r = 0; r < kDirectRows; ++r) O::init(acc[r]);
         double s0 = 0.0, s1 = 0.0;
-        for (int64_t e0 = begin; e0 < end; e0 += kDirectUnroll) {
+        for (int64_t e0 = begin + sub; e0 < end; e0 += kDirectUnroll * G) {
             uint32_t c[kDirectUnroll];
             float v[kDirectUnroll];
 #pragma unroll
             for (int u = 0; u < kDirectUnroll; ++u) {
-                c[u] = e0 + u < end ? (uint32_t)args.b.indices[e0 + u] : 0xFFFFFFFFu;
-                v[u] = e0 + u < end ? args.b.values[e0 + u] : 0.0f;
+                c[u] = e0 + u * G < end ? (uint32_t)args.b.indices[e0 + u * G] : 0xFFFFFFFFu;
+                v[u] = e0 + u * G < end ? args.b.values[e0 + u * G] : 0.0f;
             }
 #pragma unroll
             for (int u = 0; u < kDirectUnroll; ++u) {
-                if (e0 + u >= end) break;
+                if (e0 + u * G >= end) break;
                 const float b = transform_value(args.transform, v[u]);
                 norm_accumulate(args.norm, b, args.q.p, s0, s1);
                 if (c[u] < args.k) {
@@ -78,22 +82,45 @@ __global__ void __launch_bounds__(kDirectThreads) spd_direct_kernel(const Direct
                 }
             }
         }
+        if constexpr (G > 1) {                                    // (a row's lanes are neighbours and here together)
+#pragma unroll
+            for (int d = G / 2; d >= 1; d >>= 1) {
+                s0 += __shfl_xor(s0, d);
+                s1 += __shfl_xor(s1, d);
+#pragma unroll
+                for (int r = 0; r < kDirectRows; ++r) O::combine(acc[r], acc_shfl_xor<OP>(acc[r], d));
+            }
+        }
         double nb0, nb1;
         norm_derive(args.q.metric, args.q.k, s0, s1, nb0, nb1);
         for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
             constexpr int MT = decltype(metric_tag)::value;
-#pragma unroll
-            for (int r = 0; r < kDirectRows; ++r) {
-                const float d = finish_as<MT>(args.q, O::v0(acc[r]), O::v1(acc[r]), O::v2(acc[r]), s_norm[r][0], s_norm[r][1], nb0, nb1);
+            auto finish = [&](double v0, double v1, double v2, int r) {
+                const float d = finish_as<MT>(args.q, v0, v1, v2, s_norm[r][0], s_norm[r][1], nb0, nb1);
                 if constexpr (KNN) s_dist[(size_t)r * (size_t)n + (size_t)j] = MT == MT_INNER ? 0.0f - d : d;
                 else if (i0 + r < args.a.rows) args.out[(size_t)(i0 + r) * (size_t)n + (size_t)j] = d;
+            };
+            if constexpr (G == 1) {
+#pragma unroll
+                for (int r = 0; r < kDirectRows; ++r) finish(O::v0(acc[r]), O::v1(acc[r]), O::v2(acc[r]), r);
+            } else {
+                double v0 = O::v0(acc[0]), v1 = O::v1(acc[0]), v2 = O::v2(acc[0]);       // (a lane to a row of A)
+#pragma unroll
+                for (int r = 1; r < kDirectRows; ++r) {
+                    double w0 = O::v0(acc[r]), w1 = O::v1(acc[r]), w2 = O::v2(acc[r]);
+                    asm volatile("" : "+v"(w0), "+v"(w1), "+v"(w2));          // (else the sums are indexed, in memory)
+                    v0 = sub == r ? w0 : v0;
+                    v1 = sub == r ? w1 : v1;
+                    v2 = sub == r ? w2 : v2;
+                }
+                finish(v0, v1, v2, sub);
             }
         });
     }
     if constexpr (KNN) {
         __syncthreads();
         const int64_t i = i0 + wave;
-        if (i >= args.a.rows) return;
+        if (wave >= kDirectRows || i >= args.a.rows) return;
         // the k best of a wavefront's row, ascending over the lanes, 64 rows of B at a time
         const int k = args.knn_k;
         uint64_t best = kKnnUnused;
@@ -116,27 +143,30 @@ __global__ void __launch_bounds__(kDirectThreads) spd_direct_kernel(const Direct
     }
 }
 
-template <int OP> static hipError_t launch_direct_op(hipStream_t st, const DirectArgs &args) {
+template <int OP, int G> static hipError_t launch_direct_op(hipStream_t st, const DirectArgs &args) {
     const uint32_t lds = direct_lds_bytes((int64_t)args.k, args.b.rows, args.knn_k);
     const unsigned groups = (unsigned)((args.a.rows + kDirectRows - 1) / kDirectRows);
-    if (args.knn_k > 0) hipLaunchKernelGGL((spd_direct_kernel<OP, true>), dim3(groups), dim3(kDirectThreads), lds, st, args);
+    if (args.knn_k > 0) hipLaunchKernelGGL((spd_direct_kernel<OP, true, G>), dim3(groups), dim3(kDirectRowsB * G), lds, st, args);
     else
-        hipLaunchKernelGGL((spd_direct_kernel<OP, false>), dim3(groups, (unsigned)((args.b.rows + kDirectThreads - 1) / kDirectThreads)),
-                           dim3(kDirectThreads), lds, st, args);
+        hipLaunchKernelGGL((spd_direct_kernel<OP, false, G>), dim3(groups, (unsigned)((args.b.rows + kDirectRowsB - 1) / kDirectRowsB)),
+                           dim3(kDirectRowsB * G), lds, st, args);
     return hipGetLastError();
 }
+template <int OP> static hipError_t launch_direct_by(hipStream_t st, const DirectArgs &args, int lanes) {
+    return lanes == 1 ? launch_direct_op<OP, 1>(st, args) : launch_direct_op<OP, kDirectLanes>(st, args);
+}
 
-hipError_t launch_direct(hipStream_t st, int op, const DirectArgs &args) {
+hipError_t launch_direct(hipStream_t st, int op, const DirectArgs &args, int lanes) {
     switch (op) {
-    case OP_DOT: return launch_direct_op<OP_DOT>(st, args);
-    case OP_L1: return launch_direct_op<OP_L1>(st, args);
-    case OP_CANB: return launch_direct_op<OP_CANB>(st, args);
-    case OP_HAMM: return launch_direct_op<OP_HAMM>(st, args);
-    case OP_KL: return launch_direct_op<OP_KL>(st, args);
-    case OP_JS: return launch_direct_op<OP_JS>(st, args);
-    case OP_CNT: return launch_direct_op<OP_CNT>(st, args);
-    case OP_MINK: return launch_direct_op<OP_MINK>(st, args);
-    case OP_MINK_ANY: return launch_direct_op<OP_MINK_ANY>(st, args);
+    case OP_DOT: return launch_direct_by<OP_DOT>(st, args, lanes);
+    case OP_L1: return launch_direct_by<OP_L1>(st, args, lanes);
+    case OP_CANB: return launch_direct_by<OP_CANB>(st, args, lanes);
+    case OP_HAMM: return launch_direct_by<OP_HAMM>(st, args, lanes);
+    case OP_KL: return launch_direct_by<OP_KL>(st, args, lanes);
+    case OP_JS: return launch_direct_by<OP_JS>(st, args, lanes);
+    case OP_CNT: return launch_direct_by<OP_CNT>(st, args, lanes);
+    case OP_MINK: return launch_direct_by<OP_MINK>(st, args, lanes);
+    case OP_MINK_ANY: return launch_direct_by<OP_MINK_ANY>(st, args, lanes);
     default: return hipErrorInvalidValue;
     }
 }

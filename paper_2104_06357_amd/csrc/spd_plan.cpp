@@ -32,13 +32,15 @@ int occupancy_bucket(uint32_t stage_bytes, int64_t lds_total) {
 
 }  // namespace
 
-std::string check_rows(const int64_t *indptr, int64_t n_rows, int64_t longest) {
+std::string check_rows(const int64_t *indptr, int64_t n_rows, int64_t longest, int64_t *found) {
     if (n_rows && indptr[0] != 0) return "indptr[0] != 0";
-    int64_t too_long = -1;
+    int64_t too_long = -1, most = 0;
     for (int64_t j = 0; j < n_rows; ++j) {
         if (indptr[j + 1] < indptr[j]) return fmt("row pointers decrease at row", j);
         if (too_long < 0 && indptr[j + 1] - indptr[j] > longest) too_long = j;
+        most = std::max(most, indptr[j + 1] - indptr[j]);
     }
+    if (found) *found = most;
     return too_long < 0 ? std::string() : fmt("row longer than the column count", too_long);
 }
 

@@ -262,8 +262,8 @@ std::string plan_staging(int64_t n_cols, int metric, int op, bool knn, const Pla
                          int &min_r, uint64_t &dmax);
 
 // What plan_a and plan_b find wrong with row pointers, for the calls that run without their plans: empty
-// if nothing.  No row may hold more than `longest` entries.
-std::string check_rows(const int64_t *indptr, int64_t n_rows, int64_t longest);
+// if nothing.  No row may hold more than `longest` entries; `found` receives how many the longest holds.
+std::string check_rows(const int64_t *indptr, int64_t n_rows, int64_t longest, int64_t *found = nullptr);
 
 // Both return an empty string on success, else the reason.
 std::string plan_b(const int64_t *indptr, int64_t n_rows, const PlanOptions &opt, BPlan &out);

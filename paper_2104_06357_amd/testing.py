@@ -53,3 +53,14 @@ def host_list_plan(a_rows, a_nnz, b_rows, b_nnz, n_cols, metric, p=2.0, k_neighb
     if st != 0:
         raise SpdError(st, "spd_host_list_plan")
     return {name: getattr(out, name) for name, _ in _ListPlan._fields_}
+
+
+def host_direct_lanes(b_indptr, a_rows, a_nnz, n_cols, metric, p=2.0, k_neighbors=0, with_index=False) -> int:
+    import numpy as np
+    b_indptr = np.ascontiguousarray(b_indptr, dtype=np.int64)
+    out, i64 = ctypes.c_int(), ctypes.c_int64
+    st = lib().spd_host_direct_lanes(ctypes.c_void_p(b_indptr.ctypes.data), i64(b_indptr.size - 1), i64(a_rows), i64(a_nnz), i64(n_cols), metric_id(metric),
+                                     ctypes.c_float(p), int(k_neighbors), int(with_index), ctypes.byref(out))
+    if st != 0:
+        raise SpdError(st, "spd_host_direct_lanes")
+    return out.value

@@ -74,6 +74,60 @@ def test_parity(spd, metric, m, n, cols, lengths):
     h.close()
 
 
+# four lanes to a row of B: rows around the 4 entries that they hold together, the 16 in flight and several rounds of them; rows of B
+# around the 256 of a workgroup, k-NN's strides of them and its 1,024; fewer rows of A than a workgroup's four
+@pytest.mark.parametrize("metric", SERVED)
+@pytest.mark.parametrize("m,n,cols,lengths", [(1, 1, 70, (17,)), (3, 255, 200, (16, 3, 0, 15, 33, 4)), (6, 257, 100, (31, 32, 33, 1, 5)),
+                                              (2, 1024, 64, (2, 9, 8, 3, 1)), (9, 40, 128, (64, 65, 0, 47))])
+def test_four_lanes_to_a_row(spd, metric, m, n, cols, lengths):
+    rng = np.random.default_rng(m + 10 * n + cols)
+    A, B, p = _matrix(rng, m, cols, (7, 64, 0, 20)), _matrix(rng, n, cols, lengths), _p_of(metric)
+    print("direct, four lanes", metric, m, n, cols, flush=True)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], p)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = spd.Handle()
+    h.set_option("profile", 1)
+    for k in (0, min(n, 33)):
+        lanes = spd.testing.host_direct_lanes(B["indptr"], m, len(A["values"]), cols, metric, p, k)
+        assert lanes == (4 if k or max(lengths) >= 16 else 1)
+        if k == 0:
+            assert_distances_close(_np(h.pairwise(dA, dB, metric, p)), want, metric)
+        else:
+            idx, dist = h.knn(dA, dB, metric, k, p)
+            assert_knn_matches(_np(idx), _np(dist), want, k, metric, metric)
+        assert [(r["staging_kind"], r["block"]) for r in h.profile_read()] == [(7, 256 * lanes)]
+    h.close()
+
+
+@pytest.mark.parametrize("law", ["all long", "one long"])
+def test_long_rows_run_by_the_other_ways(spd, law):
+    """A lane, or four, would go through 2,048 entries one after the other while the other lanes are idle."""
+    rng = np.random.default_rng(8)
+    n, cols, k = 32 if law == "all long" else 700, 2048, 5
+    lengths = np.full(n, 2048 if law == "all long" else 3)
+    lengths[n // 2] = 2048
+    idx = [np.sort(rng.choice(cols, size=c, replace=False)) for c in lengths]
+    B = {"n_rows": n, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64),
+         "indices": np.concatenate(idx).astype(np.int32), "values": (rng.integers(1, 9, size=int(lengths.sum())) / 8.0).astype(np.float32)}
+    A = _matrix(rng, 32, cols, (5, 60, 0))
+    want = oracle.pairwise(A, B, "manhattan")
+    h = spd.Handle()
+    h.set_option("profile", 1)
+    for host in (True, False):
+        dA, dB = (spd.DeviceCsr.from_host(M, keep_host_indptr=host) for M in (A, B))
+        assert_distances_close(_np(h.pairwise(dA, dB, "l1")), want, law)
+        assert not {kind for _, kind in _kinds(h)} & {7}
+        i, d = h.knn(dA, dB, "l1", k)
+        assert not {kind for _, kind in _kinds(h)} & {7}
+        assert_knn_matches(_np(i), _np(d), want, k, "l1", law)
+        index = h.index_create(dB, "l1")
+        i, d = index.knn(dA, k)
+        assert not {kind for _, kind in _kinds(h)} & {7}
+        assert_knn_matches(_np(i), _np(d), want, k, "l1", law)
+        index.close()
+    h.close()
+
+
 def test_where_it_ends(spd):
     """One row, column, pair or entry more than it takes, k-NN over too many rows, products and knobs it does not have."""
     rng = np.random.default_rng(4)

@@ -315,3 +315,33 @@ def test_an_index_keeps_lists_that_calls_may_want_within_the_stated_memory():
         # (Minkowski's tiles are half as long: over 194,000 columns their bounds outgrow rows of 160)
         for metric in ("cosine", "l1", "canberra", "jensen_shannon") + (("minkowski",) if cols < 194_000 else ()):
             assert kept(n, mean, cols, metric) > 0, (n, mean, cols, metric)
+
+
+def test_small_calls_are_one_launch_where_no_row_of_b_is_long():
+    def lanes(m, mean_a, lengths, cols, metric, **more):
+        return spd.testing.host_direct_lanes(np.concatenate([[0], np.cumsum(lengths)]), m, m * mean_a, cols, metric, **more)
+
+    def one_long(n, short, longest):
+        return [longest] + [short] * (n - 1)
+
+    # both ways measured, others / one launch in us: 27 / 8.5, 52 / 30
+    assert lanes(256, 10, [10] * 256, 512, "l1") == 1
+    assert lanes(7, 1, [337] * 194, 512, "l1") == 4
+    # 59 / 3,140 with a lane to the row, 73 / 3,546, 31 / 1,616, 41 / 1,510, 40 / 1,309
+    assert lanes(10_633, 6, one_long(47, 700, 2_048), 2_048, "jensen_shannon") == 0
+    assert lanes(16, 17, one_long(1_024, 52, 1_000), 1_000, "minkowski", p=3.0, k_neighbors=10) == 0
+    assert lanes(3, 2, one_long(9, 400, 2_048), 2_048, "minkowski", p=3.0) == 0
+    assert lanes(16, 1, one_long(3, 10, 1_868), 2_048, "minkowski", p=3.0, k_neighbors=3) == 0
+    assert lanes(1, 3, one_long(7, 2, 1_653), 2_048, "minkowski", p=3.0, k_neighbors=7) == 0
+    # longer rows turn the choice once, sooner with an index, which leaves less for one launch to save
+    for metric in ("l1", "hamming", "jensen_shannon", "minkowski"):
+        for k in (0, 5):
+            plain, index = ([lanes(64, 10, [c] * 30, 2_048, metric, k_neighbors=k, with_index=ix) > 0 for c in (1, 4, 16, 64, 256, 1_024, 2_048)]
+                            for ix in (False, True))
+            assert plain[0] and not plain[-1] and plain == sorted(plain, reverse=True) and index == sorted(index, reverse=True)
+            assert sum(index) <= sum(plain)
+    # one entry, column, pair or row more than it takes
+    assert lanes(8, 1, [1] * 1_024, 2_048, "l1") > 0 and lanes(8, 1, [1] * 1_024, 2_049, "l1") == 0
+    assert lanes(1, 1, [1] * 32_768, 64, "l1") > 0 and lanes(1, 1, [1] * 32_769, 64, "l1") == 0
+    assert lanes(8, 1, [1] * 1_024, 64, "l1", k_neighbors=3) > 0 and lanes(8, 1, [1] * 1_025, 64, "l1", k_neighbors=3) == 0
+    assert lanes(8, 1, [1] * 64, 64, "chebyshev") == 0
