@@ -1094,7 +1094,9 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         t_begin = t;
     };
 
-    if (!lease && (!direct || ip_bytes)) {               // (a direct call stages nothing else)
+    // (a direct call stages nothing else; the entry point that allocates nothing refuses what its staging memory does not hold, whichever
+    // way a call runs)
+    if (!lease && (!direct || ip_bytes || h->no_alloc)) {
         // (sized for the two plan uploads as well, which follow the row pointers in the buffer)
         st = read_rows((index ? 0 : 32 * ((size_t)n + 4096)) + 48 * ((size_t)m + 4096));
         if (st != SPD_OK) return st;

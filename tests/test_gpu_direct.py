@@ -178,3 +178,26 @@ def test_what_is_refused(spd):
                     assert got[0] == got[1], (bad, host, got)
     h.close()
     staged.close()
+
+
+def test_static_staging_is_asked_for_as_by_the_other_ways(spd):
+    """The entry point that allocates nothing refuses operands whose plans its staging memory does not hold, also where one
+    launch would need no plan."""
+    import torch
+    h, staged = spd.Handle(), spd.Handle()
+    staged.set_option("direct", 0)
+    for m, taken in ((1_000, True), (80_000, True), (100_000, False)):
+        A, B = (spd.DeviceCsr.from_host({"n_rows": r, "n_cols": 64, "indptr": np.minimum(np.arange(r + 1), 50_000).astype(np.int64),
+                                         "indices": (np.arange(min(r, 50_000)) % 64).astype(np.int32),
+                                         "values": np.ones(min(r, 50_000), np.float32)}) for r in (m, 2))
+        out = [torch.full((m, 2), -1.0, device="cuda") for _ in range(2)]
+        for x, o in zip((h, staged), out):
+            if taken:
+                x.pairwise_static(A, B, "l1", o)
+            else:
+                with pytest.raises(spd.SpdError) as e:
+                    x.pairwise_static(A, B, "l1", o)
+                assert e.value.status_name == "SPD_ERR_WORKSPACE"
+        assert np.array_equal(_np(out[0]), _np(out[1]))
+    h.close()
+    staged.close()
