@@ -35,15 +35,18 @@ spd_status spd_host_plan_summary(const int64_t *a_indptr, int64_t a_rows, const 
                                  int n_options, char *json, size_t cap);
 
 /* Whether a call on operands of these sizes (`k_neighbors` = 0 for pairwise, `with_index` for the calls
- * on a prepared index) takes the column lists (option "match_lists"), and how it cuts them. */
+ * on a prepared index) takes the column lists (option "match_lists"), and how it cuts them.  (Of a call that takes none: how
+ * the lists over all columns would be cut.  Small calls that run in one launch: spd_host_direct_lanes.) */
 typedef struct {
-    int32_t wanted;
+    int32_t wanted;                 /* over all columns, were an index to keep them */
     int32_t tiles, tile_rows;       /* of B */
     int32_t slices, groups;         /* workgroups: slices of A's rows times groups of tiles */
     int32_t consistent;             /* what option "check_plan" finds of the cut */
     int64_t scratch_bytes;
     int64_t index_bytes;            /* what an index keeps of lists; 0: none */
     int32_t run;                    /* tiles that a wavefront goes through with a row of A */
+    int32_t way;                    /* 0: the staged scan, 1: lists over all columns, 2: over the columns that A stores */
+    int64_t columns;                /* that the lists are laid out for */
 } spd_list_plan;
 spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int64_t b_nnz, int64_t n_cols,
                               spd_metric metric, float p, int k_neighbors, int with_index,

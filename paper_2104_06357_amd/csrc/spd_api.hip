@@ -718,6 +718,7 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     MatchShape s;
     if (semiring || A->n_rows <= 0 || !match_possible(h, B, op, s)) return false;
     if (match_items(s, match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
+    if (!match_launches_fit(s, A->n_rows, A->nnz, false)) return false;
     if (h->match_lists == 2) return true;
     if (!match_suits(h, B, op, s)) return false;
     // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.34; 1,024 x 300,000 of 230, cosine
@@ -737,6 +738,7 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
     if (s.n_tiles <= 0 || s.list_entries(B->nnz) >= ((int64_t)1 << 29)) return false;
     if (match_items(s, match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
+    if (!match_launches_fit(s, A->n_rows, A->nnz, true)) return false;
     if (h->match_lists == 3) return true;
     if (h->match_lists != 1 || !scan_knobs_untouched(h) || !match_bounds_fit(s, B->nnz)) return false;
     // (where the lists over all columns have room for their bounds, the copy is not worth its time)
@@ -1903,19 +1905,27 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     const bool knn = k_neighbors > 0, swap = !knn && !with_index && swap_wanted(&h, &A, &B, run_as, nullptr);
     std::memset(out, 0, sizeof *out);
     out->wanted = match_wanted(&h, &A, &B, op, nullptr, swap, knn);
-    const MatchShape s = match_shape(h.opt.lds_budget, op, b_rows, n_cols, b_nnz);
-    if (s.n_tiles <= 0) return SPD_OK;
-    const MatchGrid g = match_grid(h.opt, s, a_rows, a_nnz, b_nnz, knn);
-    out->tiles = s.n_tiles;
-    out->tile_rows = s.tile_rows;
-    out->slices = g.slices;
-    out->groups = g.groups;
-    out->run = g.run;
     MatchShape kept;
     MatchLayout L;
-    out->index_bytes = index_keeps_lists(&h, &B, op, kept, L) ? (int64_t)L.end : 0;
-    out->consistent = match_check(h.opt, s, g, op, a_rows, b_rows, n_cols, b_nnz).empty();
-    out->scratch_bytes = (int64_t)layout_match_call(s, g, a_rows, a_nnz, b_rows, b_nnz, k_neighbors, !with_index, 0).end;
+    const bool keeps = index_keeps_lists(&h, &B, op, kept, L);
+    out->index_bytes = keeps ? (int64_t)L.end : 0;
+    MatchWay w = match_way(&h, &A, &B, op, nullptr, swap, k_neighbors, with_index != 0, keeps);
+    out->way = w.way;
+    if (w.way == 0) {                    // (the cut that the lists over all columns would have)
+        w.columns = n_cols;
+        w.s = match_shape(h.opt.lds_budget, op, b_rows, n_cols, b_nnz);
+        if (w.s.n_tiles <= 0) return SPD_OK;
+        w.g = match_grid(h.opt, w.s, a_rows, a_nnz, b_nnz, knn);
+        w.L = layout_match_call(w.s, w.g, a_rows, a_nnz, b_rows, b_nnz, k_neighbors, !with_index, 0);
+    }
+    out->columns = w.columns;
+    out->tiles = w.s.n_tiles;
+    out->tile_rows = w.s.tile_rows;
+    out->slices = w.g.slices;
+    out->groups = w.g.groups;
+    out->run = w.g.run;
+    out->consistent = match_check(h.opt, w.s, w.g, op, a_rows, b_rows, w.columns, b_nnz).empty();
+    out->scratch_bytes = (int64_t)w.L.end;
     return SPD_OK;
 }
 

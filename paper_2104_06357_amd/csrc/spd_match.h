@@ -111,6 +111,9 @@ SPD_HD constexpr bool match_serves(int op) {
            op == OP_MINK || op == OP_MINK_ANY;
 }
 
+// Whether the launches for a call's lists, of which A has m rows, are below 2^32 work-items each (`renumbered`: over A's columns).
+bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renumbered);
+
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
                               int metric, int transform, int norm, float p, double k, double *norms);
 hipError_t launch_match_least(hipStream_t st, int64_t n_rows, const MatchB &b);

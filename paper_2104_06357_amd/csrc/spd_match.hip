@@ -352,6 +352,15 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     }
 }
 
+// (28,301 rows of power-law lengths: the longest, 24,000 entries, takes a wavefront alone 72 us and a workgroup 46;
+// with many rows the workgroups' own cost counts: 300,000 rows of 230 take 354 us that way and 137 us otherwise.
+// What a workgroup to the row helps is one long row, which mean and row count only stand for: 65,536 rows of 1,820
+// take the same either way, and even rows of 230 lose by it, 60,000 of them some 40 us in proportion.  With 16 lanes to
+// the row 10,000 rows of 38 take 17 to 20 us, with 64 11 to 15)
+int match_norm_lanes(int64_t n_rows, int64_t nnz) {
+    const int64_t mean = nnz / n_rows;
+    return mean >= 128 && n_rows <= 65536 ? 256 : (mean >= 16 ? 64 : 4);
+}
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
                               int metric, int transform, int norm, float p, double k, double *norms) {
     if (n_rows <= 0) return hipSuccess;
@@ -361,15 +370,11 @@ hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float
         hipLaunchKernelGGL((spd_match_norms_kernel<G>), dim3((unsigned)((n_rows + per - 1) / per)), dim3(256), 0, st, indptr, values,
                            n_rows, nnz, metric, transform, norm, p, k, norms);
     };
-    const int64_t mean = nnz / n_rows;
-    // (28,301 rows of power-law lengths: the longest, 24,000 entries, takes a wavefront alone 72 us and a workgroup 46;
-    // with many rows the workgroups' own cost counts: 300,000 rows of 230 take 354 us that way and 137 us otherwise.
-    // What a workgroup to the row helps is one long row, which mean and row count only stand for: 65,536 rows of 1,820
-    // take the same either way, and even rows of 230 lose by it, 60,000 of them some 40 us in proportion.  With 16 lanes to
-    // the row 10,000 rows of 38 take 17 to 20 us, with 64 11 to 15)
-    if (mean >= 128 && n_rows <= 65536) go(std::integral_constant<int, 256>{});
-    else if (mean >= 16) go(std::integral_constant<int, 64>{});
-    else go(std::integral_constant<int, 4>{});
+    switch (match_norm_lanes(n_rows, nnz)) {
+    case 256: go(std::integral_constant<int, 256>{}); break;
+    case 64: go(std::integral_constant<int, 64>{}); break;
+    default: go(std::integral_constant<int, 4>{}); break;
+    }
     return hipGetLastError();
 }
 
@@ -456,13 +461,20 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     return s;
 }
 
+// Column blocks to a workgroup: some 2,048 workgroups (a run of blocks looks its rows' first entries up once).
+static uint32_t match_build_blocks(const MatchShape &s) { return std::max(1u, (uint32_t)((uint64_t)s.blocks * (uint64_t)s.n_tiles / 2048u)); }
+bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renumbered) {
+    constexpr int64_t kMost = ((int64_t)1 << 32) - 1024;
+    const int64_t per_wg = match_build_blocks(s);
+    return m * match_norm_lanes(std::max<int64_t>(m, 1), nnz_a) <= kMost && s.n_tiles * ((s.blocks + per_wg - 1) / per_wg) * kBuildThreads <= kMost &&
+           (!renumbered || nnz_a <= kMost);
+}
+
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
                               int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int transform) {
     if (n_rows <= 0) return hipSuccess;
-    // some 2,048 workgroups (a run of blocks looks its rows' first entries up once)
     const MatchShape &s = b.shape;
-    const uint32_t per_wg = std::max(1u, (uint32_t)((uint64_t)s.blocks * (uint64_t)s.n_tiles / 2048u));
-    const uint32_t wgs = ((uint32_t)s.blocks + per_wg - 1u) / per_wg;
+    const uint32_t per_wg = match_build_blocks(s), wgs = ((uint32_t)s.blocks + per_wg - 1u) / per_wg;
     const double per_row = (double)nnz / (double)n_rows / (double)s.blocks;
     auto go = [&](auto g) {
         auto kern = spd_match_build_kernel<decltype(g)::value>;

@@ -278,6 +278,26 @@ def test_column_lists_only_where_a_workgroup_can_number_its_work():
     assert plan(16_000_000)["wanted"] and not plan(200_000_000)["wanted"]
 
 
+def test_column_lists_only_where_their_launches_fit_a_grid():
+    """A launch has fewer than 2^32 work-items: over A's columns one for every stored entry of A, a wavefront for the norm of every
+    row of A, 1,024 threads for a tile."""
+    def way(m, mean_a, n, mean_b, cols, metric, **more):
+        return spd.testing.host_list_plan(m, m * mean_a, n, n * mean_b, cols, metric, **more)["way"]
+
+    assert way(4_096, 160, 500_000, 150, 1 << 20, "jaccard", k_neighbors=32) == 2
+    assert way(1 << 24, 255, 2_000, 40_000, 1 << 20, "jaccard", match_lists=3) == 2
+    assert way(1 << 24, 256, 2_000, 40_000, 1 << 20, "jaccard", match_lists=3) == 0
+    assert way(1 << 24, 256, 2_000, 40_000, 1 << 20, "jaccard", match_lists=2) == 1
+    for m in ((1 << 26) - 1_024, 1 << 26):
+        for lists in (2, 3):
+            assert (way(m, 16, 100, 200, 10_000, "l1", match_lists=lists) > 0) == (m < 1 << 26)
+            assert way(m, 15, 100, 200, 10_000, "l1", match_lists=lists) > 0
+    assert way(1_000, 10, 200_000_000, 1, 50, "l1", match_lists=2, lds_budget=163_840) == 1
+    for n in (268_000_000, 269_000_000):                   # (tiles of 64 rows: 2^22 of them are too many)
+        plan = spd.testing.host_list_plan(1_000, 10_000, n, n, 50, "l1", match_lists=2, lds_budget=16_000)
+        assert plan["consistent"] and (plan["way"] == 1) == (plan["tiles"] < 1 << 22)
+
+
 def test_the_cut_of_the_column_lists_is_consistent():
     """What check_plan verifies, over random sizes, with the lists wanted wherever a product has them."""
     rng = np.random.default_rng(23)
