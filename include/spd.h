@@ -333,7 +333,8 @@ spd_status spd_csr_validate(spd_handle *handle, const spd_csr *M, int require_no
 spd_status spd_set_option(spd_handle *handle, const char *name, int64_t value);
 
 /* Kernel timings of the last spd_pairwise / spd_knn call made with option "profile" = 1.
- * One record per launch, in launch order.  Waits for the call's kernels to finish. */
+ * One record per launch, in launch order ("columns": one for the ten launches of that copy together).  Waits for the call's
+ * kernels to finish. */
 typedef struct {
     char name[24];        /* "pack_b", "scan", "finalize", "knn_merge"; with the column lists "norms_b",
                                 ("columns", over A's columns) "lists_b", "norms_a", "knn_begin", "scan",

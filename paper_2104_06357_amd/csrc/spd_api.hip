@@ -767,15 +767,16 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
 
 
 // The norms of B's rows, and their lists.
-spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int metric, const MetricInfo &mi, const OpParams &q, bool knn) {
+spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int metric, const MetricInfo &mi, const OpParams &q) {
     LaunchTimer norms(h, "norms_b", 0, 0, 0, 0, 0, 0);
     hipError_t e = launch_match_norms(h->stream, B->indptr, B->values, B->n_rows, B->nnz, metric, mi.transform, mi.norm, q.p, q.k, mb.norms);
-    if (e == hipSuccess && knn) e = launch_match_least(h->stream, B->n_rows, mb);
     if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
     norms.done();
     return SPD_OK;
 }
-spd_status stage_lists(spd_handle *h, const spd_csr *B, const MatchB &mb, int op, const MetricInfo &mi) {
+// (`knn`: and each tile's row of the least norm)
+spd_status stage_lists(spd_handle *h, const spd_csr *B, MatchB mb, int op, const MetricInfo &mi, bool knn) {
+    if (!knn) mb.least = nullptr;
     LaunchTimer lists(h, "lists_b", 0, 0, 0, 0, 0, mb.shape.n_tiles);
     hipError_t e = launch_match_build(h->stream, B->indptr, B->indices, B->values, B->n_rows, B->nnz, (uint32_t)B->n_cols, mb,
                            match_cell_bytes(op), mi.transform);
@@ -804,7 +805,7 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     const int32_t *a_indices = A->indices;
     spd_csr listed = *B;
     if (!index_lists) {
-        st = stage_norms(h, B, mb, metric, mi, q, knn_k > 0);
+        st = stage_norms(h, B, mb, metric, mi, q);
         if (st != SPD_OK) return st;
         if (compact) {
             const MatchColumns c{reinterpret_cast<uint2 *>(ws + L.c.words), reinterpret_cast<uint32_t *>(ws + L.c.sums),
@@ -823,7 +824,7 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
             listed.n_cols = way.columns;
             mb.cols = c.totals;
         }
-        st = stage_lists(h, &listed, mb, op, mi);
+        st = stage_lists(h, &listed, mb, op, mi, knn_k > 0);
         if (st != SPD_OK) return st;
     }
     double *norms_a = reinterpret_cast<double *>(ws + L.norms_a);
@@ -1721,8 +1722,8 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         if (hipMalloc(&ix->match_dev, lists.end) == hipSuccess) {
             ix->match = match_b_at(shape, lists, reinterpret_cast<unsigned char *>(ix->match_dev));
             ix->match_op = op;
-            st = stage_norms(h, Index, ix->match, run_as, mi, q, true);
-            if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, mi);
+            st = stage_norms(h, Index, ix->match, run_as, mi, q);
+            if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, mi, true);
             if (st != SPD_OK) return st;
         } else {                         // (no memory left for the lists: the packed copy serves every call)
             ix->match_dev = nullptr;

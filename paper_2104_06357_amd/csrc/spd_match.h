@@ -48,7 +48,7 @@ struct MatchB {
                             // column + its block's number (a block has a word more for its last list's end);
                             // kMatchDense is set where the column is dense
     double *norms;          // n * 2, derived
-    double *least;          // n_tiles * 2: the norms of a tile's row of the least first norm
+    double *least;          // n_tiles * 2: the norms of a tile's row of the least first norm (k-NN)
     MatchShape shape;
     const uint32_t *cols;   // nullptr, or on the device how many columns there are (no more than the shape was made for)
 };
@@ -116,7 +116,7 @@ bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renu
 
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
                               int metric, int transform, int norm, float p, double k, double *norms);
-hipError_t launch_match_least(hipStream_t st, int64_t n_rows, const MatchB &b);
+// (after the norms; `b.least` nullptr: not asked for)
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
                               int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int transform);
 hipError_t launch_match_columns(hipStream_t st, const int32_t *a_indices, int64_t a_nnz, const int64_t *b_indptr, const int32_t *b_indices,

@@ -93,6 +93,31 @@ constexpr int kBuildThreads = 1024;
 // memory for one row while the workgroup waited: 7.6 ms for all lists, and 2.6 with whole wavefronts).
 constexpr int kBuildLong = 64, kBuildPasses = 8;
 
+// (a norm that is not a number is the least: the distances turn a sum that is not a number into 0)
+__device__ __forceinline__ bool less_norm(double a, double than) { return !(a >= than) && than == than; }
+// The norms of a tile's row of the least first norm, by a whole workgroup.
+__device__ __forceinline__ void tile_least(const double *__restrict__ norms, int rows, double *__restrict__ least, double (*s_least)[2]) {
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double d0 = __builtin_huge_val(), d1 = 0.0;
+    for (int r = tid; r < rows; r += kBuildThreads) {
+        const double2 nb = *reinterpret_cast<const double2 *>(norms + (size_t)r * 2);
+        if (less_norm(nb.x, d0)) { d0 = nb.x; d1 = nb.y; }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const double o0 = __shfl_xor(d0, d), o1 = __shfl_xor(d1, d);
+        if (less_norm(o0, d0)) { d0 = o0; d1 = o1; }
+    }
+    if (lane == 0) { s_least[wave][0] = d0; s_least[wave][1] = d1; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < kBuildThreads / kWave; ++w)
+            if (less_norm(s_least[w][0], d0)) { d0 = s_least[w][0]; d1 = s_least[w][1]; }
+        least[0] = d0;
+        least[1] = d1;
+    }
+}
+
 template <int G>
 __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                         const float *__restrict__ values, int64_t n_rows, int64_t nnz,
@@ -101,6 +126,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     extern __shared__ __align__(16) unsigned char s_raw[];
     __shared__ uint32_t s_wave[kBuildThreads / kWave];
     __shared__ uint32_t s_dense[kBuildDense], s_long[kBuildLong], s_longs;
+    __shared__ double s_least[kBuildThreads / kWave][2];
     const MatchShape &shape = b.shape;
     const uint32_t cols = b.cols ? min(*b.cols, most_cols) : most_cols;
     const uint32_t block_cols = 1u << shape.block_shift, blocks = min((uint32_t)shape.blocks, (cols + block_cols - 1u) >> shape.block_shift);
@@ -121,6 +147,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     uint32_t *s_next = s_cur + T;                                                   // ... and the next one
     uint32_t *s_end = s_next + T;
     uint32_t *ptr = b.ptr + (size_t)tile * (size_t)shape.ptr_stride;
+    if (part == 0 && b.least) tile_least(b.norms + (size_t)j0 * 2, rows, b.least + (size_t)tile * 2, s_least);
     const uint32_t block_first = (uint32_t)part * blocks_per_wg;
     const uint32_t block_last = min(block_first + blocks_per_wg, blocks);
     if (block_first >= block_last) return;
@@ -375,36 +402,6 @@ hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float
     case 64: go(std::integral_constant<int, 64>{}); break;
     default: go(std::integral_constant<int, 4>{}); break;
     }
-    return hipGetLastError();
-}
-
-// (a norm that is not a number is the least: the distances turn a sum that is not a number into 0)
-__device__ __forceinline__ bool less_norm(double a, double than) { return !(a >= than) && than == than; }
-__global__ void __launch_bounds__(256) spd_match_least_kernel(const double *__restrict__ norms, int64_t n_rows, int tile_rows,
-                                                              double *__restrict__ least) {
-    __shared__ double s_least[256][2];
-    const int64_t j0 = (int64_t)blockIdx.x * tile_rows;
-    const int rows = (int)min((int64_t)tile_rows, n_rows - j0), tid = (int)threadIdx.x;
-    double d0 = __builtin_huge_val(), d1 = 0.0;
-    for (int r = tid; r < rows; r += 256) {
-        const double2 nb = *reinterpret_cast<const double2 *>(norms + (size_t)(j0 + r) * 2);
-        if (less_norm(nb.x, d0)) { d0 = nb.x; d1 = nb.y; }
-    }
-    s_least[tid][0] = d0;
-    s_least[tid][1] = d1;
-    for (int half = 128; half >= 1; half >>= 1) {
-        __syncthreads();
-        if (tid < half && less_norm(s_least[tid + half][0], s_least[tid][0])) {
-            s_least[tid][0] = s_least[tid + half][0];
-            s_least[tid][1] = s_least[tid + half][1];
-        }
-    }
-    __syncthreads();                                          // (thread 1 stores what thread 0 has just written)
-    if (tid < 2) least[(size_t)blockIdx.x * 2 + tid] = s_least[0][tid];
-}
-hipError_t launch_match_least(hipStream_t st, int64_t n_rows, const MatchB &b) {
-    if (n_rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(spd_match_least_kernel, dim3((unsigned)b.shape.n_tiles), dim3(256), 0, st, b.norms, n_rows, (int)b.shape.tile_rows, b.least);
     return hipGetLastError();
 }
 

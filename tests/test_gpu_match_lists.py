@@ -350,6 +350,18 @@ def test_the_profile_has_a_record_for_every_launch(spd):
     h.close()
 
 
+def test_the_profile_over_the_columns_of_a(spd):
+    A, B = synth.workload(0)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = _lists(spd, match_lists=3, profile=1)
+    build = ["norms_b", "columns", "lists_b", "norms_a"]
+    h.pairwise(dA, dB, "l1")
+    assert [r["name"] for r in h.profile_read()] == build + ["scan"]
+    h.knn(dA, dB, "l1", 5)
+    assert [r["name"] for r in h.profile_read()] == build + ["knn_begin", "scan", "knn_merge"]
+    h.close()
+
+
 @pytest.mark.parametrize("metric", ["inner_product", "cosine", "kl_divergence"])
 def test_a_value_that_is_not_finite_stays_in_its_row(spd, metric):
     """Row 7 of A, shared by a workgroup's wavefronts, meets a dense column of B with an infinity: what it leaves behind the
