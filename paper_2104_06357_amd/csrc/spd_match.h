@@ -103,8 +103,8 @@ SPD_HD constexpr uint32_t match_strip_bytes(int cell_bytes, int tile_rows) { ret
 // Wavefronts of a workgroup, of which a compute unit holds one: the strips share its LDS, and where a pair's
 // sums take 16 bytes or more, there are fewer and longer strips.
 SPD_HD constexpr int match_waves(int cell_bytes) { return cell_bytes >= 16 ? 12 : 16; }
-// Upper bound of the kernel's static __shared__ use (64 words to a wavefront, the locks).
-SPD_HD constexpr int64_t match_static_lds(int cell_bytes) { return 256 + match_waves(cell_bytes) * 256; }
+// Upper bound of the kernel's static __shared__ use (64 half words to a wavefront, the locks).
+SPD_HD constexpr int64_t match_static_lds(int cell_bytes) { return 256 + match_waves(cell_bytes) * 128; }
 // The products the column lists serve.
 SPD_HD constexpr bool match_serves(int op) {
     return op == OP_DOT || op == OP_L1 || op == OP_CANB || op == OP_HAMM || op == OP_KL || op == OP_JS || op == OP_CNT ||

@@ -439,15 +439,26 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     while ((4 << (shift + 1)) <= usable / 8 && (1 << shift) < n_cols) ++shift;
     // (sparse blocks, many of them: what a block costs besides its entries.  500,000 sets over 242,000 columns, 2,432 rows to
     // the tile: 2.6 ms with 4,096 columns to the block, 2.0 with 8,192)
+    const int narrow = shift;
     if ((n_cols >> shift) >= 16 && (4 << (shift + 1)) <= usable / 4) ++shift;
     while (shift > 2 && per_col * (double)(1 << shift) * 1.25 > (double)stage_of(shift)) --shift;
-    // a workgroup for every compute unit, where there are columns enough
+    // Dense columns to a block: what its share of the entries fills, once at least (of the halves of a wide block, so that its width
+    // does not cost memory: an index may keep lists that grow to its limit and no further).
+    auto dense_of = [&](int at) {
+        const int of = std::min(at, narrow);
+        return (int32_t)std::min<double>(kBuildDense, std::max(1.0, std::floor(per_cell * (double)(1 << of))) * (double)(1 << (at - of)));
+    };
+    // a workgroup for every compute unit, where there are columns enough, and blocks so that their dense columns take no more
+    // than the entries do, and 512 KiB (12,970 rows of 6 over 10,261 columns, with an index: 41 blocks took the lists over its limit,
+    // and its calls 600 us by the scan instead of 240)
     const int64_t tiles_now = (n + s.tile_rows - 1) / s.tile_rows;
-    while (shift > 8 && tiles_now * ((n_cols + (1 << shift) - 1) >> shift) < 256) --shift;
+    auto blocks_of = [&](int at) { return (n_cols + (1 << at) - 1) >> at; };
+    while (shift > 8 && tiles_now * blocks_of(shift) < 256 &&
+           tiles_now * blocks_of(shift - 1) * dense_of(shift - 1) * (s.tile_rows / 2) * 8 <= 8 * nnz + (512 << 10)) --shift;
     s.block_shift = shift;
     s.stage = (uint32_t)stage_of(shift);
-    s.blocks = (int32_t)((n_cols + (1 << shift) - 1) >> shift);
-    s.dense_per_block = (int32_t)std::min<double>(kBuildDense, std::max(1.0, per_cell * (double)(1 << shift)));
+    s.blocks = (int32_t)blocks_of(shift);
+    s.dense_per_block = dense_of(shift);
     // a step of 64 rows of a dense column costs this share of a list's step
     const double cost = op == OP_DOT ? 0.3 : (op == OP_L1 || op == OP_CNT || op == OP_HAMM || op == OP_CANB ? 0.4 : 0.5);
     s.dense_from = std::max(1, (int32_t)(cost * s.tile_rows));

@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     extern __shared__ __align__(16) unsigned char dyn[];
     __shared__ int s_next;
     __shared__ int s_lock[KNN ? kMatchLocks : 1];
-    __shared__ int s_owner[nw][kWave];
+    __shared__ uint16_t s_owner[nw][kWave];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
     const int T = args.b.shape.tile_rows;
     const uint32_t strip_bytes = match_strip_bytes(match_cell_bytes(OP), T), plane = (uint32_t)(T + 1) * 8u;
@@ -315,14 +315,15 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         const int turned = ((lane & 15) << 2) | (lane >> 4);
         const uint32_t lane8 = (uint32_t)(lane & 15) * 8u;
         struct Chunk { uint32_t at, left; float a; };                            // left: bytes of its list from `at` on
-        int *owner = s_owner[wave];
+        // (16 bits: 64 lists of a tile are 64 * 156 chunks at most, the last group's tag is below 2^14)
+        uint16_t *owner = s_owner[wave];
         owner[lane] = 0;
         int tag = 64, carry = 0;
         // Which list a chunk belongs to: every list marks its first chunk with its lane, and a running maximum carries the
         // marks on (a mark of an earlier group is below the tag).
         auto describe = [&](int q0) {
             const uint32_t start = (uint32_t)(excl - q0);
-            if (chunks > 0 && start < 64u) owner[start] = tag + lane;
+            if (chunks > 0 && start < 64u) owner[start] = (uint16_t)(tag + lane);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             int e = owner[lane];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

@@ -329,6 +329,11 @@ def test_an_index_keeps_lists_that_calls_may_want_within_the_stated_memory():
     assert kept(20_000, 50, 20_000, "jaccard") == 0
     assert kept(20_000, 50, 20_000, "l1") > 0 and kept(20_000, 50, 20_000, "l1", force_kind=3) == 0
     assert kept(20_000, 50, 20_000, "l1", match_lists=0) == 0 and kept(8_000, 2.2, 858_000, "cosine", match_lists=2) > 0
+    # near the limit: wide column blocks, many blocks of few entries, tiles of products of 12 bytes a pair.  Calls by the scan / by lists in
+    # us: 4,897 / 800, 596 / 238, 2,961 / 268
+    for n, nnz, cols, metric in ((56_257, 5_172_942, 236_097, "hellinger"), (12_970, 77_804, 10_261, "jensen_shannon"),
+                                 (10_772, 4_546_630, 728_767, "kl_divergence")):
+        assert kept(n, nnz / n, cols, metric) > 0, (n, cols, metric)
     # the working range
     for n, mean, cols in ((300, 37, 20_000), (12_000, 37, 20_000), (5_000, 228, 102_660), (300_000, 228, 102_660), (500, 1_820, 26_000),
                           (60_000, 1_820, 26_000), (2_000, 160, 194_000), (200_000, 160, 194_000)):
