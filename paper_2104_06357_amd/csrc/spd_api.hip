@@ -672,49 +672,56 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
     return match_suits(h, B, op, s) && (int64_t)L.end <= 20 * B->nnz + 16 * B->n_rows + (1 << 20);
 }
 // What a call costs by lists and by the staged scan, in picoseconds of the whole chip.  A wavefront pays for every entry of
-// its row of A in every tile (its list's bounds; a step, where the list is not empty; what a long list takes beyond one
-// step), with k-NN for the selection in every (tile, row) too, and the last round of (tile, row)s leaves wavefronts idle.
-// The staged scan pays for every visit (a staged row, a streamed entry).  Both pay for what they make of B, for the pairs
-// they finish, and for their launches.  The constants are fitted to both ways' times of 3,000 pairs of operands (100 to
-// 12,000 rows against 600 to 300,000, rows of 1.5 to 4,000 entries, A's 1/30 to 60 times as long as B's, uniform and Zipf
-// columns, 2,000 to 2^20 of them, every product, k-NN with k = 10 to 64 and pairwise); they are within a factor of 1.5 of
-// the times of most, because row pointers do not show how A's columns meet B's.
-double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, const MatchShape &s, bool knn, bool copied) {
-    const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz;
-    const bool wide = match_doubles(op) + match_counts(op) > 1, dear = op == OP_JS;
-    const double list = nnz_b / n / (double)columns * (double)s.tile_rows;             // entries, on the mean
-    const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn);
-    const double items = std::ceil((double)match_items(s, g, A->n_rows) / s.waves);     // of a wavefront
-    const double idle = items * s.waves * (double)h->opt.n_cus / (m * s.n_tiles);
-    // (over A's columns alone the lists that A walks are longer than the mean)
-    const double entry = copied ? (wide ? 45.0 + 75.0 * std::min(1.0, list) + 160.0 * list / 64.0
-                                   : dear ? 35.0 + 45.0 * std::min(1.0, list) + 120.0 * list / 64.0 : 25.0 + 27.0 * std::min(1.0, list) + 80.0 * list / 64.0)
-                                : (wide ? 45.0 + 65.0 * std::min(1.0, list) + 95.0 * list / 64.0
-                                   : dear ? 30.0 + 30.0 * std::min(1.0, list) + 75.0 * list / 64.0 : 22.0 + 13.0 * std::min(1.0, list) + 42.0 * list / 64.0);
-    const double row = knn ? (wide ? 1600.0 : 2300.0) : 300.0;
-    // (the lists' bounds, a word per tile and column: 89 x 8,333 rows of 2.2 over 858,000 columns, k-NN, L1, staged / lists 99 / 137
-    // us, 1,514 x 20,515 of them, cosine, 200 / 235; without this term both went to the lists)
-    const double bounds = copied ? 0.0 : 11.0 * (double)s.n_tiles * (double)s.ptr_stride;
-    return (copied ? 105e6 : 65e6) + bounds + 28.0 * nnz_b + idle * s.n_tiles * (entry * nnz_a + row * m) + 0.9 * m * n;
-}
-double staged_cost(const spd_csr *A, const spd_csr *B, int op, bool swapped, bool knn) {
-    const double m = (double)A->n_rows, n = (double)B->n_rows;
-    double visit = 0.6;
+// its row of A in every tile (its list's bounds; a step, where the list is not empty), for every entry of a list it walks and for
+// every (tile, row); the last round of (tile, row)s leaves wavefronts idle, unless rows are so long that a workgroup's wavefronts share
+// them.  The staged scan pays for every visit (a staged row, a streamed entry; more where longer staged rows leave fewer of them
+// a place in LDS, and where the columns are too many for the quick maps).  Both pay for what they make of B, where no index
+// has it, for the pairs they finish, and for their launches.  The constants are fitted to both ways' times of 14,000 pairs of operands
+// (30 to 12,000 rows against 300 to 300,000, of equal, log-normal and power-law lengths of 1.5 to 3,000 entries, A's as long as
+// B's and not, uniform and Zipf columns, 2,000 to 2^20 of them, every product, k-NN with k = 1 to 64 and pairwise, with an index
+// and without); nine of ten estimates are within 0.4 to 1.35 of the times, because row pointers do not show how A's columns
+// meet B's.
+struct OpCost { double entry, step, match, row, knn_row, visit, longer, wide, pair; };
+constexpr OpCost op_cost(int op) {
     switch (op) {
-    case OP_DOT: case OP_L1: visit = 0.115; break;
-    case OP_HAMM: visit = 0.155; break;
-    case OP_CANB: visit = 0.285; break;
-    case OP_KL: visit = 0.32; break;
-    case OP_JS: visit = 0.74; break;
-    case OP_CNT: visit = 0.04; break;
-    default: break;
+    case OP_DOT: return {11.8, 12.8, 0.59, 0, 300, 0.095, 4.7e-5, 0.040, 1.6};
+    case OP_L1: return {10.9, 11.4, 0.60, 0, 330, 0.114, 3.5e-5, 0.054, 1.35};
+    case OP_HAMM: return {19.0, 12.2, 0.50, 0, 340, 0.141, 4.0e-5, 0.055, 1.7};
+    case OP_CNT: return {17.2, 15.2, 0.52, 670, 0, 0.043, 2.6e-5, 0.019, 1.8};
+    case OP_CANB: return {13.1, 3.6, 0.75, 0, 180, 0.282, 3.6e-5, 0.063, 1.5};
+    case OP_KL: return {9.6, 7.9, 0.73, 0, 250, 0.324, 6.0e-5, 0.051, 1.2};
+    case OP_JS: return {12.6, 15.4, 0.72, 0, 640, 0.703, 5.5e-5, 0.069, 2.3};
+    default: return {10.9, 13.1, 1.28, 140, 630, 0.45, 1.5e-4, 0.241, 3.5};
     }
-    // (longer staged rows leave fewer of them a place in LDS; a set metric's take a byte)
-    if (op != OP_CNT) visit += 4e-5 * (swapped ? (double)B->nnz / n : (double)A->nnz / m);
-    return 100e6 + 20.0 * (double)B->nnz + visit * (swapped ? n * (double)A->nnz : m * (double)B->nnz) + (knn ? 4.4 : 2.4) * m * n;
+}
+// What the estimates are asked to differ by: the set metrics' visits are the cheapest, the dear products' the surest.
+constexpr double lists_line(int op) { return op == OP_CNT ? 0.55 : (op == OP_DOT || op == OP_L1 || op == OP_HAMM ? 0.7 : 0.75); }
+// (`columns`: that the lists are laid out for; `made`: an index brings the lists)
+double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, const MatchShape &s, bool knn, bool made) {
+    const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz, tiles = (double)s.n_tiles;
+    const OpCost c = op_cost(op);
+    const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn);
+    const double rows = std::ceil(m / g.slices), runs = std::ceil(tiles / g.groups);          // of a workgroup
+    double idle = rows * runs * (double)h->opt.n_cus / (m * tiles);
+    if (nnz_a <= (double)g.shared_len * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
+    const double list = nnz_b / n / (double)columns * (double)s.tile_rows;                     // entries, on the mean
+    const double make = made ? 0.0 : 22.5e6 + 29.0 * nnz_b + 6.3 * tiles * (double)s.ptr_stride + 150.0 * n;
+    return (knn ? 53e6 : 27e6) + make + 2400.0 * m + 1.3 * m * n +
+           idle * (nnz_a * tiles * (c.entry + c.step * std::min(1.0, list)) + c.match * nnz_a * nnz_b / (double)columns +
+                   (c.row + (knn ? c.knn_row : 0.0)) * m * tiles);
+}
+double staged_cost(const spd_csr *A, const spd_csr *B, int op, bool swapped, bool knn, bool made) {
+    const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz;
+    const OpCost c = op_cost(op);
+    const double mean = swapped ? nnz_b / n : nnz_a / m;                                       // of the staged rows
+    const double visit = c.visit + c.longer * std::min(mean, 2000.0) + (A->n_cols > 40000 ? c.wide : 0.0);
+    const double make = made ? 0.0 : 22e6 + 13.0 * nnz_b + 1900.0 * n;
+    return (knn ? 58e6 : 31e6) + make + 5000.0 * m + 22.0 * nnz_a + 35000.0 * mean + visit * (swapped ? n * nnz_a : m * nnz_b) +
+           (c.pair + (knn ? 0.5 : 0.0)) * m * n;
 }
 // `swapped`: the staged scan would exchange the operands' roles.
-bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn) {
+bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn,
+                  bool with_index) {
     MatchShape s;
     if (semiring || A->n_rows <= 0 || !match_possible(h, B, op, s)) return false;
     if (match_items(s, match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
@@ -722,17 +729,16 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     if (h->match_lists == 2) return true;
     if (!match_suits(h, B, op, s)) return false;
     // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.34; 1,024 x 300,000 of 230, cosine
-    // 11.4 / 5.6; 4,096 x 65,536 of 1,820, L1 87 / 29, Jensen-Shannon 349 / 51; 1,000 x 10,000 of 1,360 and 20, L1 0.14 /
-    // 0.70; set metrics: 2,435 x 6,447 ratings, Dice 0.62 / 0.28, 1,187 x 6,303 rows of 214, Russell-Rao 0.34 / 0.39, 680 x
-    // 20,302 of them 0.55 / 0.60.  Of 1,264 pairs of operands with one of the other products, the line between them lets 9 of
-    // ten of those through that gain a tenth or more, and 2 in a hundred that lose as much, up to a third; the set metrics'
-    // estimate is the coarser, and their line the stricter for it (7 of 178, up to a quarter).
-    return lists_cost(h, A, B, A->n_cols, op, s, knn, false) <= (op == OP_CNT ? 0.7 : 0.85) * staged_cost(A, B, op, swapped, knn);
+    // 11.4 / 5.6; 4,096 x 65,536 of 1,820, L1 87 / 30, Jensen-Shannon 349 / 37; 593 x 12,826 of 1,850, KL, k-NN, 5.5 / 1.7; 1,000 x
+    // 10,000 of 1,360 and 20, L1 0.14 / 0.70; set metrics: 2,435 x 6,447 ratings, Dice 0.62 / 0.28, 1,187 x 6,303 rows of 214,
+    // Russell-Rao 0.34 / 0.39, 3,081 x 30,310 of 400 in Zipf columns, Jaccard 2.5 / 7.0 (which row pointers do not tell).
+    return lists_cost(h, A, B, A->n_cols, op, s, knn, with_index) <= lists_line(op) * staged_cost(A, B, op, swapped, knn, with_index);
 }
 // The columns that lists over A's columns alone are laid out for (how many A stores, the host does not know).
 int64_t columns_of(const spd_csr *A) { return std::min(A->n_cols, std::max<int64_t>(A->nnz, 1)); }
 // Whether a call is computed by lists over the columns that A stores, after a copy of both operands over these.
-bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn) {
+bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn,
+                    bool with_index) {
     if (semiring || h->match_lists == 0 || !match_serves(op) || A->n_rows <= 0 || A->nnz <= 0 || B->n_rows <= 0 || B->nnz <= 0) return false;
     if (A->n_cols > kMatchMostColumns) return false;
     const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
@@ -745,9 +751,10 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     MatchShape all;
     if (match_possible(h, B, op, all) && match_bounds_fit(all, B->nnz)) return false;
     // Both sides measured, staged / lists over A's columns in ms, k-NN: 4,096 x 500,000 sets over 2^20 columns, Jaccard 30.6 /
-    // 11.6, 3,331 x 9,539 of them 0.93 / 0.67, 87 x 21,712 0.79 / 0.45; 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.7 /
-    // 2.0, 335 x 16,402 of them, L1 0.10 / 0.12.  Of 381 pairs of operands 9 lose a tenth or more behind this line, up to a half.
-    return lists_cost(h, A, B, columns_of(A), op, s, knn, true) <= 0.95 * staged_cost(A, B, op, swapped, knn);
+    // 11.1, 3,331 x 9,539 of them 0.93 / 0.67, 87 x 21,712 0.79 / 0.45; 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.3 /
+    // 2.0, 335 x 16,402 of them, L1 0.10 / 0.12; 99 x 386,927 of them with an index, which holds nothing of these lists, cosine 0.19 /
+    // 0.26.  Of 457 pairs of operands one loses more than a tenth behind this line.
+    return lists_cost(h, A, B, columns_of(A), op, s, knn, false) <= lists_line(op) * staged_cost(A, B, op, swapped, knn, with_index);
 }
 // The way a call is computed: 0 the staged scan, 1 lists over all columns, 2 lists over the columns that A stores; and how.
 struct MatchWay { int way = 0; int64_t columns = 0; MatchShape s{}; MatchGrid g; MatchScratch L{}; };
@@ -755,8 +762,8 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
                    bool with_index, bool index_has_lists) {
     MatchWay w;
     const bool knn = knn_k > 0;
-    if (h->match_lists != 3 && match_wanted(h, A, B, op, semiring, swapped, knn) && (!with_index || index_has_lists)) w.way = 1;
-    else if (columns_wanted(h, A, B, op, semiring, swapped, knn)) w.way = 2;
+    if (h->match_lists != 3 && match_wanted(h, A, B, op, semiring, swapped, knn, with_index) && (!with_index || index_has_lists)) w.way = 1;
+    else if (columns_wanted(h, A, B, op, semiring, swapped, knn, with_index)) w.way = 2;
     if (w.way == 0) return w;
     w.columns = w.way == 2 ? columns_of(A) : A->n_cols;
     w.s = match_shape(h->opt.lds_budget, op, B->n_rows, w.columns, B->nnz);
@@ -1522,9 +1529,9 @@ spd_status spd_workspace_bytes(const spd_handle *h, const spd_csr *A, const spd_
     for (const int as_metric : {(int)metric, metric == SPD_MINKOWSKI ? (int)SPD_L1 : (int)metric}) {
         const int op = product_of(h, as_metric, 2.0f);
         const bool swap = k_neighbors == 0 && swap_wanted(h, A, B, as_metric, nullptr);
-        // (an index without lists leaves a call to the way behind them)
-        for (const bool index : {false, true}) {
-            const MatchWay w = match_way(h, A, B, op, nullptr, swap, k_neighbors, index, false);
+        // (without an index, with one that keeps no lists and with one that does)
+        for (const int index : {0, 1, 2}) {
+            const MatchWay w = match_way(h, A, B, op, nullptr, swap && index == 0, k_neighbors, index > 0, index == 2);
             if (w.way != 0) *bytes = std::max(*bytes, w.L.end);
         }
     }
@@ -1905,7 +1912,7 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     const int run_as = effective_metric((int)metric, p), op = product_of(&h, run_as, p);
     const bool knn = k_neighbors > 0, swap = !knn && !with_index && swap_wanted(&h, &A, &B, run_as, nullptr);
     std::memset(out, 0, sizeof *out);
-    out->wanted = match_wanted(&h, &A, &B, op, nullptr, swap, knn);
+    out->wanted = match_wanted(&h, &A, &B, op, nullptr, swap, knn, with_index != 0);
     MatchShape kept;
     MatchLayout L;
     const bool keeps = index_keeps_lists(&h, &B, op, kept, L);

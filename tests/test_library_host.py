@@ -259,6 +259,27 @@ def test_column_lists_against_the_scan_that_would_run():
     assert _wanted(766, 1_468, 3_599, 35, 20_000, "minkowski", match_lists=2)
 
 
+def test_column_lists_where_either_way_was_measured_the_faster():
+    def way(m, nnz_a, n, nnz_b, cols, metric, k=0, with_index=False):
+        return spd.testing.host_list_plan(m, nnz_a, n, nnz_b, cols, metric, p=3.0, k_neighbors=k, with_index=with_index)["way"]
+
+    # staged / lists in us
+    for call in ((593, 1_098_834, 12_826, 23_146_901, 25_801, "kl_divergence", 10, True),                # 5,537 / 1,725
+                 (284, 508_523, 32_451, 58_624_655, 25_871, "kl_divergence", 1),                         # 7,534 / 3,568
+                 (3_523, 6_436_960, 939, 1_723_471, 25_977, "kl_divergence", 5),                         # 2,846 / 844
+                 (3_365, 6_104_649, 606, 1_122_609, 25_803, "hamming"),                                  # 1,143 / 464
+                 (166, 80_710, 63_912, 30_733_557, 9_590, "kl_divergence", 0, True),                     # 1,582 / 479
+                 (303, 18_008, 15_994, 700_407, 26_578, "kl_divergence"),                                # 420 / 110
+                 (4_192, 9_815, 15_752, 36_404, 5_716, "minkowski"),                                     # 578 / 217
+                 (2_628, 1_644_603, 38_556, 18_370_748, 2_656, "canberra")):                             # 14,985 / 8,086
+        assert way(*call) == 1, call
+    for call in ((99, 200, 386_927, 860_302, 858_000, "cosine", 10, True),                               # 192 / 259 over A's columns
+                 (225, 16_379, 3_387, 257_241, 4_996, "l1", 64, True),                                   # 56 / 100
+                 (285, 16_409, 2_183, 121_792, 5_120, "hamming", 1, True),                               # 61 / 107
+                 (573, 182_658, 3_605, 1_203_924, 25_248, "correlation")):                               # 179 / 297
+        assert way(*call) == 0, call
+
+
 @pytest.mark.parametrize("m,n,metric,k", [(89, 8_333, "l1", 64), (1_514, 20_515, "cosine", 10), (1_783, 12_134, "cosine", 10)])
 def test_column_lists_count_their_bounds(m, n, metric, k):
     """A word per tile and column: few rows of two entries over very many columns, staged / lists in us 99 / 137, 200 / 235,
