@@ -379,14 +379,13 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     }
 }
 
-// (28,301 rows of power-law lengths: the longest, 24,000 entries, takes a wavefront alone 72 us and a workgroup 46;
-// with many rows the workgroups' own cost counts: 300,000 rows of 230 take 354 us that way and 137 us otherwise.
-// What a workgroup to the row helps is one long row, which mean and row count only stand for: 65,536 rows of 1,820
-// take the same either way, and even rows of 230 lose by it, 60,000 of them some 40 us in proportion.  With 16 lanes to
-// the row 10,000 rows of 38 take 17 to 20 us, with 64 11 to 15)
+// Lanes to a row.  A workgroup to the row where its own cost, one launch of many, counts less than the loads that it has in flight:
+// with 256 / 64 lanes in us, L1: 300 rows of 3,700 8 / 18, 939 of 1,940 13 / 24, 4,096 of 1,870 18 / 26, 5,000 of 275 11 / 12, 20,000 of
+// 280 35 / 30, 28,301 of 166 (power law, the longest 24,000) 50 / 35, 60,000 of 230 72 / 27, 65,536 of 1,760 128 / 109.  (With 16
+// lanes to the row 10,000 rows of 38 take 17 to 20 us, with 64 11 to 15.)
 int match_norm_lanes(int64_t n_rows, int64_t nnz) {
     const int64_t mean = nnz / n_rows;
-    return mean >= 128 && n_rows <= 65536 ? 256 : (mean >= 16 ? 64 : 4);
+    return mean >= 128 && n_rows <= 8192 ? 256 : (mean >= 16 ? 64 : 4);
 }
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
                               int metric, int transform, int norm, float p, double k, double *norms) {
