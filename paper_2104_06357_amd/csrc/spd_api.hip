@@ -680,7 +680,10 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
 // (30 to 12,000 rows against 300 to 300,000, of equal, log-normal and power-law lengths of 1.5 to 3,000 entries, A's as long as
 // B's and not, uniform and Zipf columns, 2,000 to 2^20 of them, every product, k-NN with k = 1 to 64 and pairwise, with an index
 // and without); nine of ten estimates are within 0.4 to 1.35 of the times, because row pointers do not show how A's columns
-// meet B's.
+// meet B's.  Columns are seldom uniform where they are many: over all columns the lists are taken to be met up to 40 times as
+// often as if they were, as far as the density leaves room for that (words, Zipf columns, rows of 230 over 102,660: some 40 times).
+// Of 1,993 random calls of the working range (words, counts, ratings, sets, n-grams, skewed lengths) one in a hundred loses a tenth or more
+// against the better of the rules before this one.
 struct OpCost { double entry, step, match, row, knn_row, visit, longer, wide, pair; };
 constexpr OpCost op_cost(int op) {
     switch (op) {
@@ -694,20 +697,20 @@ constexpr OpCost op_cost(int op) {
     default: return {10.9, 13.1, 1.28, 140, 630, 0.45, 1.5e-4, 0.241, 3.5};
     }
 }
-// What the estimates are asked to differ by: the set metrics' visits are the cheapest, the dear products' the surest.
-constexpr double lists_line(int op) { return op == OP_CNT ? 0.55 : (op == OP_DOT || op == OP_L1 || op == OP_HAMM ? 0.7 : 0.75); }
 // (`columns`: that the lists are laid out for; `made`: an index brings the lists)
-double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, const MatchShape &s, bool knn, bool made) {
+double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, const MatchShape &s, bool knn, bool made,
+                  bool skewed) {
     const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz, tiles = (double)s.n_tiles;
     const OpCost c = op_cost(op);
     const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn);
     const double rows = std::ceil(m / g.slices), runs = std::ceil(tiles / g.groups);          // of a workgroup
     double idle = rows * runs * (double)h->opt.n_cus / (m * tiles);
     if (nnz_a <= (double)g.shared_len * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
-    const double list = nnz_b / n / (double)columns * (double)s.tile_rows;                     // entries, on the mean
+    const double density = nnz_b / n / (double)columns, list = density * (double)s.tile_rows;  // entries, on the mean
+    const double met = skewed ? std::max(1.0, std::min(40.0, 0.07 / density)) : 1.0;
     const double make = made ? 0.0 : 22.5e6 + 29.0 * nnz_b + 6.3 * tiles * (double)s.ptr_stride + 150.0 * n;
     return (knn ? 53e6 : 27e6) + make + 2400.0 * m + 1.3 * m * n +
-           idle * (nnz_a * tiles * (c.entry + c.step * std::min(1.0, list)) + c.match * nnz_a * nnz_b / (double)columns +
+           idle * (nnz_a * tiles * (c.entry + c.step * std::min(1.0, list)) + c.match * met * nnz_a * density * n +
                    (c.row + (knn ? c.knn_row : 0.0)) * m * tiles);
 }
 double staged_cost(const spd_csr *A, const spd_csr *B, int op, bool swapped, bool knn, bool made) {
@@ -731,8 +734,8 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.34; 1,024 x 300,000 of 230, cosine
     // 11.4 / 5.6; 4,096 x 65,536 of 1,820, L1 87 / 30, Jensen-Shannon 349 / 37; 593 x 12,826 of 1,850, KL, k-NN, 5.5 / 1.7; 1,000 x
     // 10,000 of 1,360 and 20, L1 0.14 / 0.70; set metrics: 2,435 x 6,447 ratings, Dice 0.62 / 0.28, 1,187 x 6,303 rows of 214,
-    // Russell-Rao 0.34 / 0.39, 3,081 x 30,310 of 400 in Zipf columns, Jaccard 2.5 / 7.0 (which row pointers do not tell).
-    return lists_cost(h, A, B, A->n_cols, op, s, knn, with_index) <= lists_line(op) * staged_cost(A, B, op, swapped, knn, with_index);
+    // Russell-Rao 0.34 / 0.39, 3,081 x 30,310 of 400 in Zipf columns, Jaccard 2.5 / 7.0.
+    return lists_cost(h, A, B, A->n_cols, op, s, knn, with_index, true) <= staged_cost(A, B, op, swapped, knn, with_index);
 }
 // The columns that lists over A's columns alone are laid out for (how many A stores, the host does not know).
 int64_t columns_of(const spd_csr *A) { return std::min(A->n_cols, std::max<int64_t>(A->nnz, 1)); }
@@ -751,10 +754,11 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     MatchShape all;
     if (match_possible(h, B, op, all) && match_bounds_fit(all, B->nnz)) return false;
     // Both sides measured, staged / lists over A's columns in ms, k-NN: 4,096 x 500,000 sets over 2^20 columns, Jaccard 30.6 /
-    // 11.1, 3,331 x 9,539 of them 0.93 / 0.67, 87 x 21,712 0.79 / 0.45; 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.3 /
+    // 11.1, 3,331 x 9,539 of them 0.93 / 0.67, 46 x 56,760, Russell-Rao 0.73 / 0.30; 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.3 /
     // 2.0, 335 x 16,402 of them, L1 0.10 / 0.12; 99 x 386,927 of them with an index, which holds nothing of these lists, cosine 0.19 /
-    // 0.26.  Of 457 pairs of operands one loses more than a tenth behind this line.
-    return lists_cost(h, A, B, columns_of(A), op, s, knn, false) <= lists_line(op) * staged_cost(A, B, op, swapped, knn, with_index);
+    // 0.26, 516 x 285,865 sets with one, Dice 4.3 / 2.3.  (The estimate of these lists is the higher, as columns that A does not
+    // store cost them nothing.)
+    return lists_cost(h, A, B, columns_of(A), op, s, knn, false, false) <= 1.1 * staged_cost(A, B, op, swapped, knn, with_index);
 }
 // The way a call is computed: 0 the staged scan, 1 lists over all columns, 2 lists over the columns that A stores; and how.
 struct MatchWay { int way = 0; int64_t columns = 0; MatchShape s{}; MatchGrid g; MatchScratch L{}; };

@@ -334,6 +334,47 @@ def test_the_cut_of_the_column_lists_is_consistent():
     assert wanted > 1_000
 
 
+def test_the_cut_over_the_columns_of_a_is_consistent():
+    """The same of the lists over the columns that A stores, which may be fewer than B's rows are long, and of the default choice."""
+    rng = np.random.default_rng(29)
+    ways = [0, 0, 0]
+    for i in range(6_000):
+        m, n, cols = (int(2 ** rng.uniform(0, e)) for e in (20, 22, 30))
+        mean_a, mean_b = (min(2 ** rng.uniform(-2, 12), cols) for _ in range(2))
+        metric = ALL_METRICS[rng.integers(len(ALL_METRICS))]
+        k, with_index = int(rng.integers(0, 2)) * min(n, 64), bool(rng.integers(0, 2))
+        plan = spd.testing.host_list_plan(m, int(m * mean_a), n, int(n * mean_b), cols, metric, k_neighbors=k, with_index=with_index,
+                                          match_lists=3 if i % 2 else 1)
+        assert plan["consistent"] or not plan["way"], (m, n, cols, metric, plan)
+        if i % 2:
+            assert plan["way"] in (0, 2)
+        if plan["way"] == 2:
+            assert 1 <= plan["columns"] <= min(cols, int(m * mean_a))
+            # both operands' copies, the bits of the columns, the lists and their bounds
+            assert plan["scratch_bytes"] >= 4 * int(m * mean_a) + 16 * int(n * mean_b) + 4 * plan["tiles"] * plan["columns"] + cols // 4
+        ways[plan["way"]] += 1 if i % 2 == 0 or plan["way"] == 2 else 0
+    assert min(ways) > 100, ways
+
+
+def test_lists_over_the_columns_of_a_where_they_were_measured_the_faster():
+    def way(m, nnz_a, n, nnz_b, cols, metric, k, with_index=False):
+        return spd.testing.host_list_plan(m, nnz_a, n, nnz_b, cols, metric, k_neighbors=k, with_index=with_index)["way"]
+
+    # staged / lists over A's columns in us
+    for call in ((46, 1_181, 56_760, 7_850_605, 1 << 20, "russell_rao", 10),                             # 729 / 296
+                 (304, 18_179, 47_031, 6_320_193, 1_048_489, "jaccard", 1),                              # 928 / 415
+                 (322, 43_735, 235_775, 32_212_992, 1 << 20, "hamming", 5, True),                        # 3,254 / 2,043
+                 (2_852, 331_584, 45_723, 5_793_187, 1_048_432, "dice", 32),                             # 2,636 / 1,194
+                 (55, 105, 31_228, 69_773, 858_000, "l1", 32),                                           # 165 / 115
+                 (73, 175, 392_314, 873_637, 857_938, "l1", 32),                                         # 2,131 / 622
+                 (2_580, 5_713, 589_528, 1_311_120, 858_000, "l1", 1, True)):                            # 2,747 / 1,043
+        assert way(*call) == 2, call
+    for call in ((45, 6_537, 132_700, 18_125_390, 1 << 20, "hamming", 64, True),                         # 653 / 733
+                 (53, 107, 139_569, 309_837, 857_836, "jaccard", 1, True),                               # 74 / 126
+                 (161, 349, 106_492, 236_060, 857_888, "cosine", 32, True)):                             # 110 / 176
+        assert way(*call) == 0, call
+
+
 def test_an_index_keeps_lists_that_calls_may_want_within_the_stated_memory():
     def kept(n, mean, cols, metric, **more):
         plan = spd.testing.host_list_plan(1_000, 30_000, n, int(n * mean), cols, metric, with_index=True, **more)
