@@ -113,6 +113,66 @@ def test_chunks_of_a_batch(spd, metric):
     h.close()
 
 
+def test_a_sum_is_formed_in_the_order_of_the_columns(spd):
+    """Products of 2^55 and 1 of either sign: a sum in 64 bits depends on the order of its terms, and is the one of ascending
+    columns also where the chunks of a step hold entries of one row (lists of 1 to 16 entries, four of them to a step,
+    most with the same rows), across steps and across batches of 64 entries."""
+    rng = np.random.default_rng(60)
+    m, n, cols = 40, 640, 400
+    B = np.zeros((n, cols))
+    for c in range(cols):
+        rows = rng.choice(24, size=rng.integers(1, 17), replace=False)
+        B[rows, c] = rng.choice([-1.0, 1.0], size=len(rows))
+    B[np.arange(24, n), rng.integers(0, cols, size=n - 24)] = 1.0
+    A = np.zeros((m, cols))
+    for r in range(m):
+        chosen = rng.choice(cols, size=(4, 16, 64, 65, 200)[r % 5], replace=False)
+        A[r, chosen] = np.where(rng.random(len(chosen)) < 0.4, 2.0 ** 55, 1.0)
+    want = np.zeros((m, n))
+    for c in range(cols):
+        want += np.outer(A[:, c], B[:, c])                 # (one column after the other)
+    other = np.zeros((m, n))
+    for c in reversed(range(cols)):
+        other += np.outer(A[:, c], B[:, c])
+    assert (want[:, :24].astype(np.float32) != other[:, :24].astype(np.float32)).mean() > 0.05
+    dA, dB = (spd.DeviceCsr.from_host(synth.from_dense(M)) for M in (A, B))
+    h = _lists(spd)
+    for _ in range(3):
+        assert np.array_equal(_np(h.pairwise(dA, dB, "inner_product")), want.astype(np.float32))
+    h.close()
+
+
+@pytest.mark.parametrize("metric", ["inner_product", "cosine", "l2_expanded", "correlation", "canberra", "l1"])
+def test_sums_that_cancel(spd, metric):
+    """Pairs that share columns and whose sum is 0 all the same count as any other pair: rows of both signs in every tile, nearer and
+    farther than the rows that share nothing."""
+    rng = np.random.default_rng(61)
+    cols, m, n = 20_000, 1_024, 13_000
+    base = np.sort(rng.choice(np.arange(50, cols), size=(n, 3)), axis=1)
+    keep = np.concatenate([np.ones((n, 1), bool), np.diff(base, axis=1) > 0], axis=1)
+    size = np.where(rng.random(n) < 0.3, 0.25, 2.0)        # small rows: nearer than any that shares nothing
+    indices, values, indptr = [], [], [0]
+    for r in range(n):
+        pair = 2 * int(rng.integers(0, 25))                # (two columns below 50 of opposite sign: 0 against equal entries)
+        sign = size[r] * rng.choice([-1.0, 1.0])
+        indices += [pair, pair + 1] + base[r][keep[r]].tolist()
+        values += [sign, -sign if r % 3 else sign] + [size[r]] * int(keep[r].sum())
+        indptr.append(len(indices))
+    B = {"n_rows": n, "n_cols": cols, "indptr": np.array(indptr, np.int64), "indices": np.array(indices, np.int32), "values": np.array(values, np.float32)}
+    pairs = 2 * (np.arange(m) % 25)
+    A = {"n_rows": m, "n_cols": cols, "indptr": np.arange(m + 1, dtype=np.int64) * 2,
+         "indices": np.stack([pairs, pairs + 1], axis=1).reshape(-1).astype(np.int32), "values": np.full(2 * m, 0.5, np.float32)}
+    rows = np.arange(0, m, 37)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], rows_a=rows)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = _lists(spd)
+    assert_distances_close(_np(h.pairwise(dA, dB, metric))[rows], want, metric)
+    for k in (1, 7, 40):
+        idx, dist = h.knn(dA, dB, metric, k)
+        assert_knn_matches(_np(idx)[rows], _np(dist)[rows], want, k, metric, "%s k=%d" % (metric, k))
+    h.close()
+
+
 @pytest.mark.parametrize("metric", ["l2_expanded", "l1", "hamming", "jensen_shannon", "minkowski"])
 @pytest.mark.parametrize("m,n,cols,lengths_a,lengths_b", [
     (20, 1300, 1203, (1200, 257, 256, 900, 5, 0, 1203), (30, 3, 200)),           # rows that wavefronts share, one per tile and more
