@@ -289,8 +289,8 @@ def main():
         # LDS: what a lane must read per step (the column's map entry, the R staged values)
         value_bytes = 1.0 if metric == "jaccard" else 4.0
         lds_per_visit = LOOKUP_BYTES.get(staging, 0) / float(R) + value_bytes
-        if lists:                                         # a pair's sums, read and written: an upper bound, since
-            lds_per_visit = 32.0 if metric == "jensen_shannon" else 16.0     # dense columns are summed in registers
+        if lists:                                         # a pair's sum (or count), read and written: an upper bound,
+            lds_per_visit = 8.0 if metric == "jaccard" else 16.0             # since dense columns are summed in registers
         lds = {"achieved": visits * lds_per_visit, "peak": LDS_PEAK_BYTES, "unit": "B/s",
                "frac": round(visits * lds_per_visit / LDS_PEAK_BYTES, 4), "lds_bytes_per_visit": round(lds_per_visit, 3)}
         bound = "alu" if alu["frac"] >= lds["frac"] else "lds"
