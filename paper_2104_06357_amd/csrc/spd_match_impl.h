@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     using Acc = typename O::Acc;
     // D: 64-row pieces of a dense column that are summed in registers together; the largest tiles hold 19 for one
     // fp64 sum (one round of 19 against two of 10: 2,048 queries of 300,000 rows of 230, 10.5 -> 10.2 ms; 13 and 6
-    // leave half a round idle: 11.3), 39 for a count and 13 for two sums
+    // leave half a round idle: 11.3) and 39 for a count; a sum and a count have 13 and Minkowski's three numbers 10, in two rounds of 7
     // (Jensen-Shannon needs its registers for the logarithms)
     constexpr int U = kMatchUnroll, D = S::kOne ? (OP == OP_JS ? 10 : (S::kDoubles ? 19 : 13)) : 7, nw = match_waves(match_cell_bytes(OP));
     extern __shared__ __align__(16) unsigned char dyn[];
@@ -673,7 +673,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
 
-    // ---- the longest rows: a sixteenth of the row to each wavefront, the strips summed in a fixed order --
+    // ---- the longest rows: an even share of the row to each wavefront, the strips summed in a fixed order --
     // (a wavefront alone would hold its workgroup up long after the others are done)
     for (int ti = 0; ti < my_tiles; ++ti) {
         const int tile = group + ti * args.groups;
