@@ -26,7 +26,7 @@
  *    stream at all, so the planning of one call runs while the kernels of the one before it do.
  *    A host copy that differs from the device array gives wrong results (its last entry is
  *    checked against nnz, and no access leaves the arrays).
- *  - Sums are carried in fp64 and rounded once.  The order of a pair's terms, and with it the last place of
+ *  - Sums are carried in fp64, or in 64-bit fixed point that rounds no coarser, and rounded once.  The order of a pair's terms, and with it the last place of
  *    its distance, depends on the way the call is computed (option "match_lists") and on how it is cut, that is
  *    on the sizes of both operands, the options and the scratch; equal calls give equal bits.
  *  - Scratch memory comes from the handle's own grow-only allocation, or from the caller

@@ -520,19 +520,24 @@ int product_of(const spd_handle *h, int metric, float p) {
     return op;
 }
 
-struct MatchLayout { size_t list, ptr, norms, least, end; };
+struct MatchLayout { size_t values, rows, ptr, norms, least, scales, end; };
 MatchLayout layout_match(const MatchShape &s, int64_t n, int64_t nnz, Carver &cv) {
     MatchLayout L;
-    L.list = cv.take((size_t)s.list_entries(nnz) * 8);
+    L.values = cv.take((size_t)s.list_entries(nnz) * 4);
+    // (half of it is spare: a call asks for the scratch it has asked for, and scratch of a given size sends the same calls to the
+    // staged scan, as when an entry took eight bytes)
+    L.rows = cv.take((size_t)s.list_entries(nnz) * 4);
     L.ptr = cv.take((size_t)s.n_tiles * (size_t)s.ptr_stride * 4);
     L.norms = cv.take((size_t)n * 16);
     L.least = cv.take((size_t)s.n_tiles * 16);
+    L.scales = cv.take((size_t)n * 2);
     L.end = cv.off;
     return L;
 }
 MatchB match_b_at(const MatchShape &s, const MatchLayout &L, unsigned char *dev) {
-    return MatchB{reinterpret_cast<uint2 *>(dev + L.list), reinterpret_cast<uint32_t *>(dev + L.ptr),
-                  reinterpret_cast<double *>(dev + L.norms), reinterpret_cast<double *>(dev + L.least), s, nullptr};
+    return MatchB{reinterpret_cast<float *>(dev + L.values), reinterpret_cast<uint16_t *>(dev + L.rows), reinterpret_cast<uint32_t *>(dev + L.ptr),
+                  reinterpret_cast<double *>(dev + L.norms), reinterpret_cast<double *>(dev + L.least),
+                  reinterpret_cast<int16_t *>(dev + L.scales), s, nullptr};
 }
 // Grid of the column-list kernel: groups of tiles times slices of A's rows, one workgroup for each
 // compute unit of the chip.  Where the lists are more than the L2 caches hold, the tiles are dealt to the
@@ -569,7 +574,7 @@ int64_t match_items(const MatchShape &s, const MatchGrid &g, int64_t m) {
     return ((m + g.slices - 1) / g.slices) * ((s.n_tiles + g.groups - 1) / g.groups);
 }
 struct ColumnsLayout { size_t words, sums, totals, masks, before, a_indices, b_indptr, b_indices, b_values; };
-struct MatchScratch { MatchLayout b; ColumnsLayout c; size_t rows, norms_a, tau, part, row_off, row_lists, end; };
+struct MatchScratch { MatchLayout b; ColumnsLayout c; size_t rows, norms_a, scales_a, tau, part, row_off, row_lists, end; };
 // `columns`: 0, or the operands' column count where both are copied over A's columns first (spd_match_columns.hip).
 MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int64_t m, int64_t nnz_a, int64_t n, int64_t nnz_b, int knn_k,
                                bool with_b, int64_t columns) {
@@ -590,6 +595,7 @@ MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int64_t 
     }
     L.rows = cv.take((size_t)m * sizeof(MatchRow));
     L.norms_a = cv.take((size_t)m * 16);
+    L.scales_a = cv.take((size_t)m * 2);
     if (knn_k > 0) {
         L.tau = cv.take((size_t)m * 8);
         L.row_off = cv.take((size_t)m * 8);
@@ -610,10 +616,10 @@ std::string match_check(const PlanOptions &opt, const MatchShape &s, const Match
         return "column blocks";
     if (s.ptr_stride < n_cols + blocks) return "list bounds";
     if (s.dense_per_block < 1 || s.dense_per_block > (int32_t)kBuildDense || s.dense_from < 1 ||
-        s.tile_extra != blocks * s.dense_per_block * (T / 2)) return "dense columns";
+        s.dense_from > T || s.tile_extra != blocks * s.dense_per_block * (T - s.dense_from)) return "dense columns";
     if (s.list_entries(nnz_b) >= (int64_t)1 << 29) return "list positions";
-    const int64_t build = (int64_t)s.stage * 8 + ((int64_t)4 << s.block_shift) + 12 * T;
-    if ((int64_t)s.build_lds_bytes != build || build + 1024 > opt.lds_budget) return "build over the LDS";
+    const int64_t build = (int64_t)s.stage * 6 + ((int64_t)4 << s.block_shift) + 14 * T;
+    if ((int64_t)s.build_lds_bytes != build || s.stage % 8 != 0 || build + 1024 > opt.lds_budget) return "build over the LDS";
     if (g.slices < 1 || g.groups < 1 || g.run < 1 || g.run > tiles || g.groups > tiles || (g.by_xcd && g.groups < tiles && g.groups % 8 != 0)) return "grid";
     if (match_items(s, g, m) >= (int64_t)1 << 30) return "(tile, row)s of a workgroup";
     return std::string();
@@ -778,19 +784,20 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
 
 
 // The norms of B's rows, and their lists.
-spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int metric, const MetricInfo &mi, const OpParams &q) {
+spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int op, int metric, const MetricInfo &mi, const OpParams &q) {
     LaunchTimer norms(h, "norms_b", 0, 0, 0, 0, 0, 0);
-    hipError_t e = launch_match_norms(h->stream, B->indptr, B->values, B->n_rows, B->nnz, metric, mi.transform, mi.norm, q.p, q.k, mb.norms);
+    hipError_t e = launch_match_norms(h->stream, B->indptr, B->values, B->n_rows, B->nnz, op, metric, mi.transform, mi.norm, q.p, q.k, false,
+                                      mb.norms, mb.scales);
     if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
     norms.done();
     return SPD_OK;
 }
 // (`knn`: and each tile's row of the least norm)
-spd_status stage_lists(spd_handle *h, const spd_csr *B, MatchB mb, int op, const MetricInfo &mi, bool knn) {
+spd_status stage_lists(spd_handle *h, const spd_csr *B, MatchB mb, int op, int metric, const MetricInfo &mi, bool knn) {
     if (!knn) mb.least = nullptr;
     LaunchTimer lists(h, "lists_b", 0, 0, 0, 0, 0, mb.shape.n_tiles);
     hipError_t e = launch_match_build(h->stream, B->indptr, B->indices, B->values, B->n_rows, B->nnz, (uint32_t)B->n_cols, mb,
-                           match_cell_bytes(op), mi.transform);
+                           op, metric, mi.transform);
     if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
     lists.done();
     return SPD_OK;
@@ -816,7 +823,7 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     const int32_t *a_indices = A->indices;
     spd_csr listed = *B;
     if (!index_lists) {
-        st = stage_norms(h, B, mb, metric, mi, q);
+        st = stage_norms(h, B, mb, op, metric, mi, q);
         if (st != SPD_OK) return st;
         if (compact) {
             const MatchColumns c{reinterpret_cast<uint2 *>(ws + L.c.words), reinterpret_cast<uint32_t *>(ws + L.c.sums),
@@ -835,13 +842,14 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
             listed.n_cols = way.columns;
             mb.cols = c.totals;
         }
-        st = stage_lists(h, &listed, mb, op, mi, knn_k > 0);
+        st = stage_lists(h, &listed, mb, op, metric, mi, knn_k > 0);
         if (st != SPD_OK) return st;
     }
     double *norms_a = reinterpret_cast<double *>(ws + L.norms_a);
+    int16_t *scales_a = reinterpret_cast<int16_t *>(ws + L.scales_a);
     {
         LaunchTimer lt(h, "norms_a", 0, 0, 0, 0, 0, 0);
-        e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, metric, mi.transform, mi.norm, q.p, q.k, norms_a);
+        e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, op, metric, mi.transform, mi.norm, q.p, q.k, true, norms_a, scales_a);
         if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
         lt.done();
     }
@@ -878,6 +886,7 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     a.rows = reinterpret_cast<const MatchRow *>(ws + L.rows);
     a.m = (int32_t)m;
     a.norms_a = norms_a;
+    a.scales_a = scales_a;
     a.b_indptr = listed.indptr;
     a.b_nnz = B->nnz;
     a.b = mb;
@@ -1009,7 +1018,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     metric = effective_metric(metric, p);
     const int op = product_of(h, metric, p);
     const bool swap = knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
-    const MatchWay way = match_way(h, A, B, op, semiring, swap, knn_k, index != nullptr, index && index->match.list);
+    const MatchWay way = match_way(h, A, B, op, semiring, swap, knn_k, index != nullptr, index && index->match.values);
 
     // ---- row pointers on the host: the caller's copies, or read back (the call's only
     //      synchronisation) ----------------------------------------------------------------
@@ -1733,8 +1742,8 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         if (hipMalloc(&ix->match_dev, lists.end) == hipSuccess) {
             ix->match = match_b_at(shape, lists, reinterpret_cast<unsigned char *>(ix->match_dev));
             ix->match_op = op;
-            st = stage_norms(h, Index, ix->match, run_as, mi, q);
-            if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, mi, true);
+            st = stage_norms(h, Index, ix->match, op, run_as, mi, q);
+            if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, run_as, mi, true);
             if (st != SPD_OK) return st;
         } else {                         // (no memory left for the lists: the packed copy serves every call)
             ix->match_dev = nullptr;

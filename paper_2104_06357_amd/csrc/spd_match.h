@@ -7,9 +7,9 @@
 // call).  A wavefront takes one row of A, walks the lists of that row's columns only, and adds
 // product(a, b) to one sum per row of the tile, which lie in its own strip of LDS.  Work is done for
 // the columns that two rows share and for nothing else.  The lists are walked in chunks of 16 entries,
-// four chunks of any lists to a step.  A strip is private to its wavefront, and the sums are formed in the order of A's columns (a row of
-// B appears at most once in a list, and lanes that meet in one sum are served in ascending order, which
-// is that order): the results do not depend on the schedule.
+// four chunks of any lists to a step.  A strip is private to its wavefront.  Sums in floating point are formed in the order of A's
+// columns (a row of B appears at most once in a list, and lanes that meet in one sum are served in ascending order, which
+// is that order), sums in fixed point come out the same in any order: the results do not depend on the schedule.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -24,8 +24,8 @@ namespace spd {
 struct MatchRow { int64_t start; int32_t len, row; };
 
 // Entries behind the last list, which a step may read and does not use: 15 of a chunk, and with a tile of
-// 64 rows the 18 other pieces of a dense column that are summed together (half an entry a row).
-constexpr int64_t kMatchSpare = 640;
+// 64 rows the 18 other pieces of a dense column that are summed together (an entry a row).
+constexpr int64_t kMatchSpare = 1280;
 
 // How B's rows are cut: into tiles of rows, and the columns of a tile into blocks (a power of two of them),
 // each with room for its entries and for `dense_per_block` columns kept as one value per row of the tile.
@@ -39,16 +39,20 @@ struct MatchShape {
 };
 MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, int64_t nnz);
 
+// An entry of a list lies in two arrays, six bytes together: two loads of four and two bytes take the L1 9 clocks for 64 lanes, one
+// of eight 16 (measured with everything in the L1), and a count's entries need the two bytes alone (4,096 x 500,000 sets, Jaccard,
+// k-NN, 10.8 -> 8.9 ms a call).
 struct MatchB {
-    uint2 *list;            // {byte offset of the row's first sum in a strip, value bits}, by tile, column block and column;
-                            // a dense column: tile_rows values, 0 where the row has none.  (A stored zero keeps
-                            // its place in a list and points to a spare cell behind the strip's last; kMatchSpare
-                            // entries at the end.)
+    float *values;          // by tile, column block and column.  (A stored zero keeps its place in a list; kMatchSpare entries at the end.
+                            // A dense column: tile_rows values, 0 where the row has none.)
+    uint16_t *rows;         // byte offset of the row's first sum in a strip (a stored zero's: of a spare cell behind the strip's last);
+                            // nothing where the column is dense
     uint32_t *ptr;          // n_tiles * ptr_stride: where a column's list begins, from the tile's first entry on, at
                             // column + its block's number (a block has a word more for its last list's end);
                             // kMatchDense is set where the column is dense
     double *norms;          // n * 2, derived
     double *least;          // n_tiles * 2: the norms of a tile's row of the least first norm (k-NN)
+    int16_t *scales;        // n: the exponents of the rows whose values are listed over a power of two (match_fixed), else not used
     MatchShape shape;
     const uint32_t *cols;   // nullptr, or on the device how many columns there are (no more than the shape was made for)
 };
@@ -60,6 +64,7 @@ struct MatchArgs {
     const MatchRow *rows;
     int32_t m;
     const double *norms_a;        // m * 2, derived, by row number
+    const int16_t *scales_a;      // m: exponents, see match_fixed
     const int64_t *b_indptr;
     int64_t b_nnz;
     MatchB b;
@@ -105,6 +110,37 @@ SPD_HD constexpr uint32_t match_strip_bytes(int cell_bytes, int tile_rows) { ret
 SPD_HD constexpr int match_waves(int cell_bytes) { return cell_bytes >= 16 ? 12 : 16; }
 // Upper bound of the kernel's static __shared__ use (64 half words to a wavefront, the locks).
 SPD_HD constexpr int64_t match_static_lds(int cell_bytes) { return 256 + match_waves(cell_bytes) * 128; }
+// Sums in fixed point.  An LDS add of 64 doubles at random rows takes 25.3 clocks, of 64 integers of 64 bits 12.8 (8.1 and 6.2 without
+// bank conflicts).  A term is scaled by a power of two and added to 2 in fp64 (to 3 where it may be negative), so that its last place is
+// 2^-51: the words of such a sum count units of 2^-51, and adding them up as integers rounds no further.
+//   L1         the scale 2^-e is the row of A's: no shared entry's min(|a|, |b|) reaches 2^(e + 1), and all of them together not 2^(e + 10).
+//   Canberra   2 less the ratio, at most 2: e = 2, more for rows of A of more than 2^10 entries.
+//   dot        rows of either side are scaled by a power of two (exact) that brings their largest entry below 1 and their
+//              length below 2^5; a product is below 1 and their sum below 2^10.
+// A term is rounded to half a unit: 2^-52 of the row's largest entry (of both rows' for the dot product) where the rows have
+// up to some 1,000 entries that are alike; a sum in fp64 is rounded with every term, to 2^-53 of what it has come to.  What the distances are
+// formed from does not fall below the rows' norms, so this is as good; an inner product by itself may be far below
+// them, and its sum (and that of the 0/1 values of the set metrics as a dot product) stays in floating point.
+SPD_HD constexpr bool match_fixed(int op, int metric) {
+    return op == OP_L1 || op == OP_CANB ||
+           (op == OP_DOT && (metric == MT_COSINE || metric == MT_L2 || metric == MT_CORRELATION || metric == MT_HELLINGER));
+}
+// floor(log2 v), -1023 for 0, 1,024 for what is not finite.
+SPD_HD int match_ilog2(double v) {
+    uint64_t w;
+    __builtin_memcpy(&w, &v, 8);
+    return (int)((w >> 52) & 0x7ffu) - 1023;
+}
+// A row's exponent from its largest entry and (L1) the sum or (dot) the sum of squares of its entries.  In [-200, 200]; 0 for a row of zeros.
+SPD_HD int match_scale(int op, float largest, double sum) {
+    if (!(sum > 0.0) || !(largest > 0.0f)) return 0;
+    const int top = match_ilog2((double)largest), all = match_ilog2(sum);
+    const int e = op == OP_L1 ? (top > all - 9 ? top : all - 9) : (top + 1 > (all >> 1) - 4 ? top + 1 : (all >> 1) - 4);
+    return e < -200 ? -200 : (e > 200 ? 200 : e);
+}
+// Canberra's for a row of A of `len` entries: 2 len 2^(51 - e) below 2^62.
+SPD_HD int match_canberra_scale(int len) { return len < (1 << 10) ? 2 : 2 + (32 - 10) - __builtin_clz((unsigned)len); }
+
 // The products the column lists serve.
 SPD_HD constexpr bool match_serves(int op) {
     return op == OP_DOT || op == OP_L1 || op == OP_CANB || op == OP_HAMM || op == OP_KL || op == OP_JS || op == OP_CNT ||
@@ -114,11 +150,13 @@ SPD_HD constexpr bool match_serves(int op) {
 // Whether the launches for a call's lists, of which A has m rows, are below 2^32 work-items each (`renumbered`: over A's columns).
 bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renumbered);
 
+// `op`: the product, for the rows' scales (nullptr: not asked for); `queries`: the rows are A's, whose scaled norms carry the
+// unit of the sums too.
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
-                              int metric, int transform, int norm, float p, double k, double *norms);
+                              int op, int metric, int transform, int norm, float p, double k, bool queries, double *norms, int16_t *scales);
 // (after the norms; `b.least` nullptr: not asked for)
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
-                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int transform);
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int metric, int transform);
 hipError_t launch_match_columns(hipStream_t st, const int32_t *a_indices, int64_t a_nnz, const int64_t *b_indptr, const int32_t *b_indices,
                                 const float *b_values, int64_t b_rows, int64_t b_nnz, uint32_t n_cols, const MatchColumns &c);
 // k-NN: the rows' bounds, and where each row's candidate lists lie.

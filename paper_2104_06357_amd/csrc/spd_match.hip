@@ -13,44 +13,61 @@ namespace spd {
 // ------------------------------------------------------------------------------------
 template <int G>
 __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__restrict__ indptr, const float *__restrict__ values,
-                                                              int64_t n_rows, int64_t nnz, int metric, int transform, int norm,
-                                                              float p, double k, double *__restrict__ norms) {
+                                                              int64_t n_rows, int64_t nnz, int op, int metric, int transform, int norm,
+                                                              float p, double k, int unit_log2, double *__restrict__ norms,
+                                                              int16_t *__restrict__ scales) {
     constexpr int kRows = 256 / G;
     constexpr int64_t kLong = G < 256 ? 64 * G : INT64_MAX;
     __shared__ int s_long[kRows], s_longs;
     __shared__ double s_sum[256 / kWave][2];
+    __shared__ float s_most[256 / kWave];
     const int tid = (int)threadIdx.x, sub = tid % G;
     const int64_t row0 = (int64_t)blockIdx.x * kRows, row = row0 + tid / G;
-    auto sums = [&](int64_t from, int64_t end, int stride, double &s0, double &s1) {
+    auto sums = [&](int64_t from, int64_t end, int stride, double &s0, double &s1, float &most) {
         for (int64_t e = from; e < end; e += 4 * stride) {
             float v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) v[u] = e + u * stride < end ? values[e + u * stride] : 0.0f;
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (e + u * stride < end) norm_accumulate(norm, transform_value(transform, v[u]), p, s0, s1);
+                if (e + u * stride < end) {
+                    const float t = transform_value(transform, v[u]);
+                    norm_accumulate(norm, t, p, s0, s1);
+                    most = fmaxf(most, fabsf(t));
+                }
         }
 #pragma unroll
         for (int d = kWave / 2; d >= 1; d >>= 1)
-            if (d < stride) { s0 += __shfl_xor(s0, d); s1 += __shfl_xor(s1, d); }
+            if (d < stride) { s0 += __shfl_xor(s0, d); s1 += __shfl_xor(s1, d); most = fmaxf(most, __shfl_xor(most, d)); }
     };
-    auto write = [&](int64_t r, double s0, double s1) {
+    auto write = [&](int64_t r, double s0, double s1, float most) {
         double d0, d1;
         norm_derive(metric, k, s0, s1, d0, d1);
+        if (scales) {
+            const int e = match_scale(op, most, norm == NORM_SUM_SUMSQ ? s1 : s0);
+            scales[r] = (int16_t)e;
+            // (of rows that are scaled by 2^-e, the sum of the queries' in units of 2^unit_log2)
+            if (op == OP_DOT) {
+                if (metric == MT_L2 || metric == MT_HELLINGER) d1 = 1.0;
+                if (metric == MT_CORRELATION) d0 = ldexp(d0, -(e + unit_log2));
+                d1 = ldexp(d1, e + unit_log2);
+            }
+        }
         norms[(size_t)r * 2] = d0;
         norms[(size_t)r * 2 + 1] = d1;
     };
     // a row by all 256 lanes: its wavefronts' sums in a fixed order
     auto by_all = [&](int64_t r, int64_t begin, int64_t end) {
         double s0 = 0.0, s1 = 0.0;
-        sums(begin + tid, end, 256, s0, s1);
-        if (tid % kWave == 0) { s_sum[tid / kWave][0] = s0; s_sum[tid / kWave][1] = s1; }
+        float most = 0.0f;
+        sums(begin + tid, end, 256, s0, s1, most);
+        if (tid % kWave == 0) { s_sum[tid / kWave][0] = s0; s_sum[tid / kWave][1] = s1; s_most[tid / kWave] = most; }
         __syncthreads();
         if (tid == 0) {
             s0 = 0.0; s1 = 0.0;
 #pragma unroll
-            for (int w = 0; w < 256 / kWave; ++w) { s0 += s_sum[w][0]; s1 += s_sum[w][1]; }
-            write(r, s0, s1);
+            for (int w = 0; w < 256 / kWave; ++w) { s0 += s_sum[w][0]; s1 += s_sum[w][1]; most = fmaxf(most, s_most[w]); }
+            write(r, s0, s1, most);
         }
     };
     int64_t begin = 0, end = 0;
@@ -66,8 +83,9 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
         const bool is_long = end - begin > kLong;
         if (is_long && sub == 0) s_long[atomicAdd(&s_longs, 1)] = tid / G;
         double s0 = 0.0, s1 = 0.0;
-        sums(begin + sub, is_long ? begin : end, G, s0, s1);
-        if (row < n_rows && !is_long && sub == 0) write(row, s0, s1);
+        float most = 0.0f;
+        sums(begin + sub, is_long ? begin : end, G, s0, s1, most);
+        if (row < n_rows && !is_long && sub == 0) write(row, s0, s1, most);
         __syncthreads();
         const int longs = s_longs;
         for (int at = 0; at < longs; ++at) {
@@ -122,7 +140,7 @@ template <int G>
 __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                         const float *__restrict__ values, int64_t n_rows, int64_t nnz,
                                                                         uint32_t most_cols, MatchB b, uint32_t blocks_per_wg, uint32_t wgs, int unit,
-                                                                        int transform) {
+                                                                        int transform, bool scaled, bool with_values) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     __shared__ uint32_t s_wave[kBuildThreads / kWave];
     __shared__ uint32_t s_dense[kBuildDense], s_long[kBuildLong], s_longs;
@@ -141,11 +159,13 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     const int64_t row_first = clamp_i64(indptr[j0], 0, nnz);             // of the rows' entries
     const int64_t first = row_first + tile * shape.tile_extra;            // of the tile's lists
     const int64_t list_end = shape.list_entries(nnz) - kMatchSpare;
-    uint2 *s_stage = reinterpret_cast<uint2 *>(s_raw);                              // stage entries
-    uint32_t *s_count = reinterpret_cast<uint32_t *>(s_raw + (size_t)shape.stage * 8);   // block_cols counters, a multiple of 4
+    float *s_value = reinterpret_cast<float *>(s_raw);                              // stage entries, a multiple of 8
+    uint16_t *s_row = reinterpret_cast<uint16_t *>(s_value + shape.stage);
+    uint32_t *s_count = reinterpret_cast<uint32_t *>(s_row + shape.stage);    // block_cols counters, a multiple of 4
     uint32_t *s_cur = s_count + block_cols;                                   // where a row's block begins ...
     uint32_t *s_next = s_cur + T;                                                   // ... and the next one
     uint32_t *s_end = s_next + T;
+    int16_t *s_scale = reinterpret_cast<int16_t *>(s_end + T);
     uint32_t *ptr = b.ptr + (size_t)tile * (size_t)shape.ptr_stride;
     if (part == 0 && b.least) tile_least(b.norms + (size_t)j0 * 2, rows, b.least + (size_t)tile * 2, s_least);
     const uint32_t block_first = (uint32_t)part * blocks_per_wg;
@@ -165,6 +185,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             }
             s_cur[r] = lo;
             s_end[r] = end;
+            s_scale[r] = scaled ? b.scales[j0 + r] : (int16_t)0;
             mine += lo - begin;
         }
 #pragma unroll
@@ -173,7 +194,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         __syncthreads();
 #pragma unroll
         for (int w = 0; w < nw; ++w) base += s_wave[w];
-        base += block_first * (uint32_t)shape.dense_per_block * ((uint32_t)T / 2u);
+        base += block_first * (uint32_t)shape.dense_per_block * (uint32_t)(T - shape.dense_from);
     }
     for (uint32_t block = block_first; block < block_last; ++block) {
         const uint32_t c0 = block * block_cols, range = min(block_cols, cols - c0);
@@ -256,7 +277,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             __syncthreads();
             return at;
         };
-        const uint32_t half = (uint32_t)T / 2u, mark = (uint32_t)shape.dense_from;
+        const uint32_t whole = (uint32_t)T, mark = (uint32_t)shape.dense_from;
         uint32_t n_dense = 0u, total = 0u;
         for (uint32_t i0 = 0; i0 < block_cols; i0 += 4 * kBuildThreads) {
             const uint32_t i = i0 + 4u * (uint32_t)tid;
@@ -273,7 +294,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
                 const bool d = v[x] >= mark && rank < (uint32_t)shape.dense_per_block;
                 if (v[x] >= mark) ++rank;
                 is_dense |= d ? 1u << x : 0u;
-                size[x] = d ? half : v[x];
+                size[x] = d ? whole : v[x];
                 sum += size[x];
             }
             // counts -> starts: from the tile's first entry in memory, from the block's in LDS
@@ -293,31 +314,37 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         if (tid == 0) ptr[c0 + block + range] = base + total;
         n_dense = min(n_dense, (uint32_t)shape.dense_per_block);
         __syncthreads();
-        uint2 *__restrict__ list = b.list + first + base;          // the block's piece
+        float *__restrict__ values_at = b.values + first + base;   // the block's piece
+        uint16_t *__restrict__ rows_at = b.rows + first + base;
         const int64_t room = list_end - (first + base);            // (never reached while the row pointers hold)
         for (uint32_t d = 0; d < n_dense; ++d)
-            for (uint32_t i = s_dense[d] + (uint32_t)tid; i < s_dense[d] + half; i += kBuildThreads) {
-                if (i < shape.stage) s_stage[i] = make_uint2(0u, 0u);
-                else if (i < room) list[i] = make_uint2(0u, 0u);
+            for (uint32_t i = s_dense[d] + (uint32_t)tid; i < s_dense[d] + whole; i += kBuildThreads) {
+                if (i < shape.stage) s_value[i] = 0.0f;
+                else if (i < room) values_at[i] = 0.0f;
             }
         __threadfence_block();
         __syncthreads();
         // place
         auto place = [&](uint32_t c, float v, int r) {
-            const float t = transform_value(transform, v);
             if (c - c0 >= range) return;
+            const float t = transform_value(transform, v), scaled_t = __builtin_ldexpf(t, -(int)s_scale[r]);
             uint32_t *count = &s_count[c - c0];
             uint32_t at = *count & ~kMatchDense;
             if (*count & kMatchDense) {
-                at += (uint32_t)r >> 1;
-                if (at < shape.stage) reinterpret_cast<float *>(&s_stage[at])[r & 1] = t;
-                else if (at < room) reinterpret_cast<float *>(&list[at])[r & 1] = t;
+                at += (uint32_t)r;
+                if (at < shape.stage) s_value[at] = scaled_t;
+                else if (at < room) values_at[at] = scaled_t;
             } else {
                 // (a stored zero is absent: it goes to the spare row behind the tile's)
-                const uint2 entry = make_uint2((uint32_t)(t != 0.0f ? r : T) * (uint32_t)unit, __float_as_uint(t));
+                const uint16_t cell = (uint16_t)((uint32_t)(t != 0.0f ? r : T) * (uint32_t)unit);
                 at = atomicAdd(count, 1u);
-                if (at < shape.stage) s_stage[at] = entry;
-                else if (at < room) list[at] = entry;
+                if (at < shape.stage) {
+                    s_row[at] = cell;
+                    s_value[at] = scaled_t;
+                } else if (at < room) {
+                    rows_at[at] = cell;
+                    values_at[at] = scaled_t;
+                }
             }
         };
         constexpr uint32_t kShort = (uint32_t)(G * kBuildPasses);         // a stretch beyond it may be a whole wavefront's
@@ -364,7 +391,10 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         __syncthreads();
         const uint32_t staged = min(total, shape.stage);
         for (uint32_t i = tid; i < staged; i += kBuildThreads)
-            if (i < room) list[i] = s_stage[i];
+            if (i < room) {
+                rows_at[i] = s_row[i];
+                if (with_values || n_dense > 0u) values_at[i] = s_value[i];
+            }
         if (tid == 0) s_wave[0] = 0u;
         __syncthreads();
         {
@@ -374,7 +404,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             if (mine) atomicAdd(&s_wave[0], mine);
         }
         __syncthreads();
-        base += s_wave[0] + (uint32_t)shape.dense_per_block * half;
+        base += s_wave[0] + (uint32_t)shape.dense_per_block * (whole - mark);        // (a dense column has `mark` entries at least)
         __syncthreads();
     }
 }
@@ -388,13 +418,13 @@ int match_norm_lanes(int64_t n_rows, int64_t nnz) {
     return mean >= 128 && n_rows <= 8192 ? 256 : (mean >= 16 ? 64 : 4);
 }
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
-                              int metric, int transform, int norm, float p, double k, double *norms) {
+                              int op, int metric, int transform, int norm, float p, double k, bool queries, double *norms, int16_t *scales) {
     if (n_rows <= 0) return hipSuccess;
     auto go = [&](auto g) {
         constexpr int G = decltype(g)::value;
         const int per = 256 / G;
         hipLaunchKernelGGL((spd_match_norms_kernel<G>), dim3((unsigned)((n_rows + per - 1) / per)), dim3(256), 0, st, indptr, values,
-                           n_rows, nnz, metric, transform, norm, p, k, norms);
+                           n_rows, nnz, op, metric, transform, norm, p, k, queries ? -51 : 0, norms, match_fixed(op, metric) ? scales : nullptr);
     };
     switch (match_norm_lanes(n_rows, nnz)) {
     case 256: go(std::integral_constant<int, 256>{}); break;
@@ -430,10 +460,14 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     // A block of columns: an eighth of the LDS for counters, or twice that, and entries for four fifths, on the mean,
     // of what counters and row positions leave for its piece of the lists (the rest of a fuller block goes straight to
     // memory; narrower blocks read a row's lines more often).  Dense columns may take half as much again.
-    const int64_t usable = lds_budget - 1024, rows_bytes = 12 * (int64_t)s.tile_rows;
+    const int64_t usable = lds_budget - 1024, rows_bytes = 14 * (int64_t)s.tile_rows;
     if (usable < rows_bytes + 4096) return s;
+    // A step of 64 rows of a dense column costs half a list's step.  (From 0.3 / 0.4 / 0.5 / 0.6 of the rows on, us: 1,024 x 300,000 rows
+    // of 230, cosine, 5,796 / 5,651 / 5,638 / 5,767, k-NN of 2,048 of them, Hellinger, 7,535 / 7,570 / 7,645 / 7,909; 10,000 x 10,000 rows
+    // of 38, L1, 336 / 331 / 325 / 318; sets, Jaccard, 9,102 / 8,970 / 8,928 / 8,963.)
+    s.dense_from = std::max(1, s.tile_rows / 2);
     const double per_col = per_cell * (double)s.tile_rows;
-    auto stage_of = [&](int shift) { return (usable - rows_bytes - ((int64_t)4 << shift)) / 8; };
+    auto stage_of = [&](int shift) { return (usable - rows_bytes - ((int64_t)4 << shift)) / 48 * 8; };
     int shift = 2;
     while ((4 << (shift + 1)) <= usable / 8 && (1 << shift) < n_cols) ++shift;
     // (sparse blocks, many of them: what a block costs besides its entries.  500,000 sets over 242,000 columns, 2,432 rows to
@@ -453,17 +487,14 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     const int64_t tiles_now = (n + s.tile_rows - 1) / s.tile_rows;
     auto blocks_of = [&](int at) { return (n_cols + (1 << at) - 1) >> at; };
     while (shift > 8 && tiles_now * blocks_of(shift) < 256 &&
-           tiles_now * blocks_of(shift - 1) * dense_of(shift - 1) * (s.tile_rows / 2) * 8 <= 8 * nnz + (512 << 10)) --shift;
+           tiles_now * blocks_of(shift - 1) * dense_of(shift - 1) * (s.tile_rows - s.dense_from) * 6 <= 8 * nnz + (512 << 10)) --shift;
     s.block_shift = shift;
     s.stage = (uint32_t)stage_of(shift);
     s.blocks = (int32_t)blocks_of(shift);
     s.dense_per_block = dense_of(shift);
-    // a step of 64 rows of a dense column costs this share of a list's step
-    const double cost = op == OP_DOT ? 0.3 : (op == OP_L1 || op == OP_CNT || op == OP_HAMM || op == OP_CANB ? 0.4 : 0.5);
-    s.dense_from = std::max(1, (int32_t)(cost * s.tile_rows));
     s.ptr_stride = (n_cols + s.blocks + 3) / 4 * 4;
-    s.tile_extra = (int64_t)s.blocks * s.dense_per_block * (s.tile_rows / 2);
-    s.build_lds_bytes = s.stage * 8u + (4u << shift) + (uint32_t)rows_bytes;
+    s.tile_extra = (int64_t)s.blocks * s.dense_per_block * (s.tile_rows - s.dense_from);
+    s.build_lds_bytes = s.stage * 6u + (4u << shift) + (uint32_t)rows_bytes;
     s.n_tiles = (int32_t)((n + s.tile_rows - 1) / s.tile_rows);
     return s;
 }
@@ -478,7 +509,7 @@ bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renu
 }
 
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
-                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int cell_bytes, int transform) {
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int metric, int transform) {
     if (n_rows <= 0) return hipSuccess;
     const MatchShape &s = b.shape;
     const uint32_t per_wg = match_build_blocks(s), wgs = ((uint32_t)s.blocks + per_wg - 1u) / per_wg;
@@ -489,7 +520,7 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
         hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(kern, dim3((unsigned)s.n_tiles * wgs), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
-                           nnz, k, b, per_wg, wgs, cell_bytes >= 8 ? 8 : 4, transform);
+                           nnz, k, b, per_wg, wgs, match_cell_bytes(op) >= 8 ? 8 : 4, transform, op == OP_DOT && match_fixed(op, metric), op != OP_CNT);
         return hipGetLastError();
     };
     if (per_row >= 8.0) return go(std::integral_constant<int, 16>{});

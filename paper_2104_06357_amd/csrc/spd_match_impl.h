@@ -16,14 +16,23 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 }
 // A strip holds a pair's sums in planes, one for each number of Op<OP>::Acc (its doubles, then its count), so that the
 // rows of neighbouring lanes lie in different banks.  `at`: LDS address of the strip, `plane`: bytes of a plane of doubles.
-template <int OP> struct Sums {
-    using Acc = typename Op<OP>::Acc;
+// FIX: one sum in fixed point in the place of the double.
+struct Fixed { long long v; };
+template <int OP, bool FIX> struct Sums {
+    using Acc = std::conditional_t<FIX, Fixed, typename Op<OP>::Acc>;
+    static_assert(!FIX || (match_doubles(OP) == 1 && match_counts(OP) == 0), "one sum");
+    static __device__ __forceinline__ void init(Acc &x) {
+        if constexpr (FIX) x.v = 0; else Op<OP>::init(x);
+    }
+    static __device__ __forceinline__ void combine(Acc &x, const Acc &y) {
+        if constexpr (FIX) x.v += y.v; else Op<OP>::combine(x, y);
+    }
     static constexpr int kDoubles = match_doubles(OP), kCounts = match_counts(OP);
     static constexpr bool kOne = kDoubles + kCounts == 1;
     static constexpr uint32_t kUnit = kDoubles ? 8u : 4u;          // bytes from a row's first number to the next row's
     static __device__ __forceinline__ Acc get(uint32_t at, uint32_t plane, uint32_t row) {
         Acc x;
-        Op<OP>::init(x);
+        init(x);
 #pragma unroll
         for (int p = 0; p < kDoubles; ++p) {
             const double v = *lds_at<double>(at + (uint32_t)p * plane + row * 8u);
@@ -50,6 +59,10 @@ template <int OP> struct Sums {
     }
     // Adds to the sums of the row whose first number lies `offset` bytes into the strip.
     static __device__ __forceinline__ void add(uint32_t at, uint32_t plane, uint32_t offset, const Acc &x) {
+        if constexpr (FIX) {
+            __hip_atomic_fetch_add(lds_at<unsigned long long>(at + offset), (unsigned long long)x.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            return;
+        }
 #pragma unroll
         for (int p = 0; p < kDoubles; ++p) {
             double v;
@@ -116,6 +129,67 @@ template <int OP> __device__ __forceinline__ bool match_visit(typename Op<OP>::A
     return true;
 }
 
+// A row of A as the sums in fixed point take it (match_fixed): a term x of the row stands as `offset` + `factor` * x (dot: a * b is
+// the product itself), in [2, 4) and thus in units of 2^-51; `unit` is what one of them is worth; the row's values are taken over 2^down (dot).
+struct Scale { double factor, offset, unit; int down; };
+__device__ __forceinline__ double power_of_two(int e) { return __hiloint2double((1023 + e) << 20, 0); }
+template <int OP> __device__ __forceinline__ Scale scale_of(int e, int len) {
+    Scale s{1.0, 3.0, power_of_two(-51), 0};
+    if constexpr (OP == OP_DOT) {
+        s.down = e;
+    } else {
+        const int k = OP == OP_CANB ? match_canberra_scale(len) : e;
+        s.factor = power_of_two(-k);
+        s.offset = 2.0;
+        s.unit = power_of_two(k - 51);
+        if constexpr (OP == OP_CANB) { s.offset += 2.0 * s.factor; s.factor = -s.factor; }
+    }
+    return s;
+}
+// The words of a double in [2, 4) are 2^62 and its mantissa, which counts units of 2^-51.  Terms that are not negative stand as 2 + x:
+// a sum of such words modulo 2^62 is the sum of the units.  Dot products of either sign stand as 3 + x: the upper word less 3's
+// (the lower one is 0) leaves the units, negative ones too.
+template <int OP> __device__ __forceinline__ Fixed fixed_visit(float a, float b, const Scale &s) {
+    double t;
+    if constexpr (OP == OP_DOT) {
+        t = fma((double)a, (double)b, 3.0);
+        return Fixed{(long long)(((unsigned long long)(uint32_t)(__double2hiint(t) - 0x40080000) << 32) | (uint32_t)__double2loint(t))};
+    } else if constexpr (OP == OP_L1) {
+        t = fma((double)fabsf(median_with_zero(a, b)), s.factor, 2.0);
+    } else {
+        t = fma((double)fast_div(fabsf(a - b), fabsf(a) + fabsf(b)), s.factor, s.offset);
+    }
+    long long w;
+    __builtin_memcpy(&w, &t, 8);
+    return Fixed{w};
+}
+// A sum of Op<OP>, formed in fp64, in units.
+template <int OP> __device__ __forceinline__ Fixed fixed_sum(const typename Op<OP>::Acc &x, const Scale &s) {
+    return Fixed{(long long)__builtin_rint(x.v * (s.factor * 0x1p51))};
+}
+// The units of a sum.
+template <int OP> __device__ __forceinline__ double units_of(const Fixed &x) {
+    return OP == OP_DOT ? (double)x.v : (double)(unsigned long long)(x.v & ((1ll << 62) - 1));
+}
+// The distance of a pair from its sums and the rows' norms.
+template <int OP, bool FIX, int MT>
+__device__ __forceinline__ float distance_of(const OpParams &q, const typename Sums<OP, FIX>::Acc &c, double unit, double na0, double na1, const double2 &nb) {
+    if constexpr (FIX) {
+        const double v = units_of<OP>(c);
+        if constexpr (OP == OP_DOT) return finish_as<MT>(q, MT == MT_L2 || MT == MT_HELLINGER ? v * na1 * nb.y : v, 0.0, 0.0, na0, na1, nb.x, nb.y);
+        else return finish_as<MT>(q, v * unit, 0.0, 0.0, na0, na1, nb.x, nb.y);
+    } else {
+        using O = Op<OP>;
+        return finish_as<MT>(q, O::v0(c), O::v1(c), O::v2(c), na0, na1, nb.x, nb.y);
+    }
+}
+// Calls f(MetricTag<m>) for the metric, one that these sums serve.
+template <int OP, bool FIX, typename F> __device__ __forceinline__ void for_metric_summed(int metric, F &&f) {
+    for_metric_of<OP>(metric, [&](auto tag) {
+        if constexpr (FIX == match_fixed(OP, decltype(tag)::value)) f(tag);
+    });
+}
+
 // Lane l receives lane 63 - l's value.
 __device__ __forceinline__ uint64_t wave_reverse(uint64_t v) {
     const int from = (63 - (int)__lane_id()) << 2;
@@ -166,6 +240,13 @@ __device__ __forceinline__ int wave_scan_max(int v) {
     v = max(v, dpp_or_zero<0x143, 0xc>(v));
     return v;
 }
+// h + w in one instruction, whatever the upper half of h's register holds.  (A half is a register's lower half to the compiler; a
+// 16-bit integer it would clear the upper half of first.)
+__device__ __forceinline__ uint32_t plus_half(_Float16 h, uint32_t w) {
+    uint32_t r;
+    asm("v_mad_u32_u16 %0, %1, 1, %2" : "=v"(r) : "v"(h), "s"(w));
+    return r;
+}
 // Lane I of every row of 16 lanes, in all lanes of the row (row_newbcast).
 template <int I> __device__ __forceinline__ uint32_t row_lane(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + I, 0xf, 0xf, true);
@@ -174,11 +255,11 @@ template <int I> __device__ __forceinline__ float row_lane(float v) { return __u
 
 constexpr int kMatchUnroll = 4;          // list steps whose loads are in flight together
 
-template <int OP, bool KNN>
+template <int OP, bool KNN, bool FIX>
 __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd_match_kernel(const MatchArgs args) {
     using O = Op<OP>;
-    using S = Sums<OP>;
-    using Acc = typename O::Acc;
+    using S = Sums<OP, FIX>;
+    using Acc = typename S::Acc;
     // D: 64-row pieces of a dense column that are summed in registers together; the largest tiles hold 19 for one
     // fp64 sum (one round of 19 against two of 10: 2,048 queries of 300,000 rows of 230, 10.5 -> 10.2 ms; 13 and 6
     // leave half a round idle: 11.3) and 39 for a count; a sum and a count have 13 and Minkowski's three numbers 10, in two rounds of 7
@@ -206,7 +287,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     if (group >= args.b.shape.n_tiles) return;
     const int my_tiles = (args.b.shape.n_tiles - group + args.groups - 1) / args.groups;      // group, group + groups, ...
     Acc zero;
-    O::init(zero);
+    S::init(zero);
     for (int i = lane; i <= T; i += kWave) S::put(strip_at, plane, (uint32_t)i, zero);
     if (tid == 0) s_next = 0;
     if (KNN && tid < kMatchLocks) s_lock[tid] = 0;
@@ -240,7 +321,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         return y;
     };
     // The batch's dense columns: one value per row of the tile, lane by lane, summed in registers; then the strip.
-    auto walk_dense = [&](const unsigned char *__restrict__ list, uint32_t first8, float a, uint64_t mask) {
+    auto walk_dense = [&](const unsigned char *__restrict__ values, uint32_t first4, float a, uint64_t mask, const Scale &scale) {
         const uint32_t lane4 = (uint32_t)lane * 4u;
         for (int i0 = 0; i0 < T; i0 += D * kWave) {
             typename O::Acc sum[D];
@@ -249,7 +330,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             for (int d = 0; d < D; ++d) O::init(sum[d]);
             // (past the tile's end what lies behind the column is read, or the spare entries at the end of the lists, and not added)
             auto fetch = [&](float (&into)[D], int e) {
-                const unsigned char *col = list + ((uint32_t)__builtin_amdgcn_readlane((int)first8, e) + (uint32_t)i0 * 4u);
+                const unsigned char *col = values + ((uint32_t)__builtin_amdgcn_readlane((int)first4, e) + (uint32_t)i0 * 4u);
 #pragma unroll
                 for (int d = 0; d < D; ++d) into[d] = *reinterpret_cast<const float *>(col + lane4 + d * (kWave * 4));
             };
@@ -288,7 +369,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             for (int d = 0; d < D; ++d)
                 if (i0 + d * kWave < T) {
                     Acc acc = S::get(strip_at, plane, (uint32_t)(i0 + lane + d * kWave));
-                    O::combine(acc, sum[d]);
+                    if constexpr (FIX) S::combine(acc, fixed_sum<OP>(sum[d], scale)); else S::combine(acc, sum[d]);
                     S::put(strip_at, plane, (uint32_t)(i0 + lane + d * kWave), acc);
                 }
         }
@@ -296,25 +377,29 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // The lists are cut into chunks of 16 entries, and a step is four chunks, one to a quarter of the
     // wavefront, whichever lists they belong to (a step of one list alone is filled to 62 % by 300,000 rows of 230 and to 28 %
     // by ratings; its 13 vector instructions are 8 here: 10,000 x 10,000 rows of 38, L1, 421 -> 340 us a call, 1,024 x 300,000
-    // rows of 230, cosine, 6.6 -> 5.6 ms, 1,531 x 28,301 ratings, Canberra, 1.13 -> 0.75 ms).  What bounds it now: vector
-    // loads of 8 bytes take the L1 16 clocks a step whatever they touch, and an LDS add of 64 doubles at random rows 23.
+    // rows of 230, cosine, 6.6 -> 5.6 ms, 1,531 x 28,301 ratings, Canberra, 1.13 -> 0.75 ms).  Entries of six bytes
+    // in two arrays and sums in fixed point: L1 of 10,000 x 10,000 rows of 38 355 -> 327 us, of 4,096 x 65,536 rows of 1,820 29.3 -> 25.2
+    // ms.  What bounds a step now: nine to ten vector instructions and the chunks' share of those that describe them, 9 to 11 cache
+    // lines looked up by the L1, 13 clocks of an LDS add, all of them clocks of a compute unit.
     // 64 chunks are described at a time, a chunk to a lane: lane 16 g + i
     // holds chunk 4 i + g, so that step i finds its four descriptions in lane i of each quarter (a DPP broadcast).  Chunks
     // follow one another over the steps and over the lanes of a step in the order of A's columns, and LDS serves the
     // lanes that meet in one sum in ascending order: a sum is formed in the order of A's columns here too.
     // What a walk of no more than four steps leaves behind for the k-NN's finish: the chunks it took, and the lanes' entries.
     struct Few { int total; uint32_t cell[U], left[U]; };
-    auto walk_chunks = [&](const unsigned char *__restrict__ list, uint32_t first, uint32_t last, float a, Few &few) {
+    auto walk_chunks = [&](const unsigned char *__restrict__ values, const unsigned char *__restrict__ rows, uint32_t first, uint32_t last, float a,
+                           const Scale &scale, Few &few) {
         const int chunks = (int)((last - first + 15u) >> 4);
         const int incl = wave_scan_add(chunks), excl = incl - chunks;
         const int total = __builtin_amdgcn_readlane(incl, 63);
         if (KNN) few.total += total;
         if (total == 0) return;
-        const uint32_t base8 = first * 8u - 128u * (uint32_t)excl;               // chunk q reads from byte base8 + 128 q on
-        const uint32_t last8 = last * 8u;
+        const uint32_t base4 = first * 4u - 64u * (uint32_t)excl;                // chunk q reads values from byte base4 + 64 q on
+        const uint32_t last4 = last * 4u;
         const int turned = ((lane & 15) << 2) | (lane >> 4);
-        const uint32_t lane8 = (uint32_t)(lane & 15) * 8u;
-        struct Chunk { uint32_t at, left; float a; };                            // left: bytes of its list from `at` on
+        const uint32_t lane4 = (uint32_t)(lane & 15) * 4u;
+        struct Chunk { uint32_t at, left; float a; };                            // left: bytes of its list's values from `at` on
+        struct Entry { _Float16 cell; float v; };
         // (16 bits: 64 lists of a tile are 64 * 156 chunks at most, the last group's tag is below 2^14)
         uint16_t *owner = s_owner[wave];
         owner[lane] = 0;
@@ -333,28 +418,39 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             const int from = (__builtin_amdgcn_ds_bpermute(turned << 2, e) & 63) << 2;
             const int q = q0 + turned;
             Chunk c;
-            c.at = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)base8) + 128u * (uint32_t)q;
-            c.left = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)last8) - c.at;
+            c.at = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)base4) + 64u * (uint32_t)q;
+            c.left = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)last4) - c.at;
             c.a = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(a)));
             if (q >= total) { c.at = 0u; c.left = 0u; }
             return c;
         };
-        auto fetch = [&](uint2 (&into)[U], const Chunk &c, auto block) {
+        auto fetch_one = [&](uint32_t chunk_at) {
+            const uint32_t at = chunk_at + lane4;
+            Entry x{*reinterpret_cast<const _Float16 *>(rows + (at >> 1)), 0.0f};
+            if constexpr (OP != OP_CNT) x.v = *reinterpret_cast<const float *>(values + at);
+            return x;
+        };
+        auto fetch = [&](Entry (&into)[U], const Chunk &c, auto block) {
             constexpr int I = decltype(block)::value * U;
-            into[0] = *reinterpret_cast<const uint2 *>(list + (row_lane<I>(c.at) + lane8));
-            into[1] = *reinterpret_cast<const uint2 *>(list + (row_lane<I + 1>(c.at) + lane8));
-            into[2] = *reinterpret_cast<const uint2 *>(list + (row_lane<I + 2>(c.at) + lane8));
-            into[3] = *reinterpret_cast<const uint2 *>(list + (row_lane<I + 3>(c.at) + lane8));
+            into[0] = fetch_one(row_lane<I>(c.at));
+            into[1] = fetch_one(row_lane<I + 1>(c.at));
+            into[2] = fetch_one(row_lane<I + 2>(c.at));
+            into[3] = fetch_one(row_lane<I + 3>(c.at));
         };
-        auto add_one = [&](const uint2 &from, uint32_t left, float av) {
+        auto add_one = [&](const Entry &from, uint32_t left, float av) {
             // (everything but the LDS add itself is done for all lanes: a branch around it costs more)
-            typename O::Acc t;
-            const bool counts = match_visit<OP>(t, av, __uint_as_float(from.y), args.q);
-            uint32_t offset = from.x;
-            pin(t, offset);
-            if (lane8 < left && counts) S::add(strip_at, plane, offset, t);
+            Acc t;
+            bool counts = true;
+            if constexpr (FIX) t = fixed_visit<OP>(av, from.v, scale);
+            else counts = match_visit<OP>(t, av, from.v, args.q);
+            uint32_t at;
+            if constexpr (S::kOne) at = plus_half(from.cell, strip_at); else at = __builtin_bit_cast(uint16_t, from.cell);
+            pin(t, at);
+            if (lane4 < left && counts) {
+                if constexpr (S::kOne) S::add(0u, plane, at, t); else S::add(strip_at, plane, at, t);
+            }
         };
-        auto add = [&](const uint2 (&from)[U], const Chunk &c, auto block) {
+        auto add = [&](const Entry (&from)[U], const Chunk &c, auto block) {
             constexpr int I = decltype(block)::value * U;
             add_one(from[0], row_lane<I>(c.left), row_lane<I>(c.a));
             add_one(from[1], row_lane<I + 1>(c.left), row_lane<I + 1>(c.a));
@@ -365,13 +461,13 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         constexpr std::integral_constant<int, 1> b1{};
         constexpr std::integral_constant<int, 2> b2{};
         constexpr std::integral_constant<int, 3> b3{};
-        uint2 x[U], y[U];
+        Entry x[U], y[U];
         Chunk c = describe(0);
         fetch(x, c, b0);
         if (total <= 4 * U) {                                   // a few entries: no more steps than they take
             if constexpr (KNN) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) few.cell[u] = x[u].x;
+                for (int u = 0; u < U; ++u) few.cell[u] = __builtin_bit_cast(uint16_t, x[u].cell);
                 few.left[0] = row_lane<0>(c.left);
                 few.left[1] = row_lane<1>(c.left);
                 few.left[2] = row_lane<2>(c.left);
@@ -410,26 +506,29 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             c = next;
         }
     };
-    auto walk_lists = [&](int tile, const Lists &y, Few &few) {
+    auto walk_lists = [&](int tile, const Lists &y, const Scale &scale, Few &few) {
         const int64_t tile_first = clamp_i64(args.b_indptr[(int64_t)tile * T], 0, args.b_nnz) + tile * args.b.shape.tile_extra;
-        const unsigned char *__restrict__ list = reinterpret_cast<const unsigned char *>(args.b.list + tile_first);
+        const unsigned char *__restrict__ values = reinterpret_cast<const unsigned char *>(args.b.values + tile_first);
+        const unsigned char *__restrict__ rows = reinterpret_cast<const unsigned char *>(args.b.rows + tile_first);
         const uint32_t list_n = (uint32_t)(args.b.shape.list_entries(args.b_nnz) - kMatchSpare - tile_first);     // (no access leaves the lists)
-        const float a = transform_value(args.transform, y.a);
+        float a = transform_value(args.transform, y.a);
+        if constexpr (FIX && OP == OP_DOT) a = __builtin_ldexpf(a, -scale.down);
         uint32_t first = min(y.first & ~kMatchDense, list_n);
-        const bool dense = (y.first & kMatchDense) != 0u && match_walks<OP>(a) && first + (uint32_t)(T / 2) <= list_n;
+        const bool dense = (y.first & kMatchDense) != 0u && match_walks<OP>(a) && first + (uint32_t)T <= list_n;
         const uint64_t dense_mask = __ballot(dense);
         if (dense_mask != 0) {
             if (KNN) few.total += 4 * U + 1;
-            walk_dense(list, first * 8u, a, dense_mask);
+            walk_dense(values, first * 4u, a, dense_mask, scale);
         }
         const uint32_t last = match_walks<OP>(a) && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
-        walk_chunks(list, first, last, a, few);
+        walk_chunks(values, rows, first, last, a, scale, few);
         // (a lane reads later what other lanes of its wavefront wrote: LDS serves a wavefront in order, the
         // fence keeps the compiler to that order)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
     // What finish() reads of a row of A, loaded while the row's last lists are walked.
     struct RowOf { double na0, na1; uint64_t bound; };
+    auto load_scale = [&](int row) { return FIX && OP != OP_CANB ? (int)args.scales_a[row] : 0; };
     auto load_row = [&](int row) {
         RowOf r{args.norms_a[(size_t)row * 2], args.norms_a[(size_t)row * 2 + 1], kKnnUnused};
         if constexpr (KNN) r.bound = (uint64_t)__atomic_load_n(&args.knn_tau[row], __ATOMIC_RELAXED);
@@ -443,10 +542,10 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     bool any = false;
     // The tile's distances from the wavefront's strip, in row order: one coalesced store per 64 rows; the
     // strip is clear again afterwards.  `flush`: the row's run of tiles ends here.
-    auto finish = [&](int tile, int row, const RowOf &of, const Few &few, bool flush) {
+    auto finish = [&](int tile, int row, const RowOf &of, const Scale &scale, const Few &few, bool flush) {
         const int64_t j0 = (int64_t)tile * T;
         const int tile_n = (int)min((int64_t)T, args.n - j0);
-        const double na0 = of.na0, na1 = of.na1;
+        const double na0 = of.na0, na1 = of.na1, unit = (OP == OP_L1 ? -2.0 : -1.0) * scale.unit;            // (the sum enters the distance with that factor)
         constexpr int F = 4;                                      // rows of a lane that are in flight together
         // F rows of a lane from row i0 of the tile on: their sums and norms, by constant offsets from one address each (the
         // rows beyond the tile's last repeat it), and their places cleared again.  (With an address and a bound for every row,
@@ -480,7 +579,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             for (int i0 = (tile_n + F * kWave - 1) / (F * kWave) * (F * kWave); i0 < T; i0 += F * kWave) clear_round(i0);
         };
         if constexpr (!KNN) {
-            for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
+            for_metric_summed<OP, FIX>(args.q.metric, [&](auto metric_tag) {
                 constexpr int MT = decltype(metric_tag)::value;
                 float *__restrict__ out = args.out + (size_t)row * (size_t)args.n + (size_t)j0;
                 for (int i0 = 0; i0 < tile_n; i0 += F * kWave) {
@@ -491,14 +590,14 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                     if (i0 + F * kWave <= tile_n) {
 #pragma unroll
                         for (int u = 0; u < F; ++u) {
-                            const float d = finish_as<MT>(args.q, O::v0(c[u]), O::v1(c[u]), O::v2(c[u]), na0, na1, nb[u].x, nb[u].y);
+                            const float d = distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]);
                             __builtin_nontemporal_store(d, reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
                         }
                     } else {
 #pragma unroll
                         for (int u = 0; u < F; ++u)
                             if (i0 + u * kWave + lane < tile_n)
-                                __builtin_nontemporal_store(finish_as<MT>(args.q, O::v0(c[u]), O::v1(c[u]), O::v2(c[u]), na0, na1, nb[u].x, nb[u].y),
+                                __builtin_nontemporal_store(distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]),
                                                             reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
                     }
                     clear_round(i0);
@@ -521,11 +620,11 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 queued = 0;
             };
             auto distances = [&](float (&d)[F], const Acc (&c)[F], const double2 (&nb)[F]) {
-                for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
+                for_metric_summed<OP, FIX>(args.q.metric, [&](auto metric_tag) {
                     constexpr int MT = decltype(metric_tag)::value;
 #pragma unroll
                     for (int u = 0; u < F; ++u) {
-                        d[u] = finish_as<MT>(args.q, O::v0(c[u]), O::v1(c[u]), O::v2(c[u]), na0, na1, nb[u].x, nb[u].y);
+                        d[u] = distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]);
                         if constexpr (MT == MT_INNER) d[u] = 0.0f - d[u];
                     }
                 });
@@ -536,10 +635,10 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             if constexpr (S::kOne) {
                 if (few.total <= 4 * F && args.q.metric != MT_CORRELATION) {
                     float d = 0.0f;
-                    for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
+                    for_metric_summed<OP, FIX>(args.q.metric, [&](auto metric_tag) {
                         constexpr int MT = decltype(metric_tag)::value;
-                        d = finish_as<MT>(args.q, O::v0(zero), O::v1(zero), O::v2(zero), na0, na1,
-                                          args.b.least[(size_t)tile * 2], args.b.least[(size_t)tile * 2 + 1]);
+                        d = distance_of<OP, FIX, MT>(args.q, zero, unit, na0, na1,
+                                                     make_double2(args.b.least[(size_t)tile * 2], args.b.least[(size_t)tile * 2 + 1]));
                         if constexpr (MT == MT_INNER) d = 0.0f - d;
                     });
                     few_only = d == d && knn_key(d, (int)j0) > bound;
@@ -572,7 +671,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
 #pragma unroll
                             for (int u = 0; u < F; ++u) {
                                 c[u] = zero;
-                                if (few.total > 4 * u && (uint32_t)(lane & 15) * 8u < few.left[u]) c[u] = S::take(strip_at + few.cell[u]);
+                                if (few.total > 4 * u && (uint32_t)(lane & 15) * 4u < few.left[u]) c[u] = S::take(strip_at + few.cell[u]);
                             }
 #pragma unroll
                             for (int u = 0; u < F; ++u) {
@@ -683,11 +782,12 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             const int row = wave_uniform(rw.row), len = wave_uniform(rw.len);
             const int begin = (int)((int64_t)len * wave / nw), end = (int)((int64_t)len * (wave + 1) / nw);
             Entries x = load_entries(rw.start + begin, end - begin, 0);
+            const Scale scale = scale_of<OP>(wave_uniform(load_scale(row)), len);
             Few few{};
             for (int e0 = 0; e0 < end - begin; e0 += kWave) {
                 const Lists y = load_lists(tile, x);
                 x = load_entries(rw.start + begin, end - begin, e0 + kWave);
-                walk_lists(tile, y, few);
+                walk_lists(tile, y, scale, few);
             }
             few.total = 4 * U + 1;
             __syncthreads();
@@ -696,13 +796,13 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 S::put(strips_at, plane, (uint32_t)i, zero);
 #pragma unroll
                 for (int w = 1; w < nw; ++w) {
-                    O::combine(sum, S::get(strips_at + (uint32_t)w * strip_bytes, plane, (uint32_t)i));
+                    S::combine(sum, S::get(strips_at + (uint32_t)w * strip_bytes, plane, (uint32_t)i));
                     S::put(strips_at + (uint32_t)w * strip_bytes, plane, (uint32_t)i, zero);
                 }
                 S::put(strips_at + (uint32_t)owner * strip_bytes, plane, (uint32_t)i, sum);
             }
             __syncthreads();
-            if (wave == owner) finish(tile, row, load_row(row), few, true);
+            if (wave == owner) finish(tile, row, load_row(row), scale, few, true);
             owner = owner + 1 < nw ? owner + 1 : 0;
         }
     }
@@ -713,7 +813,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // A wavefront takes a row and a run of tiles after another and goes through their batches of 64 entries as one
     // stream: while the lists of one batch are walked, the list bounds of the next one and the entries of
     // the one after that are on their way.
-    struct Place { int tile, row, len, e0, tiles; int64_t start; };       // e0: of the batch; tiles: left of the run; row < 0: there is none
+    struct Place { int tile, row, len, e0, tiles; int64_t start; int scale; };       // e0: of the batch; tiles: left of the run; row < 0: there is none
     auto claim = [&]() {
         // (the lane number is hidden from the compiler here: were `lane == 0` also to close the loop's body,
         // it would thread the two tests together and let the other lanes round the loop ahead of lane 0)
@@ -722,7 +822,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         if (claimer == 0) at = atomicAdd(&s_next, 1);
         at = wave_uniform(at);
         const int run = at / rows_here, ti = run * args.run;
-        Place p{0, -1, 0, 0, 0, 0};
+        Place p{0, -1, 0, 0, 0, 0, 0};
         if (ti < my_tiles) {
             const MatchRow rw = args.rows[args.m_shared + slice + (at - run * rows_here) * args.slices];
             p.tile = group + ti * args.groups;
@@ -730,6 +830,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             p.row = wave_uniform(rw.row);
             p.len = wave_uniform(rw.len);
             p.start = rw.start;
+            p.scale = load_scale(p.row);
         }
         return p;
     };
@@ -761,9 +862,10 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         const Lists y1 = load_lists(p1.tile, x);
         x = load_entries(p2.start, p2.len, p2.e0);
         const RowOf of = load_row(p0.row);
-        walk_lists(p0.tile, y, few);
+        const Scale scale = scale_of<OP>(wave_uniform(p0.scale), p0.len);
+        walk_lists(p0.tile, y, scale, few);
         if (p0.e0 + kWave >= p0.len) {
-            finish(p0.tile, p0.row, of, few, p0.tiles <= 1);
+            finish(p0.tile, p0.row, of, scale, few, p0.tiles <= 1);
             few.total = 0;
         } else if (KNN) {
             few.total += 4 * U + 1;                             // (the entries of several batches are not at hand together)
@@ -795,8 +897,8 @@ template <typename Kernel> static hipError_t allow_lds(Kernel kern, std::atomic<
     return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-template <int OP, bool KNN> static hipError_t launch_match_op(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
-    auto kern = spd_match_kernel<OP, KNN>;
+template <int OP, bool KNN, bool FIX> static hipError_t launch_match_op(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
+    auto kern = spd_match_kernel<OP, KNN, FIX>;
     static std::atomic<uint32_t> allowed[kMatchDevices];
     hipError_t e = allow_lds(kern, allowed, lds_bytes, (uint32_t)match_static_lds(match_cell_bytes(OP)));
     if (e != hipSuccess) return e;
@@ -804,8 +906,15 @@ template <int OP, bool KNN> static hipError_t launch_match_op(hipStream_t st, co
     hipLaunchKernelGGL(kern, dim3((unsigned)(groups * args.slices)), dim3((unsigned)(match_waves(match_cell_bytes(OP)) * kWave)), lds_bytes, st, args);
     return hipGetLastError();
 }
+template <int OP, bool FIX> static hipError_t launch_match_summed(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
+    return args.knn_k > 0 ? launch_match_op<OP, true, FIX>(st, args, lds_bytes) : launch_match_op<OP, false, FIX>(st, args, lds_bytes);
+}
 template <int OP> static hipError_t launch_match_either(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
-    return args.knn_k > 0 ? launch_match_op<OP, true>(st, args, lds_bytes) : launch_match_op<OP, false>(st, args, lds_bytes);
+    if constexpr (OP == OP_DOT) {
+        return match_fixed(OP, args.q.metric) ? launch_match_summed<OP, true>(st, args, lds_bytes) : launch_match_summed<OP, false>(st, args, lds_bytes);
+    } else {
+        return launch_match_summed<OP, match_fixed(OP, MT_COUNT)>(st, args, lds_bytes);
+    }
 }
 
 }  // namespace spd

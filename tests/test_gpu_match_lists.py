@@ -648,3 +648,54 @@ def test_an_index_without_memory_for_the_lists_keeps_the_packed_copy(scarce):
     idx, dist = ix.knn(dA, 4)
     assert np.array_equal(_np(dist), np.sort(want, axis=1)[:, :4])
     ix.close()
+
+
+@pytest.mark.parametrize("metric", ["cosine", "l2_expanded", "correlation", "hellinger", "l1", "canberra"])
+@pytest.mark.parametrize("n,long_every", [(640, 16), (130, 1)])           # lists, and columns that more than half of the rows store
+def test_sums_in_fixed_point(spd, metric, n, long_every):
+    """Rows whose values lie 2^80 apart, of one entry and of more than 4,096 that two rows share, entries 2^26 apart in a row, rows that
+    equal one another: a term is rounded to 2^-52 of the rows' largest (match_fixed in spd_match.h), so a sum of `terms` of them is
+    off by terms * 2^-52 * largest * largest at most, and a distance by that and two roundings to single precision."""
+    rng = np.random.default_rng(n)
+    cols, m = 6_000, 20
+    signed = metric in ("cosine", "l2_expanded", "correlation", "l1", "canberra")
+
+    def matrix(rows, long_rows, exponents):
+        d = np.zeros((rows, cols))
+        for r in range(rows):
+            size = 5_400 if r % long_rows == 0 else (1, 3, 40)[r % 3]
+            c = rng.choice(cols, size=size, replace=False)
+            v = rng.integers(1, 1 << 12, size=size) * 2.0 ** rng.integers(-26, 1, size=size)
+            if signed:
+                v *= rng.choice([-1.0, 1.0], size=size)
+            d[r, c] = v * 2.0 ** exponents[r % len(exponents)]
+        return d
+
+    exponents = (0, -40, 0, 40, -1) if metric != "correlation" else (0, -20, 20)
+    A, B = matrix(m, 2, exponents), matrix(n, long_every, exponents)
+    B[16 if long_every > 1 else 1] = A[0]
+    A, B = synth.from_dense(A), synth.from_dense(B)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric])
+    h = _lists(spd)
+    got = _np(h.pairwise(spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B), metric)).astype(np.float64)
+    h.close()
+
+    def rows_of(M, f):
+        return np.array([f(M["values"][M["indptr"][r]:M["indptr"][r + 1]].astype(np.float64)) for r in range(M["n_rows"])])
+
+    terms = 5_400.0
+    units = 4.0 * terms * 2.0 ** -52                       # of rows' largest entries; 4: the norms' own sums, and a scale above the largest
+    if metric == "canberra":
+        # (a ratio is formed in single precision through a reciprocal: 2^-22 of it, on no more than the shared columns)
+        bound = 2.0 ** -22 * np.abs(want) + units * 2.0
+    elif metric == "l1":
+        size = rows_of(A, lambda v: np.abs(v).sum())[:, None] + rows_of(B, lambda v: np.abs(v).sum())[None, :]
+        bound = 2.0 ** -23 * np.abs(want) + units * size
+    elif metric in ("l2_expanded", "hellinger"):
+        f = (lambda v: (v * v).sum()) if metric == "l2_expanded" else (lambda v: v.sum())
+        size = rows_of(A, f)[:, None] + rows_of(B, f)[None, :]
+        # a root of t + e: e / root(t) at most, root(e) where t is 0
+        bound = 2.0 ** -22 * np.abs(want) + np.minimum(units * size / np.maximum(want, 1e-300), np.sqrt(units * size))
+    else:
+        bound = 2.0 ** -23 * np.abs(want) + units * (cols if metric == "correlation" else 1.0)
+    assert np.all(np.abs(got - want) <= bound), float((np.abs(got - want) / bound).max())
