@@ -50,7 +50,7 @@ struct MatchB {
     uint32_t *ptr;          // n_tiles * ptr_stride: where a column's list begins, from the tile's first entry on, at
                             // column + its block's number (a block has a word more for its last list's end);
                             // kMatchDense is set where the column is dense
-    double *norms;          // n * 2, derived
+    double *norms;          // 2 * n, derived: the first ones, then the second ones
     double *least;          // n_tiles * 2: the norms of a tile's row of the least first norm (k-NN)
     int16_t *scales;        // n: the exponents of the rows whose values are listed over a power of two (match_fixed), else not used
     MatchShape shape;
@@ -63,7 +63,7 @@ struct MatchArgs {
     const float *a_values;
     const MatchRow *rows;
     int32_t m;
-    const double *norms_a;        // m * 2, derived, by row number
+    const double *norms_a;        // 2 * m, derived, likewise
     const int16_t *scales_a;      // m: exponents, see match_fixed
     const int64_t *b_indptr;
     int64_t b_nnz;

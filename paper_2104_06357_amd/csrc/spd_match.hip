@@ -48,13 +48,13 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
             scales[r] = (int16_t)e;
             // (of rows that are scaled by 2^-e, the sum of the queries' in units of 2^unit_log2)
             if (op == OP_DOT) {
-                if (metric == MT_L2 || metric == MT_HELLINGER) d1 = 1.0;
+                if (metric == MT_L2 || metric == MT_HELLINGER) d1 = 1.0;               // (B's scale is read itself)
                 if (metric == MT_CORRELATION) d0 = ldexp(d0, -(e + unit_log2));
                 d1 = ldexp(d1, e + unit_log2);
             }
         }
-        norms[(size_t)r * 2] = d0;
-        norms[(size_t)r * 2 + 1] = d1;
+        norms[r] = d0;
+        norms[n_rows + r] = d1;
     };
     // a row by all 256 lanes: its wavefronts' sums in a fixed order
     auto by_all = [&](int64_t r, int64_t begin, int64_t end) {
@@ -114,12 +114,12 @@ constexpr int kBuildLong = 64, kBuildPasses = 8;
 // (a norm that is not a number is the least: the distances turn a sum that is not a number into 0)
 __device__ __forceinline__ bool less_norm(double a, double than) { return !(a >= than) && than == than; }
 // The norms of a tile's row of the least first norm, by a whole workgroup.
-__device__ __forceinline__ void tile_least(const double *__restrict__ norms, int rows, double *__restrict__ least, double (*s_least)[2]) {
+__device__ __forceinline__ void tile_least(const double *__restrict__ norms, const double *__restrict__ second, int rows, double *__restrict__ least, double (*s_least)[2]) {
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     double d0 = __builtin_huge_val(), d1 = 0.0;
     for (int r = tid; r < rows; r += kBuildThreads) {
-        const double2 nb = *reinterpret_cast<const double2 *>(norms + (size_t)r * 2);
-        if (less_norm(nb.x, d0)) { d0 = nb.x; d1 = nb.y; }
+        const double nb = norms[r];
+        if (less_norm(nb, d0)) { d0 = nb; d1 = second[r]; }
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
@@ -167,7 +167,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     uint32_t *s_end = s_next + T;
     int16_t *s_scale = reinterpret_cast<int16_t *>(s_end + T);
     uint32_t *ptr = b.ptr + (size_t)tile * (size_t)shape.ptr_stride;
-    if (part == 0 && b.least) tile_least(b.norms + (size_t)j0 * 2, rows, b.least + (size_t)tile * 2, s_least);
+    if (part == 0 && b.least) tile_least(b.norms + j0, b.norms + n_rows + j0, rows, b.least + (size_t)tile * 2, s_least);
     const uint32_t block_first = (uint32_t)part * blocks_per_wg;
     const uint32_t block_last = min(block_first + blocks_per_wg, blocks);
     if (block_first >= block_last) return;

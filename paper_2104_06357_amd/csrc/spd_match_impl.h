@@ -171,16 +171,33 @@ template <int OP> __device__ __forceinline__ Fixed fixed_sum(const typename Op<O
 template <int OP> __device__ __forceinline__ double units_of(const Fixed &x) {
     return OP == OP_DOT ? (double)x.v : (double)(unsigned long long)(x.v & ((1ll << 62) - 1));
 }
+// What a distance reads of a row of B: nothing, the first norm, the second one (cosine: it is 0 where the first is), the first and the
+// row's scale, or both.  They lie in planes, so that a row of the tile costs 8 or 10 bytes where the two together were 16.
+enum NormsRead { READ_NONE = 0, READ_FIRST, READ_SECOND, READ_SCALE, READ_BOTH };
+SPD_HD constexpr int norms_read(int metric, bool fixed) {
+    switch (metric) {
+    case MT_INNER: case MT_KL: case MT_KL_STRICT: case MT_RUSSELL_RAO: return READ_NONE;
+    case MT_COSINE: return READ_SECOND;
+    case MT_L2: case MT_HELLINGER: return fixed ? READ_SCALE : READ_FIRST;
+    case MT_CORRELATION: case MT_MINKOWSKI: case MT_L2_UNEXPANDED: return READ_BOTH;
+    default: return READ_FIRST;
+    }
+}
+// ... `x` the first of what is read, `y` the second norm, `e` the scale.
+struct RowNorms { double x, y; int e; };
 // The distance of a pair from its sums and the rows' norms.
 template <int OP, bool FIX, int MT>
-__device__ __forceinline__ float distance_of(const OpParams &q, const typename Sums<OP, FIX>::Acc &c, double unit, double na0, double na1, const double2 &nb) {
+__device__ __forceinline__ float distance_of(const OpParams &q, const typename Sums<OP, FIX>::Acc &c, double unit, double na0, double na1, const RowNorms &b) {
+    constexpr int R = norms_read(MT, FIX);
+    const double a0 = R == READ_SECOND ? na1 : na0, b1 = R == READ_SECOND ? b.x : b.y;
     if constexpr (FIX) {
-        const double v = units_of<OP>(c);
-        if constexpr (OP == OP_DOT) return finish_as<MT>(q, MT == MT_L2 || MT == MT_HELLINGER ? v * na1 * nb.y : v, 0.0, 0.0, na0, na1, nb.x, nb.y);
-        else return finish_as<MT>(q, v * unit, 0.0, 0.0, na0, na1, nb.x, nb.y);
+        double v = units_of<OP>(c);
+        if constexpr (OP != OP_DOT) v *= unit;
+        else if constexpr (R == READ_SCALE) v = __builtin_ldexp(v * na1, b.e);
+        return finish_as<MT>(q, v, 0.0, 0.0, a0, na1, b.x, b1);
     } else {
         using O = Op<OP>;
-        return finish_as<MT>(q, O::v0(c), O::v1(c), O::v2(c), na0, na1, nb.x, nb.y);
+        return finish_as<MT>(q, O::v0(c), O::v1(c), O::v2(c), a0, na1, b.x, b1);
     }
 }
 // Calls f(MetricTag<m>) for the metric, one that these sums serve.
@@ -530,7 +547,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     struct RowOf { double na0, na1; uint64_t bound; };
     auto load_scale = [&](int row) { return FIX && OP != OP_CANB ? (int)args.scales_a[row] : 0; };
     auto load_row = [&](int row) {
-        RowOf r{args.norms_a[(size_t)row * 2], args.norms_a[(size_t)row * 2 + 1], kKnnUnused};
+        RowOf r{args.norms_a[row], args.norms_a[(size_t)args.m + (size_t)row], kKnnUnused};
         if constexpr (KNN) r.bound = (uint64_t)__atomic_load_n(&args.knn_tau[row], __ATOMIC_RELAXED);
         return r;
     };
@@ -543,6 +560,8 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // The tile's distances from the wavefront's strip, in row order: one coalesced store per 64 rows; the
     // strip is clear again afterwards.  `flush`: the row's run of tiles ends here.
     auto finish = [&](int tile, int row, const RowOf &of, const Scale &scale, const Few &few, bool flush) {
+        int lane = (int)threadIdx.x & 63;                         // (hidden from the compiler: it would keep the addresses of every loop below
+        asm volatile("" : "+v"(lane));                            // in registers through the whole kernel, 50 more than there are)
         const int64_t j0 = (int64_t)tile * T;
         const int tile_n = (int)min((int64_t)T, args.n - j0);
         const double na0 = of.na0, na1 = of.na1, unit = (OP == OP_L1 ? -2.0 : -1.0) * scale.unit;            // (the sum enters the distance with that factor)
@@ -550,22 +569,37 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         // F rows of a lane from row i0 of the tile on: their sums and norms, by constant offsets from one address each (the
         // rows beyond the tile's last repeat it), and their places cleared again.  (With an address and a bound for every row,
         // 25 vector instructions per 64 rows, a call on 10,000 x 10,000 rows of 38 spent more on this than on the lists.)
-        const unsigned char *const norm_at = reinterpret_cast<const unsigned char *>(args.b.norms + (size_t)j0 * 2);
-        const uint32_t lane4 = (uint32_t)lane * 4u, lane16 = (uint32_t)lane * 16u;
-        auto load_round = [&](int i0, Acc (&c)[F], double2 (&nb)[F]) {
-            if (i0 + F * kWave <= tile_n) {
-                const unsigned char *from = norm_at + (uint32_t)i0 * 16u;
+        const uint32_t lane4 = (uint32_t)lane * 4u;
+        auto load_norms = [&](int reads, int i0, RowNorms (&nb)[F]) {
+            if (reads == READ_NONE) return;
+            const unsigned char *const first_at = reinterpret_cast<const unsigned char *>(args.b.norms + (reads == READ_SECOND ? args.n : 0) + j0);
+            const unsigned char *const second_at = reinterpret_cast<const unsigned char *>(args.b.norms + args.n + j0);
+            const unsigned char *const scale_at = reinterpret_cast<const unsigned char *>(args.b.scales + j0);
+            auto load = [&](auto at) {
 #pragma unroll
-                for (int u = 0; u < F; ++u) nb[u] = *reinterpret_cast<const double2 *>(from + lane16 + u * (kWave * 16));
+                for (int u = 0; u < F; ++u) nb[u].x = *reinterpret_cast<const double *>(first_at + at(u, 8u));
+                if (reads == READ_SCALE) {
+#pragma unroll
+                    for (int u = 0; u < F; ++u) nb[u].e = *reinterpret_cast<const int16_t *>(scale_at + at(u, 2u));
+                }
+                if (reads == READ_BOTH) {
+#pragma unroll
+                    for (int u = 0; u < F; ++u) nb[u].y = *reinterpret_cast<const double *>(second_at + at(u, 8u));
+                }
+            };
+            if (i0 + F * kWave <= tile_n) {
+                load([&](int u, uint32_t size) { return (uint32_t)(i0 + lane) * size + (uint32_t)(u * kWave) * size; });
+            } else {
+                load([&](int u, uint32_t size) { return (uint32_t)min(i0 + u * kWave + lane, tile_n - 1) * size; });
+            }
+        };
+        auto load_sums = [&](int i0, Acc (&c)[F]) {
+            if (i0 + F * kWave <= tile_n) {
 #pragma unroll
                 for (int u = 0; u < F; ++u) c[u] = S::get(strip_at, plane, (uint32_t)(i0 + lane + u * kWave));
             } else {
 #pragma unroll
-                for (int u = 0; u < F; ++u) {
-                    const int i = min(i0 + u * kWave + lane, tile_n - 1);
-                    nb[u] = *reinterpret_cast<const double2 *>(norm_at + (uint32_t)i * 16u);
-                    c[u] = S::get(strip_at, plane, (uint32_t)i);
-                }
+                for (int u = 0; u < F; ++u) c[u] = S::get(strip_at, plane, (uint32_t)min(i0 + u * kWave + lane, tile_n - 1));
             }
         };
         auto clear_round = [&](int i0) {
@@ -581,30 +615,50 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         if constexpr (!KNN) {
             for_metric_summed<OP, FIX>(args.q.metric, [&](auto metric_tag) {
                 constexpr int MT = decltype(metric_tag)::value;
+                constexpr int R = norms_read(MT, FIX);
                 float *__restrict__ out = args.out + (size_t)row * (size_t)args.n + (size_t)j0;
-                for (int i0 = 0; i0 < tile_n; i0 += F * kWave) {
+                // A round's norms are loaded before the round ahead stores its distances: what is loaded after a store is at hand only when the
+                // store has reached memory (10,000 x 10,000 rows of 38 with that wait in every round, L1 327 us a call, cosine 356; 316
+                // and 327 now).  The first of the whole rounds stands before the loop, so that every turn of the loop has the same loads
+                // and stores in flight.
+                const int whole = tile_n / (F * kWave) * (F * kWave);
+                RowNorms nb[F], ahead[F];
+                auto round = [&](int i0, int next) {
                     Acc c[F];
-                    double2 nb[F];
-                    load_round(i0, c, nb);
+                    load_sums(i0, c);
+                    load_norms(R, next, ahead);
+                    __builtin_amdgcn_sched_barrier(0);
                     unsigned char *to = reinterpret_cast<unsigned char *>(out + i0);
-                    if (i0 + F * kWave <= tile_n) {
 #pragma unroll
-                        for (int u = 0; u < F; ++u) {
-                            const float d = distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]);
-                            __builtin_nontemporal_store(d, reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
-                        }
-                    } else {
-#pragma unroll
-                        for (int u = 0; u < F; ++u)
-                            if (i0 + u * kWave + lane < tile_n)
-                                __builtin_nontemporal_store(distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]),
-                                                            reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
-                    }
+                    for (int u = 0; u < F; ++u)
+                        __builtin_nontemporal_store(distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]),
+                                                    reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
                     clear_round(i0);
+#pragma unroll
+                    for (int u = 0; u < F; ++u) nb[u] = ahead[u];
+                };
+                load_norms(R, 0, nb);
+                if (whole > 0) {
+                    round(0, F * kWave < tile_n ? F * kWave : 0);
+#pragma unroll 1
+                    for (int i0 = F * kWave; i0 < whole; i0 += F * kWave) round(i0, i0 + F * kWave < tile_n ? i0 + F * kWave : i0);
+                }
+                if (whole < tile_n) {
+                    Acc c[F];
+                    load_sums(whole, c);
+                    unsigned char *to = reinterpret_cast<unsigned char *>(out + whole);
+#pragma unroll
+                    for (int u = 0; u < F; ++u)
+                        if (whole + u * kWave + lane < tile_n)
+                            __builtin_nontemporal_store(distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]),
+                                                        reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
+                    clear_round(whole);
                 }
             });
             clear_behind();
         } else {
+          for_metric_summed<OP, FIX>(args.q.metric, [&](auto of_metric) {
+            constexpr int MT = decltype(of_metric)::value, reads = norms_read(MT, FIX);
             const int k = args.knn_k;
             auto kth_of = [&](uint64_t sorted, int at) {
                 return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(sorted >> 32), at) << 32) |
@@ -619,28 +673,22 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 bound = now < bound ? now : bound;
                 queued = 0;
             };
-            auto distances = [&](float (&d)[F], const Acc (&c)[F], const double2 (&nb)[F]) {
-                for_metric_summed<OP, FIX>(args.q.metric, [&](auto metric_tag) {
-                    constexpr int MT = decltype(metric_tag)::value;
+            auto distances = [&](float (&d)[F], const Acc (&c)[F], const RowNorms (&nb)[F]) {
 #pragma unroll
-                    for (int u = 0; u < F; ++u) {
-                        d[u] = distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]);
-                        if constexpr (MT == MT_INNER) d[u] = 0.0f - d[u];
-                    }
-                });
+                for (int u = 0; u < F; ++u) {
+                    d[u] = distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]);
+                    if constexpr (MT == MT_INNER) d[u] = 0.0f - d[u];
+                }
             };
             // Whether a row that shares no column could pass: the distances of one sum grow with the row's first norm, so none is
             // nearer than the tile's row of the least.  (Correlation's do not.)
             bool few_only = false;
             if constexpr (S::kOne) {
-                if (few.total <= 4 * F && args.q.metric != MT_CORRELATION) {
-                    float d = 0.0f;
-                    for_metric_summed<OP, FIX>(args.q.metric, [&](auto metric_tag) {
-                        constexpr int MT = decltype(metric_tag)::value;
-                        d = distance_of<OP, FIX, MT>(args.q, zero, unit, na0, na1,
-                                                     make_double2(args.b.least[(size_t)tile * 2], args.b.least[(size_t)tile * 2 + 1]));
-                        if constexpr (MT == MT_INNER) d = 0.0f - d;
-                    });
+                if (few.total <= 4 * F && MT != MT_CORRELATION) {
+                    float d = distance_of<OP, FIX, MT>(args.q, zero, unit, na0, na1,
+                                                       RowNorms{args.b.least[(size_t)tile * 2 + (reads == READ_SECOND ? 1 : 0)],
+                                                                args.b.least[(size_t)tile * 2 + 1], 0});
+                    if constexpr (MT == MT_INNER) d = 0.0f - d;
                     few_only = d == d && knn_key(d, (int)j0) > bound;
                 }
             }
@@ -663,7 +711,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                     }
                 } else {
                     Acc c[F];
-                    double2 nb[F];
+                    RowNorms nb[F];
                     if (S::kOne && few_only) {
                         // A few entries met the row: one lane of those that met a sum takes it and leaves its place clear
                         if constexpr (S::kOne) {
@@ -676,14 +724,20 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
 #pragma unroll
                             for (int u = 0; u < F; ++u) {
                                 i[u] = S::is_zero(c[u]) ? tile_n : (int)(few.cell[u] / S::kUnit);
-                                nb[u] = make_double2(0.0, 0.0);
-                                if (few.total > 4 * u) nb[u] = *reinterpret_cast<const double2 *>(args.b.norms + (size_t)(j0 + min(i[u], tile_n - 1)) * 2);
+                                nb[u] = RowNorms{0.0, 0.0, 0};
+                                if (few.total > 4 * u) {
+                                    const int64_t j = j0 + min(i[u], tile_n - 1);
+                                    if (reads != READ_NONE) nb[u].x = args.b.norms[(reads == READ_SECOND ? args.n : 0) + j];
+                                    if (reads == READ_SCALE) nb[u].e = args.b.scales[j];
+                                    if (reads == READ_BOTH) nb[u].y = args.b.norms[args.n + j];
+                                }
                             }
                         }
                     } else {
 #pragma unroll
                         for (int u = 0; u < F; ++u) i[u] = i0 + u * kWave + lane;
-                        load_round(i0, c, nb);
+                        load_sums(i0, c);
+                        load_norms(reads, i0, nb);
                     }
                     distances(d, c, nb);
 #pragma unroll
@@ -768,6 +822,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 queued = 0;
                 any = false;
             }
+          });
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
