@@ -109,7 +109,7 @@ constexpr int kBuildThreads = 1024;
 // Rows of a tile whose stretch of a block is longer than kBuildPasses loads of their lanes are left to whole wavefronts, as many of
 // them as fit the list (500,000 rows of 1 to 50,000 entries over 242,000 columns: four lanes went 160 times through
 // memory for one row while the workgroup waited: 7.6 ms for all lists, and 2.6 with whole wavefronts).
-constexpr int kBuildLong = 64, kBuildPasses = 8;
+constexpr int kBuildLong = 64, kBuildPasses = 8, kBuildAhead = 2;
 
 // (a norm that is not a number is the least: the distances turn a sum that is not a number into 0)
 __device__ __forceinline__ bool less_norm(double a, double than) { return !(a >= than) && than == than; }
@@ -149,15 +149,22 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     const uint32_t cols = b.cols ? min(*b.cols, most_cols) : most_cols;
     const uint32_t block_cols = 1u << shape.block_shift, blocks = min((uint32_t)shape.blocks, (cols + block_cols - 1u) >> shape.block_shift);
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int nw = kBuildThreads / kWave, groups = kBuildThreads / G, kRows = 4;
+    constexpr int nw = kBuildThreads / kWave, groups = kBuildThreads / G, kRows = 4, kAhead = kBuildAhead;
     const int sub = tid % G, group = tid / G, group_shift = lane / G * G;
     constexpr uint64_t group_mask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull);
     const int T = shape.tile_rows;
-    const int tile = (int)(blockIdx.x / wgs), part = (int)(blockIdx.x % wgs);
+    // Workgroups go round the eight XCDs in turn: an XCD takes an eighth of the (tile, part)s that follow one another, so that the
+    // lines which two blocks of a row share come from its L2 (300,000 rows of 230 entries: misses 40 -> 21 million; what is left is the
+    // latency of the phases between the barriers, one workgroup to a compute unit: with two of half the LDS and twice the blocks
+    // 1,042 -> 1,367 us).
+    const uint32_t of_xcd = (gridDim.x + 7u) >> 3, at_wg = (blockIdx.x & 7u) * of_xcd + (blockIdx.x >> 3);
+    const int tile = (int)(at_wg / wgs), part = (int)(at_wg % wgs);
+    if (tile >= shape.n_tiles) return;
     const int64_t j0 = (int64_t)tile * T;
     const int rows = (int)min((int64_t)T, n_rows - j0);
     const int64_t row_first = clamp_i64(indptr[j0], 0, nnz);             // of the rows' entries
     const int64_t first = row_first + tile * shape.tile_extra;            // of the tile's lists
+    const int32_t *const tile_indices = indices + row_first;
     const int64_t list_end = shape.list_entries(nnz) - kMatchSpare;
     float *s_value = reinterpret_cast<float *>(s_raw);                              // stage entries, a multiple of 8
     uint16_t *s_row = reinterpret_cast<uint16_t *>(s_value + shape.stage);
@@ -174,14 +181,31 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     uint32_t base = 0u;                               // entries of the columns before the block
     {
         const uint32_t c_first = block_first * block_cols;
+        const float share = (float)c_first / (float)cols;
         uint32_t mine = 0u;
         for (int r = tid; r < rows; r += kBuildThreads) {
             const uint32_t begin = (uint32_t)(clamp_i64(indptr[j0 + r], row_first, nnz) - row_first);
             const uint32_t end = max(begin, (uint32_t)(clamp_i64(indptr[j0 + r + 1], row_first, nnz) - row_first));
+            // where the row's entries of the blocks from c_first on begin: searched outwards from where they would in a row of uniform columns,
+            // mostly within the lines that are read next anyway (eight probes of a bisection were 3 of the 5 GB
+            // that 300,000 rows of 230 entries over 13 blocks read)
             uint32_t lo = begin, hi = c_first == 0u ? begin : end;
+            auto before = [&](uint32_t e) { return (uint32_t)tile_indices[e] < c_first; };
+            if (lo < hi) {
+                uint32_t at = lo + min((uint32_t)((float)(hi - lo) * share), hi - lo - 1u), step = 8u;
+                if (before(at)) {
+                    lo = at + 1u;
+                    while (lo < hi && hi - lo > step && before(lo + step)) { lo += step + 1u; step *= 2u; }
+                    hi = min(hi, lo + step);
+                } else {
+                    hi = at;
+                    while (hi - lo > step && !before(hi - step)) { hi -= step; step *= 2u; }
+                    lo = hi - lo > step ? hi - step : lo;
+                }
+            }
             while (lo < hi) {
                 const uint32_t mid = (lo + hi) >> 1;
-                if ((uint32_t)indices[row_first + mid] < c_first) lo = mid + 1; else hi = mid;
+                if (before(mid)) lo = mid + 1; else hi = mid;
             }
             s_cur[r] = lo;
             s_end[r] = end;
@@ -201,25 +225,35 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         for (uint32_t i = tid; i < block_cols; i += kBuildThreads) s_count[i] = 0u;
         if (tid == 0) s_longs = 0u;
         __syncthreads();
-        // count: G lanes to the row, four rows' first loads in flight together
+        // count: G lanes to the row, the first kAhead loads of four rows in flight together (one load ahead 1,213 us for 300,000 rows of
+        // 230 entries, two 1,085, four 1,176; 242,000 columns of sets 1,836, 1,627 and 1,583)
         for (int r0 = group; r0 < rows; r0 += kRows * groups) {
-            uint32_t pos[kRows], end[kRows], c[kRows];
+            uint32_t pos[kRows], end[kRows], c[kRows][kAhead];
+            auto load = [&](int u) {
+#pragma unroll
+                for (int x = 0; x < kAhead; ++x)
+                    c[u][x] = pos[u] + (uint32_t)(x * G + sub) < end[u] ? (uint32_t)indices[row_first + pos[u] + (uint32_t)(x * G + sub)] : 0xFFFFFFFFu;
+            };
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 const int r = r0 + u * groups;
                 pos[u] = r < rows ? s_cur[r] : 0u;
                 end[u] = r < rows ? s_end[r] : 0u;
-                c[u] = pos[u] + sub < end[u] ? (uint32_t)indices[row_first + pos[u] + sub] : 0xFFFFFFFFu;
+                load(u);
             }
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 const int r = r0 + u * groups;
-                for (int pass = 1;; ++pass) {
-                    const bool in = c[u] - c0 < range;
-                    if (in) atomicAdd(&s_count[c[u] - c0], 1u);
-                    const uint32_t n = (uint32_t)__popcll((__ballot(in) >> group_shift) & group_mask);
+                for (int pass = kAhead;; pass += kAhead) {
+                    uint32_t n = 0u;
+#pragma unroll
+                    for (int x = 0; x < kAhead; ++x) {
+                        const bool in = c[u][x] - c0 < range;
+                        if (in) atomicAdd(&s_count[c[u][x] - c0], 1u);
+                        n += (uint32_t)__popcll((__ballot(in) >> group_shift) & group_mask);
+                    }
                     pos[u] += n;
-                    if (n < (uint32_t)G) break;
+                    if (n < (uint32_t)(G * kAhead)) break;
                     if (pass >= kBuildPasses) {
                         uint32_t at = (uint32_t)kBuildLong;
                         if (sub == 0) at = atomicAdd(&s_longs, 1u);
@@ -230,7 +264,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
                         }
                         pass = -0x40000000;                      // (no place left: these lanes go on)
                     }
-                    c[u] = pos[u] + sub < end[u] ? (uint32_t)indices[row_first + pos[u] + sub] : 0xFFFFFFFFu;
+                    load(u);
                 }
                 if (r < rows && sub == 0) s_next[r] = pos[u];
             }
@@ -349,8 +383,16 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         };
         constexpr uint32_t kShort = (uint32_t)(G * kBuildPasses);         // a stretch beyond it may be a whole wavefront's
         for (int r0 = group; r0 < rows; r0 += kRows * groups) {
-            uint32_t pos[kRows], end[kRows], c[kRows];
-            float v[kRows];
+            uint32_t pos[kRows], end[kRows], c[kRows][kAhead];
+            float v[kRows][kAhead];
+            auto load = [&](int u) {
+#pragma unroll
+                for (int x = 0; x < kAhead; ++x) {
+                    const uint32_t e = pos[u] + (uint32_t)(x * G);
+                    c[u][x] = e < end[u] ? (uint32_t)indices[row_first + e] : 0xFFFFFFFFu;
+                    v[u][x] = e < end[u] ? values[row_first + e] : 0.0f;
+                }
+            };
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 const int r = r0 + u * groups;
@@ -359,16 +401,16 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
                 if (longs > 0 && end[u] - pos[u] >= kShort)
                     for (int at = 0; at < longs; ++at) end[u] = s_long[at] == (uint32_t)r ? pos[u] : end[u];
                 pos[u] += sub;
-                c[u] = pos[u] < end[u] ? (uint32_t)indices[row_first + pos[u]] : 0xFFFFFFFFu;
-                v[u] = pos[u] < end[u] ? values[row_first + pos[u]] : 0.0f;
+                load(u);
             }
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 const int r = r0 + u * groups;
                 while (pos[u] < end[u]) {
-                    place(c[u], v[u], r);
-                    pos[u] += G;
-                    if (pos[u] < end[u]) { c[u] = (uint32_t)indices[row_first + pos[u]]; v[u] = values[row_first + pos[u]]; }
+#pragma unroll
+                    for (int x = 0; x < kAhead; ++x) place(c[u][x], v[u][x], r);
+                    pos[u] += (uint32_t)(G * kAhead);
+                    if (pos[u] < end[u]) load(u);
                 }
             }
         }
@@ -519,10 +561,13 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
         static std::atomic<uint32_t> allowed[kMatchDevices];
         hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(kern, dim3((unsigned)s.n_tiles * wgs), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
+        hipLaunchKernelGGL(kern, dim3(((unsigned)s.n_tiles * wgs + 7u) / 8u * 8u), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
                            nnz, k, b, per_wg, wgs, match_cell_bytes(op) >= 8 ? 8 : 4, transform, op == OP_DOT && match_fixed(op, metric), op != OP_CNT);
         return hipGetLastError();
     };
+    // (a row's stretch in the two loads of its lanes, where that leaves no more than half of them idle: rows of 1,820 over 51 blocks 1,078 us
+    // with 16 lanes, 954 with 32; rows of 230 over 13 blocks 1,042 with 16, 1,378 with 32, 1,123 with 8)
+    if (per_row >= 24.0) return go(std::integral_constant<int, 32>{});
     if (per_row >= 8.0) return go(std::integral_constant<int, 16>{});
     return per_row >= 3.0 ? go(std::integral_constant<int, 8>{}) : go(std::integral_constant<int, 4>{});
 }
