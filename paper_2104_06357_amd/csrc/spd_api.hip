@@ -544,7 +544,7 @@ MatchB match_b_at(const MatchShape &s, const MatchLayout &L, unsigned char *dev)
 // eight XCDs, and the workgroups of an XCD go through its tiles together; smaller lists are in every L2
 // anyway, and each tile is a group.  Rows of A that hold more than a third of a wavefront's share of
 // the entries are shared by the wavefronts of a workgroup.
-struct MatchGrid { int slices = 1, groups = 1, by_xcd = 0, run = 1; int64_t shared_len = 0; };
+struct MatchGrid { int slices = 1, groups = 1, by_xcd = 0, run = 1; int64_t share = 0, shared_len = 0; };         // share: of A's entries, a wavefront's
 MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int64_t m, int64_t nnz_a, int64_t nnz_b, bool knn) {
     MatchGrid g;
     const int64_t cus = std::max(1, opt.n_cus), rows_slices = std::max<int64_t>(1, (m + s.waves - 1) / s.waves);
@@ -559,8 +559,8 @@ MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int64_t m, int
         g.slices = (int)std::max<int64_t>(1, std::min(rows_slices, cus / g.groups));
     }
     const int64_t tiles = (s.n_tiles + g.groups - 1) / g.groups;
-    const int64_t share = nnz_a * tiles / ((int64_t)g.slices * s.waves);
-    g.shared_len = std::max<int64_t>(256, share / 3);
+    g.share = nnz_a * tiles / ((int64_t)g.slices * s.waves);
+    g.shared_len = std::max<int64_t>(256, g.share / 3);
     // A wavefront goes through a run of tiles with a row: as many as leave every wavefront four rows' runs, and whose lists
     // (and bounds) together lie in half of an L2.  What a row costs besides its lists is then paid once a run, and with
     // k-NN its nearest are merged into the row's list once a run.
@@ -778,6 +778,11 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
     w.columns = w.way == 2 ? columns_of(A) : A->n_cols;
     w.s = match_shape(h->opt.lds_budget, op, B->n_rows, w.columns, B->nnz);
     w.g = match_grid(h->opt, w.s, A->n_rows, A->nnz, B->nnz, knn);
+    // Where the wavefronts that share a row add to one strip, the row costs one wait: it pays from half that length on, and pairwise,
+    // where they form its distances together too, short rows are as well with a wavefront each.  (A third / a sixth / a twelfth of
+    // the share, us: sets, Jaccard, k-NN 8,816 / 8,489 / 8,785, words, cosine 5,368 / 5,435 / 6,737; from 128 / 256 / 512 entries on: 10,000 x
+    // 10,000 rows of 38, L1 297 / 298 / 288, cosine, k-NN 504 / 507 / 534.)
+    if (match_any_order(op)) w.g.shared_len = std::max<int64_t>(knn ? 256 : 512, w.g.share / 6);
     w.L = layout_match_call(w.s, w.g, A->n_rows, A->nnz, B->n_rows, B->nnz, knn_k, w.way == 2 || !with_index, w.way == 2 ? A->n_cols : 0);
     return w;
 }

@@ -125,6 +125,8 @@ SPD_HD constexpr bool match_fixed(int op, int metric) {
     return op == OP_L1 || op == OP_CANB ||
            (op == OP_DOT && (metric == MT_COSINE || metric == MT_L2 || metric == MT_CORRELATION || metric == MT_HELLINGER));
 }
+// ... and the products whose sums are integers, but for inner products.
+SPD_HD constexpr bool match_any_order(int op) { return op == OP_L1 || op == OP_CANB || op == OP_DOT || op == OP_HAMM || op == OP_CNT; }
 // floor(log2 v), -1023 for 0, 1,024 for what is not finite.
 SPD_HD int match_ilog2(double v) {
     uint64_t w;

@@ -29,6 +29,7 @@ template <int OP, bool FIX> struct Sums {
     }
     static constexpr int kDoubles = match_doubles(OP), kCounts = match_counts(OP);
     static constexpr bool kOne = kDoubles + kCounts == 1;
+    static constexpr bool kAnyOrder = FIX || kDoubles == 0;       // integers: their sums come out the same in any order
     static constexpr uint32_t kUnit = kDoubles ? 8u : 4u;          // bytes from a row's first number to the next row's
     static __device__ __forceinline__ Acc get(uint32_t at, uint32_t plane, uint32_t row) {
         Acc x;
@@ -60,20 +61,20 @@ template <int OP, bool FIX> struct Sums {
     // Adds to the sums of the row whose first number lies `offset` bytes into the strip.
     static __device__ __forceinline__ void add(uint32_t at, uint32_t plane, uint32_t offset, const Acc &x) {
         if constexpr (FIX) {
-            __hip_atomic_fetch_add(lds_at<unsigned long long>(at + offset), (unsigned long long)x.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            __hip_atomic_fetch_add(lds_at<unsigned long long>(at + offset), (unsigned long long)x.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             return;
         }
 #pragma unroll
         for (int p = 0; p < kDoubles; ++p) {
             double v;
             __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * p, 8);
-            __hip_atomic_fetch_add(lds_at<double>(at + (uint32_t)p * plane + offset), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            __hip_atomic_fetch_add(lds_at<double>(at + (uint32_t)p * plane + offset), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
         if constexpr (kCounts) {
             int v;
             __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * kDoubles, 4);
             __hip_atomic_fetch_add(lds_at<int>(at + (uint32_t)kDoubles * plane + (kDoubles ? offset >> 1 : offset)), v, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WAVEFRONT);
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
     // A strip of one number: the row's, which becomes zero bits (what init() makes).
@@ -338,7 +339,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         return y;
     };
     // The batch's dense columns: one value per row of the tile, lane by lane, summed in registers; then the strip.
-    auto walk_dense = [&](const unsigned char *__restrict__ values, uint32_t first4, float a, uint64_t mask, const Scale &scale) {
+    auto walk_dense = [&](const unsigned char *__restrict__ values, uint32_t first4, float a, uint64_t mask, const Scale &scale, uint32_t to) {
         const uint32_t lane4 = (uint32_t)lane * 4u;
         for (int i0 = 0; i0 < T; i0 += D * kWave) {
             typename O::Acc sum[D];
@@ -385,9 +386,16 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
 #pragma unroll
             for (int d = 0; d < D; ++d)
                 if (i0 + d * kWave < T) {
-                    Acc acc = S::get(strip_at, plane, (uint32_t)(i0 + lane + d * kWave));
-                    if constexpr (FIX) S::combine(acc, fixed_sum<OP>(sum[d], scale)); else S::combine(acc, sum[d]);
-                    S::put(strip_at, plane, (uint32_t)(i0 + lane + d * kWave), acc);
+                    const uint32_t i = (uint32_t)(i0 + lane + d * kWave);
+                    if constexpr (FIX) {
+                        S::add(to, plane, i * S::kUnit, fixed_sum<OP>(sum[d], scale));
+                    } else if constexpr (S::kAnyOrder) {
+                        S::add(to, plane, i * S::kUnit, sum[d]);
+                    } else {
+                        Acc acc = S::get(to, plane, i);
+                        S::combine(acc, sum[d]);
+                        S::put(to, plane, i, acc);
+                    }
                 }
         }
     };
@@ -405,7 +413,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // What a walk of no more than four steps leaves behind for the k-NN's finish: the chunks it took, and the lanes' entries.
     struct Few { int total; uint32_t cell[U], left[U]; };
     auto walk_chunks = [&](const unsigned char *__restrict__ values, const unsigned char *__restrict__ rows, uint32_t first, uint32_t last, float a,
-                           const Scale &scale, Few &few) {
+                           const Scale &scale, uint32_t to, Few &few) {
         const int chunks = (int)((last - first + 15u) >> 4);
         const int incl = wave_scan_add(chunks), excl = incl - chunks;
         const int total = __builtin_amdgcn_readlane(incl, 63);
@@ -461,10 +469,10 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             if constexpr (FIX) t = fixed_visit<OP>(av, from.v, scale);
             else counts = match_visit<OP>(t, av, from.v, args.q);
             uint32_t at;
-            if constexpr (S::kOne) at = plus_half(from.cell, strip_at); else at = __builtin_bit_cast(uint16_t, from.cell);
+            if constexpr (S::kOne) at = plus_half(from.cell, to); else at = __builtin_bit_cast(uint16_t, from.cell);
             pin(t, at);
             if (lane4 < left && counts) {
-                if constexpr (S::kOne) S::add(0u, plane, at, t); else S::add(strip_at, plane, at, t);
+                if constexpr (S::kOne) S::add(0u, plane, at, t); else S::add(to, plane, at, t);
             }
         };
         auto add = [&](const Entry (&from)[U], const Chunk &c, auto block) {
@@ -523,7 +531,8 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             c = next;
         }
     };
-    auto walk_lists = [&](int tile, const Lists &y, const Scale &scale, Few &few) {
+    // (`to`: the strip)
+    auto walk_lists = [&](int tile, const Lists &y, const Scale &scale, uint32_t to, Few &few) {
         const int64_t tile_first = clamp_i64(args.b_indptr[(int64_t)tile * T], 0, args.b_nnz) + tile * args.b.shape.tile_extra;
         const unsigned char *__restrict__ values = reinterpret_cast<const unsigned char *>(args.b.values + tile_first);
         const unsigned char *__restrict__ rows = reinterpret_cast<const unsigned char *>(args.b.rows + tile_first);
@@ -535,10 +544,10 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         const uint64_t dense_mask = __ballot(dense);
         if (dense_mask != 0) {
             if (KNN) few.total += 4 * U + 1;
-            walk_dense(values, first * 4u, a, dense_mask, scale);
+            walk_dense(values, first * 4u, a, dense_mask, scale, to);
         }
         const uint32_t last = match_walks<OP>(a) && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
-        walk_chunks(values, rows, first, last, a, scale, few);
+        walk_chunks(values, rows, first, last, a, scale, to, few);
         // (a lane reads later what other lanes of its wavefront wrote: LDS serves a wavefront in order, the
         // fence keeps the compiler to that order)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -827,40 +836,68 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
 
-    // ---- the longest rows: an even share of the row to each wavefront, the strips summed in a fixed order --
+    // ---- the longest rows: an even share of the row to each wavefront ---------------------------------
     // (a wavefront alone would hold its workgroup up long after the others are done)
+    int owner = 0;
     for (int ti = 0; ti < my_tiles; ++ti) {
         const int tile = group + ti * args.groups;
-        int owner = 0;
         for (int at = slice; at < args.m_shared; at += args.slices) {
             const MatchRow rw = args.rows[at];
             const int row = wave_uniform(rw.row), len = wave_uniform(rw.len);
             const int begin = (int)((int64_t)len * wave / nw), end = (int)((int64_t)len * (wave + 1) / nw);
             Entries x = load_entries(rw.start + begin, end - begin, 0);
             const Scale scale = scale_of<OP>(wave_uniform(load_scale(row)), len);
+            // Sums that come out the same in any order go to one strip, the next row's to the next one: one wait a row.  Others are
+            // formed strip by strip and the strips summed in a fixed order.
+            const uint32_t owners_at = (uint32_t)wave_uniform((int)(strips_at + (uint32_t)owner * strip_bytes));
             Few few{};
             for (int e0 = 0; e0 < end - begin; e0 += kWave) {
                 const Lists y = load_lists(tile, x);
                 x = load_entries(rw.start + begin, end - begin, e0 + kWave);
-                walk_lists(tile, y, scale, few);
+                walk_lists(tile, y, scale, S::kAnyOrder ? owners_at : strip_at, few);
             }
             few.total = 4 * U + 1;
             __syncthreads();
-            for (int i = tid; i < T; i += nw * kWave) {
-                Acc sum = S::get(strips_at, plane, (uint32_t)i);
-                S::put(strips_at, plane, (uint32_t)i, zero);
+            if constexpr (!S::kAnyOrder) {
+                for (int i = tid; i < T; i += nw * kWave) {
+                    Acc sum = S::get(strips_at, plane, (uint32_t)i);
+                    S::put(strips_at, plane, (uint32_t)i, zero);
 #pragma unroll
-                for (int w = 1; w < nw; ++w) {
-                    S::combine(sum, S::get(strips_at + (uint32_t)w * strip_bytes, plane, (uint32_t)i));
-                    S::put(strips_at + (uint32_t)w * strip_bytes, plane, (uint32_t)i, zero);
+                    for (int w = 1; w < nw; ++w) {
+                        S::combine(sum, S::get(strips_at + (uint32_t)w * strip_bytes, plane, (uint32_t)i));
+                        S::put(strips_at + (uint32_t)w * strip_bytes, plane, (uint32_t)i, zero);
+                    }
+                    S::put(owners_at, plane, (uint32_t)i, sum);
                 }
-                S::put(strips_at + (uint32_t)owner * strip_bytes, plane, (uint32_t)i, sum);
+                __syncthreads();
             }
-            __syncthreads();
-            if (wave == owner) finish(tile, row, load_row(row), scale, few, true);
+            if constexpr (S::kAnyOrder && !KNN) {
+                // (the distances by all wavefronts: by one they held the next row up; 10,000 x 10,000 rows of 38, L1, with the one strip 313 -> 298 us a call)
+                const RowOf of = load_row(row);
+                const int64_t j0 = (int64_t)tile * T;
+                const int tile_n = (int)min((int64_t)T, args.n - j0);
+                const double unit = (OP == OP_L1 ? -2.0 : -1.0) * scale.unit;
+                for_metric_summed<OP, FIX>(args.q.metric, [&](auto metric_tag) {
+                    constexpr int MT = decltype(metric_tag)::value, R = norms_read(MT, FIX);
+                    float *__restrict__ out = args.out + (size_t)row * (size_t)args.n + (size_t)j0;
+                    for (int i = tid; i < T; i += nw * kWave) {
+                        if (i < tile_n) {
+                            RowNorms nb{0.0, 0.0, 0};
+                            if (R != READ_NONE) nb.x = args.b.norms[(R == READ_SECOND ? args.n : 0) + j0 + i];
+                            if (R == READ_SCALE) nb.e = args.b.scales[j0 + i];
+                            if (R == READ_BOTH) nb.y = args.b.norms[args.n + j0 + i];
+                            __builtin_nontemporal_store(distance_of<OP, FIX, MT>(args.q, S::get(owners_at, plane, (uint32_t)i), unit, of.na0, of.na1, nb), out + i);
+                        }
+                        S::put(owners_at, plane, (uint32_t)i, zero);
+                    }
+                });
+            } else if (wave == owner) {
+                finish(tile, row, load_row(row), scale, few, true);
+            }
             owner = owner + 1 < nw ? owner + 1 : 0;
         }
     }
+    if (S::kAnyOrder && !KNN && args.m_shared > 0) __syncthreads();          // (a strip may be another wavefront's to clear)
 
     // ---- the other rows: one wavefront each, no waiting for one another ------------------------------
     const int rows_here = args.m - args.m_shared > slice ? (args.m - args.m_shared - slice + args.slices - 1) / args.slices : 0;
@@ -918,7 +955,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         x = load_entries(p2.start, p2.len, p2.e0);
         const RowOf of = load_row(p0.row);
         const Scale scale = scale_of<OP>(wave_uniform(p0.scale), p0.len);
-        walk_lists(p0.tile, y, scale, few);
+        walk_lists(p0.tile, y, scale, strip_at, few);
         if (p0.e0 + kWave >= p0.len) {
             finish(p0.tile, p0.row, of, scale, few, p0.tiles <= 1);
             few.total = 0;
