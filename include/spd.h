@@ -315,8 +315,8 @@ spd_status spd_csr_validate(spd_handle *handle, const spd_csr *M, int require_no
  *                 0: never; 2: wherever the distance allows it
  *   "match_lists" the second way of computing a distance: B's rows are cut into tiles, each tile's entries
  *                 listed by column, and a wavefront walks the lists of its row of A, so that only the
- *                 columns two rows share cost anything (not for Chebyshev and the semirings that are not
- *                 spelled as a distance).  1 (default): where it pays (sparse and long enough operands, A's
+ *                 columns two rows share cost anything (Chebyshev pairwise and without an index only; not for the
+ *                 semirings that are not spelled as a distance).  1 (default): where it pays (sparse and long enough operands, A's
  *                 rows not too long against B's, no knob of the staged scan turned), over very many columns
  *                 after a copy of both operands over the columns that A stores; 0: never; 2: wherever the product
  *                 has it; 3: the same, over A's columns.  A call whose lists the caller's scratch does not hold, or the device

@@ -520,8 +520,8 @@ int product_of(const spd_handle *h, int metric, float p) {
     return op;
 }
 
-struct MatchLayout { size_t values, rows, ptr, norms, least, scales, end; };
-MatchLayout layout_match(const MatchShape &s, int64_t n, int64_t nnz, Carver &cv) {
+struct MatchLayout { size_t values, rows, ptr, norms, least, scales, ranks, tops, end; };
+MatchLayout layout_match(const MatchShape &s, int op, int64_t n, int64_t nnz, Carver &cv) {
     MatchLayout L;
     L.values = cv.take((size_t)s.list_entries(nnz) * 4);
     // (half of it is spare: a call asks for the scratch it has asked for, and scratch of a given size sends the same calls to the
@@ -531,12 +531,18 @@ MatchLayout layout_match(const MatchShape &s, int64_t n, int64_t nnz, Carver &cv
     L.norms = cv.take((size_t)n * 16);
     L.least = cv.take((size_t)s.n_tiles * 16);
     L.scales = cv.take((size_t)n * 2);
+    L.ranks = L.tops = 0;
+    if (op == OP_CHEB) {
+        L.ranks = cv.take((size_t)nnz);
+        L.tops = cv.take((size_t)n * kRanks * 4);
+    }
     L.end = cv.off;
     return L;
 }
 MatchB match_b_at(const MatchShape &s, const MatchLayout &L, unsigned char *dev) {
     return MatchB{reinterpret_cast<float *>(dev + L.values), reinterpret_cast<uint16_t *>(dev + L.rows), reinterpret_cast<uint32_t *>(dev + L.ptr),
                   reinterpret_cast<double *>(dev + L.norms), reinterpret_cast<double *>(dev + L.least),
+                  L.tops ? reinterpret_cast<uint8_t *>(dev + L.ranks) : nullptr, reinterpret_cast<float *>(dev + L.tops),
                   reinterpret_cast<int16_t *>(dev + L.scales), s, nullptr};
 }
 // Grid of the column-list kernel: groups of tiles times slices of A's rows, one workgroup for each
@@ -574,13 +580,13 @@ int64_t match_items(const MatchShape &s, const MatchGrid &g, int64_t m) {
     return ((m + g.slices - 1) / g.slices) * ((s.n_tiles + g.groups - 1) / g.groups);
 }
 struct ColumnsLayout { size_t words, sums, totals, masks, before, a_indices, b_indptr, b_indices, b_values; };
-struct MatchScratch { MatchLayout b; ColumnsLayout c; size_t rows, norms_a, scales_a, tau, part, row_off, row_lists, end; };
+struct MatchScratch { MatchLayout b; ColumnsLayout c; size_t rows, norms_a, scales_a, ranks_a, tops_a, tau, part, row_off, row_lists, end; };
 // `columns`: 0, or the operands' column count where both are copied over A's columns first (spd_match_columns.hip).
-MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int64_t m, int64_t nnz_a, int64_t n, int64_t nnz_b, int knn_k,
+MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int op, int64_t m, int64_t nnz_a, int64_t n, int64_t nnz_b, int knn_k,
                                bool with_b, int64_t columns) {
     MatchScratch L{};
     Carver cv;
-    if (with_b) L.b = layout_match(s, n, nnz_b, cv);
+    if (with_b) L.b = layout_match(s, op, n, nnz_b, cv);
     if (columns > 0) {
         const size_t words = ((size_t)columns + 31) / 32, masks = ((size_t)nnz_b + 63) / 64;
         L.c.words = cv.take(words * 8);
@@ -596,6 +602,10 @@ MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int64_t 
     L.rows = cv.take((size_t)m * sizeof(MatchRow));
     L.norms_a = cv.take((size_t)m * 16);
     L.scales_a = cv.take((size_t)m * 2);
+    if (op == OP_CHEB) {
+        L.ranks_a = cv.take((size_t)nnz_a);
+        L.tops_a = cv.take((size_t)m * kRanks * 4);
+    }
     if (knn_k > 0) {
         L.tau = cv.take((size_t)m * 8);
         L.row_off = cv.take((size_t)m * 8);
@@ -616,7 +626,7 @@ std::string match_check(const PlanOptions &opt, const MatchShape &s, const Match
         return "column blocks";
     if (s.ptr_stride < n_cols + blocks) return "list bounds";
     if (s.dense_per_block < 1 || s.dense_per_block > (int32_t)kBuildDense || s.dense_from < 1 ||
-        s.dense_from > T || s.tile_extra != blocks * s.dense_per_block * (T - s.dense_from)) return "dense columns";
+        s.dense_from > T + 1 || s.tile_extra != blocks * s.dense_per_block * s.dense_room()) return "dense columns";
     if (s.list_entries(nnz_b) >= (int64_t)1 << 29) return "list positions";
     const int64_t build = (int64_t)s.stage * 6 + ((int64_t)4 << s.block_shift) + 14 * T;
     if ((int64_t)s.build_lds_bytes != build || s.stage % 8 != 0 || build + 1024 > opt.lds_budget) return "build over the LDS";
@@ -670,9 +680,9 @@ bool match_suits(const spd_handle *h, const spd_csr *B, int op, const MatchShape
 // Whether an index keeps the lists, and their layout in its memory: only lists that a call may want, and no more of
 // them than the header states (a small B over many columns has more bounds than entries).
 bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape &s, MatchLayout &L) {
-    if (!match_possible(h, B, op, s)) return false;
+    if (!match_possible(h, B, op, s) || !match_serves_knn(op)) return false;
     Carver cv;
-    L = layout_match(s, B->n_rows, B->nnz, cv);
+    L = layout_match(s, op, B->n_rows, B->nnz, cv);
     if (h->match_lists == 2) return true;
     if (op == OP_CNT) return false;                // (counts come out the same by the scan, which is as fast where a call has no B to prepare)
     return match_suits(h, B, op, s) && (int64_t)L.end <= 20 * B->nnz + 16 * B->n_rows + (1 << 20);
@@ -700,6 +710,7 @@ constexpr OpCost op_cost(int op) {
     case OP_CANB: return {13.1, 3.6, 0.75, 0, 180, 0.282, 3.6e-5, 0.063, 1.5};
     case OP_KL: return {9.6, 7.9, 0.73, 0, 250, 0.324, 6.0e-5, 0.051, 1.2};
     case OP_JS: return {12.6, 15.4, 0.72, 0, 640, 0.703, 5.5e-5, 0.069, 2.3};
+    case OP_CHEB: return {13.1, 14.0, 0.90, 0, 0, 0.26, 4.0e-5, 0.060, 1.6};
     default: return {10.9, 13.1, 1.28, 140, 630, 0.45, 1.5e-4, 0.241, 3.5};
     }
 }
@@ -725,7 +736,9 @@ double staged_cost(const spd_csr *A, const spd_csr *B, int op, bool swapped, boo
     const double mean = swapped ? nnz_b / n : nnz_a / m;                                       // of the staged rows
     const double visit = c.visit + c.longer * std::min(mean, 2000.0) + (A->n_cols > 40000 ? c.wide : 0.0);
     const double make = made ? 0.0 : 22e6 + 13.0 * nnz_b + 1900.0 * n;
-    return (knn ? 58e6 : 31e6) + make + 5000.0 * m + 22.0 * nnz_a + 35000.0 * mean + visit * (swapped ? n * nnz_a : m * nnz_b) +
+    // (Chebyshev ranks the entries of the rows that it stages: 34 x 969 rows of 1,550 2,777 us, by lists 554; 304 x 604 rows of 23 186 / 94;
+    // 2,026 x 7,507 ratings 11,152 / 703; 3,148 x 4,764 rows of 1,790 25,963 / 3,002)
+    return (knn ? 58e6 : 31e6) + make + 5000.0 * m + 22.0 * nnz_a + (op == OP_CHEB ? 2e6 : 35000.0) * mean + visit * (swapped ? n * nnz_a : m * nnz_b) +
            (c.pair + (knn ? 0.5 : 0.0)) * m * n;
 }
 // `swapped`: the staged scan would exchange the operands' roles.
@@ -733,6 +746,8 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
                   bool with_index) {
     MatchShape s;
     if (semiring || A->n_rows <= 0 || !match_possible(h, B, op, s)) return false;
+    if ((knn || with_index) && !match_serves_knn(op)) return false;
+    if (op == OP_CHEB && A->n_rows + B->n_rows >= (int64_t)1 << 26) return false;             // (a wavefront to the row that is ranked)
     if (match_items(s, match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
     if (!match_launches_fit(s, A->n_rows, A->nnz, false)) return false;
     if (h->match_lists == 2) return true;
@@ -748,7 +763,7 @@ int64_t columns_of(const spd_csr *A) { return std::min(A->n_cols, std::max<int64
 // Whether a call is computed by lists over the columns that A stores, after a copy of both operands over these.
 bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn,
                     bool with_index) {
-    if (semiring || h->match_lists == 0 || !match_serves(op) || A->n_rows <= 0 || A->nnz <= 0 || B->n_rows <= 0 || B->nnz <= 0) return false;
+    if (semiring || h->match_lists == 0 || !match_serves_knn(op) || A->n_rows <= 0 || A->nnz <= 0 || B->n_rows <= 0 || B->nnz <= 0) return false;
     if (A->n_cols > kMatchMostColumns) return false;
     const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
     if (s.n_tiles <= 0 || s.list_entries(B->nnz) >= ((int64_t)1 << 29)) return false;
@@ -783,7 +798,7 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
     // the share, us: sets, Jaccard, k-NN 8,816 / 8,489 / 8,785, words, cosine 5,368 / 5,435 / 6,737; from 128 / 256 / 512 entries on: 10,000 x
     // 10,000 rows of 38, L1 297 / 298 / 288, cosine, k-NN 504 / 507 / 534.)
     if (match_any_order(op)) w.g.shared_len = std::max<int64_t>(knn ? 256 : 512, w.g.share / 6);
-    w.L = layout_match_call(w.s, w.g, A->n_rows, A->nnz, B->n_rows, B->nnz, knn_k, w.way == 2 || !with_index, w.way == 2 ? A->n_cols : 0);
+    w.L = layout_match_call(w.s, w.g, op, A->n_rows, A->nnz, B->n_rows, B->nnz, knn_k, w.way == 2 || !with_index, w.way == 2 ? A->n_cols : 0);
     return w;
 }
 
@@ -828,7 +843,16 @@ spd_status start_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int me
     start.a_indices = A->indices;
     start.listed = *B;
     if (!index_lists) {
-        st = stage_norms(h, B, start.b, op, metric, mi, q);
+        if (op == OP_CHEB) {
+            LaunchTimer lt(h, "norms_b", 0, 0, 0, 0, 0, 0);
+            e = launch_match_ranks(h->stream, RankedRows{B->indptr, B->values, n, B->nnz, 0, start.b.ranks, start.b.tops},
+                                   RankedRows{A->indptr, A->values, m, A->nnz, 1, reinterpret_cast<uint8_t *>(ws + L.ranks_a),
+                                              reinterpret_cast<float *>(ws + L.tops_a)});
+            if (e != hipSuccess) return hip_fail(h, e, "rank kernel");
+            lt.done();
+        } else {
+            st = stage_norms(h, B, start.b, op, metric, mi, q);
+        }
         if (st != SPD_OK) return st;
         if (compact) {
             const MatchColumns c{reinterpret_cast<uint2 *>(ws + L.c.words), reinterpret_cast<uint32_t *>(ws + L.c.sums),
@@ -850,6 +874,7 @@ spd_status start_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int me
         st = stage_lists(h, &start.listed, start.b, op, metric, mi, knn_k > 0);
         if (st != SPD_OK) return st;
     }
+    if (op == OP_CHEB) return SPD_OK;
     LaunchTimer lt(h, "norms_a", 0, 0, 0, 0, 0, 0);
     e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, op, metric, mi.transform, mi.norm, q.p, q.k, true,
                            reinterpret_cast<double *>(ws + L.norms_a), reinterpret_cast<int16_t *>(ws + L.scales_a));
@@ -903,6 +928,10 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     a.m = (int32_t)m;
     a.norms_a = reinterpret_cast<const double *>(ws + L.norms_a);
     a.scales_a = reinterpret_cast<const int16_t *>(ws + L.scales_a);
+    a.ranks_a = reinterpret_cast<const uint8_t *>(ws + L.ranks_a);
+    a.tops_a = reinterpret_cast<const float *>(ws + L.tops_a);
+    a.b_indices = start.listed.indices;
+    a.b_values = start.listed.values;
     a.b_indptr = start.listed.indptr;
     a.b_nnz = B->nnz;
     a.b = start.b;
@@ -1972,7 +2001,7 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
         w.s = match_shape(h.opt.lds_budget, op, b_rows, n_cols, b_nnz);
         if (w.s.n_tiles <= 0) return SPD_OK;
         w.g = match_grid(h.opt, w.s, a_rows, a_nnz, b_nnz, knn);
-        w.L = layout_match_call(w.s, w.g, a_rows, a_nnz, b_rows, b_nnz, k_neighbors, !with_index, 0);
+        w.L = layout_match_call(w.s, w.g, op, a_rows, a_nnz, b_rows, b_nnz, k_neighbors, !with_index, 0);
     }
     out->columns = w.columns;
     out->tiles = w.s.n_tiles;

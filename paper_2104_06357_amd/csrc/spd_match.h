@@ -35,6 +35,7 @@ struct MatchShape {
     uint32_t stage;                         // entries of a block that pass through LDS together
     int64_t ptr_stride, tile_extra;         // words of a tile's list bounds; entries beyond the tile's own
     uint32_t lds_bytes, build_lds_bytes;
+    SPD_HD int32_t dense_room() const { return tile_rows > dense_from ? tile_rows - dense_from : 0; }       // entries more than such a column has
     SPD_HD int64_t list_entries(int64_t nnz) const { return nnz + n_tiles * tile_extra + kMatchSpare; }
 };
 MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, int64_t nnz);
@@ -52,6 +53,8 @@ struct MatchB {
                             // kMatchDense is set where the column is dense
     double *norms;          // 2 * n, derived: the first ones, then the second ones
     double *least;          // n_tiles * 2: the norms of a tile's row of the least first norm (k-NN)
+    uint8_t *ranks;         // Chebyshev: of B's entries, kRanks or more where it is not among the row's kRanks largest
+    float *tops;            // ... kRanks * n: the rows' largest magnitudes, the first of all rows, the second ..., 0 where a row has no more
     int16_t *scales;        // n: the exponents of the rows whose values are listed over a power of two (match_fixed), else not used
     MatchShape shape;
     const uint32_t *cols;   // nullptr, or on the device how many columns there are (no more than the shape was made for)
@@ -65,6 +68,10 @@ struct MatchArgs {
     int32_t m;
     const double *norms_a;        // 2 * m, derived, likewise
     const int16_t *scales_a;      // m: exponents, see match_fixed
+    const uint8_t *ranks_a;       // Chebyshev: of A's entries, and kRanks magnitudes of every row, one row after the other
+    const float *tops_a;
+    const int32_t *b_indices;     // ... and B's rows, for the pairs whose kRanks largest entries of a row were all met
+    const float *b_values;
     const int64_t *b_indptr;
     int64_t b_nnz;
     MatchB b;
@@ -102,7 +109,7 @@ constexpr int64_t kMatchL2Bytes = 4 << 20;      // of one XCD
 SPD_HD constexpr int match_doubles(int op) {
     return op == OP_DOT || op == OP_L1 || op == OP_CANB || op == OP_KL || op == OP_JS ? 1 : (op == OP_MINK || op == OP_MINK_ANY ? 2 : 0);
 }
-SPD_HD constexpr int match_counts(int op) { return op == OP_HAMM || op == OP_CNT || op == OP_KL || op == OP_MINK || op == OP_MINK_ANY ? 1 : 0; }
+SPD_HD constexpr int match_counts(int op) { return op == OP_CHEB ? 3 : op == OP_HAMM || op == OP_CNT || op == OP_KL || op == OP_MINK || op == OP_MINK_ANY ? 1 : 0; }
 SPD_HD constexpr int match_cell_bytes(int op) { return 8 * match_doubles(op) + 4 * match_counts(op); }
 SPD_HD constexpr uint32_t match_strip_bytes(int cell_bytes, int tile_rows) { return ((uint32_t)(tile_rows + 1) * (uint32_t)cell_bytes + 7u) / 8u * 8u; }
 // Wavefronts of a workgroup, of which a compute unit holds one: the strips share its LDS, and where a pair's
@@ -146,8 +153,13 @@ SPD_HD int match_canberra_scale(int len) { return len < (1 << 10) ? 2 : 2 + (32 
 // The products the column lists serve.
 SPD_HD constexpr bool match_serves(int op) {
     return op == OP_DOT || op == OP_L1 || op == OP_CANB || op == OP_HAMM || op == OP_KL || op == OP_JS || op == OP_CNT ||
-           op == OP_MINK || op == OP_MINK_ANY;
+           op == OP_MINK || op == OP_MINK_ANY || op == OP_CHEB;
 }
+// Chebyshev: the maximum over the columns that both rows store is completed from the largest entry of either row that the other does
+// not store.  The entries of a row are ranked by magnitude; a pair keeps a bit for each of the kRanks largest of either row that was
+// met, so that the first one that was not is known.  Pairwise only; a (tile, row) has no distance before its bits are complete.
+constexpr int kRanks = 32, kRankShift = 10, kRankedRows = 832;      // (rank and row share an entry's 16 bits; a round of finishing holds 13 x 64 rows)
+SPD_HD constexpr bool match_serves_knn(int op) { return match_serves(op) && op != OP_CHEB; }
 
 // Whether the launches for a call's lists, of which A has m rows, are below 2^32 work-items each (`renumbered`: over A's columns).
 bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renumbered);
@@ -156,6 +168,9 @@ bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renu
 // unit of the sums too.
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
                               int op, int metric, int transform, int norm, float p, double k, bool queries, double *norms, int16_t *scales);
+// Ranks and largest magnitudes of two operands' rows (`by_row`: the magnitudes of a row one after the other, else in planes).
+struct RankedRows { const int64_t *indptr; const float *values; int64_t n_rows, nnz; int by_row; uint8_t *ranks; float *tops; };
+hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const RankedRows &second);
 // (after the norms; `b.least` nullptr: not asked for)
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
                               int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int metric, int transform);

@@ -97,6 +97,90 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
 }
 
 // ------------------------------------------------------------------------------------
+// Chebyshev: every entry's rank by magnitude in its row, and the row's largest magnitudes.  A wavefront to the row.  The 32nd largest
+// of what the lanes' largest entries are bounds the row's 32nd; what reaches it is queued and merged with the 64 largest so far when 64
+// are waiting, so that a long row is sorted two or three times and not for every 64 entries (7,777 rows of 37, the longest
+// 2,000, and 3,333 of them, a launch each, sorted for every 64 entries: 28 us each; 17 for both now).
+// ------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) spd_match_ranks_kernel(const RankedRows first, const RankedRows second) {
+    const int lane = (int)threadIdx.x & 63;
+    const int64_t at = (int64_t)blockIdx.x * 4 + wave_uniform((int)threadIdx.x >> 6);
+    const bool is_first = at < first.n_rows;
+    const RankedRows &o = is_first ? first : second;
+    const int64_t row = is_first ? at : at - first.n_rows;
+    if (row >= o.n_rows) return;
+    const int64_t begin = clamp_i64(o.indptr[row], 0, o.nnz), end = clamp_i64(o.indptr[row + 1], begin, o.nnz);
+    constexpr uint64_t kNone = ~0ull;                              // (keys ascend with falling magnitudes; then by place)
+    auto key_of = [&](int64_t e, float v) { return e < end && v != 0.0f ? ((uint64_t)~__float_as_uint(fabsf(v)) << 32) | (uint32_t)(e - begin) : kNone; };
+    auto kth = [&](uint64_t sorted) {
+        return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(sorted >> 32), kRanks - 1) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)sorted, kRanks - 1);
+    };
+    uint64_t best = kNone, bar = kNone, queue = kNone;
+    int queued = 0;
+    auto merge = [&]() {
+        const uint64_t c = wave_sort_desc(lane < queued ? queue : kNone, lane);
+        best = wave_merge_asc(c < best ? c : best, lane);
+        const uint64_t now = kth(best);
+        bar = now < bar ? now : bar;
+        queued = 0;
+    };
+    if (end - begin > 2 * kWave) {
+        uint64_t mine = kNone;
+        for (int64_t e0 = begin + lane; e0 < end; e0 += 4 * kWave) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = e0 + u * kWave < end ? o.values[e0 + u * kWave] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint64_t key = key_of(e0 + u * kWave, v[u]);
+                mine = key < mine ? key : mine;
+            }
+        }
+        bar = kth(wave_merge_asc(wave_sort_desc(mine, lane), lane));
+    }
+    for (int64_t e0 = begin; e0 < end; e0 += 4 * kWave) {
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = e0 + u * kWave + lane < end ? o.values[e0 + u * kWave + lane] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t e = e0 + u * kWave + lane;
+            if (e < end) o.ranks[e] = 255;
+            const uint64_t key = key_of(e, v[u]);
+            bool pass = key != kNone && key <= bar;
+            uint64_t mask = __ballot(pass);
+            if (mask == 0) continue;
+            if (queued + (int)__popcll(mask) > kWave) {
+                merge();
+                pass = pass && key <= bar;
+                mask = __ballot(pass);
+                if (mask == 0) continue;
+            }
+            // the passing lanes' keys go to the queue's next places (a permutation of the lanes)
+            const int n_pass = (int)__popcll(mask);
+            const int to = pass ? queued + (int)lane_rank_in(mask) : queued + n_pass + (int)lane_rank_in(~mask);
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_permute((to & 63) << 2, (int)(uint32_t)key);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_permute((to & 63) << 2, (int)(uint32_t)(key >> 32));
+            if (lane >= queued && lane < queued + n_pass) queue = ((uint64_t)hi << 32) | lo;
+            queued += n_pass;
+        }
+    }
+    merge();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");          // (an entry's rank replaces what another lane wrote there)
+    if (lane < kRanks) {
+        if (best != kNone) o.ranks[begin + (int64_t)(uint32_t)best] = (uint8_t)lane;
+        o.tops[o.by_row ? row * kRanks + lane : (int64_t)lane * o.n_rows + row] = best != kNone ? __uint_as_float(~(uint32_t)(best >> 32)) : 0.0f;
+    }
+}
+hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const RankedRows &second) {
+    const int64_t rows = first.n_rows + second.n_rows;
+    if (rows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(spd_match_ranks_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, first, second);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------
 // B: a tile's entries by column.  A workgroup takes a run of column blocks of one tile.  The rows ascend in
 // their columns, so a row's entries of a block are a stretch of it, found where the block before ended:
 // every entry is read once to count and once (from the caches) to place.  Counters and the block's piece
@@ -146,6 +230,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     __shared__ uint32_t s_dense[kBuildDense], s_long[kBuildLong], s_longs;
     __shared__ double s_least[kBuildThreads / kWave][2];
     const MatchShape &shape = b.shape;
+    const uint8_t *const ranks = b.ranks;
     const uint32_t cols = b.cols ? min(*b.cols, most_cols) : most_cols;
     const uint32_t block_cols = 1u << shape.block_shift, blocks = min((uint32_t)shape.blocks, (cols + block_cols - 1u) >> shape.block_shift);
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -218,7 +303,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         __syncthreads();
 #pragma unroll
         for (int w = 0; w < nw; ++w) base += s_wave[w];
-        base += block_first * (uint32_t)shape.dense_per_block * (uint32_t)(T - shape.dense_from);
+        base += block_first * (uint32_t)shape.dense_per_block * (uint32_t)shape.dense_room();
     }
     for (uint32_t block = block_first; block < block_last; ++block) {
         const uint32_t c0 = block * block_cols, range = min(block_cols, cols - c0);
@@ -359,7 +444,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         __threadfence_block();
         __syncthreads();
         // place
-        auto place = [&](uint32_t c, float v, int r) {
+        auto place = [&](uint32_t c, float v, int r, uint32_t rank) {
             if (c - c0 >= range) return;
             const float t = transform_value(transform, v), scaled_t = __builtin_ldexpf(t, -(int)s_scale[r]);
             uint32_t *count = &s_count[c - c0];
@@ -370,7 +455,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
                 else if (at < room) values_at[at] = scaled_t;
             } else {
                 // (a stored zero is absent: it goes to the spare row behind the tile's)
-                const uint16_t cell = (uint16_t)((uint32_t)(t != 0.0f ? r : T) * (uint32_t)unit);
+                const uint16_t cell = (uint16_t)((uint32_t)(t != 0.0f ? r : T) * (uint32_t)unit + (min(rank, 2u * kRanks - 1u) << kRankShift));
                 at = atomicAdd(count, 1u);
                 if (at < shape.stage) {
                     s_row[at] = cell;
@@ -385,12 +470,14 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         for (int r0 = group; r0 < rows; r0 += kRows * groups) {
             uint32_t pos[kRows], end[kRows], c[kRows][kAhead];
             float v[kRows][kAhead];
+            uint32_t rank[kRows][kAhead];
             auto load = [&](int u) {
 #pragma unroll
                 for (int x = 0; x < kAhead; ++x) {
                     const uint32_t e = pos[u] + (uint32_t)(x * G);
                     c[u][x] = e < end[u] ? (uint32_t)indices[row_first + e] : 0xFFFFFFFFu;
                     v[u][x] = e < end[u] ? values[row_first + e] : 0.0f;
+                    rank[u][x] = ranks && e < end[u] ? ranks[row_first + e] : 0u;
                 }
             };
 #pragma unroll
@@ -408,7 +495,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
                 const int r = r0 + u * groups;
                 while (pos[u] < end[u]) {
 #pragma unroll
-                    for (int x = 0; x < kAhead; ++x) place(c[u][x], v[u][x], r);
+                    for (int x = 0; x < kAhead; ++x) place(c[u][x], v[u][x], r, rank[u][x]);
                     pos[u] += (uint32_t)(G * kAhead);
                     if (pos[u] < end[u]) load(u);
                 }
@@ -420,14 +507,16 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             for (uint32_t pos = s_cur[r]; pos < end; pos += kRows * 64u) {
                 uint32_t c[kRows];
                 float v[kRows];
+                uint32_t rank[kRows];
 #pragma unroll
                 for (int u = 0; u < kRows; ++u) {
                     const uint32_t e = pos + (uint32_t)(u * 64 + lane);
+                    rank[u] = ranks && e < end ? ranks[row_first + e] : 0u;
                     c[u] = e < end ? (uint32_t)indices[row_first + e] : 0xFFFFFFFFu;
                     v[u] = e < end ? values[row_first + e] : 0.0f;
                 }
 #pragma unroll
-                for (int u = 0; u < kRows; ++u) place(c[u], v[u], r);
+                for (int u = 0; u < kRows; ++u) place(c[u], v[u], r, rank[u]);
             }
         }
         __syncthreads();
@@ -446,7 +535,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             if (mine) atomicAdd(&s_wave[0], mine);
         }
         __syncthreads();
-        base += s_wave[0] + (uint32_t)shape.dense_per_block * (whole - mark);        // (a dense column has `mark` entries at least)
+        base += s_wave[0] + (uint32_t)shape.dense_per_block * (uint32_t)shape.dense_room();        // (a dense column has `mark` entries at least)
         __syncthreads();
     }
 }
@@ -483,6 +572,7 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     s.waves = match_waves(cell);
     const int64_t strip = (lds_budget - match_static_lds(cell)) / s.waves;
     int64_t most = ((strip - 7) / cell - 1) / kWave * kWave;    // (a spare row behind them)
+    if (op == OP_CHEB) most = std::min<int64_t>(most, kRankedRows);
     if (most < kWave) return s;
     const double per_cell = (double)nnz / (double)n / (double)n_cols;
     if (cell <= 8 && op != OP_JS) {
@@ -507,7 +597,7 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     // A step of 64 rows of a dense column costs half a list's step.  (From 0.3 / 0.4 / 0.5 / 0.6 of the rows on, us: 1,024 x 300,000 rows
     // of 230, cosine, 5,796 / 5,651 / 5,638 / 5,767, k-NN of 2,048 of them, Hellinger, 7,535 / 7,570 / 7,645 / 7,909; 10,000 x 10,000 rows
     // of 38, L1, 336 / 331 / 325 / 318; sets, Jaccard, 9,102 / 8,970 / 8,928 / 8,963.)
-    s.dense_from = std::max(1, s.tile_rows / 2);
+    s.dense_from = op == OP_CHEB ? s.tile_rows + 1 : std::max(1, s.tile_rows / 2);         // (Chebyshev: an entry has a rank, a column of values none)
     const double per_col = per_cell * (double)s.tile_rows;
     auto stage_of = [&](int shift) { return (usable - rows_bytes - ((int64_t)4 << shift)) / 48 * 8; };
     int shift = 2;
@@ -529,13 +619,13 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     const int64_t tiles_now = (n + s.tile_rows - 1) / s.tile_rows;
     auto blocks_of = [&](int at) { return (n_cols + (1 << at) - 1) >> at; };
     while (shift > 8 && tiles_now * blocks_of(shift) < 256 &&
-           tiles_now * blocks_of(shift - 1) * dense_of(shift - 1) * (s.tile_rows - s.dense_from) * 6 <= 8 * nnz + (512 << 10)) --shift;
+           tiles_now * blocks_of(shift - 1) * dense_of(shift - 1) * s.dense_room() * 6 <= 8 * nnz + (512 << 10)) --shift;
     s.block_shift = shift;
     s.stage = (uint32_t)stage_of(shift);
     s.blocks = (int32_t)blocks_of(shift);
     s.dense_per_block = dense_of(shift);
     s.ptr_stride = (n_cols + s.blocks + 3) / 4 * 4;
-    s.tile_extra = (int64_t)s.blocks * s.dense_per_block * (s.tile_rows - s.dense_from);
+    s.tile_extra = (int64_t)s.blocks * s.dense_per_block * s.dense_room();
     s.build_lds_bytes = s.stage * 6u + (4u << shift) + (uint32_t)rows_bytes;
     s.n_tiles = (int32_t)((n + s.tile_rows - 1) / s.tile_rows);
     return s;
@@ -562,7 +652,7 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
         hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(kern, dim3(((unsigned)s.n_tiles * wgs + 7u) / 8u * 8u), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
-                           nnz, k, b, per_wg, wgs, match_cell_bytes(op) >= 8 ? 8 : 4, transform, op == OP_DOT && match_fixed(op, metric), op != OP_CNT);
+                           nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op == OP_DOT && match_fixed(op, metric), op != OP_CNT);
         return hipGetLastError();
     };
     // (a row's stretch in the two loads of its lanes, where that leaves no more than half of them idle: rows of 1,820 over 51 blocks 1,078 us
@@ -596,7 +686,7 @@ hipError_t launch_match_b(hipStream_t st, int op, const MatchArgs &args, uint32_
 hipError_t launch_match(hipStream_t st, int op, const MatchArgs &args, uint32_t lds_bytes) {
     switch (op) {
     case OP_DOT: case OP_L1: case OP_HAMM: case OP_CNT: case OP_CANB: return launch_match_a(st, op, args, lds_bytes);
-    case OP_KL: case OP_JS: case OP_MINK: case OP_MINK_ANY: return launch_match_b(st, op, args, lds_bytes);
+    case OP_KL: case OP_JS: case OP_MINK: case OP_MINK_ANY: case OP_CHEB: return launch_match_b(st, op, args, lds_bytes);
     default: return hipErrorInvalidValue;
     }
 }

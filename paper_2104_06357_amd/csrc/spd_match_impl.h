@@ -18,14 +18,15 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 // rows of neighbouring lanes lie in different banks.  `at`: LDS address of the strip, `plane`: bytes of a plane of doubles.
 // FIX: one sum in fixed point in the place of the double.
 struct Fixed { long long v; };
+struct Ranked { uint32_t m, met_a, met_b; };         // Chebyshev: the maximum (a float's bits), which of the rows' largest entries were met
 template <int OP, bool FIX> struct Sums {
-    using Acc = std::conditional_t<FIX, Fixed, typename Op<OP>::Acc>;
+    using Acc = std::conditional_t<FIX, Fixed, std::conditional_t<OP == OP_CHEB, Ranked, typename Op<OP>::Acc>>;
     static_assert(!FIX || (match_doubles(OP) == 1 && match_counts(OP) == 0), "one sum");
     static __device__ __forceinline__ void init(Acc &x) {
-        if constexpr (FIX) x.v = 0; else Op<OP>::init(x);
+        if constexpr (FIX) x.v = 0; else if constexpr (OP == OP_CHEB) x = Ranked{0u, 0u, 0u}; else Op<OP>::init(x);
     }
     static __device__ __forceinline__ void combine(Acc &x, const Acc &y) {
-        if constexpr (FIX) x.v += y.v; else Op<OP>::combine(x, y);
+        if constexpr (FIX) x.v += y.v; else if constexpr (OP != OP_CHEB) Op<OP>::combine(x, y);
     }
     static constexpr int kDoubles = match_doubles(OP), kCounts = match_counts(OP);
     static constexpr bool kOne = kDoubles + kCounts == 1;
@@ -34,25 +35,34 @@ template <int OP, bool FIX> struct Sums {
     static __device__ __forceinline__ Acc get(uint32_t at, uint32_t plane, uint32_t row) {
         Acc x;
         init(x);
+        if constexpr (OP == OP_CHEB) {
+            return Ranked{*lds_at<uint32_t>(at + row * 4u), *lds_at<uint32_t>(at + plane / 2u + row * 4u), *lds_at<uint32_t>(at + plane + row * 4u)};
+        }
 #pragma unroll
         for (int p = 0; p < kDoubles; ++p) {
             const double v = *lds_at<double>(at + (uint32_t)p * plane + row * 8u);
             __builtin_memcpy(reinterpret_cast<unsigned char *>(&x) + 8 * p, &v, 8);
         }
-        if constexpr (kCounts) {
+        if constexpr (kCounts == 1) {
             const int v = *lds_at<int>(at + (uint32_t)kDoubles * plane + row * 4u);
             __builtin_memcpy(reinterpret_cast<unsigned char *>(&x) + 8 * kDoubles, &v, 4);
         }
         return x;
     }
     static __device__ __forceinline__ void put(uint32_t at, uint32_t plane, uint32_t row, const Acc &x) {
+        if constexpr (OP == OP_CHEB) {
+            *lds_at<uint32_t>(at + row * 4u) = x.m;
+            *lds_at<uint32_t>(at + plane / 2u + row * 4u) = x.met_a;
+            *lds_at<uint32_t>(at + plane + row * 4u) = x.met_b;
+            return;
+        }
 #pragma unroll
         for (int p = 0; p < kDoubles; ++p) {
             double v;
             __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * p, 8);
             *lds_at<double>(at + (uint32_t)p * plane + row * 8u) = v;
         }
-        if constexpr (kCounts) {
+        if constexpr (kCounts == 1) {
             int v;
             __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * kDoubles, 4);
             *lds_at<int>(at + (uint32_t)kDoubles * plane + row * 4u) = v;
@@ -60,6 +70,12 @@ template <int OP, bool FIX> struct Sums {
     }
     // Adds to the sums of the row whose first number lies `offset` bytes into the strip.
     static __device__ __forceinline__ void add(uint32_t at, uint32_t plane, uint32_t offset, const Acc &x) {
+        if constexpr (OP == OP_CHEB) {
+            (void)__hip_atomic_fetch_max(lds_at<uint32_t>(at + offset), x.m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            (void)__hip_atomic_fetch_or(lds_at<uint32_t>(at + plane / 2u + offset), x.met_a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            (void)__hip_atomic_fetch_or(lds_at<uint32_t>(at + plane + offset), x.met_b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            return;
+        }
         if constexpr (FIX) {
             __hip_atomic_fetch_add(lds_at<unsigned long long>(at + offset), (unsigned long long)x.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             return;
@@ -70,7 +86,7 @@ template <int OP, bool FIX> struct Sums {
             __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * p, 8);
             __hip_atomic_fetch_add(lds_at<double>(at + (uint32_t)p * plane + offset), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        if constexpr (kCounts) {
+        if constexpr (kCounts == 1) {
             int v;
             __builtin_memcpy(&v, reinterpret_cast<const unsigned char *>(&x) + 8 * kDoubles, 4);
             __hip_atomic_fetch_add(lds_at<int>(at + (uint32_t)kDoubles * plane + (kDoubles ? offset >> 1 : offset)), v, __ATOMIC_RELAXED,
@@ -177,7 +193,7 @@ template <int OP> __device__ __forceinline__ double units_of(const Fixed &x) {
 enum NormsRead { READ_NONE = 0, READ_FIRST, READ_SECOND, READ_SCALE, READ_BOTH };
 SPD_HD constexpr int norms_read(int metric, bool fixed) {
     switch (metric) {
-    case MT_INNER: case MT_KL: case MT_KL_STRICT: case MT_RUSSELL_RAO: return READ_NONE;
+    case MT_INNER: case MT_KL: case MT_KL_STRICT: case MT_RUSSELL_RAO: case MT_CHEBYSHEV: return READ_NONE;
     case MT_COSINE: return READ_SECOND;
     case MT_L2: case MT_HELLINGER: return fixed ? READ_SCALE : READ_FIRST;
     case MT_CORRELATION: case MT_MINKOWSKI: case MT_L2_UNEXPANDED: return READ_BOTH;
@@ -196,6 +212,8 @@ __device__ __forceinline__ float distance_of(const OpParams &q, const typename S
         if constexpr (OP != OP_DOT) v *= unit;
         else if constexpr (R == READ_SCALE) v = __builtin_ldexp(v * na1, b.e);
         return finish_as<MT>(q, v, 0.0, 0.0, a0, na1, b.x, b1);
+    } else if constexpr (OP == OP_CHEB) {
+        return 0.0f;                                               // (not formed from these: finish_ranked)
     } else {
         using O = Op<OP>;
         return finish_as<MT>(q, O::v0(c), O::v1(c), O::v2(c), a0, na1, b.x, b1);
@@ -314,19 +332,24 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // 64 entries of a row of A, one per lane, on their way to the strip: first the entries, then the lists of
     // their columns, then the lists' entries.  Each stage is loaded while the stage before it is at work on
     // something else, so that the three round trips to memory are not waited for in turn.
-    struct Entries { uint32_t c; float v; };
-    struct Lists { uint32_t first, last; float a; };
+    // (`met`: Chebyshev, the bit of the entry's rank)
+    struct Entries { uint32_t c; float v; uint32_t met; };
+    struct Lists { uint32_t first, last; float a; uint32_t met; };
     auto load_entries = [&](int64_t start, int len, int e0) {
-        Entries x{0xFFFFFFFFu, 0.0f};
+        Entries x{0xFFFFFFFFu, 0.0f, 0u};
         if (e0 + lane < len) {
             x.c = (uint32_t)args.a_indices[start + e0 + lane];
             x.v = args.a_values[start + e0 + lane];
+            if constexpr (OP == OP_CHEB) {
+                const uint32_t rank = args.ranks_a[start + e0 + lane];
+                x.met = rank < (uint32_t)kRanks ? 1u << rank : 0u;
+            }
         }
         return x;
     };
     auto load_lists = [&](int tile, const Entries &x) {
         const uint32_t *__restrict__ ptr = args.b.ptr + (size_t)tile * (size_t)args.b.shape.ptr_stride;
-        Lists y{0u, 0u, 0.0f};
+        Lists y{0u, 0u, 0.0f, 0u};
         if (x.c < args.k) {
             const uint32_t at = x.c + (x.c >> args.b.shape.block_shift);
             // (both in one load: 64 lanes at as many lines take the L1 as long for four bytes as for eight)
@@ -336,6 +359,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             y.last = two.last;
         }
         y.a = x.v;
+        y.met = x.met;
         return y;
     };
     // The batch's dense columns: one value per row of the tile, lane by lane, summed in registers; then the strip.
@@ -390,7 +414,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                     if constexpr (FIX) {
                         S::add(to, plane, i * S::kUnit, fixed_sum<OP>(sum[d], scale));
                     } else if constexpr (S::kAnyOrder) {
-                        S::add(to, plane, i * S::kUnit, sum[d]);
+                        if constexpr (OP != OP_CHEB) S::add(to, plane, i * S::kUnit, sum[d]);          // (which has no dense columns)
                     } else {
                         Acc acc = S::get(to, plane, i);
                         S::combine(acc, sum[d]);
@@ -413,7 +437,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // What a walk of no more than four steps leaves behind for the k-NN's finish: the chunks it took, and the lanes' entries.
     struct Few { int total; uint32_t cell[U], left[U]; };
     auto walk_chunks = [&](const unsigned char *__restrict__ values, const unsigned char *__restrict__ rows, uint32_t first, uint32_t last, float a,
-                           const Scale &scale, uint32_t to, Few &few) {
+                           uint32_t met, const Scale &scale, uint32_t to, Few &few) {
         const int chunks = (int)((last - first + 15u) >> 4);
         const int incl = wave_scan_add(chunks), excl = incl - chunks;
         const int total = __builtin_amdgcn_readlane(incl, 63);
@@ -423,7 +447,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         const uint32_t last4 = last * 4u;
         const int turned = ((lane & 15) << 2) | (lane >> 4);
         const uint32_t lane4 = (uint32_t)(lane & 15) * 4u;
-        struct Chunk { uint32_t at, left; float a; };                            // left: bytes of its list's values from `at` on
+        struct Chunk { uint32_t at, left; float a; uint32_t met; };                            // left: bytes of its list's values from `at` on
         struct Entry { _Float16 cell; float v; };
         // (16 bits: 64 lists of a tile are 64 * 156 chunks at most, the last group's tag is below 2^14)
         uint16_t *owner = s_owner[wave];
@@ -446,6 +470,8 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             c.at = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)base4) + 64u * (uint32_t)q;
             c.left = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)last4) - c.at;
             c.a = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(a)));
+            c.met = 0u;
+            if constexpr (OP == OP_CHEB) c.met = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)met);
             if (q >= total) { c.at = 0u; c.left = 0u; }
             return c;
         };
@@ -462,13 +488,23 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             into[2] = fetch_one(row_lane<I + 2>(c.at));
             into[3] = fetch_one(row_lane<I + 3>(c.at));
         };
-        auto add_one = [&](const Entry &from, uint32_t left, float av) {
+        auto add_one = [&](const Entry &from, uint32_t left, float av, uint32_t met) {
             // (everything but the LDS add itself is done for all lanes: a branch around it costs more)
             Acc t;
             bool counts = true;
-            if constexpr (FIX) t = fixed_visit<OP>(av, from.v, scale);
-            else counts = match_visit<OP>(t, av, from.v, args.q);
             uint32_t at;
+            if constexpr (OP == OP_CHEB) {
+                const uint32_t cell = __builtin_bit_cast(uint16_t, from.cell), rank = cell >> kRankShift;
+                const float d = fabsf(av - from.v);
+                t = Ranked{__float_as_uint(d), met, rank < (uint32_t)kRanks ? 1u << (rank & 31u) : 0u};
+                at = (cell & ((1u << kRankShift) - 1u)) * 4u;
+                counts = d == d;                                  // (as a maximum passes over what is not a number)
+                pin(t, at);
+                if (lane4 < left && counts) S::add(to, plane, at, t);
+                return;
+            }
+            if constexpr (FIX) t = fixed_visit<OP>(av, from.v, scale);
+            else if constexpr (OP != OP_CHEB) counts = match_visit<OP>(t, av, from.v, args.q);
             if constexpr (S::kOne) at = plus_half(from.cell, to); else at = __builtin_bit_cast(uint16_t, from.cell);
             pin(t, at);
             if (lane4 < left && counts) {
@@ -477,10 +513,10 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         };
         auto add = [&](const Entry (&from)[U], const Chunk &c, auto block) {
             constexpr int I = decltype(block)::value * U;
-            add_one(from[0], row_lane<I>(c.left), row_lane<I>(c.a));
-            add_one(from[1], row_lane<I + 1>(c.left), row_lane<I + 1>(c.a));
-            add_one(from[2], row_lane<I + 2>(c.left), row_lane<I + 2>(c.a));
-            add_one(from[3], row_lane<I + 3>(c.left), row_lane<I + 3>(c.a));
+            add_one(from[0], row_lane<I>(c.left), row_lane<I>(c.a), OP == OP_CHEB ? row_lane<I>(c.met) : 0u);
+            add_one(from[1], row_lane<I + 1>(c.left), row_lane<I + 1>(c.a), OP == OP_CHEB ? row_lane<I + 1>(c.met) : 0u);
+            add_one(from[2], row_lane<I + 2>(c.left), row_lane<I + 2>(c.a), OP == OP_CHEB ? row_lane<I + 2>(c.met) : 0u);
+            add_one(from[3], row_lane<I + 3>(c.left), row_lane<I + 3>(c.a), OP == OP_CHEB ? row_lane<I + 3>(c.met) : 0u);
         };
         constexpr std::integral_constant<int, 0> b0{};
         constexpr std::integral_constant<int, 1> b1{};
@@ -498,13 +534,13 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 few.left[2] = row_lane<2>(c.left);
                 few.left[3] = row_lane<3>(c.left);
             }
-            add_one(x[0], row_lane<0>(c.left), row_lane<0>(c.a));
+            add_one(x[0], row_lane<0>(c.left), row_lane<0>(c.a), OP == OP_CHEB ? row_lane<0>(c.met) : 0u);
             if (total <= 4) return;
-            add_one(x[1], row_lane<1>(c.left), row_lane<1>(c.a));
+            add_one(x[1], row_lane<1>(c.left), row_lane<1>(c.a), OP == OP_CHEB ? row_lane<1>(c.met) : 0u);
             if (total <= 8) return;
-            add_one(x[2], row_lane<2>(c.left), row_lane<2>(c.a));
+            add_one(x[2], row_lane<2>(c.left), row_lane<2>(c.a), OP == OP_CHEB ? row_lane<2>(c.met) : 0u);
             if (total <= 12) return;
-            add_one(x[3], row_lane<3>(c.left), row_lane<3>(c.a));
+            add_one(x[3], row_lane<3>(c.left), row_lane<3>(c.a), OP == OP_CHEB ? row_lane<3>(c.met) : 0u);
             return;
         }
         fetch(y, c, b1);
@@ -542,12 +578,14 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         uint32_t first = min(y.first & ~kMatchDense, list_n);
         const bool dense = (y.first & kMatchDense) != 0u && match_walks<OP>(a) && first + (uint32_t)T <= list_n;
         const uint64_t dense_mask = __ballot(dense);
-        if (dense_mask != 0) {
-            if (KNN) few.total += 4 * U + 1;
-            walk_dense(values, first * 4u, a, dense_mask, scale, to);
+        if constexpr (OP != OP_CHEB) {
+            if (dense_mask != 0) {
+                if (KNN) few.total += 4 * U + 1;
+                walk_dense(values, first * 4u, a, dense_mask, scale, to);
+            }
         }
         const uint32_t last = match_walks<OP>(a) && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
-        walk_chunks(values, rows, first, last, a, scale, to, few);
+        walk_chunks(values, rows, first, last, a, y.met, scale, to, few);
         // (a lane reads later what other lanes of its wavefront wrote: LDS serves a wavefront in order, the
         // fence keeps the compiler to that order)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -566,6 +604,103 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     uint64_t queue = kKnnUnused;          // ... and `queued` keys that are not merged yet
     int queued = 0;
     bool any = false;
+    // Chebyshev: the distances of the 64 rows from `from` on, and of those `step` further ..., from the strip at `at`, whose places are
+    // cleared.  All of them are formed before the first is stored.
+    auto finish_ranked = [&](int tile, int row, int64_t a_begin, int a_len, uint32_t at, int from, int step) {
+      if constexpr (OP == OP_CHEB) {
+        constexpr int G = kRankedRows / kWave;
+        const int64_t j0 = (int64_t)tile * T;
+        const int tile_n = (int)min((int64_t)T, args.n - j0);
+        const float top_a = lane < kRanks ? args.tops_a[(size_t)row * kRanks + (size_t)lane] : 0.0f;
+        float d[G];
+        uint32_t doubt = 0u;                                     // (a bit a round) all of a row's largest entries were met, and smaller ones may exceed d
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            d[g] = 0.0f;
+            const int i = from + g * step + lane;
+            if (from + g * step >= T) continue;
+            const Acc c = S::get(at, plane, (uint32_t)i);
+            S::put(at, plane, (uint32_t)i, zero);
+            const uint32_t first_a = ~c.met_a ? (uint32_t)__builtin_ctz(~c.met_a) : (uint32_t)kRanks, first_b = ~c.met_b ? (uint32_t)__builtin_ctz(~c.met_b) : (uint32_t)kRanks;
+            const float next_a = __shfl(top_a, (int)min(first_a, (uint32_t)kRanks - 1u));
+            const float next_b = args.b.tops[(size_t)min(first_b, (uint32_t)kRanks - 1u) * (size_t)args.n + (size_t)(j0 + min(i, tile_n - 1))];
+            float most = __uint_as_float(c.m);
+            most = first_a < (uint32_t)kRanks ? fmaxf(most, next_a) : most;
+            most = first_b < (uint32_t)kRanks ? fmaxf(most, next_b) : most;
+            d[g] = most;
+            if ((first_a == (uint32_t)kRanks && next_a > most) || (first_b == (uint32_t)kRanks && next_b > most)) doubt |= 1u << g;
+        }
+        if (__ballot(doubt != 0u) != 0) {
+            // the largest entry of one row, beyond what the pair has, in a column that the other does not store: by the whole wavefront
+            auto beyond = [&](const int32_t *xi, const float *xv, int64_t x0, int64_t x1, const int32_t *yi, const float *yv, int64_t y0, int64_t y1, float most) {
+                // (rows that are all met are mostly alike: an entry is looked for at its own place in the other row first, then outwards)
+                for (int64_t e0 = x0 + lane; e0 < x1; e0 += 4 * kWave) {
+                    float v[4], w[4];
+                    int32_t col[4], at_guess[4];
+                    int64_t guess[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int64_t e = e0 + u * kWave;
+                        guess[u] = min(y0 + (e - x0), y1 - 1);
+                        v[u] = e < x1 ? fabsf(xv[e]) : 0.0f;
+                        col[u] = e < x1 ? xi[e] : 0;
+                        at_guess[u] = y0 < y1 ? yi[guess[u]] : -1;
+                        w[u] = y0 < y1 ? yv[guess[u]] : 0.0f;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (!(v[u] > most)) continue;
+                        if (at_guess[u] == col[u]) {
+                            if (w[u] == 0.0f) most = v[u];
+                            continue;
+                        }
+                        int64_t lo = y0, hi = y1, step = 1;
+                        if (at_guess[u] < col[u]) {
+                            lo = min(guess[u] + 1, y1);
+                            while (hi - lo > step && yi[lo + step] < col[u]) { lo += step + 1; step *= 2; }
+                            hi = min(hi, lo + step + 1);
+                        } else {
+                            hi = max(guess[u], y0);
+                            while (hi - lo > step && yi[hi - step] >= col[u]) { hi -= step; step *= 2; }
+                            lo = max(lo, hi - step);
+                        }
+                        while (lo < hi) {
+                            const int64_t mid = (lo + hi) >> 1;
+                            if (yi[mid] < col[u]) lo = mid + 1; else hi = mid;
+                        }
+                        if (!(lo < y1 && yi[lo] == col[u] && yv[lo] != 0.0f)) most = v[u];
+                    }
+                }
+#pragma unroll
+                for (int w = 32; w >= 1; w >>= 1) most = fmaxf(most, __shfl_xor(most, w));
+                return most;
+            };
+#pragma unroll 1
+            for (int g = 0; g < G; ++g) {
+                for (uint64_t left = __ballot((doubt >> g) & 1u); left; left &= left - 1) {
+                    const int l = (int)__builtin_ctzll(left), i = from + g * step + l;
+                    if (i >= tile_n) continue;
+                    const int64_t b0 = clamp_i64(args.b_indptr[j0 + i], 0, args.b_nnz), b1 = clamp_i64(args.b_indptr[j0 + i + 1], b0, args.b_nnz);
+                    float mine = 0.0f;
+#pragma unroll
+                    for (int u = 0; u < G; ++u) mine = u == g ? d[u] : mine;
+                    float most = __shfl(mine, l);
+                    most = beyond(args.a_indices, args.a_values, a_begin, a_begin + a_len, args.b_indices, args.b_values, b0, b1, most);
+                    most = beyond(args.b_indices, args.b_values, b0, b1, args.a_indices, args.a_values, a_begin, a_begin + a_len, most);
+#pragma unroll
+                    for (int u = 0; u < G; ++u) d[u] = u == g && lane == l ? most : d[u];
+                }
+            }
+        }
+        float *__restrict__ out = args.out + (size_t)row * (size_t)args.n + (size_t)j0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int i = from + g * step + lane;
+            if (i < tile_n) __builtin_nontemporal_store(d[g], out + i);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      }
+    };
     // The tile's distances from the wavefront's strip, in row order: one coalesced store per 64 rows; the
     // strip is clear again afterwards.  `flush`: the row's run of tiles ends here.
     auto finish = [&](int tile, int row, const RowOf &of, const Scale &scale, const Few &few, bool flush) {
@@ -871,7 +1006,9 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 }
                 __syncthreads();
             }
-            if constexpr (S::kAnyOrder && !KNN) {
+            if constexpr (OP == OP_CHEB) {
+                finish_ranked(tile, row, rw.start, len, owners_at, wave * kWave, nw * kWave);
+            } else if constexpr (S::kAnyOrder && !KNN) {
                 // (the distances by all wavefronts: by one they held the next row up; 10,000 x 10,000 rows of 38, L1, with the one strip 313 -> 298 us a call)
                 const RowOf of = load_row(row);
                 const int64_t j0 = (int64_t)tile * T;
@@ -892,7 +1029,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                     }
                 });
             } else if (wave == owner) {
-                finish(tile, row, load_row(row), scale, few, true);
+                if constexpr (OP != OP_CHEB) finish(tile, row, load_row(row), scale, few, true);
             }
             owner = owner + 1 < nw ? owner + 1 : 0;
         }
@@ -957,7 +1094,8 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         const Scale scale = scale_of<OP>(wave_uniform(p0.scale), p0.len);
         walk_lists(p0.tile, y, scale, strip_at, few);
         if (p0.e0 + kWave >= p0.len) {
-            finish(p0.tile, p0.row, of, scale, few, p0.tiles <= 1);
+            if constexpr (OP == OP_CHEB) finish_ranked(p0.tile, p0.row, p0.start, p0.len, strip_at, 0, kWave);
+            else finish(p0.tile, p0.row, of, scale, few, p0.tiles <= 1);
             few.total = 0;
         } else if (KNN) {
             few.total += 4 * U + 1;                             // (the entries of several batches are not at hand together)

@@ -699,3 +699,47 @@ def test_sums_in_fixed_point(spd, metric, n, long_every):
     else:
         bound = 2.0 ** -23 * np.abs(want) + units * (cols if metric == "correlation" else 1.0)
     assert np.all(np.abs(got - want) <= bound), float((np.abs(got - want) / bound).max())
+
+
+@pytest.mark.parametrize("m,n,cols,lengths_a,lengths_b", [
+    (1, 1, 5, (3,), (4,)), (3, 63, 70, (1, 7, 0), (1, 0, 2, 40)),
+    (70, 65, 200, (31, 32, 33, 64, 65, 130, 0), (31, 32, 33, 2, 100)),           # all the ranked entries of a row and one more
+    (40, 2_600, 300, (40, 2, 90, 64), (5, 0, 40, 9, 33)),                        # several tiles, the last one short
+    (20, 1_700, 3_003, (2_900, 1_300, 700, 5, 0), (30, 3, 900)),                 # rows that wavefronts share
+])
+def test_chebyshev_by_lists(spd, m, n, cols, lengths_a, lengths_b):
+    """The maximum over shared columns completed from the largest entry that the other row does not store: ranks at their end, rows
+    all of whose ranked entries are met (B holds rows of A, and some of them with small entries left out or added), entries that
+    tie, stored zeros, either sign.  The staged scan's bits: both take maxima of the same differences."""
+    rng = np.random.default_rng(cols + n)
+    A, B = _matrix(rng, m, cols, lengths_a), _matrix(rng, n, cols, lengths_b)
+    for M in (A, B):
+        M["values"] *= rng.choice(np.array([-1.0, 1.0], np.float32), size=len(M["values"]))
+
+    def rows_of(M):
+        return [(M["indices"][M["indptr"][r]:M["indptr"][r + 1]], M["values"][M["indptr"][r]:M["indptr"][r + 1]]) for r in range(M["n_rows"])]
+
+    rows = rows_of(B)
+    for at, r in enumerate(range(0, m, 3)):                # copies of rows of A, whole, without their least entry, and with one more
+        c, v = rows_of(A)[r]
+        if at % 3 == 1 and len(c):
+            keep = np.arange(len(c)) != np.argmin(np.abs(v))
+            c, v = c[keep], v[keep]
+        elif at % 3 == 2 and len(c) < cols:
+            more = int(np.setdiff1d(np.arange(cols), c)[0])
+            where = int(np.searchsorted(c, more))
+            c, v = np.insert(c, where, more), np.insert(v, where, np.float32(1.0 / 16.0))
+        rows[(at * 7 + 1) % n] = (c, v)
+    B = {"n_rows": n, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum([len(c) for c, _ in rows])]).astype(np.int64),
+         "indices": np.concatenate([c for c, _ in rows]).astype(np.int32), "values": np.concatenate([v for _, v in rows]).astype(np.float32)}
+    print("chebyshev by lists", m, n, cols, flush=True)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h, staged = _lists(spd, profile=1), _lists(spd, match_lists=0)
+    got = _np(h.pairwise(dA, dB, "chebyshev"))
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    assert_distances_close(got, oracle.pairwise(A, B, "chebyshev"), "chebyshev")
+    assert np.array_equal(got, _np(staged.pairwise(dA, dB, "chebyshev")))
+    idx, dist = h.knn(dA, dB, "chebyshev", min(n, 5))      # (by the scan)
+    assert np.array_equal(_np(dist), np.sort(got, axis=1)[:, :min(n, 5)])
+    h.close()
+    staged.close()
