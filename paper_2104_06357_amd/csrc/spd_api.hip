@@ -579,6 +579,8 @@ MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int64_t m, int
 int64_t match_items(const MatchShape &s, const MatchGrid &g, int64_t m) {
     return ((m + g.slices - 1) / g.slices) * ((s.n_tiles + g.groups - 1) / g.groups);
 }
+// Counters and locks that go up with A's rows, all 0 (MatchArgs::next).
+size_t match_counters_bytes(const MatchGrid &g, bool knn) { return (size_t)g.groups * (knn ? 1 + kMatchRowLocks : 1) * 4; }
 struct ColumnsLayout { size_t words, sums, totals, masks, before, a_indices, b_indptr, b_indices, b_values; };
 struct MatchScratch { MatchLayout b; ColumnsLayout c; size_t rows, norms_a, scales_a, ranks_a, tops_a, tau, part, row_off, row_lists, end; };
 // `columns`: 0, or the operands' column count where both are copied over A's columns first (spd_match_columns.hip).
@@ -599,7 +601,7 @@ MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int op, 
         L.c.b_indices = cv.take((size_t)nnz_b * 4);
         L.c.b_values = cv.take((size_t)nnz_b * 4);
     }
-    L.rows = cv.take((size_t)m * sizeof(MatchRow));
+    L.rows = cv.take((size_t)m * sizeof(MatchRow) + match_counters_bytes(g, knn_k > 0));       // (the counters behind them)
     L.norms_a = cv.take((size_t)m * 16);
     L.scales_a = cv.take((size_t)m * 2);
     if (op == OP_CHEB) {
@@ -896,7 +898,8 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     spd_status st = SPD_OK;
     // A's rows, longest first (to within an eighth of their length): a counting sort into the pinned buffer
     int64_t shared = 0;
-    st = ensure_pinned(h, align256(ip_bytes) + (size_t)m * sizeof(MatchRow));
+    const size_t rows_bytes = (size_t)m * sizeof(MatchRow) + match_counters_bytes(g, knn_k > 0);
+    st = ensure_pinned(h, align256(ip_bytes) + rows_bytes);
     if (st != SPD_OK) return st;
     MatchRow *rows = reinterpret_cast<MatchRow *>(reinterpret_cast<unsigned char *>(h->pinned) + align256(ip_bytes));
     {
@@ -919,7 +922,8 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
         const std::string why = match_check_rows(rows, m, shared, g.shared_len, a_ip);
         if (!why.empty()) return fail(h, SPD_ERR_UNSUPPORTED, "internal plan check failed: " + why);
     }
-    e = hipMemcpyAsync(ws + L.rows, rows, (size_t)m * sizeof(MatchRow), hipMemcpyHostToDevice, h->stream);
+    std::memset(rows + m, 0, match_counters_bytes(g, knn_k > 0));
+    e = hipMemcpyAsync(ws + L.rows, rows, rows_bytes, hipMemcpyHostToDevice, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "upload of A's rows");
     MatchArgs a;
     a.a_indices = start.a_indices;
@@ -940,6 +944,7 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     a.transform = mi.transform;
     a.q = q;
     a.m_shared = (int32_t)shared;
+    a.next = reinterpret_cast<uint32_t *>(ws + L.rows + (size_t)m * sizeof(MatchRow));
     a.slices = g.slices;
     a.groups = g.groups;
     a.by_xcd = g.by_xcd;

@@ -80,6 +80,7 @@ struct MatchArgs {
     int32_t transform;
     OpParams q;
     int32_t m_shared;             // the first rows, which the wavefronts of a workgroup share
+    uint32_t *next;               // per group, 0 before the launch: (tile, row)s of these rows that are taken; k-NN: behind them kMatchRowLocks locks a group
     int32_t slices, groups;       // grid: groups of tiles (g, g + groups, ...) x slices of A's rows (s, s + slices, ...)
     int32_t by_xcd;               // 1: the slices of a group share an XCD
     int32_t run;                  // tiles of its group that a wavefront goes through with a row
@@ -103,6 +104,7 @@ struct MatchColumns {
 
 constexpr int64_t kMatchMostColumns = 1 << 28;    // that are renumbered (16 bytes per 64 of them)
 constexpr uint32_t kBuildDense = 32;            // dense columns of a block at most
+constexpr int kMatchRowLocks = 64;              // of a group, by row
 constexpr int kMatchStagingKind = 6;            // how spd_profile_read names this kernel's staging
 constexpr int64_t kMatchL2Bytes = 4 << 20;      // of one XCD
 // Bytes that a pair's sums take in a strip: its doubles and its count.

@@ -702,8 +702,9 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
       }
     };
     // The tile's distances from the wavefront's strip, in row order: one coalesced store per 64 rows; the
-    // strip is clear again afterwards.  `flush`: the row's run of tiles ends here.
-    auto finish = [&](int tile, int row, const RowOf &of, const Scale &scale, const Few &few, bool flush) {
+    // strip is clear again afterwards.  `flush`: the row's run of tiles ends here; `lock`: k-NN, of a row that other workgroups
+    // take in other tiles, else null.
+    auto finish = [&](int tile, int row, const RowOf &of, const Scale &scale, const Few &few, bool flush, int *lock) {
         int lane = (int)threadIdx.x & 63;                         // (hidden from the compiler: it would keep the addresses of every loop below
         asm volatile("" : "+v"(lane));                            // in registers through the whole kernel, 50 more than there are)
         const int64_t j0 = (int64_t)tile * T;
@@ -939,25 +940,31 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             if (flush && any) {
                 merge();                                          // (what is queued joins the run's list, if it has one)
                 // into the row's list of this group, under a lock (two wavefronts of the workgroup may be at one row, in
-                // different tiles); the holder waits for nothing
-                int *lock = &s_lock[row & (kMatchLocks - 1)];
+                // different tiles, or of several workgroups, where the lock lies in memory); the holder waits for nothing
+                const bool in_memory = lock != nullptr;
+                int *const row_lock = &s_lock[row & (kMatchLocks - 1)];
                 int first_lane = lane;
                 asm volatile("" : "+v"(first_lane));              // (see the claim below)
                 if (first_lane == 0) {
                     int spins = 0;
-                    while (atomicCAS(lock, 0, 1) != 0 && ++spins < kKnnLockSpins) __builtin_amdgcn_s_sleep(1);
+                    if (in_memory) {
+                        while (atomicCAS(lock, 0, 1) != 0 && ++spins < kKnnLockSpins) __builtin_amdgcn_s_sleep(1);
+                    } else {
+                        while (atomicCAS(row_lock, 0, 1) != 0 && ++spins < kKnnLockSpins) __builtin_amdgcn_s_sleep(1);
+                    }
                 }
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                if (in_memory) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
                 KnnEntry *part = args.knn_part + ((size_t)row * (size_t)args.groups + (size_t)group) * (size_t)k;
                 const uint64_t theirs = lane < k ? knn_key(part[lane].d, part[lane].j) : kKnnUnused;
                 const uint64_t turned = wave_reverse(theirs);
                 best = wave_merge_asc(turned < best ? turned : best, lane);
                 if (lane >= k) best = kKnnUnused;
                 if (lane < k) part[lane] = KnnEntry{float_from_order_key((uint32_t)(best >> 32)), (int)(uint32_t)best};
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                if (in_memory) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent"); else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 const uint64_t now = kth_of(best, k - 1);
                 if (first_lane == 0) {
-                    __atomic_store_n(lock, 0, __ATOMIC_RELAXED);
+                    if (in_memory) __hip_atomic_store(lock, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    else __atomic_store_n(row_lock, 0, __ATOMIC_RELAXED);
                     if (now < kKnnUnused) atomicMin(&args.knn_tau[row], (unsigned long long)now);
                 }
             }
@@ -974,9 +981,23 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // ---- the longest rows: an even share of the row to each wavefront ---------------------------------
     // (a wavefront alone would hold its workgroup up long after the others are done)
     int owner = 0;
-    for (int ti = 0; ti < my_tiles; ++ti) {
+    // With integer sums a workgroup takes a (tile, row) of its group after another, the longest rows of a tile first: the slice that has
+    // the longest row of all would be the last by far, and the workgroups of an XCD would drift apart in their tiles.  (1,531 x 28,301
+    // ratings, Canberra, 488 -> 404 us; 4,096 x 500,000 sets, Jaccard, k-NN 8.46 -> 7.65 ms.)  Not with k-NN over few tiles: a row's first
+    // tiles would be gone through at once, without a bound (10,000 x 10,000 rows of 38, cosine 510 -> 579 us).
+    const bool taken = S::kAnyOrder && (!KNN || args.by_xcd != 0);
+    __shared__ int s_item[2];
+    int item = 0, turn = 0;
+    if (taken && args.m_shared > 0) {
+        if (tid == 0) s_item[0] = (int)atomicAdd(&args.next[group], 1u);
+        __syncthreads();
+        item = s_item[0];
+    }
+    for (int ti = taken ? item / max(args.m_shared, 1) : 0; ti < my_tiles;) {
         const int tile = group + ti * args.groups;
-        for (int at = slice; at < args.m_shared; at += args.slices) {
+        for (int at = taken ? item - ti * args.m_shared : slice; at < args.m_shared; at += args.slices) {
+            int next = 0;
+            if (taken && tid == 0) next = (int)atomicAdd(&args.next[group], 1u);
             const MatchRow rw = args.rows[at];
             const int row = wave_uniform(rw.row), len = wave_uniform(rw.len);
             const int begin = (int)((int64_t)len * wave / nw), end = (int)((int64_t)len * (wave + 1) / nw);
@@ -992,6 +1013,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 walk_lists(tile, y, scale, S::kAnyOrder ? owners_at : strip_at, few);
             }
             few.total = 4 * U + 1;
+            if (taken && tid == 0) s_item[turn ^ 1] = next;
             __syncthreads();
             if constexpr (!S::kAnyOrder) {
                 for (int i = tid; i < T; i += nw * kWave) {
@@ -1029,12 +1051,18 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                     }
                 });
             } else if (wave == owner) {
-                if constexpr (OP != OP_CHEB) finish(tile, row, load_row(row), scale, few, true);
+                if constexpr (OP != OP_CHEB) finish(tile, row, load_row(row), scale, few, true, taken ? reinterpret_cast<int *>(args.next) + args.groups + group * kMatchRowLocks + (row & (kMatchRowLocks - 1)) : nullptr);
             }
             owner = owner + 1 < nw ? owner + 1 : 0;
+            if (taken) {
+                turn ^= 1;
+                item = s_item[turn];
+                break;
+            }
         }
+        ti = taken ? (args.m_shared > 0 ? item / args.m_shared : my_tiles) : ti + 1;
     }
-    if (S::kAnyOrder && !KNN && args.m_shared > 0) __syncthreads();          // (a strip may be another wavefront's to clear)
+    if (taken && !KNN && args.m_shared > 0) __syncthreads();          // (a strip may be another wavefront's to clear)
 
     // ---- the other rows: one wavefront each, no waiting for one another ------------------------------
     const int rows_here = args.m - args.m_shared > slice ? (args.m - args.m_shared - slice + args.slices - 1) / args.slices : 0;
@@ -1095,7 +1123,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         walk_lists(p0.tile, y, scale, strip_at, few);
         if (p0.e0 + kWave >= p0.len) {
             if constexpr (OP == OP_CHEB) finish_ranked(p0.tile, p0.row, p0.start, p0.len, strip_at, 0, kWave);
-            else finish(p0.tile, p0.row, of, scale, few, p0.tiles <= 1);
+            else finish(p0.tile, p0.row, of, scale, few, p0.tiles <= 1, nullptr);
             few.total = 0;
         } else if (KNN) {
             few.total += 4 * U + 1;                             // (the entries of several batches are not at hand together)
