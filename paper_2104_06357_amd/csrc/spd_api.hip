@@ -165,7 +165,7 @@ struct spd_index {
     void *dev = nullptr;
     size_t dev_bytes = 0;
     BDevice bd;
-    MatchB match{};              // the column lists of the same rows, where the product has them (list == nullptr: none)
+    MatchB match{};              // the column lists of the same rows, where the product has them (values == nullptr: none)
     void *match_dev = nullptr;
     int match_op = -1;
 };

@@ -7,7 +7,8 @@
 // call).  A wavefront takes one row of A, walks the lists of that row's columns only, and adds
 // product(a, b) to one sum per row of the tile, which lie in its own strip of LDS.  Work is done for
 // the columns that two rows share and for nothing else.  The lists are walked in chunks of 16 entries,
-// four chunks of any lists to a step.  A strip is private to its wavefront.  Sums in floating point are formed in the order of A's
+// four chunks of any lists to a step.  A strip is private to its wavefront, but for the longest rows
+// where sums are integers.  Sums in floating point are formed in the order of A's
 // columns (a row of B appears at most once in a list, and lanes that meet in one sum are served in ascending order, which
 // is that order), sums in fixed point come out the same in any order: the results do not depend on the schedule.
 #pragma once
