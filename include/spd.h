@@ -26,7 +26,9 @@
  *    stream at all, so the planning of one call runs while the kernels of the one before it do.
  *    A host copy that differs from the device array gives wrong results (its last entry is
  *    checked against nnz, and no access leaves the arrays).
- *  - Sums are carried in fp64, or in 64-bit fixed point that rounds no coarser, and rounded once.  The order of a pair's terms, and with it the last place of
+ *  - Sums are carried in fp64 and rounded once.  (L1 and Canberra by the column lists: in 64-bit fixed point, whose unit is 2^-51 of a
+ *    row's largest entry, or of its sum over 512 if that is more, and for Canberra 2^-49, or 2^-58 of a row's length from 1,024 entries on.
+ *    What reaches below a unit is rounded to half of one.)  The order of a pair's terms, and with it the last place of
  *    its distance, depends on the way the call is computed (option "match_lists") and on how it is cut, that is
  *    on the sizes of both operands, the options and the scratch; equal calls give equal bits.
  *  - Scratch memory comes from the handle's own grow-only allocation, or from the caller

@@ -520,7 +520,7 @@ int product_of(const spd_handle *h, int metric, float p) {
     return op;
 }
 
-struct MatchLayout { size_t values, rows, ptr, norms, least, scales, ranks, tops, end; };
+struct MatchLayout { size_t values, rows, ptr, norms, least, ranks, tops, end; };
 MatchLayout layout_match(const MatchShape &s, int op, int64_t n, int64_t nnz, Carver &cv) {
     MatchLayout L;
     L.values = cv.take((size_t)s.list_entries(nnz) * 4);
@@ -530,7 +530,6 @@ MatchLayout layout_match(const MatchShape &s, int op, int64_t n, int64_t nnz, Ca
     L.ptr = cv.take((size_t)s.n_tiles * (size_t)s.ptr_stride * 4);
     L.norms = cv.take((size_t)n * 16);
     L.least = cv.take((size_t)s.n_tiles * 16);
-    L.scales = cv.take((size_t)n * 2);
     L.ranks = L.tops = 0;
     if (op == OP_CHEB) {
         L.ranks = cv.take((size_t)nnz);
@@ -542,8 +541,7 @@ MatchLayout layout_match(const MatchShape &s, int op, int64_t n, int64_t nnz, Ca
 MatchB match_b_at(const MatchShape &s, const MatchLayout &L, unsigned char *dev) {
     return MatchB{reinterpret_cast<float *>(dev + L.values), reinterpret_cast<uint16_t *>(dev + L.rows), reinterpret_cast<uint32_t *>(dev + L.ptr),
                   reinterpret_cast<double *>(dev + L.norms), reinterpret_cast<double *>(dev + L.least),
-                  L.tops ? reinterpret_cast<uint8_t *>(dev + L.ranks) : nullptr, reinterpret_cast<float *>(dev + L.tops),
-                  reinterpret_cast<int16_t *>(dev + L.scales), s, nullptr};
+                  L.tops ? reinterpret_cast<uint8_t *>(dev + L.ranks) : nullptr, reinterpret_cast<float *>(dev + L.tops), s, nullptr};
 }
 // Grid of the column-list kernel: groups of tiles times slices of A's rows, one workgroup for each
 // compute unit of the chip.  Where the lists are more than the L2 caches hold, the tiles are dealt to the
@@ -603,7 +601,7 @@ MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int op, 
     }
     L.rows = cv.take((size_t)m * sizeof(MatchRow) + match_counters_bytes(g, knn_k > 0));       // (the counters behind them)
     L.norms_a = cv.take((size_t)m * 16);
-    L.scales_a = cv.take((size_t)m * 2);
+    if (op == OP_L1) L.scales_a = cv.take((size_t)m * 2);
     if (op == OP_CHEB) {
         L.ranks_a = cv.take((size_t)nnz_a);
         L.tops_a = cv.take((size_t)m * kRanks * 4);
@@ -630,7 +628,7 @@ std::string match_check(const PlanOptions &opt, const MatchShape &s, const Match
     if (s.dense_per_block < 1 || s.dense_per_block > (int32_t)kBuildDense || s.dense_from < 1 ||
         s.dense_from > T + 1 || s.tile_extra != blocks * s.dense_per_block * s.dense_room()) return "dense columns";
     if (s.list_entries(nnz_b) >= (int64_t)1 << 29) return "list positions";
-    const int64_t build = (int64_t)s.stage * 6 + ((int64_t)4 << s.block_shift) + 14 * T;
+    const int64_t build = (int64_t)s.stage * 6 + ((int64_t)4 << s.block_shift) + 12 * T;
     if ((int64_t)s.build_lds_bytes != build || s.stage % 8 != 0 || build + 1024 > opt.lds_budget) return "build over the LDS";
     if (g.slices < 1 || g.groups < 1 || g.run < 1 || g.run > tiles || g.groups > tiles || (g.by_xcd && g.groups < tiles && g.groups % 8 != 0)) return "grid";
     if (match_items(s, g, m) >= (int64_t)1 << 30) return "(tile, row)s of a workgroup";
@@ -806,20 +804,20 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
 
 
 // The norms of B's rows, and their lists.
-spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int op, int metric, const MetricInfo &mi, const OpParams &q) {
+spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int metric, const MetricInfo &mi, const OpParams &q) {
     LaunchTimer norms(h, "norms_b", 0, 0, 0, 0, 0, 0);
-    hipError_t e = launch_match_norms(h->stream, B->indptr, B->values, B->n_rows, B->nnz, op, metric, mi.transform, mi.norm, q.p, q.k, false,
-                                      mb.norms, mb.scales);
+    hipError_t e = launch_match_norms(h->stream, B->indptr, B->values, B->n_rows, B->nnz, metric, mi.transform, mi.norm, q.p, q.k,
+                                      mb.norms, nullptr);
     if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
     norms.done();
     return SPD_OK;
 }
 // (`knn`: and each tile's row of the least norm)
-spd_status stage_lists(spd_handle *h, const spd_csr *B, MatchB mb, int op, int metric, const MetricInfo &mi, bool knn) {
+spd_status stage_lists(spd_handle *h, const spd_csr *B, MatchB mb, int op, const MetricInfo &mi, bool knn) {
     if (!knn) mb.least = nullptr;
     LaunchTimer lists(h, "lists_b", 0, 0, 0, 0, 0, mb.shape.n_tiles);
     hipError_t e = launch_match_build(h->stream, B->indptr, B->indices, B->values, B->n_rows, B->nnz, (uint32_t)B->n_cols, mb,
-                           op, metric, mi.transform);
+                           op, mi.transform);
     if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
     lists.done();
     return SPD_OK;
@@ -853,7 +851,7 @@ spd_status start_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int me
             if (e != hipSuccess) return hip_fail(h, e, "rank kernel");
             lt.done();
         } else {
-            st = stage_norms(h, B, start.b, op, metric, mi, q);
+            st = stage_norms(h, B, start.b, metric, mi, q);
         }
         if (st != SPD_OK) return st;
         if (compact) {
@@ -873,13 +871,13 @@ spd_status start_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int me
             start.listed.n_cols = way.columns;
             start.b.cols = c.totals;
         }
-        st = stage_lists(h, &start.listed, start.b, op, metric, mi, knn_k > 0);
+        st = stage_lists(h, &start.listed, start.b, op, mi, knn_k > 0);
         if (st != SPD_OK) return st;
     }
     if (op == OP_CHEB) return SPD_OK;
     LaunchTimer lt(h, "norms_a", 0, 0, 0, 0, 0, 0);
-    e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, op, metric, mi.transform, mi.norm, q.p, q.k, true,
-                           reinterpret_cast<double *>(ws + L.norms_a), reinterpret_cast<int16_t *>(ws + L.scales_a));
+    e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, metric, mi.transform, mi.norm, q.p, q.k,
+                           reinterpret_cast<double *>(ws + L.norms_a), op == OP_L1 ? reinterpret_cast<int16_t *>(ws + L.scales_a) : nullptr);
     if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
     lt.done();
     return SPD_OK;
@@ -939,6 +937,7 @@ spd_status run_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metr
     a.b_indptr = start.listed.indptr;
     a.b_nnz = B->nnz;
     a.b = start.b;
+    a.norms_b = start.b.norms + (metric == MT_COSINE ? n : 0);
     a.n = n;
     a.k = (uint32_t)way.columns;
     a.transform = mi.transform;
@@ -1811,8 +1810,8 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         if (hipMalloc(&ix->match_dev, lists.end) == hipSuccess) {
             ix->match = match_b_at(shape, lists, reinterpret_cast<unsigned char *>(ix->match_dev));
             ix->match_op = op;
-            st = stage_norms(h, Index, ix->match, op, run_as, mi, q);
-            if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, run_as, mi, true);
+            st = stage_norms(h, Index, ix->match, run_as, mi, q);
+            if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, mi, true);
             if (st != SPD_OK) return st;
         } else {                         // (no memory left for the lists: the packed copy serves every call)
             ix->match_dev = nullptr;

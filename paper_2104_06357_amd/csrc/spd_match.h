@@ -56,7 +56,6 @@ struct MatchB {
     double *least;          // n_tiles * 2: the norms of a tile's row of the least first norm (k-NN)
     uint8_t *ranks;         // Chebyshev: of B's entries, kRanks or more where it is not among the row's kRanks largest
     float *tops;            // ... kRanks * n: the rows' largest magnitudes, the first of all rows, the second ..., 0 where a row has no more
-    int16_t *scales;        // n: the exponents of the rows whose values are listed over a power of two (match_fixed), else not used
     MatchShape shape;
     const uint32_t *cols;   // nullptr, or on the device how many columns there are (no more than the shape was made for)
 };
@@ -68,7 +67,8 @@ struct MatchArgs {
     const MatchRow *rows;
     int32_t m;
     const double *norms_a;        // 2 * m, derived, likewise
-    const int16_t *scales_a;      // m: exponents, see match_fixed
+    const double *norms_b;        // k-NN: those of B's that distances read first (norms_read), the first ones or the second ones
+    const int16_t *scales_a;      // m: L1, the rows' exponents (match_fixed)
     const uint8_t *ranks_a;       // Chebyshev: of A's entries, and kRanks magnitudes of every row, one row after the other
     const float *tops_a;
     const int32_t *b_indices;     // ... and B's rows, for the pairs whose kRanks largest entries of a row were all met
@@ -121,33 +121,32 @@ SPD_HD constexpr int match_waves(int cell_bytes) { return cell_bytes >= 16 ? 12 
 // Upper bound of the kernel's static __shared__ use (64 half words to a wavefront, the locks).
 SPD_HD constexpr int64_t match_static_lds(int cell_bytes) { return 256 + match_waves(cell_bytes) * 128; }
 // Sums in fixed point.  An LDS add of 64 doubles at random rows takes 25.3 clocks, of 64 integers of 64 bits 12.8 (8.1 and 6.2 without
-// bank conflicts).  A term is scaled by a power of two and added to 2 in fp64 (to 3 where it may be negative), so that its last place is
+// bank conflicts).  A term is scaled by a power of two and added to 2 in fp64, so that its last place is
 // 2^-51: the words of such a sum count units of 2^-51, and adding them up as integers rounds no further.
 //   L1         the scale 2^-e is the row of A's: no shared entry's min(|a|, |b|) reaches 2^(e + 1), and all of them together not 2^(e + 10).
 //   Canberra   2 less the ratio, at most 2: e = 2, more for rows of A of more than 2^10 entries.
-//   dot        rows of either side are scaled by a power of two (exact) that brings their largest entry below 1 and their
-//              length below 2^5; a product is below 1 and their sum below 2^10.
-// A term is rounded to half a unit: 2^-52 of the row's largest entry (of both rows' for the dot product) where the rows have
-// up to some 1,000 entries that are alike; a sum in fp64 is rounded with every term, to 2^-53 of what it has come to.  What the distances are
-// formed from does not fall below the rows' norms, so this is as good; an inner product by itself may be far below
-// them, and its sum (and that of the 0/1 values of the set metrics as a dot product) stays in floating point.
-SPD_HD constexpr bool match_fixed(int op, int metric) {
-    return op == OP_L1 || op == OP_CANB ||
-           (op == OP_DOT && (metric == MT_COSINE || metric == MT_L2 || metric == MT_CORRELATION || metric == MT_HELLINGER));
-}
-// ... and the products whose sums are integers, but for inner products.
-SPD_HD constexpr bool match_any_order(int op) { return op == OP_L1 || op == OP_CANB || op == OP_DOT || op == OP_HAMM || op == OP_CNT; }
+// A term has 24 bits, and a sum is exact while none reaches below a unit: L1 of rows whose entries lie within 2^28 of their largest (fp64: within
+// 2^29, less the sum's growth), Canberra of rows of up to 1,023 entries (a ratio is 0 or 2^-25 at least).  Beyond that a term is
+// rounded to half a unit, where a sum in fp64 is rounded with every term, to 2^-53 of what it has come to: L1 of rows whose entries lie
+// 2^40 apart, 0.8 to 7e-15 of the rows' norms with fixed point and 0.2 to 2.6e-15 with fp64; Canberra of 24,000 entries
+// has units of 2^-44, and a distance of such a row an ulp of 2^-38.
+// Not the dot product: its terms have 48 bits, so that each is rounded, to 2^-52 of both rows' largest entries, where the norms it is
+// set against are fp64 sums.  Euclidean distances of equal rows of 37 normal values came out as 3.5e-8 of the norm for
+// 9e-9, rows of two values as 7e-9 for 0.
+SPD_HD constexpr bool match_fixed(int op) { return op == OP_L1 || op == OP_CANB; }
+// ... and the products whose sums are counts.
+SPD_HD constexpr bool match_any_order(int op) { return match_fixed(op) || op == OP_HAMM || op == OP_CNT; }
 // floor(log2 v), -1023 for 0, 1,024 for what is not finite.
 SPD_HD int match_ilog2(double v) {
     uint64_t w;
     __builtin_memcpy(&w, &v, 8);
     return (int)((w >> 52) & 0x7ffu) - 1023;
 }
-// A row's exponent from its largest entry and (L1) the sum or (dot) the sum of squares of its entries.  In [-200, 200]; 0 for a row of zeros.
-SPD_HD int match_scale(int op, float largest, double sum) {
+// L1's exponent for a row of A from its largest entry and the sum of them.  In [-200, 200]; 0 for a row of zeros.
+SPD_HD int match_scale(float largest, double sum) {
     if (!(sum > 0.0) || !(largest > 0.0f)) return 0;
     const int top = match_ilog2((double)largest), all = match_ilog2(sum);
-    const int e = op == OP_L1 ? (top > all - 9 ? top : all - 9) : (top + 1 > (all >> 1) - 4 ? top + 1 : (all >> 1) - 4);
+    const int e = top > all - 9 ? top : all - 9;
     return e < -200 ? -200 : (e > 200 ? 200 : e);
 }
 // Canberra's for a row of A of `len` entries: 2 len 2^(51 - e) below 2^62.
@@ -167,16 +166,15 @@ SPD_HD constexpr bool match_serves_knn(int op) { return match_serves(op) && op !
 // Whether the launches for a call's lists, of which A has m rows, are below 2^32 work-items each (`renumbered`: over A's columns).
 bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renumbered);
 
-// `op`: the product, for the rows' scales (nullptr: not asked for); `queries`: the rows are A's, whose scaled norms carry the
-// unit of the sums too.
+// (`scales` nullptr: not asked for)
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
-                              int op, int metric, int transform, int norm, float p, double k, bool queries, double *norms, int16_t *scales);
+                              int metric, int transform, int norm, float p, double k, double *norms, int16_t *scales);
 // Ranks and largest magnitudes of two operands' rows (`by_row`: the magnitudes of a row one after the other, else in planes).
 struct RankedRows { const int64_t *indptr; const float *values; int64_t n_rows, nnz; int by_row; uint8_t *ranks; float *tops; };
 hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const RankedRows &second);
 // (after the norms; `b.least` nullptr: not asked for)
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
-                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int metric, int transform);
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int transform);
 hipError_t launch_match_columns(hipStream_t st, const int32_t *a_indices, int64_t a_nnz, const int64_t *b_indptr, const int32_t *b_indices,
                                 const float *b_values, int64_t b_rows, int64_t b_nnz, uint32_t n_cols, const MatchColumns &c);
 // k-NN: the rows' bounds, and where each row's candidate lists lie.

@@ -13,8 +13,8 @@ namespace spd {
 // ------------------------------------------------------------------------------------
 template <int G>
 __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__restrict__ indptr, const float *__restrict__ values,
-                                                              int64_t n_rows, int64_t nnz, int op, int metric, int transform, int norm,
-                                                              float p, double k, int unit_log2, double *__restrict__ norms,
+                                                              int64_t n_rows, int64_t nnz, int metric, int transform, int norm,
+                                                              float p, double k, double *__restrict__ norms,
                                                               int16_t *__restrict__ scales) {
     constexpr int kRows = 256 / G;
     constexpr int64_t kLong = G < 256 ? 64 * G : INT64_MAX;
@@ -43,16 +43,7 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
     auto write = [&](int64_t r, double s0, double s1, float most) {
         double d0, d1;
         norm_derive(metric, k, s0, s1, d0, d1);
-        if (scales) {
-            const int e = match_scale(op, most, norm == NORM_SUM_SUMSQ ? s1 : s0);
-            scales[r] = (int16_t)e;
-            // (of rows that are scaled by 2^-e, the sum of the queries' in units of 2^unit_log2)
-            if (op == OP_DOT) {
-                if (metric == MT_L2 || metric == MT_HELLINGER) d1 = 1.0;               // (B's scale is read itself)
-                if (metric == MT_CORRELATION) d0 = ldexp(d0, -(e + unit_log2));
-                d1 = ldexp(d1, e + unit_log2);
-            }
-        }
+        if (scales) scales[r] = (int16_t)match_scale(most, s0);
         norms[r] = d0;
         norms[n_rows + r] = d1;
     };
@@ -224,7 +215,7 @@ template <int G>
 __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                         const float *__restrict__ values, int64_t n_rows, int64_t nnz,
                                                                         uint32_t most_cols, MatchB b, uint32_t blocks_per_wg, uint32_t wgs, int unit,
-                                                                        int transform, bool scaled, bool with_values) {
+                                                                        int transform, bool with_values) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     __shared__ uint32_t s_wave[kBuildThreads / kWave];
     __shared__ uint32_t s_dense[kBuildDense], s_long[kBuildLong], s_longs;
@@ -257,7 +248,6 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     uint32_t *s_cur = s_count + block_cols;                                   // where a row's block begins ...
     uint32_t *s_next = s_cur + T;                                                   // ... and the next one
     uint32_t *s_end = s_next + T;
-    int16_t *s_scale = reinterpret_cast<int16_t *>(s_end + T);
     uint32_t *ptr = b.ptr + (size_t)tile * (size_t)shape.ptr_stride;
     if (part == 0 && b.least) tile_least(b.norms + j0, b.norms + n_rows + j0, rows, b.least + (size_t)tile * 2, s_least);
     const uint32_t block_first = (uint32_t)part * blocks_per_wg;
@@ -294,7 +284,6 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             }
             s_cur[r] = lo;
             s_end[r] = end;
-            s_scale[r] = scaled ? b.scales[j0 + r] : (int16_t)0;
             mine += lo - begin;
         }
 #pragma unroll
@@ -446,23 +435,23 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         // place
         auto place = [&](uint32_t c, float v, int r, uint32_t rank) {
             if (c - c0 >= range) return;
-            const float t = transform_value(transform, v), scaled_t = __builtin_ldexpf(t, -(int)s_scale[r]);
+            const float t = transform_value(transform, v);
             uint32_t *count = &s_count[c - c0];
             uint32_t at = *count & ~kMatchDense;
             if (*count & kMatchDense) {
                 at += (uint32_t)r;
-                if (at < shape.stage) s_value[at] = scaled_t;
-                else if (at < room) values_at[at] = scaled_t;
+                if (at < shape.stage) s_value[at] = t;
+                else if (at < room) values_at[at] = t;
             } else {
                 // (a stored zero is absent: it goes to the spare row behind the tile's)
                 const uint16_t cell = (uint16_t)((uint32_t)(t != 0.0f ? r : T) * (uint32_t)unit + (min(rank, 2u * kRanks - 1u) << kRankShift));
                 at = atomicAdd(count, 1u);
                 if (at < shape.stage) {
                     s_row[at] = cell;
-                    s_value[at] = scaled_t;
+                    s_value[at] = t;
                 } else if (at < room) {
                     rows_at[at] = cell;
-                    values_at[at] = scaled_t;
+                    values_at[at] = t;
                 }
             }
         };
@@ -549,13 +538,13 @@ int match_norm_lanes(int64_t n_rows, int64_t nnz) {
     return mean >= 128 && n_rows <= 8192 ? 256 : (mean >= 16 ? 64 : 4);
 }
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
-                              int op, int metric, int transform, int norm, float p, double k, bool queries, double *norms, int16_t *scales) {
+                              int metric, int transform, int norm, float p, double k, double *norms, int16_t *scales) {
     if (n_rows <= 0) return hipSuccess;
     auto go = [&](auto g) {
         constexpr int G = decltype(g)::value;
         const int per = 256 / G;
         hipLaunchKernelGGL((spd_match_norms_kernel<G>), dim3((unsigned)((n_rows + per - 1) / per)), dim3(256), 0, st, indptr, values,
-                           n_rows, nnz, op, metric, transform, norm, p, k, queries ? -51 : 0, norms, match_fixed(op, metric) ? scales : nullptr);
+                           n_rows, nnz, metric, transform, norm, p, k, norms, scales);
     };
     switch (match_norm_lanes(n_rows, nnz)) {
     case 256: go(std::integral_constant<int, 256>{}); break;
@@ -592,12 +581,13 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     // A block of columns: an eighth of the LDS for counters, or twice that, and entries for four fifths, on the mean,
     // of what counters and row positions leave for its piece of the lists (the rest of a fuller block goes straight to
     // memory; narrower blocks read a row's lines more often).  Dense columns may take half as much again.
-    const int64_t usable = lds_budget - 1024, rows_bytes = 14 * (int64_t)s.tile_rows;
+    const int64_t usable = lds_budget - 1024, rows_bytes = 12 * (int64_t)s.tile_rows;
     if (usable < rows_bytes + 4096) return s;
-    // A step of 64 rows of a dense column costs half a list's step.  (From 0.3 / 0.4 / 0.5 / 0.6 of the rows on, us: 1,024 x 300,000 rows
-    // of 230, cosine, 5,796 / 5,651 / 5,638 / 5,767, k-NN of 2,048 of them, Hellinger, 7,535 / 7,570 / 7,645 / 7,909; 10,000 x 10,000 rows
-    // of 38, L1, 336 / 331 / 325 / 318; sets, Jaccard, 9,102 / 8,970 / 8,928 / 8,963.)
-    s.dense_from = op == OP_CHEB ? s.tile_rows + 1 : std::max(1, s.tile_rows / 2);         // (Chebyshev: an entry has a rank, a column of values none)
+    // A step of 64 rows of a dense column costs half a list's step, and a third where that adds doubles.  (Dot products from a third / 0.4 / a
+    // half of the rows on, us: 1,024 x 300,000 rows of 230, cosine, 5,385 / 5,344 / 5,519, k-NN of 2,048 of them, Hellinger, 7,304 /
+    // 7,489 / 8,115; 10,000 x 10,000 rows of 38, cosine, 312 / 311 / 307.  From 0.3 / 0.4 / 0.5 / 0.6 on: the same rows of 38, L1, 336 /
+    // 331 / 325 / 318; sets, Jaccard, 9,102 / 8,970 / 8,928 / 8,963.  Chebyshev: an entry has a rank, a column of values none.)
+    s.dense_from = op == OP_CHEB ? s.tile_rows + 1 : std::max(1, s.tile_rows / (op == OP_DOT ? 3 : 2));
     const double per_col = per_cell * (double)s.tile_rows;
     auto stage_of = [&](int shift) { return (usable - rows_bytes - ((int64_t)4 << shift)) / 48 * 8; };
     int shift = 2;
@@ -641,7 +631,7 @@ bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renu
 }
 
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
-                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int metric, int transform) {
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int transform) {
     if (n_rows <= 0) return hipSuccess;
     const MatchShape &s = b.shape;
     const uint32_t per_wg = match_build_blocks(s), wgs = ((uint32_t)s.blocks + per_wg - 1u) / per_wg;
@@ -652,7 +642,7 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
         hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(kern, dim3(((unsigned)s.n_tiles * wgs + 7u) / 8u * 8u), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
-                           nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op == OP_DOT && match_fixed(op, metric), op != OP_CNT);
+                           nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op != OP_CNT);
         return hipGetLastError();
     };
     // (a row's stretch in the two loads of its lanes, where that leaves no more than half of them idle: rows of 1,820 over 51 blocks 1,078 us

@@ -16,10 +16,11 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 }
 // A strip holds a pair's sums in planes, one for each number of Op<OP>::Acc (its doubles, then its count), so that the
 // rows of neighbouring lanes lie in different banks.  `at`: LDS address of the strip, `plane`: bytes of a plane of doubles.
-// FIX: one sum in fixed point in the place of the double.
+// Fixed: one sum in fixed point in the place of the double.
 struct Fixed { long long v; };
 struct Ranked { uint32_t m, met_a, met_b; };         // Chebyshev: the maximum (a float's bits), which of the rows' largest entries were met
-template <int OP, bool FIX> struct Sums {
+template <int OP> struct Sums {
+    static constexpr bool FIX = match_fixed(OP);
     using Acc = std::conditional_t<FIX, Fixed, std::conditional_t<OP == OP_CHEB, Ranked, typename Op<OP>::Acc>>;
     static_assert(!FIX || (match_doubles(OP) == 1 && match_counts(OP) == 0), "one sum");
     static __device__ __forceinline__ void init(Acc &x) {
@@ -146,32 +147,25 @@ template <int OP> __device__ __forceinline__ bool match_visit(typename Op<OP>::A
     return true;
 }
 
-// A row of A as the sums in fixed point take it (match_fixed): a term x of the row stands as `offset` + `factor` * x (dot: a * b is
-// the product itself), in [2, 4) and thus in units of 2^-51; `unit` is what one of them is worth; the row's values are taken over 2^down (dot).
-struct Scale { double factor, offset, unit; int down; };
+// A row of A as the sums in fixed point take it (match_fixed): a term x of the row stands as `offset` + `factor` * x, in [2, 4)
+// and thus in units of 2^-51; `unit` is what one of them is worth.
+struct Scale { double factor, offset, unit; };
 __device__ __forceinline__ double power_of_two(int e) { return __hiloint2double((1023 + e) << 20, 0); }
 template <int OP> __device__ __forceinline__ Scale scale_of(int e, int len) {
-    Scale s{1.0, 3.0, power_of_two(-51), 0};
-    if constexpr (OP == OP_DOT) {
-        s.down = e;
-    } else {
+    Scale s{1.0, 2.0, 1.0};
+    if constexpr (match_fixed(OP)) {
         const int k = OP == OP_CANB ? match_canberra_scale(len) : e;
         s.factor = power_of_two(-k);
-        s.offset = 2.0;
         s.unit = power_of_two(k - 51);
         if constexpr (OP == OP_CANB) { s.offset += 2.0 * s.factor; s.factor = -s.factor; }
     }
     return s;
 }
-// The words of a double in [2, 4) are 2^62 and its mantissa, which counts units of 2^-51.  Terms that are not negative stand as 2 + x:
-// a sum of such words modulo 2^62 is the sum of the units.  Dot products of either sign stand as 3 + x: the upper word less 3's
-// (the lower one is 0) leaves the units, negative ones too.
+// The words of a double in [2, 4) are 2^62 and its mantissa, which counts units of 2^-51: a sum of such words modulo 2^62 is
+// the sum of the units.
 template <int OP> __device__ __forceinline__ Fixed fixed_visit(float a, float b, const Scale &s) {
     double t;
-    if constexpr (OP == OP_DOT) {
-        t = fma((double)a, (double)b, 3.0);
-        return Fixed{(long long)(((unsigned long long)(uint32_t)(__double2hiint(t) - 0x40080000) << 32) | (uint32_t)__double2loint(t))};
-    } else if constexpr (OP == OP_L1) {
+    if constexpr (OP == OP_L1) {
         t = fma((double)fabsf(median_with_zero(a, b)), s.factor, 2.0);
     } else {
         t = fma((double)fast_div(fabsf(a - b), fabsf(a) + fabsf(b)), s.factor, s.offset);
@@ -185,45 +179,33 @@ template <int OP> __device__ __forceinline__ Fixed fixed_sum(const typename Op<O
     return Fixed{(long long)__builtin_rint(x.v * (s.factor * 0x1p51))};
 }
 // The units of a sum.
-template <int OP> __device__ __forceinline__ double units_of(const Fixed &x) {
-    return OP == OP_DOT ? (double)x.v : (double)(unsigned long long)(x.v & ((1ll << 62) - 1));
-}
-// What a distance reads of a row of B: nothing, the first norm, the second one (cosine: it is 0 where the first is), the first and the
-// row's scale, or both.  They lie in planes, so that a row of the tile costs 8 or 10 bytes where the two together were 16.
-enum NormsRead { READ_NONE = 0, READ_FIRST, READ_SECOND, READ_SCALE, READ_BOTH };
-SPD_HD constexpr int norms_read(int metric, bool fixed) {
+__device__ __forceinline__ double units_of(const Fixed &x) { return (double)(unsigned long long)(x.v & ((1ll << 62) - 1)); }
+// What a distance reads of a row of B: nothing, the first norm, the second one (cosine: it is 0 where the first is), or both.
+// They lie in planes, so that a row of the tile costs 8 bytes where the two together were 16.
+enum NormsRead { READ_NONE = 0, READ_FIRST, READ_SECOND, READ_BOTH };
+SPD_HD constexpr int norms_read(int metric) {
     switch (metric) {
     case MT_INNER: case MT_KL: case MT_KL_STRICT: case MT_RUSSELL_RAO: case MT_CHEBYSHEV: return READ_NONE;
     case MT_COSINE: return READ_SECOND;
-    case MT_L2: case MT_HELLINGER: return fixed ? READ_SCALE : READ_FIRST;
     case MT_CORRELATION: case MT_MINKOWSKI: case MT_L2_UNEXPANDED: return READ_BOTH;
     default: return READ_FIRST;
     }
 }
-// ... `x` the first of what is read, `y` the second norm, `e` the scale.
-struct RowNorms { double x, y; int e; };
+// ... `x` the first of what is read, `y` the second norm.
+struct RowNorms { double x, y; };
 // The distance of a pair from its sums and the rows' norms.
-template <int OP, bool FIX, int MT>
-__device__ __forceinline__ float distance_of(const OpParams &q, const typename Sums<OP, FIX>::Acc &c, double unit, double na0, double na1, const RowNorms &b) {
-    constexpr int R = norms_read(MT, FIX);
+template <int OP, int MT>
+__device__ __forceinline__ float distance_of(const OpParams &q, const typename Sums<OP>::Acc &c, double unit, double na0, double na1, const RowNorms &b) {
+    constexpr int R = norms_read(MT);
     const double a0 = R == READ_SECOND ? na1 : na0, b1 = R == READ_SECOND ? b.x : b.y;
-    if constexpr (FIX) {
-        double v = units_of<OP>(c);
-        if constexpr (OP != OP_DOT) v *= unit;
-        else if constexpr (R == READ_SCALE) v = __builtin_ldexp(v * na1, b.e);
-        return finish_as<MT>(q, v, 0.0, 0.0, a0, na1, b.x, b1);
+    if constexpr (match_fixed(OP)) {
+        return finish_as<MT>(q, units_of(c) * unit, 0.0, 0.0, a0, na1, b.x, b1);
     } else if constexpr (OP == OP_CHEB) {
         return 0.0f;                                               // (not formed from these: finish_ranked)
     } else {
         using O = Op<OP>;
         return finish_as<MT>(q, O::v0(c), O::v1(c), O::v2(c), a0, na1, b.x, b1);
     }
-}
-// Calls f(MetricTag<m>) for the metric, one that these sums serve.
-template <int OP, bool FIX, typename F> __device__ __forceinline__ void for_metric_summed(int metric, F &&f) {
-    for_metric_of<OP>(metric, [&](auto tag) {
-        if constexpr (FIX == match_fixed(OP, decltype(tag)::value)) f(tag);
-    });
 }
 
 // Lane l receives lane 63 - l's value.
@@ -291,10 +273,12 @@ template <int I> __device__ __forceinline__ float row_lane(float v) { return __u
 
 constexpr int kMatchUnroll = 4;          // list steps whose loads are in flight together
 
-template <int OP, bool KNN, bool FIX>
+// BOTH: k-NN whose distances read both norms (Minkowski's and correlation).
+template <int OP, bool KNN, bool BOTH>
 __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd_match_kernel(const MatchArgs args) {
     using O = Op<OP>;
-    using S = Sums<OP, FIX>;
+    using S = Sums<OP>;
+    constexpr bool FIX = S::FIX;
     using Acc = typename S::Acc;
     // D: 64-row pieces of a dense column that are summed in registers together; the largest tiles hold 19 for one
     // fp64 sum (one round of 19 against two of 10: 2,048 queries of 300,000 rows of 230, 10.5 -> 10.2 ms; 13 and 6
@@ -573,8 +557,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         const unsigned char *__restrict__ values = reinterpret_cast<const unsigned char *>(args.b.values + tile_first);
         const unsigned char *__restrict__ rows = reinterpret_cast<const unsigned char *>(args.b.rows + tile_first);
         const uint32_t list_n = (uint32_t)(args.b.shape.list_entries(args.b_nnz) - kMatchSpare - tile_first);     // (no access leaves the lists)
-        float a = transform_value(args.transform, y.a);
-        if constexpr (FIX && OP == OP_DOT) a = __builtin_ldexpf(a, -scale.down);
+        const float a = transform_value(args.transform, y.a);
         uint32_t first = min(y.first & ~kMatchDense, list_n);
         const bool dense = (y.first & kMatchDense) != 0u && match_walks<OP>(a) && first + (uint32_t)T <= list_n;
         const uint64_t dense_mask = __ballot(dense);
@@ -592,7 +575,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     };
     // What finish() reads of a row of A, loaded while the row's last lists are walked.
     struct RowOf { double na0, na1; uint64_t bound; };
-    auto load_scale = [&](int row) { return FIX && OP != OP_CANB ? (int)args.scales_a[row] : 0; };
+    auto load_scale = [&](int row) { return OP == OP_L1 ? (int)args.scales_a[row] : 0; };
     auto load_row = [&](int row) {
         RowOf r{args.norms_a[row], args.norms_a[(size_t)args.m + (size_t)row], kKnnUnused};
         if constexpr (KNN) r.bound = (uint64_t)__atomic_load_n(&args.knn_tau[row], __ATOMIC_RELAXED);
@@ -705,8 +688,10 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // strip is clear again afterwards.  `flush`: the row's run of tiles ends here; `lock`: k-NN, of a row that other workgroups
     // take in other tiles, else null.
     auto finish = [&](int tile, int row, const RowOf &of, const Scale &scale, const Few &few, bool flush, int *lock) {
-        int lane = (int)threadIdx.x & 63;                         // (hidden from the compiler: it would keep the addresses of every loop below
-        asm volatile("" : "+v"(lane));                            // in registers through the whole kernel, 50 more than there are)
+        // (hidden from the compiler: it would keep the addresses of every loop below in registers through the whole kernel, 50 more than
+        // there are.  k-NN by fp64 sums has them: 4,096 x 663,000 n-grams, cosine, 2,083 -> 2,032 us)
+        int lane = (int)threadIdx.x & 63;
+        if constexpr (!KNN || FIX) asm volatile("" : "+v"(lane));
         const int64_t j0 = (int64_t)tile * T;
         const int tile_n = (int)min((int64_t)T, args.n - j0);
         const double na0 = of.na0, na1 = of.na1, unit = (OP == OP_L1 ? -2.0 : -1.0) * scale.unit;            // (the sum enters the distance with that factor)
@@ -715,19 +700,13 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         // rows beyond the tile's last repeat it), and their places cleared again.  (With an address and a bound for every row,
         // 25 vector instructions per 64 rows, a call on 10,000 x 10,000 rows of 38 spent more on this than on the lists.)
         const uint32_t lane4 = (uint32_t)lane * 4u;
-        auto load_norms = [&](int reads, int i0, RowNorms (&nb)[F]) {
-            if (reads == READ_NONE) return;
-            const unsigned char *const first_at = reinterpret_cast<const unsigned char *>(args.b.norms + (reads == READ_SECOND ? args.n : 0) + j0);
+        auto load_norms = [&](const double *first, bool both, int i0, RowNorms (&nb)[F]) {
+            const unsigned char *const first_at = reinterpret_cast<const unsigned char *>(first + j0);
             const unsigned char *const second_at = reinterpret_cast<const unsigned char *>(args.b.norms + args.n + j0);
-            const unsigned char *const scale_at = reinterpret_cast<const unsigned char *>(args.b.scales + j0);
             auto load = [&](auto at) {
 #pragma unroll
                 for (int u = 0; u < F; ++u) nb[u].x = *reinterpret_cast<const double *>(first_at + at(u, 8u));
-                if (reads == READ_SCALE) {
-#pragma unroll
-                    for (int u = 0; u < F; ++u) nb[u].e = *reinterpret_cast<const int16_t *>(scale_at + at(u, 2u));
-                }
-                if (reads == READ_BOTH) {
+                if (both) {
 #pragma unroll
                     for (int u = 0; u < F; ++u) nb[u].y = *reinterpret_cast<const double *>(second_at + at(u, 8u));
                 }
@@ -758,9 +737,9 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             for (int i0 = (tile_n + F * kWave - 1) / (F * kWave) * (F * kWave); i0 < T; i0 += F * kWave) clear_round(i0);
         };
         if constexpr (!KNN) {
-            for_metric_summed<OP, FIX>(args.q.metric, [&](auto metric_tag) {
+            for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
                 constexpr int MT = decltype(metric_tag)::value;
-                constexpr int R = norms_read(MT, FIX);
+                constexpr int R = norms_read(MT);
                 float *__restrict__ out = args.out + (size_t)row * (size_t)args.n + (size_t)j0;
                 // A round's norms are loaded before the round ahead stores its distances: what is loaded after a store is at hand only when the
                 // store has reached memory (10,000 x 10,000 rows of 38 with that wait in every round, L1 327 us a call, cosine 356; 316
@@ -768,21 +747,24 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 // and stores in flight.
                 const int whole = tile_n / (F * kWave) * (F * kWave);
                 RowNorms nb[F], ahead[F];
+                auto load = [&](int i0, RowNorms (&into)[F]) {
+                    if constexpr (R != READ_NONE) load_norms(args.b.norms + (R == READ_SECOND ? args.n : 0), R == READ_BOTH, i0, into);
+                };
                 auto round = [&](int i0, int next) {
                     Acc c[F];
                     load_sums(i0, c);
-                    load_norms(R, next, ahead);
+                    load(next, ahead);
                     __builtin_amdgcn_sched_barrier(0);
                     unsigned char *to = reinterpret_cast<unsigned char *>(out + i0);
 #pragma unroll
                     for (int u = 0; u < F; ++u)
-                        __builtin_nontemporal_store(distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]),
+                        __builtin_nontemporal_store(distance_of<OP, MT>(args.q, c[u], unit, na0, na1, nb[u]),
                                                     reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
                     clear_round(i0);
 #pragma unroll
                     for (int u = 0; u < F; ++u) nb[u] = ahead[u];
                 };
-                load_norms(R, 0, nb);
+                load(0, nb);
                 if (whole > 0) {
                     round(0, F * kWave < tile_n ? F * kWave : 0);
 #pragma unroll 1
@@ -795,15 +777,15 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
 #pragma unroll
                     for (int u = 0; u < F; ++u)
                         if (whole + u * kWave + lane < tile_n)
-                            __builtin_nontemporal_store(distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]),
+                            __builtin_nontemporal_store(distance_of<OP, MT>(args.q, c[u], unit, na0, na1, nb[u]),
                                                         reinterpret_cast<float *>(to + lane4 + u * (kWave * 4)));
                     clear_round(whole);
                 }
             });
             clear_behind();
         } else {
-          for_metric_summed<OP, FIX>(args.q.metric, [&](auto of_metric) {
-            constexpr int MT = decltype(of_metric)::value, reads = norms_read(MT, FIX);
+            // (the metric is settled where distances are formed: an instance of all this for each of the dot product's is
+            // too much to be inlined, and what it then keeps in memory cost 4,096 x 663,000 n-grams 8.5 ms for 2.0)
             const int k = args.knn_k;
             auto kth_of = [&](uint64_t sorted, int at) {
                 return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(sorted >> 32), at) << 32) |
@@ -818,23 +800,27 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 bound = now < bound ? now : bound;
                 queued = 0;
             };
-            auto distances = [&](float (&d)[F], const Acc (&c)[F], const RowNorms (&nb)[F]) {
+            auto distances = [&](auto &d, const auto &c, const auto &nb) {
+                for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
+                    constexpr int MT = decltype(metric_tag)::value;
+                    if constexpr (BOTH != (norms_read(MT) == READ_BOTH)) return;
 #pragma unroll
-                for (int u = 0; u < F; ++u) {
-                    d[u] = distance_of<OP, FIX, MT>(args.q, c[u], unit, na0, na1, nb[u]);
-                    if constexpr (MT == MT_INNER) d[u] = 0.0f - d[u];
-                }
+                    for (int u = 0; u < (int)(sizeof(d) / sizeof(d[0])); ++u) {
+                        d[u] = distance_of<OP, MT>(args.q, c[u], unit, na0, na1, nb[u]);
+                        if constexpr (MT == MT_INNER) d[u] = 0.0f - d[u];
+                    }
+                });
             };
             // Whether a row that shares no column could pass: the distances of one sum grow with the row's first norm, so none is
             // nearer than the tile's row of the least.  (Correlation's do not.)
             bool few_only = false;
             if constexpr (S::kOne) {
-                if (few.total <= 4 * F && MT != MT_CORRELATION) {
-                    float d = distance_of<OP, FIX, MT>(args.q, zero, unit, na0, na1,
-                                                       RowNorms{args.b.least[(size_t)tile * 2 + (reads == READ_SECOND ? 1 : 0)],
-                                                                args.b.least[(size_t)tile * 2 + 1], 0});
-                    if constexpr (MT == MT_INNER) d = 0.0f - d;
-                    few_only = d == d && knn_key(d, (int)j0) > bound;
+                if (!BOTH && few.total <= 4 * F) {
+                    float d[1] = {0.0f};
+                    const Acc c[1] = {zero};
+                    const RowNorms nb[1] = {{args.b.least[(size_t)tile * 2 + (args.norms_b != args.b.norms ? 1 : 0)], args.b.least[(size_t)tile * 2 + 1]}};
+                    distances(d, c, nb);
+                    few_only = d[0] == d[0] && knn_key(d[0], (int)j0) > bound;
                 }
             }
             // The row's first tile goes twice through the strip: first the distances replace the sums and every lane keeps the
@@ -869,12 +855,11 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
 #pragma unroll
                             for (int u = 0; u < F; ++u) {
                                 i[u] = S::is_zero(c[u]) ? tile_n : (int)(few.cell[u] / S::kUnit);
-                                nb[u] = RowNorms{0.0, 0.0, 0};
+                                nb[u] = RowNorms{0.0, 0.0};
                                 if (few.total > 4 * u) {
                                     const int64_t j = j0 + min(i[u], tile_n - 1);
-                                    if (reads != READ_NONE) nb[u].x = args.b.norms[(reads == READ_SECOND ? args.n : 0) + j];
-                                    if (reads == READ_SCALE) nb[u].e = args.b.scales[j];
-                                    if (reads == READ_BOTH) nb[u].y = args.b.norms[args.n + j];
+                                    nb[u].x = args.norms_b[j];
+                                    if (BOTH) nb[u].y = args.b.norms[args.n + j];
                                 }
                             }
                         }
@@ -882,7 +867,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
 #pragma unroll
                         for (int u = 0; u < F; ++u) i[u] = i0 + u * kWave + lane;
                         load_sums(i0, c);
-                        load_norms(reads, i0, nb);
+                        load_norms(args.norms_b, BOTH, i0, nb);
                     }
                     distances(d, c, nb);
 #pragma unroll
@@ -941,7 +926,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 merge();                                          // (what is queued joins the run's list, if it has one)
                 // into the row's list of this group, under a lock (two wavefronts of the workgroup may be at one row, in
                 // different tiles, or of several workgroups, where the lock lies in memory); the holder waits for nothing
-                const bool in_memory = lock != nullptr;
+                const bool in_memory = S::kAnyOrder && lock != nullptr;
                 int *const row_lock = &s_lock[row & (kMatchLocks - 1)];
                 int first_lane = lane;
                 asm volatile("" : "+v"(first_lane));              // (see the claim below)
@@ -973,7 +958,6 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 queued = 0;
                 any = false;
             }
-          });
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
@@ -1036,16 +1020,15 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 const int64_t j0 = (int64_t)tile * T;
                 const int tile_n = (int)min((int64_t)T, args.n - j0);
                 const double unit = (OP == OP_L1 ? -2.0 : -1.0) * scale.unit;
-                for_metric_summed<OP, FIX>(args.q.metric, [&](auto metric_tag) {
-                    constexpr int MT = decltype(metric_tag)::value, R = norms_read(MT, FIX);
+                for_metric_of<OP>(args.q.metric, [&](auto metric_tag) {
+                    constexpr int MT = decltype(metric_tag)::value, R = norms_read(MT);
                     float *__restrict__ out = args.out + (size_t)row * (size_t)args.n + (size_t)j0;
                     for (int i = tid; i < T; i += nw * kWave) {
                         if (i < tile_n) {
-                            RowNorms nb{0.0, 0.0, 0};
+                            RowNorms nb{0.0, 0.0};
                             if (R != READ_NONE) nb.x = args.b.norms[(R == READ_SECOND ? args.n : 0) + j0 + i];
-                            if (R == READ_SCALE) nb.e = args.b.scales[j0 + i];
                             if (R == READ_BOTH) nb.y = args.b.norms[args.n + j0 + i];
-                            __builtin_nontemporal_store(distance_of<OP, FIX, MT>(args.q, S::get(owners_at, plane, (uint32_t)i), unit, of.na0, of.na1, nb), out + i);
+                            __builtin_nontemporal_store(distance_of<OP, MT>(args.q, S::get(owners_at, plane, (uint32_t)i), unit, of.na0, of.na1, nb), out + i);
                         }
                         S::put(owners_at, plane, (uint32_t)i, zero);
                     }
@@ -1155,8 +1138,8 @@ template <typename Kernel> static hipError_t allow_lds(Kernel kern, std::atomic<
     return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-template <int OP, bool KNN, bool FIX> static hipError_t launch_match_op(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
-    auto kern = spd_match_kernel<OP, KNN, FIX>;
+template <int OP, bool KNN, bool BOTH> static hipError_t launch_match_op(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
+    auto kern = spd_match_kernel<OP, KNN, BOTH>;
     static std::atomic<uint32_t> allowed[kMatchDevices];
     hipError_t e = allow_lds(kern, allowed, lds_bytes, (uint32_t)match_static_lds(match_cell_bytes(OP)));
     if (e != hipSuccess) return e;
@@ -1164,15 +1147,12 @@ template <int OP, bool KNN, bool FIX> static hipError_t launch_match_op(hipStrea
     hipLaunchKernelGGL(kern, dim3((unsigned)(groups * args.slices)), dim3((unsigned)(match_waves(match_cell_bytes(OP)) * kWave)), lds_bytes, st, args);
     return hipGetLastError();
 }
-template <int OP, bool FIX> static hipError_t launch_match_summed(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
-    return args.knn_k > 0 ? launch_match_op<OP, true, FIX>(st, args, lds_bytes) : launch_match_op<OP, false, FIX>(st, args, lds_bytes);
-}
 template <int OP> static hipError_t launch_match_either(hipStream_t st, const MatchArgs &args, uint32_t lds_bytes) {
+    if (args.knn_k <= 0) return launch_match_op<OP, false, false>(st, args, lds_bytes);
     if constexpr (OP == OP_DOT) {
-        return match_fixed(OP, args.q.metric) ? launch_match_summed<OP, true>(st, args, lds_bytes) : launch_match_summed<OP, false>(st, args, lds_bytes);
-    } else {
-        return launch_match_summed<OP, match_fixed(OP, MT_COUNT)>(st, args, lds_bytes);
+        if (args.q.metric == MT_CORRELATION) return launch_match_op<OP, true, true>(st, args, lds_bytes);
     }
+    return launch_match_op<OP, true, OP == OP_MINK || OP == OP_MINK_ANY>(st, args, lds_bytes);
 }
 
 }  // namespace spd

@@ -743,3 +743,22 @@ def test_chebyshev_by_lists(spd, m, n, cols, lengths_a, lengths_b):
     assert np.array_equal(_np(dist), np.sort(got, axis=1)[:, :min(n, 5)])
     h.close()
     staged.close()
+
+
+@pytest.mark.parametrize("metric", ["l2_expanded", "hellinger"])
+def test_equal_rows_of_two_entries_lie_at_distance_0(spd, metric):
+    """The products of two single precision numbers are exact in 64 bits and their sum is rounded once, in the norms as in the inner
+    product: nothing is left of |a|^2 - 2 <a, b> + |b|^2 where a and b are equal, whatever the values."""
+    rng = np.random.default_rng(12)
+    rows, cols = 400, 150
+    c = np.sort(np.array([rng.choice(cols, size=2, replace=False) for _ in range(rows)]), axis=1)
+    A = {"n_rows": rows, "n_cols": cols, "indptr": 2 * np.arange(rows + 1, dtype=np.int64), "indices": c.reshape(-1).astype(np.int32),
+         "values": np.abs(rng.standard_normal(2 * rows)).astype(np.float32)}
+    h = _lists(spd, profile=1)
+    dA = spd.DeviceCsr.from_host(A)
+    got = _np(h.pairwise(dA, dA, metric))
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    assert np.all(np.diag(got) == 0.0), int((np.diag(got) != 0.0).sum())
+    _, dist = h.knn(dA, dA, metric, 1)
+    assert np.all(_np(dist) == 0.0)
+    h.close()
