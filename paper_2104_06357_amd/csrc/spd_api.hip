@@ -601,7 +601,7 @@ MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int op, 
     }
     L.rows = cv.take((size_t)m * sizeof(MatchRow) + match_counters_bytes(g, knn_k > 0));       // (the counters behind them)
     L.norms_a = cv.take((size_t)m * 16);
-    if (op == OP_L1) L.scales_a = cv.take((size_t)m * 2);
+    if (match_fixed(op)) L.scales_a = cv.take((size_t)m * 2);
     if (op == OP_CHEB) {
         L.ranks_a = cv.take((size_t)nnz_a);
         L.tops_a = cv.take((size_t)m * kRanks * 4);
@@ -877,7 +877,7 @@ spd_status start_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int me
     if (op == OP_CHEB) return SPD_OK;
     LaunchTimer lt(h, "norms_a", 0, 0, 0, 0, 0, 0);
     e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, metric, mi.transform, mi.norm, q.p, q.k,
-                           reinterpret_cast<double *>(ws + L.norms_a), op == OP_L1 ? reinterpret_cast<int16_t *>(ws + L.scales_a) : nullptr);
+                           reinterpret_cast<double *>(ws + L.norms_a), match_fixed(op) ? reinterpret_cast<int16_t *>(ws + L.scales_a) : nullptr);
     if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
     lt.done();
     return SPD_OK;

@@ -68,7 +68,7 @@ struct MatchArgs {
     int32_t m;
     const double *norms_a;        // 2 * m, derived, likewise
     const double *norms_b;        // k-NN: those of B's that distances read first (norms_read), the first ones or the second ones
-    const int16_t *scales_a;      // m: L1, the rows' exponents (match_fixed)
+    const int16_t *scales_a;      // m: L1, the rows' exponents (match_fixed); Canberra, 1 where a row is wild
     const uint8_t *ranks_a;       // Chebyshev: of A's entries, and kRanks magnitudes of every row, one row after the other
     const float *tops_a;
     const int32_t *b_indices;     // ... and B's rows, for the pairs whose kRanks largest entries of a row were all met
@@ -149,6 +149,10 @@ SPD_HD int match_scale(float largest, double sum) {
     const int e = top > all - 9 ? top : all - 9;
     return e < -200 ? -200 : (e > 200 ? 200 : e);
 }
+// Canberra: whether a row of A, whose entries' magnitudes lie from `least` (but 0) to `largest`, can meet a row of finite values where |a| + |b|
+// or its reciprocal is not finite in single precision, or |a - b| is not: no sum is below 2^-100 or, half an ulp of the largest number being 2^103,
+// rounded to infinity else.  Such a row is walked column by column.
+SPD_HD bool match_wild(float least, float largest) { return !(least >= 0x1p-100f && largest < 0x1p102f); }
 // Canberra's for a row of A of `len` entries: 2 len 2^(51 - e) below 2^62.
 SPD_HD int match_canberra_scale(int len) { return len < (1 << 10) ? 2 : 2 + (32 - 10) - __builtin_clz((unsigned)len); }
 

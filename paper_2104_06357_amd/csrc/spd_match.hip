@@ -11,7 +11,7 @@ namespace spd {
 // entries a lane wait for the whole workgroup, one after the other (500,000 rows of 1 to 50,000 entries: 332 us while a
 // wavefront went through the longest alone, 260 now)
 // ------------------------------------------------------------------------------------
-template <int G>
+template <int G, bool SCALES>
 __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__restrict__ indptr, const float *__restrict__ values,
                                                               int64_t n_rows, int64_t nnz, int metric, int transform, int norm,
                                                               float p, double k, double *__restrict__ norms,
@@ -20,10 +20,10 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
     constexpr int64_t kLong = G < 256 ? 64 * G : INT64_MAX;
     __shared__ int s_long[kRows], s_longs;
     __shared__ double s_sum[256 / kWave][2];
-    __shared__ float s_most[256 / kWave];
+    __shared__ float s_most[256 / kWave], s_least[256 / kWave];
     const int tid = (int)threadIdx.x, sub = tid % G;
     const int64_t row0 = (int64_t)blockIdx.x * kRows, row = row0 + tid / G;
-    auto sums = [&](int64_t from, int64_t end, int stride, double &s0, double &s1, float &most) {
+    auto sums = [&](int64_t from, int64_t end, int stride, double &s0, double &s1, float &most, float &least) {
         for (int64_t e = from; e < end; e += 4 * stride) {
             float v[4];
 #pragma unroll
@@ -33,32 +33,42 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
                 if (e + u * stride < end) {
                     const float t = transform_value(transform, v[u]);
                     norm_accumulate(norm, t, p, s0, s1);
-                    most = fmaxf(most, fabsf(t));
+                    if constexpr (SCALES) {
+                        most = fmaxf(most, fabsf(t));
+                        least = t != 0.0f ? fminf(least, fabsf(t)) : least;
+                    }
                 }
         }
 #pragma unroll
         for (int d = kWave / 2; d >= 1; d >>= 1)
-            if (d < stride) { s0 += __shfl_xor(s0, d); s1 += __shfl_xor(s1, d); most = fmaxf(most, __shfl_xor(most, d)); }
+            if (d < stride) {
+                s0 += __shfl_xor(s0, d);
+                s1 += __shfl_xor(s1, d);
+                if constexpr (SCALES) {
+                    most = fmaxf(most, __shfl_xor(most, d));
+                    least = fminf(least, __shfl_xor(least, d));
+                }
+            }
     };
-    auto write = [&](int64_t r, double s0, double s1, float most) {
+    auto write = [&](int64_t r, double s0, double s1, float most, float least) {
         double d0, d1;
         norm_derive(metric, k, s0, s1, d0, d1);
-        if (scales) scales[r] = (int16_t)match_scale(most, s0);
+        if constexpr (SCALES) scales[r] = (int16_t)(metric == MT_CANBERRA ? match_wild(least, most) : match_scale(most, s0));
         norms[r] = d0;
         norms[n_rows + r] = d1;
     };
     // a row by all 256 lanes: its wavefronts' sums in a fixed order
     auto by_all = [&](int64_t r, int64_t begin, int64_t end) {
         double s0 = 0.0, s1 = 0.0;
-        float most = 0.0f;
-        sums(begin + tid, end, 256, s0, s1, most);
-        if (tid % kWave == 0) { s_sum[tid / kWave][0] = s0; s_sum[tid / kWave][1] = s1; s_most[tid / kWave] = most; }
+        float most = 0.0f, least = 1.0f;
+        sums(begin + tid, end, 256, s0, s1, most, least);
+        if (tid % kWave == 0) { s_sum[tid / kWave][0] = s0; s_sum[tid / kWave][1] = s1; s_most[tid / kWave] = most; s_least[tid / kWave] = least; }
         __syncthreads();
         if (tid == 0) {
             s0 = 0.0; s1 = 0.0;
 #pragma unroll
-            for (int w = 0; w < 256 / kWave; ++w) { s0 += s_sum[w][0]; s1 += s_sum[w][1]; most = fmaxf(most, s_most[w]); }
-            write(r, s0, s1, most);
+            for (int w = 0; w < 256 / kWave; ++w) { s0 += s_sum[w][0]; s1 += s_sum[w][1]; most = fmaxf(most, s_most[w]); least = fminf(least, s_least[w]); }
+            write(r, s0, s1, most, least);
         }
     };
     int64_t begin = 0, end = 0;
@@ -74,9 +84,9 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
         const bool is_long = end - begin > kLong;
         if (is_long && sub == 0) s_long[atomicAdd(&s_longs, 1)] = tid / G;
         double s0 = 0.0, s1 = 0.0;
-        float most = 0.0f;
-        sums(begin + sub, is_long ? begin : end, G, s0, s1, most);
-        if (row < n_rows && !is_long && sub == 0) write(row, s0, s1, most);
+        float most = 0.0f, least = 1.0f;
+        sums(begin + sub, is_long ? begin : end, G, s0, s1, most, least);
+        if (row < n_rows && !is_long && sub == 0) write(row, s0, s1, most, least);
         __syncthreads();
         const int longs = s_longs;
         for (int at = 0; at < longs; ++at) {
@@ -543,8 +553,8 @@ hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float
     auto go = [&](auto g) {
         constexpr int G = decltype(g)::value;
         const int per = 256 / G;
-        hipLaunchKernelGGL((spd_match_norms_kernel<G>), dim3((unsigned)((n_rows + per - 1) / per)), dim3(256), 0, st, indptr, values,
-                           n_rows, nnz, metric, transform, norm, p, k, norms, scales);
+        hipLaunchKernelGGL((scales ? spd_match_norms_kernel<G, true> : spd_match_norms_kernel<G, false>), dim3((unsigned)((n_rows + per - 1) / per)),
+                           dim3(256), 0, st, indptr, values, n_rows, nnz, metric, transform, norm, p, k, norms, scales);
     };
     switch (match_norm_lanes(n_rows, nnz)) {
     case 256: go(std::integral_constant<int, 256>{}); break;

@@ -128,8 +128,6 @@ template <int OP> __device__ __forceinline__ bool match_visit(typename Op<OP>::A
         x.c = 1;
     } else if constexpr (OP == OP_HAMM) {
         x.c = (a != b) ? -1 : -2;
-    } else if constexpr (OP == OP_CANB) {
-        x.v = (double)fast_div(fabsf(a - b), fabsf(a) + fabsf(b)) - 2.0;
     } else if constexpr (OP == OP_JS) {
         x.v = (double)Op<OP>::term(a, b) - ((double)a + (double)b);
         return b > 0.0f;
@@ -148,11 +146,11 @@ template <int OP> __device__ __forceinline__ bool match_visit(typename Op<OP>::A
 }
 
 // A row of A as the sums in fixed point take it (match_fixed): a term x of the row stands as `offset` + `factor` * x, in [2, 4)
-// and thus in units of 2^-51; `unit` is what one of them is worth.
-struct Scale { double factor, offset, unit; };
+// and thus in units of 2^-51; `unit` is what one of them is worth.  `wild`: Canberra, see match_wild.
+struct Scale { double factor, offset, unit; bool wild; };
 __device__ __forceinline__ double power_of_two(int e) { return __hiloint2double((1023 + e) << 20, 0); }
 template <int OP> __device__ __forceinline__ Scale scale_of(int e, int len) {
-    Scale s{1.0, 2.0, 1.0};
+    Scale s{1.0, 2.0, 1.0, OP == OP_CANB && e != 0};
     if constexpr (match_fixed(OP)) {
         const int k = OP == OP_CANB ? match_canberra_scale(len) : e;
         s.factor = power_of_two(-k);
@@ -173,6 +171,12 @@ template <int OP> __device__ __forceinline__ Fixed fixed_visit(float a, float b,
     long long w;
     __builtin_memcpy(&w, &t, 8);
     return Fixed{w};
+}
+// The same for a column of a row that is wild: |a - b| / (|a| + |b|) of numbers that are brought to where neither the sum nor its reciprocal
+// leaves single precision (one that is 2^53 below the other adds nothing to the ratio of 1).
+__device__ __forceinline__ Fixed wild_visit(float a, float b, const Scale &s) {
+    const float by = fabsf(a) < 1.0f && fabsf(b) < 1.0f ? 0x1p96f : 0x1p-96f;
+    return fixed_visit<OP_CANB>(a * by, b * by, s);
 }
 // A sum of Op<OP>, formed in fp64, in units.
 template <int OP> __device__ __forceinline__ Fixed fixed_sum(const typename Op<OP>::Acc &x, const Scale &s) {
@@ -551,6 +555,27 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             c = next;
         }
     };
+    // The batch's lists and dense columns of a row that is wild, one after the other.
+    auto walk_wild = [&](const unsigned char *__restrict__ values, const unsigned char *__restrict__ rows, uint32_t first, uint32_t last, bool dense,
+                         float a, const Scale &scale, uint32_t to) {
+        if constexpr (OP == OP_CANB) {
+            const uint32_t end = dense ? first + (uint32_t)T : last;
+            const uint64_t dense_mask = __ballot(dense);
+#pragma unroll 1
+            for (uint64_t left = __ballot(first < end); left; left &= left - 1) {
+                const int e = (int)__builtin_ctzll(left);
+                const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)first, e), to_end = (uint32_t)__builtin_amdgcn_readlane((int)end, e);
+                const float ae = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), e));
+#pragma unroll 1
+                for (uint32_t i = from + (uint32_t)lane; i < to_end; i += kWave) {
+                    const float b = reinterpret_cast<const float *>(values)[i];
+                    if (b == 0.0f) continue;
+                    const uint32_t cell = (dense_mask >> e) & 1u ? (i - from) * S::kUnit : (uint32_t)reinterpret_cast<const uint16_t *>(rows)[i];
+                    S::add(to, plane, cell, wild_visit(ae, b, scale));
+                }
+            }
+        }
+    };
     // (`to`: the strip)
     auto walk_lists = [&](int tile, const Lists &y, const Scale &scale, uint32_t to, Few &few) {
         const int64_t tile_first = clamp_i64(args.b_indptr[(int64_t)tile * T], 0, args.b_nnz) + tile * args.b.shape.tile_extra;
@@ -561,6 +586,13 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         uint32_t first = min(y.first & ~kMatchDense, list_n);
         const bool dense = (y.first & kMatchDense) != 0u && match_walks<OP>(a) && first + (uint32_t)T <= list_n;
         const uint64_t dense_mask = __ballot(dense);
+        if (OP == OP_CANB && scale.wild) {
+            const uint32_t last = match_walks<OP>(a) && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
+            walk_wild(values, rows, first, last, dense, a, scale, to);
+            if (KNN) few.total += 4 * U + 1;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            return;
+        }
         if constexpr (OP != OP_CHEB) {
             if (dense_mask != 0) {
                 if (KNN) few.total += 4 * U + 1;
@@ -575,7 +607,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     };
     // What finish() reads of a row of A, loaded while the row's last lists are walked.
     struct RowOf { double na0, na1; uint64_t bound; };
-    auto load_scale = [&](int row) { return OP == OP_L1 ? (int)args.scales_a[row] : 0; };
+    auto load_scale = [&](int row) { return FIX ? (int)args.scales_a[row] : 0; };
     auto load_row = [&](int row) {
         RowOf r{args.norms_a[row], args.norms_a[(size_t)args.m + (size_t)row], kKnnUnused};
         if constexpr (KNN) r.bound = (uint64_t)__atomic_load_n(&args.knn_tau[row], __ATOMIC_RELAXED);

@@ -762,3 +762,33 @@ def test_equal_rows_of_two_entries_lie_at_distance_0(spd, metric):
     _, dist = h.knn(dA, dA, metric, 1)
     assert np.all(_np(dist) == 0.0)
     h.close()
+
+
+@pytest.mark.parametrize("n", [640, 70])                # lists, and columns that more than half of the rows store
+def test_canberra_of_values_at_the_ends_of_their_range(spd, n):
+    """Entries whose magnitudes add up to less than 2^-126, the reciprocal of which single precision does not hold, or to more than it
+    holds, equal to their partners, near them and of the other sign: a ratio is between 0 and 1 all the same."""
+    rng = np.random.default_rng(n)
+    cols, m = 90, 24
+
+    def matrix(rows, share):
+        d = np.zeros((rows, cols))
+        for r in range(rows):
+            c = rng.choice(cols, size=60 if r % share == 0 else 7, replace=False)
+            kind = rng.integers(0, 4, size=len(c))
+            kind[0] = 0
+            tiny, large = rng.integers(1, 1 << 9, size=len(c)) * 2.0 ** -149, rng.integers(1 << 22, 1 << 24, size=len(c)) * 2.0 ** 104
+            d[r, c] = np.choose(kind, [tiny, large, 2.0 ** -140 * np.ones(len(c)), rng.integers(1, 9, size=len(c)) / 8.0]) * rng.choice([-1.0, 1.0], size=len(c))
+        return d
+
+    A, B = matrix(m, 3), matrix(n, 1 if n < 100 else 16)
+    B[5] = A[0]
+    A, B = synth.from_dense(A), synth.from_dense(B)
+    h = _lists(spd, profile=1)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    want = oracle.pairwise(A, B, "canberra")
+    assert_distances_close(_np(h.pairwise(dA, dB, "canberra")), want, "canberra")
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    idx, dist = h.knn(dA, dB, "canberra", 9)
+    assert_knn_matches(_np(idx), _np(dist), want, 9, "canberra", "canberra")
+    h.close()
