@@ -127,7 +127,9 @@ struct spd_handle {
     bool ws_external = false;
     void *own_ws = nullptr;      // the handle's own allocation
     size_t own_ws_bytes = 0;
-    int32_t *flag = nullptr;     // device word for spd_csr_validate
+    int32_t *flag = nullptr;     // device words: the first one for spd_csr_validate, the one at kRowsWord for RowsVerdict
+    static constexpr int kRowsWord = 32;
+    uint32_t rows_looked_at = 0; // calls that had their row pointers looked at on the device
     void *static_ws = nullptr;   // this device's copy of `scratch`
     bool no_alloc = false;       // inside spd_pairwise_static: nothing may be allocated
     bool profile = false;
@@ -804,20 +806,20 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
 
 
 // The norms of B's rows, and their lists.
-spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int metric, const MetricInfo &mi, const OpParams &q) {
+spd_status stage_norms(spd_handle *h, const spd_csr *B, const MatchB &mb, int metric, const MetricInfo &mi, const OpParams &q, const RowsVerdict &seen) {
     LaunchTimer norms(h, "norms_b", 0, 0, 0, 0, 0, 0);
     hipError_t e = launch_match_norms(h->stream, B->indptr, B->values, B->n_rows, B->nnz, metric, mi.transform, mi.norm, q.p, q.k,
-                                      mb.norms, nullptr);
+                                      seen, mb.norms, nullptr);
     if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
     norms.done();
     return SPD_OK;
 }
 // (`knn`: and each tile's row of the least norm)
-spd_status stage_lists(spd_handle *h, const spd_csr *B, MatchB mb, int op, const MetricInfo &mi, bool knn) {
+spd_status stage_lists(spd_handle *h, const spd_csr *B, MatchB mb, int op, const MetricInfo &mi, bool knn, const RowsVerdict &seen) {
     if (!knn) mb.least = nullptr;
     LaunchTimer lists(h, "lists_b", 0, 0, 0, 0, 0, mb.shape.n_tiles);
     hipError_t e = launch_match_build(h->stream, B->indptr, B->indices, B->values, B->n_rows, B->nnz, (uint32_t)B->n_cols, mb,
-                           op, mi.transform);
+                           op, mi.transform, seen);
     if (e != hipSuccess) return hip_fail(h, e, "column-list kernels");
     lists.done();
     return SPD_OK;
@@ -826,7 +828,7 @@ spd_status stage_lists(spd_handle *h, const spd_csr *B, MatchB mb, int op, const
 // What of a call by lists needs no row pointers on the host: B's norms and lists, A's norms.
 struct MatchStart { MatchB b; spd_csr listed; const int32_t *a_indices; };
 spd_status start_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, int op, int knn_k, const OpParams &q,
-                       const MetricInfo &mi, const MatchWay &way, const spd_index *index, MatchStart &start) {
+                       const MetricInfo &mi, const MatchWay &way, const spd_index *index, const RowsVerdict &seen, MatchStart &start) {
     const int64_t m = A->n_rows, n = B->n_rows;
     const MatchShape &s = way.s;
     const MatchScratch &L = way.L;
@@ -847,11 +849,11 @@ spd_status start_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int me
             LaunchTimer lt(h, "norms_b", 0, 0, 0, 0, 0, 0);
             e = launch_match_ranks(h->stream, RankedRows{B->indptr, B->values, n, B->nnz, 0, start.b.ranks, start.b.tops},
                                    RankedRows{A->indptr, A->values, m, A->nnz, 1, reinterpret_cast<uint8_t *>(ws + L.ranks_a),
-                                              reinterpret_cast<float *>(ws + L.tops_a)});
+                                              reinterpret_cast<float *>(ws + L.tops_a)}, seen);
             if (e != hipSuccess) return hip_fail(h, e, "rank kernel");
             lt.done();
         } else {
-            st = stage_norms(h, B, start.b, metric, mi, q);
+            st = stage_norms(h, B, start.b, metric, mi, q, seen);
         }
         if (st != SPD_OK) return st;
         if (compact) {
@@ -871,12 +873,12 @@ spd_status start_match(spd_handle *h, const spd_csr *A, const spd_csr *B, int me
             start.listed.n_cols = way.columns;
             start.b.cols = c.totals;
         }
-        st = stage_lists(h, &start.listed, start.b, op, mi, knn_k > 0);
+        st = stage_lists(h, &start.listed, start.b, op, mi, knn_k > 0, seen);
         if (st != SPD_OK) return st;
     }
     if (op == OP_CHEB) return SPD_OK;
     LaunchTimer lt(h, "norms_a", 0, 0, 0, 0, 0, 0);
-    e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, metric, mi.transform, mi.norm, q.p, q.k,
+    e = launch_match_norms(h->stream, A->indptr, A->values, m, A->nnz, metric, mi.transform, mi.norm, q.p, q.k, seen,
                            reinterpret_cast<double *>(ws + L.norms_a), match_fixed(op) ? reinterpret_cast<int16_t *>(ws + L.scales_a) : nullptr);
     if (e != hipSuccess) return hip_fail(h, e, "norm kernel");
     lt.done();
@@ -1171,22 +1173,38 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         t_begin = t;
     };
 
-    // Where the row pointers have to be read back, the kernels that read them on the device (and stay within the arrays whatever they
-    // say) run meanwhile, and a call that is then refused waits for them: 1,531 x 28,301 ratings, Canberra, 521 -> 496 us a call.
+    // Where the row pointers have to be read back, the kernels that read them on the device run meanwhile (and do nothing where a
+    // first look at them there finds what the host will refuse), and a call that is then refused waits for them: 1,531 x 28,301
+    // ratings, Canberra, 521 -> 496 us a call.
     const OpParams params = op_params(metric, p, A->n_cols, nullptr);
     MatchStart start;
     bool begun = false;
-    auto begin_lists = [&]() -> spd_status {
-        if (!lists || begun) return SPD_OK;
+    auto begin_lists = [&](const RowsVerdict &seen) -> spd_status {
         begun = true;
-        return start_match(h, A, B, metric, op, knn_k, params, metric_info(metric), way, index, start);
+        return start_match(h, A, B, metric, op, knn_k, params, metric_info(metric), way, index, seen, start);
+    };
+    auto begin_unseen = [&]() -> spd_status {
+        if (!lists) return SPD_OK;
+        uint32_t *const word = reinterpret_cast<uint32_t *>(h->flag) + spd_handle::kRowsWord;
+        if (h->rows_looked_at++ == 0u) {                       // (0 is no call's number; such a call waits for a copy: it is not captured)
+            e = hipMemsetAsync(word, 0, sizeof *word, h->stream);
+            if (e != hipSuccess) return hip_fail(h, e, "hipMemsetAsync");
+            h->rows_looked_at = 1u;
+        }
+        e = launch_match_look_at_rows(h->stream, A->indptr, m, A->nnz, index || same ? nullptr : B->indptr, n, B->nnz, word, h->rows_looked_at);
+        if (e != hipSuccess) return hip_fail(h, e, "kernel of the row pointers");
+        return begin_lists(RowsVerdict{word, h->rows_looked_at});
+    };
+    auto refused = [&](spd_status why) {                         // (a call that is refused leaves nothing running)
+        if (begun) (void)hipStreamSynchronize(h->stream);
+        return why;
     };
     // (a direct call stages nothing else; the entry point that allocates nothing refuses what its staging memory does not hold, whichever
     // way a call runs)
     if (!lease && (!direct || ip_bytes || h->no_alloc)) {
         // (sized for the two plan uploads as well, which follow the row pointers in the buffer)
-        st = read_rows((index ? 0 : 32 * ((size_t)n + 4096)) + 48 * ((size_t)m + 4096), begin_lists);
-        if (st != SPD_OK) return st;
+        st = read_rows((index ? 0 : 32 * ((size_t)n + 4096)) + 48 * ((size_t)m + 4096), begin_unseen);
+        if (st != SPD_OK) return refused(st);
     }
     locate();
     st = check_ends();
@@ -1196,13 +1214,10 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         st = index || (b_checked && !b_staged) ? SPD_OK : refuse_rows(h, "B", b_ip, n, A->n_cols, b_staged);
         if (st == SPD_OK) st = refuse_rows(h, "A", a_ip, m, A->n_cols, !b_staged);
     }
-    if (st != SPD_OK) {
-        if (begun) (void)hipStreamSynchronize(h->stream);        // (a call that is refused leaves nothing running)
-        return st;
-    }
+    if (st != SPD_OK) return refused(st);
     if (direct) return run_direct(h, A, B, metric, op, knn_k, params, metric_info(metric), direct, out, out_idx, out_dist);
     if (lists) {
-        st = begin_lists();
+        if (!begun) st = begin_lists(RowsVerdict{nullptr, 0u});
         if (st != SPD_OK) return st;
         return run_match(h, A, B, metric, op, knn_k, params, metric_info(metric), way, start, a_ip, ip_bytes, out, out_idx, out_dist);
     }
@@ -1810,8 +1825,8 @@ spd_status spd_index_create(spd_handle *h, const spd_csr *Index, spd_metric metr
         if (hipMalloc(&ix->match_dev, lists.end) == hipSuccess) {
             ix->match = match_b_at(shape, lists, reinterpret_cast<unsigned char *>(ix->match_dev));
             ix->match_op = op;
-            st = stage_norms(h, Index, ix->match, run_as, mi, q);
-            if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, mi, true);
+            st = stage_norms(h, Index, ix->match, run_as, mi, q, RowsVerdict{nullptr, 0u});
+            if (st == SPD_OK) st = stage_lists(h, Index, ix->match, op, mi, true, RowsVerdict{nullptr, 0u});
             if (st != SPD_OK) return st;
         } else {                         // (no memory left for the lists: the packed copy serves every call)
             ix->match_dev = nullptr;

@@ -170,15 +170,23 @@ SPD_HD constexpr bool match_serves_knn(int op) { return match_serves(op) && op !
 // Whether the launches for a call's lists, of which A has m rows, are below 2^32 work-items each (`renumbered`: over A's columns).
 bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renumbered);
 
+// Row pointers that the host has not seen when the kernels which go by them are launched: no row leaves the arrays, but rows may
+// overlap, and all of them together be any number of times as long (0, nnz, 0, nnz, ...).  They are looked at on the device first, and these
+// kernels do nothing where `*word` is `malformed` (a number that no earlier call on the word had).  word nullptr: the host has.
+struct RowsVerdict { const uint32_t *word; uint32_t malformed; };
+// Writes `malformed` to *word where pointers do not begin at 0, fall or do not end at nnz (`b` nullptr: of one operand alone).
+hipError_t launch_match_look_at_rows(hipStream_t st, const int64_t *a, int64_t m, int64_t a_nnz, const int64_t *b, int64_t n, int64_t b_nnz,
+                                     uint32_t *word, uint32_t malformed);
+
 // (`scales` nullptr: not asked for)
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
-                              int metric, int transform, int norm, float p, double k, double *norms, int16_t *scales);
+                              int metric, int transform, int norm, float p, double k, const RowsVerdict &seen, double *norms, int16_t *scales);
 // Ranks and largest magnitudes of two operands' rows (`by_row`: the magnitudes of a row one after the other, else in planes).
 struct RankedRows { const int64_t *indptr; const float *values; int64_t n_rows, nnz; int by_row; uint8_t *ranks; float *tops; };
-hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const RankedRows &second);
+hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const RankedRows &second, const RowsVerdict &seen);
 // (after the norms; `b.least` nullptr: not asked for)
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
-                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int transform);
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int transform, const RowsVerdict &seen);
 hipError_t launch_match_columns(hipStream_t st, const int32_t *a_indices, int64_t a_nnz, const int64_t *b_indptr, const int32_t *b_indices,
                                 const float *b_values, int64_t b_rows, int64_t b_nnz, uint32_t n_cols, const MatchColumns &c);
 // k-NN: the rows' bounds, and where each row's candidate lists lie.

@@ -7,6 +7,30 @@
 namespace spd {
 
 // ------------------------------------------------------------------------------------
+// row pointers that the host has not seen yet
+// ------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) spd_match_look_at_rows_kernel(const int64_t *__restrict__ a, int64_t m, int64_t a_nnz,
+                                                                     const int64_t *__restrict__ b, int64_t n, int64_t b_nnz, uint32_t *word,
+                                                                     uint32_t malformed) {
+    const int64_t all = m + 1 + (b ? n + 1 : 0), step = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < all; i += step) {
+        const bool of_a = i <= m;
+        const int64_t *p = of_a ? a : b;
+        const int64_t r = of_a ? i : i - (m + 1), rows = of_a ? m : n, nnz = of_a ? a_nnz : b_nnz;
+        const int64_t at = p[r], before = r > 0 ? p[r - 1] : 0;
+        if ((r == 0 && at != 0) || at < before || (r == rows && at != nnz)) __atomic_store_n(word, malformed, __ATOMIC_RELAXED);
+    }
+}
+hipError_t launch_match_look_at_rows(hipStream_t st, const int64_t *a, int64_t m, int64_t a_nnz, const int64_t *b, int64_t n, int64_t b_nnz,
+                                     uint32_t *word, uint32_t malformed) {
+    const int64_t all = m + 1 + (b ? n + 1 : 0);
+    hipLaunchKernelGGL(spd_match_look_at_rows_kernel, dim3((unsigned)std::min<int64_t>(4096, (all + 255) / 256)), dim3(256), 0, st, a, m, a_nnz, b, n,
+                       b_nnz, word, malformed);
+    return hipGetLastError();
+}
+__device__ __forceinline__ bool rows_malformed(const RowsVerdict &seen) { return seen.word && *seen.word == seen.malformed; }
+
+// ------------------------------------------------------------------------------------
 // row norms: G lanes to the row, four entries of a lane in flight; with up to 64 lanes to the row, rows of more than 64
 // entries a lane wait for the whole workgroup, one after the other (500,000 rows of 1 to 50,000 entries: 332 us while a
 // wavefront went through the longest alone, 260 now)
@@ -14,8 +38,9 @@ namespace spd {
 template <int G, bool SCALES>
 __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__restrict__ indptr, const float *__restrict__ values,
                                                               int64_t n_rows, int64_t nnz, int metric, int transform, int norm,
-                                                              float p, double k, double *__restrict__ norms,
+                                                              float p, double k, const RowsVerdict seen, double *__restrict__ norms,
                                                               int16_t *__restrict__ scales) {
+    if (rows_malformed(seen)) return;
     constexpr int kRows = 256 / G;
     constexpr int64_t kLong = G < 256 ? 64 * G : INT64_MAX;
     __shared__ int s_long[kRows], s_longs;
@@ -103,7 +128,8 @@ __global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__r
 // are waiting, so that a long row is sorted two or three times and not for every 64 entries (7,777 rows of 37, the longest
 // 2,000, and 3,333 of them, a launch each, sorted for every 64 entries: 28 us each; 17 for both now).
 // ------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) spd_match_ranks_kernel(const RankedRows first, const RankedRows second) {
+__global__ void __launch_bounds__(256) spd_match_ranks_kernel(const RankedRows first, const RankedRows second, const RowsVerdict seen) {
+    if (rows_malformed(seen)) return;
     const int lane = (int)threadIdx.x & 63;
     const int64_t at = (int64_t)blockIdx.x * 4 + wave_uniform((int)threadIdx.x >> 6);
     const bool is_first = at < first.n_rows;
@@ -174,10 +200,10 @@ __global__ void __launch_bounds__(256) spd_match_ranks_kernel(const RankedRows f
         o.tops[o.by_row ? row * kRanks + lane : (int64_t)lane * o.n_rows + row] = best != kNone ? __uint_as_float(~(uint32_t)(best >> 32)) : 0.0f;
     }
 }
-hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const RankedRows &second) {
+hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const RankedRows &second, const RowsVerdict &seen) {
     const int64_t rows = first.n_rows + second.n_rows;
     if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(spd_match_ranks_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, first, second);
+    hipLaunchKernelGGL(spd_match_ranks_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, first, second, seen);
     return hipGetLastError();
 }
 
@@ -225,7 +251,8 @@ template <int G>
 __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                         const float *__restrict__ values, int64_t n_rows, int64_t nnz,
                                                                         uint32_t most_cols, MatchB b, uint32_t blocks_per_wg, uint32_t wgs, int unit,
-                                                                        int transform, bool with_values) {
+                                                                        int transform, bool with_values, const RowsVerdict seen) {
+    if (rows_malformed(seen)) return;
     extern __shared__ __align__(16) unsigned char s_raw[];
     __shared__ uint32_t s_wave[kBuildThreads / kWave];
     __shared__ uint32_t s_dense[kBuildDense], s_long[kBuildLong], s_longs;
@@ -548,13 +575,13 @@ int match_norm_lanes(int64_t n_rows, int64_t nnz) {
     return mean >= 128 && n_rows <= 8192 ? 256 : (mean >= 16 ? 64 : 4);
 }
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
-                              int metric, int transform, int norm, float p, double k, double *norms, int16_t *scales) {
+                              int metric, int transform, int norm, float p, double k, const RowsVerdict &seen, double *norms, int16_t *scales) {
     if (n_rows <= 0) return hipSuccess;
     auto go = [&](auto g) {
         constexpr int G = decltype(g)::value;
         const int per = 256 / G;
         hipLaunchKernelGGL((scales ? spd_match_norms_kernel<G, true> : spd_match_norms_kernel<G, false>), dim3((unsigned)((n_rows + per - 1) / per)),
-                           dim3(256), 0, st, indptr, values, n_rows, nnz, metric, transform, norm, p, k, norms, scales);
+                           dim3(256), 0, st, indptr, values, n_rows, nnz, metric, transform, norm, p, k, seen, norms, scales);
     };
     switch (match_norm_lanes(n_rows, nnz)) {
     case 256: go(std::integral_constant<int, 256>{}); break;
@@ -641,7 +668,7 @@ bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renu
 }
 
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
-                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int transform) {
+                              int64_t n_rows, int64_t nnz, uint32_t k, const MatchB &b, int op, int transform, const RowsVerdict &seen) {
     if (n_rows <= 0) return hipSuccess;
     const MatchShape &s = b.shape;
     const uint32_t per_wg = match_build_blocks(s), wgs = ((uint32_t)s.blocks + per_wg - 1u) / per_wg;
@@ -652,7 +679,7 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
         hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(kern, dim3(((unsigned)s.n_tiles * wgs + 7u) / 8u * 8u), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
-                           nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op != OP_CNT);
+                           nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op != OP_CNT, seen);
         return hipGetLastError();
     };
     // (a row's stretch in the two loads of its lanes, where that leaves no more than half of them idle: rows of 1,820 over 51 blocks 1,078 us

@@ -792,3 +792,69 @@ def test_canberra_of_values_at_the_ends_of_their_range(spd, n):
     idx, dist = h.knn(dA, dB, "canberra", 9)
     assert_knn_matches(_np(idx), _np(dist), want, 9, "canberra", "canberra")
     h.close()
+
+
+@pytest.mark.parametrize("entry,metric,lists", [("pairwise", "chebyshev", 2)] + [
+    (entry, metric, lists) for entry, metric in (("pairwise", "l1"), ("pairwise", "cosine"), ("knn", "canberra"), ("index_knn", "jaccard"))
+    for lists in (2, 3)])
+def test_row_pointers_on_the_gpu_alone(spd, lists, entry, metric):
+    """What is launched before the row pointers are on the host: the results of the call that brings them, the same refusals, nothing
+    written for a call that is refused, and a sound call after one."""
+    import torch
+    rng = np.random.default_rng(8)
+    A, B = _matrix(rng, 40, 60, (3, 17, 0, 9)), _matrix(rng, 70, 60, (5, 1, 30))
+    h = spd.Handle()
+    h.set_option("match_lists", lists)
+    h.set_option("profile", 1)
+
+    def call(h, MA, MB, keep):
+        dA, dB = (spd.DeviceCsr.from_host(M, keep_host_indptr=keep) for M in (MA, MB))
+        if entry == "pairwise":
+            out = [h.pairwise(dA, dB, metric)]
+        elif entry == "knn":
+            out = h.knn(dA, dB, metric, 7)
+        else:
+            ix = h.index_create(spd.DeviceCsr.from_host(B), metric)
+            out = ix.knn(dA, 7)
+        out = [_np(x) for x in out]
+        if entry == "index_knn":
+            ix.close()
+        return out
+
+    want = call(h, A, B, True)
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    scratch = torch.empty(1 << 22, dtype=torch.uint8, device="cuda")
+    h.set_workspace(scratch)
+    for fault in ("pointers do not begin at 0", "pointers decrease", "all entries in every other row", "last pointer", "row longer than the column count"):
+        for which in (0, 1) if entry != "index_knn" else (0,):
+            M = [{name: (value.copy() if hasattr(value, "copy") else value) for name, value in X.items()} for X in (A, B)]
+            ip = M[which]["indptr"]
+            if fault == "pointers do not begin at 0":
+                ip[0] = 1
+            elif fault == "pointers decrease":
+                ip[5] = ip[9] + 1
+            elif fault == "all entries in every other row":
+                ip[1:-1:2] = ip[-1]
+                ip[2:-1:2] = 0
+            elif fault == "last pointer":
+                ip[-1] += 1
+            else:
+                ip[1:-1] = ip[-1]                           # (the first row has them all)
+            print("row pointers on the GPU alone", lists, entry, metric, fault, which, flush=True)
+            scratch.fill_(0xA5)
+            status = []
+            for keep in (True, False):
+                try:
+                    call(h, M[0], M[1], keep)
+                    status.append("SPD_OK")
+                except spd.SpdError as e:
+                    status.append(e.status_name)
+            assert status[0] == status[1]
+            if fault != "row longer than the column count":
+                assert status[1] != "SPD_OK"
+                # (over A's columns those are counted beside the row pointers)
+                assert lists == 3 or bool((scratch == 0xA5).all().item())
+    for got, same in zip(call(h, A, B, False), want):
+        assert np.array_equal(got, same)
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    h.close()
