@@ -548,10 +548,9 @@ MatchB match_b_at(const MatchShape &s, const MatchLayout &L, unsigned char *dev)
 // Grid of the column-list kernel: groups of tiles times slices of A's rows, one workgroup for each
 // compute unit of the chip.  Where the lists are more than the L2 caches hold, the tiles are dealt to the
 // eight XCDs, and the workgroups of an XCD go through its tiles together; smaller lists are in every L2
-// anyway, and each tile is a group.  Rows of A that hold more than a third of a wavefront's share of
-// the entries are shared by the wavefronts of a workgroup.
+// anyway, and each tile is a group.  Rows of A from `shared_len` entries on are shared by the wavefronts of a workgroup.
 struct MatchGrid { int slices = 1, groups = 1, by_xcd = 0, run = 1; int64_t share = 0, shared_len = 0; };         // share: of A's entries, a wavefront's
-MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int64_t m, int64_t nnz_a, int64_t nnz_b, bool knn) {
+MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int op, int64_t m, int64_t nnz_a, int64_t nnz_b, bool knn) {
     MatchGrid g;
     const int64_t cus = std::max(1, opt.n_cus), rows_slices = std::max<int64_t>(1, (m + s.waves - 1) / s.waves);
     if (s.n_tiles >= 16 && nnz_b * 8 > kMatchL2Bytes) {
@@ -565,8 +564,14 @@ MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int64_t m, int
         g.slices = (int)std::max<int64_t>(1, std::min(rows_slices, cus / g.groups));
     }
     const int64_t tiles = (s.n_tiles + g.groups - 1) / g.groups;
+    // Shared rows: those of a third of a wavefront's share of A's entries.  Where the wavefronts add to one strip, such a row costs one wait:
+    // it pays from half that length on, and pairwise, where they form its distances together too, short rows are as well with a
+    // wavefront each.  (A third / a sixth / a twelfth of the share, us: sets, Jaccard, k-NN 8,816 / 8,489 / 8,785; from 128 / 256 /
+    // 512 entries on: 10,000 x 10,000 rows of 38, L1 297 / 298 / 288.  Fp64 sums take a strip for each wavefront: inner products of 2,000 x
+    // 30,000 counts, a third / a sixth, 7,766 / 8,379.)
     g.share = nnz_a * tiles / ((int64_t)g.slices * s.waves);
-    g.shared_len = std::max<int64_t>(256, g.share / 3);
+    const bool one_strip = match_any_order(op);
+    g.shared_len = std::max<int64_t>(one_strip && !knn ? 512 : 256, g.share / (one_strip ? 6 : 3));
     // A wavefront goes through a run of tiles with a row: as many as leave every wavefront four rows' runs, and whose lists
     // (and bounds) together lie in half of an L2.  What a row costs besides its lists is then paid once a run, and with
     // k-NN its nearest are merged into the row's list once a run.
@@ -721,10 +726,12 @@ double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64
                   bool skewed) {
     const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz, tiles = (double)s.n_tiles;
     const OpCost c = op_cost(op);
-    const MatchGrid g = match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn);
+    const MatchGrid g = match_grid(h->opt, s, op, A->n_rows, A->nnz, B->nnz, knn);
     const double rows = std::ceil(m / g.slices), runs = std::ceil(tiles / g.groups);          // of a workgroup
     double idle = rows * runs * (double)h->opt.n_cus / (m * tiles);
-    if (nnz_a <= (double)g.shared_len * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
+    // (a third of the share for every product, as when the constants were fitted: with the marks of the kernels, 90 of 55,684 random calls
+    // take the other way, and 60 of these are 1.4 times as slow by it on the mean)
+    if (nnz_a <= (double)std::max<int64_t>(256, g.share / 3) * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
     const double density = nnz_b / n / (double)columns, list = density * (double)s.tile_rows;  // entries, on the mean
     const double met = skewed ? std::max(1.0, std::min(40.0, 0.07 / density)) : 1.0;
     const double make = made ? 0.0 : 22.5e6 + 29.0 * nnz_b + 6.3 * tiles * (double)s.ptr_stride + 150.0 * n;
@@ -750,7 +757,7 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     if (semiring || A->n_rows <= 0 || !match_possible(h, B, op, s)) return false;
     if ((knn || with_index) && !match_serves_knn(op)) return false;
     if (op == OP_CHEB && A->n_rows + B->n_rows >= (int64_t)1 << 26) return false;             // (a wavefront to the row that is ranked)
-    if (match_items(s, match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
+    if (match_items(s, match_grid(h->opt, s, op, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
     if (!match_launches_fit(s, A->n_rows, A->nnz, false)) return false;
     if (h->match_lists == 2) return true;
     if (!match_suits(h, B, op, s)) return false;
@@ -769,7 +776,7 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     if (A->n_cols > kMatchMostColumns) return false;
     const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
     if (s.n_tiles <= 0 || s.list_entries(B->nnz) >= ((int64_t)1 << 29)) return false;
-    if (match_items(s, match_grid(h->opt, s, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
+    if (match_items(s, match_grid(h->opt, s, op, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
     if (!match_launches_fit(s, A->n_rows, A->nnz, true)) return false;
     if (h->match_lists == 3) return true;
     if (h->match_lists != 1 || !scan_knobs_untouched(h) || !match_bounds_fit(s, B->nnz)) return false;
@@ -794,12 +801,7 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
     if (w.way == 0) return w;
     w.columns = w.way == 2 ? columns_of(A) : A->n_cols;
     w.s = match_shape(h->opt.lds_budget, op, B->n_rows, w.columns, B->nnz);
-    w.g = match_grid(h->opt, w.s, A->n_rows, A->nnz, B->nnz, knn);
-    // Where the wavefronts that share a row add to one strip, the row costs one wait: it pays from half that length on, and pairwise,
-    // where they form its distances together too, short rows are as well with a wavefront each.  (A third / a sixth / a twelfth of
-    // the share, us: sets, Jaccard, k-NN 8,816 / 8,489 / 8,785, words, cosine 5,368 / 5,435 / 6,737; from 128 / 256 / 512 entries on: 10,000 x
-    // 10,000 rows of 38, L1 297 / 298 / 288, cosine, k-NN 504 / 507 / 534.)
-    if (match_any_order(op)) w.g.shared_len = std::max<int64_t>(knn ? 256 : 512, w.g.share / 6);
+    w.g = match_grid(h->opt, w.s, op, A->n_rows, A->nnz, B->nnz, knn);
     w.L = layout_match_call(w.s, w.g, op, A->n_rows, A->nnz, B->n_rows, B->nnz, knn_k, w.way == 2 || !with_index, w.way == 2 ? A->n_cols : 0);
     return w;
 }
@@ -2019,7 +2021,7 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
         w.columns = n_cols;
         w.s = match_shape(h.opt.lds_budget, op, b_rows, n_cols, b_nnz);
         if (w.s.n_tiles <= 0) return SPD_OK;
-        w.g = match_grid(h.opt, w.s, a_rows, a_nnz, b_nnz, knn);
+        w.g = match_grid(h.opt, w.s, op, a_rows, a_nnz, b_nnz, knn);
         w.L = layout_match_call(w.s, w.g, op, a_rows, a_nnz, b_rows, b_nnz, k_neighbors, !with_index, 0);
     }
     out->columns = w.columns;

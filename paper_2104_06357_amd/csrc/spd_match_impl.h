@@ -284,6 +284,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     using S = Sums<OP>;
     constexpr bool FIX = S::FIX;
     using Acc = typename S::Acc;
+    static_assert(S::kAnyOrder || !match_any_order(OP), "rows are shared from half the length on where the wavefronts add to one strip");
     // D: 64-row pieces of a dense column that are summed in registers together; the largest tiles hold 19 for one
     // fp64 sum (one round of 19 against two of 10: 2,048 queries of 300,000 rows of 230, 10.5 -> 10.2 ms; 13 and 6
     // leave half a round idle: 11.3) and 39 for a count; a sum and a count have 13 and Minkowski's three numbers 10, in two rounds of 7
