@@ -523,12 +523,11 @@ int product_of(const spd_handle *h, int metric, float p) {
 }
 
 struct MatchLayout { size_t values, rows, ptr, norms, least, ranks, tops, end; };
-MatchLayout layout_match(const MatchShape &s, int op, int64_t n, int64_t nnz, Carver &cv) {
+// (`spare`: bytes behind the entries' rows)
+MatchLayout layout_match(const MatchShape &s, int op, int64_t n, int64_t nnz, size_t spare, Carver &cv) {
     MatchLayout L;
     L.values = cv.take((size_t)s.list_entries(nnz) * 4);
-    // (half of it is spare: a call asks for the scratch it has asked for, and scratch of a given size sends the same calls to the
-    // staged scan, as when an entry took eight bytes)
-    L.rows = cv.take((size_t)s.list_entries(nnz) * 4);
+    L.rows = cv.take((size_t)s.list_entries(nnz) * 2 + spare);
     L.ptr = cv.take((size_t)s.n_tiles * (size_t)s.ptr_stride * 4);
     L.norms = cv.take((size_t)n * 16);
     L.least = cv.take((size_t)s.n_tiles * 16);
@@ -593,7 +592,9 @@ MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int op, 
                                bool with_b, int64_t columns) {
     MatchScratch L{};
     Carver cv;
-    if (with_b) L.b = layout_match(s, op, n, nnz_b, cv);
+    // (two bytes to a stored entry are spare in scratch, so that scratch of a given size, the static array among it, sends mostly the same
+    // calls to the staged scan as when an entry took eight)
+    if (with_b) L.b = layout_match(s, op, n, nnz_b, (size_t)nnz_b * 2, cv);
     if (columns > 0) {
         const size_t words = ((size_t)columns + 31) / 32, masks = ((size_t)nnz_b + 63) / 64;
         L.c.words = cv.take(words * 8);
@@ -689,7 +690,7 @@ bool match_suits(const spd_handle *h, const spd_csr *B, int op, const MatchShape
 bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape &s, MatchLayout &L) {
     if (!match_possible(h, B, op, s) || !match_serves_knn(op)) return false;
     Carver cv;
-    L = layout_match(s, op, B->n_rows, B->nnz, cv);
+    L = layout_match(s, op, B->n_rows, B->nnz, 0, cv);
     if (h->match_lists == 2) return true;
     if (op == OP_CNT) return false;                // (counts come out the same by the scan, which is as fast where a call has no B to prepare)
     return match_suits(h, B, op, s) && (int64_t)L.end <= 20 * B->nnz + 16 * B->n_rows + (1 << 20);

@@ -396,6 +396,10 @@ def test_an_index_keeps_lists_that_calls_may_want_within_the_stated_memory():
     for n, nnz, cols, metric in ((56_257, 5_172_942, 236_097, "hellinger"), (12_970, 77_804, 10_261, "jensen_shannon"),
                                  (10_772, 4_546_630, 728_767, "kl_divergence")):
         assert kept(n, nnz / n, cols, metric) > 0, (n, cols, metric)
+    # ... and with an entry of six bytes, and six to what a dense column may need: sizes whose lists eight left out
+    for n, nnz, cols, metric in ((94_601, 70_971, 2_890, "jensen_shannon"), (172_261, 19_812, 862, "cosine"), (3_570, 1_759, 42_690, "l1"),
+                                 (15_919, 8_254, 20_697, "hamming"), (185_974, 572_974, 10_395, "hamming")):
+        assert kept(n, nnz / n, cols, metric) > 0, (n, cols, metric)
     # the working range
     for n, mean, cols in ((300, 37, 20_000), (12_000, 37, 20_000), (5_000, 228, 102_660), (300_000, 228, 102_660), (500, 1_820, 26_000),
                           (60_000, 1_820, 26_000), (2_000, 160, 194_000), (200_000, 160, 194_000)):
