@@ -655,6 +655,10 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     s.tile_extra = (int64_t)s.blocks * s.dense_per_block * s.dense_room();
     s.build_lds_bytes = s.stage * 6u + (4u << shift) + (uint32_t)rows_bytes;
     s.n_tiles = (int32_t)((n + s.tile_rows - 1) / s.tile_rows);
+    if (op == OP_DOT && s.list_entries(nnz) >= (int64_t)1 << 29) {         // (positions end there: no more room than other products' columns take)
+        s.dense_from = std::max(1, s.tile_rows / 2);
+        s.tile_extra = (int64_t)s.blocks * s.dense_per_block * s.dense_room();
+    }
     return s;
 }
 

@@ -319,6 +319,13 @@ def test_column_lists_only_where_their_launches_fit_a_grid():
         assert plan["consistent"] and (plan["way"] == 1) == (plan["tiles"] < 1 << 22)
 
 
+def test_inner_products_of_as_many_entries_as_other_products_take_the_lists():
+    """Dense columns of a dot product begin at fewer rows and need more room; positions of list entries end at 2^29 for all products."""
+    for n, nnz, cols in ((380_421, 331_064_897, 20_521), (380_421, 360_000_000, 20_521), (300_000, 440_000_000, 102_660)):
+        plans = [spd.testing.host_list_plan(12, 3_500, n, nnz, cols, metric, match_lists=2) for metric in ("inner_product", "cosine", "l1", "canberra")]
+        assert len({p["way"] for p in plans}) == 1 and all(p["consistent"] == p["wanted"] for p in plans), (n, nnz, cols)
+
+
 def test_the_cut_of_the_column_lists_is_consistent():
     """What check_plan verifies, over random sizes, with the lists wanted wherever a product has them."""
     rng = np.random.default_rng(23)
