@@ -627,6 +627,7 @@ MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int op, 
 std::string match_check(const PlanOptions &opt, const MatchShape &s, const MatchGrid &g, int op, int64_t m, int64_t n, int64_t n_cols,
                         int64_t nnz_b) {
     const int64_t T = s.tile_rows, tiles = s.n_tiles, blocks = s.blocks, cell = match_cell_bytes(op);
+    if (op == OP_CHEB && T > kRankedRows) return "ranked rows";
     if (T < kWave || T % kWave != 0 || tiles * T < n || (tiles - 1) * T >= n) return "tiles do not cover B";
     if (s.waves != match_waves((int)cell) || s.lds_bytes != (uint32_t)s.waves * match_strip_bytes((int)cell, (int)T) ||
         (int64_t)s.lds_bytes + match_static_lds((int)cell) > opt.lds_budget) return "strips over the LDS";
@@ -757,9 +758,8 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     MatchShape s;
     if (semiring || A->n_rows <= 0 || !match_possible(h, B, op, s)) return false;
     if ((knn || with_index) && !match_serves_knn(op)) return false;
-    if (op == OP_CHEB && A->n_rows + B->n_rows >= (int64_t)1 << 26) return false;             // (a wavefront to the row that is ranked)
     if (match_items(s, match_grid(h->opt, s, op, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
-    if (!match_launches_fit(s, A->n_rows, A->nnz, false)) return false;
+    if (!match_launches_fit(s, op, A->n_rows, A->nnz, B->n_rows, false)) return false;
     if (h->match_lists == 2) return true;
     if (!match_suits(h, B, op, s)) return false;
     // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.34; 1,024 x 300,000 of 230, cosine
@@ -778,7 +778,7 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
     if (s.n_tiles <= 0 || s.list_entries(B->nnz) >= ((int64_t)1 << 29)) return false;
     if (match_items(s, match_grid(h->opt, s, op, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
-    if (!match_launches_fit(s, A->n_rows, A->nnz, true)) return false;
+    if (!match_launches_fit(s, op, A->n_rows, A->nnz, B->n_rows, true)) return false;
     if (h->match_lists == 3) return true;
     if (h->match_lists != 1 || !scan_knobs_untouched(h) || !match_bounds_fit(s, B->nnz)) return false;
     // (where the lists over all columns have room for their bounds, the copy is not worth its time)

@@ -168,7 +168,7 @@ constexpr int kRanks = 32, kRankShift = 10, kRankedRows = 832;      // (rank and
 SPD_HD constexpr bool match_serves_knn(int op) { return match_serves(op) && op != OP_CHEB; }
 
 // Whether the launches for a call's lists, of which A has m rows, are below 2^32 work-items each (`renumbered`: over A's columns).
-bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renumbered);
+bool match_launches_fit(const MatchShape &s, int op, int64_t m, int64_t nnz_a, int64_t n, bool renumbered);
 
 // Row pointers that the host has not seen when the kernels which go by them are launched: no row leaves the arrays, but rows may
 // overlap, and all of them together be any number of times as long (0, nnz, 0, nnz, ...).  They are looked at on the device first, and these

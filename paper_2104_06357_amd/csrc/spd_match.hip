@@ -200,10 +200,11 @@ __global__ void __launch_bounds__(256) spd_match_ranks_kernel(const RankedRows f
         o.tops[o.by_row ? row * kRanks + lane : (int64_t)lane * o.n_rows + row] = best != kNone ? __uint_as_float(~(uint32_t)(best >> 32)) : 0.0f;
     }
 }
+static int64_t match_ranks_grid(int64_t rows) { return (rows + 3) / 4; }
 hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const RankedRows &second, const RowsVerdict &seen) {
     const int64_t rows = first.n_rows + second.n_rows;
     if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(spd_match_ranks_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, first, second, seen);
+    hipLaunchKernelGGL(spd_match_ranks_kernel, dim3((unsigned)match_ranks_grid(rows)), dim3(256), 0, st, first, second, seen);
     return hipGetLastError();
 }
 
@@ -664,11 +665,16 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
 
 // Column blocks to a workgroup: some 2,048 workgroups (a run of blocks looks its rows' first entries up once).
 static uint32_t match_build_blocks(const MatchShape &s) { return std::max(1u, (uint32_t)((uint64_t)s.blocks * (uint64_t)s.n_tiles / 2048u)); }
-bool match_launches_fit(const MatchShape &s, int64_t m, int64_t nnz_a, bool renumbered) {
-    constexpr int64_t kMost = ((int64_t)1 << 32) - 1024;
+// (its workgroups in whole rounds of the eight XCDs)
+static int64_t match_build_grid(const MatchShape &s) {
     const int64_t per_wg = match_build_blocks(s);
-    return m * match_norm_lanes(std::max<int64_t>(m, 1), nnz_a) <= kMost && s.n_tiles * ((s.blocks + per_wg - 1) / per_wg) * kBuildThreads <= kMost &&
-           (!renumbered || nnz_a <= kMost);
+    return (s.n_tiles * ((s.blocks + per_wg - 1) / per_wg) + 7) / 8 * 8;
+}
+bool match_launches_fit(const MatchShape &s, int op, int64_t m, int64_t nnz_a, int64_t n, bool renumbered) {
+    constexpr int64_t kMost = ((int64_t)1 << 32) - 1024;
+    // (B's norms: of fewer than 2^30 rows and, from 16 entries to the row on, 2^25 of them, by its lists' positions)
+    return (op == OP_CHEB ? match_ranks_grid(m + n) * 256 <= kMost : m * match_norm_lanes(std::max<int64_t>(m, 1), nnz_a) <= kMost) &&
+           match_build_grid(s) * kBuildThreads <= kMost && (!renumbered || nnz_a <= kMost);
 }
 
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
@@ -682,7 +688,7 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
         static std::atomic<uint32_t> allowed[kMatchDevices];
         hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(kern, dim3(((unsigned)s.n_tiles * wgs + 7u) / 8u * 8u), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
+        hipLaunchKernelGGL(kern, dim3((unsigned)match_build_grid(s)), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
                            nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op != OP_CNT, seen);
         return hipGetLastError();
     };

@@ -317,6 +317,10 @@ def test_column_lists_only_where_their_launches_fit_a_grid():
     for n in (268_000_000, 269_000_000):                   # (tiles of 64 rows: 2^22 of them are too many)
         plan = spd.testing.host_list_plan(1_000, 10_000, n, n, 50, "l1", match_lists=2, lds_budget=16_000)
         assert plan["consistent"] and (plan["way"] == 1) == (plan["tiles"] < 1 << 22)
+    for tiles in ((1 << 22) - 16, (1 << 22) - 5):           # (... and whole rounds of eight of them)
+        assert (way(1_000, 10, 64 * tiles, 1, 50, "l1", match_lists=2, lds_budget=16_000) == 1) == (tiles == (1 << 22) - 16)
+    for rows in ((1 << 26) - 24, (1 << 26) - 3):            # (a wavefront to the row that is ranked)
+        assert (way(rows - 100, 2, 100, 20, 1_000, "chebyshev", match_lists=2) == 1) == (rows == (1 << 26) - 24)
 
 
 def test_inner_products_of_as_many_entries_as_other_products_take_the_lists():
