@@ -571,6 +571,13 @@ MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int op, int64_
     g.share = nnz_a * tiles / ((int64_t)g.slices * s.waves);
     const bool one_strip = match_any_order(op);
     g.shared_len = std::max<int64_t>(one_strip && !knn ? 512 : 256, g.share / (one_strip ? 6 : 3));
+    // Chebyshev: a row of A that is like many of B's costs its wavefront two microseconds a pair (spd_match_impl.h).  Where a wavefront to the row
+    // leaves half of the compute units idle, rows of some length are all shared: 500 x 500 rows of 50 ones over one support 880 -> 152 us
+    // (staged scan 271), 1,000 x 1,000 of 100 1,258 -> 639 (1,314), of 100 normal values 205 -> 136; 237 x 5,101 rows of 223 194 -> 145.
+    if (op == OP_CHEB && !g.by_xcd && 2 * (int64_t)g.slices * g.groups <= cus && nnz_a >= 16 * m) {
+        g.slices = (int)std::max<int64_t>(1, std::min<int64_t>(m, cus / g.groups));
+        g.shared_len = 0;
+    }
     // A wavefront goes through a run of tiles with a row: as many as leave every wavefront four rows' runs, and whose lists
     // (and bounds) together lie in half of an L2.  What a row costs besides its lists is then paid once a run, and with
     // k-NN its nearest are merged into the row's list once a run.

@@ -647,62 +647,81 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
             if ((first_a == (uint32_t)kRanks && next_a > most) || (first_b == (uint32_t)kRanks && next_b > most)) doubt |= 1u << g;
         }
         if (__ballot(doubt != 0u) != 0) {
-            // the largest entry of one row, beyond what the pair has, in a column that the other does not store: by the whole wavefront
-            auto beyond = [&](const int32_t *xi, const float *xv, int64_t x0, int64_t x1, const int32_t *yi, const float *yv, int64_t y0, int64_t y1, float most) {
-                // (rows that are all met are mostly alike: an entry is looked for at its own place in the other row first, then outwards)
-                for (int64_t e0 = x0 + lane; e0 < x1; e0 += 4 * kWave) {
-                    float v[4], w[4];
-                    int32_t col[4], at_guess[4];
-                    int64_t guess[4];
+            // The largest entry of one row, beyond what the pair has, in a column that the other does not store: by the whole wavefront.
+            // Rows that are all met are mostly alike: an entry is looked for at its own place in the other row first, then next
+            // to it, then outwards, and the other way round only where the columns are not the same ones.  (1,000 x 1,000 rows of 100
+            // ones over one support: 2,513 us with both ways always and a reduction through LDS, 1,320 by the staged scan, 560 now, of which
+            // the grid gives half; over supports that differ by a column 1,936, 884 and 610.  Both rows in one pass: 677 and 523, but ratings,
+            // whose pairs' first pass mostly settles the second, 347 -> 406.)
+            auto stored = [](const int32_t *yi, const float *yv, int y1, int guess, int32_t at_guess, int32_t col) {
+                const bool up = at_guess < col;
+                int lo = 0, hi = y1, step = 1;
+                const int next = up ? guess + 1 : guess - 1;
+                if (next < 0 || next >= y1) return false;
+                const int32_t c = yi[next];
+                const float w = yv[next];
+                if (c == col) return w != 0.0f;
+                if (up) {
+                    if (c > col) return false;
+                    lo = next + 1;
+                    while (hi - lo > step && yi[lo + step] < col) { lo += step + 1; step *= 2; }
+                    hi = min(hi, lo + step + 1);
+                } else {
+                    if (c < col) return false;
+                    hi = next;
+                    while (hi - lo > step && yi[hi - step] >= col) { hi -= step; step *= 2; }
+                    lo = max(lo, hi - step);
+                }
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (yi[mid] < col) lo = mid + 1; else hi = mid;
+                }
+                return lo < y1 && yi[lo] == col && yv[lo] != 0.0f;
+            };
+            // (`alike`: whether the entries of both rows are the same columns', and no stored zero hides one of the other's)
+            auto beyond = [&](const int32_t *xi, const float *xv, int lx, const int32_t *yi, const float *yv, int ly, float most, bool &alike) {
+                alike = lx == ly;
+                for (int e = lane; e < lx; e += 2 * kWave) {
+                    float v[2], w[2];
+                    int32_t col[2], at_guess[2];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int64_t e = e0 + u * kWave;
-                        guess[u] = min(y0 + (e - x0), y1 - 1);
-                        v[u] = e < x1 ? fabsf(xv[e]) : 0.0f;
-                        col[u] = e < x1 ? xi[e] : 0;
-                        at_guess[u] = y0 < y1 ? yi[guess[u]] : -1;
-                        w[u] = y0 < y1 ? yv[guess[u]] : 0.0f;
+                    for (int u = 0; u < 2; ++u) {
+                        const int x = e + u * kWave, guess = max(min(x, ly - 1), 0);
+                        v[u] = x < lx ? fabsf(xv[x]) : 0.0f;
+                        col[u] = x < lx ? xi[x] : 0;
+                        at_guess[u] = ly > 0 ? yi[guess] : -1;
+                        w[u] = ly > 0 ? yv[guess] : 0.0f;
                     }
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        if (!(v[u] > most)) continue;
-                        if (at_guess[u] == col[u]) {
-                            if (w[u] == 0.0f) most = v[u];
-                            continue;
-                        }
-                        int64_t lo = y0, hi = y1, step = 1;
-                        if (at_guess[u] < col[u]) {
-                            lo = min(guess[u] + 1, y1);
-                            while (hi - lo > step && yi[lo + step] < col[u]) { lo += step + 1; step *= 2; }
-                            hi = min(hi, lo + step + 1);
-                        } else {
-                            hi = max(guess[u], y0);
-                            while (hi - lo > step && yi[hi - step] >= col[u]) { hi -= step; step *= 2; }
-                            lo = max(lo, hi - step);
-                        }
-                        while (lo < hi) {
-                            const int64_t mid = (lo + hi) >> 1;
-                            if (yi[mid] < col[u]) lo = mid + 1; else hi = mid;
-                        }
-                        if (!(lo < y1 && yi[lo] == col[u] && yv[lo] != 0.0f)) most = v[u];
+                    for (int u = 0; u < 2; ++u) {
+                        const int x = e + u * kWave;
+                        const bool here = at_guess[u] == col[u];
+                        alike &= x >= lx || (here && v[u] != 0.0f);
+                        if (v[u] > most && !(here ? w[u] != 0.0f : stored(yi, yv, ly, min(x, ly - 1), at_guess[u], col[u]))) most = v[u];
                     }
                 }
-#pragma unroll
-                for (int w = 32; w >= 1; w >>= 1) most = fmaxf(most, __shfl_xor(most, w));
-                return most;
+                alike = __ballot(!alike) == 0;
+                return __int_as_float(__builtin_amdgcn_readlane(wave_scan_max(__float_as_int(most)), 63));          // (none is negative)
             };
 #pragma unroll 1
             for (int g = 0; g < G; ++g) {
-                for (uint64_t left = __ballot((doubt >> g) & 1u); left; left &= left - 1) {
+                uint64_t left = __ballot((doubt >> g) & 1u);
+                if (left == 0) continue;
+                const int64_t j = j0 + min(from + g * step + lane, tile_n - 1);
+                const int64_t first = clamp_i64(args.b_indptr[j], 0, args.b_nnz), last = clamp_i64(args.b_indptr[j + 1], first, args.b_nnz);
+                for (; left; left &= left - 1) {
                     const int l = (int)__builtin_ctzll(left), i = from + g * step + l;
                     if (i >= tile_n) continue;
-                    const int64_t b0 = clamp_i64(args.b_indptr[j0 + i], 0, args.b_nnz), b1 = clamp_i64(args.b_indptr[j0 + i + 1], b0, args.b_nnz);
+                    const int64_t b0 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(first >> 32), l) << 32) |
+                                                 (uint32_t)__builtin_amdgcn_readlane((int)first, l));
+                    const int lb = __builtin_amdgcn_readlane((int)(last - first), l);
                     float mine = 0.0f;
 #pragma unroll
                     for (int u = 0; u < G; ++u) mine = u == g ? d[u] : mine;
-                    float most = __shfl(mine, l);
-                    most = beyond(args.a_indices, args.a_values, a_begin, a_begin + a_len, args.b_indices, args.b_values, b0, b1, most);
-                    most = beyond(args.b_indices, args.b_values, b0, b1, args.a_indices, args.a_values, a_begin, a_begin + a_len, most);
+                    float most = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), l));
+                    bool alike;
+                    most = beyond(args.a_indices + a_begin, args.a_values + a_begin, a_len, args.b_indices + b0, args.b_values + b0, lb, most, alike);
+                    if (!alike) most = beyond(args.b_indices + b0, args.b_values + b0, lb, args.a_indices + a_begin, args.a_values + a_begin, a_len, most, alike);
 #pragma unroll
                     for (int u = 0; u < G; ++u) d[u] = u == g && lane == l ? most : d[u];
                 }

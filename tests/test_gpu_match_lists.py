@@ -858,3 +858,41 @@ def test_row_pointers_on_the_gpu_alone(spd, lists, entry, metric):
         assert np.array_equal(got, same)
     assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
     h.close()
+
+
+@pytest.mark.parametrize("m,n", [(60, 70), (60, 900), (4_200, 66)])              # all rows shared, several tiles, a wavefront to the row
+@pytest.mark.parametrize("size,kind", [(32, "one support"), (33, "one support"), (70, "one support"), (70, "a column less"), (150, "a column less"),
+                                       (70, "ones and twos"), (140, "stored zeros"), (70, "other places")])
+def test_chebyshev_of_rows_that_are_nearly_alike(spd, m, n, size, kind):
+    """Rows of A whose 32 largest entries B's rows all store: what decides is among the others, in columns that only one of the two rows
+    stores, at the same place in both rows, next to it or elsewhere.  The staged scan's bits."""
+    rng = np.random.default_rng(size + n)
+    cols = 400
+    support = np.sort(rng.choice(np.arange(100, cols), size=size, replace=False))
+
+    def matrix(rows):
+        d = np.zeros((rows, cols), np.float32)
+        d[:, support] = 1.0
+        if kind == "a column less":
+            d[np.arange(rows), rng.choice(support, size=rows)] = 0.0
+        elif kind == "ones and twos":
+            d[:, support[: size // 2]] = 2.0
+            d[np.arange(rows), rng.choice(support[size // 2:], size=rows)] = rng.integers(0, 3, size=rows)
+        elif kind == "other places":
+            for r in range(rows):                          # (entries in front of the shared ones: these lie at other places in the two rows)
+                d[r, rng.choice(100, size=r % 5, replace=False)] = 0.5
+        return d
+
+    dense = [matrix(m), matrix(n)]
+    A, B = (synth.from_dense(d.astype(np.float64)) for d in dense)
+    if kind == "stored zeros":
+        for M in (A, B):
+            M["values"][rng.choice(len(M["values"]), size=len(M["values"]) // 100, replace=False)] = 0.0
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h, staged = _lists(spd, profile=1), _lists(spd, match_lists=0)
+    got = _np(h.pairwise(dA, dB, "chebyshev"))
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    assert np.array_equal(got, _np(staged.pairwise(dA, dB, "chebyshev")))
+    assert_distances_close(got[:40], oracle.pairwise(synth.slice_rows(A, 0, 40), B, "chebyshev"), "chebyshev")
+    h.close()
+    staged.close()
