@@ -712,7 +712,8 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
 // (30 to 12,000 rows against 300 to 300,000, of equal, log-normal and power-law lengths of 1.5 to 3,000 entries, A's as long as
 // B's and not, uniform and Zipf columns, 2,000 to 2^20 of them, every product, k-NN with k = 1 to 64 and pairwise, with an index
 // and without); nine of ten estimates are within 0.4 to 1.35 of the times, because row pointers do not show how A's columns
-// meet B's.  Columns are seldom uniform where they are many: over all columns the lists are taken to be met up to 40 times as
+// meet B's.  (Fitted with lists of eight bytes an entry and long rows dealt to slices; since then the lists take up to a third less,
+// so that calls near the line may go by the scan where lists would be a little faster.)  Columns are seldom uniform where they are many: over all columns the lists are taken to be met up to 40 times as
 // often as if they were, as far as the density leaves room for that (words, Zipf columns, rows of 230 over 102,660: some 40 times).
 // Of 1,993 random calls of the working range (words, counts, ratings, sets, n-grams, skewed lengths) one in a hundred loses a tenth or more
 // against the better of the rules before this one.
@@ -769,8 +770,8 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     if (!match_launches_fit(s, op, A->n_rows, A->nnz, B->n_rows, false)) return false;
     if (h->match_lists == 2) return true;
     if (!match_suits(h, B, op, s)) return false;
-    // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.34; 1,024 x 300,000 of 230, cosine
-    // 11.4 / 5.6; 4,096 x 65,536 of 1,820, L1 87 / 30, Jensen-Shannon 349 / 37; 593 x 12,826 of 1,850, KL, k-NN, 5.5 / 1.7; 1,000 x
+    // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.28; 1,024 x 300,000 of 230, cosine
+    // 11.4 / 5.4; 4,096 x 65,536 of 1,820, L1 87 / 25, Jensen-Shannon 349 / 37; with lists as they were when the constants were fitted, 593 x 12,826 of 1,850, KL, k-NN, 5.5 / 1.7; 1,000 x
     // 10,000 of 1,360 and 20, L1 0.14 / 0.70; set metrics: 2,435 x 6,447 ratings, Dice 0.62 / 0.28, 1,187 x 6,303 rows of 214,
     // Russell-Rao 0.34 / 0.39, 3,081 x 30,310 of 400 in Zipf columns, Jaccard 2.5 / 7.0.
     return lists_cost(h, A, B, A->n_cols, op, s, knn, with_index, true) <= staged_cost(A, B, op, swapped, knn, with_index);
@@ -792,7 +793,7 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     MatchShape all;
     if (match_possible(h, B, op, all) && match_bounds_fit(all, B->nnz)) return false;
     // Both sides measured, staged / lists over A's columns in ms, k-NN: 4,096 x 500,000 sets over 2^20 columns, Jaccard 30.6 /
-    // 11.1, 3,331 x 9,539 of them 0.93 / 0.67, 46 x 56,760, Russell-Rao 0.73 / 0.30; 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.3 /
+    // 7.3; with lists as they were when the constants were fitted, 3,331 x 9,539 of them 0.93 / 0.67, 46 x 56,760, Russell-Rao 0.73 / 0.30; 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.3 /
     // 2.0, 335 x 16,402 of them, L1 0.10 / 0.12; 99 x 386,927 of them with an index, which holds nothing of these lists, cosine 0.19 /
     // 0.26, 516 x 285,865 sets with one, Dice 4.3 / 2.3.  (The estimate of these lists is the higher, as columns that A does not
     // store cost them nothing.)

@@ -794,8 +794,8 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 constexpr int R = norms_read(MT);
                 float *__restrict__ out = args.out + (size_t)row * (size_t)args.n + (size_t)j0;
                 // A round's norms are loaded before the round ahead stores its distances: what is loaded after a store is at hand only when the
-                // store has reached memory (10,000 x 10,000 rows of 38 with that wait in every round, L1 327 us a call, cosine 356; 316
-                // and 327 now).  The first of the whole rounds stands before the loop, so that every turn of the loop has the same loads
+                // store has reached memory (10,000 x 10,000 rows of 38, L1, 327 us a call with that wait in every round, 316
+                // without).  The first of the whole rounds stands before the loop, so that every turn of the loop has the same loads
                 // and stores in flight.
                 const int whole = tile_n / (F * kWave) * (F * kWave);
                 RowNorms nb[F], ahead[F];
@@ -1020,7 +1020,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // With integer sums a workgroup takes a (tile, row) of its group after another, the longest rows of a tile first: the slice that has
     // the longest row of all would be the last by far, and the workgroups of an XCD would drift apart in their tiles.  (1,531 x 28,301
     // ratings, Canberra, 488 -> 404 us; 4,096 x 500,000 sets, Jaccard, k-NN 8.46 -> 7.65 ms.)  Not with k-NN over few tiles: a row's first
-    // tiles would be gone through at once, without a bound (10,000 x 10,000 rows of 38, cosine 510 -> 579 us).
+    // tiles would be gone through at once, without a bound (10,000 x 10,000 rows of 38, cosine by sums in fixed point 510 -> 579 us).
     const bool taken = S::kAnyOrder && (!KNN || args.by_xcd != 0);
     __shared__ int s_item[2];
     int item = 0, turn = 0;

@@ -654,8 +654,9 @@ def test_an_index_without_memory_for_the_lists_keeps_the_packed_copy(scarce):
 @pytest.mark.parametrize("n,long_every", [(640, 16), (130, 1)])           # lists, and columns that more than half of the rows store
 def test_sums_in_fixed_point(spd, metric, n, long_every):
     """Rows whose values lie 2^80 apart, of one entry and of more than 4,096 that two rows share, entries 2^26 apart in a row, rows that
-    equal one another: a term is rounded to 2^-52 of the rows' largest (match_fixed in spd_match.h), so a sum of `terms` of them is
-    off by terms * 2^-52 * largest * largest at most, and a distance by that and two roundings to single precision."""
+    equal one another.  L1 and Canberra: a term is rounded to 2^-52 of the row's largest (match_fixed in spd_match.h), so a sum of
+    `terms` of them is off by terms * 2^-52 * largest at most.  The distances of a dot product, whose sums are in fp64: by terms * 2^-53 of
+    what the sum has come to.  A distance is off by that and two roundings to single precision."""
     rng = np.random.default_rng(n)
     cols, m = 6_000, 20
     signed = metric in ("cosine", "l2_expanded", "correlation", "l1", "canberra")
