@@ -270,8 +270,10 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     // Workgroups go round the eight XCDs in turn: an XCD takes an eighth of the (tile, part)s that follow one another, so that the
     // lines which two blocks of a row share come from its L2 (300,000 rows of 230 entries: misses 40 -> 21 million; what is left is the
     // latency of the phases between the barriers, one workgroup to a compute unit: with two of half the LDS and twice the blocks
-    // 1,042 -> 1,367 us).
-    const uint32_t of_xcd = (gridDim.x + 7u) >> 3, at_wg = (blockIdx.x & 7u) * of_xcd + (blockIdx.x >> 3);
+    // 1,042 -> 1,367 us).  Not where they are hardly more than the 256 compute units: in the order of the grid the few that take a second
+    // turn are of the last tile, which is short (KL, 260 workgroups for 10,000 rows, 41 -> 32 us; L1, 360 of them, 46 in either order, and
+    // the walk after it 2 us longer).
+    const uint32_t of_xcd = (gridDim.x + 7u) >> 3, at_wg = gridDim.x > 288u ? (blockIdx.x & 7u) * of_xcd + (blockIdx.x >> 3) : blockIdx.x;
     const int tile = (int)(at_wg / wgs), part = (int)(at_wg % wgs);
     if (tile >= shape.n_tiles) return;
     const int64_t j0 = (int64_t)tile * T;
