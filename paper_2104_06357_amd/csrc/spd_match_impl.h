@@ -978,7 +978,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 merge();                                          // (what is queued joins the run's list, if it has one)
                 // into the row's list of this group, under a lock (two wavefronts of the workgroup may be at one row, in
                 // different tiles, or of several workgroups, where the lock lies in memory); the holder waits for nothing
-                const bool in_memory = S::kAnyOrder && lock != nullptr;
+                const bool in_memory = lock != nullptr;
                 int *const row_lock = &s_lock[row & (kMatchLocks - 1)];
                 int first_lane = lane;
                 asm volatile("" : "+v"(first_lane));              // (see the claim below)
@@ -1017,11 +1017,13 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     // ---- the longest rows: an even share of the row to each wavefront ---------------------------------
     // (a wavefront alone would hold its workgroup up long after the others are done)
     int owner = 0;
-    // With integer sums a workgroup takes a (tile, row) of its group after another, the longest rows of a tile first: the slice that has
+    // A workgroup takes a (tile, row) of its group after another, the longest rows of a tile first: the slice that has
     // the longest row of all would be the last by far, and the workgroups of an XCD would drift apart in their tiles.  (1,531 x 28,301
-    // ratings, Canberra, 488 -> 404 us; 4,096 x 500,000 sets, Jaccard, k-NN 8.46 -> 7.65 ms.)  Not with k-NN over few tiles: a row's first
+    // ratings, Canberra, 488 -> 404 us; 4,096 x 500,000 sets, Jaccard, k-NN 8.46 -> 7.65 ms.  Sums in fp64, which are formed in the same order
+    // whichever workgroup takes the row: the same ratings, cosine, 460 -> 384, KL 708 -> 510, k-NN 752 -> 584; 979 x 88,197 rows of 230,
+    // cosine, 1,926 -> 1,647; 10,000 x 10,000 rows of 38 313 -> 317.)  Not with k-NN over few tiles: a row's first
     // tiles would be gone through at once, without a bound (10,000 x 10,000 rows of 38, cosine by sums in fixed point 510 -> 579 us).
-    const bool taken = S::kAnyOrder && (!KNN || args.by_xcd != 0);
+    const bool taken = !KNN || args.by_xcd != 0;
     __shared__ int s_item[2];
     int item = 0, turn = 0;
     if (taken && args.m_shared > 0) {

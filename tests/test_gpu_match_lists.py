@@ -897,3 +897,33 @@ def test_chebyshev_of_rows_that_are_nearly_alike(spd, m, n, size, kind):
     assert_distances_close(got[:40], oracle.pairwise(synth.slice_rows(A, 0, 40), B, "chebyshev"), "chebyshev")
     h.close()
     staged.close()
+
+
+@pytest.mark.parametrize("metric", ["cosine", "correlation", "canberra", "kl_divergence", "jensen_shannon", "minkowski"])
+@pytest.mark.parametrize("n,mean_b", [(1_500, 30), (22_000, 30)])                # few tiles, and tiles that are dealt to the XCDs
+def test_long_rows_go_to_the_workgroups_as_they_come(spd, metric, n, mean_b):
+    """Most of A's rows are shared by the wavefronts of a workgroup, and which workgroup takes one depends on the schedule: the same bits
+    every time, and the oracle's distances."""
+    rng = np.random.default_rng(n)
+    cols, m = 3_001, 90
+
+    def matrix(rows, mean):
+        lengths = np.minimum(cols, np.maximum(1, (mean * rng.exponential(size=rows)).astype(int)))
+        c = [np.sort(rng.choice(cols, size=k, replace=False)) for k in lengths]
+        return {"n_rows": rows, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64),
+                "indices": np.concatenate(c).astype(np.int32), "values": rng.integers(1, 1 << 20, size=int(lengths.sum())).astype(np.float32) / (1 << 20)}
+
+    A, B = matrix(m, 900), matrix(n, mean_b)
+    h = _lists(spd)
+    p = _p_of(metric)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], p)
+    first = _np(h.pairwise(dA, dB, metric, p)).copy()
+    assert_distances_close(first, want, metric)
+    idx, dist = (_np(x).copy() for x in h.knn(dA, dB, metric, 20, p))
+    assert_knn_matches(idx, dist, want, 20, metric, metric)
+    for _ in range(4):
+        assert np.array_equal(first, _np(h.pairwise(dA, dB, metric, p)))
+        i2, d2 = h.knn(dA, dB, metric, 20, p)
+        assert np.array_equal(idx, _np(i2)) and np.array_equal(dist, _np(d2))
+    h.close()
