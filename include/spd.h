@@ -42,6 +42,9 @@
  *    Jensen-Shannon expect non-negative values (anything else is undefined, and reported by
  *    spd_csr_validate()); for KL and Jensen-Shannon the quotient of two entries of one column
  *    must lie within the fp32 range.
+ *    Canberra divides through a reciprocal in single precision: a column counts 0, infinity or no number where
+ *    |x| + |y| lies outside [2^-126, 2^126] (by the column lists it counts its quotient there too where A's row
+ *    holds an entry below 2^-100 or from 2^102 on).
  */
 #ifndef SPD_H
 #define SPD_H

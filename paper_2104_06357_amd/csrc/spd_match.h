@@ -151,7 +151,8 @@ SPD_HD int match_scale(float largest, double sum) {
 }
 // Canberra: whether a row of A, whose entries' magnitudes lie from `least` (but 0) to `largest`, can meet a row of finite values where |a| + |b|
 // or its reciprocal is not finite in single precision, or |a - b| is not: no sum is below 2^-100 or, half an ulp of the largest number being 2^103,
-// rounded to infinity else.  Such a row is walked column by column.
+// rounded to infinity else.  Such a row is walked column by column.  (Another row may meet an entry above 2^126 all the same: the reciprocal is
+// 0 there and the quotient with it, as by the staged scan.)
 SPD_HD bool match_wild(float least, float largest) { return !(least >= 0x1p-100f && largest < 0x1p102f); }
 // Canberra's for a row of A of `len` entries: 2 len 2^(51 - e) below 2^62.
 SPD_HD int match_canberra_scale(int len) { return len < (1 << 10) ? 2 : 2 + (32 - 10) - __builtin_clz((unsigned)len); }
