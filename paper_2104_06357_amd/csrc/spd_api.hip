@@ -599,9 +599,9 @@ MatchScratch layout_match_call(const MatchShape &s, const MatchGrid &g, int op, 
                                bool with_b, int64_t columns) {
     MatchScratch L{};
     Carver cv;
-    // (two bytes to a stored entry are spare in scratch, so that scratch of a given size, the static array among it, sends mostly the same
-    // calls to the staged scan as when an entry took eight)
-    if (with_b) L.b = layout_match(s, op, n, nnz_b, (size_t)nnz_b * 2, cv);
+    // (eight bytes to a stored entry in scratch, what its gaps leave of them spare, so that scratch of a given size, the static array among it, sends
+    // the same calls to the staged scan as when an entry took eight)
+    if (with_b) L.b = layout_match(s, op, n, nnz_b, (size_t)std::max<int64_t>(0, 2 * nnz_b - 6 * (s.room_of(nnz_b) - nnz_b)), cv);
     if (columns > 0) {
         const size_t words = ((size_t)columns + 31) / 32, masks = ((size_t)nnz_b + 63) / 64;
         L.c.words = cv.take(words * 8);
@@ -644,6 +644,8 @@ std::string match_check(const PlanOptions &opt, const MatchShape &s, const Match
     if (s.dense_per_block < 1 || s.dense_per_block > (int32_t)kBuildDense || s.dense_from < 1 ||
         s.dense_from > T + 1 || s.tile_extra != blocks * s.dense_per_block * s.dense_room()) return "dense columns";
     if (s.list_entries(nnz_b) >= (int64_t)1 << 29) return "list positions";
+    if (s.aligned && 1.3125 * std::min((double)nnz_b, (double)T * (double)n_cols) + (double)s.tile_extra >= (double)s.position_bits())
+        return "list positions and gaps";
     const int64_t build = (int64_t)s.stage * 6 + ((int64_t)4 << s.block_shift) + 12 * T;
     if ((int64_t)s.build_lds_bytes != build || s.stage % 8 != 0 || build + 1024 > opt.lds_budget) return "build over the LDS";
     if (g.slices < 1 || g.groups < 1 || g.run < 1 || g.run > tiles || g.groups > tiles || (g.by_xcd && g.groups < tiles && g.groups % 8 != 0)) return "grid";
@@ -697,11 +699,19 @@ bool match_suits(const spd_handle *h, const spd_csr *B, int op, const MatchShape
 // them than the header states (a small B over many columns has more bounds than entries).
 bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape &s, MatchLayout &L) {
     if (!match_possible(h, B, op, s) || !match_serves_knn(op)) return false;
-    Carver cv;
-    L = layout_match(s, op, B->n_rows, B->nnz, 0, cv);
+    const int64_t most = 20 * B->nnz + 16 * B->n_rows + (1 << 20);
+    auto lay_out = [&] {
+        Carver cv;
+        L = layout_match(s, op, B->n_rows, B->nnz, 0, cv);
+    };
+    lay_out();
+    if ((int64_t)L.end > most && s.aligned) {      // (what fits without gaps is kept without them)
+        s.aligned = 0;
+        lay_out();
+    }
     if (h->match_lists == 2) return true;
     if (op == OP_CNT) return false;                // (counts come out the same by the scan, which is as fast where a call has no B to prepare)
-    return match_suits(h, B, op, s) && (int64_t)L.end <= 20 * B->nnz + 16 * B->n_rows + (1 << 20);
+    return match_suits(h, B, op, s) && (int64_t)L.end <= most;
 }
 // What a call costs by lists and by the staged scan, in picoseconds of the whole chip.  A wavefront pays for every entry of
 // its row of A in every tile (its list's bounds; a step, where the list is not empty), for every entry of a list it walks and for
@@ -1155,8 +1165,11 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     }
     bool lists = way.way != 0 && !direct;
     if (lists) {
-        if (way.way == 1 && index && (index->match_op != op || std::memcmp(&index->match.shape, &way.s, sizeof way.s) != 0))
-            lists = false;              // (created under other options)
+        if (way.way == 1 && index) {
+            MatchShape kept = index->match.shape;
+            kept.aligned = way.s.aligned;               // (an index may hold its lists without gaps)
+            if (index->match_op != op || std::memcmp(&kept, &way.s, sizeof way.s) != 0) lists = false;              // (created under other options)
+        }
         // (a caller's scratch that does not hold the lists still serves the staged scan)
         if (h->ws_external && way.L.end > h->ws_bytes) lists = false;
         // (and so does a device that has no memory left for them; so much is not asked for again)

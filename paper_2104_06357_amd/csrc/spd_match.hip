@@ -248,6 +248,15 @@ __device__ __forceinline__ void tile_least(const double *__restrict__ norms, con
     }
 }
 
+// Lists that follow one another: entries before the first that begins at a line (kMatchLine), and from there on (-1: none does).
+struct Stretch { uint32_t before; int32_t after; };
+__device__ __forceinline__ uint32_t to_line(uint32_t at) { return (at + kMatchLine - 1u) & ~(kMatchLine - 1u); }
+__device__ __forceinline__ uint32_t end_of(uint32_t at, const Stretch &x) { return x.after < 0 ? at + x.before : to_line(at + x.before) + (uint32_t)x.after; }
+__device__ __forceinline__ Stretch then(const Stretch &x, const Stretch &y) {
+    if (x.after < 0) return Stretch{x.before + y.before, y.after};
+    return Stretch{x.before, (int32_t)end_of((uint32_t)x.after, y)};
+}
+
 template <int G>
 __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                         const float *__restrict__ values, int64_t n_rows, int64_t nnz,
@@ -255,7 +264,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
                                                                         int transform, bool with_values, const RowsVerdict seen) {
     if (rows_malformed(seen)) return;
     extern __shared__ __align__(16) unsigned char s_raw[];
-    __shared__ uint32_t s_wave[kBuildThreads / kWave];
+    __shared__ uint32_t s_wave[kBuildThreads / kWave], s_second[kBuildThreads / kWave];
     __shared__ uint32_t s_dense[kBuildDense], s_long[kBuildLong], s_longs;
     __shared__ double s_least[kBuildThreads / kWave][2];
     const MatchShape &shape = b.shape;
@@ -279,7 +288,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     const int64_t j0 = (int64_t)tile * T;
     const int rows = (int)min((int64_t)T, n_rows - j0);
     const int64_t row_first = clamp_i64(indptr[j0], 0, nnz);             // of the rows' entries
-    const int64_t first = row_first + tile * shape.tile_extra;            // of the tile's lists
+    const int64_t first = shape.room_of(row_first) + tile * shape.tile_extra;            // of the tile's lists
     const int32_t *const tile_indices = indices + row_first;
     const int64_t list_end = shape.list_entries(nnz) - kMatchSpare;
     float *s_value = reinterpret_cast<float *>(s_raw);                              // stage entries, a multiple of 8
@@ -293,7 +302,7 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     const uint32_t block_first = (uint32_t)part * blocks_per_wg;
     const uint32_t block_last = min(block_first + blocks_per_wg, blocks);
     if (block_first >= block_last) return;
-    uint32_t base = 0u;                               // entries of the columns before the block
+    uint32_t before = 0u;                             // entries of the columns before the block
     {
         const uint32_t c_first = block_first * block_cols;
         const float share = (float)c_first / (float)cols;
@@ -305,22 +314,22 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             // mostly within the lines that are read next anyway (eight probes of a bisection were 3 of the 5 GB
             // that 300,000 rows of 230 entries over 13 blocks read)
             uint32_t lo = begin, hi = c_first == 0u ? begin : end;
-            auto before = [&](uint32_t e) { return (uint32_t)tile_indices[e] < c_first; };
+            auto earlier = [&](uint32_t e) { return (uint32_t)tile_indices[e] < c_first; };
             if (lo < hi) {
                 uint32_t at = lo + min((uint32_t)((float)(hi - lo) * share), hi - lo - 1u), step = 8u;
-                if (before(at)) {
+                if (earlier(at)) {
                     lo = at + 1u;
-                    while (lo < hi && hi - lo > step && before(lo + step)) { lo += step + 1u; step *= 2u; }
+                    while (lo < hi && hi - lo > step && earlier(lo + step)) { lo += step + 1u; step *= 2u; }
                     hi = min(hi, lo + step);
                 } else {
                     hi = at;
-                    while (hi - lo > step && !before(hi - step)) { hi -= step; step *= 2u; }
+                    while (hi - lo > step && !earlier(hi - step)) { hi -= step; step *= 2u; }
                     lo = hi - lo > step ? hi - step : lo;
                 }
             }
             while (lo < hi) {
                 const uint32_t mid = (lo + hi) >> 1;
-                if (before(mid)) lo = mid + 1; else hi = mid;
+                if (earlier(mid)) lo = mid + 1; else hi = mid;
             }
             s_cur[r] = lo;
             s_end[r] = end;
@@ -331,9 +340,12 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         if (lane == 0) s_wave[wave] = mine;
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < nw; ++w) base += s_wave[w];
-        base += block_first * (uint32_t)shape.dense_per_block * (uint32_t)shape.dense_room();
+        for (int w = 0; w < nw; ++w) before += s_wave[w];
     }
+    // Where a block's piece begins in the tile's lists, `entries` before it.
+    auto piece_of = [&](uint32_t entries, uint32_t block) {
+        return (uint32_t)shape.room_of(entries) + block * (uint32_t)shape.dense_per_block * (uint32_t)shape.dense_room();
+    };
     for (uint32_t block = block_first; block < block_last; ++block) {
         const uint32_t c0 = block * block_cols, range = min(block_cols, cols - c0);
         for (uint32_t i = tid; i < block_cols; i += kBuildThreads) s_count[i] = 0u;
@@ -408,63 +420,89 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             }
             __syncthreads();
         }
-        // which columns are dense: the first of the block that reach the mark, in column order (so that the
-        // same columns are dense in every run)
-        auto scan4 = [&](uint32_t mine, uint32_t &carry) {          // exclusive over the workgroup, from `carry` on
-            uint32_t incl = mine;
+        // Which columns are dense: the first of the block that reach the mark, in column order (so that the same columns are dense in every
+        // run).  A thread has some columns that follow one another.
+        const uint32_t mine = ((block_cols + kBuildThreads - 1u) / kBuildThreads + 3u) & ~3u, mine_first = (uint32_t)tid * mine;
+        auto columns = [&](auto &&each) {
+            for (uint32_t i = mine_first; i < min(mine_first + mine, block_cols); i += 4u) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(s_count + i);
+                each(i, v.x);
+                each(i + 1u, v.y);
+                each(i + 2u, v.z);
+                each(i + 3u, v.w);
+            }
+        };
+        const uint32_t whole = (uint32_t)T, mark = (uint32_t)shape.dense_from, most_dense = (uint32_t)shape.dense_per_block;
+        uint32_t rank = 0u, n_dense = 0u, entries = 0u;             // columns that reach the mark before the thread's, all of them; the block's entries
+        {
+            uint32_t marked = 0u, sum = 0u;
+            columns([&](uint32_t, uint32_t v) { marked += v >= mark ? 1u : 0u; sum += v; });
+            rank = marked;
 #pragma unroll
             for (int d = 1; d < kWave; d <<= 1) {
-                const uint32_t up = (uint32_t)__shfl_up((int)incl, d);
-                if (lane >= d) incl += up;
+                const uint32_t r = (uint32_t)__shfl_up((int)rank, d);
+                sum += (uint32_t)__shfl_xor((int)sum, d);
+                if (lane >= d) rank += r;
             }
-            if (lane == 63) s_wave[wave] = incl;
+            if (lane == 63) { s_wave[wave] = rank; s_second[wave] = sum; }
             __syncthreads();
-            uint32_t at = carry + incl - mine;
+            rank -= marked;
 #pragma unroll
-            for (int w = 0; w < nw; ++w) { at += w < wave ? s_wave[w] : 0u; carry += s_wave[w]; }
+            for (int w = 0; w < nw; ++w) { rank += w < wave ? s_wave[w] : 0u; n_dense += s_wave[w]; entries += s_second[w]; }
+            n_dense = min(n_dense, most_dense);
             __syncthreads();
-            return at;
-        };
-        const uint32_t whole = (uint32_t)T, mark = (uint32_t)shape.dense_from;
-        uint32_t n_dense = 0u, total = 0u;
-        for (uint32_t i0 = 0; i0 < block_cols; i0 += 4 * kBuildThreads) {
-            const uint32_t i = i0 + 4u * (uint32_t)tid;
-            uint32_t v[4] = {0u, 0u, 0u, 0u};
-            if (i < block_cols)
-#pragma unroll
-                for (int x = 0; x < 4; ++x) v[x] = s_count[i + x];
-            uint32_t mine = 0u;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) mine += v[x] >= mark ? 1u : 0u;
-            uint32_t rank = scan4(mine, n_dense), size[4], is_dense = 0u, sum = 0u;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const bool d = v[x] >= mark && rank < (uint32_t)shape.dense_per_block;
-                if (v[x] >= mark) ++rank;
-                is_dense |= d ? 1u << x : 0u;
-                size[x] = d ? whole : v[x];
-                sum += size[x];
-            }
-            // counts -> starts: from the tile's first entry in memory, from the block's in LDS
-            uint32_t at = scan4(sum, total), r = rank - mine;
-            if (i < block_cols) {
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const uint32_t flag = (is_dense >> x) & 1u ? kMatchDense : 0u;
-                    if (flag) s_dense[r] = at;
-                    if (v[x] >= mark) ++r;
-                    s_count[i + x] = at | flag;
-                    if (i + x < range) ptr[c0 + block + i + x] = (base + at) | flag;
-                    at += size[x];
-                }
-            }
         }
-        if (tid == 0) ptr[c0 + block + range] = base + total;
-        n_dense = min(n_dense, (uint32_t)shape.dense_per_block);
+        // Counts -> starts, which count from a line's beginning in memory and in LDS, `phase` before the block's piece.  Long lists and dense columns
+        // begin at a line; what they leave free before them is nobody's.  (A block whose gaps are more than its room has none.)
+        const uint32_t base = piece_of(before, block), phase = (uint32_t)(first + base) & (kMatchLine - 1u);
+        const uint32_t limit = phase + piece_of(before + entries, block + 1u) - base;
+        uint32_t line = shape.aligned ? kMatchLine : 0xFFFFFFFFu, at = phase, total = phase;
+        auto piece = [&](uint32_t v, bool dense) {
+            return line <= whole && (dense || v >= line) ? Stretch{0u, (int32_t)(dense ? whole : v)} : Stretch{dense ? whole : v, -1};
+        };
+        for (;;) {
+            Stretch incl{0u, -1};
+            uint32_t r = rank;
+            columns([&](uint32_t, uint32_t v) {
+                incl = then(incl, piece(v, v >= mark && r < most_dense));
+                r += v >= mark ? 1u : 0u;
+            });
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const Stretch up{(uint32_t)__shfl_up((int)incl.before, d), __shfl_up(incl.after, d)};
+                if (lane >= d) incl = then(up, incl);
+            }
+            const Stretch lower{(uint32_t)__shfl_up((int)incl.before, 1), __shfl_up(incl.after, 1)};
+            if (lane == 63) { s_wave[wave] = incl.before; s_second[wave] = (uint32_t)incl.after; }
+            __syncthreads();
+            at = total = phase;
+#pragma unroll
+            for (int w = 0; w < nw; ++w) {
+                total = end_of(total, Stretch{s_wave[w], (int32_t)s_second[w]});
+                at = w + 1 == wave ? total : at;
+            }
+            if (lane > 0) at = end_of(at, lower);
+            __syncthreads();
+            if (total <= limit || line > whole) break;
+            line = 0xFFFFFFFFu;
+        }
+        {
+            uint32_t r = rank;
+            columns([&](uint32_t i, uint32_t v) {
+                const bool dense = v >= mark && r < most_dense;
+                const uint32_t flag = dense ? kMatchDense : 0u, end = end_of(at, piece(v, dense)), from = end - (dense ? whole : v);
+                if (dense) s_dense[r] = from;
+                r += v >= mark ? 1u : 0u;
+                s_count[i] = from | flag;
+                if (i < range) ptr[c0 + block + i] = (base + from - phase) | (from - at) << kMatchGapShift | flag;
+                at = end;
+            });
+        }
+        if (tid == 0) ptr[c0 + block + range] = base + total - phase;
         __syncthreads();
-        float *__restrict__ values_at = b.values + first + base;   // the block's piece
-        uint16_t *__restrict__ rows_at = b.rows + first + base;
-        const int64_t room = list_end - (first + base);            // (never reached while the row pointers hold)
+        float *__restrict__ values_at = b.values + first + base - phase;   // the block's piece
+        uint16_t *__restrict__ rows_at = b.rows + first + base - phase;
+        const int64_t room = list_end - (first + base - phase);    // (never reached while the row pointers hold)
         for (uint32_t d = 0; d < n_dense; ++d)
             for (uint32_t i = s_dense[d] + (uint32_t)tid; i < s_dense[d] + whole; i += kBuildThreads) {
                 if (i < shape.stage) s_value[i] = 0.0f;
@@ -550,21 +588,13 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         }
         __syncthreads();
         const uint32_t staged = min(total, shape.stage);
-        for (uint32_t i = tid; i < staged; i += kBuildThreads)
+        for (uint32_t i = phase + tid; i < staged; i += kBuildThreads)
             if (i < room) {
                 rows_at[i] = s_row[i];
                 if (with_values || n_dense > 0u) values_at[i] = s_value[i];
             }
-        if (tid == 0) s_wave[0] = 0u;
-        __syncthreads();
-        {
-            // the next block's piece begins behind this one's entries and its room for dense columns
-            uint32_t mine = 0u;
-            for (int r = tid; r < rows; r += kBuildThreads) { mine += s_next[r] - s_cur[r]; s_cur[r] = s_next[r]; }
-            if (mine) atomicAdd(&s_wave[0], mine);
-        }
-        __syncthreads();
-        base += s_wave[0] + (uint32_t)shape.dense_per_block * (uint32_t)shape.dense_room();        // (a dense column has `mark` entries at least)
+        for (int r = tid; r < rows; r += kBuildThreads) s_cur[r] = s_next[r];
+        before += entries;
         __syncthreads();
     }
 }
@@ -662,6 +692,10 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
         s.dense_from = std::max(1, s.tile_rows / 2);
         s.tile_extra = (int64_t)s.blocks * s.dense_per_block * s.dense_room();
     }
+    // Lists at lines of memory, where a tile's positions and a gap fit a word and all positions their limit.
+    s.aligned = 1;
+    const double tile_most = 1.3125 * std::min((double)nnz, (double)s.tile_rows * (double)n_cols) + (double)s.tile_extra;
+    if (tile_most >= (double)(s.position_bits() - 64u) || s.list_entries(nnz) >= (int64_t)1 << 29) s.aligned = 0;
     return s;
 }
 

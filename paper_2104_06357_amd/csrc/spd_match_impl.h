@@ -579,16 +579,18 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
     };
     // (`to`: the strip)
     auto walk_lists = [&](int tile, const Lists &y, const Scale &scale, uint32_t to, Few &few) {
-        const int64_t tile_first = clamp_i64(args.b_indptr[(int64_t)tile * T], 0, args.b_nnz) + tile * args.b.shape.tile_extra;
+        const int64_t tile_first = args.b.shape.room_of(clamp_i64(args.b_indptr[(int64_t)tile * T], 0, args.b_nnz)) + tile * args.b.shape.tile_extra;
         const unsigned char *__restrict__ values = reinterpret_cast<const unsigned char *>(args.b.values + tile_first);
         const unsigned char *__restrict__ rows = reinterpret_cast<const unsigned char *>(args.b.rows + tile_first);
         const uint32_t list_n = (uint32_t)(args.b.shape.list_entries(args.b_nnz) - kMatchSpare - tile_first);     // (no access leaves the lists)
         const float a = transform_value(args.transform, y.a);
-        uint32_t first = min(y.first & ~kMatchDense, list_n);
+        const uint32_t position = args.b.shape.position_bits(), gap = args.b.shape.gap_bits();
+        const uint32_t first = min(y.first & position, list_n);
+        const uint32_t end = (y.last & position) - ((y.last >> kMatchGapShift) & gap);
         const bool dense = (y.first & kMatchDense) != 0u && match_walks<OP>(a) && first + (uint32_t)T <= list_n;
         const uint64_t dense_mask = __ballot(dense);
         if (OP == OP_CANB && scale.wild) {
-            const uint32_t last = match_walks<OP>(a) && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
+            const uint32_t last = match_walks<OP>(a) && (y.first & kMatchDense) == 0u ? max(first, min(end, list_n)) : first;
             walk_wild(values, rows, first, last, dense, a, scale, to);
             if (KNN) few.total += 4 * U + 1;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -600,7 +602,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 walk_dense(values, first * 4u, a, dense_mask, scale, to);
             }
         }
-        const uint32_t last = match_walks<OP>(a) && (y.first & kMatchDense) == 0u ? max(first, min(y.last & ~kMatchDense, list_n)) : first;
+        const uint32_t last = match_walks<OP>(a) && (y.first & kMatchDense) == 0u ? max(first, min(end, list_n)) : first;
         walk_chunks(values, rows, first, last, a, y.met, scale, to, few);
         // (a lane reads later what other lanes of its wavefront wrote: LDS serves a wavefront in order, the
         // fence keeps the compiler to that order)

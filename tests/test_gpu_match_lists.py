@@ -927,3 +927,27 @@ def test_long_rows_go_to_the_workgroups_as_they_come(spd, metric, n, mean_b):
         i2, d2 = h.knn(dA, dB, metric, 20, p)
         assert np.array_equal(idx, _np(i2)) and np.array_equal(dist, _np(d2))
     h.close()
+
+
+# Columns that so many rows store (in turn): around the 16 entries from which on a list begins at a line, with short lists between them; all of them
+# lists whose gaps would take more than their block's room, so that it has none; and such that nearly all of its room is gaps.
+@pytest.mark.parametrize("metric", ["l1", "cosine", "jaccard", "chebyshev"])
+@pytest.mark.parametrize("stored", [(15, 16, 17, 1, 31, 32, 33, 3, 0, 48), (17,), (49, 2, 50, 1, 1, 47)])
+def test_lists_that_begin_at_lines(spd, metric, stored):
+    rng = np.random.default_rng(len(stored))
+    n, cols = 700, 260
+    d = np.zeros((n, cols))
+    for c in range(cols):
+        d[rng.choice(n, size=stored[c % len(stored)], replace=False), c] = rng.integers(1, 9, size=stored[c % len(stored)]) / 8.0
+    B = synth.from_dense(d)
+    A = _matrix(rng, 40, cols, (3, 64, 65, 1, 130, 0, 17, 260))
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    print("lists at lines", metric, stored, flush=True)
+    h = _lists(spd, profile=1)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric])
+    assert_distances_close(_np(h.pairwise(dA, dB, metric)), want, metric)
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    if metric != "chebyshev":
+        idx, dist = h.knn(dA, dB, metric, 9)
+        assert_knn_matches(_np(idx), _np(dist), want, 9, metric, metric)
+    h.close()
