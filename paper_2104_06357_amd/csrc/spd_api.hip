@@ -638,15 +638,15 @@ std::string match_check(const PlanOptions &opt, const MatchShape &s, const Match
     if (T < kWave || T % kWave != 0 || tiles * T < n || (tiles - 1) * T >= n) return "tiles do not cover B";
     if (s.waves != match_waves((int)cell) || s.lds_bytes != (uint32_t)s.waves * match_strip_bytes((int)cell, (int)T) ||
         (int64_t)s.lds_bytes + match_static_lds((int)cell) > opt.lds_budget) return "strips over the LDS";
-    if (s.block_shift < 2 || s.block_shift > 30 || (blocks << s.block_shift) < n_cols || ((blocks - 1) << s.block_shift) >= n_cols)
+    if (s.block_shift < 2 || s.block_shift > 13 || s.stage < 64 || T > 2496 || (blocks << s.block_shift) < n_cols || ((blocks - 1) << s.block_shift) >= n_cols)
         return "column blocks";
     if (s.ptr_stride < n_cols + blocks) return "list bounds";
-    if (s.dense_per_block < 1 || s.dense_per_block > (int32_t)kBuildDense || s.dense_from < 1 ||
-        s.dense_from > T + 1 || s.tile_extra != blocks * s.dense_per_block * s.dense_room()) return "dense columns";
+    if (s.dense_per < 1 || s.dense_per > (int32_t)kBuildDensePer || s.dense_shift < s.block_shift || s.dense_shift > 13 || s.dense_from < 1 ||
+        s.dense_from > T + 1 || s.tile_extra != (int64_t)s.dense_before((int32_t)blocks) * s.dense_room()) return "dense columns";
     if (s.list_entries(nnz_b) >= (int64_t)1 << 29) return "list positions";
     if (s.aligned && 1.3125 * std::min((double)nnz_b, (double)T * (double)n_cols) + (double)s.tile_extra >= (double)s.position_bits())
         return "list positions and gaps";
-    const int64_t build = (int64_t)s.stage * 6 + ((int64_t)4 << s.block_shift) + 12 * T;
+    const int64_t build = (int64_t)s.stage * 6 + ((int64_t)4 << s.block_shift) + 4 * T;
     if ((int64_t)s.build_lds_bytes != build || s.stage % 8 != 0 || build + 1024 > opt.lds_budget) return "build over the LDS";
     if (g.slices < 1 || g.groups < 1 || g.run < 1 || g.run > tiles || g.groups > tiles || (g.by_xcd && g.groups < tiles && g.groups % 8 != 0)) return "grid";
     if (match_items(s, g, m) >= (int64_t)1 << 30) return "(tile, row)s of a workgroup";

@@ -29,14 +29,15 @@ struct MatchRow { int64_t start; int32_t len, row; };
 constexpr int64_t kMatchSpare = 1280;
 
 // How B's rows are cut: into tiles of rows, and the columns of a tile into blocks (a power of two of them),
-// each with room for its entries and for `dense_per_block` columns kept as one value per row of the tile.
+// each with room for its entries; `dense_per` of 2^dense_shift columns may be kept as one value per row of the tile.
 struct MatchShape {
     int32_t tile_rows, n_tiles, waves;      // n_tiles 0: the product or the sizes do not fit
-    int32_t block_shift, blocks, dense_per_block, dense_from;      // dense_from: entries that make a column dense
+    int32_t block_shift, blocks, dense_shift, dense_per, dense_from;      // dense_from: entries that make a column dense
     uint32_t stage;                         // entries of a block that pass through LDS together
+    int32_t aligned;                        // 1: lists of kMatchLine entries or more and dense columns begin at multiples of kMatchLine, see below
     int64_t ptr_stride, tile_extra;         // words of a tile's list bounds; entries beyond the tile's own
     uint32_t lds_bytes, build_lds_bytes;
-    int32_t aligned, unused;                // 1: lists of kMatchLine entries or more and dense columns begin at multiples of kMatchLine, see below
+    SPD_HD int32_t dense_before(int32_t block) const { return (int32_t)(((int64_t)block * dense_per + (1 << (dense_shift - block_shift)) - 1) >> (dense_shift - block_shift)); }
     SPD_HD int32_t dense_room() const { return tile_rows > dense_from ? tile_rows - dense_from : 0; }       // entries more than such a column has
     // The room that so many entries have in the lists: with gaps between aligned lists five sixteenths more.  (What follows one another
     // has at least its own room: the sum of two rooms is no more than the room of both.)
@@ -116,7 +117,7 @@ struct MatchColumns {
 };
 
 constexpr int64_t kMatchMostColumns = 1 << 28;    // that are renumbered (16 bytes per 64 of them)
-constexpr uint32_t kBuildDense = 32;            // dense columns of a block at most
+constexpr uint32_t kBuildDense = 64, kBuildDensePer = 32;          // dense columns of a block at most, and that have room of their own
 constexpr int kMatchRowLocks = 64;              // of a group, by row
 constexpr int kMatchStagingKind = 6;            // how spd_profile_read names this kernel's staging
 constexpr int64_t kMatchL2Bytes = 4 << 20;      // of one XCD

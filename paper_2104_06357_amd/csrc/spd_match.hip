@@ -210,18 +210,24 @@ hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const Ran
 
 // ------------------------------------------------------------------------------------
 // B: a tile's entries by column.  A workgroup takes a run of column blocks of one tile.  The rows ascend in
-// their columns, so a row's entries of a block are a stretch of it, found where the block before ended:
-// every entry is read once to count and once (from the caches) to place.  Counters and the block's piece
-// of the list lie in LDS and the piece is written out whole.  (Counters in memory that eight XCDs share
+// their columns, so a row's entries of a block are a stretch of it, whose end a lane to the row searches from where the block before ended.  The
+// stretches are lined up one behind the other, and the lanes take their entries as they stand in this line, every entry once: it is counted, the
+// count before it is its place in its column's list, and it waits in registers for the lists' starts.  Counters and the block's
+// piece of the lists lie in LDS and the piece is written out whole.  (Counters in memory that eight XCDs share
 // run at 2.6e10 atomics a second: 300,000 rows of 230 entries took 7.1 ms; one workgroup per tile with
-// scattered 8-byte stores 1.74 ms.)  The order inside a list is whatever the wavefronts make it: no sum
-// depends on it, because a row of B appears in a list at most once.
+// scattered 8-byte stores 1.74 ms; a few lanes to every row, which went through its stretch twice, 1.06, with 240 vector instructions an entry.)
+// The order inside a list is whatever the wavefronts make it: no sum depends on it, because a row of B appears in a list at most once.
 // ------------------------------------------------------------------------------------
-constexpr int kBuildThreads = 1024;
-// Rows of a tile whose stretch of a block is longer than kBuildPasses loads of their lanes are left to whole wavefronts, as many of
-// them as fit the list (500,000 rows of 1 to 50,000 entries over 242,000 columns: four lanes went 160 times through
-// memory for one row while the workgroup waited: 7.6 ms for all lists, and 2.6 with whole wavefronts).
-constexpr int kBuildLong = 64, kBuildPasses = 8, kBuildAhead = 2;
+// Two workgroups to a compute unit, as far as LDS and registers go: what a block takes is mostly waiting, for one load after the other and at barriers.  (With one
+// of 1,024 lanes / two of 512, us: 10,000 rows of 38 46 / 23, 7,777 of them 41 / 20, 28,301 ratings 95 / 72, 663,000 n-grams 96 / 44, 300,000
+// rows of 230 936 / 850, 65,536 of 1,820 917 / 805, 500,000 sets 895 / 860; as before, a few lanes to every row, 49, 36, 131, 81, 1,096, 972, 1,582.)
+constexpr int kBuildThreads = 512, kBuildPerCu = 2;
+constexpr int build_rows(int tile_rows) { return tile_rows <= kBuildThreads ? 1 : (tile_rows <= 3 * kBuildThreads ? 3 : 5); }          // of a lane
+constexpr int build_held(int rows) { return rows == 1 ? 24 : 16; }          // entries that a lane holds
+constexpr int kBuildProbe = 8;                                              // entries that a lane looks at together
+// A block of more entries than the lanes hold is gone through twice, so many at a time.
+constexpr uint32_t kBuildWindow = 8192;
+constexpr int kAgain = 4;                                                   // ... and of a lane's so many in flight together
 
 // (a norm that is not a number is the least: the distances turn a sum that is not a number into 0)
 __device__ __forceinline__ bool less_norm(double a, double than) { return !(a >= than) && than == than; }
@@ -257,29 +263,29 @@ __device__ __forceinline__ Stretch then(const Stretch &x, const Stretch &y) {
     return Stretch{x.before, (int32_t)end_of((uint32_t)x.after, y)};
 }
 
-template <int G>
-__global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
+// Sixteen bytes at once.
+struct __align__(16) Eight { uint16_t v[8]; };
+struct __align__(16) Four { float v[4]; };
+
+template <int R>
+__global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                         const float *__restrict__ values, int64_t n_rows, int64_t nnz,
                                                                         uint32_t most_cols, MatchB b, uint32_t blocks_per_wg, uint32_t wgs, int unit,
                                                                         int transform, bool with_values, const RowsVerdict seen) {
     if (rows_malformed(seen)) return;
+    constexpr int nw = kBuildThreads / kWave, K = build_held(R);
     extern __shared__ __align__(16) unsigned char s_raw[];
-    __shared__ uint32_t s_wave[kBuildThreads / kWave], s_second[kBuildThreads / kWave];
-    __shared__ uint32_t s_dense[kBuildDense], s_long[kBuildLong], s_longs;
-    __shared__ double s_least[kBuildThreads / kWave][2];
+    __shared__ uint32_t s_wave[nw], s_second[nw], s_lens[R][nw], s_first[nw], s_dense[kBuildDense];
+    __shared__ double s_least[nw][2];
     const MatchShape &shape = b.shape;
     const uint8_t *const ranks = b.ranks;
     const uint32_t cols = b.cols ? min(*b.cols, most_cols) : most_cols;
     const uint32_t block_cols = 1u << shape.block_shift, blocks = min((uint32_t)shape.blocks, (cols + block_cols - 1u) >> shape.block_shift);
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int nw = kBuildThreads / kWave, groups = kBuildThreads / G, kRows = 4, kAhead = kBuildAhead;
-    const int sub = tid % G, group = tid / G, group_shift = lane / G * G;
-    constexpr uint64_t group_mask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull);
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
     const int T = shape.tile_rows;
     // Workgroups go round the eight XCDs in turn: an XCD takes an eighth of the (tile, part)s that follow one another, so that the
-    // lines which two blocks of a row share come from its L2 (300,000 rows of 230 entries: misses 40 -> 21 million; what is left is the
-    // latency of the phases between the barriers, one workgroup to a compute unit: with two of half the LDS and twice the blocks
-    // 1,042 -> 1,367 us).  Not where they are hardly more than the 256 compute units: in the order of the grid the few that take a second
+    // lines which two blocks of a row share come from its L2 (300,000 rows of 230 entries: misses 40 -> 21 million).  Not where they are hardly more
+    // than the 256 compute units: in the order of the grid the few that take a second
     // turn are of the last tile, which is short (KL, 260 workgroups for 10,000 rows, 41 -> 32 us; L1, 360 of them, 46 in either order, and
     // the walk after it 2 us longer).
     const uint32_t of_xcd = (gridDim.x + 7u) >> 3, at_wg = gridDim.x > 288u ? (blockIdx.x & 7u) * of_xcd + (blockIdx.x >> 3) : blockIdx.x;
@@ -289,52 +295,91 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     const int rows = (int)min((int64_t)T, n_rows - j0);
     const int64_t row_first = clamp_i64(indptr[j0], 0, nnz);             // of the rows' entries
     const int64_t first = shape.room_of(row_first) + tile * shape.tile_extra;            // of the tile's lists
-    const int32_t *const tile_indices = indices + row_first;
     const int64_t list_end = shape.list_entries(nnz) - kMatchSpare;
     float *s_value = reinterpret_cast<float *>(s_raw);                              // stage entries, a multiple of 8
     uint16_t *s_row = reinterpret_cast<uint16_t *>(s_value + shape.stage);
     uint32_t *s_count = reinterpret_cast<uint32_t *>(s_row + shape.stage);    // block_cols counters, a multiple of 4
-    uint32_t *s_cur = s_count + block_cols;                                   // where a row's block begins ...
-    uint32_t *s_next = s_cur + T;                                                   // ... and the next one
-    uint32_t *s_end = s_next + T;
+    uint32_t *s_delta = s_count + block_cols;                                 // from a place in the line of stretches to the row's entry there
     uint32_t *ptr = b.ptr + (size_t)tile * (size_t)shape.ptr_stride;
+    // (positions are below 2^29: the tile's entries by byte offsets of 32 bits)
+    const unsigned char *const tile_columns = reinterpret_cast<const unsigned char *>(indices + row_first);
+    const unsigned char *const tile_values = reinterpret_cast<const unsigned char *>(values + row_first);
+    const uint8_t *const tile_ranks = ranks + row_first;
     if (part == 0 && b.least) tile_least(b.norms + j0, b.norms + n_rows + j0, rows, b.least + (size_t)tile * 2, s_least);
     const uint32_t block_first = (uint32_t)part * blocks_per_wg;
     const uint32_t block_last = min(block_first + blocks_per_wg, blocks);
     if (block_first >= block_last) return;
+    // Rows tid, tid + kBuildThreads, ...: where the block's entries begin, where the row ends, and entries to a column.
+    uint32_t cur[R], row_end[R];
+    float per_col[R];
+    // The first entry from `at` on whose column is not below `target`, of all the lane's rows at once: by the entries round where it should lie, then where these
+    // say it should, then by halves.
+    auto find = [&](uint32_t (&at)[R], uint32_t target, float ahead) {
+        constexpr int N = kBuildProbe;
+        struct __attribute__((packed, aligned(4))) Probe { uint32_t c[N]; };
+        if (nnz < N) {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                while (at[j] < row_end[j] && (uint32_t)indices[row_first + at[j]] < target) ++at[j];
+            return;
+        }
+        const int last = (int)min(nnz - N - row_first, (int64_t)INT32_MAX);          // (may lie before the tile)
+        uint32_t hi[R];
+        int guess[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            hi[j] = row_end[j];
+            guess[j] = (int)at[j] + (int)(per_col[j] * ahead);
+        }
+        for (int round = 0;; ++round) {
+            bool open = false;
+            Probe x[R];
+            int from[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (at[j] >= hi[j]) continue;
+                from[j] = min(max((int)at[j], min(guess[j] - N / 2, (int)hi[j] - N)), last);
+                x[j] = *reinterpret_cast<const Probe *>(tile_columns + (int64_t)from[j] * 4);
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (at[j] >= hi[j]) continue;
+                int less = 0;
+#pragma unroll
+                for (int u = 0; u < N; ++u) less += from[j] + u < (int)at[j] || (from[j] + u < (int)hi[j] && x[j].c[u] < target) ? 1 : 0;
+                if (less == 0) {
+                    hi[j] = (uint32_t)from[j];
+                    guess[j] = from[j] - 1 - (int)((float)(x[j].c[0] - target) * per_col[j]);
+                } else if (less == N) {
+                    at[j] = min((uint32_t)(from[j] + N), hi[j]);
+                    guess[j] = from[j] + N + (int)((float)(target - x[j].c[N - 1]) * per_col[j]);
+                } else {
+                    at[j] = hi[j] = (uint32_t)(from[j] + less);
+                }
+                if (round >= 2) guess[j] = (int)((at[j] + hi[j]) >> 1);
+                open |= at[j] < hi[j];
+            }
+            if (__ballot(open) == 0) break;
+        }
+    };
     uint32_t before = 0u;                             // entries of the columns before the block
     {
         const uint32_t c_first = block_first * block_cols;
-        const float share = (float)c_first / (float)cols;
-        uint32_t mine = 0u;
-        for (int r = tid; r < rows; r += kBuildThreads) {
-            const uint32_t begin = (uint32_t)(clamp_i64(indptr[j0 + r], row_first, nnz) - row_first);
-            const uint32_t end = max(begin, (uint32_t)(clamp_i64(indptr[j0 + r + 1], row_first, nnz) - row_first));
-            // where the row's entries of the blocks from c_first on begin: searched outwards from where they would in a row of uniform columns,
-            // mostly within the lines that are read next anyway (eight probes of a bisection were 3 of the 5 GB
-            // that 300,000 rows of 230 entries over 13 blocks read)
-            uint32_t lo = begin, hi = c_first == 0u ? begin : end;
-            auto earlier = [&](uint32_t e) { return (uint32_t)tile_indices[e] < c_first; };
-            if (lo < hi) {
-                uint32_t at = lo + min((uint32_t)((float)(hi - lo) * share), hi - lo - 1u), step = 8u;
-                if (earlier(at)) {
-                    lo = at + 1u;
-                    while (lo < hi && hi - lo > step && earlier(lo + step)) { lo += step + 1u; step *= 2u; }
-                    hi = min(hi, lo + step);
-                } else {
-                    hi = at;
-                    while (hi - lo > step && !earlier(hi - step)) { hi -= step; step *= 2u; }
-                    lo = hi - lo > step ? hi - step : lo;
-                }
+        uint32_t mine = 0u, begin[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int r = tid + j * kBuildThreads;
+            begin[j] = row_end[j] = 0u;
+            if (r < rows) {
+                begin[j] = (uint32_t)(clamp_i64(indptr[j0 + r], row_first, nnz) - row_first);
+                row_end[j] = max(begin[j], (uint32_t)(clamp_i64(indptr[j0 + r + 1], row_first, nnz) - row_first));
             }
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (earlier(mid)) lo = mid + 1; else hi = mid;
-            }
-            s_cur[r] = lo;
-            s_end[r] = end;
-            mine += lo - begin;
+            cur[j] = begin[j];
+            per_col[j] = (float)(row_end[j] - begin[j]) / (float)cols;
         }
+        if (block_first > 0u) find(cur, c_first, (float)c_first);
+#pragma unroll
+        for (int j = 0; j < R; ++j) mine += cur[j] - begin[j];
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) mine += (uint32_t)__shfl_xor((int)mine, d);
         if (lane == 0) s_wave[wave] = mine;
@@ -344,82 +389,128 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
     }
     // Where a block's piece begins in the tile's lists, `entries` before it.
     auto piece_of = [&](uint32_t entries, uint32_t block) {
-        return (uint32_t)shape.room_of(entries) + block * (uint32_t)shape.dense_per_block * (uint32_t)shape.dense_room();
+        return (uint32_t)shape.room_of(entries) + (uint32_t)shape.dense_before((int32_t)block) * (uint32_t)shape.dense_room();
     };
+    // Marks of the line's places where a row's stretch begins (its row, from 1 on), in LDS that the piece takes later: what lanes hold, or a window
+    // behind the places that are staged then.
+    uint16_t *const marks_behind = reinterpret_cast<uint16_t *>(s_value + (shape.stage - min(kBuildWindow, shape.stage) / 64u * 32u));
+    const uint32_t held = min((uint32_t)(K * kBuildThreads), shape.stage * 2u) & ~63u, window = min(kBuildWindow, shape.stage) & ~63u;
     for (uint32_t block = block_first; block < block_last; ++block) {
         const uint32_t c0 = block * block_cols, range = min(block_cols, cols - c0);
-        for (uint32_t i = tid; i < block_cols; i += kBuildThreads) s_count[i] = 0u;
-        if (tid == 0) s_longs = 0u;
-        __syncthreads();
-        // count: G lanes to the row, the first kAhead loads of four rows in flight together (one load ahead 1,213 us for 300,000 rows of
-        // 230 entries, two 1,085, four 1,176; 242,000 columns of sets 1,836, 1,627 and 1,583)
-        for (int r0 = group; r0 < rows; r0 += kRows * groups) {
-            uint32_t pos[kRows], end[kRows], c[kRows][kAhead];
-            auto load = [&](int u) {
+        for (uint32_t i = 4u * (uint32_t)tid; i < block_cols; i += 4u * kBuildThreads) *reinterpret_cast<uint4 *>(s_count + i) = uint4{0u, 0u, 0u, 0u};
+        uint32_t next[R], off[R], entries = 0u;
 #pragma unroll
-                for (int x = 0; x < kAhead; ++x)
-                    c[u][x] = pos[u] + (uint32_t)(x * G + sub) < end[u] ? (uint32_t)indices[row_first + pos[u] + (uint32_t)(x * G + sub)] : 0xFFFFFFFFu;
-            };
+        for (int j = 0; j < R; ++j) next[j] = block + 1u < blocks ? cur[j] : row_end[j];
+        if (block + 1u < blocks) find(next, c0 + block_cols, (float)block_cols);
 #pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                const int r = r0 + u * groups;
-                pos[u] = r < rows ? s_cur[r] : 0u;
-                end[u] = r < rows ? s_end[r] : 0u;
-                load(u);
-            }
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                const int r = r0 + u * groups;
-                for (int pass = kAhead;; pass += kAhead) {
-                    uint32_t n = 0u;
-#pragma unroll
-                    for (int x = 0; x < kAhead; ++x) {
-                        const bool in = c[u][x] - c0 < range;
-                        if (in) atomicAdd(&s_count[c[u][x] - c0], 1u);
-                        n += (uint32_t)__popcll((__ballot(in) >> group_shift) & group_mask);
-                    }
-                    pos[u] += n;
-                    if (n < (uint32_t)(G * kAhead)) break;
-                    if (pass >= kBuildPasses) {
-                        uint32_t at = (uint32_t)kBuildLong;
-                        if (sub == 0) at = atomicAdd(&s_longs, 1u);
-                        at = (uint32_t)__shfl((int)at, group_shift);
-                        if (at < (uint32_t)kBuildLong) {
-                            if (sub == 0) s_long[at] = (uint32_t)r;
-                            break;
-                        }
-                        pass = -0x40000000;                      // (no place left: these lanes go on)
-                    }
-                    load(u);
-                }
-                if (r < rows && sub == 0) s_next[r] = pos[u];
-            }
+        for (int j = 0; j < R; ++j) {
+            if (j * kBuildThreads >= rows) continue;
+            const int incl = wave_scan_add((int)(next[j] - cur[j]));
+            if (lane == 63) s_lens[j][wave] = (uint32_t)incl;
+            off[j] = (uint32_t)incl - (next[j] - cur[j]);
         }
         __syncthreads();
-        const int longs = (int)min(s_longs, (uint32_t)kBuildLong);
-        if (longs > 0) {
-            for (int at = wave; at < longs; at += nw) {
-                const int r = (int)s_long[at];
-                uint32_t pos = s_next[r];
-                const uint32_t end = s_end[r];
-                for (uint32_t n = kRows * 64u; n == kRows * 64u;) {
-                    uint32_t c[kRows];
 #pragma unroll
-                    for (int u = 0; u < kRows; ++u)
-                        c[u] = pos + (uint32_t)(u * 64 + lane) < end ? (uint32_t)indices[row_first + pos + (uint32_t)(u * 64 + lane)] : 0xFFFFFFFFu;
-                    n = 0u;
+        for (int j = 0; j < R; ++j) {
+            if (j * kBuildThreads >= rows) continue;
+            off[j] += entries;
 #pragma unroll
-                    for (int u = 0; u < kRows; ++u) {
-                        const bool in = c[u] - c0 < range;
-                        if (in) atomicAdd(&s_count[c[u] - c0], 1u);
-                        n += (uint32_t)__popcll(__ballot(in));
-                    }
-                    pos += n;
-                }
-                if (lane == 0) s_next[r] = pos;
+            for (int w = 0; w < nw; ++w) { off[j] += w < wave ? s_lens[j][w] : 0u; entries += s_lens[j][w]; }
+            const int r = tid + j * kBuildThreads;
+            if (r < rows) s_delta[r] = cur[j] - off[j];
+        }
+        const bool once = entries <= held;
+        uint16_t *s_mark = once ? reinterpret_cast<uint16_t *>(s_raw) : marks_behind;
+        // The line's places from w0 on, up to w1, an even share (`steps` times 64) to each wavefront.
+        uint32_t w0 = 0u, w1 = 0u, steps = 0u, carry = 0u;
+        auto mark = [&](uint32_t begin, uint32_t end) {
+            w0 = begin;
+            w1 = end;
+            steps = (w1 - w0 + (uint32_t)(kWave * nw) - 1u) / (uint32_t)(kWave * nw);
+            for (uint32_t i = 8u * (uint32_t)tid; i < w1 - w0; i += 8u * kBuildThreads) *reinterpret_cast<uint4 *>(s_mark + i) = uint4{0u, 0u, 0u, 0u};
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const uint32_t r = (uint32_t)(tid + j * kBuildThreads), from = max(off[j], w0), to = min(off[j] + (next[j] - cur[j]), w1);
+                if (j * kBuildThreads >= rows || from >= to) continue;
+                if (from == off[j]) s_mark[from - w0] = (uint16_t)(r + 1u);
+                const uint32_t share = steps * kWave;
+                for (uint32_t w = (from - w0 + share - 1u) / share; w < (uint32_t)nw && w0 + w * share < to; ++w) s_first[w] = r + 1u;
             }
             __syncthreads();
+            carry = s_first[wave];
+        };
+        // The wavefront's places, 64 after 64: the lane's row and its entry's position.
+        auto place_of = [&](uint32_t step, uint32_t &row, uint32_t &e) {
+            const uint32_t p = ((uint32_t)wave * steps + step) * kWave + (uint32_t)lane;
+            const bool in = step < steps && p < w1 - w0;
+            const int m = wave_scan_max(max(in ? (int)s_mark[p] : 0, (int)carry));
+            carry = (uint32_t)__builtin_amdgcn_readlane(m, 63);
+            row = (uint32_t)m - 1u;
+            e = in ? s_delta[row] + w0 + p : 0u;
+            return in;
+        };
+        // What a lane holds of an entry: column, row and rank (13, 12 and 6 bits; ~0: nothing), its value, and the entries of its list that were counted before
+        // (16 bits each).
+        uint32_t hold[K], hold_before[K / 2];
+        float hold_value[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) { hold[k] = 0xFFFFFFFFu; hold_value[k] = 0.0f; hold_before[k / 2] = 0u; }
+        if (once) {
+            mark(0u, entries);
+            constexpr int H = R == 5 ? K / 2 : K;               // entries whose loads are in flight together
+#pragma unroll
+            for (int h = 0; h < K; h += H) {
+                uint32_t c[H], row[H];
+#pragma unroll
+                for (int x = 0; x < H; ++x) { c[x] = 0xFFFFFFFFu; row[x] = 0u; }
+#pragma unroll
+                for (int g = 0; g < H; g += 4) {
+                    if ((uint32_t)(h + g) >= steps) continue;
+#pragma unroll
+                    for (int x = g; x < g + 4; ++x) {
+                        uint32_t e;
+                        if (place_of((uint32_t)(h + x), row[x], e)) {
+                            c[x] = *reinterpret_cast<const uint32_t *>(tile_columns + e * 4u);
+                            hold_value[h + x] = *reinterpret_cast<const float *>(tile_values + e * 4u);
+                            if (ranks) row[x] |= (uint32_t)tile_ranks[e] << 16;
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int g = 0; g < H; g += 4) {
+                    if ((uint32_t)(h + g) >= steps) continue;
+#pragma unroll
+                    for (int x = g; x < g + 4; ++x) {
+                        const uint32_t col = c[x] - c0;
+                        if (col < range) {
+                            hold[h + x] = col | (row[x] & 0xFFFu) << 13 | min(row[x] >> 16, 2u * kRanks - 1u) << 25;
+                            hold_before[(h + x) / 2] |= atomicAdd(&s_count[col], 1u) << (16 * (x & 1));
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else {
+            for (uint32_t w = 0u; w < entries; w += window) {
+                mark(w, min(w + window, entries));
+                for (uint32_t k = 0u; k < steps; k += kAgain) {
+                    uint32_t c[kAgain];
+#pragma unroll
+                    for (int x = 0; x < kAgain; ++x) {
+                        uint32_t row, e;
+                        c[x] = 0xFFFFFFFFu;
+                        if (place_of(k + (uint32_t)x, row, e)) c[x] = *reinterpret_cast<const uint32_t *>(tile_columns + e * 4u);
+                    }
+#pragma unroll
+                    for (int x = 0; x < kAgain; ++x)
+                        if (c[x] - c0 < range) atomicAdd(&s_count[c[x] - c0], 1u);
+                }
+                __syncthreads();
+            }
         }
+        __syncthreads();
         // Which columns are dense: the first of the block that reach the mark, in column order (so that the same columns are dense in every
         // run).  A thread has some columns that follow one another.
         const uint32_t mine = ((block_cols + kBuildThreads - 1u) / kBuildThreads + 3u) & ~3u, mine_first = (uint32_t)tid * mine;
@@ -432,23 +523,21 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
                 each(i + 3u, v.w);
             }
         };
-        const uint32_t whole = (uint32_t)T, mark = (uint32_t)shape.dense_from, most_dense = (uint32_t)shape.dense_per_block;
-        uint32_t rank = 0u, n_dense = 0u, entries = 0u;             // columns that reach the mark before the thread's, all of them; the block's entries
+        // (as many as the block's share of their room holds, and half of the room for gaps: where few columns have most of the entries, they lie
+        // in few blocks)
+        const uint32_t whole = (uint32_t)T, dense_mark = (uint32_t)shape.dense_from, room_of_gaps = (uint32_t)(shape.room_of(before + entries) - shape.room_of(before)) - entries;
+        const uint32_t most_dense = min(kBuildDense, (uint32_t)(shape.dense_before((int32_t)block + 1) - shape.dense_before((int32_t)block)) +
+                                                         (shape.dense_room() > 0 ? room_of_gaps / 2u / (uint32_t)shape.dense_room() : 0u));
+        uint32_t rank = 0u, n_dense = 0u;                          // columns that reach the mark before the thread's, and all of them
         {
-            uint32_t marked = 0u, sum = 0u;
-            columns([&](uint32_t, uint32_t v) { marked += v >= mark ? 1u : 0u; sum += v; });
-            rank = marked;
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) {
-                const uint32_t r = (uint32_t)__shfl_up((int)rank, d);
-                sum += (uint32_t)__shfl_xor((int)sum, d);
-                if (lane >= d) rank += r;
-            }
-            if (lane == 63) { s_wave[wave] = rank; s_second[wave] = sum; }
+            uint32_t marked = 0u;
+            columns([&](uint32_t, uint32_t v) { marked += v >= dense_mark ? 1u : 0u; });
+            rank = (uint32_t)wave_scan_add((int)marked);
+            if (lane == 63) s_wave[wave] = rank;
             __syncthreads();
             rank -= marked;
 #pragma unroll
-            for (int w = 0; w < nw; ++w) { rank += w < wave ? s_wave[w] : 0u; n_dense += s_wave[w]; entries += s_second[w]; }
+            for (int w = 0; w < nw; ++w) { rank += w < wave ? s_wave[w] : 0u; n_dense += s_wave[w]; }
             n_dense = min(n_dense, most_dense);
             __syncthreads();
         }
@@ -464,8 +553,8 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
             Stretch incl{0u, -1};
             uint32_t r = rank;
             columns([&](uint32_t, uint32_t v) {
-                incl = then(incl, piece(v, v >= mark && r < most_dense));
-                r += v >= mark ? 1u : 0u;
+                incl = then(incl, piece(v, v >= dense_mark && r < most_dense));
+                r += v >= dense_mark ? 1u : 0u;
             });
 #pragma unroll
             for (int d = 1; d < kWave; d <<= 1) {
@@ -489,10 +578,10 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         {
             uint32_t r = rank;
             columns([&](uint32_t i, uint32_t v) {
-                const bool dense = v >= mark && r < most_dense;
+                const bool dense = v >= dense_mark && r < most_dense;
                 const uint32_t flag = dense ? kMatchDense : 0u, end = end_of(at, piece(v, dense)), from = end - (dense ? whole : v);
                 if (dense) s_dense[r] = from;
-                r += v >= mark ? 1u : 0u;
+                r += v >= dense_mark ? 1u : 0u;
                 s_count[i] = from | flag;
                 if (i < range) ptr[c0 + block + i] = (base + from - phase) | (from - at) << kMatchGapShift | flag;
                 at = end;
@@ -503,97 +592,98 @@ __global__ void __launch_bounds__(kBuildThreads) spd_match_build_kernel(const in
         float *__restrict__ values_at = b.values + first + base - phase;   // the block's piece
         uint16_t *__restrict__ rows_at = b.rows + first + base - phase;
         const int64_t room = list_end - (first + base - phase);    // (never reached while the row pointers hold)
-        for (uint32_t d = 0; d < n_dense; ++d)
-            for (uint32_t i = s_dense[d] + (uint32_t)tid; i < s_dense[d] + whole; i += kBuildThreads) {
-                if (i < shape.stage) s_value[i] = 0.0f;
-                else if (i < room) values_at[i] = 0.0f;
-            }
-        __threadfence_block();
-        __syncthreads();
-        // place
-        auto place = [&](uint32_t c, float v, int r, uint32_t rank) {
-            if (c - c0 >= range) return;
-            const float t = transform_value(transform, v);
-            uint32_t *count = &s_count[c - c0];
-            uint32_t at = *count & ~kMatchDense;
-            if (*count & kMatchDense) {
-                at += (uint32_t)r;
-                if (at < shape.stage) s_value[at] = t;
-                else if (at < room) values_at[at] = t;
-            } else {
-                // (a stored zero is absent: it goes to the spare row behind the tile's)
-                const uint16_t cell = (uint16_t)((uint32_t)(t != 0.0f ? r : T) * (uint32_t)unit + (min(rank, 2u * kRanks - 1u) << kRankShift));
-                at = atomicAdd(count, 1u);
-                if (at < shape.stage) {
-                    s_row[at] = cell;
-                    s_value[at] = t;
-                } else if (at < room) {
-                    rows_at[at] = cell;
-                    values_at[at] = t;
+        // From the lanes where all of the piece is staged, else as the entries come again.
+        const bool from_lanes = once && total <= shape.stage;
+        const uint32_t stage = from_lanes ? shape.stage : shape.stage - window / 2u;
+        s_mark = marks_behind;
+        if (n_dense > 0u) {
+            for (uint32_t d = 0; d < n_dense; ++d)
+                for (uint32_t i = s_dense[d] + (uint32_t)tid; i < s_dense[d] + whole; i += kBuildThreads) {
+                    if (i < stage) s_value[i] = 0.0f;
+                    else if (i < room) values_at[i] = 0.0f;
                 }
-            }
+            __threadfence_block();
+            __syncthreads();
+        }
+        auto cell_of = [&](uint32_t row, uint32_t rank_in_row, float t) {          // (a stored zero is absent: it goes to the spare row behind the tile's)
+            return (uint16_t)((t != 0.0f ? row : (uint32_t)T) * (uint32_t)unit + (rank_in_row << kRankShift));
         };
-        constexpr uint32_t kShort = (uint32_t)(G * kBuildPasses);         // a stretch beyond it may be a whole wavefront's
-        for (int r0 = group; r0 < rows; r0 += kRows * groups) {
-            uint32_t pos[kRows], end[kRows], c[kRows][kAhead];
-            float v[kRows][kAhead];
-            uint32_t rank[kRows][kAhead];
-            auto load = [&](int u) {
+        if (from_lanes) {
+            if (transform != TR_ID) {
 #pragma unroll
-                for (int x = 0; x < kAhead; ++x) {
-                    const uint32_t e = pos[u] + (uint32_t)(x * G);
-                    c[u][x] = e < end[u] ? (uint32_t)indices[row_first + e] : 0xFFFFFFFFu;
-                    v[u][x] = e < end[u] ? values[row_first + e] : 0.0f;
-                    rank[u][x] = ranks && e < end[u] ? ranks[row_first + e] : 0u;
-                }
-            };
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                const int r = r0 + u * groups;
-                pos[u] = r < rows ? s_cur[r] : 0u;
-                end[u] = r < rows ? s_next[r] : 0u;
-                if (longs > 0 && end[u] - pos[u] >= kShort)
-                    for (int at = 0; at < longs; ++at) end[u] = s_long[at] == (uint32_t)r ? pos[u] : end[u];
-                pos[u] += sub;
-                load(u);
+                for (int k = 0; k < K; ++k) hold_value[k] = transform_value(transform, hold_value[k]);
             }
 #pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                const int r = r0 + u * groups;
-                while (pos[u] < end[u]) {
+            for (int g = 0; g < K; g += 4) {
+                if ((uint32_t)g >= steps) continue;
 #pragma unroll
-                    for (int x = 0; x < kAhead; ++x) place(c[u][x], v[u][x], r, rank[u][x]);
-                    pos[u] += (uint32_t)(G * kAhead);
-                    if (pos[u] < end[u]) load(u);
+                for (int k = g; k < g + 4; ++k) {
+                    if (hold[k] == 0xFFFFFFFFu) continue;
+                    const uint32_t start = s_count[hold[k] & 0x1FFFu], row = (hold[k] >> 13) & 0xFFFu;
+                    const bool dense = (start & kMatchDense) != 0u;
+                    const uint32_t at = (start & ~kMatchDense) + (dense ? row : (hold_before[k / 2] >> (16 * (k & 1))) & 0xFFFFu);
+                    s_value[at] = hold_value[k];
+                    s_row[at] = cell_of(row, hold[k] >> 25, hold_value[k]);          // (of a dense column nothing reads it)
                 }
             }
-        }
-        for (int at = wave; at < longs; at += nw) {
-            const int r = (int)s_long[at];
-            const uint32_t end = s_next[r];
-            for (uint32_t pos = s_cur[r]; pos < end; pos += kRows * 64u) {
-                uint32_t c[kRows];
-                float v[kRows];
-                uint32_t rank[kRows];
+        } else {
+            for (uint32_t w = 0u; w < entries; w += window) {
+                mark(w, min(w + window, entries));
+                for (uint32_t k = 0u; k < steps; k += kAgain) {
+                    uint32_t c[kAgain], row[kAgain];
+                    float v[kAgain];
 #pragma unroll
-                for (int u = 0; u < kRows; ++u) {
-                    const uint32_t e = pos + (uint32_t)(u * 64 + lane);
-                    rank[u] = ranks && e < end ? ranks[row_first + e] : 0u;
-                    c[u] = e < end ? (uint32_t)indices[row_first + e] : 0xFFFFFFFFu;
-                    v[u] = e < end ? values[row_first + e] : 0.0f;
+                    for (int x = 0; x < kAgain; ++x) {
+                        uint32_t e;
+                        c[x] = 0xFFFFFFFFu;
+                        if (place_of(k + (uint32_t)x, row[x], e)) {
+                            c[x] = *reinterpret_cast<const uint32_t *>(tile_columns + e * 4u);
+                            v[x] = *reinterpret_cast<const float *>(tile_values + e * 4u);
+                            if (ranks) row[x] |= min((uint32_t)tile_ranks[e], 2u * kRanks - 1u) << 16;
+                        }
+                    }
+#pragma unroll
+                    for (int x = 0; x < kAgain; ++x) {
+                        const uint32_t col = c[x] - c0;
+                        if (col >= range) continue;
+                        const float t = transform_value(transform, v[x]);
+                        const uint32_t start = s_count[col], r = row[x] & 0xFFFFu;
+                        const bool dense = (start & kMatchDense) != 0u;
+                        const uint32_t at = dense ? (start & ~kMatchDense) + r : atomicAdd(&s_count[col], 1u);
+                        const uint16_t cell = cell_of(r, row[x] >> 16, t);
+                        if (at < stage) {
+                            s_value[at] = t;
+                            s_row[at] = cell;
+                        } else if (at < room) {
+                            values_at[at] = t;
+                            if (!dense) rows_at[at] = cell;
+                        }
+                    }
                 }
-#pragma unroll
-                for (int u = 0; u < kRows; ++u) place(c[u], v[u], r, rank[u]);
+                __syncthreads();
             }
         }
         __syncthreads();
-        const uint32_t staged = min(total, shape.stage);
-        for (uint32_t i = phase + tid; i < staged; i += kBuildThreads)
-            if (i < room) {
-                rows_at[i] = s_row[i];
-                if (with_values || n_dense > 0u) values_at[i] = s_value[i];
+        // (in memory as in LDS a piece begins `phase` entries behind a line)
+        const uint32_t staged = (uint32_t)max((int64_t)0, min((int64_t)min(total, stage), room));
+        const bool values_too = with_values || n_dense > 0u;
+        for (uint32_t i = 8u * (uint32_t)tid; i < staged; i += 8u * kBuildThreads) {
+            if (i >= phase && i + 8u <= staged) {
+                *reinterpret_cast<Eight *>(rows_at + i) = *reinterpret_cast<const Eight *>(s_row + i);
+            } else {
+                for (uint32_t x = max(i, phase); x < min(i + 8u, staged); ++x) rows_at[x] = s_row[x];
             }
-        for (int r = tid; r < rows; r += kBuildThreads) s_cur[r] = s_next[r];
+        }
+        if (values_too)
+            for (uint32_t i = 4u * (uint32_t)tid; i < staged; i += 4u * kBuildThreads) {
+                if (i >= phase && i + 4u <= staged) {
+                    *reinterpret_cast<Four *>(values_at + i) = *reinterpret_cast<const Four *>(s_value + i);
+                } else {
+                    for (uint32_t x = max(i, phase); x < min(i + 4u, staged); ++x) values_at[x] = s_value[x];
+                }
+            }
+#pragma unroll
+        for (int j = 0; j < R; ++j) cur[j] = next[j];
         before += entries;
         __syncthreads();
     }
@@ -649,48 +739,56 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
     s.tile_rows = (int32_t)(((n + tiles - 1) / tiles + kWave - 1) / kWave * kWave);
     s.lds_bytes = (uint32_t)s.waves * match_strip_bytes(cell, s.tile_rows);
     // A block of columns: an eighth of the LDS for counters, or twice that, and entries for four fifths, on the mean,
-    // of what counters and row positions leave for its piece of the lists (the rest of a fuller block goes straight to
-    // memory; narrower blocks read a row's lines more often).  Dense columns may take half as much again.
-    const int64_t usable = lds_budget - 1024, rows_bytes = 12 * (int64_t)s.tile_rows;
-    if (usable < rows_bytes + 4096) return s;
+    // of what counters and row positions leave for its piece of the lists, and of what the lanes hold (a fuller block is gone through
+    // twice; narrower blocks read a row's lines more often).  Dense columns may take half as much again: so many to so many columns as
+    // blocks have that take a compute unit each.
     // A step of 64 rows of a dense column costs half a list's step, and a third where that adds doubles.  (Dot products from a third / 0.4 / a
     // half of the rows on, us: 1,024 x 300,000 rows of 230, cosine, 5,385 / 5,344 / 5,519, k-NN of 2,048 of them, Hellinger, 7,304 /
     // 7,489 / 8,115; 10,000 x 10,000 rows of 38, cosine, 312 / 311 / 307.  From 0.3 / 0.4 / 0.5 / 0.6 on: the same rows of 38, L1, 336 /
     // 331 / 325 / 318; sets, Jaccard, 9,102 / 8,970 / 8,928 / 8,963.  Chebyshev: an entry has a rank, a column of values none.)
     s.dense_from = op == OP_CHEB ? s.tile_rows + 1 : std::max(1, s.tile_rows / (op == OP_DOT ? 3 : 2));
     const double per_col = per_cell * (double)s.tile_rows;
-    auto stage_of = [&](int shift) { return (usable - rows_bytes - ((int64_t)4 << shift)) / 48 * 8; };
-    int shift = 2;
-    while ((4 << (shift + 1)) <= usable / 8 && (1 << shift) < n_cols) ++shift;
-    // (sparse blocks, many of them: what a block costs besides its entries.  500,000 sets over 242,000 columns, 2,432 rows to
-    // the tile: 2.6 ms with 4,096 columns to the block, 2.0 with 8,192)
-    const int narrow = shift;
-    if ((n_cols >> shift) >= 16 && (4 << (shift + 1)) <= usable / 4) ++shift;
-    while (shift > 2 && per_col * (double)(1 << shift) * 1.25 > (double)stage_of(shift)) --shift;
-    // Dense columns to a block: what its share of the entries fills, once at least (of the halves of a wide block, so that its width
-    // does not cost memory: an index may keep lists that grow to its limit and no further).
-    auto dense_of = [&](int at) {
-        const int of = std::min(at, narrow);
-        return (int32_t)std::min<double>(kBuildDense, std::max(1.0, std::floor(per_cell * (double)(1 << of))) * (double)(1 << (at - of)));
-    };
-    // a workgroup for every compute unit, where there are columns enough, and blocks so that their dense columns take no more
-    // than the entries do, and 512 KiB (12,970 rows of 6 over 10,261 columns, with an index: 41 blocks took the lists over its limit,
-    // and its calls 600 us by the scan instead of 240)
     const int64_t tiles_now = (n + s.tile_rows - 1) / s.tile_rows;
     auto blocks_of = [&](int at) { return (n_cols + (1 << at) - 1) >> at; };
-    while (shift > 8 && tiles_now * blocks_of(shift) < 256 &&
-           tiles_now * blocks_of(shift - 1) * dense_of(shift - 1) * s.dense_room() * 6 <= 8 * nnz + (512 << 10)) --shift;
+    auto stage_of = [&](int64_t usable, int64_t rows_bytes, int shift) { return (usable - rows_bytes - ((int64_t)4 << shift)) / 48 * 8; };
+    {
+        const int64_t usable = lds_budget - 1024, rows_bytes = 12 * (int64_t)s.tile_rows;
+        if (usable < rows_bytes + 4096) return s;
+        int shift = 2;
+        while ((4 << (shift + 1)) <= usable / 8 && (1 << shift) < n_cols) ++shift;
+        const int narrow = shift;
+        if ((n_cols >> shift) >= 16 && (4 << (shift + 1)) <= usable / 4) ++shift;
+        while (shift > 2 && per_col * (double)(1 << shift) * 1.25 > (double)stage_of(usable, rows_bytes, shift)) --shift;
+        // What the columns' share of the entries fills, once at least (of the halves of many columns, so that their number
+        // does not cost memory: an index may keep lists that grow to its limit and no further).
+        auto dense_of = [&](int at) {
+            const int of = std::min(at, narrow);
+            return (int32_t)std::min<double>(kBuildDensePer, std::max(1.0, std::floor(per_cell * (double)(1 << of))) * (double)(1 << (at - of)));
+        };
+        // (a workgroup for every compute unit, where there are columns enough, and so that dense columns take no more
+        // than the entries do, and 512 KiB: 12,970 rows of 6 over 10,261 columns, with an index: 41 blocks took the lists over its limit,
+        // and its calls 600 us by the scan instead of 240)
+        while (shift > 8 && tiles_now * blocks_of(shift) < 256 &&
+               tiles_now * blocks_of(shift - 1) * dense_of(shift - 1) * s.dense_room() * 6 <= 8 * nnz + (512 << 10)) --shift;
+        s.dense_shift = shift;
+        s.dense_per = dense_of(shift);
+    }
+    // Two workgroups to a compute unit, since what a block takes is mostly waiting for one thing after the other.
+    const int64_t usable = lds_budget / kBuildPerCu - 1024, rows_bytes = 4 * (int64_t)s.tile_rows, held = build_held(build_rows(s.tile_rows)) * kBuildThreads;
+    if (usable < rows_bytes + 2048) return s;
+    int shift = s.dense_shift;
+    while (shift > 2 && ((4 << shift) > usable / 4 ||
+                         per_col * (double)(1 << shift) * 1.25 > (double)std::min(stage_of(usable, rows_bytes, shift), held))) --shift;
     s.block_shift = shift;
-    s.stage = (uint32_t)stage_of(shift);
+    s.stage = (uint32_t)stage_of(usable, rows_bytes, shift);
     s.blocks = (int32_t)blocks_of(shift);
-    s.dense_per_block = dense_of(shift);
     s.ptr_stride = (n_cols + s.blocks + 3) / 4 * 4;
-    s.tile_extra = (int64_t)s.blocks * s.dense_per_block * s.dense_room();
+    s.tile_extra = (int64_t)s.dense_before(s.blocks) * s.dense_room();
     s.build_lds_bytes = s.stage * 6u + (4u << shift) + (uint32_t)rows_bytes;
     s.n_tiles = (int32_t)((n + s.tile_rows - 1) / s.tile_rows);
     if (op == OP_DOT && s.list_entries(nnz) >= (int64_t)1 << 29) {         // (positions end there: no more room than other products' columns take)
         s.dense_from = std::max(1, s.tile_rows / 2);
-        s.tile_extra = (int64_t)s.blocks * s.dense_per_block * s.dense_room();
+        s.tile_extra = (int64_t)s.dense_before(s.blocks) * s.dense_room();
     }
     // Lists at lines of memory, where a tile's positions and a gap fit a word and all positions their limit.
     s.aligned = 1;
@@ -708,9 +806,9 @@ static int64_t match_build_grid(const MatchShape &s) {
 }
 bool match_launches_fit(const MatchShape &s, int op, int64_t m, int64_t nnz_a, int64_t n, bool renumbered) {
     constexpr int64_t kMost = ((int64_t)1 << 32) - 1024;
-    // (B's norms: of fewer than 2^30 rows and, from 16 entries to the row on, 2^25 of them, by its lists' positions)
+    // (The build's launches lie a factor of two below that: the line stays where it was with workgroups of 1,024.  B's norms: of fewer than 2^30 rows and, from 16 entries to the row on, 2^25 of them, by its lists' positions)
     return (op == OP_CHEB ? match_ranks_grid(m + n) * 256 <= kMost : m * match_norm_lanes(std::max<int64_t>(m, 1), nnz_a) <= kMost) &&
-           match_build_grid(s) * kBuildThreads <= kMost && (!renumbered || nnz_a <= kMost);
+           match_build_grid(s) * 2 * kBuildThreads <= kMost && (!renumbered || nnz_a <= kMost);
 }
 
 hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32_t *indices, const float *values,
@@ -718,9 +816,8 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
     if (n_rows <= 0) return hipSuccess;
     const MatchShape &s = b.shape;
     const uint32_t per_wg = match_build_blocks(s), wgs = ((uint32_t)s.blocks + per_wg - 1u) / per_wg;
-    const double per_row = (double)nnz / (double)n_rows / (double)s.blocks;
-    auto go = [&](auto g) {
-        auto kern = spd_match_build_kernel<decltype(g)::value>;
+    auto go = [&](auto rows) {
+        auto kern = spd_match_build_kernel<decltype(rows)::value>;
         static std::atomic<uint32_t> allowed[kMatchDevices];
         hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
@@ -728,11 +825,11 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
                            nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op != OP_CNT, seen);
         return hipGetLastError();
     };
-    // (a row's stretch in the two loads of its lanes, where that leaves no more than half of them idle: rows of 1,820 over 51 blocks 1,078 us
-    // with 16 lanes, 954 with 32; rows of 230 over 13 blocks 1,042 with 16, 1,378 with 32, 1,123 with 8)
-    if (per_row >= 24.0) return go(std::integral_constant<int, 32>{});
-    if (per_row >= 8.0) return go(std::integral_constant<int, 16>{});
-    return per_row >= 3.0 ? go(std::integral_constant<int, 8>{}) : go(std::integral_constant<int, 4>{});
+    switch (build_rows(s.tile_rows)) {
+    case 1: return go(std::integral_constant<int, 1>{});
+    case 3: return go(std::integral_constant<int, 3>{});
+    default: return go(std::integral_constant<int, 5>{});
+    }
 }
 
 __global__ void __launch_bounds__(256) spd_match_knn_begin_kernel(unsigned long long *tau, int64_t *row_off, int32_t *row_lists,

@@ -951,3 +951,32 @@ def test_lists_that_begin_at_lines(spd, metric, stored):
         idx, dist = h.knn(dA, dB, metric, 9)
         assert_knn_matches(_np(idx), _np(dist), want, 9, metric, metric)
     h.close()
+
+
+# Blocks of the build: one that stores far more entries than a workgroup's lanes hold (nearly all rows store the same 70 columns of
+# thousands), rows whose stretch of a block is most of it, no more entries than are looked at together, and tiles of more rows than lanes.
+@pytest.mark.parametrize("metric", ["l1", "cosine", "hellinger", "jaccard", "minkowski", "chebyshev"])
+@pytest.mark.parametrize("kind", ["full block", "long rows", "few entries"])
+def test_blocks_of_the_build(spd, metric, kind):
+    rng = np.random.default_rng(3)
+    n, cols = (2_600, 9_000) if kind == "full block" else ((1_100, 12_000) if kind == "long rows" else (3, 40))
+    rows = []
+    for r in range(n):
+        if kind == "full block":
+            c = np.concatenate([100 + rng.choice(70, size=60, replace=False), rng.integers(0, cols, size=2)])
+        elif kind == "long rows":
+            c = rng.choice(cols, size=11_000, replace=False) if r in (3, 700) else rng.integers(0, cols, size=4)
+        else:
+            c = rng.integers(0, cols, size=(2, 0, 3)[r])
+        rows.append(np.unique(c))
+    indptr = np.concatenate([[0], np.cumsum([len(c) for c in rows])]).astype(np.int64)
+    B = {"n_rows": n, "n_cols": cols, "indptr": indptr, "indices": np.concatenate(rows).astype(np.int32),
+         "values": (rng.integers(0, 17, size=int(indptr[-1])) / 8.0).astype(np.float32)}
+    A = _matrix(rng, 30, cols, (3, 64, 65, 1, 130, 0, 17, 2_000))
+    print("blocks of the build", metric, kind, flush=True)
+    h = _lists(spd, profile=1)
+    p = _p_of(metric)
+    got = _np(h.pairwise(spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B), metric, p))
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    assert_distances_close(got, oracle.pairwise(A, B, ORACLE_NAME[metric], p), metric)
+    h.close()
