@@ -720,59 +720,60 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
 // every (tile, row); the last round of (tile, row)s leaves wavefronts idle, unless rows are so long that a workgroup's wavefronts share
 // them.  The staged scan pays for every visit (a staged row, a streamed entry; more where longer staged rows leave fewer of them
 // a place in LDS, and where the columns are too many for the quick maps).  Both pay for what they make of B, where no index
-// has it, for the pairs they finish, and for their launches.  The constants are fitted to both ways' times of 14,000 pairs of operands
-// (30 to 12,000 rows against 300 to 300,000, of equal, log-normal and power-law lengths of 1.5 to 3,000 entries, A's as long as
-// B's and not, uniform and Zipf columns, 2,000 to 2^20 of them, every product, k-NN with k = 1 to 64 and pairwise, with an index
-// and without); nine of ten estimates are within 0.4 to 1.35 of the times, because row pointers do not show how A's columns
-// meet B's.  (Fitted with lists of eight bytes an entry and long rows dealt to slices; since then the lists take up to a third less,
-// so that calls near the line may go by the scan where lists would be faster: of 77 random pairwise calls by cosine, L1 and inner products 8, which lists
-// would take 1.1 to 2.0 times less, mostly under 300 rows against 10,000 to 180,000; none of them, and of 73 by Chebyshev none beyond 1.05, is slower by
-// lists than by the scan.)  Columns are seldom uniform where they are many: over all columns the lists are taken to be met up to 40 times as
+// has it, for the pairs they finish, and for their launches.  The constants are fitted to all ways' times of 11,688 pairs of operands
+// (of the working range: words, counts, ratings, sets, n-grams, skewed lengths; and of 30 to 12,000 rows against 300 to 300,000, of equal, log-normal
+// and power-law lengths of 1.5 to 3,000 entries, A's as long as
+// B's and not, uniform and Zipf columns, 2,000 to 2^20 of them; every product, k-NN with k = 1 to 64 and pairwise, with an index
+// and without); nine of ten estimates are within 0.5 to 1.5 of the times, because row pointers do not show how A's columns
+// meet B's, nor its longest row.  Columns are seldom uniform where they are many: over all columns the lists are taken to be met up to 40 times as
 // often as if they were, as far as the density leaves room for that (words, Zipf columns, rows of 230 over 102,660: some 40 times).
-// Of 1,993 random calls of the working range (words, counts, ratings, sets, n-grams, skewed lengths) one in a hundred loses a tenth or more
-// against the better of the rules before this one.
-struct OpCost { double entry, step, match, row, knn_row, visit, longer, wide, pair; };
+// The estimates of lists are weighed by what chose best between the ways (`bias`: pairwise and k-NN, over all columns and over A's).  Chosen so, the
+// calls take 5 % more than by the best way on the mean, 17 % by the constants before (fitted with lists that took up to a third longer), which
+// sent most calls near the line to the scan: 371 x 33,325 sets, Dice, k-NN, 810 us by it and 326 by lists, 3,247 x 7,668 counts, Jaccard, 4,622 and
+// 2,050, 86 x 8,953 ratings 344 and 173.  One call in 25 is slower by a tenth than with these, mostly where few rows of A of very different lengths meet tiles
+// of long rows.
+struct OpCost { double entry, step, match, row, knn_row, visit, longer, wide, pair, knn_pair; double bias[2][2]; };
 constexpr OpCost op_cost(int op) {
     switch (op) {
-    case OP_DOT: return {11.8, 12.8, 0.59, 0, 300, 0.095, 4.7e-5, 0.040, 1.6};
-    case OP_L1: return {10.9, 11.4, 0.60, 0, 330, 0.114, 3.5e-5, 0.054, 1.35};
-    case OP_HAMM: return {19.0, 12.2, 0.50, 0, 340, 0.141, 4.0e-5, 0.055, 1.7};
-    case OP_CNT: return {17.2, 15.2, 0.52, 670, 0, 0.043, 2.6e-5, 0.019, 1.8};
-    case OP_CANB: return {13.1, 3.6, 0.75, 0, 180, 0.282, 3.6e-5, 0.063, 1.5};
-    case OP_KL: return {9.6, 7.9, 0.73, 0, 250, 0.324, 6.0e-5, 0.051, 1.2};
-    case OP_JS: return {12.6, 15.4, 0.72, 0, 640, 0.703, 5.5e-5, 0.069, 2.3};
-    case OP_CHEB: return {13.1, 14.0, 0.90, 0, 0, 0.26, 4.0e-5, 0.060, 1.6};
-    default: return {10.9, 13.1, 1.28, 140, 630, 0.45, 1.5e-4, 0.241, 3.5};
+    case OP_DOT: return {14, 21.1, 0.293, 47.4, 40.1, 0.0969, 5.33e-05, 0.0478, 1.76, 1.68, {{1.26, 1.35}, {1.1, 1.35}}};
+    case OP_L1: return {15.9, 10.4, 0.155, 0, 0, 0.111, 4.74e-05, 0.0738, 1.6, 1.72, {{0.9, 1.1}, {1.2, 1.25}}};
+    case OP_HAMM: return {21.6, 6.28, 0.284, 456, 1.93e+03, 0.142, 4.2e-05, 0.0965, 1.74, 2.57, {{0.8, 1.5}, {1, 1}}};
+    case OP_CNT: return {18.1, 6.37, 0.28, 616, 524, 0.0371, 4.12e-05, 0.0585, 1.86, 1.91, {{1, 1.5}, {1, 1}}};
+    case OP_CANB: return {12.5, 16.7, 0.18, 0, 400, 0.299, 2.36e-05, 0.0747, 1.46, 2.38, {{0.9, 1.1}, {1, 1.1}}};
+    case OP_KL: return {10.8, 25.3, 0.493, 0, 428, 0.345, 4.03e-05, 0.065, 1.97, 1.61, {{0.9, 1.35}, {0.9, 1}}};
+    case OP_JS: return {18, 20.5, 0.575, 137, 649, 0.755, 6.29e-06, 0.0663, 3.83, 4.57, {{0.8, 1.35}, {1, 1.5}}};
+    case OP_CHEB: return {13.7, 23.1, 0.352, 502, 0, 0.337, 0.000211, 0.069, 3.78, 3.24, {{0.9, 1}, {1, 1}}};
+    case OP_MINK_ANY: return {18.8, 42.8, 0.735, 690, 1.1e+03, 0.664, 0.000272, 0.234, 4.09, 7.42, {{1.1, 1.5}, {1, 1.2}}};
+    default: return {21.9, 30.5, 0.686, 585, 746, 0.555, 0.000169, 0.233, 3.49, 5.4, {{1, 1.5}, {0.9, 1}}};
     }
 }
-// (`columns`: that the lists are laid out for; `made`: an index brings the lists)
+// (`columns`: that the lists are laid out for; `of_a`: over these alone, after a copy; `made`: an index brings the lists)
 double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, const MatchShape &s, bool knn, bool made,
-                  bool skewed) {
+                  bool of_a) {
     const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz, tiles = (double)s.n_tiles;
     const OpCost c = op_cost(op);
     const MatchGrid g = match_grid(h->opt, s, op, A->n_rows, A->nnz, B->nnz, knn);
     const double rows = std::ceil(m / g.slices), runs = std::ceil(tiles / g.groups);          // of a workgroup
     double idle = rows * runs * (double)h->opt.n_cus / (m * tiles);
-    // (a third of the share for every product, as when the constants were fitted: with the marks of the kernels, 90 of 55,684 random calls
-    // take the other way, and 60 of these are 1.4 times as slow by it on the mean)
+    // (a third of the share for every product, as when the constants were fitted)
     if (nnz_a <= (double)std::max<int64_t>(256, g.share / 3) * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
     const double density = nnz_b / n / (double)columns, list = density * (double)s.tile_rows;  // entries, on the mean
-    const double met = skewed ? std::max(1.0, std::min(40.0, 0.07 / density)) : 1.0;
-    const double make = made ? 0.0 : 22.5e6 + 29.0 * nnz_b + 6.3 * tiles * (double)s.ptr_stride + 150.0 * n;
-    return (knn ? 53e6 : 27e6) + make + 2400.0 * m + 1.3 * m * n +
+    const double met = of_a ? 1.0 : std::max(1.0, std::min(40.0, 0.07 / density));
+    const double make = made ? 0.0 : 20.5e6 + 20.6 * nnz_b + 7.8 * tiles * (double)s.ptr_stride + 250.0 * n;
+    return c.bias[knn][of_a] * ((knn ? 58.5e6 : 24.9e6) + make + (of_a ? 35.5e6 + 0.85 * nnz_b : 0.0) + 6280.0 * m + 1.0 * m * n +
            idle * (nnz_a * tiles * (c.entry + c.step * std::min(1.0, list)) + c.match * met * nnz_a * density * n +
-                   (c.row + (knn ? c.knn_row : 0.0)) * m * tiles);
+                   (c.row + (knn ? c.knn_row : 0.0)) * m * tiles));
 }
 double staged_cost(const spd_csr *A, const spd_csr *B, int op, bool swapped, bool knn, bool made) {
     const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz;
     const OpCost c = op_cost(op);
     const double mean = swapped ? nnz_b / n : nnz_a / m;                                       // of the staged rows
     const double visit = c.visit + c.longer * std::min(mean, 2000.0) + (A->n_cols > 40000 ? c.wide : 0.0);
-    const double make = made ? 0.0 : 22e6 + 13.0 * nnz_b + 1900.0 * n;
+    const double make = made ? 0.0 : 18.3e6 + 15.0 * nnz_b + 2580.0 * n;
     // (Chebyshev ranks the entries of the rows that it stages: 34 x 969 rows of 1,550 2,777 us, by lists 554; 304 x 604 rows of 23 186 / 94;
     // 2,026 x 7,507 ratings 11,152 / 703; 3,148 x 4,764 rows of 1,790 25,963 / 3,002)
-    return (knn ? 58e6 : 31e6) + make + 5000.0 * m + 22.0 * nnz_a + (op == OP_CHEB ? 2e6 : 35000.0) * mean + visit * (swapped ? n * nnz_a : m * nnz_b) +
-           (c.pair + (knn ? 0.5 : 0.0)) * m * n;
+    return (knn ? 70.6e6 : 46.1e6) + make + 9830.0 * m + 21.8 * nnz_a + (op == OP_CHEB ? 552000.0 : 35800.0) * mean + visit * (swapped ? n * nnz_a : m * nnz_b) +
+           (knn ? c.knn_pair : c.pair) * m * n;
 }
 // `swapped`: the staged scan would exchange the operands' roles.
 bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn,
@@ -784,11 +785,10 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     if (!match_launches_fit(s, op, A->n_rows, A->nnz, B->n_rows, false)) return false;
     if (h->match_lists == 2) return true;
     if (!match_suits(h, B, op, s)) return false;
-    // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.28; 1,024 x 300,000 of 230, cosine
-    // 11.4 / 5.4; 4,096 x 65,536 of 1,820, L1 87 / 25, Jensen-Shannon 349 / 37; with lists as they were when the constants were fitted, 593 x 12,826 of 1,850, KL, k-NN, 5.5 / 1.7; 1,000 x
-    // 10,000 of 1,360 and 20, L1 0.14 / 0.70; set metrics: 2,435 x 6,447 ratings, Dice 0.62 / 0.28, 1,187 x 6,303 rows of 214,
-    // Russell-Rao 0.34 / 0.39, 3,081 x 30,310 of 400 in Zipf columns, Jaccard 2.5 / 7.0.
-    return lists_cost(h, A, B, A->n_cols, op, s, knn, with_index, true) <= staged_cost(A, B, op, swapped, knn, with_index);
+    // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.26; 1,024 x 300,000 of 230, cosine
+    // 11.4 / 5.2; 4,096 x 65,536 of 1,820, L1 87 / 23.6, Jensen-Shannon 349 / 35; 238 x 6,574 of 95, Canberra, with an index 0.21 / 0.026; 1,000 x
+    // 10,000 of 1,360 and 20, L1 0.14 / 0.70; set metrics: 3,247 x 7,668 counts, Jaccard 4.6 / 2.1, 72 x 15,967 rows of 218, k-NN 0.22 / 0.41.
+    return lists_cost(h, A, B, A->n_cols, op, s, knn, with_index, false) <= staged_cost(A, B, op, swapped, knn, with_index);
 }
 // The columns that lists over A's columns alone are laid out for (how many A stores, the host does not know).
 int64_t columns_of(const spd_csr *A) { return std::min(A->n_cols, std::max<int64_t>(A->nnz, 1)); }
@@ -803,25 +803,27 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     if (!match_launches_fit(s, op, A->n_rows, A->nnz, B->n_rows, true)) return false;
     if (h->match_lists == 3) return true;
     if (h->match_lists != 1 || !scan_knobs_untouched(h) || !match_bounds_fit(s, B->nnz, 4)) return false;
-    // (where the lists over all columns have room for their bounds, the copy is not worth its time)
-    MatchShape all;
-    if (match_possible(h, B, op, all) && match_bounds_fit(all, B->nnz)) return false;
     // Both sides measured, staged / lists over A's columns in ms, k-NN: 4,096 x 500,000 sets over 2^20 columns, Jaccard 30.6 /
-    // 7.3; with lists as they were when the constants were fitted, 3,331 x 9,539 of them 0.93 / 0.67, 46 x 56,760, Russell-Rao 0.73 / 0.30; 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.3 /
-    // 2.0, 335 x 16,402 of them, L1 0.10 / 0.12; 99 x 386,927 of them with an index, which holds nothing of these lists, cosine 0.19 /
-    // 0.26, 516 x 285,865 sets with one, Dice 4.3 / 2.3.  (The estimate of these lists is the higher, as columns that A does not
-    // store cost them nothing.)
-    return lists_cost(h, A, B, columns_of(A), op, s, knn, false, false) <= 1.1 * staged_cost(A, B, op, swapped, knn, with_index);
+    // 6.4, 371 x 33,325 of them, Dice 0.81 / 0.33 (over all columns 0.48), 59 x 15,538 0.51 / 0.24 (0.31); 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.3 /
+    // 2.0.
+    return lists_cost(h, A, B, columns_of(A), op, s, knn, false, true) <= staged_cost(A, B, op, swapped, knn, with_index);
 }
+constexpr int64_t kMatchFewColumns = 1 << 15;
 // The way a call is computed: 0 the staged scan, 1 lists over all columns, 2 lists over the columns that A stores; and how.
 struct MatchWay { int way = 0; int64_t columns = 0; MatchShape s{}; MatchGrid g; MatchScratch L{}; };
 MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, int knn_k,
                    bool with_index, bool index_has_lists) {
     MatchWay w;
     const bool knn = knn_k > 0;
-    if (h->match_lists != 3 && match_wanted(h, A, B, op, semiring, swapped, knn, with_index) && (!with_index || index_has_lists)) w.way = 1;
-    else if (columns_wanted(h, A, B, op, semiring, swapped, knn, with_index)) w.way = 2;
+    const bool all = h->match_lists != 3 && match_wanted(h, A, B, op, semiring, swapped, knn, with_index) && (!with_index || index_has_lists);
+    // (few columns have room for their bounds: where the lists over all of them do not pay, neither does a copy)
+    const bool of_a = h->match_lists != 2 && (all || h->match_lists == 3 || A->n_cols > kMatchFewColumns) && columns_wanted(h, A, B, op, semiring, swapped, knn, with_index);
+    w.way = all ? 1 : (of_a ? 2 : 0);
     if (w.way == 0) return w;
+    if (all && of_a) {                   // (the copy may cost less than the bounds and the entries of columns that A does not store)
+        const MatchShape over_all = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz), over_a = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
+        if (lists_cost(h, A, B, columns_of(A), op, over_a, knn, false, true) < lists_cost(h, A, B, A->n_cols, op, over_all, knn, with_index, false)) w.way = 2;
+    }
     w.columns = w.way == 2 ? columns_of(A) : A->n_cols;
     w.s = match_shape(h->opt.lds_budget, op, B->n_rows, w.columns, B->nnz);
     w.g = match_grid(h->opt, w.s, op, A->n_rows, A->nnz, B->nnz, knn);
