@@ -271,7 +271,7 @@ template <int R>
 __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                         const float *__restrict__ values, int64_t n_rows, int64_t nnz,
                                                                         uint32_t most_cols, MatchB b, uint32_t blocks_per_wg, uint32_t wgs, int unit,
-                                                                        int transform, bool with_values, const RowsVerdict seen) {
+                                                                        int transform, bool with_values, bool positive, const RowsVerdict seen) {
     if (rows_malformed(seen)) return;
     constexpr int nw = kBuildThreads / kWave, K = build_held(R);
     extern __shared__ __align__(16) unsigned char s_raw[];
@@ -605,8 +605,9 @@ __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const
             __threadfence_block();
             __syncthreads();
         }
-        auto cell_of = [&](uint32_t row, uint32_t rank_in_row, float t) {          // (a stored zero is absent: it goes to the spare row behind the tile's)
-            return (uint16_t)((t != 0.0f ? row : (uint32_t)T) * (uint32_t)unit + (rank_in_row << kRankShift));
+        // (a stored zero is absent: it goes to the spare row behind the tile's, and for the products of positive entries what is not positive)
+        auto cell_of = [&](uint32_t row, uint32_t rank_in_row, float t) {
+            return (uint16_t)(((positive ? t > 0.0f : t != 0.0f) ? row : (uint32_t)T) * (uint32_t)unit + (rank_in_row << kRankShift));
         };
         if (from_lanes) {
             if (transform != TR_ID) {
@@ -822,7 +823,7 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
         hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(kern, dim3((unsigned)match_build_grid(s)), dim3(kBuildThreads), s.build_lds_bytes, st, indptr, indices, values, n_rows,
-                           nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op != OP_CNT, seen);
+                           nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op != OP_CNT, op == OP_JS || op == OP_KL, seen);
         return hipGetLastError();
     };
     switch (build_rows(s.tile_rows)) {

@@ -120,21 +120,18 @@ template <int OP> struct Sums {
 };
 
 // One column both rows store: the products of Op<OP>, without the tests for absent entries that the
-// staged scan needs (neither lists nor rows hold zeros).  Returns whether the column counts; where it does not, x
-// is not to be used.  match_walks: whether any column of an entry of A can count.
+// staged scan needs (neither lists nor rows hold zeros, nor for Jensen-Shannon and KL what is not positive).  match_walks: whether any column of an entry of A can count.
 template <int OP> __device__ __forceinline__ bool match_walks(float a) { return OP == OP_JS || OP == OP_KL ? a > 0.0f : a != 0.0f; }
-template <int OP> __device__ __forceinline__ bool match_visit(typename Op<OP>::Acc &x, float a, float b, const OpParams &q) {
+template <int OP> __device__ __forceinline__ void match_visit(typename Op<OP>::Acc &x, float a, float b, const OpParams &q) {
     if constexpr (OP == OP_CNT) {
         x.c = 1;
     } else if constexpr (OP == OP_HAMM) {
         x.c = (a != b) ? -1 : -2;
     } else if constexpr (OP == OP_JS) {
         x.v = (double)Op<OP>::term(a, b) - ((double)a + (double)b);
-        return b > 0.0f;
     } else if constexpr (OP == OP_KL) {
         x.v = (double)(a * fast_log2(divide(a, divisor_of(b))));
         x.hits = 1;
-        return b > 0.0f;
     } else if constexpr (OP == OP_MINK) {
         Op<OP>::init(x);
         for_degree(q.p, [&](auto tag) { Op<OP>::template visit_as<decltype(tag)::value>(x, a, Op<OP>::prep(b, q), q); });
@@ -142,7 +139,6 @@ template <int OP> __device__ __forceinline__ bool match_visit(typename Op<OP>::A
         Op<OP>::init(x);
         Op<OP>::visit(x, a, Op<OP>::prep(b, q), q);
     }
-    return true;
 }
 
 // A row of A as the sums in fixed point take it (match_fixed): a term x of the row stands as `offset` + `factor` * x, in [2, 4)
@@ -480,23 +476,22 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
         auto add_one = [&](const Entry &from, uint32_t left, float av, uint32_t met) {
             // (everything but the LDS add itself is done for all lanes: a branch around it costs more)
             Acc t;
-            bool counts = true;
             uint32_t at;
             if constexpr (OP == OP_CHEB) {
                 const uint32_t cell = __builtin_bit_cast(uint16_t, from.cell), rank = cell >> kRankShift;
                 const float d = fabsf(av - from.v);
                 t = Ranked{__float_as_uint(d), met, rank < (uint32_t)kRanks ? 1u << (rank & 31u) : 0u};
                 at = (cell & ((1u << kRankShift) - 1u)) * 4u;
-                counts = d == d;                                  // (as a maximum passes over what is not a number)
+                const bool counts = d == d;                       // (as a maximum passes over what is not a number)
                 pin(t, at);
                 if (lane4 < left && counts) S::add(to, plane, at, t);
                 return;
             }
             if constexpr (FIX) t = fixed_visit<OP>(av, from.v, scale);
-            else if constexpr (OP != OP_CHEB) counts = match_visit<OP>(t, av, from.v, args.q);
+            else if constexpr (OP != OP_CHEB) match_visit<OP>(t, av, from.v, args.q);
             if constexpr (S::kOne) at = plus_half(from.cell, to); else at = __builtin_bit_cast(uint16_t, from.cell);
             pin(t, at);
-            if (lane4 < left && counts) {
+            if (lane4 < left) {
                 if constexpr (S::kOne) S::add(0u, plane, at, t); else S::add(to, plane, at, t);
             }
         };
@@ -893,6 +888,21 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                         i[u] = i0 + u * kWave + lane;
                         d[u] = *lds_at<float>(strip_at + (uint32_t)min(i[u], tile_n - 1) * S::kUnit);
                         d[u] = i[u] < tile_n ? d[u] : __builtin_nanf("");
+                    }
+                } else if (S::kOne && few_only && few.total <= 4) {
+                    // One step of entries met the row, as mostly where they are few: one lane of those that met a sum takes it and leaves its
+                    // place clear.
+                    if constexpr (S::kOne) {
+                        Acc met[1] = {zero};
+                        if ((uint32_t)(lane & 15) * 4u < few.left[0]) met[0] = S::take(strip_at + few.cell[0]);
+                        i[0] = S::is_zero(met[0]) ? tile_n : (int)(few.cell[0] / S::kUnit);
+                        const int64_t j = j0 + min(i[0], tile_n - 1);
+                        const RowNorms nb[1] = {{args.norms_b[j], BOTH ? args.b.norms[args.n + j] : 0.0}};
+                        float formed[1] = {0.0f};
+                        distances(formed, met, nb);
+                        d[0] = i[0] < tile_n ? formed[0] : __builtin_nanf("");
+#pragma unroll
+                        for (int u = 1; u < F; ++u) { d[u] = __builtin_nanf(""); i[u] = tile_n; }
                     }
                 } else {
                     Acc c[F];
