@@ -31,95 +31,183 @@ hipError_t launch_match_look_at_rows(hipStream_t st, const int64_t *a, int64_t m
 __device__ __forceinline__ bool rows_malformed(const RowsVerdict &seen) { return seen.word && *seen.word == seen.malformed; }
 
 // ------------------------------------------------------------------------------------
-// row norms: G lanes to the row, four entries of a lane in flight; with up to 64 lanes to the row, rows of more than 64
-// entries a lane wait for the whole workgroup, one after the other (500,000 rows of 1 to 50,000 entries: 332 us while a
-// wavefront went through the longest alone, 260 now)
+// row norms.  The sums of a row: entries from `from` on, `stride` apart, U of a lane in flight.
 // ------------------------------------------------------------------------------------
-template <int G, bool SCALES>
-__global__ void __launch_bounds__(256) spd_match_norms_kernel(const int64_t *__restrict__ indptr, const float *__restrict__ values,
-                                                              int64_t n_rows, int64_t nnz, int metric, int transform, int norm,
-                                                              float p, double k, const RowsVerdict seen, double *__restrict__ norms,
-                                                              int16_t *__restrict__ scales) {
-    if (rows_malformed(seen)) return;
-    constexpr int kRows = 256 / G;
-    constexpr int64_t kLong = G < 256 ? 64 * G : INT64_MAX;
+struct NormSums { double s0, s1; float most, least; };
+struct NormArgs {
+    const int64_t *indptr;
+    const float *values;
+    int64_t n_rows, nnz;
+    int metric, transform, norm;
+    float p;
+    double k;
+    RowsVerdict seen;
+    double *norms;
+    int16_t *scales;
+};
+template <bool SCALES> __device__ __forceinline__ void norm_add(const NormArgs &a, float v, NormSums &x) {          // (v = 0 adds nothing)
+    const float t = transform_value(a.transform, v);
+    norm_accumulate(a.norm, t, a.p, x.s0, x.s1);
+    if constexpr (SCALES) {
+        x.most = fmaxf(x.most, fabsf(t));
+        x.least = t != 0.0f ? fminf(x.least, fabsf(t)) : x.least;
+    }
+}
+template <bool SCALES, int U> __device__ __forceinline__ void norm_sums(const NormArgs &a, int64_t from, int64_t end, int stride, NormSums &x) {
+    for (int64_t e = from; e < end; e += U * stride) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = e + u * stride < end ? a.values[e + u * stride] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) norm_add<SCALES>(a, v[u], x);
+    }
+}
+// Over the lanes of a wavefront, to its last one.
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_add(double v) {
+    return v + __hiloint2double(dpp_or_zero<CTRL, ROWS>(__double2hiint(v)), dpp_or_zero<CTRL, ROWS>(__double2loint(v)));
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+    v = dpp_add<0x111, 0xf>(v);                             // row_shr:1, 2, 4, 8; row_bcast:15, row_bcast:31
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);
+    return dpp_add<0x143, 0xc>(v);
+}
+template <bool SCALES> __device__ __forceinline__ void norm_reduce_last(int norm, NormSums &x) {
+    x.s0 = wave_sum_last(x.s0);
+    if (norm == NORM_SUM_SUMSQ || norm == NORM_SUM_POW || norm >= NORM_SEMI) x.s1 = wave_sum_last(x.s1);
+    if constexpr (SCALES) {                                  // (magnitudes: their bits are in their order)
+        x.most = __int_as_float(wave_scan_max(__float_as_int(x.most)));
+        x.least = __int_as_float(INT32_MAX - wave_scan_max(INT32_MAX - __float_as_int(x.least)));
+    }
+}
+template <bool SCALES> __device__ __forceinline__ void norm_write(const NormArgs &a, int64_t r, const NormSums &x) {
+    double d0, d1;
+    norm_derive(a.metric, a.k, x.s0, x.s1, d0, d1);
+    if constexpr (SCALES) a.scales[r] = (int16_t)(a.metric == MT_CANBERRA ? match_wild(x.least, x.most) : match_scale(x.most, x.s0));
+    a.norms[r] = d0;
+    a.norms[a.n_rows + r] = d1;
+}
+// A row by all 256 lanes of a workgroup: its wavefronts' sums in a fixed order.  (All of them come here, and wait for one another.)
+template <bool SCALES> __device__ __forceinline__ void norm_by_all(const NormArgs &a, int64_t r, NormSums (&s_part)[256 / kWave]) {
+    const int tid = (int)threadIdx.x;
+    const int64_t begin = clamp_i64(a.indptr[r], 0, a.nnz), end = clamp_i64(a.indptr[r + 1], begin, a.nnz);
+    NormSums x{0.0, 0.0, 0.0f, 1.0f};
+    norm_sums<SCALES, 8>(a, begin + tid, end, 256, x);
+    norm_reduce_last<SCALES>(a.norm, x);
+    if (tid % kWave == kWave - 1) s_part[tid / kWave] = x;
+    __syncthreads();
+    if (tid == 0) {
+        NormSums all{0.0, 0.0, 0.0f, 1.0f};
+#pragma unroll
+        for (int w = 0; w < 256 / kWave; ++w) {
+            all.s0 += s_part[w].s0;
+            all.s1 += s_part[w].s1;
+            all.most = fmaxf(all.most, s_part[w].most);
+            all.least = fminf(all.least, s_part[w].least);
+        }
+        norm_write<SCALES>(a, r, all);
+    }
+    __syncthreads();
+}
+// A workgroup to the row.
+template <bool SCALES> __global__ void __launch_bounds__(256) spd_match_norms_kernel(const NormArgs a) {
+    if (rows_malformed(a.seen)) return;
+    __shared__ NormSums s_part[256 / kWave];
+    norm_by_all<SCALES>(a, blockIdx.x, s_part);
+}
+// A wavefront to `per_wave` rows that follow one another: the next one's entries are on their way while one is summed, and the numbers
+// that distances read are derived for all of them together, a row to a lane (a wavefront each, with sums through LDS and square roots for one lane of
+// it, 300,000 rows of 230 entries: 157 us, 109 now).  Rows of more than 4,096 entries wait for the whole workgroup, one after
+// the other (500,000 rows of 1 to 50,000 entries: 332 us while a wavefront went through the longest alone, 250, 219 now).
+constexpr int kNormRows = 8;
+template <bool SCALES> __global__ void __launch_bounds__(256) spd_match_norms_rows_kernel(const NormArgs a, int per_wave) {
+    if (rows_malformed(a.seen)) return;
+    constexpr int kLong = 64 * kWave;
+    __shared__ NormSums s_part[256 / kWave];
+    __shared__ int s_long[256 / kWave * kNormRows], s_longs;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
+    const int64_t block_first = (int64_t)blockIdx.x * (256 / kWave) * per_wave, first = block_first + (int64_t)wave * per_wave;
+    const int rows = (int)max((int64_t)0, min((int64_t)per_wave, a.n_rows - first));
+    if (tid == 0) s_longs = 0;
+    __syncthreads();
+    // lane i: where row i begins; the last one's end with the lane behind
+    const int64_t begins = lane <= rows && first <= a.n_rows ? clamp_i64(a.indptr[first + min(lane, rows)], 0, a.nnz) : 0;
+    auto bound = [&](int i) {
+        return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(begins >> 32), i) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)begins, i));
+    };
+    auto fetch = [&](int i, int64_t &begin, int64_t &end, float (&v)[4]) {
+        begin = bound(i);
+        end = max(begin, bound(i + 1));
+        if (end - begin > kLong) {
+            if (lane == 0) s_long[atomicAdd(&s_longs, 1)] = wave * per_wave + i;
+            end = begin;
+        }
+        const int64_t e = begin + lane;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = e + u * kWave < end ? a.values[e + u * kWave] : 0.0f;
+    };
+    NormSums mine{0.0, 0.0, 0.0f, 1.0f};
+    float cur[4], ahead[4];
+    int64_t begin = 0, end = 0;
+    if (rows > 0) fetch(0, begin, end, cur);
+    for (int i = 0; i < rows; ++i) {
+        int64_t begin1 = 0, end1 = 0;
+        if (i + 1 < rows) fetch(i + 1, begin1, end1, ahead);
+        NormSums x{0.0, 0.0, 0.0f, 1.0f};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) norm_add<SCALES>(a, cur[u], x);
+        norm_sums<SCALES, 4>(a, begin + 4 * kWave + lane, end, kWave, x);
+        norm_reduce_last<SCALES>(a.norm, x);
+        auto last = [&](double v) { return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63), __builtin_amdgcn_readlane(__double2loint(v), 63)); };
+        auto last_of = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)); };
+        // (the last lane's sums are read by all lanes: within the branch they would not be formed there)
+        const NormSums row{last(x.s0), last(x.s1), last_of(x.most), last_of(x.least)};
+        if (lane == i) mine = row;
+        begin = begin1;
+        end = end1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) cur[u] = ahead[u];
+    }
+    const int64_t behind = clamp_i64(__shfl_down((long long)begins, 1), begins, INT64_MAX);
+    if (lane < rows && behind - begins <= kLong) norm_write<SCALES>(a, first + lane, mine);
+    __syncthreads();
+    const int longs = s_longs;
+    for (int at = 0; at < longs; ++at) norm_by_all<SCALES>(a, block_first + s_long[at], s_part);
+}
+// Four lanes to a row of few entries; rows of more than 256 wait for the whole workgroup.
+template <bool SCALES> __global__ void __launch_bounds__(256) spd_match_norms_short_kernel(const NormArgs a) {
+    if (rows_malformed(a.seen)) return;
+    constexpr int G = 4, kRows = 256 / G, kLong = 64 * G;
+    __shared__ NormSums s_part[256 / kWave];
     __shared__ int s_long[kRows], s_longs;
-    __shared__ double s_sum[256 / kWave][2];
-    __shared__ float s_most[256 / kWave], s_least[256 / kWave];
     const int tid = (int)threadIdx.x, sub = tid % G;
     const int64_t row0 = (int64_t)blockIdx.x * kRows, row = row0 + tid / G;
-    auto sums = [&](int64_t from, int64_t end, int stride, double &s0, double &s1, float &most, float &least) {
-        for (int64_t e = from; e < end; e += 4 * stride) {
-            float v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = e + u * stride < end ? values[e + u * stride] : 0.0f;
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (e + u * stride < end) {
-                    const float t = transform_value(transform, v[u]);
-                    norm_accumulate(norm, t, p, s0, s1);
-                    if constexpr (SCALES) {
-                        most = fmaxf(most, fabsf(t));
-                        least = t != 0.0f ? fminf(least, fabsf(t)) : least;
-                    }
-                }
-        }
-#pragma unroll
-        for (int d = kWave / 2; d >= 1; d >>= 1)
-            if (d < stride) {
-                s0 += __shfl_xor(s0, d);
-                s1 += __shfl_xor(s1, d);
-                if constexpr (SCALES) {
-                    most = fmaxf(most, __shfl_xor(most, d));
-                    least = fminf(least, __shfl_xor(least, d));
-                }
-            }
-    };
-    auto write = [&](int64_t r, double s0, double s1, float most, float least) {
-        double d0, d1;
-        norm_derive(metric, k, s0, s1, d0, d1);
-        if constexpr (SCALES) scales[r] = (int16_t)(metric == MT_CANBERRA ? match_wild(least, most) : match_scale(most, s0));
-        norms[r] = d0;
-        norms[n_rows + r] = d1;
-    };
-    // a row by all 256 lanes: its wavefronts' sums in a fixed order
-    auto by_all = [&](int64_t r, int64_t begin, int64_t end) {
-        double s0 = 0.0, s1 = 0.0;
-        float most = 0.0f, least = 1.0f;
-        sums(begin + tid, end, 256, s0, s1, most, least);
-        if (tid % kWave == 0) { s_sum[tid / kWave][0] = s0; s_sum[tid / kWave][1] = s1; s_most[tid / kWave] = most; s_least[tid / kWave] = least; }
-        __syncthreads();
-        if (tid == 0) {
-            s0 = 0.0; s1 = 0.0;
-#pragma unroll
-            for (int w = 0; w < 256 / kWave; ++w) { s0 += s_sum[w][0]; s1 += s_sum[w][1]; most = fmaxf(most, s_most[w]); least = fminf(least, s_least[w]); }
-            write(r, s0, s1, most, least);
-        }
-    };
     int64_t begin = 0, end = 0;
-    if (row < n_rows) {
-        begin = clamp_i64(indptr[row], 0, nnz);
-        end = clamp_i64(indptr[row + 1], begin, nnz);
+    if (row < a.n_rows) {
+        begin = clamp_i64(a.indptr[row], 0, a.nnz);
+        end = clamp_i64(a.indptr[row + 1], begin, a.nnz);
     }
-    if constexpr (G == 256) {
-        by_all(row, begin, end);                             // (a row to the workgroup: there is one)
-    } else {
-        if (tid == 0) s_longs = 0;
-        __syncthreads();
-        const bool is_long = end - begin > kLong;
-        if (is_long && sub == 0) s_long[atomicAdd(&s_longs, 1)] = tid / G;
-        double s0 = 0.0, s1 = 0.0;
-        float most = 0.0f, least = 1.0f;
-        sums(begin + sub, is_long ? begin : end, G, s0, s1, most, least);
-        if (row < n_rows && !is_long && sub == 0) write(row, s0, s1, most, least);
-        __syncthreads();
-        const int longs = s_longs;
-        for (int at = 0; at < longs; ++at) {
-            const int64_t r = row0 + s_long[at], from = clamp_i64(indptr[r], 0, nnz);
-            by_all(r, from, clamp_i64(indptr[r + 1], from, nnz));
-            __syncthreads();
+    if (tid == 0) s_longs = 0;
+    __syncthreads();
+    const bool is_long = end - begin > kLong;
+    if (is_long && sub == 0) s_long[atomicAdd(&s_longs, 1)] = tid / G;
+    NormSums x{0.0, 0.0, 0.0f, 1.0f};
+    norm_sums<SCALES, 4>(a, begin + sub, is_long ? begin : end, G, x);
+#pragma unroll
+    for (int d = G / 2; d >= 1; d >>= 1) {
+        x.s0 += __shfl_xor(x.s0, d);
+        x.s1 += __shfl_xor(x.s1, d);
+        if constexpr (SCALES) {
+            x.most = fmaxf(x.most, __shfl_xor(x.most, d));
+            x.least = fminf(x.least, __shfl_xor(x.least, d));
         }
     }
+    if (row < a.n_rows && !is_long && sub == 0) norm_write<SCALES>(a, row, x);
+    __syncthreads();
+    const int longs = s_longs;
+    for (int at = 0; at < longs; ++at) norm_by_all<SCALES>(a, row0 + s_long[at], s_part);
 }
 
 // ------------------------------------------------------------------------------------
@@ -309,12 +397,11 @@ __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const
     const uint32_t block_first = (uint32_t)part * blocks_per_wg;
     const uint32_t block_last = min(block_first + blocks_per_wg, blocks);
     if (block_first >= block_last) return;
-    // Rows tid, tid + kBuildThreads, ...: where the block's entries begin, where the row ends, and entries to a column.
+    // Rows tid, tid + kBuildThreads, ...: where the block's entries begin, and where the row ends.
     uint32_t cur[R], row_end[R];
-    float per_col[R];
-    // The first entry from `at` on whose column is not below `target`, of all the lane's rows at once: by the entries round where it should lie, then where these
+    // The first entry from `at` on, where column `from_col` begins, whose column is not below `target`, of all the lane's rows at once: by the entries round where it should lie, then where these
     // say it should, then by halves.
-    auto find = [&](uint32_t (&at)[R], uint32_t target, float ahead) {
+    auto find = [&](uint32_t (&at)[R], uint32_t target, uint32_t from_col) {
         constexpr int N = kBuildProbe;
         struct __attribute__((packed, aligned(4))) Probe { uint32_t c[N]; };
         if (nnz < N) {
@@ -326,9 +413,12 @@ __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const
         const int last = (int)min(nnz - N - row_first, (int64_t)INT32_MAX);          // (may lie before the tile)
         uint32_t hi[R];
         int guess[R];
+        float per_col[R];                          // entries to a column
+        const float share = 1.0f / (float)(cols - from_col), ahead = (float)(target - from_col);
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             hi[j] = row_end[j];
+            per_col[j] = (float)(hi[j] - at[j]) * share;
             guess[j] = (int)at[j] + (int)(per_col[j] * ahead);
         }
         for (int round = 0;; ++round) {
@@ -375,9 +465,8 @@ __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const
                 row_end[j] = max(begin[j], (uint32_t)(clamp_i64(indptr[j0 + r + 1], row_first, nnz) - row_first));
             }
             cur[j] = begin[j];
-            per_col[j] = (float)(row_end[j] - begin[j]) / (float)cols;
         }
-        if (block_first > 0u) find(cur, c_first, (float)c_first);
+        if (block_first > 0u) find(cur, c_first, 0u);
 #pragma unroll
         for (int j = 0; j < R; ++j) mine += cur[j] - begin[j];
 #pragma unroll
@@ -401,7 +490,7 @@ __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const
         uint32_t next[R], off[R], entries = 0u;
 #pragma unroll
         for (int j = 0; j < R; ++j) next[j] = block + 1u < blocks ? cur[j] : row_end[j];
-        if (block + 1u < blocks) find(next, c0 + block_cols, (float)block_cols);
+        if (block + 1u < blocks) find(next, c0 + block_cols, c0);
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             if (j * kBuildThreads >= rows) continue;
@@ -454,10 +543,13 @@ __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const
         // (16 bits each).
         uint32_t hold[K], hold_before[K / 2];
         float hold_value[K];
+        auto hold_nothing = [&]() {
 #pragma unroll
-        for (int k = 0; k < K; ++k) { hold[k] = 0xFFFFFFFFu; hold_value[k] = 0.0f; hold_before[k / 2] = 0u; }
+            for (int k = 0; k < K; ++k) { hold[k] = 0xFFFFFFFFu; hold_value[k] = 0.0f; hold_before[k / 2] = 0u; }
+        };
         if (once) {
             mark(0u, entries);
+            hold_nothing();
             constexpr int H = R == 5 ? K / 2 : K;               // entries whose loads are in flight together
 #pragma unroll
             for (int h = 0; h < K; h += H) {
@@ -509,6 +601,7 @@ __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const
                 }
                 __syncthreads();
             }
+            hold_nothing();                                     // (behind the loop: what it holds needs no registers there)
         }
         __syncthreads();
         // Which columns are dense: the first of the block that reach the mark, in column order (so that the same columns are dense in every
@@ -523,11 +616,11 @@ __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const
                 each(i + 3u, v.w);
             }
         };
-        // (as many as the block's share of their room holds, and half of the room for gaps: where few columns have most of the entries, they lie
-        // in few blocks)
+        // (as many as the block's share of their room holds; and half of its room for gaps, in a block that is gone through twice: where few columns have
+        // most of the entries, they may lie in few blocks)
         const uint32_t whole = (uint32_t)T, dense_mark = (uint32_t)shape.dense_from, room_of_gaps = (uint32_t)(shape.room_of(before + entries) - shape.room_of(before)) - entries;
         const uint32_t most_dense = min(kBuildDense, (uint32_t)(shape.dense_before((int32_t)block + 1) - shape.dense_before((int32_t)block)) +
-                                                         (shape.dense_room() > 0 ? room_of_gaps / 2u / (uint32_t)shape.dense_room() : 0u));
+                                                         (!once && shape.dense_room() > 0 ? room_of_gaps / 2u / (uint32_t)shape.dense_room() : 0u));
         uint32_t rank = 0u, n_dense = 0u;                          // columns that reach the mark before the thread's, and all of them
         {
             uint32_t marked = 0u;
@@ -701,17 +794,21 @@ int match_norm_lanes(int64_t n_rows, int64_t nnz) {
 hipError_t launch_match_norms(hipStream_t st, const int64_t *indptr, const float *values, int64_t n_rows, int64_t nnz,
                               int metric, int transform, int norm, float p, double k, const RowsVerdict &seen, double *norms, int16_t *scales) {
     if (n_rows <= 0) return hipSuccess;
-    auto go = [&](auto g) {
-        constexpr int G = decltype(g)::value;
-        const int per = 256 / G;
-        hipLaunchKernelGGL((scales ? spd_match_norms_kernel<G, true> : spd_match_norms_kernel<G, false>), dim3((unsigned)((n_rows + per - 1) / per)),
-                           dim3(256), 0, st, indptr, values, n_rows, nnz, metric, transform, norm, p, k, seen, norms, scales);
+    const NormArgs a{indptr, values, n_rows, nnz, metric, transform, norm, p, k, seen, norms, scales};
+    auto go = [&](auto with_scales) {
+        constexpr bool S = decltype(with_scales)::value;
+        switch (match_norm_lanes(n_rows, nnz)) {
+        case 256: hipLaunchKernelGGL(spd_match_norms_kernel<S>, dim3((unsigned)n_rows), dim3(256), 0, st, a); break;
+        case 64: {
+            // (as many rows as leave every place of the chip for a wavefront taken; one where a row has more entries than are loaded ahead)
+            const int per_wave = nnz > 4 * kWave * n_rows ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(kNormRows, n_rows / 8192));
+            hipLaunchKernelGGL(spd_match_norms_rows_kernel<S>, dim3((unsigned)((n_rows + 4 * per_wave - 1) / (4 * per_wave))), dim3(256), 0, st, a, per_wave);
+            break;
+        }
+        default: hipLaunchKernelGGL(spd_match_norms_short_kernel<S>, dim3((unsigned)((n_rows + 63) / 64)), dim3(256), 0, st, a); break;
+        }
     };
-    switch (match_norm_lanes(n_rows, nnz)) {
-    case 256: go(std::integral_constant<int, 256>{}); break;
-    case 64: go(std::integral_constant<int, 64>{}); break;
-    default: go(std::integral_constant<int, 4>{}); break;
-    }
+    if (scales) go(std::true_type{}); else go(std::false_type{});
     return hipGetLastError();
 }
 
