@@ -571,6 +571,9 @@ MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int op, int64_
     g.share = nnz_a * tiles / ((int64_t)g.slices * s.waves);
     const bool one_strip = match_any_order(op);
     g.shared_len = std::max<int64_t>(one_strip && !knn ? 512 : 256, g.share / (one_strip ? 6 : 3));
+    // (Where a workgroup has a (tile, row) for every wavefront, a strip for each of them is paid for by rows of twice the mean length at least.  (573 x 3,605 rows of 319, log-normal, us before and
+    // after: correlation 155 / 128, KL 137 / 116, Jensen-Shannon k-NN 226 / 197; 4,000 x 6,000 rows of 1,820, cosine, 4,621 / 4,047.)
+    if (!one_strip && (m / g.slices) * tiles >= s.waves) g.shared_len = std::max<int64_t>(g.shared_len, 2 * nnz_a / m);
     // Chebyshev: a row of A that is like many of B's costs its wavefront two microseconds a pair (spd_match_impl.h).  Where a wavefront to the row
     // leaves half of the compute units idle, rows of some length are all shared: 500 x 500 rows of 50 ones over one support 880 -> 152 us
     // (staged scan 271), 1,000 x 1,000 of 100 1,258 -> 639 (1,314), of 100 normal values 205 -> 136; 237 x 5,101 rows of 223 194 -> 145.
@@ -727,29 +730,30 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
 // and without); nine of ten estimates are within 0.5 to 1.5 of the times, because row pointers do not show how A's columns
 // meet B's, nor its longest row.  Columns are seldom uniform where they are many: over all columns the lists are taken to be met up to 40 times as
 // often as if they were, as far as the density leaves room for that (words, Zipf columns, rows of 230 over 102,660: some 40 times).
-// The estimates of lists are weighed by what chose best between the ways (`bias`: pairwise and k-NN, over all columns and over A's).  Chosen so, the
-// calls take 5 % more than by the best way on the mean, 17 % by the constants before (fitted with lists that took up to a third longer), which
-// sent most calls near the line to the scan: 371 x 33,325 sets, Dice, k-NN, 810 us by it and 326 by lists, 3,247 x 7,668 counts, Jaccard, 4,622 and
-// 2,050, 86 x 8,953 ratings 344 and 173.  One call in 25 is slower by a tenth than with these, mostly where few rows of A of very different lengths meet tiles
-// of long rows.
+// The estimates of lists are weighed by what chose best between the ways (`bias`: pairwise and k-NN, over all columns and over A's).  Constants from
+// lists that took up to a third longer sent most calls near the line to the scan: 371 x 33,325 sets, Dice, k-NN, 810 us by it and 326 by
+// lists, 3,247 x 7,668 counts, Jaccard, 4,622 and 2,050, 86 x 8,953 ratings 344 and 173.  Of the working range (without an index, 650 random
+// calls) calls took 12 % more than by the best way on the mean, and take 3 to 4 % more now; what is chosen wrongly is mostly few rows of A against words by set
+// metrics, whose Zipf columns are met more often than in any other data.
 struct OpCost { double entry, step, match, row, knn_row, visit, longer, wide, pair, knn_pair; double bias[2][2]; };
 constexpr OpCost op_cost(int op) {
     switch (op) {
-    case OP_DOT: return {14, 21.1, 0.293, 47.4, 40.1, 0.0969, 5.33e-05, 0.0478, 1.76, 1.68, {{1.26, 1.35}, {1.1, 1.35}}};
-    case OP_L1: return {15.9, 10.4, 0.155, 0, 0, 0.111, 4.74e-05, 0.0738, 1.6, 1.72, {{0.9, 1.1}, {1.2, 1.25}}};
-    case OP_HAMM: return {21.6, 6.28, 0.284, 456, 1.93e+03, 0.142, 4.2e-05, 0.0965, 1.74, 2.57, {{0.8, 1.5}, {1, 1}}};
-    case OP_CNT: return {18.1, 6.37, 0.28, 616, 524, 0.0371, 4.12e-05, 0.0585, 1.86, 1.91, {{1, 1.5}, {1, 1}}};
-    case OP_CANB: return {12.5, 16.7, 0.18, 0, 400, 0.299, 2.36e-05, 0.0747, 1.46, 2.38, {{0.9, 1.1}, {1, 1.1}}};
-    case OP_KL: return {10.8, 25.3, 0.493, 0, 428, 0.345, 4.03e-05, 0.065, 1.97, 1.61, {{0.9, 1.35}, {0.9, 1}}};
-    case OP_JS: return {18, 20.5, 0.575, 137, 649, 0.755, 6.29e-06, 0.0663, 3.83, 4.57, {{0.8, 1.35}, {1, 1.5}}};
+    case OP_DOT: return {14, 21.1, 0.293, 47.4, 40.1, 0.0969, 5.33e-05, 0.0478, 1.76, 1.68, {{0.85, 0.95}, {1.05, 1.2}}};
+    case OP_L1: return {15.9, 10.4, 0.155, 0, 0, 0.111, 4.74e-05, 0.0738, 1.6, 1.72, {{0.9, 0.95}, {1.08, 1.2}}};
+    case OP_HAMM: return {21.6, 6.28, 0.284, 456, 1.93e+03, 0.142, 4.2e-05, 0.0965, 1.74, 2.57, {{0.8, 1}, {0.9, 0.9}}};
+    case OP_CNT: return {18.1, 6.37, 0.7, 616, 524, 0.0371, 4.12e-05, 0.0585, 1.86, 1.91, {{1, 1.2}, {0.85, 1.1}}};
+    case OP_CANB: return {12.5, 16.7, 0.18, 0, 400, 0.299, 2.36e-05, 0.0747, 1.46, 2.38, {{0.85, 0.9}, {1, 1}}};
+    case OP_KL: return {10.8, 25.3, 0.493, 0, 428, 0.345, 4.03e-05, 0.065, 1.97, 1.61, {{0.9, 1}, {0.9, 1}}};
+    case OP_JS: return {18, 20.5, 0.575, 137, 649, 0.755, 6.29e-06, 0.0663, 3.83, 4.57, {{0.9, 0.95}, {1, 1}}};
     case OP_CHEB: return {13.7, 23.1, 0.352, 502, 0, 0.337, 0.000211, 0.069, 3.78, 3.24, {{0.9, 1}, {1, 1}}};
-    case OP_MINK_ANY: return {18.8, 42.8, 0.735, 690, 1.1e+03, 0.664, 0.000272, 0.234, 4.09, 7.42, {{1.1, 1.5}, {1, 1.2}}};
-    default: return {21.9, 30.5, 0.686, 585, 746, 0.555, 0.000169, 0.233, 3.49, 5.4, {{1, 1.5}, {0.9, 1}}};
+    case OP_MINK_ANY: return {18.8, 42.8, 0.735, 690, 1.1e+03, 0.664, 0.000272, 0.234, 4.09, 7.42, {{1.1, 1.2}, {1, 1.1}}};
+    default: return {21.9, 30.5, 0.686, 585, 746, 0.555, 0.000169, 0.233, 3.49, 5.4, {{1, 1.1}, {0.9, 1}}};
     }
 }
-// (`columns`: that the lists are laid out for; `of_a`: over these alone, after a copy; `made`: an index brings the lists)
-double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, const MatchShape &s, bool knn, bool made,
-                  bool of_a) {
+// (`columns`: that the lists are laid out for; `of_a`: over these alone, after a copy; `made`: an index brings the lists;
+// `between`: what of it tells lists from lists, which are met alike.)
+double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, int metric, const MatchShape &s, bool knn, bool made,
+                  bool of_a, bool between = false) {
     const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz, tiles = (double)s.n_tiles;
     const OpCost c = op_cost(op);
     const MatchGrid g = match_grid(h->opt, s, op, A->n_rows, A->nnz, B->nnz, knn);
@@ -758,9 +762,11 @@ double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64
     // (a third of the share for every product, as when the constants were fitted)
     if (nnz_a <= (double)std::max<int64_t>(256, g.share / 3) * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
     const double density = nnz_b / n / (double)columns, list = density * (double)s.tile_rows;  // entries, on the mean
-    const double met = of_a ? 1.0 : std::max(1.0, std::min(40.0, 0.07 / density));
+    const double met = between ? 0.0 : std::max(1.0, std::min(40.0, 0.07 / density));
+    // (correlation reads two norms a pair: 573 x 3,605 rows of 319, all of a length / log-normal, by the scan 147 / 227 us, by lists 164 / 128)
+    const double weight = between ? 1.0 : c.bias[knn][of_a] * (metric == MT_CORRELATION && !knn ? 1.65 : 1.0);
     const double make = made ? 0.0 : 20.5e6 + 20.6 * nnz_b + 7.8 * tiles * (double)s.ptr_stride + 250.0 * n;
-    return c.bias[knn][of_a] * ((knn ? 58.5e6 : 24.9e6) + make + (of_a ? 35.5e6 + 0.85 * nnz_b : 0.0) + 6280.0 * m + 1.0 * m * n +
+    return weight * ((knn ? 58.5e6 : 24.9e6) + make + (of_a ? 35.5e6 + 0.85 * nnz_b : 0.0) + 6280.0 * m + 1.0 * m * n +
            idle * (nnz_a * tiles * (c.entry + c.step * std::min(1.0, list)) + c.match * met * nnz_a * density * n +
                    (c.row + (knn ? c.knn_row : 0.0)) * m * tiles));
 }
@@ -772,11 +778,13 @@ double staged_cost(const spd_csr *A, const spd_csr *B, int op, bool swapped, boo
     const double make = made ? 0.0 : 18.3e6 + 15.0 * nnz_b + 2580.0 * n;
     // (Chebyshev ranks the entries of the rows that it stages: 34 x 969 rows of 1,550 2,777 us, by lists 554; 304 x 604 rows of 23 186 / 94;
     // 2,026 x 7,507 ratings 11,152 / 703; 3,148 x 4,764 rows of 1,790 25,963 / 3,002)
-    return (knn ? 70.6e6 : 46.1e6) + make + 9830.0 * m + 21.8 * nnz_a + (op == OP_CHEB ? 552000.0 : 35800.0) * mean + visit * (swapped ? n * nnz_a : m * nnz_b) +
-           (knn ? c.knn_pair : c.pair) * m * n;
+    // (of few columns the staged rows are dense strips)
+    const double by_columns = A->n_cols < 8192 ? 0.9 : (A->n_cols < 16384 ? 1.0 : (A->n_cols < 40000 ? 1.1 : (A->n_cols < 131072 ? 0.95 : 1.0)));
+    return by_columns * ((knn ? 70.6e6 : 46.1e6) + make + 9830.0 * m + 21.8 * nnz_a + (op == OP_CHEB ? 552000.0 : 35800.0) * mean + visit * (swapped ? n * nnz_a : m * nnz_b) +
+           (knn ? c.knn_pair : c.pair) * m * n);
 }
 // `swapped`: the staged scan would exchange the operands' roles.
-bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn,
+bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const spd_semiring *semiring, bool swapped, bool knn,
                   bool with_index) {
     MatchShape s;
     if (semiring || A->n_rows <= 0 || !match_possible(h, B, op, s)) return false;
@@ -788,12 +796,12 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.26; 1,024 x 300,000 of 230, cosine
     // 11.4 / 5.2; 4,096 x 65,536 of 1,820, L1 87 / 23.6, Jensen-Shannon 349 / 35; 238 x 6,574 of 95, Canberra, with an index 0.21 / 0.026; 1,000 x
     // 10,000 of 1,360 and 20, L1 0.14 / 0.70; set metrics: 3,247 x 7,668 counts, Jaccard 4.6 / 2.1, 72 x 15,967 rows of 218, k-NN 0.22 / 0.41.
-    return lists_cost(h, A, B, A->n_cols, op, s, knn, with_index, false) <= staged_cost(A, B, op, swapped, knn, with_index);
+    return lists_cost(h, A, B, A->n_cols, op, metric, s, knn, with_index, false) <= staged_cost(A, B, op, swapped, knn, with_index);
 }
 // The columns that lists over A's columns alone are laid out for (how many A stores, the host does not know).
 int64_t columns_of(const spd_csr *A) { return std::min(A->n_cols, std::max<int64_t>(A->nnz, 1)); }
 // Whether a call is computed by lists over the columns that A stores, after a copy of both operands over these.
-bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, bool knn,
+bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const spd_semiring *semiring, bool swapped, bool knn,
                     bool with_index) {
     if (semiring || h->match_lists == 0 || !match_serves_knn(op) || A->n_rows <= 0 || A->nnz <= 0 || B->n_rows <= 0 || B->nnz <= 0) return false;
     if (A->n_cols > kMatchMostColumns) return false;
@@ -806,23 +814,23 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     // Both sides measured, staged / lists over A's columns in ms, k-NN: 4,096 x 500,000 sets over 2^20 columns, Jaccard 30.6 /
     // 6.4, 371 x 33,325 of them, Dice 0.81 / 0.33 (over all columns 0.48), 59 x 15,538 0.51 / 0.24 (0.31); 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.3 /
     // 2.0.
-    return lists_cost(h, A, B, columns_of(A), op, s, knn, false, true) <= staged_cost(A, B, op, swapped, knn, with_index);
+    return lists_cost(h, A, B, columns_of(A), op, metric, s, knn, false, true) <= staged_cost(A, B, op, swapped, knn, with_index);
 }
 constexpr int64_t kMatchFewColumns = 1 << 15;
 // The way a call is computed: 0 the staged scan, 1 lists over all columns, 2 lists over the columns that A stores; and how.
 struct MatchWay { int way = 0; int64_t columns = 0; MatchShape s{}; MatchGrid g; MatchScratch L{}; };
-MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, const spd_semiring *semiring, bool swapped, int knn_k,
+MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const spd_semiring *semiring, bool swapped, int knn_k,
                    bool with_index, bool index_has_lists) {
     MatchWay w;
     const bool knn = knn_k > 0;
-    const bool all = h->match_lists != 3 && match_wanted(h, A, B, op, semiring, swapped, knn, with_index) && (!with_index || index_has_lists);
+    const bool all = h->match_lists != 3 && match_wanted(h, A, B, op, metric, semiring, swapped, knn, with_index) && (!with_index || index_has_lists);
     // (few columns have room for their bounds: where the lists over all of them do not pay, neither does a copy)
-    const bool of_a = h->match_lists != 2 && (all || h->match_lists == 3 || A->n_cols > kMatchFewColumns) && columns_wanted(h, A, B, op, semiring, swapped, knn, with_index);
+    const bool of_a = h->match_lists != 2 && (all || h->match_lists == 3 || A->n_cols > kMatchFewColumns) && columns_wanted(h, A, B, op, metric, semiring, swapped, knn, with_index);
     w.way = all ? 1 : (of_a ? 2 : 0);
     if (w.way == 0) return w;
     if (all && of_a) {                   // (the copy may cost less than the bounds and the entries of columns that A does not store)
         const MatchShape over_all = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz), over_a = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
-        if (lists_cost(h, A, B, columns_of(A), op, over_a, knn, false, true) < lists_cost(h, A, B, A->n_cols, op, over_all, knn, with_index, false)) w.way = 2;
+        if (lists_cost(h, A, B, columns_of(A), op, metric, over_a, knn, false, true, true) < lists_cost(h, A, B, A->n_cols, op, metric, over_all, knn, with_index, false, true)) w.way = 2;
     }
     w.columns = w.way == 2 ? columns_of(A) : A->n_cols;
     w.s = match_shape(h->opt.lds_budget, op, B->n_rows, w.columns, B->nnz);
@@ -1096,7 +1104,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     metric = effective_metric(metric, p);
     const int op = product_of(h, metric, p);
     const bool swap = knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
-    const MatchWay way = match_way(h, A, B, op, semiring, swap, knn_k, index != nullptr, index && index->match.values);
+    const MatchWay way = match_way(h, A, B, op, metric, semiring, swap, knn_k, index != nullptr, index && index->match.values);
 
     // ---- row pointers on the host: the caller's copies, or read back (the call's only
     //      synchronisation) ----------------------------------------------------------------
@@ -1657,7 +1665,7 @@ spd_status spd_workspace_bytes(const spd_handle *h, const spd_csr *A, const spd_
         const bool swap = k_neighbors == 0 && swap_wanted(h, A, B, as_metric, nullptr);
         // (without an index, with one that keeps no lists and with one that does)
         for (const int index : {0, 1, 2}) {
-            const MatchWay w = match_way(h, A, B, op, nullptr, swap && index == 0, k_neighbors, index > 0, index == 2);
+            const MatchWay w = match_way(h, A, B, op, as_metric, nullptr, swap && index == 0, k_neighbors, index > 0, index == 2);
             if (w.way != 0) *bytes = std::max(*bytes, w.L.end);
         }
     }
@@ -2038,12 +2046,12 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     const int run_as = effective_metric((int)metric, p), op = product_of(&h, run_as, p);
     const bool knn = k_neighbors > 0, swap = !knn && !with_index && swap_wanted(&h, &A, &B, run_as, nullptr);
     std::memset(out, 0, sizeof *out);
-    out->wanted = match_wanted(&h, &A, &B, op, nullptr, swap, knn, with_index != 0);
+    out->wanted = match_wanted(&h, &A, &B, op, run_as, nullptr, swap, knn, with_index != 0);
     MatchShape kept;
     MatchLayout L;
     const bool keeps = index_keeps_lists(&h, &B, op, kept, L);
     out->index_bytes = keeps ? (int64_t)L.end : 0;
-    MatchWay w = match_way(&h, &A, &B, op, nullptr, swap, k_neighbors, with_index != 0, keeps);
+    MatchWay w = match_way(&h, &A, &B, op, run_as, nullptr, swap, k_neighbors, with_index != 0, keeps);
     out->way = w.way;
     if (w.way == 0) {                    // (the cut that the lists over all columns would have)
         w.columns = n_cols;
