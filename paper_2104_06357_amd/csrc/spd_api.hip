@@ -571,7 +571,7 @@ MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int op, int64_
     g.share = nnz_a * tiles / ((int64_t)g.slices * s.waves);
     const bool one_strip = match_any_order(op);
     g.shared_len = std::max<int64_t>(one_strip && !knn ? 512 : 256, g.share / (one_strip ? 6 : 3));
-    // (Where a workgroup has a (tile, row) for every wavefront, a strip for each of them is paid for by rows of twice the mean length at least.  (573 x 3,605 rows of 319, log-normal, us before and
+    // Where a workgroup has a (tile, row) for every wavefront, a strip for each of them is paid for by rows of twice the mean length at least.  (573 x 3,605 rows of 319, log-normal, us before and
     // after: correlation 155 / 128, KL 137 / 116, Jensen-Shannon k-NN 226 / 197; 4,000 x 6,000 rows of 1,820, cosine, 4,621 / 4,047.)
     if (!one_strip && (m / g.slices) * tiles >= s.waves) g.shared_len = std::max<int64_t>(g.shared_len, 2 * nnz_a / m);
     // Chebyshev: a row of A that is like many of B's costs its wavefront two microseconds a pair (spd_match_impl.h).  Where a wavefront to the row
