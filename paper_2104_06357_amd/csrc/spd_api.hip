@@ -817,6 +817,13 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     return lists_cost(h, A, B, columns_of(A), op, metric, s, knn, false, true) <= staged_cost(A, B, op, swapped, knn, with_index);
 }
 constexpr int64_t kMatchFewColumns = 1 << 15;
+// Whether lists over all columns have room for their bounds.  They may not over few columns either: 32,768 of them for 660,000 rows of few entries,
+// 16,384 for two million.  (Staged / over A's columns in us: 200 x 1,000,000 rows of 5 over 32,768, cosine 3,392 / 748, L1, k-NN 3,337 / 780; 3,000 x 900,000
+// of 3, Canberra, k-NN 9,013 / 1,503; 4,096 x 2,000,000 of 2 over 16,384, cosine, k-NN 18,106 / 4,756.)
+bool all_columns_fit(const spd_handle *h, const spd_csr *B, int op) {
+    MatchShape s;
+    return match_possible(h, B, op, s) && match_bounds_fit(s, B->nnz);
+}
 // The way a call is computed: 0 the staged scan, 1 lists over all columns, 2 lists over the columns that A stores; and how.
 struct MatchWay { int way = 0; int64_t columns = 0; MatchShape s{}; MatchGrid g; MatchScratch L{}; };
 MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const spd_semiring *semiring, bool swapped, int knn_k,
@@ -824,8 +831,10 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
     MatchWay w;
     const bool knn = knn_k > 0;
     const bool all = h->match_lists != 3 && match_wanted(h, A, B, op, metric, semiring, swapped, knn, with_index) && (!with_index || index_has_lists);
-    // (few columns have room for their bounds: where the lists over all of them do not pay, neither does a copy)
-    const bool of_a = h->match_lists != 2 && (all || h->match_lists == 3 || A->n_cols > kMatchFewColumns) && columns_wanted(h, A, B, op, metric, semiring, swapped, knn, with_index);
+    // (where the lists over few columns have room for their bounds and do not pay, neither does a copy; where many rows of B leave them none,
+    // the copy is what there is)
+    const bool of_a = h->match_lists != 2 && (all || h->match_lists == 3 || A->n_cols > kMatchFewColumns || !all_columns_fit(h, B, op)) &&
+                      columns_wanted(h, A, B, op, metric, semiring, swapped, knn, with_index);
     w.way = all ? 1 : (of_a ? 2 : 0);
     if (w.way == 0) return w;
     if (all && of_a) {                   // (the copy may cost less than the bounds and the entries of columns that A does not store)

@@ -386,6 +386,20 @@ def test_lists_over_the_columns_of_a_where_they_were_measured_the_faster():
         assert way(*call) == 0, call
 
 
+def test_many_short_rows_over_few_columns_take_the_copy():
+    """The bounds of the lists over all columns, a word per tile and column, have no room beside so many short rows."""
+    # staged / lists over A's columns in us
+    for m, n, mean, cols, metric, k in ((200, 1_000_000, 5, 32_768, "cosine", 0),                        # 3,392 / 748
+                                        (200, 1_000_000, 5, 32_768, "l1", 10),                           # 3,337 / 780
+                                        (1_000, 1_000_000, 5, 32_768, "l1", 10),                         # 5,111 / 1,121
+                                        (1_000, 700_000, 4, 32_000, "cosine", 10),                       # 3,225 / 655
+                                        (100, 1_200_000, 6, 30_000, "canberra", 0),                      # 4,311 / 849
+                                        (3_000, 900_000, 3, 32_768, "canberra", 10),                     # 9,013 / 1,503
+                                        (4_096, 2_000_000, 2, 16_384, "l1", 10)):                        # 19,735 / 5,611
+        plan = spd.testing.host_list_plan(m, m * mean, n, n * mean, cols, metric, k_neighbors=k)
+        assert plan["way"] == 2 and plan["consistent"], (m, n, mean, cols, metric, plan)
+
+
 def test_an_index_keeps_lists_that_calls_may_want_within_the_stated_memory():
     def kept(n, mean, cols, metric, **more):
         plan = spd.testing.host_list_plan(1_000, 30_000, n, int(n * mean), cols, metric, with_index=True, **more)
