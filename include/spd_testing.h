@@ -36,7 +36,8 @@ spd_status spd_host_plan_summary(const int64_t *a_indptr, int64_t a_rows, const 
 
 /* Whether a call on operands of these sizes (`k_neighbors` = 0 for pairwise, `with_index` for the calls
  * on a prepared index) takes the column lists (option "match_lists"), and how it cuts them.  (Of a call that takes none: how
- * the lists over all columns would be cut.  Small calls that run in one launch: spd_host_direct_lanes.) */
+ * the lists over all columns would be cut.  Small calls that run in one launch: spd_host_direct_lanes.)  Besides the options,
+ * "scratch": bytes that the caller lends. */
 typedef struct {
     int32_t wanted;                 /* over all columns, were an index to keep them */
     int32_t tiles, tile_rows;       /* of B */

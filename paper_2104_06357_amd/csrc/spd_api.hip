@@ -825,9 +825,10 @@ bool all_columns_fit(const spd_handle *h, const spd_csr *B, int op) {
     return match_possible(h, B, op, s) && match_bounds_fit(s, B->nnz);
 }
 // The way a call is computed: 0 the staged scan, 1 lists over all columns, 2 lists over the columns that A stores; and how.
+// `room`: bytes of scratch that there may be.
 struct MatchWay { int way = 0; int64_t columns = 0; MatchShape s{}; MatchGrid g; MatchScratch L{}; };
 MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const spd_semiring *semiring, bool swapped, int knn_k,
-                   bool with_index, bool index_has_lists) {
+                   bool with_index, bool index_has_lists, size_t room) {
     MatchWay w;
     const bool knn = knn_k > 0;
     const bool all = h->match_lists != 3 && match_wanted(h, A, B, op, metric, semiring, swapped, knn, with_index) && (!with_index || index_has_lists);
@@ -835,18 +836,26 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
     // the copy is what there is)
     const bool of_a = h->match_lists != 2 && (all || h->match_lists == 3 || A->n_cols > kMatchFewColumns || !all_columns_fit(h, B, op)) &&
                       columns_wanted(h, A, B, op, metric, semiring, swapped, knn, with_index);
-    w.way = all ? 1 : (of_a ? 2 : 0);
-    if (w.way == 0) return w;
+    auto lay_out = [&](int way) {
+        w.way = way;
+        w.columns = way == 2 ? columns_of(A) : A->n_cols;
+        w.s = match_shape(h->opt.lds_budget, op, B->n_rows, w.columns, B->nnz);
+        w.g = match_grid(h->opt, w.s, op, A->n_rows, A->nnz, B->nnz, knn);
+        w.L = layout_match_call(w.s, w.g, op, A->n_rows, A->nnz, B->n_rows, B->nnz, knn_k, way == 2 || !with_index, way == 2 ? A->n_cols : 0);
+    };
+    if (!all && !of_a) return w;
     if (all && of_a) {                   // (the copy may cost less than the bounds and the entries of columns that A does not store)
         const MatchShape over_all = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz), over_a = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
-        if (lists_cost(h, A, B, columns_of(A), op, metric, over_a, knn, false, true, true) < lists_cost(h, A, B, A->n_cols, op, metric, over_all, knn, with_index, false, true)) w.way = 2;
+        if (lists_cost(h, A, B, columns_of(A), op, metric, over_a, knn, false, true, true) < lists_cost(h, A, B, A->n_cols, op, metric, over_all, knn, with_index, false, true)) {
+            lay_out(2);
+            if (w.L.end <= room) return w;            // (it may also take more scratch: with an index the lists over all columns take next to none)
+        }
     }
-    w.columns = w.way == 2 ? columns_of(A) : A->n_cols;
-    w.s = match_shape(h->opt.lds_budget, op, B->n_rows, w.columns, B->nnz);
-    w.g = match_grid(h->opt, w.s, op, A->n_rows, A->nnz, B->nnz, knn);
-    w.L = layout_match_call(w.s, w.g, op, A->n_rows, A->nnz, B->n_rows, B->nnz, knn_k, w.way == 2 || !with_index, w.way == 2 ? A->n_cols : 0);
+    lay_out(all ? 1 : 2);
     return w;
 }
+// The scratch that a call's lists may take: what the caller lends, or less than the device refused.
+size_t scratch_room(const spd_handle *h) { return h->ws_external ? h->ws_bytes : h->lists_refused - 1; }
 
 
 // The norms of B's rows, and their lists.
@@ -1113,7 +1122,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     metric = effective_metric(metric, p);
     const int op = product_of(h, metric, p);
     const bool swap = knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
-    const MatchWay way = match_way(h, A, B, op, metric, semiring, swap, knn_k, index != nullptr, index && index->match.values);
+    MatchWay way = match_way(h, A, B, op, metric, semiring, swap, knn_k, index != nullptr, index && index->match.values, scratch_room(h));
 
     // ---- row pointers on the host: the caller's copies, or read back (the call's only
     //      synchronisation) ----------------------------------------------------------------
@@ -1185,7 +1194,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         }
     }
     bool lists = way.way != 0 && !direct;
-    if (lists) {
+    while (lists) {
         if (way.way == 1 && index) {
             MatchShape kept = index->match.shape;
             kept.aligned = way.s.aligned;               // (an index may hold its lists without gaps)
@@ -1194,17 +1203,17 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         // (a caller's scratch that does not hold the lists still serves the staged scan)
         if (h->ws_external && way.L.end > h->ws_bytes) lists = false;
         // (and so does a device that has no memory left for them; so much is not asked for again)
-        if (lists && !h->ws_external) {
-            const spd_status room = way.L.end < h->lists_refused ? ensure_workspace(h, way.L.end) : SPD_ERR_WORKSPACE;
-            if (room == SPD_ERR_WORKSPACE) {
-                h->lists_refused = std::min(h->lists_refused, way.L.end);
-                h->err.clear();
-                (void)hipGetLastError();
-                lists = false;
-            } else if (room != SPD_OK) {
-                return room;
-            }
-        }
+        if (!lists || h->ws_external) break;
+        const spd_status room = way.L.end < h->lists_refused ? ensure_workspace(h, way.L.end) : SPD_ERR_WORKSPACE;
+        if (room == SPD_OK) break;
+        if (room != SPD_ERR_WORKSPACE) return room;
+        h->lists_refused = std::min(h->lists_refused, way.L.end);
+        h->err.clear();
+        (void)hipGetLastError();
+        // (the lists over all columns, where the copy was preferred to them, may still have room)
+        const bool copied = way.way == 2;
+        if (copied) way = match_way(h, A, B, op, metric, semiring, swap, knn_k, index != nullptr, index && index->match.values, scratch_room(h));
+        lists = copied && way.way == 1;
     }
     swapped = swap && !lists && !direct;
     if (swapped) std::swap(A, B);           // from here on A is the staged operand, B the streamed one
@@ -1674,7 +1683,7 @@ spd_status spd_workspace_bytes(const spd_handle *h, const spd_csr *A, const spd_
         const bool swap = k_neighbors == 0 && swap_wanted(h, A, B, as_metric, nullptr);
         // (without an index, with one that keeps no lists and with one that does)
         for (const int index : {0, 1, 2}) {
-            const MatchWay w = match_way(h, A, B, op, as_metric, nullptr, swap && index == 0, k_neighbors, index > 0, index == 2);
+            const MatchWay w = match_way(h, A, B, op, as_metric, nullptr, swap && index == 0, k_neighbors, index > 0, index == 2, SIZE_MAX);
             if (w.way != 0) *bytes = std::max(*bytes, w.L.end);
         }
     }
@@ -2048,6 +2057,11 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     if ((int)metric < 0 || (int)metric >= SPD_METRIC_COUNT) return SPD_ERR_BAD_METRIC;
     spd_handle h;
     for (int i = 0; i < n_options; ++i) {
+        if (std::strcmp(option_names[i], "scratch") == 0) {
+            h.ws_external = true;
+            h.ws_bytes = (size_t)option_values[i];
+            continue;
+        }
         const spd_status st = spd_set_option(&h, option_names[i], option_values[i]);
         if (st != SPD_OK) return st;
     }
@@ -2060,7 +2074,8 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     MatchLayout L;
     const bool keeps = index_keeps_lists(&h, &B, op, kept, L);
     out->index_bytes = keeps ? (int64_t)L.end : 0;
-    MatchWay w = match_way(&h, &A, &B, op, run_as, nullptr, swap, k_neighbors, with_index != 0, keeps);
+    MatchWay w = match_way(&h, &A, &B, op, run_as, nullptr, swap, k_neighbors, with_index != 0, keeps, scratch_room(&h));
+    if (w.way != 0 && h.ws_external && w.L.end > h.ws_bytes) w.way = 0;
     out->way = w.way;
     if (w.way == 0) {                    // (the cut that the lists over all columns would have)
         w.columns = n_cols;

@@ -328,6 +328,36 @@ def test_refusals_and_documented_scratch(spd):
     h.close()
 
 
+def test_scratch_for_the_lists_over_all_columns_alone(spd):
+    """Scratch that holds the lists over all columns and not the copy, which would be preferred: the bits of the former."""
+    import torch
+    rng = np.random.default_rng(83)
+    m, n, cols, nnz = 283, 83_003, 74_017, 2_663_779
+
+    def matrix(rows, entries):
+        cell = np.unique(rng.integers(0, rows * cols, size=entries))
+        indptr = np.concatenate([[0], np.cumsum(np.bincount(cell // cols, minlength=rows))]).astype(np.int64)
+        return spd.DeviceCsr.from_host({"n_rows": rows, "n_cols": cols, "indptr": indptr, "indices": (cell % cols).astype(np.int32),
+                                        "values": (rng.random(len(cell)) + 0.01).astype(np.float32)})
+
+    dA, dB = matrix(m, 984), matrix(n, nnz)
+    sizes = (m, dA.nnz, n, dB.nnz, cols, "hellinger")
+    plans = [spd.testing.host_list_plan(*sizes, match_lists=way) for way in (1, 2)]
+    assert plans[0]["way"] == 2 and plans[1]["scratch_bytes"] < plans[0]["scratch_bytes"]
+    want = _lists(spd).pairwise(dA, dB, "hellinger")
+    h = spd.Handle()
+    h.set_option("check_plan", 1)
+    h.set_option("profile", 1)
+    h.set_workspace(torch.empty(plans[1]["scratch_bytes"] + 4_096, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(h.pairwise(dA, dB, "hellinger"), want)
+    names = {r["name"] for r in h.profile_read()}
+    assert "lists_b" in names and "columns" not in names
+    h.set_workspace(torch.empty(plans[0]["scratch_bytes"], dtype=torch.uint8, device="cuda"))
+    assert torch.allclose(h.pairwise(dA, dB, "hellinger"), want, rtol=2.5e-7, atol=1e-7)
+    assert "columns" in {r["name"] for r in h.profile_read()}
+    h.close()
+
+
 def test_scratch_for_the_scan_alone(spd):
     """Scratch that holds what the staged scan needs and not the lists, lent by the caller or the static array: the same bits as
     the staged scan, and two roundings of reordered fp64 sums from the lists."""

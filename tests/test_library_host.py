@@ -400,6 +400,16 @@ def test_many_short_rows_over_few_columns_take_the_copy():
         assert plan["way"] == 2 and plan["consistent"], (m, n, mean, cols, metric, plan)
 
 
+def test_scratch_for_the_lists_over_all_columns_alone():
+    """Where the copy over A's columns is preferred and takes more scratch than there is, the lists over all columns serve the call."""
+    for call, k in (((283, 984, 83_003, 2_663_779, 74_017, "hellinger"), 0), ((115, 2_105, 209_197, 2_773_272, 60_897, "russell_rao"), 10)):
+        plan = lambda **more: spd.testing.host_list_plan(*call, k_neighbors=k, **more)
+        free, all_columns = plan(), plan(match_lists=2)
+        assert free["way"] == 2 and all_columns["scratch_bytes"] < free["scratch_bytes"]
+        for scratch, way in ((free["scratch_bytes"], 2), (free["scratch_bytes"] - 1, 1), (all_columns["scratch_bytes"], 1), (all_columns["scratch_bytes"] - 1, 0)):
+            assert plan(scratch=scratch)["way"] == way, (call, scratch, way)
+
+
 def test_an_index_keeps_lists_that_calls_may_want_within_the_stated_memory():
     def kept(n, mean, cols, metric, **more):
         plan = spd.testing.host_list_plan(1_000, 30_000, n, int(n * mean), cols, metric, with_index=True, **more)
