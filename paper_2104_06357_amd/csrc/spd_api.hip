@@ -763,10 +763,12 @@ double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64
     if (nnz_a <= (double)std::max<int64_t>(256, g.share / 3) * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
     const double density = nnz_b / n / (double)columns, list = density * (double)s.tile_rows;  // entries, on the mean
     const double met = between ? 0.0 : std::max(1.0, std::min(40.0, 0.07 / density));
-    // (correlation reads two norms a pair: 573 x 3,605 rows of 319, all of a length / log-normal, by the scan 147 / 227 us, by lists 164 / 128)
-    const double weight = between ? 1.0 : c.bias[knn][of_a] * (metric == MT_CORRELATION && !knn ? 1.65 : 1.0);
+    const double weight = between ? 1.0 : c.bias[knn][of_a];
+    // (two norms a pair: 0.66 ps more, fitted to 570 calls by correlation, pairwise, and 2,200 by Minkowski's, whose constants hold them.  573 x 3,605 rows of 319,
+    // all of a length / log-normal, correlation, by the scan 138 / 207 us, by lists 160 / 131, cosine 140 / 215 and 163 / 128)
+    const double pair = metric == MT_CORRELATION ? 1.66 : 1.0;
     const double make = made ? 0.0 : 20.5e6 + 20.6 * nnz_b + 7.8 * tiles * (double)s.ptr_stride + 250.0 * n;
-    return weight * ((knn ? 58.5e6 : 24.9e6) + make + (of_a ? 35.5e6 + 0.85 * nnz_b : 0.0) + 6280.0 * m + 1.0 * m * n +
+    return weight * ((knn ? 58.5e6 : 24.9e6) + make + (of_a ? 35.5e6 + 0.85 * nnz_b : 0.0) + 6280.0 * m + pair * m * n +
            idle * (nnz_a * tiles * (c.entry + c.step * std::min(1.0, list)) + c.match * met * nnz_a * density * n +
                    (c.row + (knn ? c.knn_row : 0.0)) * m * tiles));
 }

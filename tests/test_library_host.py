@@ -275,9 +275,33 @@ def test_column_lists_where_either_way_was_measured_the_faster():
         assert way(*call) == 1, call
     for call in ((99, 200, 386_927, 860_302, 858_000, "cosine", 10, True),                               # 192 / 259 over A's columns
                  (225, 16_379, 3_387, 257_241, 4_996, "l1", 64, True),                                   # 56 / 100
-                 (285, 16_409, 2_183, 121_792, 5_120, "hamming", 1, True),                               # 61 / 107
-                 (573, 182_658, 3_605, 1_203_924, 25_248, "correlation")):                               # 179 / 297
+                 (285, 16_409, 2_183, 121_792, 5_120, "hamming", 1, True)):                              # 61 / 107
         assert way(*call) == 0, call
+
+
+def test_correlation_goes_the_way_of_the_other_dot_products():
+    """It reads a second norm a pair, and its lists and visits are cosine's: both ways take the same times by either metric."""
+    def way(m, nnz_a, n, nnz_b, cols, metric):
+        return spd.testing.host_list_plan(m, nnz_a, n, nnz_b, cols, metric)["way"]
+
+    # by correlation, staged / lists in us
+    for call in ((307, 40_824, 3_449, 517_333, 193_879),                                                 # 312 / 124
+                 (72, 141_200, 35_647, 65_078_019, 26_000),                                              # 3,055 / 1,357
+                 (106, 195_719, 12_282, 22_371_889, 25_958),                                             # 1,166 / 520
+                 (212, 360_947, 4_950, 9_034_151, 25_864),                                               # 589 / 376
+                 (91, 5_303, 3_171, 391_568, 193_823),                                                   # 147 / 91
+                 (573, 185_212, 3_605, 1_255_751, 60_000),                                               # 314 / 128, rows of one length 158 / 160
+                 (573, 182_658, 3_605, 1_203_924, 25_248)):                                              # 207 / 131, rows of one length 138 / 160
+        assert way(*call, "correlation") == 1, call
+    rng = np.random.default_rng(41)
+    apart = lists = 0
+    for _ in range(3_000):                                 # words, counts and ratings
+        cols, mean, least, most = ((102_660, 228, 5_000, 300_000), (26_000, 1_820, 500, 60_000), (194_000, 160, 2_000, 200_000))[rng.integers(3)]
+        m, n = int(np.exp(rng.uniform(np.log(17), np.log(4_000)))), int(np.exp(rng.uniform(np.log(least), np.log(most))))
+        ways = [way(m, m * mean, n, n * mean, cols, metric) for metric in ("cosine", "correlation")]
+        lists += ways[0] != 0
+        apart += ways[0] != ways[1]
+    assert lists > 1_500 and apart < 30, (lists, apart)
 
 
 @pytest.mark.parametrize("m,n,metric,k", [(89, 8_333, "l1", 64), (1_514, 20_515, "cosine", 10), (1_783, 12_134, "cosine", 10)])
