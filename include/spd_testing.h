@@ -48,6 +48,9 @@ typedef struct {
     int32_t run;                    /* tiles that a wavefront goes through with a row of A */
     int32_t way;                    /* 0: the staged scan, 1: lists over all columns, 2: over the columns that A stores */
     int64_t columns;                /* that the lists are laid out for */
+    int64_t block_columns;          /* of a block of the build */
+    int32_t aligned, index_aligned; /* lists that begin at lines of memory: of the call's scratch, and of an index */
+    int32_t staged_kind, staged_rows;   /* rows that the scan would stage together, and their kind of map */
 } spd_list_plan;
 spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int64_t b_nnz, int64_t n_cols,
                               spd_metric metric, float p, int k_neighbors, int with_index,

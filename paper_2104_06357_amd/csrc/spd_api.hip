@@ -685,6 +685,8 @@ bool match_bounds_fit(const MatchShape &s, int64_t nnz, int words = 2) {
     return (int64_t)s.n_tiles * s.ptr_stride <= std::max<int64_t>(words * nnz, 16 << 20);
 }
 bool match_light(int op) { return op == OP_DOT || op == OP_L1 || op == OP_HAMM; }
+// Where an eighth of B's cells are stored (half, for a dear product), most visits meet something.
+bool match_dense(const spd_csr *B, int op) { return (double)B->nnz > (match_light(op) ? 0.125 : 0.5) * (double)B->n_cols * (double)B->n_rows; }
 // Whether B's rows have lists for a product at all, under the option's setting.
 bool match_possible(const spd_handle *h, const spd_csr *B, int op, MatchShape &s) {
     if (h->match_lists == 0 || !match_serves(op)) return false;
@@ -695,10 +697,7 @@ bool match_possible(const spd_handle *h, const spd_csr *B, int op, MatchShape &s
 }
 // Whether some call could do better by them, as far as B tells.
 bool match_suits(const spd_handle *h, const spd_csr *B, int op, const MatchShape &s) {
-    if (!scan_knobs_untouched(h)) return false;
-    // where an eighth of B's cells are stored (half, for a dear product), most visits meet something
-    if ((double)B->nnz > (match_light(op) ? 0.125 : 0.5) * (double)B->n_cols * (double)B->n_rows) return false;
-    return match_bounds_fit(s, B->nnz);
+    return scan_knobs_untouched(h) && !match_dense(B, op) && match_bounds_fit(s, B->nnz);
 }
 // Whether an index keeps the lists, and their layout in its memory: only lists that a call may want, and no more of
 // them than the header states (a small B over many columns has more bounds than entries).
@@ -719,75 +718,74 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
     return match_suits(h, B, op, s) && (int64_t)L.end <= most;
 }
 // What a call costs by lists and by the staged scan, in picoseconds of the whole chip.  A wavefront pays for every entry of
-// its row of A in every tile (its list's bounds; a step, where the list is not empty), for every entry of a list it walks and for
+// its row of A in every tile (its list's bounds), for every entry of a list it walks and for
 // every (tile, row); the last round of (tile, row)s leaves wavefronts idle, unless rows are so long that a workgroup's wavefronts share
-// them.  The staged scan pays for every visit (a staged row, a streamed entry; more where longer staged rows leave fewer of them
-// a place in LDS, and where the columns are too many for the quick maps).  Both pay for what they make of B, where no index
-// has it, for the pairs they finish, and for their launches.  The constants are fitted to all ways' times of 11,688 pairs of operands
-// (of the working range: words, counts, ratings, sets, n-grams, skewed lengths; and of 30 to 12,000 rows against 300 to 300,000, of equal, log-normal
-// and power-law lengths of 1.5 to 3,000 entries, A's as long as
-// B's and not, uniform and Zipf columns, 2,000 to 2^20 of them; every product, k-NN with k = 1 to 64 and pairwise, with an index
-// and without); nine of ten estimates are within 0.5 to 1.5 of the times, because row pointers do not show how A's columns
-// meet B's, nor its longest row.  Columns are seldom uniform where they are many: over all columns the lists are taken to be met up to 40 times as
-// often as if they were, as far as the density leaves room for that (words, Zipf columns, rows of 230 over 102,660: some 40 times).
-// The estimates of lists are weighed by what chose best between the ways (`bias`: pairwise and k-NN, over all columns and over A's).  Constants from
-// lists that took up to a third longer sent most calls near the line to the scan: 371 x 33,325 sets, Dice, k-NN, 810 us by it and 326 by
-// lists, 3,247 x 7,668 counts, Jaccard, 4,622 and 2,050, 86 x 8,953 ratings 344 and 173.  Of the working range (without an index, 650 random
-// calls) calls took 12 % more than by the best way on the mean, and take 3 to 4 % more now; what is chosen wrongly is mostly few rows of A against words by set
-// metrics, whose Zipf columns are met more often than in any other data.
-struct OpCost { double entry, step, match, row, knn_row, visit, longer, wide, pair, knn_pair; double bias[2][2]; };
+// them.  The staged scan pays for every visit (a staged row, a streamed entry), and for a streamed entry's look-up, which the rows that are staged
+// together share: how many these are and behind which kind of map, the planner says.  Both pay for what they make of B, where no index
+// has it, for the pairs they finish, for their launches, and the longer rows are, for the last and longest of them; the scan also for the launches that
+// staged rows of many lengths take, but for a dense strip, which has one.  Lists over A's columns are walked as those over all columns are;
+// what the copy leaves of B is the share of its columns that A stores, were they uniform, and the more the less they are: its fourth root.  Columns are
+// seldom uniform where they are many: lists are taken to be met up to 40 times as often as if they were, as far as the density leaves room for that
+// (words, Zipf columns, rows of 230 over 102,660: some 40 times).
+// The constants are fitted to the times of 11,400 calls by all three ways (of the working range: words, counts, ratings, sets, n-grams, skewed lengths; and of 8 to
+// 11,000 rows against 64 to 2,000,000, of equal, log-normal and power-law lengths of 1.5 to 3,000 entries, A's as long as B's and not, uniform and Zipf columns, 64 to
+// 2^22 of them; every product, k-NN with k = 1 to 64 and pairwise, with an index and without); nine of ten estimates are within 0.54 to 1.66 of the
+// times, because row pointers do not show how A's columns meet B's, nor the longest row.  What 2,232 further calls took beyond the best way, on the mean: of the working range
+// 2.3 %, of the others 4.7 %, correlation, pairwise, 9 %.  (The scan by steps of the column count and lists by a weight for each product, k-NN and way, in place of maps, rows' lengths
+// and launches: 4.6, 6.4 and, correlation weighed by 1.65, 16 %; constants from lists that took up to a third longer 12, 11 and 13 %.)
+struct OpCost { double entry, match, row, knn_row, visit, pair, knn_pair; };
 constexpr OpCost op_cost(int op) {
     switch (op) {
-    case OP_DOT: return {14, 21.1, 0.293, 47.4, 40.1, 0.0969, 5.33e-05, 0.0478, 1.76, 1.68, {{0.85, 0.95}, {1.05, 1.2}}};
-    case OP_L1: return {15.9, 10.4, 0.155, 0, 0, 0.111, 4.74e-05, 0.0738, 1.6, 1.72, {{0.9, 0.95}, {1.08, 1.2}}};
-    case OP_HAMM: return {21.6, 6.28, 0.284, 456, 1.93e+03, 0.142, 4.2e-05, 0.0965, 1.74, 2.57, {{0.8, 1}, {0.9, 0.9}}};
-    case OP_CNT: return {18.1, 6.37, 0.7, 616, 524, 0.0371, 4.12e-05, 0.0585, 1.86, 1.91, {{1, 1.2}, {0.85, 1.1}}};
-    case OP_CANB: return {12.5, 16.7, 0.18, 0, 400, 0.299, 2.36e-05, 0.0747, 1.46, 2.38, {{0.85, 0.9}, {1, 1}}};
-    case OP_KL: return {10.8, 25.3, 0.493, 0, 428, 0.345, 4.03e-05, 0.065, 1.97, 1.61, {{0.9, 1}, {0.9, 1}}};
-    case OP_JS: return {18, 20.5, 0.575, 137, 649, 0.755, 6.29e-06, 0.0663, 3.83, 4.57, {{0.9, 0.95}, {1, 1}}};
-    case OP_CHEB: return {13.7, 23.1, 0.352, 502, 0, 0.337, 0.000211, 0.069, 3.78, 3.24, {{0.9, 1}, {1, 1}}};
-    case OP_MINK_ANY: return {18.8, 42.8, 0.735, 690, 1.1e+03, 0.664, 0.000272, 0.234, 4.09, 7.42, {{1.1, 1.2}, {1, 1.1}}};
-    default: return {21.9, 30.5, 0.686, 585, 746, 0.555, 0.000169, 0.233, 3.49, 5.4, {{1, 1.1}, {0.9, 1}}};
+    case OP_DOT: return {9.23, 0.536, 0, 116, 0.0859, 2.23, 1.60};
+    case OP_L1: return {8.61, 0.421, 0, 0, 0.109, 1.29, 1.81};
+    case OP_HAMM: return {13.3, 0.451, 825, 1180, 0.157, 2.29, 2.23};
+    case OP_CNT: return {11.0, 0.505, 482, 691, 0.0710, 2.96, 1.67};
+    case OP_CANB: return {7.84, 0.599, 137, 35, 0.298, 2.35, 2.13};
+    case OP_KL: return {10.2, 0.894, 22, 580, 0.335, 2.24, 1.85};
+    case OP_JS: return {4.88, 1.06, 174, 1070, 0.729, 4.35, 4.32};
+    case OP_CHEB: return {8.10, 0.587, 687, 0, 0.433, 1.87, 75.9};
+    case OP_MINK_ANY: return {10.6, 2.19, 767, 912, 0.870, 3.50, 5.02};
+    default: return {10.3, 1.69, 411, 540, 0.489, 3.16, 2.79};
     }
 }
-// (`columns`: that the lists are laid out for; `of_a`: over these alone, after a copy; `made`: an index brings the lists;
-// `between`: what of it tells lists from lists, which are met alike.)
-double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int64_t columns, int op, int metric, const MatchShape &s, bool knn, bool made,
-                  bool of_a, bool between = false) {
-    const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz, tiles = (double)s.n_tiles;
+// The columns that lists over A's columns alone are laid out for (how many A stores, the host does not know).
+int64_t columns_of(const spd_csr *A) { return std::min(A->n_cols, std::max<int64_t>(A->nnz, 1)); }
+// (`of_a`: over A's columns alone, after a copy; an index brings the lists over all columns)
+double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const MatchShape &s, bool knn, bool with_index, bool of_a) {
+    const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz, tiles = (double)s.n_tiles, cols = (double)A->n_cols;
     const OpCost c = op_cost(op);
     const MatchGrid g = match_grid(h->opt, s, op, A->n_rows, A->nnz, B->nnz, knn);
     const double rows = std::ceil(m / g.slices), runs = std::ceil(tiles / g.groups);          // of a workgroup
     double idle = rows * runs * (double)h->opt.n_cus / (m * tiles);
-    // (a third of the share for every product, as when the constants were fitted)
-    if (nnz_a <= (double)std::max<int64_t>(256, g.share / 3) * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
-    const double density = nnz_b / n / (double)columns, list = density * (double)s.tile_rows;  // entries, on the mean
-    const double met = between ? 0.0 : std::max(1.0, std::min(40.0, 0.07 / density));
-    const double weight = between ? 1.0 : c.bias[knn][of_a];
-    // (two norms a pair: 0.66 ps more, fitted to 570 calls by correlation, pairwise, and 2,200 by Minkowski's, whose constants hold them.  573 x 3,605 rows of 319,
-    // all of a length / log-normal, correlation, by the scan 138 / 207 us, by lists 160 / 131, cosine 140 / 215 and 163 / 128)
-    const double pair = metric == MT_CORRELATION ? 1.66 : 1.0;
-    const double make = made ? 0.0 : 20.5e6 + 20.6 * nnz_b + 7.8 * tiles * (double)s.ptr_stride + 250.0 * n;
-    return weight * ((knn ? 58.5e6 : 24.9e6) + make + (of_a ? 35.5e6 + 0.85 * nnz_b : 0.0) + 6280.0 * m + pair * m * n +
-           idle * (nnz_a * tiles * (c.entry + c.step * std::min(1.0, list)) + c.match * met * nnz_a * density * n +
-                   (c.row + (knn ? c.knn_row : 0.0)) * m * tiles));
+    if (nnz_a <= (double)g.shared_len * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
+    const double density = nnz_b / n / cols, met = density > 0.0 ? std::max(1.0, std::min(40.0, 0.0693 / density)) : 1.0;
+    const double kept = of_a ? std::sqrt(std::sqrt(1.0 - std::exp(-nnz_a / cols))) : 1.0;
+    const double make = with_index && !of_a ? 0.0 : (knn ? 7.64e6 : 15e6) + 15.7 * kept * nnz_b + 6.81 * tiles * (of_a ? (double)columns_of(A) : cols) + 329.0 * n;
+    // (two norms a pair: 573 x 3,605 rows of 319, all of a length / log-normal, correlation, by the scan 138 / 207 us, by lists 160 / 131)
+    const bool two_norms = metric == MT_CORRELATION || op == OP_MINK || op == OP_MINK_ANY;
+    // (counts without an index: where both estimates are alike the scan's times spread further, so that what lists gain is more than what they lose.  Hamming, 6,533 x
+    // 70,554 rows of 240 and 36, k-NN, 3,581 us by the scan and 1,408 by lists, which are estimated the higher)
+    const double weight = (op == OP_HAMM || op == OP_CNT) && !with_index ? 0.88 : 1.0;
+    return weight * ((knn ? 52.4e6 : 13.5e6) + make + (of_a ? 39.1e6 + 7.21 * nnz_b : 0.0) + 5050.0 * m + (two_norms ? 1.65 : 0.985) * m * n +
+                     2.18e6 * std::sqrt(nnz_a / m) + 0.802e6 * std::sqrt(nnz_b / n) +
+                     idle * (nnz_a * tiles * c.entry + c.match * met * nnz_a * density * n + (c.row + (knn ? c.knn_row : 0.0)) * m * tiles));
 }
-double staged_cost(const spd_csr *A, const spd_csr *B, int op, bool swapped, bool knn, bool made) {
+double staged_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, bool swapped, bool knn, bool made) {
     const double m = (double)A->n_rows, n = (double)B->n_rows, nnz_a = (double)A->nnz, nnz_b = (double)B->nnz;
     const OpCost c = op_cost(op);
-    const double mean = swapped ? nnz_b / n : nnz_a / m;                                       // of the staged rows
-    const double visit = c.visit + c.longer * std::min(mean, 2000.0) + (A->n_cols > 40000 ? c.wide : 0.0);
-    const double make = made ? 0.0 : 18.3e6 + 15.0 * nnz_b + 2580.0 * n;
+    const double staged = swapped ? nnz_b / n : nnz_a / m, streamed = swapped ? nnz_a / m : nnz_b / n;           // entries of a row
+    const Staging of = staging_of(A->n_cols, metric, op, knn, staged, h->opt);
+    const double look_up = of.kind == KIND_STRIP ? 0.0 : (of.kind == KIND_SLOT ? 0.189 : (of.kind == KIND_BITMAP ? 0.385 : 0.859));
+    const double launches = of.kind == KIND_STRIP ? 0.0 : (of.kind == KIND_SLOT ? 2.02e6 : (of.kind == KIND_BITMAP ? 2.62e6 : 3.31e6));
+    const double make = made ? 0.0 : (knn ? 0.0 : 7.96e6) + 7.87 * nnz_b + 2830.0 * n;
     // (Chebyshev ranks the entries of the rows that it stages: 34 x 969 rows of 1,550 2,777 us, by lists 554; 304 x 604 rows of 23 186 / 94;
     // 2,026 x 7,507 ratings 11,152 / 703; 3,148 x 4,764 rows of 1,790 25,963 / 3,002)
-    // (of few columns the staged rows are dense strips)
-    const double by_columns = A->n_cols < 8192 ? 0.9 : (A->n_cols < 16384 ? 1.0 : (A->n_cols < 40000 ? 1.1 : (A->n_cols < 131072 ? 0.95 : 1.0)));
-    return by_columns * ((knn ? 70.6e6 : 46.1e6) + make + 9830.0 * m + 21.8 * nnz_a + (op == OP_CHEB ? 552000.0 : 35800.0) * mean + visit * (swapped ? n * nnz_a : m * nnz_b) +
-           (knn ? c.knn_pair : c.pair) * m * n);
+    return (knn ? 61.6e6 : 30.2e6) + make + 5900.0 * m + 5.97 * nnz_a + (op == OP_CHEB ? 865000.0 * staged : 0.0) + launches * std::sqrt(staged) + 2.01e6 * std::sqrt(streamed) +
+           (c.visit + look_up / std::max(1, of.rows)) * (swapped ? n * nnz_a : m * nnz_b) + (knn ? c.knn_pair : c.pair) * m * n;
 }
-// `swapped`: the staged scan would exchange the operands' roles.
-bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const spd_semiring *semiring, bool swapped, bool knn,
-                  bool with_index) {
+// Whether a call is computed by lists over all columns, were an index to keep them (`staged`: the staged scan's estimate).
+bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const spd_semiring *semiring, double staged, bool knn,
+                  bool with_index, double *cost = nullptr) {
     MatchShape s;
     if (semiring || A->n_rows <= 0 || !match_possible(h, B, op, s)) return false;
     if ((knn || with_index) && !match_serves_knn(op)) return false;
@@ -798,13 +796,12 @@ bool match_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     // Both sides measured, staged / lists in ms: 10,000 x 10,000 rows of 38, L1 0.65 / 0.26; 1,024 x 300,000 of 230, cosine
     // 11.4 / 5.2; 4,096 x 65,536 of 1,820, L1 87 / 23.6, Jensen-Shannon 349 / 35; 238 x 6,574 of 95, Canberra, with an index 0.21 / 0.026; 1,000 x
     // 10,000 of 1,360 and 20, L1 0.14 / 0.70; set metrics: 3,247 x 7,668 counts, Jaccard 4.6 / 2.1, 72 x 15,967 rows of 218, k-NN 0.22 / 0.41.
-    return lists_cost(h, A, B, A->n_cols, op, metric, s, knn, with_index, false) <= staged_cost(A, B, op, swapped, knn, with_index);
+    const double lists = lists_cost(h, A, B, op, metric, s, knn, with_index, false);
+    if (cost) *cost = lists;
+    return lists <= staged;
 }
-// The columns that lists over A's columns alone are laid out for (how many A stores, the host does not know).
-int64_t columns_of(const spd_csr *A) { return std::min(A->n_cols, std::max<int64_t>(A->nnz, 1)); }
 // Whether a call is computed by lists over the columns that A stores, after a copy of both operands over these.
-bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const spd_semiring *semiring, bool swapped, bool knn,
-                    bool with_index) {
+bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int op, int metric, const spd_semiring *semiring, double staged, bool knn, bool with_index, double *cost) {
     if (semiring || h->match_lists == 0 || !match_serves_knn(op) || A->n_rows <= 0 || A->nnz <= 0 || B->n_rows <= 0 || B->nnz <= 0) return false;
     if (A->n_cols > kMatchMostColumns) return false;
     const MatchShape s = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
@@ -812,19 +809,13 @@ bool columns_wanted(const spd_handle *h, const spd_csr *A, const spd_csr *B, int
     if (match_items(s, match_grid(h->opt, s, op, A->n_rows, A->nnz, B->nnz, knn), A->n_rows) >= (int64_t)1 << 30) return false;
     if (!match_launches_fit(s, op, A->n_rows, A->nnz, B->n_rows, true)) return false;
     if (h->match_lists == 3) return true;
-    if (h->match_lists != 1 || !scan_knobs_untouched(h) || !match_bounds_fit(s, B->nnz, 4)) return false;
+    if (h->match_lists != 1 || !scan_knobs_untouched(h) || match_dense(B, op) || !match_bounds_fit(s, B->nnz, 4)) return false;
     // Both sides measured, staged / lists over A's columns in ms, k-NN: 4,096 x 500,000 sets over 2^20 columns, Jaccard 30.6 /
     // 6.4, 371 x 33,325 of them, Dice 0.81 / 0.33 (over all columns 0.48), 59 x 15,538 0.51 / 0.24 (0.31); 4,096 x 663,000 rows of 2.2 over 858,000, cosine 5.3 /
-    // 2.0.
-    return lists_cost(h, A, B, columns_of(A), op, metric, s, knn, false, true) <= staged_cost(A, B, op, swapped, knn, with_index);
-}
-constexpr int64_t kMatchFewColumns = 1 << 15;
-// Whether lists over all columns have room for their bounds.  They may not over few columns either: 32,768 of them for 660,000 rows of few entries,
-// 16,384 for two million.  (Staged / over A's columns in us: 200 x 1,000,000 rows of 5 over 32,768, cosine 3,392 / 748, L1, k-NN 3,337 / 780; 3,000 x 900,000
-// of 3, Canberra, k-NN 9,013 / 1,503; 4,096 x 2,000,000 of 2 over 16,384, cosine, k-NN 18,106 / 4,756.)
-bool all_columns_fit(const spd_handle *h, const spd_csr *B, int op) {
-    MatchShape s;
-    return match_possible(h, B, op, s) && match_bounds_fit(s, B->nnz);
+    // 2.0.  Few columns may have no room for their bounds beside many short rows either: 200 x 1,000,000 rows of 5 over 32,768, cosine, pairwise 3.4 / 0.75; 3,000 x
+    // 900,000 of 3, Canberra 9.0 / 1.5; 4,096 x 2,000,000 of 2 over 16,384, cosine 18.1 / 4.8.
+    *cost = lists_cost(h, A, B, op, metric, s, knn, with_index, true);
+    return *cost <= staged;
 }
 // The way a call is computed: 0 the staged scan, 1 lists over all columns, 2 lists over the columns that A stores; and how.
 // `room`: bytes of scratch that there may be.
@@ -833,11 +824,11 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
                    bool with_index, bool index_has_lists, size_t room) {
     MatchWay w;
     const bool knn = knn_k > 0;
-    const bool all = h->match_lists != 3 && match_wanted(h, A, B, op, metric, semiring, swapped, knn, with_index) && (!with_index || index_has_lists);
-    // (where the lists over few columns have room for their bounds and do not pay, neither does a copy; where many rows of B leave them none,
-    // the copy is what there is)
-    const bool of_a = h->match_lists != 2 && (all || h->match_lists == 3 || A->n_cols > kMatchFewColumns || !all_columns_fit(h, B, op)) &&
-                      columns_wanted(h, A, B, op, metric, semiring, swapped, knn, with_index);
+    // (`swapped`: the staged scan would exchange the operands' roles)
+    const double staged = h->match_lists == 1 && !semiring && A->n_rows > 0 && B->n_rows > 0 ? staged_cost(h, A, B, op, metric, swapped, knn, with_index) : 0.0;
+    double over_all = 0.0, over_a = 0.0;
+    const bool all = h->match_lists != 3 && (!with_index || index_has_lists) && match_wanted(h, A, B, op, metric, semiring, staged, knn, with_index, &over_all);
+    const bool of_a = h->match_lists != 2 && columns_wanted(h, A, B, op, metric, semiring, staged, knn, with_index, &over_a);
     auto lay_out = [&](int way) {
         w.way = way;
         w.columns = way == 2 ? columns_of(A) : A->n_cols;
@@ -846,12 +837,9 @@ MatchWay match_way(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
         w.L = layout_match_call(w.s, w.g, op, A->n_rows, A->nnz, B->n_rows, B->nnz, knn_k, way == 2 || !with_index, way == 2 ? A->n_cols : 0);
     };
     if (!all && !of_a) return w;
-    if (all && of_a) {                   // (the copy may cost less than the bounds and the entries of columns that A does not store)
-        const MatchShape over_all = match_shape(h->opt.lds_budget, op, B->n_rows, A->n_cols, B->nnz), over_a = match_shape(h->opt.lds_budget, op, B->n_rows, columns_of(A), B->nnz);
-        if (lists_cost(h, A, B, columns_of(A), op, metric, over_a, knn, false, true, true) < lists_cost(h, A, B, A->n_cols, op, metric, over_all, knn, with_index, false, true)) {
-            lay_out(2);
-            if (w.L.end <= room) return w;            // (it may also take more scratch: with an index the lists over all columns take next to none)
-        }
+    if (all && of_a && over_a < over_all) {          // (the copy may cost less than the bounds and the entries of columns that A does not store)
+        lay_out(2);
+        if (w.L.end <= room) return w;                // (it may also take more scratch)
     }
     lay_out(all ? 1 : 2);
     return w;
@@ -1124,7 +1112,8 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
     metric = effective_metric(metric, p);
     const int op = product_of(h, metric, p);
     const bool swap = knn_k == 0 && !index && swap_wanted(h, A, B, metric, semiring);
-    MatchWay way = match_way(h, A, B, op, metric, semiring, swap, knn_k, index != nullptr, index && index->match.values, scratch_room(h));
+    MatchWay way;
+    auto choose_way = [&] { way = match_way(h, A, B, op, metric, semiring, swap, knn_k, index != nullptr, index && index->match.values, scratch_room(h)); };
 
     // ---- row pointers on the host: the caller's copies, or read back (the call's only
     //      synchronisation) ----------------------------------------------------------------
@@ -1195,7 +1184,8 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
             direct = direct_lanes(h, A, B, op, knn_k, chain, false);
         }
     }
-    bool lists = way.way != 0 && !direct;
+    if (!direct) choose_way();
+    bool lists = way.way != 0;
     while (lists) {
         if (way.way == 1 && index) {
             MatchShape kept = index->match.shape;
@@ -1214,7 +1204,7 @@ spd_status run(spd_handle *h, const spd_csr *A, const spd_csr *B, int metric, fl
         (void)hipGetLastError();
         // (the lists over all columns, where the copy was preferred to them, may still have room)
         const bool copied = way.way == 2;
-        if (copied) way = match_way(h, A, B, op, metric, semiring, swap, knn_k, index != nullptr, index && index->match.values, scratch_room(h));
+        if (copied) choose_way();
         lists = copied && way.way == 1;
     }
     swapped = swap && !lists && !direct;
@@ -2071,11 +2061,15 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     const int run_as = effective_metric((int)metric, p), op = product_of(&h, run_as, p);
     const bool knn = k_neighbors > 0, swap = !knn && !with_index && swap_wanted(&h, &A, &B, run_as, nullptr);
     std::memset(out, 0, sizeof *out);
-    out->wanted = match_wanted(&h, &A, &B, op, run_as, nullptr, swap, knn, with_index != 0);
+    out->wanted = match_wanted(&h, &A, &B, op, run_as, nullptr, a_rows > 0 && b_rows > 0 ? staged_cost(&h, &A, &B, op, run_as, swap, knn, with_index != 0) : 0.0, knn, with_index != 0);
     MatchShape kept;
     MatchLayout L;
     const bool keeps = index_keeps_lists(&h, &B, op, kept, L);
     out->index_bytes = keeps ? (int64_t)L.end : 0;
+    out->index_aligned = keeps ? kept.aligned : 0;
+    const Staging staging = staging_of(n_cols, run_as, op, knn, swap ? (double)b_nnz / (double)std::max<int64_t>(b_rows, 1) : (double)a_nnz / (double)std::max<int64_t>(a_rows, 1), h.opt);
+    out->staged_kind = staging.kind;
+    out->staged_rows = staging.rows;
     MatchWay w = match_way(&h, &A, &B, op, run_as, nullptr, swap, k_neighbors, with_index != 0, keeps, scratch_room(&h));
     if (w.way != 0 && h.ws_external && w.L.end > h.ws_bytes) w.way = 0;
     out->way = w.way;
@@ -2087,6 +2081,8 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
         w.L = layout_match_call(w.s, w.g, op, a_rows, a_nnz, b_rows, b_nnz, k_neighbors, !with_index, 0);
     }
     out->columns = w.columns;
+    out->block_columns = (int64_t)1 << w.s.block_shift;
+    out->aligned = w.s.aligned;
     out->tiles = w.s.n_tiles;
     out->tile_rows = w.s.tile_rows;
     out->slices = w.g.slices;

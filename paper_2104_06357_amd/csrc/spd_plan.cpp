@@ -271,8 +271,8 @@ bool staging_fits(int kind, int R, uint64_t sumlen, uint32_t k, bool cheb, int64
 
 }  // namespace
 
-std::string plan_staging(int64_t n_cols, int metric, int op, bool knn, const PlanOptions &opt, int &kind, int &max_r,
-                         int &min_r, uint64_t &dmax) {
+// The kind, and how many rows it would stage at most and at least were LDS no limit.
+static std::string staging_kind(int64_t n_cols, int metric, int op, bool knn, const PlanOptions &opt, int &kind, int &max_r, int &min_r) {
     const bool cheb = sum_is_max(metric);
     const uint32_t k = (uint32_t)n_cols;
     max_r = std::min(opt.max_rows, 16);
@@ -304,7 +304,17 @@ std::string plan_staging(int64_t n_cols, int metric, int op, bool knn, const Pla
         else if ((int64_t)bitmap_words(k) * 8 <= budget / 3) kind = KIND_BITMAP;
         else kind = KIND_HASH;
     }
-    if (kind < KIND_STRIP || kind > KIND_BITMAP) return "bad staging kind";
+    return kind < KIND_STRIP || kind > KIND_BITMAP ? "bad staging kind" : std::string();
+}
+std::string plan_staging(int64_t n_cols, int metric, int op, bool knn, const PlanOptions &opt, int &kind, int &max_r,
+                         int &min_r, uint64_t &dmax) {
+    const std::string why = staging_kind(n_cols, metric, op, knn, opt, kind, max_r, min_r);
+    if (!why.empty()) return why;
+    const bool cheb = sum_is_max(metric);
+    const uint32_t k = (uint32_t)n_cols;
+    auto words = [&](int R) { return table_words(op, R); };
+    auto lists = [&](int R) { return knn ? (uint32_t)R : 0u; };
+    const int64_t budget = opt.lds_budget - kStaticLds;
     dmax = 0;
     if (kind == KIND_BLOOM) {
         if (!bloom_serves(op)) return "Bloom staging does not serve this product";
@@ -325,6 +335,18 @@ std::string plan_staging(int64_t n_cols, int metric, int op, bool knn, const Pla
     }
     dmax = lo;
     return std::string();
+}
+
+Staging staging_of(int64_t n_cols, int metric, int op, bool knn, double length, const PlanOptions &opt) {
+    int kind = 0, max_r = 1, min_r = 1;
+    if (!staging_kind(n_cols, metric, op, knn, opt, kind, max_r, min_r).empty()) return Staging{0, 0};
+    const double entries = std::min(length, (double)n_cols);
+    auto fits = [&](int R) {
+        return staging_fits(kind, table_words(op, R), (uint64_t)(R * entries), (uint32_t)n_cols, sum_is_max(metric), opt.lds_budget - kStaticLds, knn ? (uint32_t)R : 0u);
+    };
+    if (kind == KIND_BLOOM) max_r = 1;
+    else while (max_r > min_r && !fits(max_r)) max_r /= 2;
+    return Staging{kind, max_r};
 }
 
 // ------------------------------------------------------------------------------------

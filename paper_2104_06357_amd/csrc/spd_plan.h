@@ -261,6 +261,10 @@ struct BPlan {
 std::string plan_staging(int64_t n_cols, int metric, int op, bool knn, const PlanOptions &opt, int &kind, int &max_r,
                          int &min_r, uint64_t &dmax);
 
+// How many rows of `length` entries are staged together, and behind which kind of map (0: none is).
+struct Staging { int kind, rows; };
+Staging staging_of(int64_t n_cols, int metric, int op, bool knn, double length, const PlanOptions &opt);
+
 // What plan_a and plan_b find wrong with row pointers, for the calls that run without their plans: empty
 // if nothing.  No row may hold more than `longest` entries; `found` receives how many the longest holds.
 std::string check_rows(const int64_t *indptr, int64_t n_rows, int64_t longest, int64_t *found = nullptr);

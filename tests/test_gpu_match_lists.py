@@ -332,7 +332,7 @@ def test_scratch_for_the_lists_over_all_columns_alone(spd):
     """Scratch that holds the lists over all columns and not the copy, which would be preferred: the bits of the former."""
     import torch
     rng = np.random.default_rng(83)
-    m, n, cols, nnz = 283, 83_003, 74_017, 2_663_779
+    m, n, cols, nnz = 133, 13_649, 328_013, 2_082_360
 
     def matrix(rows, entries):
         cell = np.unique(rng.integers(0, rows * cols, size=entries))
@@ -340,20 +340,20 @@ def test_scratch_for_the_lists_over_all_columns_alone(spd):
         return spd.DeviceCsr.from_host({"n_rows": rows, "n_cols": cols, "indptr": indptr, "indices": (cell % cols).astype(np.int32),
                                         "values": (rng.random(len(cell)) + 0.01).astype(np.float32)})
 
-    dA, dB = matrix(m, 984), matrix(n, nnz)
-    sizes = (m, dA.nnz, n, dB.nnz, cols, "hellinger")
+    dA, dB = matrix(m, 137), matrix(n, nnz)
+    sizes = (m, dA.nnz, n, dB.nnz, cols, "l2_expanded")
     plans = [spd.testing.host_list_plan(*sizes, match_lists=way) for way in (1, 2)]
     assert plans[0]["way"] == 2 and plans[1]["scratch_bytes"] < plans[0]["scratch_bytes"]
-    want = _lists(spd).pairwise(dA, dB, "hellinger")
+    want = _lists(spd).pairwise(dA, dB, "l2_expanded")
     h = spd.Handle()
     h.set_option("check_plan", 1)
     h.set_option("profile", 1)
     h.set_workspace(torch.empty(plans[1]["scratch_bytes"] + 4_096, dtype=torch.uint8, device="cuda"))
-    assert torch.equal(h.pairwise(dA, dB, "hellinger"), want)
+    assert torch.equal(h.pairwise(dA, dB, "l2_expanded"), want)
     names = {r["name"] for r in h.profile_read()}
     assert "lists_b" in names and "columns" not in names
     h.set_workspace(torch.empty(plans[0]["scratch_bytes"], dtype=torch.uint8, device="cuda"))
-    assert torch.allclose(h.pairwise(dA, dB, "hellinger"), want, rtol=2.5e-7, atol=1e-7)
+    assert torch.allclose(h.pairwise(dA, dB, "l2_expanded"), want, rtol=2.5e-7, atol=1e-7)
     assert "columns" in {r["name"] for r in h.profile_read()}
     h.close()
 

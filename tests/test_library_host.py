@@ -424,9 +424,32 @@ def test_many_short_rows_over_few_columns_take_the_copy():
         assert plan["way"] == 2 and plan["consistent"], (m, n, mean, cols, metric, plan)
 
 
+def test_calls_that_estimates_without_maps_and_launches_sent_the_slower_way():
+    def plan(m, nnz_a, n, nnz_b, cols, metric, k, with_index):
+        return spd.testing.host_list_plan(m, nnz_a, n, nnz_b, cols, metric, p=3.0, k_neighbors=k, with_index=with_index)
+
+    # staged / lists over all columns / over A's in us
+    for want, call in ((2, (10, 17_433, 653_968, 19_871_029, 801_333, "minkowski", 0, False)),           # 5,231 / 6,300 / 771
+                       (2, (48, 16_506, 16_102, 1_135_587, 1_953_194, "kl_divergence", 0, False)),       # 469 / 318 / 102
+                       (2, (275, 46_199, 256_474, 34_595_634, 1_048_576, "dice", 1, False)),             # 3,838 / - / 1,176
+                       (2, (417, 117_487, 72_252, 9_886_247, 1_048_447, "russell_rao", 5, False)),       # 1,650 / - / 468
+                       (2, (773, 259_693, 81_326, 14_935_108, 1_324_059, "russell_rao", 32, True)),      # 1,854 / - / 614
+                       (2, (79, 1_347, 66_155, 699_988, 548_212, "jensen_shannon", 0, True)),            # 321 / - / 104
+                       (0, (3_035, 2_460_418, 251, 546, 1_558_033, "l1", 0, True)),                      # 63 / - / 247
+                       (0, (245, 114_662, 2_392, 12_094, 17_153, "l2_unexpanded", 32, False)),           # 61 / 192 / 233
+                       (0, (222, 95_908, 4_494, 1_493_679, 121_762, "hamming", 0, False)),               # 135 / 408 / 460
+                       (0, (148, 164_243, 11_371, 7_706_568, 10_950, "inner_product", 0, True))):        # 204 / 567 / 777
+        assert plan(*call)["way"] == want, call
+    # the scan's maps: a strip of few columns, slots, a bitmap, a table, and fewer rows of them the longer they are
+    kinds = [plan(1_000, 40_000, 20_000, 800_000, cols, "l1", 0, False)["staged_kind"] for cols in (2_000, 20_000, 100_000, 400_000)]
+    assert kinds == [1, 2, 5, 3]
+    rows = [plan(1_000, 1_000 * mean, 20_000, 800_000, 100_000, "l1", 0, False)["staged_rows"] for mean in (40, 2_000, 8_000, 30_000)]
+    assert rows == sorted(rows, reverse=True) and rows[0] == 8 and rows[-1] == 1, rows
+
+
 def test_scratch_for_the_lists_over_all_columns_alone():
     """Where the copy over A's columns is preferred and takes more scratch than there is, the lists over all columns serve the call."""
-    for call, k in (((283, 984, 83_003, 2_663_779, 74_017, "hellinger"), 0), ((115, 2_105, 209_197, 2_773_272, 60_897, "russell_rao"), 10)):
+    for call, k in (((133, 137, 13_649, 2_082_360, 328_013, "l2_expanded"), 0), ((39, 131, 78_887, 2_049_022, 69_229, "inner_product"), 10)):
         plan = lambda **more: spd.testing.host_list_plan(*call, k_neighbors=k, **more)
         free, all_columns = plan(), plan(match_lists=2)
         assert free["way"] == 2 and all_columns["scratch_bytes"] < free["scratch_bytes"]
