@@ -168,8 +168,8 @@ spd_status spd_knn(spd_handle *handle, const spd_csr *Q, const spd_csr *Index, s
  * column lists (option "match_lists" as it stands at creation) and they take no more than that, up to 20
  * bytes per stored entry, 16 per row and 1 MiB more); spd_index_pairwise /
  * spd_index_knn then return what spd_pairwise / spd_knn return for the same operands: bit for bit where
- * both take the same way (k-NN calls do wherever the index keeps the lists; a pairwise call without an index may
- * exchange its operands' roles, and with them the way it takes), and else to the last place.
+ * both take the same way (a call without an index also pays for what it makes of B, and a pairwise one may
+ * exchange its operands' roles: either may find another way the faster), and else to the last place.
  * The index keeps the pointers of `Index`, not a copy: the three arrays must stay valid and
  * unchanged until spd_index_destroy.  The work is enqueued on the creating handle's stream; use
  * the index with that handle (or, after synchronising its stream, with another handle on the same
@@ -322,10 +322,10 @@ spd_status spd_csr_validate(spd_handle *handle, const spd_csr *M, int require_no
  *                 listed by column, and a wavefront walks the lists of its row of A, so that only the
  *                 columns two rows share cost anything (Chebyshev pairwise and without an index only; not for the
  *                 semirings that are not spelled as a distance).  1 (default): where it pays (sparse and long enough operands, A's
- *                 rows not too long against B's, no knob of the staged scan turned), over very many columns
- *                 after a copy of both operands over the columns that A stores; 0: never; 2: wherever the product
+ *                 rows not too long against B's, no knob of the staged scan turned), where that costs less or there is no room
+ *                 for the lists over all columns after a copy of both operands over the columns that A stores; 0: never; 2: wherever the product
  *                 has it; 3: the same, over A's columns.  A call whose lists the caller's scratch does not hold, or the device
- *                 has no memory for, runs by the staged scan; the handle asks the device for that much again
+ *                 has no memory for, runs by the lists over all columns if these fit and pay and else by the staged scan; the handle asks the device for that much again
  *                 only after the option is set again.  The sums' order differs between the two ways.
  *   "direct"      1 (default): a small call (up to 2,048 columns, 2^19 pairs, 2^16 stored entries an operand, 2^15 rows of B, k-NN
  *                 over up to 1,024; not Chebyshev and the semirings that are not spelled as a distance; no other

@@ -650,7 +650,7 @@ std::string match_check(const PlanOptions &opt, const MatchShape &s, const Match
     if (s.aligned && 1.3125 * std::min((double)nnz_b, (double)T * (double)n_cols) + (double)s.tile_extra >= (double)s.position_bits())
         return "list positions and gaps";
     const int64_t build = (int64_t)s.stage * 6 + ((int64_t)4 << s.block_shift) + 4 * T;
-    if ((int64_t)s.build_lds_bytes != build || s.stage % 8 != 0 || build + 1024 > opt.lds_budget) return "build over the LDS";
+    if ((int64_t)s.build_lds_bytes != build || s.stage % 8 != 0 || (build + 1024) * kBuildPerCu > opt.lds_budget) return "build over the LDS";
     if (g.slices < 1 || g.groups < 1 || g.run < 1 || g.run > tiles || g.groups > tiles || (g.by_xcd && g.groups < tiles && g.groups % 8 != 0)) return "grid";
     if (match_items(s, g, m) >= (int64_t)1 << 30) return "(tile, row)s of a workgroup";
     return std::string();

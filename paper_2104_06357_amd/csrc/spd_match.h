@@ -118,6 +118,7 @@ struct MatchColumns {
 
 constexpr int64_t kMatchMostColumns = 1 << 28;    // that are renumbered (16 bytes per 64 of them)
 constexpr uint32_t kBuildDense = 64, kBuildDensePer = 32;          // dense columns of a block at most, and that have room of their own
+constexpr int kBuildPerCu = 2;                  // workgroups of the build that share a compute unit's LDS
 constexpr int kMatchRowLocks = 64;              // of a group, by row
 constexpr int kMatchStagingKind = 6;            // how spd_profile_read names this kernel's staging
 constexpr int64_t kMatchL2Bytes = 4 << 20;      // of one XCD

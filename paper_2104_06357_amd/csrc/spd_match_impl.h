@@ -861,7 +861,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                 });
             };
             // Whether a row that shares no column could pass: the distances of one sum grow with the row's first norm, so none is
-            // nearer than the tile's row of the least.  (Correlation's do not.)
+            // nearer than the tile's row of the least.  (Correlation's do not: few_only stands for one norm a row.)
             bool few_only = false;
             if constexpr (S::kOne) {
                 if (!BOTH && few.total <= 4 * F) {
@@ -897,7 +897,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                         if ((uint32_t)(lane & 15) * 4u < few.left[0]) met[0] = S::take(strip_at + few.cell[0]);
                         i[0] = S::is_zero(met[0]) ? tile_n : (int)(few.cell[0] / S::kUnit);
                         const int64_t j = j0 + min(i[0], tile_n - 1);
-                        const RowNorms nb[1] = {{args.norms_b[j], BOTH ? args.b.norms[args.n + j] : 0.0}};
+                        const RowNorms nb[1] = {{args.norms_b[j], 0.0}};
                         float formed[1] = {0.0f};
                         distances(formed, met, nb);
                         d[0] = i[0] < tile_n ? formed[0] : __builtin_nanf("");
@@ -920,11 +920,7 @@ __global__ void __launch_bounds__(match_waves(match_cell_bytes(OP)) * kWave) spd
                             for (int u = 0; u < F; ++u) {
                                 i[u] = S::is_zero(c[u]) ? tile_n : (int)(few.cell[u] / S::kUnit);
                                 nb[u] = RowNorms{0.0, 0.0};
-                                if (few.total > 4 * u) {
-                                    const int64_t j = j0 + min(i[u], tile_n - 1);
-                                    nb[u].x = args.norms_b[j];
-                                    if (BOTH) nb[u].y = args.b.norms[args.n + j];
-                                }
+                                if (few.total > 4 * u) nb[u].x = args.norms_b[j0 + min(i[u], tile_n - 1)];
                             }
                         }
                     } else {
