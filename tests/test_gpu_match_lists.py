@@ -984,29 +984,107 @@ def test_lists_that_begin_at_lines(spd, metric, stored):
 
 
 # Blocks of the build: one that stores far more entries than a workgroup's lanes hold (nearly all rows store the same 70 columns of
-# thousands), rows whose stretch of a block is most of it, no more entries than are looked at together, and tiles of more rows than lanes.
-@pytest.mark.parametrize("metric", ["l1", "cosine", "hellinger", "jaccard", "minkowski", "chebyshev"])
-@pytest.mark.parametrize("kind", ["full block", "long rows", "few entries"])
+# thousands), rows whose stretch of a block is most of it, in all no more entries than are looked at together, in one block and on both sides of
+# blocks' ends; with tiles of up to three rows to a lane, ("long tile") of up to five and ("short tile") of one.
+@pytest.mark.parametrize("metric", ["l1", "cosine", "hellinger", "jaccard", "hamming", "minkowski", "chebyshev"])
+@pytest.mark.parametrize("kind", ["full block", "long tile", "short tile", "long rows", "few entries", "few entries of several blocks"])
 def test_blocks_of_the_build(spd, metric, kind):
     rng = np.random.default_rng(3)
-    n, cols = (2_600, 9_000) if kind == "full block" else ((1_100, 12_000) if kind == "long rows" else (3, 40))
+    n, cols = {"full block": (2_600, 9_000), "long tile": (2_400, 9_000), "short tile": (900, 9_000), "long rows": (1_100, 12_000), "few entries": (3, 40),
+               "few entries of several blocks": (3, 9_000)}[kind]
+    budget = 40_000 if kind == "short tile" else 163_840
+    cut = spd.testing.host_list_plan(30, 2_000, n, {"few entries": 7, "few entries of several blocks": 7, "long rows": 26_000}.get(kind, 62 * n), cols, metric,
+                                     _p_of(metric), match_lists=2, lds_budget=budget)
+    width = cut["block_columns"]
+    assert kind != "long tile" or metric not in ("jaccard", "hamming") or cut["tile_rows"] > 3 * 512
+    assert kind != "short tile" or cut["tile_rows"] <= 512
+    assert (width < cols) == (kind != "few entries")
     rows = []
     for r in range(n):
-        if kind == "full block":
+        if kind in ("full block", "long tile", "short tile"):
             c = np.concatenate([100 + rng.choice(70, size=60, replace=False), rng.integers(0, cols, size=2)])
         elif kind == "long rows":
             c = rng.choice(cols, size=11_000, replace=False) if r in (3, 700) else rng.integers(0, cols, size=4)
-        else:
+        elif kind == "few entries":
             c = rng.integers(0, cols, size=(2, 0, 3)[r])
-        rows.append(np.unique(c))
+        else:
+            c = ((0, width - 1, width, cols - 1), (), (width - 1, width + 1, 2 * width))[r]
+        rows.append(np.unique(np.asarray(c, dtype=np.int64)))
     indptr = np.concatenate([[0], np.cumsum([len(c) for c in rows])]).astype(np.int64)
     B = {"n_rows": n, "n_cols": cols, "indptr": indptr, "indices": np.concatenate(rows).astype(np.int32),
          "values": (rng.integers(0, 17, size=int(indptr[-1])) / 8.0).astype(np.float32)}
-    A = _matrix(rng, 30, cols, (3, 64, 65, 1, 130, 0, 17, 2_000))
+    if kind == "few entries of several blocks":
+        assert 0 < len(B["values"]) < 8
+        B["values"] = 1.0 + np.arange(len(B["values"]), dtype=np.float32) / 8.0
+    A = _matrix(rng, 30, cols, (3, 64, 65, 1, 130, 0, 17, cols if kind == "few entries of several blocks" else 2_000))
     print("blocks of the build", metric, kind, flush=True)
-    h = _lists(spd, profile=1)
+    h = _lists(spd, profile=1, lds_budget=budget)
     p = _p_of(metric)
     got = _np(h.pairwise(spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B), metric, p))
     assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
     assert_distances_close(got, oracle.pairwise(A, B, ORACLE_NAME[metric], p), metric)
+    h.close()
+
+
+# Many rows, several of which a wavefront sums one after the other: of 4,096 entries and more among those of one wavefront, at its ends and at the ends of a
+# workgroup's and of all, with short and empty ones between.  As B's rows, and as A's, whose scales are found with the norms.
+@pytest.mark.parametrize("metric", ["cosine", "correlation", "l2_expanded", "l1", "canberra", "jensen_shannon", "minkowski"])
+def test_norms_of_many_rows_with_long_ones_among_them(spd, metric):
+    rng = np.random.default_rng(29)
+    n, cols = 65_600, 9_000
+    lengths = rng.integers(0, 36, size=n)
+    lengths[[0, 3, 4, 7, 8, 31, 32, 40_000, 40_001, n - 9, n - 1]] = (4_096, 4_097, 9_000, 5_000, 4_097, 8_000, 4_100, 6_000, 4_095, 7_000, 4_500)
+    parts = [np.unique(rng.integers(0, cols, size=L)) if L < 4_000 else np.sort(rng.choice(cols, size=L, replace=False)) for L in lengths]
+    indptr = np.concatenate([[0], np.cumsum([len(c) for c in parts])]).astype(np.int64)
+    assert 16 * n <= indptr[-1] <= 256 * n                     # (a wavefront to the row; eight rows of so many)
+    B = {"n_rows": n, "n_cols": cols, "indptr": indptr, "indices": np.concatenate(parts).astype(np.int32),
+         "values": (rng.integers(1, 17, size=int(indptr[-1])) / 8.0).astype(np.float32)}
+    A = _matrix(rng, 12, cols, (3, 64, 65, 1, 130, 0, 17, 4_500))
+    p = _p_of(metric)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], p)
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = _lists(spd, profile=1)
+    print("norms of many rows", metric, flush=True)
+    assert_distances_close(_np(h.pairwise(dA, dB, metric, p)), want, metric)
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    assert_distances_close(_np(h.pairwise(dB, dA, metric, p)), want.T, metric + ", the long operand first")
+    h.close()
+
+
+# An index whose lists would take more than it may keep if they began at lines of memory, and do not without the gaps: such lists are kept, and calls that
+# lay theirs out with gaps go by them.
+@pytest.mark.parametrize("metric,nnz", [("cosine", 240_000), ("l1", 200_000), ("canberra", 200_000), ("jensen_shannon", 200_000), ("hamming", 152_000),
+                                        ("kl_divergence", 230_000), ("minkowski", 286_000)])
+def test_an_index_that_keeps_its_lists_without_gaps(spd, metric, nnz):
+    rng = np.random.default_rng(35)
+    n, cols = 3_500, 160_000
+    heavy = np.concatenate([c + cols * rng.choice(n, size=15 + 16 * c, replace=False) for c in range(80)])          # 15 to 1,279 rows store these columns
+    light = np.setdiff1d(np.unique(rng.integers(0, n * cols, size=nnz)), heavy)
+    cell = np.sort(np.concatenate([heavy, rng.choice(light, size=nnz - len(heavy), replace=False)]))
+    B = {"n_rows": n, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum(np.bincount(cell // cols, minlength=n))]).astype(np.int64),
+         "indices": (cell % cols).astype(np.int32), "values": (rng.integers(1, 17, size=nnz) / 8.0).astype(np.float32)}
+    cell = np.unique(np.concatenate([r * cols + np.unique(np.concatenate([rng.integers(0, 90, size=30), rng.integers(0, cols, size=12)])) for r in range(60)]))
+    A = {"n_rows": 60, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum(np.bincount(cell // cols, minlength=60))]).astype(np.int64),
+         "indices": (cell % cols).astype(np.int32), "values": (rng.integers(1, 17, size=len(cell)) / 8.0).astype(np.float32)}
+    p = _p_of(metric)
+    plan = spd.testing.host_list_plan(60, len(cell), n, nnz, cols, metric, p, with_index=True)
+    assert plan["index_bytes"] > 0 and not plan["index_aligned"] and plan["aligned"], plan
+    dA, dB = spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B)
+    h = spd.Handle()
+    h.set_option("check_plan", 1)
+    h.set_option("profile", 1)
+    index = h.index_create(dB, metric, p)
+    h.set_option("match_lists", 2)
+    print("index without gaps", metric, flush=True)
+    want = oracle.pairwise(A, B, ORACLE_NAME[metric], p)
+    got = index.pairwise(dA)
+    names = [(r["name"], r["staging_kind"]) for r in h.profile_read()]
+    assert ("scan", 6) in names and "lists_b" not in [name for name, _ in names], names
+    assert_distances_close(_np(got), want, metric)
+    idx, dist = index.knn(dA, 20)
+    assert ("scan", 6) in [(r["name"], r["staging_kind"]) for r in h.profile_read()]
+    assert_knn_matches(_np(idx), _np(dist), want, 20, metric, metric)
+    if metric in ("l1", "canberra", "hamming"):                # (sums that no order changes)
+        assert np.array_equal(_np(got), _np(h.pairwise(dA, dB, metric, p)))
+    index.close()
     h.close()
