@@ -34,7 +34,8 @@ struct MatchShape {
     int32_t tile_rows, n_tiles, waves;      // n_tiles 0: the product or the sizes do not fit
     int32_t block_shift, blocks, dense_shift, dense_per, dense_from;      // dense_from: entries that make a column dense
     uint32_t stage;                         // entries of a block that pass through LDS together
-    int32_t aligned;                        // 1: lists of kMatchLine entries or more and dense columns begin at multiples of kMatchLine, see below
+    int16_t held;                           // entries that a lane of the build holds
+    int16_t aligned;                        // 1: lists of kMatchLine entries or more and dense columns begin at multiples of kMatchLine, see below
     int64_t ptr_stride, tile_extra;         // words of a tile's list bounds; entries beyond the tile's own
     uint32_t lds_bytes, build_lds_bytes;
     SPD_HD int32_t dense_before(int32_t block) const { return (int32_t)(((int64_t)block * dense_per + (1 << (dense_shift - block_shift)) - 1) >> (dense_shift - block_shift)); }

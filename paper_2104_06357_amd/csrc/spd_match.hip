@@ -311,7 +311,9 @@ hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const Ran
 // rows of 230 936 / 850, 65,536 of 1,820 917 / 805, 500,000 sets 895 / 860; as before, a few lanes to every row, 49, 36, 131, 81, 1,096, 972, 1,582.)
 constexpr int kBuildThreads = 512;
 constexpr int build_rows(int tile_rows) { return tile_rows <= kBuildThreads ? 1 : (tile_rows <= 3 * kBuildThreads ? 3 : 5); }          // of a lane
-constexpr int build_held(int rows) { return rows == 1 ? 24 : 16; }          // entries that a lane holds
+// Entries that a lane holds: fewer of a lane with more rows, whose ends take registers too, but where the half as many again make blocks of twice the columns.
+constexpr int kBuildHeld = 16, kBuildHeldMore = 24;
+constexpr int build_held(int rows) { return rows == 1 ? kBuildHeldMore : kBuildHeld; }
 constexpr int kBuildProbe = 8;                                              // entries that a lane looks at together
 // A block of more entries than the lanes hold is gone through twice, so many at a time.
 constexpr uint32_t kBuildWindow = 8192;
@@ -355,13 +357,13 @@ __device__ __forceinline__ Stretch then(const Stretch &x, const Stretch &y) {
 struct __align__(16) Eight { uint16_t v[8]; };
 struct __align__(16) Four { float v[4]; };
 
-template <int R>
+template <int R, int K>
 __global__ void __launch_bounds__(kBuildThreads, 4) spd_match_build_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                         const float *__restrict__ values, int64_t n_rows, int64_t nnz,
                                                                         uint32_t most_cols, MatchB b, uint32_t blocks_per_wg, uint32_t wgs, int unit,
                                                                         int transform, bool with_values, bool positive, const RowsVerdict seen) {
     if (rows_malformed(seen)) return;
-    constexpr int nw = kBuildThreads / kWave, K = build_held(R);
+    constexpr int nw = kBuildThreads / kWave;
     extern __shared__ __align__(16) unsigned char s_raw[];
     __shared__ uint32_t s_wave[nw], s_second[nw], s_lens[R][nw], s_first[nw], s_dense[kBuildDense];
     __shared__ double s_least[nw][2];
@@ -872,11 +874,25 @@ MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, in
         s.dense_per = dense_of(shift);
     }
     // Two workgroups to a compute unit, since what a block takes is mostly waiting for one thing after the other.
-    const int64_t usable = lds_budget / kBuildPerCu - 1024, rows_bytes = 4 * (int64_t)s.tile_rows, held = build_held(build_rows(s.tile_rows)) * kBuildThreads;
+    const int64_t usable = lds_budget / kBuildPerCu - 1024, rows_bytes = 4 * (int64_t)s.tile_rows;
     if (usable < rows_bytes + 2048) return s;
-    int shift = s.dense_shift;
-    while (shift > 2 && ((4 << shift) > usable / 4 ||
-                         per_col * (double)(1 << shift) * 1.25 > (double)std::min(stage_of(usable, rows_bytes, shift), held))) --shift;
+    // A block as wide as its entries fit on the mean and a twelfth more (columns that are uniform fill the blocks of a tile alike: 60,000 rows of 1,820, KL, blocks of 64 columns
+    // 1,671 us, of 128, 91 % full, 1,035; where they are not, wider blocks pay all the same: 300,000 rows of 230 899 / 699), and a quarter more where that leaves the chip less
+    // than its two workgroups to a compute unit (8,000 of these 32 / 44).  Jensen-Shannon's 1,551 us are 1,087 with lanes that hold half as many again, and so twice the
+    // columns; held for nothing these cost a tenth (KL 1,035 / 1,200, ratings 385 / 432).
+    auto widest = [&](int64_t held, double spare) {
+        int shift = s.dense_shift;
+        while (shift > 2 && ((4 << shift) > usable / 4 ||
+                             per_col * (double)(1 << shift) * spare > (double)std::min(stage_of(usable, rows_bytes, shift), held * kBuildThreads))) --shift;
+        return shift;
+    };
+    const int lane_rows = build_rows(s.tile_rows);
+    int held = build_held(lane_rows), shift = widest(held, 1.25);
+    const int wider = widest(held, 1.08), more = lane_rows == 3 ? widest(kBuildHeldMore, 1.08) : wider;
+    auto fills = [&](int at) { return tiles_now * blocks_of(at) >= 256 * kBuildPerCu; };
+    if (wider > shift && fills(wider)) shift = wider;
+    if (more > shift && fills(more)) { shift = more; held = kBuildHeldMore; }
+    s.held = (int16_t)held;
     s.block_shift = shift;
     s.stage = (uint32_t)stage_of(usable, rows_bytes, shift);
     s.blocks = (int32_t)blocks_of(shift);
@@ -914,8 +930,8 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
     if (n_rows <= 0) return hipSuccess;
     const MatchShape &s = b.shape;
     const uint32_t per_wg = match_build_blocks(s), wgs = ((uint32_t)s.blocks + per_wg - 1u) / per_wg;
-    auto go = [&](auto rows) {
-        auto kern = spd_match_build_kernel<decltype(rows)::value>;
+    auto go = [&](auto rows, auto held) {
+        auto kern = spd_match_build_kernel<decltype(rows)::value, decltype(held)::value>;
         static std::atomic<uint32_t> allowed[kMatchDevices];
         hipError_t err = allow_lds(kern, allowed, s.build_lds_bytes, 1024u);
         if (err != hipSuccess) return err;
@@ -923,10 +939,12 @@ hipError_t launch_match_build(hipStream_t st, const int64_t *indptr, const int32
                            nnz, k, b, per_wg, wgs, op == OP_CHEB ? 1 : (match_cell_bytes(op) >= 8 ? 8 : 4), transform, op != OP_CNT, op == OP_JS || op == OP_KL, seen);
         return hipGetLastError();
     };
+    constexpr std::integral_constant<int, kBuildHeld> few{};
+    constexpr std::integral_constant<int, kBuildHeldMore> more{};
     switch (build_rows(s.tile_rows)) {
-    case 1: return go(std::integral_constant<int, 1>{});
-    case 3: return go(std::integral_constant<int, 3>{});
-    default: return go(std::integral_constant<int, 5>{});
+    case 1: return go(std::integral_constant<int, 1>{}, more);
+    case 3: return s.held == kBuildHeld ? go(std::integral_constant<int, 3>{}, few) : go(std::integral_constant<int, 3>{}, more);
+    default: return go(std::integral_constant<int, 5>{}, few);
     }
 }
 

@@ -1026,6 +1026,30 @@ def test_blocks_of_the_build(spd, metric, kind):
     h.close()
 
 
+# Blocks as wide as what lanes hold fits: nine tenths full and, of a few thousand, some beyond (which are gone through twice), with the 16 entries of a lane
+# and, where that doubles the width, 24.
+@pytest.mark.parametrize("metric", ["kl_divergence", "jensen_shannon", "chebyshev", "cosine"])
+def test_full_blocks_of_the_build(spd, metric):
+    rng = np.random.default_rng(71)
+    n, cols = 12_200, 6_600
+    share = np.exp(0.35 * rng.standard_normal(cols)).clip(0.5, 2.0)
+    share *= 0.0695 / share.mean()
+    rows, indices = np.nonzero(rng.random((n, cols), dtype=np.float32) < share)
+    B = {"n_rows": n, "n_cols": cols, "indptr": np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int64),
+         "indices": indices.astype(np.int32), "values": (rng.integers(1, 17, size=len(indices)) / 8.0).astype(np.float32)}
+    A = _matrix(rng, 30, cols, (3, 64, 65, 1, 130, 0, 17, 2_000))
+    cut = spd.testing.host_list_plan(30, int(A["indptr"][-1]), n, len(indices), cols, metric, match_lists=2)
+    entries = len(indices) / cols * cut["tile_rows"] / n * cut["block_columns"]
+    held = (16 if metric in ("kl_divergence", "chebyshev") else 24) * 512
+    assert cut["block_columns"] == 128 and held / 1.25 < entries < held / 1.08, (cut, entries)
+    print("full blocks", metric, flush=True)
+    h = _lists(spd, profile=1)
+    got = _np(h.pairwise(spd.DeviceCsr.from_host(A), spd.DeviceCsr.from_host(B), metric))
+    assert {r["staging_kind"] for r in h.profile_read() if r["name"] == "scan"} == {6}
+    assert_distances_close(got, oracle.pairwise(A, B, ORACLE_NAME[metric]), metric)
+    h.close()
+
+
 # Many rows, several of which a wavefront sums one after the other: of 4,096 entries and more among those of one wavefront, at its ends and at the ends of a
 # workgroup's and of all, with short and empty ones between.  As B's rows, and as A's, whose scales are found with the norms.
 @pytest.mark.parametrize("metric", ["cosine", "correlation", "l2_expanded", "l1", "canberra", "jensen_shannon", "minkowski"])

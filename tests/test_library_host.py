@@ -410,6 +410,19 @@ def test_lists_over_the_columns_of_a_where_they_were_measured_the_faster():
         assert way(*call) == 0, call
 
 
+def test_blocks_of_the_build_are_as_wide_as_their_entries_fit():
+    def columns(n, mean, cols, metric):
+        return spd.testing.host_list_plan(32, 32 * mean, n, n * mean, cols, metric, match_lists=2)["block_columns"]
+
+    # the build in us, narrower / so
+    assert columns(60_000, 1_824, 26_000, "kl_divergence") == 128                                        # 1,671 / 1,042
+    assert columns(60_000, 1_824, 26_000, "chebyshev") == 128                                            # 2,009 / 1,250
+    assert columns(60_000, 1_824, 26_000, "jensen_shannon") == 128                                       # 1,551 / 1,105
+    assert columns(300_000, 228, 102_660, "kl_divergence") == 4_096                                      # 899 / 701
+    # two workgroups to a compute unit come first: 31.7 / 43.8 with the wider
+    assert columns(8_000, 228, 102_660, "kl_divergence") == 2_048
+
+
 def test_many_short_rows_over_few_columns_take_the_copy():
     """The bounds of the lists over all columns, a word per tile and column, have no room beside so many short rows."""
     # staged / lists over A's columns in us
