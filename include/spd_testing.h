@@ -51,6 +51,7 @@ typedef struct {
     int64_t block_columns;          /* of a block of the build */
     int32_t aligned, index_aligned; /* lists that begin at lines of memory: of the call's scratch, and of an index */
     int32_t staged_kind, staged_rows;   /* rows that the scan would stage together, and their kind of map */
+    int64_t shared_len;             /* rows of A of more entries are shared by the wavefronts of a workgroup */
 } spd_list_plan;
 spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int64_t b_nnz, int64_t n_cols,
                               spd_metric metric, float p, int k_neighbors, int with_index,

@@ -571,9 +571,17 @@ MatchGrid match_grid(const PlanOptions &opt, const MatchShape &s, int op, int64_
     g.share = nnz_a * tiles / ((int64_t)g.slices * s.waves);
     const bool one_strip = match_any_order(op);
     g.shared_len = std::max<int64_t>(one_strip && !knn ? 512 : 256, g.share / (one_strip ? 6 : 3));
-    // Where a workgroup has a (tile, row) for every wavefront, a strip for each of them is paid for by rows of twice the mean length at least.  (573 x 3,605 rows of 319, log-normal, us before and
-    // after: correlation 155 / 128, KL 137 / 116, Jensen-Shannon k-NN 226 / 197; 4,000 x 6,000 rows of 1,820, cosine, 4,621 / 4,047.)
-    if (!one_strip && (m / g.slices) * tiles >= s.waves) g.shared_len = std::max<int64_t>(g.shared_len, 2 * nnz_a / m);
+    // A strip for each wavefront, and the sum of the strips, is paid for where the (tile, row)s are too few for the wavefronts to end together, or by rows of twice the mean
+    // length at least.  Too few are less than one or one and a quarter to the wavefront where a row's walk takes less than its strips' sum, and
+    // more where it takes longer; with k-NN, whose selection is one wavefront's, fewer.  (All rows of 256 entries or a third of the share shared / where there is
+    // one for every wavefront not / so, the walk in us: cosine, 64 x 60,000 counts 898 / 920 / 835, k-NN 1,150 / 942 / 946, 1,500 x 6,000 words 208 / 173 / 173; KL, 32 x
+    // 60,000 counts 593 / 678 / 571, 130 x 60,000 1,519 / 1,603 / 1,442; Minkowski, 130 x 20,000 1,146 / 1,470 / 1,141.)
+    if (!one_strip) {
+        const double per_wave = (double)((m / g.slices) * tiles) / s.waves, list = (double)nnz_b / ((double)s.n_tiles * (double)s.ptr_stride);
+        const bool light = (double)nnz_a / (double)m * std::max(1.0, list / 16.0) / 2.0 < (double)s.tile_rows;
+        const double enough = light ? (knn ? 1.0 : 1.25) : (knn ? 1.5 : 2.75 * match_cell_bytes(op) / 8.0);
+        if (per_wave >= enough) g.shared_len = std::max<int64_t>(g.shared_len, 2 * nnz_a / m);
+    }
     // Chebyshev: a row of A that is like many of B's costs its wavefront two microseconds a pair (spd_match_impl.h).  Where a wavefront to the row
     // leaves half of the compute units idle, rows of some length are all shared: 500 x 500 rows of 50 ones over one support 880 -> 152 us
     // (staged scan 271), 1,000 x 1,000 of 100 1,258 -> 639 (1,314), of 100 normal values 205 -> 136; 237 x 5,101 rows of 223 194 -> 145.
@@ -2088,6 +2096,7 @@ spd_status spd_host_list_plan(int64_t a_rows, int64_t a_nnz, int64_t b_rows, int
     out->slices = w.g.slices;
     out->groups = w.g.groups;
     out->run = w.g.run;
+    out->shared_len = w.g.shared_len;
     out->consistent = match_check(h.opt, w.s, w.g, op, a_rows, b_rows, w.columns, b_nnz).empty();
     out->scratch_bytes = (int64_t)w.L.end;
     return SPD_OK;

@@ -42,7 +42,7 @@ class _ListPlan(ctypes.Structure):
     _fields_ = [(name, ctypes.c_int32) for name in ("wanted", "tiles", "tile_rows", "slices", "groups", "consistent")] + [
         (name, ctypes.c_int64) for name in ("scratch_bytes", "index_bytes")] + [
         ("run", ctypes.c_int32), ("way", ctypes.c_int32), ("columns", ctypes.c_int64), ("block_columns", ctypes.c_int64)] + [
-        (name, ctypes.c_int32) for name in ("aligned", "index_aligned", "staged_kind", "staged_rows")]
+        (name, ctypes.c_int32) for name in ("aligned", "index_aligned", "staged_kind", "staged_rows")] + [("shared_len", ctypes.c_int64)]
 
 
 def host_list_plan(a_rows, a_nnz, b_rows, b_nnz, n_cols, metric, p=2.0, k_neighbors=0, with_index=False, **options) -> dict:

@@ -423,6 +423,29 @@ def test_blocks_of_the_build_are_as_wide_as_their_entries_fit():
     assert columns(8_000, 228, 102_660, "kl_divergence") == 2_048
 
 
+def test_long_rows_are_shared_where_the_wavefronts_have_few_between_them():
+    def shared(m, mean_a, n, mean, cols, metric, k=0):
+        return spd.testing.host_list_plan(m, m * mean_a, n, n * mean, cols, metric, p=3.0, k_neighbors=k, match_lists=2)["shared_len"] < 2 * mean_a
+
+    counts, words = (1_824, 26_000), (256, 102_660)
+    # rows from 256 entries or a third of a share on in parts / from twice the mean length on, the walk in us
+    for m, n, (mean, cols), metric in ((32, 60_000, counts, "kl_divergence"),                            # 571 / 678
+                                       (64, 60_000, counts, "cosine"),                                   # 835 / 920
+                                       (130, 60_000, counts, "kl_divergence"),                           # 1,442 / 1,603
+                                       (32, 20_000, counts, "cosine"),                                   # 307 / 384
+                                       (130, 20_000, counts, "minkowski"),                               # 1,141 / 1,470
+                                       (300, 4_000, counts, "minkowski")):                               # 580 / 736
+        assert shared(m, mean, n, mean, cols, metric), (m, n, metric)
+    for m, n, (mean, cols), metric, k in ((1_500, 6_000, words, "cosine", 0),                            # 205 / 173
+                                          (1_500, 6_000, words, "cosine", 10),                           # 322 / 242
+                                          (700, 6_000, words, "kl_divergence", 0),                       # 232 / 210
+                                          (64, 60_000, counts, "cosine", 10),                            # 1,105 / 942
+                                          (3_000, 20_000, counts, "kl_divergence", 0)):
+        assert not shared(m, mean, n, mean, cols, metric, k), (m, n, metric, k)
+    # sums that need no order go to one strip
+    assert shared(32, 1_824, 60_000, 1_824, 26_000, "l1")
+
+
 def test_many_short_rows_over_few_columns_take_the_copy():
     """The bounds of the lists over all columns, a word per tile and column, have no room beside so many short rows."""
     # staged / lists over A's columns in us
