@@ -739,7 +739,7 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
 // 11,000 rows against 64 to 2,000,000, of equal, log-normal and power-law lengths of 1.5 to 3,000 entries, A's as long as B's and not, uniform and Zipf columns, 64 to
 // 2^22 of them; every product, k-NN with k = 1 to 64 and pairwise, with an index and without); nine of ten estimates are within 0.54 to 1.66 of the
 // times, because row pointers do not show how A's columns meet B's, nor the longest row.  What 2,232 further calls took beyond the best way, on the mean: of the working range
-// 2.3 %, of the others 4.7 %, correlation, pairwise, 9 %.  (The scan by steps of the column count and lists by a weight for each product, k-NN and way, in place of maps, rows' lengths
+// 2.3 %, of the others 4.5 %, correlation, pairwise, 9 %.  (The scan by steps of the column count and lists by a weight for each product, k-NN and way, in place of maps, rows' lengths
 // and launches: 4.6, 6.4 and, correlation weighed by 1.65, 16 %; constants from lists that took up to a third longer 12, 11 and 13 %.)
 struct OpCost { double entry, match, row, knn_row, visit, pair, knn_pair; };
 constexpr OpCost op_cost(int op) {
@@ -747,7 +747,7 @@ constexpr OpCost op_cost(int op) {
     case OP_DOT: return {9.23, 0.536, 0, 116, 0.0859, 2.23, 1.60};
     case OP_L1: return {8.61, 0.421, 0, 0, 0.109, 1.29, 1.81};
     case OP_HAMM: return {13.3, 0.451, 825, 1180, 0.157, 2.29, 2.23};
-    case OP_CNT: return {11.0, 0.505, 482, 691, 0.0710, 2.96, 1.67};
+    case OP_CNT: return {11.0, 0.450, 482, 691, 0.0710, 2.96, 1.67};
     case OP_CANB: return {7.84, 0.599, 137, 35, 0.298, 2.35, 2.13};
     case OP_KL: return {10.2, 0.894, 22, 580, 0.335, 2.24, 1.85};
     case OP_JS: return {4.88, 1.06, 174, 1070, 0.729, 4.35, 4.32};
@@ -766,14 +766,17 @@ double lists_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int o
     const double rows = std::ceil(m / g.slices), runs = std::ceil(tiles / g.groups);          // of a workgroup
     double idle = rows * runs * (double)h->opt.n_cus / (m * tiles);
     if (nnz_a <= (double)g.shared_len * m) idle *= std::ceil(rows * runs / s.waves) * s.waves / (rows * runs);
-    const double density = nnz_b / n / cols, met = density > 0.0 ? std::max(1.0, std::min(40.0, 0.0693 / density)) : 1.0;
+    const double density = nnz_b / n / cols, skew = density > 0.0 ? std::max(1.0, 0.0693 / density) : 1.0;
+    // (sets' tiles are twice as long, and more of what they are met by are dense columns, which cost every row of the tile: 184 x 9,756 words, Jaccard, k-NN, by the scan 184 us, by
+    // lists 313; 65 x 33,887 267 and 390)
+    const double met = op == OP_CNT ? std::min(80.0, std::pow(skew, 1.2)) : std::min(40.0, skew);
     const double kept = of_a ? std::sqrt(std::sqrt(1.0 - std::exp(-nnz_a / cols))) : 1.0;
     const double make = with_index && !of_a ? 0.0 : (knn ? 7.64e6 : 15e6) + 15.7 * kept * nnz_b + 6.81 * tiles * (of_a ? (double)columns_of(A) : cols) + 329.0 * n;
     // (two norms a pair: 573 x 3,605 rows of 319, all of a length / log-normal, correlation, by the scan 138 / 207 us, by lists 160 / 131)
     const bool two_norms = metric == MT_CORRELATION || op == OP_MINK || op == OP_MINK_ANY;
     // (counts without an index: where both estimates are alike the scan's times spread further, so that what lists gain is more than what they lose.  Hamming, 6,533 x
     // 70,554 rows of 240 and 36, k-NN, 3,581 us by the scan and 1,408 by lists, which are estimated the higher)
-    const double weight = (op == OP_HAMM || op == OP_CNT) && !with_index ? 0.88 : 1.0;
+    const double weight = with_index ? 1.0 : (op == OP_HAMM ? 0.88 : (op == OP_CNT ? 0.94 : 1.0));
     return weight * ((knn ? 52.4e6 : 13.5e6) + make + (of_a ? 39.1e6 + 7.21 * nnz_b : 0.0) + 5050.0 * m + (two_norms ? 1.65 : 0.985) * m * n +
                      2.18e6 * std::sqrt(nnz_a / m) + 0.802e6 * std::sqrt(nnz_b / n) +
                      idle * (nnz_a * tiles * c.entry + c.match * met * nnz_a * density * n + (c.row + (knn ? c.knn_row : 0.0)) * m * tiles));

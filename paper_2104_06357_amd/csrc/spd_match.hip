@@ -307,11 +307,12 @@ hipError_t launch_match_ranks(hipStream_t st, const RankedRows &first, const Ran
 // The order inside a list is whatever the wavefronts make it: no sum depends on it, because a row of B appears in a list at most once.
 // ------------------------------------------------------------------------------------
 // Two workgroups to a compute unit, as far as LDS and registers go: what a block takes is mostly waiting, for one load after the other and at barriers.  (With one
-// of 1,024 lanes / two of 512, us: 10,000 rows of 38 46 / 23, 7,777 of them 41 / 20, 28,301 ratings 95 / 72, 663,000 n-grams 96 / 44, 300,000
-// rows of 230 936 / 850, 65,536 of 1,820 917 / 805, 500,000 sets 895 / 860; as before, a few lanes to every row, 49, 36, 131, 81, 1,096, 972, 1,582.)
+// of 1,024 lanes / two of 512, when they were compared, us: 10,000 rows of 38 46 / 23, 7,777 of them 41 / 20, 28,301 ratings 95 / 72, 663,000 n-grams 96 / 44, 300,000
+// rows of 230 936 / 850, 65,536 of 1,820 917 / 805, 500,000 sets 895 / 860; a few lanes to every row 49, 36, 131, 81, 1,096, 972, 1,582.)
 constexpr int kBuildThreads = 512;
 constexpr int build_rows(int tile_rows) { return tile_rows <= kBuildThreads ? 1 : (tile_rows <= 3 * kBuildThreads ? 3 : 5); }          // of a lane
-// Entries that a lane holds: fewer of a lane with more rows, whose ends take registers too, but where the half as many again make blocks of twice the columns.
+// Entries that a lane holds: fewer of a lane with more rows, whose ends take registers too, but where half as many again make blocks of twice the columns.  (All instances
+// take the 128 registers that four wavefronts to a SIMD leave: with 16 entries and three rows 6 are spilled, with 24 52.)
 constexpr int kBuildHeld = 16, kBuildHeldMore = 24;
 constexpr int build_held(int rows) { return rows == 1 ? kBuildHeldMore : kBuildHeld; }
 constexpr int kBuildProbe = 8;                                              // entries that a lane looks at together

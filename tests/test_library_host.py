@@ -474,7 +474,12 @@ def test_calls_that_estimates_without_maps_and_launches_sent_the_slower_way():
                        (0, (3_035, 2_460_418, 251, 546, 1_558_033, "l1", 0, True)),                      # 63 / - / 247
                        (0, (245, 114_662, 2_392, 12_094, 17_153, "l2_unexpanded", 32, False)),           # 61 / 192 / 233
                        (0, (222, 95_908, 4_494, 1_493_679, 121_762, "hamming", 0, False)),               # 135 / 408 / 460
-                       (0, (148, 164_243, 11_371, 7_706_568, 10_950, "inner_product", 0, True))):        # 204 / 567 / 777
+                       (0, (148, 164_243, 11_371, 7_706_568, 10_950, "inner_product", 0, True)),         # 204 / 567 / 777
+                       # words, whose rows store many columns that most rows store
+                       (0, (184, 40_638, 9_756, 2_111_019, 102_602, "jaccard", 1, False)),               # 184 / 313 / -
+                       (0, (62, 14_856, 36_208, 7_871_693, 102_571, "jaccard", 10, False)),              # 270 / 446 / -
+                       (0, (1_073, 228_568, 22_501, 4_881_044, 102_482, "dice", 32, True)),              # 572 / 859 / -
+                       (1, (378, 86_000, 251_417, 54_600_000, 102_660, "dice", 10, False))):             # 3,790 / 2,752 / 3,101
         assert plan(*call)["way"] == want, call
     # the scan's maps: a strip of few columns, slots, a bitmap, a table, and fewer rows of them the longer they are
     kinds = [plan(1_000, 40_000, 20_000, 800_000, cols, "l1", 0, False)["staged_kind"] for cols in (2_000, 20_000, 100_000, 400_000)]
