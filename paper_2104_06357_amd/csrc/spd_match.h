@@ -31,11 +31,13 @@ constexpr int64_t kMatchSpare = 1280;
 // How B's rows are cut: into tiles of rows, and the columns of a tile into blocks (a power of two of them),
 // each with room for its entries; `dense_per` of 2^dense_shift columns may be kept as one value per row of the tile.
 struct MatchShape {
-    int32_t tile_rows, n_tiles, waves;      // n_tiles 0: the product or the sizes do not fit
+    int32_t tile_rows, n_tiles;             // n_tiles 0: the product or the sizes do not fit
+    int16_t waves, held;                    // of a workgroup of the walk; entries that a lane of the build holds
     int32_t block_shift, blocks, dense_shift, dense_per, dense_from;      // dense_from: entries that make a column dense
     uint32_t stage;                         // entries of a block that pass through LDS together
-    int16_t held;                           // entries that a lane of the build holds
-    int16_t aligned;                        // 1: lists of kMatchLine entries or more and dense columns begin at multiples of kMatchLine, see below
+    // 1: lists of kMatchLine entries or more and dense columns begin at multiples of kMatchLine, see below.  (The walk reads it where its registers are short: from 16 bits
+    // 663,000 n-grams, k-NN, take 1,828 us for 1,809.)
+    int32_t aligned;
     int64_t ptr_stride, tile_extra;         // words of a tile's list bounds; entries beyond the tile's own
     uint32_t lds_bytes, build_lds_bytes;
     SPD_HD int32_t dense_before(int32_t block) const { return (int32_t)(((int64_t)block * dense_per + (1 << (dense_shift - block_shift)) - 1) >> (dense_shift - block_shift)); }
@@ -51,7 +53,7 @@ struct MatchShape {
 // The L1 looks a load of 64 lanes up by 16 lanes and by lines of 64 bytes: a chunk of 16 entries costs two look-ups where it begins at such a
 // line (one for its values, one for its rows), and 3.4 anywhere; 64 rows of a dense column four, and eight.  (Anywhere / at lines: look-ups of 4,096 x
 // 65,536 rows of 1,820, L1, 9.4e9 / 7.4e9, lines fetched from L2 4.3e9 / 3.7e9, the walk 23.4 / 21.6 ms; 1,024 x 300,000 rows of 230, cosine,
-// 2.1e9 / 1.6e9 look-ups, 4.35 / 4.16 ms: its loads' addresses, four clocks for 64 lanes wherever they lie, take 88 % of the time.)
+// 2.1e9 / 1.6e9 look-ups, 4.35 / 4.16 ms: its loads' addresses, five clocks and a half a load wherever they lie, take 88 % of the time.)
 constexpr uint32_t kMatchLine = 16, kMatchGapShift = 27;
 MatchShape match_shape(int64_t lds_budget, int op, int64_t n, int64_t n_cols, int64_t nnz);
 
