@@ -739,7 +739,7 @@ bool index_keeps_lists(const spd_handle *h, const spd_csr *B, int op, MatchShape
 // 11,000 rows against 64 to 2,000,000, of equal, log-normal and power-law lengths of 1.5 to 3,000 entries, A's as long as B's and not, uniform and Zipf columns, 64 to
 // 2^22 of them; every product, k-NN with k = 1 to 64 and pairwise, with an index and without); nine of ten estimates are within 0.54 to 1.66 of the
 // times, because row pointers do not show how A's columns meet B's, nor the longest row.  What 2,232 further calls took beyond the best way, on the mean: of the working range
-// 2.3 %, of the others 4.5 %, correlation, pairwise, 9 %.  (The scan by steps of the column count and lists by a weight for each product, k-NN and way, in place of maps, rows' lengths
+// 1.8 %, of the others 4.5 %, correlation, pairwise, 8 %.  (The scan by steps of the column count and lists by a weight for each product, k-NN and way, in place of maps, rows' lengths
 // and launches: 4.6, 6.4 and, correlation weighed by 1.65, 16 %; constants from lists that took up to a third longer 12, 11 and 13 %.)
 struct OpCost { double entry, match, row, knn_row, visit, pair, knn_pair; };
 constexpr OpCost op_cost(int op) {
@@ -788,7 +788,9 @@ double staged_cost(const spd_handle *h, const spd_csr *A, const spd_csr *B, int 
     const Staging of = staging_of(A->n_cols, metric, op, knn, staged, h->opt);
     const double look_up = of.kind == KIND_STRIP ? 0.0 : (of.kind == KIND_SLOT ? 0.189 : (of.kind == KIND_BITMAP ? 0.385 : 0.859));
     const double launches = of.kind == KIND_STRIP ? 0.0 : (of.kind == KIND_SLOT ? 2.02e6 : (of.kind == KIND_BITMAP ? 2.62e6 : 3.31e6));
-    const double make = made ? 0.0 : (knn ? 0.0 : 7.96e6) + 7.87 * nnz_b + 2830.0 * n;
+    // (what making B ready takes grows with its rows' lengths, some 2.3 times an entry's at 1,820: without that 204 calls of up to 200 such rows against many took 10 % more than
+    // by the best way, with it 1.4 %; k-NN, Hellinger, 88 x 26,958 1,973 us, by lists 1,069, pairwise, Canberra, 31 x 19,632 1,086 / 762)
+    const double make = made ? 0.0 : (knn ? 0.0 : 7.96e6) + (7.87 + 0.0055 * std::min(2000.0, nnz_b / n)) * nnz_b + 2830.0 * n;
     // (Chebyshev ranks the entries of the rows that it stages: 34 x 969 rows of 1,550 2,777 us, by lists 554; 304 x 604 rows of 23 186 / 94;
     // 2,026 x 7,507 ratings 11,152 / 703; 3,148 x 4,764 rows of 1,790 25,963 / 3,002)
     return (knn ? 61.6e6 : 30.2e6) + make + 5900.0 * m + 5.97 * nnz_a + (op == OP_CHEB ? 865000.0 * staged : 0.0) + launches * std::sqrt(staged) + 2.01e6 * std::sqrt(streamed) +

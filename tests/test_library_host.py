@@ -479,7 +479,14 @@ def test_calls_that_estimates_without_maps_and_launches_sent_the_slower_way():
                        (0, (184, 40_638, 9_756, 2_111_019, 102_602, "jaccard", 1, False)),               # 184 / 313 / -
                        (0, (62, 14_856, 36_208, 7_871_693, 102_571, "jaccard", 10, False)),              # 270 / 446 / -
                        (0, (1_073, 228_568, 22_501, 4_881_044, 102_482, "dice", 32, True)),              # 572 / 859 / -
-                       (1, (378, 86_000, 251_417, 54_600_000, 102_660, "dice", 10, False))):             # 3,790 / 2,752 / 3,101
+                       (1, (378, 86_000, 251_417, 54_600_000, 102_660, "dice", 10, False)),              # 3,790 / 2,752 / 3,101
+                       # few long rows against many: most of the scan's time goes into making B ready, the more the longer B's rows are
+                       (1, (88, 138_589, 26_958, 49_192_777, 25_946, "hellinger", 10, False)),           # 1,973 / 1,069 / -
+                       (1, (31, 66_323, 19_632, 35_679_941, 26_000, "canberra", 0, False)),              # 1,086 / 762 / -
+                       (1, (36, 61_070, 33_011, 59_949_140, 25_987, "l1", 0, False)),                    # 1,694 / 942 / -
+                       (1, (23, 37_526, 9_196, 16_915_257, 26_000, "hamming", 0, False)),                # 458 / 311 / -
+                       (1, (19, 31_920, 25_736, 46_613_550, 26_000, "dice", 5, False)),                  # 1,031 / 705 / -
+                       (1, (54, 95_458, 7_022, 12_689_675, 25_848, "minkowski", 1, False))):             # 1,005 / 651 / -
         assert plan(*call)["way"] == want, call
     # the scan's maps: a strip of few columns, slots, a bitmap, a table, and fewer rows of them the longer they are
     kinds = [plan(1_000, 40_000, 20_000, 800_000, cols, "l1", 0, False)["staged_kind"] for cols in (2_000, 20_000, 100_000, 400_000)]
